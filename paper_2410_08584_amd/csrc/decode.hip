@@ -1,16 +1,14 @@
 // Decode-phase attention against the (evicted) KV cache (Eq. (5); Algorithm 2).
-// Memory-bound: one query per head, every cached row read exactly once.
-// Split-KV: grid = (splits, units).  A split is a fixed number of cached rows
-// (chosen on the host from the capacity), and how many splits of a unit have
-// work follows from the length that lives on the device: a short (evicted)
-// cache occupies few workgroups, all of the same size, and the dispatcher
-// balances them.  Inside a workgroup 16 lanes cover one cached row (16 bytes
-// each at d = 128 bf16), so a wave reads 4 rows per step as full 256-byte
-// lines (the rows of the next step are requested before the current ones are
-// consumed), reduces the dot product over the 16 lanes with shuffles and keeps
-// an online-softmax state per row group; row groups, waves and finally splits
-// are merged with the usual (max, sum, weighted output) rule.  All query
-// heads of a KV group are served from the same read.
+// Memory-bound: one query per head, every cached row read exactly once, all
+// query heads of a KV group served from the same read.
+// Split-KV: grid = (splits, units).  The number of splits is chosen on the host
+// (from the units and the capacity); a split's rows are the unit's device-resident
+// length over that number, so every workgroup has work on short and full caches.
+// Groups of two and more heads run on the matrix cores, 16 cached rows per wave
+// step (attend_split); a single head runs on the vector units, where 16 lanes
+// cover one cached row (16 bytes each at d = 128 bf16), reduce the dot product with
+// shuffles and keep an online-softmax state per row group (attend_rows).  Waves and
+// finally splits are merged with the usual (max, sum, weighted output) rule.
 #include <algorithm>
 #include <mutex>
 
@@ -65,41 +63,126 @@ __device__ __forceinline__ void load_queries(const T* q, int b, int g, int G, in
     }
 }
 
-// The 4 waves' states in red[wave][head][o[D], m, l] -> the workgroup's partial state.
-// partial layout: [(unit*G + head_in_group) * nsplit + split][D + 2]  (o[D], m, l), log2 domain
+// The partial states (o[D], m, l; log2 domain) of a launch: the outputs of all (unit, head, split) first, each D floats
+// on a 16-byte boundary, then their (m, l) pairs.
+struct PartialOut {
+    float* o; float* ml; int nsplit;                         // rows of one unit: head * nsplit + split
+    __device__ __forceinline__ PartialOut(float* part, int D, int u, int G, int nsplit_, int units) : nsplit(nsplit_) {
+        o = part + (int64_t)u * G * nsplit * D;
+        ml = part + (int64_t)units * G * nsplit * D + (int64_t)u * G * nsplit * 2;
+    }
+};
+
+// A 16-byte load past the caches that are not coherent between XCDs (the states were written through by other
+// workgroups of the same launch).
+__device__ __forceinline__ floatx4 load16_coherent(const float* base, int byte_offset) {
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, 0x7FFFFFFF, 0x00020000);
+    return __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, byte_offset, 0, 16));   // sc1: device scope
+}
+
+// The waves' states in red[wave][head][o[D], m, l] -> the workgroup's partial state.
 // COHERENT: the partial state is read by another workgroup of the same launch (possibly on another XCD,
 // whose L2 is not coherent with this one's): written through with device-scope stores.
-template <int D, int GT, bool COHERENT = false>
-__device__ __forceinline__ void combine_waves(float (&red)[4][GT][D + 2], int u, int G, int gbase, int split, int nsplit, float* part) {
+template <int D, int GT, int WAVES, bool COHERENT = false>
+__device__ __forceinline__ void combine_waves(float (&red)[WAVES][GT][D + 2], int heads, const PartialOut& po, int gbase, int split) {
     auto put = [](float* p, float v) {
         if constexpr (COHERENT) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else *p = v;
     };
-    for (int wi = threadIdx.x; wi < GT * D; wi += 256) {
+    for (int wi = threadIdx.x; wi < heads * D; wi += 64 * WAVES) {
         const int t = wi / D, dd = wi - t * D;
-        if (gbase + t >= G) continue;
         float M = -INFINITY;
 #pragma unroll
-        for (int ww = 0; ww < 4; ++ww) M = fmaxf(M, red[ww][t][D]);
+        for (int ww = 0; ww < WAVES; ++ww) M = fmaxf(M, red[ww][t][D]);
         float acc = 0.f, lsum = 0.f;
         if (M > -INFINITY) {
 #pragma unroll
-            for (int ww = 0; ww < 4; ++ww) {
+            for (int ww = 0; ww < WAVES; ++ww) {
                 const float a = fast_exp2(red[ww][t][D] - M);
                 acc += red[ww][t][dd] * a;
                 lsum += red[ww][t][D + 1] * a;
             }
         }
-        float* dst = part + (((int64_t)u * G + gbase + t) * nsplit + split) * (D + 2);
-        put(dst + dd, acc);
-        if (dd == 0) { put(dst + D, M); put(dst + D + 1, lsum); }
+        const int64_t row = (int64_t)(gbase + t) * po.nsplit + split;
+        put(po.o + row * D + dd, acc);
+        if (dd == 0) { put(po.ml + 2 * row, M); put(po.ml + 2 * row + 1, lsum); }
+    }
+}
+
+// The partial states of one unit's splits -> its output rows, by a workgroup of THREADS threads.  One wave per head
+// first turns the splits' (max, sum) pairs into weights a_s / sum_s(a_s l_s), a_s = exp2(m_s - max), one split per
+// lane; then every thread accumulates four output elements over every SG-th split, eight independent 16-byte loads at a
+// time, and the SG partial sums of an element meet in LDS (added in a fixed order).
+// nsplit <= 64.  COHERENT: the states were written by other workgroups of the same launch.
+struct MergeLds { float wgt[8][64]; floatx4 sum[1024]; };
+
+template <typename T, int D, int THREADS, bool COHERENT>
+__device__ __forceinline__ void merge_splits(const PartialOut& po, int G, int nsplit, MergeLds& lds, T* __restrict__ out) {
+    static_assert(THREADS <= 1024 && 8 * (D / 4) <= 256 && THREADS >= 256, "eight heads fit one pass");
+    auto get = [](const float* p) {
+        if constexpr (COHERENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else return *p;
+    };
+    auto get4 = [](const float* p, int off) {
+        if constexpr (COHERENT) return load16_coherent(p, off);
+        else return *reinterpret_cast<const floatx4*>(reinterpret_cast<const char*>(p) + off);
+    };
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+    for (int t0 = 0; t0 < G; t0 += 8) {                      // groups larger than 8 heads: 8 at a time
+        const int gt = min(8, G - t0), cols = gt * (D / 4);  // four output elements each
+        const int SG = min(THREADS / cols, nsplit);          // >= 1; fewer, longer chains were 1-3 us a launch slower at 8 splits
+        const int sg = tid / cols, col = tid - sg * cols, t = col / (D / 4);
+        const int off = (t0 + t) * po.nsplit * (D * 4) + (col - t * (D / 4)) * 16;   // the unit's base is wave-uniform
+        constexpr int kBatch = 8;                            // 16: 140 VGPRs, and 168 us instead of 139 for four one-head layers
+        floatx4 v[kBatch];
+        auto fetch = [&](int s0) {
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q)
+                if (q * SG < nsplit) v[q] = get4(po.o, off + min(s0 + q * SG, nsplit - 1) * (D * 4));   // uniform over the workgroup
+        };
+        if (sg < SG) fetch(sg);                              // on their way while the weights are formed
+        __syncthreads();
+        for (int h = w; h < gt; h += THREADS / 64) {
+            const float* p = po.ml + (int64_t)(t0 + h) * po.nsplit * 2;
+            const float ms = lane < nsplit ? get(p + 2 * lane) : -INFINITY;
+            const float ls = lane < nsplit ? get(p + 2 * lane + 1) : 0.f;
+            float M = ms;
+#pragma unroll
+            for (int x = 32; x; x >>= 1) M = fmaxf(M, __shfl_xor(M, x));
+            const float a = M > -INFINITY ? fast_exp2(ms - M) : 0.f;
+            float tot = a * ls;
+#pragma unroll
+            for (int x = 32; x; x >>= 1) tot += __shfl_xor(tot, x);
+            lds.wgt[h][lane] = tot > 0.f ? a / tot : 0.f;
+        }
+        __syncthreads();
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+        if (sg < SG) {
+            for (int s0 = sg; s0 < nsplit; s0 += kBatch * SG) {
+                if (s0 != sg) fetch(s0);
+#pragma unroll
+                for (int q = 0; q < kBatch; ++q)
+                    if (s0 + q * SG < nsplit) acc += lds.wgt[t][s0 + q * SG] * v[q];
+            }
+        }
+        if (SG > 1) {
+            if (sg < SG) lds.sum[tid] = acc;
+            __syncthreads();
+            if (sg == 0)
+                for (int x = 1; x < SG; ++x) acc += lds.sum[x * cols + col];
+        }
+        if (sg == 0) {
+            T* dst = out + (int64_t)t0 * D + col * 4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dst[e] = to_out<T>(acc[e]);
+        }
     }
 }
 
 // Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state.
 template <int D, int GT, bool COHERENT = false>
 __device__ __forceinline__ void write_partial(float (&m)[GT], float (&l)[GT], float (&o)[GT][D / 16], float (&red)[4][GT][D + 2],
-                                              int u, int G, int gbase, int split, int nsplit, float* part) {
+                                              int heads, const PartialOut& po, int gbase, int split) {
     constexpr int EPL = D / 16;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
 #pragma unroll
@@ -119,7 +202,7 @@ __device__ __forceinline__ void write_partial(float (&m)[GT], float (&l)[GT], fl
         }
     }
     __syncthreads();
-    combine_waves<D, GT, COHERENT>(red, u, G, gbase, split, nsplit, part);
+    combine_waves<D, GT, 4, COHERENT>(red, heads, po, gbase, split);
 }
 
 // rows [r_begin, r_end) of a segment of L rows that split `split` of nsplit handles (multiples of 16 rows)
@@ -138,15 +221,49 @@ __device__ __forceinline__ void split_range64(int L, int split, int nsplit, int&
     r_end = min(L, r_begin + per);
 }
 
-// Rows per split for a cache of `cap` rows: 256 for short caches, more for long ones so that a unit never
-// has more than kDecRowSplits splits (the merge reads one partial state per split).  A multiple of 16.
-constexpr int kDecRowSplits = 16;
-static inline int rows_per_split(int cap) {
-    const int per = ((cap + kDecRowSplits - 1) / kDecRowSplits + 15) & ~15;
-    return per < 256 ? 256 : per;        // 128 ... 512 rows measured within 5 % of each other on 2000-row caches
-}
+// ---------------------------------------------------------------- attention over a cache as stored
+// One wave works on tiles of 16 cached rows with the matrix cores, all query heads of the group in the 16 columns:
+//   S = K q^T     A = 16 cached rows, B = the queries: a bf16 row feeds v_mfma_f32_16x16x32_bf16, an fp32 row
+//                 v_mfma_f32_16x16x4_f32 (products exact or fp32, sums fp32); lane (j, kk) receives the scores of
+//                 head j for rows 4 kk .. 4 kk + 3.
+//   O^T += V^T P  with v_mfma_f32_16x16x4_f32: step r contracts rows {4 kk + r}, so the score registers are the B
+//                 operand as they are, and the A operand of output block e is element e of the lane's piece of row
+//                 4 kk + r - a 16-byte load of the row, widened to fp32.  No value crosses lanes, P stays fp32.
+// The offset of the exponentials follows the running maximum of a head lazily (moves when it is exceeded by
+// 2^kDecLazyLog2), so the accumulators are rescaled on few tiles.
+constexpr float kDecLazyLog2 = 8.f;
+// A group of one head keeps the vector units (attend_rows, 16 lanes per row): 15 of the 16 columns would be empty and
+// the fp32 products of 16 rows cost 1024 matrix cycles whatever the columns hold.  One step at B = 4, 32 heads, 2050 rows:
+// 33 us against 36 us on the matrix cores; B = 1, 28 heads on 4, 7200 rows: 86 us (16 lanes per row, seven heads in
+// turn, 64 workgroups) against 14 us.
+template <int GT> constexpr bool kDecMfma = GT > 1;
+template <int GT> constexpr int kDecWaves = kDecMfma<GT> ? 8 : 4;        // waves per workgroup (8: 14.0 us, 4: 18.5 us at the shape above)
+constexpr int kDecTile = 16;          // cached rows per wave step
 
 template <typename T, int EPL> struct alignas(sizeof(T) * EPL > 16 ? 16 : sizeof(T) * EPL) RawChunk { T v[EPL]; };
+
+template <typename T, int D>
+struct DecTile {
+    static constexpr int NK = D * (int)sizeof(T) / 64;       // 16-byte pieces of a K row per lane (4 lanes cover 64 bytes)
+    uintx4 k[NK];
+    RawChunk<T, D / 16> v[4];
+};
+
+// a b^T of one 16-byte piece per lane: short chains, which the caller adds up pairwise.  One the rounding error into a score (1.3e-6 of the output against 0.4e-6).
+__device__ __forceinline__ floatx4 mma16(const uintx4& a, const uintx4& b, __bf16) {
+    const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), zero, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mma16(const uintx4& a, const uintx4& b, float) {
+    const floatx4 fa = __builtin_bit_cast(floatx4, a), fb = __builtin_bit_cast(floatx4, b);
+    floatx4 x = {0.f, 0.f, 0.f, 0.f}, y = x;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        x = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[e], fb[e], x, 0, 0, 0);
+        y = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[e + 2], fb[e + 2], y, 0, 0, 0);
+    }
+    return x + y;
+}
 
 template <typename T, int EPL>
 __device__ __forceinline__ void raw_to_floats(const RawChunk<T, EPL>& r, float (&f)[EPL]) {
@@ -189,96 +306,172 @@ __device__ __forceinline__ void attend_rows(const T* Kb, const T* Vb, T* Kw, T* 
     }
 }
 
-template <typename T, int D, int GT>
-__global__ __launch_bounds__(256) void decode_partial_kernel(
-    const T* __restrict__ q, const T* __restrict__ Kc, const T* __restrict__ Vc,
-    const int32_t* __restrict__ len, int cap, int Hq, int Hkv, int gbase, float c,
-    float* __restrict__ part, int rows, int max_splits)
+// rows of the cache that split `split` of nsplit takes (multiples of a tile)
+__device__ __forceinline__ int rows_per_split(int L, int nsplit) {
+    return max(kDecTile, ((L + nsplit - 1) / nsplit + kDecTile - 1) / kDecTile * kDecTile);
+}
+
+// Rows [r_begin, r_end) of one unit against heads gbase .. gbase + GT - 1 of its group; the workgroup's state goes to
+// `part`.  Kb / Vb: the unit's cache.  Row `new_row` (>= 0 only in the fused step) comes from kn / vn and is written
+// to the cache.
+template <typename T, int D, int GT, bool COHERENT>
+__device__ __forceinline__ void attend_split(const T* q0, int heads, float c, T* Kb, T* Vb, const T* kn, const T* vn, int new_row,
+                                             int r_begin, int r_end, float (&red)[kDecWaves<GT>][GT][D + 2],
+                                             const PartialOut& po, int gbase, int split)
+{
+    constexpr int EPL = D / 16, NK = DecTile<T, D>::NK, E16 = 16 / (int)sizeof(T);
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 15, kk = lane >> 4;
+    using Tile = DecTile<T, D>;
+    using Raw = RawChunk<T, EPL>;
+    auto fetch = [&](int t0, Tile& x) {
+        const int rk = min(t0 + j, r_end - 1);               // rows past the end re-read the last one and weigh nothing
+        const T* kp = (rk == new_row ? kn : Kb + (int64_t)rk * D) + kk * E16;
+#pragma unroll
+        for (int cc = 0; cc < NK; ++cc) x.k[cc] = load16(kp + cc * 4 * E16);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int rv = min(t0 + 4 * kk + r, r_end - 1);
+            x.v[r] = *reinterpret_cast<const Raw*>((rv == new_row ? vn : Vb + (int64_t)rv * D) + j * EPL);
+        }
+    };
+    const int step = kDecWaves<GT> * kDecTile;
+    int t0 = r_begin + w * kDecTile;
+    Tile cur;
+    if (t0 < r_end) fetch(t0, cur);
+    uintx4 qf[NK];
+#pragma unroll
+    for (int cc = 0; cc < NK; ++cc) {
+        qf[cc] = uintx4{0, 0, 0, 0};
+        if (j < heads) qf[cc] = load16(q0 + (int64_t)j * D + kk * E16 + cc * 4 * E16);
+    }
+    float m = -INFINITY, l = 0.f;                            // head j
+    floatx4 o[EPL];                                          // o[e][r]: element EPL (4 kk + r) + e of head j
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) o[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (; t0 < r_end; t0 += step) {
+        Tile nxt;
+        if (t0 + step < r_end) fetch(t0 + step, nxt);        // in flight while this tile is multiplied
+        if (new_row >= t0 && new_row < t0 + kDecTile) {
+            if (t0 + j == new_row) {
+#pragma unroll
+                for (int cc = 0; cc < NK; ++cc) store16(Kb + (int64_t)new_row * D + kk * E16 + cc * 4 * E16, cur.k[cc]);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (t0 + 4 * kk + r == new_row) *reinterpret_cast<Raw*>(Vb + (int64_t)new_row * D + j * EPL) = cur.v[r];
+        }
+        floatx4 sp[NK];
+#pragma unroll
+        for (int cc = 0; cc < NK; ++cc) sp[cc] = mma16(cur.k[cc], qf[cc], T());
+#pragma unroll
+        for (int half = NK / 2; half; half >>= 1)
+#pragma unroll
+            for (int cc = 0; cc < half; ++cc) sp[cc] += sp[cc + half];
+        floatx4 s = sp[0];
+        float vf[4][EPL];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) RowChunk<T, EPL>::load(cur.v[r].v, vf[r]);
+        if (t0 + kDecTile > r_end) {                         // the last tile of the split: wave-uniform
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (t0 + 4 * kk + r >= r_end) {
+                    s[r] = -INFINITY;
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) vf[r][e] = 0.f;    // zero weight times an infinite element would be NaN
+                }
+        }
+        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c;
+        if (__any(mx > m + kDecLazyLog2)) {
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx), a = m_new > -INFINITY ? fast_exp2(m - m_new) : 1.f;
+            l *= a;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) o[e] *= a;
+            m = m_new;
+        }
+        const float ms = m > -INFINITY ? m : 0.f;
+        float p[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { p[r] = fast_exp2(fmaf(s[r], c, -ms)); l += p[r]; }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][e], p[r], o[e], 0, 0, 0);
+        cur = nxt;
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (j < heads) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) red[w][j][EPL * (4 * kk + r) + e] = o[e][r];
+        if (kk == 0) { red[w][j][D] = m; red[w][j][D + 1] = l; }
+    }
+    __syncthreads();
+    combine_waves<D, GT, kDecWaves<GT>, COHERENT>(red, heads, po, gbase, split);
+}
+
+template <typename T, int D, int GT, bool COHERENT>
+__device__ __forceinline__ void attend_split_valu(const T* q0, int heads, float c, T* Kb, T* Vb, const T* kn, const T* vn, int new_row,
+                                                  int r_begin, int r_end, float (&red)[4][GT][D + 2],
+                                                  const PartialOut& po, int gbase, int split)
 {
     constexpr int EPL = D / 16;
-    __shared__ float red[4][GT][D + 2];
-    const int G = Hq / Hkv;
-    const int split = blockIdx.x, u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
-    const int L = max(0, min(len[u], cap));
-    const int r_begin = split * rows, r_end = min(L, r_begin + rows);
-    if (split > 0 && r_begin >= L) return;                  // split 0 always reports (an empty state when L = 0)
-
-    float qv[GT][EPL];
-    load_queries<T, D, GT>(q, b, g, G, Hq, gbase, sub, c, qv);
-    float m[GT], l[GT], o[GT][EPL];
+    const int tid = threadIdx.x, sub = tid & 15;
+    float qv[GT][EPL], m[GT], l[GT], o[GT][EPL];
 #pragma unroll
     for (int t = 0; t < GT; ++t) {
         m[t] = -INFINITY; l[t] = 0.f;
+        if (t < heads) RowChunk<T, EPL>::load(q0 + (int64_t)t * D + sub * EPL, qv[t]);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) o[t][e] = 0.f;
+        for (int e = 0; e < EPL; ++e) { qv[t][e] = t < heads ? qv[t][e] * c : 0.f; o[t][e] = 0.f; }
     }
-    const T* Kb = Kc + (int64_t)u * cap * D + sub * EPL;
-    const T* Vb = Vc + (int64_t)u * cap * D + sub * EPL;
-    attend_rows<T, D, GT>(Kb, Vb, nullptr, nullptr, nullptr, nullptr, -1, r_begin, r_end, w * 4 + rg, qv, m, l, o);
-    write_partial<D, GT>(m, l, o, red, u, G, gbase, split, max_splits, part);
+    Kb += sub * EPL; Vb += sub * EPL;
+    if constexpr (COHERENT) { kn += sub * EPL; vn += sub * EPL; }         // the fused step: the only caller with a new row
+    attend_rows<T, D, GT>(Kb, Vb, Kb, Vb, kn, vn, new_row, r_begin, r_end, tid >> 4, qv, m, l, o);
+    write_partial<D, GT, COHERENT>(m, l, o, red, heads, po, gbase, split);
 }
 
-// The partial states of one unit's splits -> its output rows.  One wave per head first turns the splits'
-// (max, sum) pairs into weights a_s / sum_s(a_s l_s), a_s = exp2(m_s - max), one split per lane; then every
-// thread accumulates one output element over the splits, eight independent loads at a time.
-// nsplit <= 64.  COHERENT: the states were written by other workgroups of the same launch.
-template <typename T, int D, bool COHERENT>
-__device__ __forceinline__ void merge_splits(const float* __restrict__ part, int u, int G, int nsplit, int max_splits,
-                                             float (&wgt)[8][64], T* __restrict__ out) {
-    auto get = [](const float* p) {
-        if constexpr (COHERENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else return *p;
-    };
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    for (int t0 = 0; t0 < G; t0 += 8) {                      // groups larger than 8 heads: 8 at a time
-        const int gt = min(8, G - t0);
-        __syncthreads();
-        for (int t = w; t < gt; t += 4) {
-            const float* p = part + ((int64_t)u * G + t0 + t) * max_splits * (D + 2);
-            const float ms = lane < nsplit ? get(p + lane * (D + 2) + D) : -INFINITY;
-            const float ls = lane < nsplit ? get(p + lane * (D + 2) + D + 1) : 0.f;
-            float M = ms;
-#pragma unroll
-            for (int off = 32; off; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-            const float a = M > -INFINITY ? fast_exp2(ms - M) : 0.f;
-            float tot = a * ls;
-#pragma unroll
-            for (int off = 32; off; off >>= 1) tot += __shfl_xor(tot, off);
-            wgt[t][lane] = tot > 0.f ? a / tot : 0.f;
-        }
-        __syncthreads();
-        for (int wi = tid; wi < gt * D; wi += 256) {
-            const int t = wi / D, dd = wi - t * D;
-            const float* p = part + ((int64_t)u * G + t0 + t) * max_splits * (D + 2) + dd;
-            float acc = 0.f;
-            for (int s0 = 0; s0 < nsplit; s0 += 8) {
-                float v[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = get(p + (int64_t)min(s0 + j, nsplit - 1) * (D + 2));
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc = fmaf(s0 + j < nsplit ? wgt[t][s0 + j] : 0.f, v[j], acc);
-            }
-            out[((int64_t)u * G + t0 + t) * D + dd] = to_out<T>(acc);
-        }
-    }
+template <typename T, int D, int GT, bool COHERENT, typename... A>
+__device__ __forceinline__ void attend_one(A&&... a) {
+    if constexpr (kDecMfma<GT>) attend_split<T, D, GT, COHERENT>(a...);
+    else attend_split_valu<T, D, GT, COHERENT>(a...);
 }
 
-// Splits of unit u that hold rows: from the device-resident length when `len` is given, else `fixed`.
-__device__ __forceinline__ int unit_splits(const int32_t* len, int u, int cap, int rows, int fixed) {
-    if (!len) return fixed;
+template <typename T, int D, int GT>
+__global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_partial_kernel(
+    const T* __restrict__ q, const T* __restrict__ Kc, const T* __restrict__ Vc,
+    const int32_t* __restrict__ len, int cap, int Hq, int Hkv, int gbase, float c, float* __restrict__ part)
+{
+    __shared__ float red[kDecWaves<GT>][GT][D + 2];
+    const int G = Hq / Hkv;
+    const int split = blockIdx.x, u = blockIdx.y;
     const int L = max(0, min(len[u], cap));
+    const int rows = rows_per_split(L, gridDim.x);
+    const int r_begin = split * rows, r_end = min(L, r_begin + rows);
+    if (split > 0 && r_begin >= L) return;                  // split 0 always reports (an empty state when L = 0)
+    const PartialOut po(part, D, u, G, gridDim.x, gridDim.y);
+    attend_one<T, D, GT, false>(q + ((int64_t)u * G + gbase) * D, min(GT, G - gbase), c, const_cast<T*>(Kc) + (int64_t)u * cap * D,
+                                  const_cast<T*>(Vc) + (int64_t)u * cap * D, nullptr, nullptr, -1, r_begin, r_end, red, po, gbase, split);
+}
+
+// Splits of unit u that hold rows: from the device-resident length when `len` is given, else all of them.
+__device__ __forceinline__ int unit_splits(const int32_t* len, int u, int cap, int nsplit) {
+    if (!len) return nsplit;
+    const int L = max(0, min(len[u], cap)), rows = rows_per_split(L, nsplit);
     return max(1, (L + rows - 1) / rows);
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_combine_kernel(const float* __restrict__ part, const int32_t* __restrict__ len,
-                                                             int cap, int rows, int nsplit_fixed, int max_splits, int G,
-                                                             T* __restrict__ o)
+template <typename T, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void decode_combine_kernel(const float* __restrict__ part, const int32_t* __restrict__ len,
+                                                             int cap, int nsplit, int G, T* __restrict__ o)
 {
-    __shared__ float wgt[8][64];
+    __shared__ MergeLds lds;
     const int u = blockIdx.x;
-    merge_splits<T, D, false>(part, u, G, unit_splits(len, u, cap, rows, nsplit_fixed), max_splits, wgt, o);
+    merge_splits<T, D, THREADS, false>(PartialOut(const_cast<float*>(part), D, u, G, nsplit, gridDim.x), G, unit_splits(len, u, cap, nsplit), lds,
+                                   o + (int64_t)u * G * D);
 }
 
 // ---------------------------------------------------------------- one launch per decode step
@@ -290,41 +483,27 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __rest
 // Since all workgroups have read len before the last one arrives, the update cannot be seen by a reader of
 // the old value.
 template <typename T, int D, int GT>
-__global__ __launch_bounds__(256) void decode_step_kernel(
+__global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_step_kernel(
     const T* __restrict__ q, T* __restrict__ Kc, T* __restrict__ Vc, int32_t* __restrict__ len, int cap,
     const T* __restrict__ k_new, const T* __restrict__ v_new, int Hq, int Hkv, float c,
-    float* __restrict__ part, int rows, int max_splits, unsigned* __restrict__ arrived, T* __restrict__ out)
+    float* __restrict__ part, unsigned* __restrict__ arrived, T* __restrict__ out)
 {
-    constexpr int EPL = D / 16;
-    __shared__ float red[4][GT][D + 2];
-    __shared__ float wgt[8][64];
+    __shared__ union { float red[kDecWaves<GT>][GT][D + 2]; MergeLds merge; } lds;
     __shared__ int is_last;
     const int G = Hq / Hkv;
-    const int split = blockIdx.x, u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
+    const int split = blockIdx.x, u = blockIdx.y, tid = threadIdx.x;
     const int Lraw = len[u];
     const bool room = Lraw >= 0 && Lraw < cap;               // a full cache is left unchanged, as by the append call
     const int L0 = max(0, min(Lraw, cap));
     const int L = L0 + (room ? 1 : 0);                       // rows attended: the new one included
+    const int rows = rows_per_split(L, gridDim.x);
     const int r_begin = split * rows, r_end = min(L, r_begin + rows);
     const int nsplit = max(1, (L + rows - 1) / rows);
+    const PartialOut po(part, D, u, G, gridDim.x, gridDim.y);
 
-    if (split < nsplit) {
-        float qv[GT][EPL];
-        load_queries<T, D, GT>(q, b, g, G, Hq, 0, sub, c, qv);
-        float m[GT], l[GT], o[GT][EPL];
-#pragma unroll
-        for (int t = 0; t < GT; ++t) {
-            m[t] = -INFINITY; l[t] = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) o[t][e] = 0.f;
-        }
-        T* Kb = Kc + (int64_t)u * cap * D + sub * EPL;
-        T* Vb = Vc + (int64_t)u * cap * D + sub * EPL;
-        attend_rows<T, D, GT>(Kb, Vb, Kb, Vb, k_new + (int64_t)u * D + sub * EPL, v_new + (int64_t)u * D + sub * EPL,
-                              room ? L0 : -1, r_begin, r_end, w * 4 + rg, qv, m, l, o);
-        write_partial<D, GT, true>(m, l, o, red, u, G, 0, split, max_splits, part);
-    }
+    if (split < nsplit)
+        attend_one<T, D, GT, true>(q + (int64_t)u * G * D, G, c, Kc + (int64_t)u * cap * D, Vc + (int64_t)u * cap * D,
+                                     k_new + (int64_t)u * D, v_new + (int64_t)u * D, room ? L0 : -1, r_begin, r_end, lds.red, po, 0, split);
 
     // The partial state went out with device-scope (write-through) stores: once they have completed
     // (vmcnt 0) it is visible to every XCD, and only then is this workgroup counted.  A release fence
@@ -334,7 +513,7 @@ __global__ __launch_bounds__(256) void decode_step_kernel(
     if (tid == 0) is_last = atomicAdd(&arrived[u], 1u) == gridDim.x - 1u;
     __syncthreads();
     if (!is_last) return;
-    merge_splits<T, D, true>(part, u, G, nsplit, max_splits, wgt, out);
+    merge_splits<T, D, 64 * kDecWaves<GT>, true>(po, G, nsplit, lds.merge, out + (int64_t)u * G * D);
     if (tid == 0) {
         if (room) len[u] = Lraw + 1;
         arrived[u] = 0u;                                     // ready for the next step
@@ -424,7 +603,7 @@ __global__ __launch_bounds__(256) void decode_q_partial_kernel(
             attend_row<EPL, GT>(valid, kf, vf, qv, m, l, o);
         }
     }
-    write_partial<D, GT>(m, l, o, red, u, G, gbase, split, nsplit, part);
+    write_partial<D, GT>(m, l, o, red, min(GT, G - gbase), PartialOut(part, D, u, G, nsplit, gridDim.y), gbase, split);
 }
 
 // ---- the same, for small query groups (GT <= 2): 4 lanes per row.
@@ -435,7 +614,6 @@ __global__ __launch_bounds__(256) void decode_q_partial_kernel(
 //   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j zero_j + sum_j (p_j scale_j) code_j,
 // i.e. one conversion and one FMA per element and side.  The softmax offset follows the running maximum lazily
 // (moves only when exceeded by 2^kDecLazyLog2), so the accumulators are rescaled on few rows.
-constexpr float kDecLazyLog2 = 8.f;
 
 // sum over the 4 lanes of a quad (lanes 4i .. 4i+3), result in all four, by two in-register lane permutes
 __device__ __forceinline__ float quad_sum(float v) {
@@ -654,7 +832,7 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
         }
     }
     __syncthreads();
-    combine_waves<D, GT>(red, u, G, gbase, split, nsplit, part);
+    combine_waves<D, GT, 4>(red, min(GT, G - gbase), PartialOut(part, D, u, G, nsplit, gridDim.y), gbase, split);
 }
 
 static int decode_splits(const zipvl_dims& d, int cap) {
@@ -665,37 +843,49 @@ static int decode_splits(const zipvl_dims& d, int cap) {
     return s < 1 ? 1 : (s > kDecMaxSplit ? kDecMaxSplit : s);
 }
 
-static int row_splits(int cap) { const int r = rows_per_split(cap); return (cap + r - 1) / r; }
+// Partial states that the workspace of a cache of `cap` rows holds per head.
+static int workspace_splits(const zipvl_dims& d, int cap) {
+    const int per = std::max(256, ((cap + 15) / 16 + 15) / 16 * 16);
+    return std::max(decode_splits(d, cap), (cap + per - 1) / per);
+}
+
+// Workgroups per unit of the kernels over a cache as stored: all of them have work whatever the lengths are (a split is
+// the unit's rows over this number).  256 of 8 waves (one per CU: 512 is 3-10 % slower from 32 units on, and as fast below)
+// or 1024 of 4 waves (512: 151 us for four layers of 128 units, 1024: 131, 2048: 142), never more than the workspace has room for.
+static int attend_splits(const zipvl_dims& d, int cap) {
+    const int units = d.B * d.Hkv;
+    return std::max(1, std::min(workspace_splits(d, cap), ((d.Hq / d.Hkv > 1 ? 256 : 1024) + units - 1) / units));
+}
 
 size_t decode_workspace_bytes(const zipvl_dims& d, int cap) {
-    const int s = std::max(decode_splits(d, cap), row_splits(cap));     // either split scheme fits
-    return (size_t)d.B * d.Hq * s * (d.d + 2) * sizeof(float);
+    return (size_t)d.B * d.Hq * workspace_splits(d, cap) * (d.d + 2) * sizeof(float);
 }
 
 template <typename T, int D>
 static int launch_decode_t(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
                            const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
-    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, rows = rows_per_split(cap), max_splits = row_splits(cap);
+    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, nsplit = attend_splits(d, cap);
     const float c = scale * kLog2e;
-    dim3 grid(max_splits, units);
-#define ZIPVL_DEC(GT, GB)                                                                            \
-    hipLaunchKernelGGL((decode_partial_kernel<T, D, GT>), grid, dim3(256), 0, st, (const T*)q,       \
-        (const T*)Kc, (const T*)Vc, len, cap, d.Hq, d.Hkv, GB, c, (float*)ws, rows, max_splits)
+#define ZIPVL_DEC(GT)                                                                                \
+    hipLaunchKernelGGL((decode_partial_kernel<T, D, GT>), dim3(nsplit, units), dim3(64 * kDecWaves<GT>), 0, st, \
+        (const T*)q, (const T*)Kc, (const T*)Vc, len, cap, d.Hq, d.Hkv, gb, c, (float*)ws)
     for (int gb = 0; gb < G; gb += 8) {
-        const int rem = G - gb;
         KernelTimer tm(ZIPVL_K_DECODE_PARTIAL, st);
-        if (rem >= 5) ZIPVL_DEC(8, gb);
-        else if (rem >= 3) ZIPVL_DEC(4, gb);
-        else if (rem == 2) ZIPVL_DEC(2, gb);
-        else ZIPVL_DEC(1, gb);
+        if (G > 1) ZIPVL_DEC(8);
+        else ZIPVL_DEC(1);
         int rc = check_launch("decode_partial");
         if (rc) return rc;
     }
 #undef ZIPVL_DEC
     KernelTimer tm(ZIPVL_K_DECODE_COMBINE, st);
-    hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(units), dim3(256), 0, st,
-        (const float*)ws, len, cap, rows, 0, max_splits, G, (T*)o);
+    // as many threads as in the fused step, which makes the two paths add the splits in the same order
+    if (G > 1)
+        hipLaunchKernelGGL((decode_combine_kernel<T, D, 64 * kDecWaves<8>>), dim3(units), dim3(64 * kDecWaves<8>), 0, st,
+            (const float*)ws, len, cap, nsplit, G, (T*)o);
+    else
+        hipLaunchKernelGGL((decode_combine_kernel<T, D, 64 * kDecWaves<1>>), dim3(units), dim3(64 * kDecWaves<1>), 0, st,
+            (const float*)ws, len, cap, nsplit, G, (T*)o);
     return check_launch("decode_combine");
 }
 
@@ -732,8 +922,8 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
     }
 #undef ZIPVL_DECQ
     KernelTimer tm(ZIPVL_K_DECODE_COMBINE, st);
-    hipLaunchKernelGGL((decode_combine_kernel<T, D>), dim3(units), dim3(256), 0, st,
-        (const float*)ws, (const int32_t*)nullptr, 0, 1, nsplit, nsplit, G, (T*)o);
+    hipLaunchKernelGGL((decode_combine_kernel<T, D, 256>), dim3(units), dim3(256), 0, st,
+        (const float*)ws, (const int32_t*)nullptr, 0, nsplit, G, (T*)o);
     return check_launch("decode_combine");
 }
 
@@ -747,7 +937,7 @@ template <typename T, int D>
 static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,
                                 const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
-    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, rows = rows_per_split(cap), max_splits = row_splits(cap);
+    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv;
     unsigned* arrived = (unsigned*)ws;
     float* part = (float*)((char*)ws + step_counter_bytes(d));
     if (G > 8) {                                            // several passes over the cache per step: not fused
@@ -756,14 +946,12 @@ static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len,
         return launch_decode_attn(q, Kc, Vc, len, cap, d, scale, o, part, st);
     }
     const float c = scale * kLog2e;
-    dim3 grid(max_splits, units);
+    const dim3 grid(attend_splits(d, cap), units);
     KernelTimer tm(ZIPVL_K_DECODE_STEP, st);
 #define ZIPVL_STEP(GT)                                                                               \
-    hipLaunchKernelGGL((decode_step_kernel<T, D, GT>), grid, dim3(256), 0, st, (const T*)q, (T*)Kc, (T*)Vc, len, cap, \
-        (const T*)k_new, (const T*)v_new, d.Hq, d.Hkv, c, part, rows, max_splits, arrived, (T*)o)
-    if (G >= 5) ZIPVL_STEP(8);
-    else if (G >= 3) ZIPVL_STEP(4);
-    else if (G == 2) ZIPVL_STEP(2);
+    hipLaunchKernelGGL((decode_step_kernel<T, D, GT>), grid, dim3(64 * kDecWaves<GT>), 0, st, (const T*)q, (T*)Kc, (T*)Vc, len, cap, \
+        (const T*)k_new, (const T*)v_new, d.Hq, d.Hkv, c, part, arrived, (T*)o)
+    if (G > 1) ZIPVL_STEP(8);
     else ZIPVL_STEP(1);
 #undef ZIPVL_STEP
     return check_launch("decode_step");

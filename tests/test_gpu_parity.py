@@ -924,3 +924,39 @@ def test_decode_256_fused_steps_bit_identical_to_append_then_attention_at_the_st
     for u in (0, 1, 2, 3, 77):
         ref = oz.decode_attention(host64(q[u]), host64(Ka[u]), host64(Va[u]), int(expect[u]), scale)
         assert np.abs(oh[u] - ref).max() <= 2e-2
+
+
+@pytest.mark.parametrize("dtype,d,G", [("bf16", 128, 7), ("bf16", 64, 2), ("f32", 64, 4), ("f32", 128, 8)])
+def test_decode_of_head_groups_at_tile_edges(dtype, d, G):
+    """Groups of several heads on the matrix cores (16 cached rows per wave step): lengths on both sides of a tile, of a
+    workgroup step and of the capacity, the new row first and last of its tile, NaN in every row that is not part of the
+    cache yet.  Fused step against the oracle, and bit for bit against append + attention."""
+    say(f"decode tile edges dtype={dtype} d={d} G={G}")
+    lens = [0, 1, 14, 15, 16, 17, 127, 128, 255, 256, 511, 599, 600]
+    units, cap = len(lens), 600
+    w = make_custom(1, units * G, units, cap, d, dtype, seed=35)
+    Kc, Vc = dev(w.K, dtype).reshape(units, cap, d).clone(), dev(w.V, dtype).reshape(units, cap, d).clone()
+    for u, L in enumerate(lens):
+        Kc[u, L:] = float("nan")
+        Vc[u, L:] = float("nan")
+    g = torch.Generator(device=DEV); g.manual_seed(36)
+    dt = Kc.dtype
+    q = (2 * torch.randn((units * G, d), generator=g, device=DEV)).to(dt)
+    kn, vn = torch.randn((units, d), generator=g, device=DEV).to(dt), torch.randn((units, d), generator=g, device=DEV).to(dt)
+    la = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    Kb, Vb, lb = Kc.clone(), Vc.clone(), la.clone()
+    ws = z.decode_step_workspace(1, units * G, units, cap, d, Kc)
+    o = z.zipvl_decode_step(q, Kc, Vc, la, kn, vn, w.scale, B=1, Hq=units * G, Hkv=units, ws=ws)
+    z.zipvl_kv_append(Kb, Vb, lb, kn, vn, B=1, Hkv=units)
+    ob = z.zipvl_decode_attn(q, Kb, Vb, lb, w.scale, B=1, Hq=units * G, Hkv=units)
+    torch.cuda.synchronize()
+    assert torch.equal(o, ob) and la.tolist() == lb.tolist() == [min(L + 1, cap) for L in lens]
+    assert torch.equal(Kc.view(torch.uint8), Kb.view(torch.uint8)) and torch.equal(Vc.view(torch.uint8), Vb.view(torch.uint8))
+    worst = 0.0
+    for u, L in enumerate(lens):
+        L1 = min(L + 1, cap)
+        Kh, Vh = host64(Kc[u, :L1]), host64(Vc[u, :L1])
+        for h in range(u * G, u * G + G):
+            worst = max(worst, np.abs(host64(o[h]) - oz.decode_attention(host64(q[h]), Kh, Vh, L1, w.scale)).max())
+    say(f"  worst |do| = {worst:.3e}")
+    assert worst <= ATOL_OUT[dtype]
