@@ -249,7 +249,8 @@ struct DecTile {
     RawChunk<T, D / 16> v[4];
 };
 
-// a b^T of one 16-byte piece per lane: short chains, which the caller adds up pairwise.  One the rounding error into a score (1.3e-6 of the output against 0.4e-6).
+// a b^T of one 16-byte piece per lane: short chains, which the caller adds up pairwise.  One fp32 chain through all of
+// d = 128 puts 3.5 times the rounding error into the output (1.3e-6 against 0.35e-6 relative; 28 heads on 4, 2400 rows).
 __device__ __forceinline__ floatx4 mma16(const uintx4& a, const uintx4& b, __bf16) {
     const floatx4 zero = {0.f, 0.f, 0.f, 0.f};
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), zero, 0, 0, 0);

@@ -20,6 +20,13 @@ __device__ __forceinline__ unsigned lds_address(const char* p) {
     return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
 }
 
+// a wave-uniform pointer in scalar registers, wherever the compiler computed it
+__device__ __forceinline__ const char* scalar_ptr(const char* p) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+}
+
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 // One 1-KiB direct-to-LDS load of the wave: lane L's 16 bytes at gbase + goff land at LDS byte
@@ -35,7 +42,21 @@ __device__ __forceinline__ void load_kib_to_lds(const char* gbase, int goff, uns
                  :: "s"(m0v), "v"(goff), "s"(gbase) : "memory", "m0");
 }
 
-// The same load, placed by data flow instead of by program order: it is tied to a register (`pin`, passed
+// The same with a 64-bit address per lane, for rows that lie 4 GiB and more apart.
+__device__ __forceinline__ void load_kib_to_lds_at(const char* lane_ptr, unsigned lds_base) {
+    const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :: "s"(m0v), "v"(lane_ptr) : "memory", "m0");
+}
+
+// 4 bytes per lane: lane L's dword at gbase + goff lands at LDS byte lds_base + 4 L.
+__device__ __forceinline__ void load_dwords_to_lds(const char* gbase, int goff, unsigned lds_base) {
+    const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                 :: "s"(m0v), "v"(goff), "s"(gbase) : "memory", "m0");
+}
+
+// The first load, placed by data flow instead of by program order: it is tied to a register (`pin`, passed
 // through unchanged) so that it issues after the instruction that produced `pin` and before the one that
 // consumes it, without ordering the surrounding LDS reads the way a statement with side effects would.
 // The buffers written must not be read before a barrier that is preceded by a wait for all of the wave's loads.

@@ -487,6 +487,27 @@ def test_all_rows_scores_match_the_oracle(case):
     assert np.all(np.abs(mass_h.sum(axis=1) - 1.0) < 1e-4)
 
 
+@pytest.mark.parametrize("n,d,dtype,gain", [(700, 128, "bf16", 12.0), (700, 128, "bf16", 80.0), (257, 64, "f32", 60.0), (129, 128, "f32", 12.0)])
+def test_all_rows_scores_with_logits_that_outgrow_the_first_block(n, d, dtype, gain):
+    """Logits far above those of the first keys, ragged lengths, strided inputs ([n, heads, d] in memory).
+    A log2-domain exponent x carries sqrt(d) 2^-24 |x| < 1e-6 |x| from the fp32 product sum and its roundings."""
+    say(f"score_all_rows n={n} d={d} {dtype} gain={gain}")
+    w = make_custom(1, 4, 2, n, d, dtype, seed=72, m=64)
+    K32 = w.K.copy()
+    late = [n // 2, n - 30, n - 2]
+    K32[:, :, late] = (gain / 4) * w.Q[:, ::2, late] / np.linalg.norm(w.Q[:, ::2, late], axis=-1, keepdims=True)
+    Q = dev(w.Q, dtype).transpose(1, 2).contiguous().transpose(1, 2)
+    K = dev(K32, dtype).transpose(1, 2).contiguous().transpose(1, 2)
+    mass, rank = z.zipvl_score_all_rows(Q, K, w.scale)
+    torch.cuda.synchronize()
+    Qh, Kh = host64(Q)[0], host64(K)[0]
+    big = max(np.abs(Qh[h] @ Kh[h // 2].T).max() for h in range(4)) * w.scale * 1.4427
+    say(f"  largest log2-domain logit {big:.0f}")
+    mo, ro = oz.token_scores(Qh, Kh, np.arange(n), w.scale)
+    for got, ref in ((mass, mo), (rank, ro)):
+        assert (np.abs(host64(got) - ref) <= 1e-9 + (1e-5 + 1e-6 * big) * np.abs(ref)).all()
+
+
 def test_all_rows_scores_at_cfg2_shape_against_sampled_columns():
     say("score_all_rows at n=3072, 32 heads (sampled heads)")
     w = make_workload(2)
