@@ -66,7 +66,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     constexpr int CH = C::CH, RB = C::RB, SK = C::SK, KBS = C::KBS, NLD = C::NLD, kStageBytes = C::STG;
     constexpr int kThreads = 64 * NWV;
     extern __shared__ __attribute__((aligned(16))) char kstage[];   // kStageBufs stage buffers
-    __shared__ int sp[ZIPVL_MAX_PROBES];
+    __shared__ __attribute__((aligned(16))) int sp[ZIPVL_MAX_PROBES];
     __shared__ float2 wstat[PASS == 1 ? NWV : 1][32];                // pass 1: per-wave row statistics
     __shared__ __attribute__((aligned(16))) float row_bias[PASS == 2 ? NWV : 1][32];
     __shared__ float colbuf[PASS == 2 ? 2 : 1][PASS == 2 ? NWV : 1][PASS == 2 ? SK : 1];
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             // merge the chunk statistics of this task's 32 rows: lane = (row, half of the chunks)
             float M = -INFINITY, L = 0.f;
             const float2* p = partial + (int64_t)bh * nsplit * np + nb * 32;     // wave-uniform base; the rest fits 32 bits (host check)
-            for (int s0 = h; s0 < nsplit; s0 += 16) {                // 8 independent loads per lane and round
+            for (int s0 = h; s0 < nsplit; s0 += 16) {                // 8 independent loads per lane and round (16: 47 -> 53 us for the 18432-token pass pair, 32 spills)
                 float2 v[8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
@@ -184,9 +184,17 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                     mass[(int64_t)u * n + j] = a;
                 } else {
                     a /= (float)G;
-                    int cnt = 0;
-                    if (j <= Pmin) cnt = m;
-                    else for (int q = 0; q < m; ++q) cnt += sp[q] >= j ? 1 : 0;
+                    // probes at or after j: m less those before it (sp ascends).  By bisection: counting all 128 one by one
+                    // took half of pass 2 with random probes (40 heads, n = 4096, m = 128: 53 -> 22 us).
+                    int cnt = m;
+                    if (j > Pmin) {
+                        int before = 0;
+#pragma unroll
+                        for (int step = ZIPVL_MAX_PROBES / 2; step; step >>= 1)
+                            if (before + step <= m && sp[before + step - 1] < j) before += step;
+                        if (before < m && sp[before] < j) ++before;          // all ZIPVL_MAX_PROBES of them
+                        cnt = m - before;
+                    }
                     mass[(int64_t)u * n + j] = a / (float)m;
                     if (rank) rank[(int64_t)u * n + j] = cnt > 0 ? a / (float)cnt : 0.f;
                 }
@@ -251,9 +259,13 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                         float sum = 0.f;
                         if (masked) {
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                const float pr = fast_exp2(fmaf(acc[r], c, -rb[r]));
-                                sum += jb + i > sp[nb * 32 + acc_row(r, h)] ? 0.f : pr;
+                            for (int a = 0; a < 4; ++a) {
+                                const uintx4 pos = *reinterpret_cast<const uintx4*>(&sp[nb * 32 + 8 * a + 4 * h]);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    const float pr = fast_exp2(fmaf(acc[4 * a + e], c, -rb[4 * a + e]));
+                                    sum += jb + i > (int)pos[e] ? 0.f : pr;
+                                }
                             }
                         } else {
 #pragma unroll

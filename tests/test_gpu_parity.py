@@ -186,6 +186,23 @@ def test_select_status_word_reports_inputs_outside_the_contract():
     assert int(k2[0]) == int(k[0]) and torch.equal(idx2[0, :int(k2[0])], idx[0, :int(k2[0])])
 
 
+@pytest.mark.parametrize("m", [1, 2, 63, 64, 65, 127, 128])
+def test_rank_divides_by_the_probes_at_or_after_each_key(m):
+    """Eq. (8)'s count for every key of a 300-token unit, with probes scattered over it (first key a probe, last not):
+    mass and rank come from one sum, so rank * count = mass * m up to two roundings."""
+    say(f"score rank counts m={m}")
+    n = 300
+    r = np.random.Generator(np.random.PCG64(m))
+    pos = np.sort(np.concatenate([[0], 1 + r.permutation(n - 3)[: m - 1]])) if m > 1 else np.array([137])
+    w = make_custom(1, 2, 1, n, 64, "f32", seed=73, m=64)
+    mass, rank = z.zipvl_score(dev(w.Q, "f32"), dev(w.K, "f32"), pos, w.scale)
+    torch.cuda.synchronize()
+    cnt = (pos[:, None] >= np.arange(n)[None, :]).sum(axis=0)
+    a, b = host64(mass)[0] * m, host64(rank)[0] * cnt
+    assert (host64(rank)[0][cnt == 0] == 0).all() and (host64(mass)[0][cnt == 0] == 0).all()
+    assert (np.abs(a - b) <= 4 * 2.0 ** -24 * a).all()
+
+
 def test_scores_per_query_head_are_the_single_head_scores():
     """ZIPVL_SCORE_PER_QHEAD: one row per query head, nothing averaged (the paper's single-head equations); the group
     mean of those rows is what the default mode returns."""
