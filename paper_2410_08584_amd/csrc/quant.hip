@@ -10,6 +10,7 @@
 // `quantize_rows` then handles 16 rows per wave pass, 16 lanes per row like the
 // decode kernels, so every code row is written as one contiguous store per lane.
 #include <atomic>
+#include <type_traits>
 
 #include "launch.h"
 #include "rowops.h"
@@ -63,34 +64,76 @@ __global__ __launch_bounds__(kSlotThreads) void token_slots_kernel(
     }
 }
 
-template <int EPL, int BITS>
-__device__ __forceinline__ void quantize_chunk(const float (&x)[EPL], uint8_t* codes, uint32_t* params, int64_t row, int D, int sub) {
+// minimum / maximum over the 16 lanes of a row, result in all of them (lane permutes inside the row, no LDS)
+template <bool MAX>
+__device__ __forceinline__ float row16_extreme(float v) {
+    auto step = [&](auto ctrl) {
+        const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
+        v = MAX ? fmaxf(v, o) : fminf(v, o);
+    };
+    step(std::integral_constant<int, 0xB1>());       // quad_perm [1,0,3,2]
+    step(std::integral_constant<int, 0x4E>());       // quad_perm [2,3,0,1]
+    step(std::integral_constant<int, 0x141>());      // mirror of 8: the other quad
+    step(std::integral_constant<int, 0x140>());      // mirror of 16: the other 8
+    return v;
+}
+
+// Codes and parameters of one row (EPL elements in each of its 16 lanes) at 4 or 2 bits, chosen per row: one
+// instruction stream serves the rows of both widths that share a wave.
+// The code is rint of the correctly rounded (x - zero) / scale.  The product with a reciprocal lies within 1e-5 of that
+// quotient wherever it is below 16, so the two round to the same code unless it comes that close to a half; only
+// then (about one wave step in a hundred) are the divisions taken.
+template <int EPL>
+__device__ __forceinline__ uint32_t quantize_chunk(const float (&x)[EPL], bool wide, uint32_t& params) {
     float lo = x[0], hi = x[0];
 #pragma unroll
     for (int e = 1; e < EPL; ++e) { lo = fminf(lo, x[e]); hi = fmaxf(hi, x[e]); }
-#pragma unroll
-    for (int off = 1; off < 16; off <<= 1) {
-        lo = fminf(lo, __shfl_xor(lo, off));
-        hi = fmaxf(hi, __shfl_xor(hi, off));
-    }
-    constexpr float qmax = (float)((1 << BITS) - 1);
+    lo = row16_extreme<false>(lo);
+    hi = row16_extreme<true>(hi);
+    const float qmax = wide ? 15.f : 3.f;
     const _Float16 zero_h = (_Float16)lo;
-    float step = (hi - lo) * (float)(1.0 / (double)qmax);
+    float step = (hi - lo) * (wide ? (float)(1.0 / 15.0) : (float)(1.0 / 3.0));
     asm volatile("" : "+v"(step));            // the product is rounded to fp32 first: no fused multiply-convert
     const _Float16 scale_h = (_Float16)step;
     const float zero = (float)zero_h, scale = (float)scale_h;
+    const float inv = scale > 0.f ? __builtin_amdgcn_rcpf(scale) : 0.f;
+    const int bits = wide ? 4 : 2;
     uint32_t word = 0;
+    float off = 0.f;                                         // largest distance from the nearest integer
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        float t = scale > 0.f ? (x[e] - zero) / scale : 0.f;
-        t = fminf(fmaxf(__builtin_rintf(t), 0.f), qmax);
-        word |= (uint32_t)t << (e * BITS);
+    for (int e = EPL - 1; e >= 0; --e) {
+        const float t = (x[e] - zero) * inv, q = __builtin_rintf(t);
+        off = fmaxf(off, fabsf(t - q));
+        word = (word << bits) | (uint32_t)fminf(fmaxf(q, 0.f), qmax);
     }
-    using W = typename CodeWord<EPL, BITS>::type;
-    *reinterpret_cast<W*>(codes + row * (D * BITS / 8) + sub * sizeof(W)) = (W)word;
-    if (sub == 0)
-        params[row] = (uint32_t)__builtin_bit_cast(uint16_t, scale_h) | ((uint32_t)__builtin_bit_cast(uint16_t, zero_h) << 16);
+    if (__any(off > 0.49999f)) {
+        word = 0;
+#pragma unroll
+        for (int e = EPL - 1; e >= 0; --e) {
+            float t = scale > 0.f ? (x[e] - zero) / scale : 0.f;
+            t = fminf(fmaxf(__builtin_rintf(t), 0.f), qmax);
+            word = (word << bits) | (uint32_t)t;
+        }
+    }
+    params = (uint32_t)__builtin_bit_cast(uint16_t, scale_h) | ((uint32_t)__builtin_bit_cast(uint16_t, zero_h) << 16);
+    return word;
 }
+
+// one lane's EPL elements of a row as loaded
+template <typename T, int EPL>
+struct RawRow {
+    T v[EPL];
+    __device__ __forceinline__ void load(const T* p) {
+        struct alignas(sizeof(T) * EPL > 16 ? 16 : sizeof(T) * EPL) Raw { T v[EPL]; };
+        const Raw r = *reinterpret_cast<const Raw*>(p);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) v[e] = r.v[e];
+    }
+    __device__ __forceinline__ void floats(float (&f)[EPL]) const {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) f[e] = (float)v[e];
+    }
+};
 
 struct QTensorOut {
     uint8_t* hi_codes; uint32_t* hi_params;
@@ -117,26 +160,50 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(
     }
     const T* Kb = K + b * ks0 + g * ks1 + sub * EPL;
     const T* Vb = V + b * vs0 + g * vs1 + sub * EPL;
-    const int j0 = blockIdx.x * kQuantRows;
-#pragma unroll 1
-    for (int p = 0; p < kQuantRows / 16; ++p) {
-        const int j = j0 + p * 16 + rl;                                 // uniform over the 16 lanes of a row
-        if (j >= n) continue;
-        const int s = slot[(int64_t)ut * n + j];
-        float kf[EPL], vf[EPL];
-        RowChunk<T, EPL>::load(Kb + (int64_t)j * ks2, kf);
-        RowChunk<T, EPL>::load(Vb + (int64_t)j * vs2, vf);
-        if (s >= 0) {
-            if (s < cap_hi) {
-                const int64_t row = (int64_t)u * cap_hi + s;
-                quantize_chunk<EPL, 4>(kf, Kq.hi_codes, Kq.hi_params, row, D, sub);
-                quantize_chunk<EPL, 4>(vf, Vq.hi_codes, Vq.hi_params, row, D, sub);
-            }
-        } else if (~s < cap_lo) {
-            const int64_t row = (int64_t)u * cap_lo + ~s;
-            quantize_chunk<EPL, 2>(kf, Kq.lo_codes, Kq.lo_params, row, D, sub);
-            quantize_chunk<EPL, 2>(vf, Vq.lo_codes, Vq.lo_params, row, D, sub);
+    const int32_t* slots = slot + (int64_t)ut * n;
+    const int j0 = blockIdx.x * kQuantRows + rl;
+    constexpr int kPasses = kQuantRows / 16;
+    // rows past the end are loaded from the last one and dropped
+    RawRow<T, EPL> kr, vr;
+    int s = slots[min(j0, n - 1)];
+    kr.load(Kb + (int64_t)min(j0, n - 1) * ks2);
+    vr.load(Vb + (int64_t)min(j0, n - 1) * vs2);
+    using W4 = typename CodeWord<EPL, 4>::type;
+    using W2 = typename CodeWord<EPL, 2>::type;
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        const int j = j0 + p * 16, jn = min(j + 16, n - 1);             // uniform over the 16 lanes of a row
+        RawRow<T, EPL> kx, vx;
+        int sx = 0;
+        if (p + 1 < kPasses) {                                          // the next rows are on their way while these are coded
+            sx = slots[jn];
+            kx.load(Kb + (int64_t)jn * ks2);
+            vx.load(Vb + (int64_t)jn * vs2);
         }
+        const bool wide = s >= 0;
+        const int i = wide ? s : ~s;
+        float f[EPL];
+        uint32_t kp, vp;
+        kr.floats(f);
+        const uint32_t kw = quantize_chunk<EPL>(f, wide, kp);
+        vr.floats(f);
+        const uint32_t vw = quantize_chunk<EPL>(f, wide, vp);
+        if (j < n) {
+            if (wide) {
+                if (i < cap_hi) {
+                    const int64_t row = (int64_t)u * cap_hi + i;
+                    reinterpret_cast<W4*>(Kq.hi_codes + row * (D / 2))[sub] = (W4)kw;
+                    reinterpret_cast<W4*>(Vq.hi_codes + row * (D / 2))[sub] = (W4)vw;
+                    if (sub == 0) { Kq.hi_params[row] = kp; Vq.hi_params[row] = vp; }
+                }
+            } else if (i < cap_lo) {
+                const int64_t row = (int64_t)u * cap_lo + i;
+                reinterpret_cast<W2*>(Kq.lo_codes + row * (D / 4))[sub] = (W2)kw;
+                reinterpret_cast<W2*>(Vq.lo_codes + row * (D / 4))[sub] = (W2)vw;
+                if (sub == 0) { Kq.lo_params[row] = kp; Vq.lo_params[row] = vp; }
+            }
+        }
+        kr = kx; vr = vx; s = sx;
     }
 }
 

@@ -684,6 +684,47 @@ def test_quantize_kv_bit_exact_and_decode_over_it(dtype, d):
     assert worst <= ATOL_OUT[dtype]
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 128), ("bf16", 128), ("f32", 64), ("bf16", 64)])
+def test_quantize_kv_codes_at_half_steps_and_degenerate_rows(dtype, d):
+    """Quotients on and next to k + 1/2, constant rows, ranges whose fp16 scale is 0, subnormal or infinite: the codes are those
+    of the correctly rounded division, bit for bit."""
+    say(f"quantize_kv half steps dtype={dtype} d={d}")
+    r = np.random.Generator(np.random.PCG64(63))
+    n = 211
+    X = np.empty((n, d), dtype=np.float32)
+    for i in range(n):
+        top = 15 if i % 2 else 3
+        scale = np.float32(np.float16(2.0 ** r.integers(-12, 6) * (1 if i % 3 == 0 else r.uniform(1, 2))))
+        zero = np.float32(np.float16(r.choice([0.0, -1.5, 3.25]) * scale))
+        half = (r.integers(0, top, d) + 0.5).astype(np.float32)
+        row = zero + scale * half
+        row = np.where(r.random(d) < 0.3, np.nextafter(row, np.float32(r.choice([-1e9, 1e9]))), row)
+        row[0], row[1] = zero, zero + scale * np.float32(top)
+        X[i] = row
+    X[5], X[6] = 0.75, 0.0                                    # constant rows: scale 0
+    X[7] = r.standard_normal(d) * 1e6                         # scale and zero infinite in fp16
+    X[8] = r.standard_normal(d) * 1e-9                        # scale rounds to 0
+    X[9] = r.standard_normal(d) * 3e-7                        # subnormal scale
+    X[10] = 3.0e4 * np.sign(r.standard_normal(d))             # finite zero, large scale
+    K = dev(X, dtype).reshape(1, 1, n, d)
+    idx = torch.zeros((1, n), dtype=torch.int32, device=DEV)
+    odd = np.arange(1, n, 2)
+    idx[0, :len(odd)] = torch.from_numpy(odd.astype(np.int32)).to(DEV)
+    cache = z.zipvl_quantize_kv(K, K, idx, torch.tensor([len(odd)], dtype=torch.int32, device=DEV), n, n)
+    torch.cuda.synchronize()
+    Xh = host64(K)[0, 0].astype(np.float32)
+    for t in (cache.K, cache.V):
+        for name, bits, rows in (("hi", 4, odd), ("lo", 2, np.arange(0, n, 2))):
+            with np.errstate(all="ignore"):
+                codes, scale, zero = oz.quantize_rows(Xh[rows], bits)
+            got = t[name + "_codes"][0, :len(rows)].cpu().numpy()
+            got = ((got[:, :, None] >> (np.arange(8 // bits) * bits)) & (2 ** bits - 1)).reshape(len(rows), d)
+            par = t[name + "_params"][0, :len(rows)].cpu().numpy()
+            assert par[:, 0].tobytes() == scale.tobytes() and par[:, 1].tobytes() == zero.tobytes()
+            finite = np.isfinite(scale) & np.isfinite(zero)               # inf / inf: the oracle's cast of NaN is not defined
+            assert np.array_equal(got[finite], codes[finite])
+
+
 @pytest.mark.parametrize("Hq,Hkv", [(4, 4), (8, 2), (14, 2)])
 def test_decode_over_quantised_cache_for_every_group_size(Hq, Hkv):
     say(f"decode_attn_q Hq={Hq} Hkv={Hkv}")
