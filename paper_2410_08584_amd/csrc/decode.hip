@@ -11,6 +11,7 @@
 // finally splits are merged with the usual (max, sum, weighted output) rule.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "launch.h"
 #include "rowops.h"
@@ -40,25 +41,6 @@ __device__ __forceinline__ void attend_row(bool valid, const float (&kf)[EPL], c
 #pragma unroll
             for (int e = 0; e < EPL; ++e) o[t][e] = o[t][e] * a + p * vf[e];
             m[t] = m_new;
-        }
-    }
-}
-
-// this lane's EPL elements of the group's queries, pre-multiplied by the softmax scale (log2 domain)
-template <typename T, int D, int GT>
-__device__ __forceinline__ void load_queries(const T* q, int b, int g, int G, int Hq, int gbase, int sub, float c,
-                                             float (&qv)[GT][D / 16]) {
-    constexpr int EPL = D / 16;
-#pragma unroll
-    for (int t = 0; t < GT; ++t) {
-        const int hh = gbase + t;
-        if (hh < G) {
-            RowChunk<T, EPL>::load(q + ((int64_t)(b * Hq + g * G + hh)) * D + sub * EPL, qv[t]);
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) qv[t][e] *= c;
-        } else {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) qv[t][e] = 0.f;
         }
     }
 }
@@ -205,15 +187,7 @@ __device__ __forceinline__ void write_partial(float (&m)[GT], float (&l)[GT], fl
     combine_waves<D, GT, 4, COHERENT>(red, heads, po, gbase, split);
 }
 
-// rows [r_begin, r_end) of a segment of L rows that split `split` of nsplit handles (multiples of 16 rows)
-__device__ __forceinline__ void split_range(int L, int split, int nsplit, int& r_begin, int& r_end) {
-    int per = (L + nsplit - 1) / nsplit;
-    per = (per + 15) & ~15;
-    r_begin = split * per;
-    r_end = min(L, r_begin + per);
-}
-
-// the same in multiples of 64 rows (16 rows per wave step)
+// rows [r_begin, r_end) of a segment of L rows that split `split` of nsplit handles (multiples of 64 rows: 16 per wave step)
 __device__ __forceinline__ void split_range64(int L, int split, int nsplit, int& r_begin, int& r_end) {
     int per = (L + nsplit - 1) / nsplit;
     per = (per + 63) & ~63;
@@ -522,108 +496,10 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_step_kernel(
 }
 
 // ---------------------------------------------------------------- mixed-precision cache
-// Codes of EPL consecutive elements at BITS bits each (element e in bits [e*BITS, e*BITS+BITS) of the
-// little-endian word) -> floats zero + scale * code.
-
-template <int EPL, int BITS>
-__device__ __forceinline__ void load_quantized(const uint8_t* codes, const uint32_t* params, int64_t row, int D, int sub,
-                                               float (&f)[EPL]) {
-    using W = typename CodeWord<EPL, BITS>::type;
-    const uint32_t word = *reinterpret_cast<const W*>(codes + row * (D * BITS / 8) + sub * sizeof(W));
-    const uint32_t par = params[row];                       // fp16 scale (low half), fp16 zero (high half)
-    const float scale = (float)__builtin_bit_cast(_Float16, (uint16_t)(par & 0xFFFFu));
-    const float zero = (float)__builtin_bit_cast(_Float16, (uint16_t)(par >> 16));
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) f[e] = fmaf(scale, (float)((word >> (e * BITS)) & ((1u << BITS) - 1u)), zero);
-}
-
 struct QTensor {                 // device pointers of one mixed-precision tensor, by value in the kernel arguments
     const uint8_t* hi_codes; const uint32_t* hi_params;
     const uint8_t* lo_codes; const uint32_t* lo_params;
 };
-
-// Eq. (5) over [4-bit rows of T | 2-bit rows of the other tokens | rows appended during decoding].
-template <typename T, int D, int GT>
-__global__ __launch_bounds__(256) void decode_q_partial_kernel(
-    const T* __restrict__ q, QTensor Kq, QTensor Vq, const int32_t* __restrict__ len_hi, const int32_t* __restrict__ len_lo,
-    int cap_hi, int cap_lo, const T* __restrict__ Kt, const T* __restrict__ Vt, const int32_t* __restrict__ len_t, int cap_t,
-    int Hq, int Hkv, int gbase, float c, float* __restrict__ part, int nsplit)
-{
-    constexpr int EPL = D / 16;
-    __shared__ float red[4][GT][D + 2];
-    const int G = Hq / Hkv;
-    const int split = blockIdx.x, u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
-    float qv[GT][EPL];
-    load_queries<T, D, GT>(q, b, g, G, Hq, gbase, sub, c, qv);
-    float m[GT], l[GT], o[GT][EPL];
-#pragma unroll
-    for (int t = 0; t < GT; ++t) {
-        m[t] = -INFINITY; l[t] = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) o[t][e] = 0.f;
-    }
-    int r_begin, r_end;
-    {   // important tokens, 4 bits
-        const int L = max(0, min(len_hi[u], cap_hi));
-        split_range(L, split, nsplit, r_begin, r_end);
-        const int64_t base = (int64_t)u * cap_hi;
-        for (int r = r_begin + w * 4 + rg; r - rg - w * 4 < r_end; r += 16) {
-            const bool valid = r < r_end;
-            const int64_t row = base + (valid ? r : r_begin);
-            float kf[EPL], vf[EPL];
-            load_quantized<EPL, 4>(Kq.hi_codes, Kq.hi_params, row, D, sub, kf);
-            load_quantized<EPL, 4>(Vq.hi_codes, Vq.hi_params, row, D, sub, vf);
-            attend_row<EPL, GT>(valid, kf, vf, qv, m, l, o);
-        }
-    }
-    {   // the other tokens, 2 bits
-        const int L = max(0, min(len_lo[u], cap_lo));
-        split_range(L, split, nsplit, r_begin, r_end);
-        const int64_t base = (int64_t)u * cap_lo;
-        for (int r = r_begin + w * 4 + rg; r - rg - w * 4 < r_end; r += 16) {
-            const bool valid = r < r_end;
-            const int64_t row = base + (valid ? r : r_begin);
-            float kf[EPL], vf[EPL];
-            load_quantized<EPL, 2>(Kq.lo_codes, Kq.lo_params, row, D, sub, kf);
-            load_quantized<EPL, 2>(Vq.lo_codes, Vq.lo_params, row, D, sub, vf);
-            attend_row<EPL, GT>(valid, kf, vf, qv, m, l, o);
-        }
-    }
-    if (Kt) {   // rows appended during decoding, as stored
-        const int L = max(0, min(len_t[u], cap_t));
-        split_range(L, split, nsplit, r_begin, r_end);
-        const T* Kb = Kt + (int64_t)u * cap_t * D + sub * EPL;
-        const T* Vb = Vt + (int64_t)u * cap_t * D + sub * EPL;
-        for (int r = r_begin + w * 4 + rg; r - rg - w * 4 < r_end; r += 16) {
-            const bool valid = r < r_end;
-            const int rr = valid ? r : r_begin;
-            float kf[EPL], vf[EPL];
-            RowChunk<T, EPL>::load(Kb + (int64_t)rr * D, kf);
-            RowChunk<T, EPL>::load(Vb + (int64_t)rr * D, vf);
-            attend_row<EPL, GT>(valid, kf, vf, qv, m, l, o);
-        }
-    }
-    write_partial<D, GT>(m, l, o, red, min(GT, G - gbase), PartialOut(part, D, u, G, nsplit, gridDim.y), gbase, split);
-}
-
-// ---- the same, for small query groups (GT <= 2): 4 lanes per row.
-// A 4-bit row of d = 128 is 64 bytes: with 16 lanes per row a lane would hold 4 bytes and the per-row work
-// (cross-lane sums, softmax update) would dominate.  Here a lane holds d/4 consecutive elements (16 bytes of 4-bit
-// codes, 8 bytes of 2-bit codes), a wave covers 16 rows per step, and the arithmetic runs on the codes:
-//   q . (zero + scale * code) = zero * sum(q) + scale * (q . code),
-//   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j zero_j + sum_j (p_j scale_j) code_j,
-// i.e. one conversion and one FMA per element and side.  The softmax offset follows the running maximum lazily
-// (moves only when exceeded by 2^kDecLazyLog2), so the accumulators are rescaled on few rows.
-
-// sum over the 4 lanes of a quad (lanes 4i .. 4i+3), result in all four, by two in-register lane permutes
-__device__ __forceinline__ float quad_sum(float v) {
-    int x = __float_as_int(v);
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
-    x = __float_as_int(v);
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
-    return v;
-}
 
 // the NB-byte code string of one lane -> EPL = NB * 8 / BITS floats (codes as numbers), element e at bits [e*BITS, ..)
 template <int BITS, int NW>
@@ -659,6 +535,229 @@ template <> __device__ __forceinline__ void load_words<1>(const uint8_t* p, uint
     w[0] = *reinterpret_cast<const uint32_t*>(p);
 }
 
+__device__ __forceinline__ void unpack_params(uint32_t v, float& scale, float& zero) {   // fp16 scale (low half), fp16 zero (high half)
+    scale = (float)__builtin_bit_cast(_Float16, (uint16_t)(v & 0xFFFFu));
+    zero = (float)__builtin_bit_cast(_Float16, (uint16_t)(v >> 16));
+}
+
+// Eq. (5) over [4-bit rows of T | 2-bit rows of the other tokens | rows appended during decoding], for groups of several
+// heads: the tiles of attend_split.  V rows are dequantised to fp32 (zero + scale * code) in registers.  K rows are for fp32
+// queries; bf16 queries meet the doubled codes about their middle, 2 code - 15 or 2 code - 3, in exact bf16 products:
+//   q . (zero + scale * code) = (zero + scale * mid) * sum(q) + scale / 2 * (q . (2 code - 2 mid))
+// (either term is of the size of the scores then; with plain codes they cancel: 2.4e-6 of the output, fp32 queries, against
+// 0.36e-6 dequantised).
+// Lane (j, kk) reads a quarter kk of the codes of K row j in one piece (the queries are held in that order) and, of the V
+// rows 4 kk + r, the codes of elements EPL j ... EPL j + EPL - 1.  The tiles of the three parts form one list, dealt to
+// splits and waves in turn.  One step of 28 heads on 4, 18432 rows: 36 us a layer (append and merge
+// included), 66 with the heads in turn on the vector units.
+template <typename T, int D, int GT>
+__global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
+    const T* __restrict__ q, QTensor Kq, QTensor Vq, const int32_t* __restrict__ len_hi, const int32_t* __restrict__ len_lo,
+    int cap_hi, int cap_lo, const T* __restrict__ Kt, const T* __restrict__ Vt, const int32_t* __restrict__ len_t, int cap_t,
+    int Hq, int Hkv, int gbase, float c, float* __restrict__ part, int nsplit)
+{
+    constexpr bool kExact = sizeof(T) == 2;                              // codes meet the queries in bf16
+    constexpr int EPL = D / 16, QE = D / 4, E16 = 16 / (int)sizeof(T), NK = QE / E16, NP = kExact ? 4 : 1, NW4 = QE / 8, NW2 = QE / 16;
+    __shared__ float red[kDecWaves<GT>][GT][D + 2];
+    const int G = Hq / Hkv, heads = min(GT, G - gbase);
+    const int split = blockIdx.x, u = blockIdx.y;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 15, kk = lane >> 4;
+    const int L4 = max(0, min(len_hi[u], cap_hi)), L2 = max(0, min(len_lo[u], cap_lo)), Lt = Kt ? max(0, min(len_t[u], cap_t)) : 0;
+    const int T4 = (L4 + kDecTile - 1) / kDecTile, T2 = (L2 + kDecTile - 1) / kDecTile, Tt = (Lt + kDecTile - 1) / kDecTile;
+    const int per = (T4 + T2 + Tt + nsplit - 1) / nsplit;
+    const int t_end = min(T4 + T2 + Tt, (split + 1) * per), t_codes = min(t_end, T4 + T2);
+
+    struct Codes { uint32_t k[NW4], kp[NP], v[4], vp[4]; };
+    auto fetch = [&](int t, Codes& x) {
+        const bool hi = t < T4;                                          // wave-uniform
+        const int t0 = (hi ? t : t - T4) * kDecTile, last = (hi ? L4 : L2) - 1;
+        const int64_t base = (int64_t)u * (hi ? cap_hi : cap_lo);
+        const uint32_t* kpar = hi ? Kq.hi_params : Kq.lo_params;
+        const uint32_t* vpar = hi ? Vq.hi_params : Vq.lo_params;
+        const int64_t rk = base + min(t0 + j, last);                     // rows past the end re-read the last one and weigh nothing
+        if (hi) {
+            load_words<NW4>(Kq.hi_codes + rk * (D / 2) + kk * (QE / 2), x.k);
+        } else {
+            uint32_t lo[NW2];
+            load_words<NW2>(Kq.lo_codes + rk * (D / 4) + kk * (QE / 4), lo);
+#pragma unroll
+            for (int i = 0; i < NW2; ++i) x.k[i] = lo[i];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int64_t row = base + min(t0 + 4 * kk + r, last);
+            if (hi) x.v[r] = reinterpret_cast<const typename CodeWord<EPL, 4>::type*>(Vq.hi_codes + row * (D / 2))[j];
+            else x.v[r] = reinterpret_cast<const typename CodeWord<EPL, 2>::type*>(Vq.lo_codes + row * (D / 4))[j];
+            x.vp[r] = vpar[row];
+            if (kExact) x.kp[r % NP] = kpar[row];
+        }
+        if (!kExact) x.kp[0] = kpar[rk];
+    };
+    int t = split * per + w;
+    Codes cur;
+    if (t < t_codes) fetch(t, cur);
+
+    uintx4 qf[NK];                                                       // elements QE kk ... of head j
+    float qsum = 0.f;
+#pragma unroll
+    for (int cc = 0; cc < NK; ++cc) {
+        qf[cc] = uintx4{0, 0, 0, 0};
+        if (j < heads) {
+            const T* qp = q + ((int64_t)u * G + gbase + j) * D + kk * QE + cc * E16;
+            float f[E16];
+            qf[cc] = load16(qp);
+            RowChunk<T, E16>::load(qp, f);
+#pragma unroll
+            for (int e = 0; e < E16; ++e) qsum += f[e];
+        }
+    }
+    qsum += __shfl_xor(qsum, 16);
+    qsum += __shfl_xor(qsum, 32);
+    auto products = [&](const uintx4 (&kf)[NK]) {
+        floatx4 sp[NK];
+#pragma unroll
+        for (int cc = 0; cc < NK; ++cc) sp[cc] = mma16(kf[cc], qf[cc], T());
+#pragma unroll
+        for (int half = NK / 2; half; half >>= 1)
+#pragma unroll
+            for (int cc = 0; cc < half; ++cc) sp[cc] += sp[cc + half];
+        return sp[0];
+    };
+    float m = -INFINITY, l = 0.f;                                        // head j
+    floatx4 o[EPL];                                                      // o[e][r]: element EPL (4 kk + r) + e of head j
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) o[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // one tile of which the first `left` rows exist; s: its scores before the softmax scale
+    auto attend = [&](floatx4 s, float (&vf)[4][EPL], int left) {
+        if (left < kDecTile) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (4 * kk + r >= left) {
+                    s[r] = -INFINITY;
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) vf[r][e] = 0.f;        // zero weight times an infinite element would be NaN
+                }
+        }
+        const float mx1 = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])) * c;
+        if (__any(mx1 > m + kDecLazyLog2)) {
+            float mx = fmaxf(mx1, __shfl_xor(mx1, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx), a = m_new > -INFINITY ? fast_exp2(m - m_new) : 1.f;
+            l *= a;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) o[e] *= a;
+            m = m_new;
+        }
+        const float ms = m > -INFINITY ? m : 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float p = fast_exp2(fmaf(s[r], c, -ms));
+            l += p;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) o[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][e], p, o[e], 0, 0, 0);
+        }
+    };
+    for (; t < t_codes; t += kDecWaves<GT>) {
+        Codes nxt;
+        if (t + kDecWaves<GT> < t_codes) fetch(t + kDecWaves<GT>, nxt);  // in flight while this tile is multiplied
+        const bool hi = t < T4;
+        float kv[QE], vf[4][EPL], scale, zero;
+        if (hi) {
+            codes_to_floats<4, NW4>(cur.k, kv);
+        } else {
+            uint32_t lo[NW2];
+#pragma unroll
+            for (int i = 0; i < NW2; ++i) lo[i] = cur.k[i];
+            codes_to_floats<2, NW2>(lo, kv);
+        }
+        const float two_mid = hi ? 15.f : 3.f;
+        if (!kExact) unpack_params(cur.kp[0], scale, zero);
+        uintx4 kf[NK];
+#pragma unroll
+        for (int cc = 0; cc < NK; ++cc) {
+            RawChunk<T, E16> raw;
+#pragma unroll
+            for (int e = 0; e < E16; ++e) raw.v[e] = to_out<T>(kExact ? fmaf(2.f, kv[cc * E16 + e], -two_mid) : fmaf(scale, kv[cc * E16 + e], zero));
+            kf[cc] = __builtin_bit_cast(uintx4, raw);
+        }
+        floatx4 s = products(kf);
+        if (kExact) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                unpack_params(cur.kp[r % NP], scale, zero);
+                s[r] = fmaf(0.5f * scale, s[r], fmaf(0.5f * scale, two_mid, zero) * qsum);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            unpack_params(cur.vp[r], scale, zero);
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) vf[r][e] = fmaf(scale, (float)(hi ? (cur.v[r] >> (4 * e)) & 15u : (cur.v[r] >> (2 * e)) & 3u), zero);
+        }
+        attend(s, vf, hi ? L4 - t * kDecTile : L2 - (t - T4) * kDecTile);
+        cur = nxt;
+    }
+    for (; t < t_end; t += kDecWaves<GT>) {                              // rows appended during decoding, as stored
+        const int t0 = (t - T4 - T2) * kDecTile;
+        const T* kp = Kt + ((int64_t)u * cap_t + min(t0 + j, Lt - 1)) * D + kk * QE;
+        uintx4 kf[NK];
+#pragma unroll
+        for (int cc = 0; cc < NK; ++cc) kf[cc] = load16(kp + cc * E16);
+        float vf[4][EPL];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) RowChunk<T, EPL>::load(Vt + ((int64_t)u * cap_t + min(t0 + 4 * kk + r, Lt - 1)) * D + j * EPL, vf[r]);
+        attend(products(kf), vf, Lt - t0);
+    }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (j < heads) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) red[w][j][EPL * (4 * kk + r) + e] = o[e][r];
+        if (kk == 0) { red[w][j][D] = m; red[w][j][D + 1] = l; }
+    }
+    __syncthreads();
+    combine_waves<D, GT, kDecWaves<GT>>(red, heads, PartialOut(part, D, u, G, nsplit, gridDim.y), gbase, split);
+}
+
+// ---- the same, for one head per group: 4 lanes per row.
+// A 4-bit row of d = 128 is 64 bytes: with 16 lanes per row a lane would hold 4 bytes and the per-row work
+// (cross-lane sums, softmax update) would dominate.  Here a lane holds d/4 consecutive elements (16 bytes of 4-bit
+// codes, 8 bytes of 2-bit codes), a wave covers 16 rows per step, and the arithmetic runs on the codes:
+//   q . (zero + scale * code) = zero * sum(q) + scale * (q . code),
+//   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j zero_j + sum_j (p_j scale_j) code_j,
+// i.e. one FMA and 0.6 instructions of unpacking per element and side (MixCodes; 1.25 to 1.5 with conversions to fp32:
+// 174 us instead of 160 for four layers of 128 units x 8192 rows).  The softmax offset follows the running maximum lazily
+// (moves only when exceeded by 2^kDecLazyLog2), so the accumulators are rescaled on few rows.
+
+// sum over the 4 lanes of a quad (lanes 4i .. 4i+3), result in all four, by two in-register lane permutes
+__device__ __forceinline__ float quad_sum(float v) {
+    int x = __float_as_int(v);
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+    x = __float_as_int(v);
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+    return v;
+}
+
+// Codes as fp16 numbers without a conversion: a masked field of a word is, in either half, the subnormal
+// code * 2^(shift - 24), which v_fma_mix_f32 multiplies as it is; the other factor makes up for the powers of two, exactly.
+// Pair k of a word: elements k and k + PER / 2 in its low and high half.
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+template <int BITS> struct MixCodes {
+    static constexpr int PER = 32 / BITS, PAIRS = PER / 2;
+    static constexpr int FIT = 10 / BITS;                                // fields that lie inside the ten mantissa bits
+    static constexpr int MOVE = BITS == 4 ? 8 : FIT * BITS;              // the others are shifted down by this
+    static constexpr int KEPT = MOVE / BITS;                             // pairs taken before the shift
+    __host__ __device__ static constexpr int shift(int k) { return BITS * (k % KEPT); }
+    __device__ static __forceinline__ halfx2 pair(uint32_t w, int k) {
+        const uint32_t x = k < KEPT ? w : w >> MOVE;
+        return __builtin_bit_cast(halfx2, x & ((uint32_t)((1u << BITS) - 1u) * 0x00010001u << shift(k)));
+    }
+    __host__ __device__ static constexpr float field(int e) { return (float)(1u << shift(e % PAIRS)); }   // of element e of a word
+};
+static_assert(MixCodes<4>::PAIRS <= 2 * MixCodes<4>::KEPT && MixCodes<2>::PAIRS <= 2 * MixCodes<2>::KEPT, "one shift reaches every field");
+
 template <typename T, int D, int GT>
 __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
     const T* __restrict__ q, QTensor Kq, QTensor Vq, const int32_t* __restrict__ len_hi, const int32_t* __restrict__ len_lo,
@@ -691,15 +790,11 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
 #pragma unroll
         for (int e = 0; e < EPL; ++e) o[t][e] = 0.f;
     }
-    // one cached row: kd[t] = q_t . (this lane's K codes), score = kz * qsum + ks * sum over lanes of kd; then
-    // o += (p * vs) * (V codes), zacc += p * vz
-    auto attend = [&](bool valid, const float (&kc)[EPL], float ks, float kz, const float (&vc)[EPL], float vs, float vz) {
+    // one cached row: dsum[t] = q_t . (this lane's part of the K row); then o += (p * vs) (V codes), zacc += p * vz
+    auto attend = [&](bool valid, auto&& dot, float ks, float kz, auto&& axpy, float vs, float vz) {
 #pragma unroll
         for (int t = 0; t < GT; ++t) {
-            float dsum = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) dsum = fmaf(qv[t][e], kc[e], dsum);
-            dsum = quad_sum(dsum);
+            const float dsum = quad_sum(dot(qv[t]));
             const float sc = valid ? fmaf(ks, dsum, kz * qsum[t]) : -INFINITY;
             const bool grow = sc > m[t] + kDecLazyLog2;
             if (__any(grow)) {
@@ -713,15 +808,51 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
             const float p = valid ? fast_exp2(sc - m[t]) : 0.f;
             l[t] += p;
             zacc[t] = fmaf(p, vz, zacc[t]);
-            const float pv = p * vs;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) o[t][e] = fmaf(pv, vc[e], o[t][e]);
+            axpy(p * vs, o[t]);
         }
     };
-    auto unpack_params = [](uint32_t v, float& scale, float& zero) {
-        scale = (float)__builtin_bit_cast(_Float16, (uint16_t)(v & 0xFFFFu));
-        zero = (float)__builtin_bit_cast(_Float16, (uint16_t)(v >> 16));
+    // a row's codes (BITS wide, NW words per lane): dot with the queries, whose elements carry 1 / MixCodes::field, and
+    // weighted sum into the outputs
+    auto attend_codes = [&](auto bits, bool valid, const auto& kw, float ks, float kz, const auto& vw, float vs, float vz) {
+        using M = MixCodes<decltype(bits)::value>;
+        constexpr int NW = EPL / M::PER;
+        attend(valid, [&](const float (&qt)[EPL]) {
+            float d = 0.f;
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int k = 0; k < M::PAIRS; ++k) {
+                    const halfx2 x = M::pair(kw[i], k);
+                    d = fmaf(qt[i * M::PER + k], (float)x[0], d);
+                    d = fmaf(qt[i * M::PER + M::PAIRS + k], (float)x[1], d);
+                }
+            return d;
+        }, ks * 0x1p24f, kz, [&](float pv, float (&ot)[EPL]) {
+            float pk[M::KEPT];                                           // pv * 2^(24 - shift)
+#pragma unroll
+            for (int k = 0; k < M::KEPT; ++k) pk[k] = pv * (0x1p24f / M::field(k));
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int k = 0; k < M::PAIRS; ++k) {
+                    const halfx2 x = M::pair(vw[i], k);
+                    float& a0 = ot[i * M::PER + k];
+                    float& a1 = ot[i * M::PER + M::PAIRS + k];
+                    a0 = fmaf(pk[k % M::KEPT], (float)x[0], a0);
+                    a1 = fmaf(pk[k % M::KEPT], (float)x[1], a1);
+                }
+        }, vs, vz);
     };
+    // the queries' elements carry the factor of the codes they meet: powers of two, exact
+    auto rescale_queries = [&](auto&& factor) {
+#pragma unroll
+        for (int t = 0; t < GT; ++t)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) qv[t][e] *= factor(e);
+    };
+    using Four = std::integral_constant<int, 4>;
+    using Two = std::integral_constant<int, 2>;
+    rescale_queries([](int e) { return 1.f / MixCodes<4>::field(e % 8); });
     int r_begin, r_end;
     {   // important tokens, 4 bits
         constexpr int NW = EPL * 4 / 32;
@@ -744,12 +875,10 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
             uint32_t kw2[NW], vw2[NW], kp2 = 0, vp2 = 0;
             const bool more = r + 64 - rg - w * 16 < r_end;
             if (more) fetch(r + 64, kw2, vw2, kp2, vp2);
-            float ks, kz, vs, vz, kc[EPL], vc[EPL];
+            float ks, kz, vs, vz;
             unpack_params(kp, ks, kz);
             unpack_params(vp, vs, vz);
-            codes_to_floats<4, NW>(kw, kc);
-            codes_to_floats<4, NW>(vw, vc);
-            attend(valid, kc, ks, kz, vc, vs, vz);
+            attend_codes(Four(), valid, kw, ks, kz, vw, vs, vz);
             if (more) {
 #pragma unroll
                 for (int i = 0; i < NW; ++i) { kw[i] = kw2[i]; vw[i] = vw2[i]; }
@@ -757,6 +886,7 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
             }
         }
     }
+    rescale_queries([](int e) { return MixCodes<4>::field(e % 8) / MixCodes<2>::field(e % 16); });
     {   // the other tokens, 2 bits
         constexpr int NW = EPL * 2 / 32;
         const int L = max(0, min(len_lo[u], cap_lo));
@@ -778,12 +908,10 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
             uint32_t kw2[NW], vw2[NW], kp2 = 0, vp2 = 0;
             const bool more = r + 64 - rg - w * 16 < r_end;
             if (more) fetch(r + 64, kw2, vw2, kp2, vp2);
-            float ks, kz, vs, vz, kc[EPL], vc[EPL];
+            float ks, kz, vs, vz;
             unpack_params(kp, ks, kz);
             unpack_params(vp, vs, vz);
-            codes_to_floats<2, NW>(kw, kc);
-            codes_to_floats<2, NW>(vw, vc);
-            attend(valid, kc, ks, kz, vc, vs, vz);
+            attend_codes(Two(), valid, kw, ks, kz, vw, vs, vz);
             if (more) {
 #pragma unroll
                 for (int i = 0; i < NW; ++i) { kw[i] = kw2[i]; vw[i] = vw2[i]; }
@@ -791,6 +919,7 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
             }
         }
     }
+    rescale_queries([](int e) { return MixCodes<2>::field(e % 16); });
     if (Kt) {   // rows appended during decoding, as stored: "codes" are the values, scale 1, zero 0
         const int L = max(0, min(len_t[u], cap_t));
         split_range64(L, split, nsplit, r_begin, r_end);
@@ -810,7 +939,15 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
 #pragma unroll
                 for (int e = 0; e < 8; ++e) vc[8 * e8 + e] = f[e];
             }
-            attend(valid, kc, 1.f, 0.f, vc, 1.f, 0.f);
+            attend(valid, [&](const float (&qt)[EPL]) {
+                float d = 0.f;
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) d = fmaf(qt[e], kc[e], d);
+                return d;
+            }, 1.f, 0.f, [&](float pv, float (&ot)[EPL]) {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) ot[e] = fmaf(pv, vc[e], ot[e]);
+            }, 1.f, 0.f);
         }
     }
     // fold the zero-point sums into the outputs, merge the 16 row groups of the wave, then the 4 waves
@@ -895,29 +1032,20 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
                              const int32_t* len_lo, int32_t cap_hi, int32_t cap_lo, const void* Kt, const void* Vt,
                              const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
-    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, nsplit = decode_splits(d, cap_hi + cap_lo + cap_t);
+    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, cap = cap_hi + cap_lo + cap_t;
+    const int nsplit = G > 1 ? attend_splits(d, cap) : decode_splits(d, cap);
     const float c = scale * kLog2e;
-    dim3 grid(nsplit, units);
     const QTensor kq{(const uint8_t*)Kq.hi_codes, (const uint32_t*)Kq.hi_params, (const uint8_t*)Kq.lo_codes, (const uint32_t*)Kq.lo_params};
     const QTensor vq{(const uint8_t*)Vq.hi_codes, (const uint32_t*)Vq.hi_params, (const uint8_t*)Vq.lo_codes, (const uint32_t*)Vq.lo_params};
-#define ZIPVL_DECQ(GT, GB)                                                                           \
-    hipLaunchKernelGGL((decode_q_partial_kernel<T, D, GT>), grid, dim3(256), 0, st, (const T*)q, kq, vq, \
-        len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t, d.Hq, d.Hkv, GB, c, (float*)ws, nsplit)
+#define ZIPVL_DECQ(KERNEL, GT, THREADS)                                                              \
+    hipLaunchKernelGGL((KERNEL<T, D, GT>), dim3(nsplit, units), dim3(THREADS), 0, st, (const T*)q, kq, vq, \
+        len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t, d.Hq, d.Hkv, gb, c, (float*)ws, nsplit)
     for (int gb = 0; gb < G; gb += 8) {
-        const int rem = G - gb;
         KernelTimer tm(ZIPVL_K_DECODE_Q_PARTIAL, st);
-        if (G <= 2) {
-            if (rem == 2)
-                hipLaunchKernelGGL((decode_q4_partial_kernel<T, D, 2>), grid, dim3(256), 0, st, (const T*)q, kq, vq,
-                    len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t, d.Hq, d.Hkv, gb, c, (float*)ws, nsplit);
-            else
-                hipLaunchKernelGGL((decode_q4_partial_kernel<T, D, 1>), grid, dim3(256), 0, st, (const T*)q, kq, vq,
-                    len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t, d.Hq, d.Hkv, gb, c, (float*)ws, nsplit);
-        }
-        else if (rem >= 5) ZIPVL_DECQ(8, gb);
-        else if (rem >= 3) ZIPVL_DECQ(4, gb);
-        else if (rem == 2) ZIPVL_DECQ(2, gb);
-        else ZIPVL_DECQ(1, gb);
+        // one head: the vector units, as over a cache as stored (four layers of 128 units x 8192 rows 160 us, 440 on the matrix
+        // cores); two and more: the matrix cores (two heads, 32 units x 4000: 122 -> 100 us)
+        if (G > 1) ZIPVL_DECQ(decode_q_partial_kernel, 8, 64 * kDecWaves<8>);
+        else ZIPVL_DECQ(decode_q4_partial_kernel, 1, 256);
         int rc = check_launch("decode_q_partial");
         if (rc) return rc;
     }

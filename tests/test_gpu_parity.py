@@ -750,6 +750,40 @@ def test_decode_over_quantised_cache_for_every_group_size(Hq, Hkv):
     assert worst <= 2e-2
 
 
+@pytest.mark.parametrize("dtype,d,G", [("bf16", 128, 1), ("f32", 64, 1), ("bf16", 128, 7), ("bf16", 64, 2), ("f32", 128, 4), ("f32", 64, 8)])
+def test_decode_over_quantised_cache_at_tile_edges(dtype, d, G):
+    """Part lengths (4-bit, 2-bit, appended) on both sides of the 16-row tiles, each part empty once; NaN in the appended rows
+    that do not exist yet.  fp32: the oracle's dequantised rows are exact, the sums are not: 5e-5 of outputs of order one."""
+    say(f"decode_attn_q tile edges dtype={dtype} d={d} G={G}")
+    n, cap_t = 530, 40
+    kept = [0, 1, 15, 16, 17, 33, 256, 514, 529, 530]
+    tail = [0, 1, 15, 16, 17, 40, 0, 33, 1, 0]
+    units = len(kept)
+    w = make_custom(1, units * G, units, n, d, dtype, seed=67)
+    r = np.random.Generator(np.random.PCG64(68))
+    idx = np.zeros((units, n), dtype=np.int32)
+    for u, k in enumerate(kept):
+        idx[u, :k] = np.sort(r.choice(n, k, replace=False))
+    cache = z.zipvl_quantize_kv(dev(w.K, dtype), dev(w.V, dtype), torch.from_numpy(idx).to(DEV),
+                                torch.tensor(kept, dtype=torch.int32, device=DEV), n, n)
+    q = dev(r.standard_normal((units * G, d)).astype(np.float32), dtype)
+    Kt, Vt = (dev(r.standard_normal((units, cap_t, d)).astype(np.float32), dtype) for _ in range(2))
+    for u, t in enumerate(tail):
+        Kt[u, t:] = float("nan")
+        Vt[u, t:] = float("nan")
+    o = z.zipvl_decode_attn_q(q, cache, w.scale, B=1, Hq=units * G, Hkv=units, K_tail=Kt, V_tail=Vt,
+                              len_tail=torch.tensor(tail, dtype=torch.int32, device=DEV))
+    torch.cuda.synchronize()
+    worst = 0.0
+    for u, (k, t) in enumerate(zip(kept, tail)):
+        qc = oz.quantize_kv(w.K[0, u], w.V[0, u], idx[u, :k])
+        for h in range(u * G, u * G + G):
+            ref = oz.decode_attention_quantized(host64(q[h]), qc, w.scale, host64(Kt[u, :t]), host64(Vt[u, :t]))
+            worst = max(worst, np.abs(host64(o[h]) - ref).max())
+    say(f"  worst |do| = {worst:.3e}")
+    assert worst <= (2e-2 if dtype == "bf16" else 5e-5)
+
+
 def test_quantize_kv_with_one_set_per_batch_element_and_without_T():
     say("quantize_kv T_PER_BATCH / idx=NULL")
     B, Hq, Hkv, n, d, dtype = 2, 4, 4, 1000, 128, "bf16"
