@@ -140,18 +140,13 @@ __device__ void radix_descent(const Keys& keys, double tau, uint32_t cnt_target,
                 }
                 lc += c[t]; ls += s[t];
             }
-            uint32_t ic = lc;
-            unsigned long long is = ls;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t tc = __shfl_up(ic, o);
-                const unsigned long long ts = WITH_SUM ? __shfl_up(is, o) : 0ull;
-                if (tid >= o) { ic += tc; is += ts; }
-            }
+            const uint32_t ic = wave_scan(lc);
+            const unsigned long long is = WITH_SUM ? wave_scan(ls) : 0ull;
             unsigned long long target;
             if (WITH_SUM) {
                 if (pass == 0) {
-                    const unsigned long long W = __shfl(is, 63);
+                    const unsigned long long W = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(is >> 32), 63) << 32) |
+                                                 (uint32_t)__builtin_amdgcn_readlane((int)is, 63);
                     // ceil(tau * W): one IEEE double multiply, then ceil (W < 2^53)
                     const double prod = tau * (double)W;
                     target = (unsigned long long)ceil(prod);
@@ -303,12 +298,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
             }
         }
         const uint32_t cg = __popc(gm), ce = __popc(em);
-        uint32_t ig = cg, ie = ce;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t tg = __shfl_up(ig, o), te = __shfl_up(ie, o);
-            if (lane >= o) { ig += tg; ie += te; }
-        }
+        const uint32_t both = wave_scan(cg | ce << 16);    // at most 64 * 32 each
+        const uint32_t ig = both & 0xFFFFu, ie = both >> 16;
         if (lane == 63) { sh.wave_cnt[wave] = ig; sh.wave_eq[wave] = ie; }
         __syncthreads();
         uint32_t gt_before = gt_run + (ig - cg), eq_before = eq_run + (ie - ce), tot_g = 0, tot_e = 0;

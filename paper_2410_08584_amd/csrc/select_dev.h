@@ -20,6 +20,29 @@ constexpr int kSelBinShift = 19;
 constexpr int kSelMaxCand = 2048;           // elements of one bin that are gathered into a list
 constexpr int kSumBits = 41;                // a packed slot: count << 41 | integer score sum (sum of a unit < 2^41)
 
+// Inclusive sum over the wave's lanes 0 .. this one, by lane permutes inside the register file: four shifts inside rows of
+// 16 lanes, then row 0's total to row 1 (and 2's to 3), then lane 31's to the upper half.  Six dependent steps of a few
+// clocks each; a shuffle through LDS takes some 100 clocks a step and a selection unit runs about nine scans one after
+// the other.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t lanes_moved(uint32_t v) {            // 0 in lanes that receive nothing
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long lanes_moved(unsigned long long v) {
+    return ((unsigned long long)lanes_moved<CTRL, ROWS>((uint32_t)(v >> 32)) << 32) | lanes_moved<CTRL, ROWS>((uint32_t)v);
+}
+template <typename U>
+__device__ __forceinline__ U wave_scan(U v) {
+    v += lanes_moved<0x111, 0xF>(v);
+    v += lanes_moved<0x112, 0xF>(v);
+    v += lanes_moved<0x114, 0xF>(v);
+    v += lanes_moved<0x118, 0xF>(v);
+    v += lanes_moved<0x142, 0xA>(v);
+    v += lanes_moved<0x143, 0xC>(v);
+    return v;
+}
+
 // Order-preserving 31-bit key of a non-negative fp32 score: its bit pattern.  Scores are >= 0 by
 // contract; anything with the sign bit set (-0 included) is ordered and summed as zero.
 __device__ __forceinline__ uint32_t orderable(float x) {
@@ -71,14 +94,8 @@ template <int NTH>
 __device__ __forceinline__ void block_scan(uint32_t lc, unsigned long long ls, TailShared& sh,
                                            uint32_t& ec, unsigned long long& es, uint32_t& tc, unsigned long long& ts) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t ic = lc;
-    unsigned long long is = ls;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t c2 = __shfl_up(ic, o);
-        const unsigned long long s2 = __shfl_up(is, o);
-        if (lane >= o) { ic += c2; is += s2; }
-    }
+    const uint32_t ic = wave_scan(lc);
+    const unsigned long long is = wave_scan(ls);
     if (lane == 63) { sh.wcnt[wave] = ic; sh.wsum[wave] = is; }
     __syncthreads();
     ec = ic - lc; es = is - ls; tc = 0; ts = 0;
@@ -228,14 +245,8 @@ __device__ void descend_low(const Src& src, unsigned long long target, TailShare
                 s[t] = WITH_SUM ? (v & ((1ull << kSumBits) - 1ull)) : 0ull;
                 lc += c[t]; ls += s[t];
             }
-            uint32_t ic = lc;
-            unsigned long long is = ls;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t c2 = __shfl_up(ic, o);
-                const unsigned long long s2 = __shfl_up(is, o);
-                if (tid >= o) { ic += c2; is += s2; }
-            }
+            const uint32_t ic = wave_scan(lc);
+            const unsigned long long is = wave_scan(ls);
             uint32_t rc = base_cnt + (ic - lc);
             unsigned long long rs = base_sum + (is - ls);
 #pragma unroll
@@ -318,12 +329,8 @@ __device__ void emit_block(const uint32_t* lds_keys, int b0, int bn, uint32_t vs
         }
     }
     const uint32_t cg = __popc(gm), ce = __popc(em);
-    uint32_t ig = cg, ie = ce;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t tg = __shfl_up(ig, o), te = __shfl_up(ie, o);
-        if (lane >= o) { ig += tg; ie += te; }
-    }
+    const uint32_t both = wave_scan(cg | ce << 16);    // at most 64 * 32 each
+    const uint32_t ig = both & 0xFFFFu, ie = both >> 16;
     if (lane == 63) { sh.wave_cnt[wave] = ig; sh.wave_eq[wave] = ie; }
     __syncthreads();
     uint32_t gt_before = gt_run + (ig - cg), eq_before = eq_run + (ie - ce), tot_g = 0, tot_e = 0;
