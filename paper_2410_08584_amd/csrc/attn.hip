@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
     const T* __restrict__ K, const T* __restrict__ V,
     int64_t ks0, int64_t ks1, int64_t ks2, int64_t vs0, int64_t vs1, int64_t vs2,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
-    T* __restrict__ Kp, T* __restrict__ Vp, int n, int npad, int Hkv, int rows_are_kept, int skip_k, int t_per_batch)
+    T* __restrict__ Kp, T* __restrict__ Vp, int n, int npad, int Hkv, int rows_are_kept, int skip_k, int t_per_batch, int tile0)
 {
     constexpr int EPF = Elem<T>::kPerFrag;
     constexpr int CPR = D / EPF;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
     constexpr bool VROWS = Elem<T>::kBytes == 2;
     __shared__ __attribute__((aligned(16))) T tile[VROWS ? EPF : kBN * LS];
     const int u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
-    const int t0 = blockIdx.x * kBN;
+    const int t0 = (tile0 + (int)blockIdx.x) * kBN;       // packed row r of the unit is row tile0 * kBN + r
     const int ut = t_per_batch ? b : u;                   // row of idx / k that holds this unit's T
     int kk = kcnt ? kcnt[ut] : n;
     kk = max(0, min(kk, n));
@@ -109,8 +109,9 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
             if (!skip_k) kv = load16(Kb + (int64_t)src * ks2 + cc * EPF);
             vv = load16(Vb + (int64_t)src * vs2 + cc * EPF);
         }
-        if (!skip_k) store16(Kp + ((int64_t)u * npad + row) * D + cc * EPF, kv);
-        if (VROWS) store16(Vp + ((int64_t)u * npad + row) * D + cc * EPF, vv);      // rows past k are zero rows
+        const int64_t out = ((int64_t)u * npad + row - tile0 * kBN) * D + cc * EPF;
+        if (!skip_k) store16(Kp + out, kv);
+        if (VROWS) store16(Vp + out, vv);      // rows past k are zero rows
         else store16(tile + r * LS + cc * EPF, vv);
     }
     if (VROWS) return;
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     const T* __restrict__ Kp, int64_t kp0, int64_t kp1, const T* __restrict__ Vp, int64_t vp0, int64_t vp1,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
     T* __restrict__ O, int n, int npad, int ntq, int ug, int BH, int Hq, int Hkv, float c, int out_compact, int compute_blocks,
-    int t_per_batch, int v_in_place)
+    int t_per_batch, int v_in_place, const T* __restrict__ Kl, const T* __restrict__ Vl, int whole_tiles)
 {
     using C = AttnCfg<T, D, NW, QB>;
     constexpr int kBM = C::BM, kNT = C::NT, kRW = 32 * QB;   // queries per workgroup, threads, queries per wave
@@ -351,6 +352,11 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     const int my_tiles = min(ntiles, wave_last_row / kBN + 1);   // later tiles lie wholly in this wave's future
     const char* kg = reinterpret_cast<const char*>(Kp + b * kp0 + g * kp1);   // row-major kept K rows of this unit
     const char* vg = reinterpret_cast<const char*>(Vp + b * vp0 + g * vp1);   // V tiles of this unit (V^T tiles for fp32)
+    // Tiles from whole_tiles on (the ragged last one of a cache that is read in place) lie in the workspace.  All scalar.
+    const int64_t last_tile = (int64_t)(b * Hkv + g) * C::TILE_BYTES;
+    const int64_t klast = reinterpret_cast<const char*>(Kl) + last_tile - kg, vlast = reinterpret_cast<const char*>(Vl) + last_tile - vg;
+    auto ktile = [&](int t) { return kg + (t < whole_tiles ? (int64_t)t * C::TILE_BYTES : klast); };
+    auto vtile = [&](int t) { return vg + (t < whole_tiles ? (int64_t)t * C::TILE_BYTES : vlast); };
     char* const Kb0 = smem;
     char* const Vb0 = smem + 2 * C::TILE_BYTES;
     const int sw = k_row_swizzle<C::KRB>(i);
@@ -364,9 +370,9 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     // The first tiles are requested before anything else is loaded: their addresses need only scalars, while the
     // query rows below wait for their positions first (two round trips).
     auto request_first_tiles = [&]() {
-        tile_to_lds<C::KRB, NW, C::NLD>(kg, Kb0, w, koff);
-        tile_to_lds<C::VRB, NW, C::NLD>(vg, Vb0, w, voff);
-        if (ntiles > 1) tile_to_lds<C::KRB, NW, C::NLD>(kg + C::TILE_BYTES, Kb0 + C::TILE_BYTES, w, koff);
+        tile_to_lds<C::KRB, NW, C::NLD>(ktile(0), Kb0, w, koff);
+        tile_to_lds<C::VRB, NW, C::NLD>(vtile(0), Vb0, w, voff);
+        if (ntiles > 1) tile_to_lds<C::KRB, NW, C::NLD>(ktile(1), Kb0 + C::TILE_BYTES, w, koff);
     };
     request_first_tiles();
     // kept-token coordinates of this lane's QB queries, their positions, their Q fragments
@@ -489,8 +495,8 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         // one tile t-1 leaves at the middle barrier (second half).  In the steady state they are issued one
         // at a time, each tied to one exponential (a burst of them stalls every wave of the workgroup at the
         // address unit); elsewhere in one go.  Past the last tile the last tile is fetched again, unread.
-        const char* kgt = kg + (int64_t)min(t + 2, ntiles - 1) * C::TILE_BYTES;
-        const char* vgt = vg + (int64_t)min(t + 1, ntiles - 1) * C::TILE_BYTES;
+        const char* kgt = ktile(min(t + 2, ntiles - 1));
+        const char* vgt = vtile(min(t + 1, ntiles - 1));
         const unsigned kl = klds + (t & 1) * C::TILE_BYTES, vl = vlds + ((t + 1) & 1) * C::TILE_BYTES;
         auto fetch_k = [&]() {
 #pragma unroll
@@ -700,7 +706,7 @@ size_t prefill_workspace_bytes(const zipvl_dims& d) {
 
 template <typename T, int D, int NW, int QB>
 static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
-                        float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, void* O, hipStream_t st)
+                        float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, int whole_tiles, void* O, hipStream_t st)
 {
     using C = AttnCfg<T, D, NW, QB>;
     static std::atomic<bool> attr_done{false};       // raising the dynamic-LDS cap is idempotent
@@ -731,7 +737,7 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
             skip_k ? d.k_strides[1] : (int64_t)npad * D,
             skip_v ? (const T*)V : Vp, skip_v ? d.v_strides[0] : (int64_t)d.Hkv * npad * D,
             skip_v ? d.v_strides[1] : (int64_t)npad * D, idx, k, (T*)O, d.n, npad, ntq, ug, BH, d.Hq, d.Hkv,
-            scale * kLog2e, out_compact, (int)blocks, t_per_batch, skip_v);
+            scale * kLog2e, out_compact, (int)blocks, t_per_batch, skip_v, Kp, Vp, whole_tiles);
     }
     return check_launch("flash_kept");
 }
@@ -749,25 +755,31 @@ static int launch_prefill_t(const void* Q, const void* K, const void* V, const z
     const int rows_are_kept = (flags & ZIPVL_KV_ALREADY_COMPACT) ? 1 : 0;
     const int t_per_batch = (flags & ZIPVL_T_PER_BATCH) ? 1 : 0;
 
-    // An evicted cache with contiguous rows and whole 64-row tiles is read in place (K always, V when the
-    // transposing LDS read applies: then nothing is packed).  Rows between k and the end of the last tile
-    // may hold anything: K rows there are masked, V rows there are cleared once they are in LDS.
-    const int in_place = (rows_are_kept && d.n % kBN == 0) ? 1 : 0;
-    const int skip_k = (in_place && d.k_strides[2] == D) ? 1 : 0;
-    const int skip_v = (in_place && Elem<T>::kBytes == 2 && d.v_strides[2] == D) ? 1 : 0;
-    if (!(skip_k && skip_v)) {
+    // An evicted cache with contiguous rows is read in place (K always, V when the transposing LDS read applies), but for
+    // a last tile that the n rows do not fill: that one is packed (it holds kept rows only when nearly all are kept), and
+    // only where both tensors are read in place.  32 heads, n = 2933: packing all of it took 8.5 us of 64.
+    // Rows between k and the end of the last tile may hold anything: K rows there are masked, V rows there are cleared
+    // once they are in LDS.
+    const bool k_rows = rows_are_kept && d.k_strides[2] == D, v_rows = rows_are_kept && Elem<T>::kBytes == 2 && d.v_strides[2] == D;
+    const bool whole = d.n % kBN == 0;
+    const int skip_k = (k_rows && (whole || v_rows)) ? 1 : 0, skip_v = (v_rows && (whole || k_rows)) ? 1 : 0;
+    const bool tail_only = skip_k && skip_v && !whole;
+    const int whole_tiles = tail_only ? d.n / kBN : npad / kBN;
+    if (tail_only) VTp = Kp + (size_t)units * kBN * D;
+    if (!(skip_k && skip_v) || tail_only) {
         KernelTimer tm(ZIPVL_K_PACK_KV, st);
-        hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(npad / kBN, units), dim3(256), 0, st,
+        hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(tail_only ? 1 : npad / kBN, units), dim3(256), 0, st,
             (const T*)K, (const T*)V, d.k_strides[0], d.k_strides[1], d.k_strides[2],
-            d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, Kp, VTp, d.n, npad, d.Hkv, rows_are_kept, skip_k, t_per_batch);
+            d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, Kp, VTp, d.n, tail_only ? kBN : npad, d.Hkv, rows_are_kept,
+            tail_only ? 0 : skip_k, t_per_batch, tail_only ? whole_tiles : 0);
         int rc = check_launch("pack_kv");
         if (rc) return rc;
     }
 
     if constexpr (Elem<T>::kBytes == 2)
-        return launch_flash<T, D, kFlashWavesBf16, kFlashBlocksBf16>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, O, st);
+        return launch_flash<T, D, kFlashWavesBf16, kFlashBlocksBf16>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, whole_tiles, O, st);
     else
-        return launch_flash<T, D, 4, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, O, st);
+        return launch_flash<T, D, 4, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, whole_tiles, O, st);
 }
 
 int launch_sparse_prefill(const void* Q, const void* K, const void* V, const zipvl_dims& d,

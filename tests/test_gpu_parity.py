@@ -352,9 +352,34 @@ def test_attention_compact_output_rows():
     _attention_case(1, 4, 2, 500, 128, "bf16", [333, 128], seed=7, flags=z.OUT_COMPACT)
 
 
+@pytest.mark.parametrize("n,d,ks", [(40, 128, [40, 39]), (65, 128, [65, 64]), (129, 64, [129, 1]), (333, 128, [333, 320]), (333, 128, [321, 319]),
+                                    (447, 64, [447, 446])])
+def test_attention_reads_a_ragged_cache_up_to_its_last_row(n, d, ks):
+    """Evicted caches whose last 64-row tile is not full, with kept counts in and next to that tile: everything before it
+    is read in place, NaN beyond k.  Bit for bit the attention that gathers from the whole K, V."""
+    say(f"attention KV_ALREADY_COMPACT ragged n={n} d={d} k={ks}")
+    B, Hq, Hkv, dtype = 1, 4, 2, "bf16"
+    w = make_custom(B, Hq, Hkv, n, d, dtype, seed=10, m=min(64, n))
+    Q, K, V = dev(w.Q, dtype), dev(w.K, dtype), dev(w.V, dtype)
+    r = np.random.Generator(np.random.PCG64(11))
+    idx = np.zeros((2, n), dtype=np.int32)
+    for u in range(2):
+        idx[u, :ks[u]] = np.sort(r.choice(n, ks[u], replace=False))
+    idx_d, k_d = torch.from_numpy(idx).to(DEV), torch.tensor(ks, dtype=torch.int32, device=DEV)
+    Kc = torch.full((2, n, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    Vc = torch.full((2, n, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+    z.zipvl_compact_kv(K, V, idx_d, k_d, n, Kc=Kc, Vc=Vc)
+    for flags in (z.OUT_FULL, z.OUT_COMPACT):
+        O1, O2 = torch.zeros_like(Q), torch.zeros_like(Q)
+        z.zipvl_sparse_prefill(Q, K, V, idx_d, k_d, w.scale, flags, O=O1)
+        z.zipvl_sparse_prefill(Q, Kc.view(B, Hkv, n, d), Vc.view(B, Hkv, n, d), idx_d, k_d, w.scale, flags | z.KV_ALREADY_COMPACT, O=O2)
+        torch.cuda.synchronize()
+        assert torch.equal(O1, O2) and not torch.isnan(O2.float()).any()
+
+
 @pytest.mark.parametrize("n,gain", [(400, 1.0), (448, 1.0), (448, 40.0)])
 def test_attention_on_already_compacted_cache(n, gain):
-    # n = 448 (whole 64-row tiles, contiguous rows) reads the evicted K cache in place; n = 400 repacks it;
+    # n = 448 (whole 64-row tiles, contiguous rows) reads the evicted cache in place; n = 400 packs its last tile;
     # gain 40: logits far outside the range the offset-free pass accepts, so every workgroup repeats its keys
     say(f"attention KV_ALREADY_COMPACT n={n} gain={gain}")
     B, Hq, Hkv, d, dtype = 1, 4, 2, 128, "bf16"
