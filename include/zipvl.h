@@ -176,6 +176,8 @@ int zipvl_share_scores(const float* mass, const float* rank, int B, int Hkv, int
  * T must hold strictly ascending positions in [0, n) (not checked: the values live on the device).
  * flags: ZIPVL_OUT_FULL (default) | ZIPVL_OUT_COMPACT | ZIPVL_KV_ALREADY_COMPACT | ZIPVL_T_PER_BATCH
  * (with ZIPVL_T_PER_BATCH, T of unit u is idx[b, 0..k[b]-1]).
+ * With ZIPVL_KV_ALREADY_COMPACT no row of K, V at or beyond k[u] is read: a cache of zipvl_compact_kv with cap = max k
+ * is enough (dims->n is still the number of tokens; the K, V strides say where the units' rows are).
  * O [device] [B,Hq,n,d] contiguous, dtype as the inputs.
  * ws [device] zipvl_workspace_bytes(ZIPVL_OP_SPARSE_PREFILL, dims, 0) bytes, 256-byte aligned.
  * Numerics: accumulation in fp32; probabilities of a bf16 call are rounded to bf16 before they weigh V and before

@@ -4,7 +4,7 @@
 // Two kernels:
 //   pack   gathers K[T] and V[T] into the workspace, once per KV head, zero-filling
 //          the ragged tail.  bf16: both row-major (the P.V operand is fetched from
-//          LDS with the transposing read, so an evicted cache with whole tiles is
+//          LDS with the transposing read, so an evicted cache with contiguous rows is
 //          read in place and nothing is packed at all); fp32: V[T] transposed
 //          ([d][64 keys] tiles), so that both MFMA operands are contiguous fragments.
 //   flash  one workgroup = 128 kept queries of one query head (4 waves x 32
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
     const T* __restrict__ K, const T* __restrict__ V,
     int64_t ks0, int64_t ks1, int64_t ks2, int64_t vs0, int64_t vs1, int64_t vs2,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
-    T* __restrict__ Kp, T* __restrict__ Vp, int n, int npad, int Hkv, int rows_are_kept, int skip_k, int t_per_batch, int tile0)
+    T* __restrict__ Kp, T* __restrict__ Vp, int n, int npad, int Hkv, int rows_are_kept, int skip_k, int t_per_batch)
 {
     constexpr int EPF = Elem<T>::kPerFrag;
     constexpr int CPR = D / EPF;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
     constexpr bool VROWS = Elem<T>::kBytes == 2;
     __shared__ __attribute__((aligned(16))) T tile[VROWS ? EPF : kBN * LS];
     const int u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
-    const int t0 = (tile0 + (int)blockIdx.x) * kBN;       // packed row r of the unit is row tile0 * kBN + r
+    const int t0 = blockIdx.x * kBN;
     const int ut = t_per_batch ? b : u;                   // row of idx / k that holds this unit's T
     int kk = kcnt ? kcnt[ut] : n;
     kk = max(0, min(kk, n));
@@ -109,9 +109,8 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
             if (!skip_k) kv = load16(Kb + (int64_t)src * ks2 + cc * EPF);
             vv = load16(Vb + (int64_t)src * vs2 + cc * EPF);
         }
-        const int64_t out = ((int64_t)u * npad + row - tile0 * kBN) * D + cc * EPF;
-        if (!skip_k) store16(Kp + out, kv);
-        if (VROWS) store16(Vp + out, vv);      // rows past k are zero rows
+        if (!skip_k) store16(Kp + ((int64_t)u * npad + row) * D + cc * EPF, kv);
+        if (VROWS) store16(Vp + ((int64_t)u * npad + row) * D + cc * EPF, vv);      // rows past k are zero rows
         else store16(tile + r * LS + cc * EPF, vv);
     }
     if (VROWS) return;
@@ -159,17 +158,31 @@ __device__ __forceinline__ void tile_load(const char* gtile, int q, const int (&
     if constexpr (kOffsetsRepeat<RB, NW>) load_kib_to_lds(gtile + q * NW * 1024, off[0], lds_dst);
     else load_kib_to_lds(gtile, off[q], lds_dst);
 }
+// the same for whole tiles, placed by data flow (load_kib_to_lds_pinned)
 template <int RB, int NW, int NLD>
 __device__ __forceinline__ void tile_load_pinned(const char* gtile, int q, const int (&off)[NLD], unsigned lds_dst, unsigned& pin) {
     if constexpr (kOffsetsRepeat<RB, NW>) load_kib_to_lds_pinned(gtile + q * NW * 1024, off[0], lds_dst, pin);
     else load_kib_to_lds_pinned(gtile, off[q], lds_dst, pin);
 }
 
-template <int RB, int NW, int NLD>
-__device__ __forceinline__ void tile_to_lds(const char* gtile, char* lbuf, int w, const int (&off)[NLD]) {
-    const unsigned lbase = lds_address(lbuf);
+// Only the first `rows` rows of the tile may be read: fewer than kBN happens once per head, at its last tile, and the
+// rows after them are then filled from the last one, chunk for chunk.  That form derives its offsets again from the
+// thread index, so that the key loop carries nothing for it.
+template <int RB, int NW, int NLD, bool VSWZ = false>
+__device__ __forceinline__ void tile_to_lds(const char* gtile, unsigned lds_dst, const int (&off)[NLD], int rows) {
+    if (rows >= kBN) {
 #pragma unroll
-    for (int q = 0; q < NLD; ++q) tile_load<RB, NW, NLD>(gtile, q, off, lbase + (q * NW + w) * 1024);
+        for (int q = 0; q < NLD; ++q) tile_load<RB, NW, NLD>(gtile, q, off, lds_dst + q * NW * 1024);
+    } else {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+#pragma unroll 1
+        for (int q = 0; q < NLD; ++q) {
+            const int o = q * NW * 1024 + tid * 16, r = o / RB, p = (o % RB) >> 4;
+            const int chunk = (p ^ (VSWZ ? v_row_swizzle<RB>(r) : k_row_swizzle<RB>(r))) << 4;
+            load_kib_to_lds(gtile, min(r, rows - 1) * RB + chunk, lds_dst + q * NW * 1024);
+        }
+    }
 }
 
 // S^T = K Q^T for 32 keys (block blk of the 64-key tile in LDS buffer kb) and the wave's QB query blocks:
@@ -286,7 +299,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     const T* __restrict__ Kp, int64_t kp0, int64_t kp1, const T* __restrict__ Vp, int64_t vp0, int64_t vp1,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
     T* __restrict__ O, int n, int npad, int ntq, int ug, int BH, int Hq, int Hkv, float c, int out_compact, int compute_blocks,
-    int t_per_batch, int v_in_place, const T* __restrict__ Kl, const T* __restrict__ Vl, int whole_tiles)
+    int t_per_batch, int k_in_place, int v_in_place)
 {
     using C = AttnCfg<T, D, NW, QB>;
     constexpr int kBM = C::BM, kNT = C::NT, kRW = 32 * QB;   // queries per workgroup, threads, queries per wave
@@ -352,11 +365,12 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     const int my_tiles = min(ntiles, wave_last_row / kBN + 1);   // later tiles lie wholly in this wave's future
     const char* kg = reinterpret_cast<const char*>(Kp + b * kp0 + g * kp1);   // row-major kept K rows of this unit
     const char* vg = reinterpret_cast<const char*>(Vp + b * vp0 + g * vp1);   // V tiles of this unit (V^T tiles for fp32)
-    // Tiles from whole_tiles on (the ragged last one of a cache that is read in place) lie in the workspace.  All scalar.
-    const int64_t last_tile = (int64_t)(b * Hkv + g) * C::TILE_BYTES;
-    const int64_t klast = reinterpret_cast<const char*>(Kl) + last_tile - kg, vlast = reinterpret_cast<const char*>(Vl) + last_tile - vg;
-    auto ktile = [&](int t) { return kg + (t < whole_tiles ? (int64_t)t * C::TILE_BYTES : klast); };
-    auto vtile = [&](int t) { return vg + (t < whole_tiles ? (int64_t)t * C::TILE_BYTES : vlast); };
+    // An evicted cache that is read in place need not hold a row at or beyond k: the tile with row k - 1 is loaded as far
+    // as that row (what stands for later rows is masked and weighs nothing).  Packed tiles are whole.  The steps that
+    // request it run outside the steady state: at most 1 us of 289 at 128 heads x 8192 tokens.
+    const int krows = k_in_place ? kk : npad, vrows = C::VROWS && v_in_place ? kk : npad;
+    const int whole_tiles = min(krows, vrows) / kBN;
+    const int steady_end = ntiles <= whole_tiles ? ntiles : whole_tiles - 2;   // the steps before this request whole tiles only
     char* const Kb0 = smem;
     char* const Vb0 = smem + 2 * C::TILE_BYTES;
     const int sw = k_row_swizzle<C::KRB>(i);
@@ -367,12 +381,19 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     PV<T, D, NW, QB>::lane_offsets(lane, vlane);
 
     const unsigned klds = lds_address(Kb0) + w * 1024, vlds = lds_address(Vb0) + w * 1024;
+    auto load_k = [&](int t, int buf) {
+        tile_to_lds<C::KRB, NW, C::NLD>(kg + (int64_t)t * C::TILE_BYTES, klds + buf * C::TILE_BYTES, koff, krows - t * kBN);
+    };
+    auto load_v = [&](int t, int buf) {
+        const int rows = C::VROWS ? vrows - t * kBN : kBN;
+        tile_to_lds<C::VRB, NW, C::NLD, C::VROWS>(vg + (int64_t)t * C::TILE_BYTES, vlds + buf * C::TILE_BYTES, voff, rows);
+    };
     // The first tiles are requested before anything else is loaded: their addresses need only scalars, while the
     // query rows below wait for their positions first (two round trips).
     auto request_first_tiles = [&]() {
-        tile_to_lds<C::KRB, NW, C::NLD>(ktile(0), Kb0, w, koff);
-        tile_to_lds<C::VRB, NW, C::NLD>(vtile(0), Vb0, w, voff);
-        if (ntiles > 1) tile_to_lds<C::KRB, NW, C::NLD>(ktile(1), Kb0 + C::TILE_BYTES, w, koff);
+        load_k(0, 0);
+        load_v(0, 0);
+        if (ntiles > 1) load_k(1, 1);
     };
     request_first_tiles();
     // kept-token coordinates of this lane's QB queries, their positions, their Q fragments
@@ -495,17 +516,10 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         // one tile t-1 leaves at the middle barrier (second half).  In the steady state they are issued one
         // at a time, each tied to one exponential (a burst of them stalls every wave of the workgroup at the
         // address unit); elsewhere in one go.  Past the last tile the last tile is fetched again, unread.
-        const char* kgt = ktile(min(t + 2, ntiles - 1));
-        const char* vgt = vtile(min(t + 1, ntiles - 1));
+        const int kt = min(t + 2, ntiles - 1), vt = min(t + 1, ntiles - 1);
+        const char* kgt = kg + (int64_t)kt * C::TILE_BYTES;
+        const char* vgt = vg + (int64_t)vt * C::TILE_BYTES;
         const unsigned kl = klds + (t & 1) * C::TILE_BYTES, vl = vlds + ((t + 1) & 1) * C::TILE_BYTES;
-        auto fetch_k = [&]() {
-#pragma unroll
-            for (int q = 0; q < C::NLD; ++q) tile_load<C::KRB, NW, C::NLD>(kgt, q, koff, kl + q * NW * 1024);
-        };
-        auto fetch_v = [&]() {
-#pragma unroll
-            for (int q = 0; q < C::NLD; ++q) tile_load<C::VRB, NW, C::NLD>(vgt, q, voff, vl + q * NW * 1024);
-        };
         // load L of a half rides on exponential (2L+1) * 16 / (2 NLD) of that half's key block
         auto fetch_after_exp = [&](int blk, int r, float& pinned) {
 #pragma unroll
@@ -520,14 +534,6 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         const bool has_pv = t >= 1 && t - 1 < my_tiles, has_s = t < my_tiles, has_next = t + 1 < my_tiles;
         const char* kb = Kb0 + ((t + 1) & 1) * C::TILE_BYTES;
         const char* vb = Vb0 + ((t + 1) & 1) * C::TILE_BYTES;          // V tile t-1
-        if (C::VROWS && v_in_place && t >= 1 && t * kBN > kk) {
-            // A V tile read in place from the evicted cache may hold anything in its rows past k; their
-            // probabilities are exact zeros, but 0 * NaN is not: clear those rows in LDS (last tile only).
-            char* vt = Vb0 + ((t + 1) & 1) * C::TILE_BYTES;
-            const uintx4 z = {0, 0, 0, 0};
-            for (int q = tid + (kk - (t - 1) * kBN) * (C::VRB / 16); q < kBN * (C::VRB / 16); q += kNT) store16(vt + q * 16, z);
-            __syncthreads();
-        }
         float mc[QB], sum[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) { mc[qb] = 0.f; sum[qb] = 0.f; }
@@ -567,7 +573,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
                 }
             }
         };
-        const bool steady = has_pv && has_next && !SAFE;
+        const bool steady = has_pv && has_next && t < steady_end && !SAFE;
         // ---- first half: P.V of tile t-1 | exponentials of key block 0 of tile t | requests for K tile t+2
         if (steady) {
             if constexpr (kExplicit) steady_half(std::integral_constant<int, 0>{}, vb, sc, sn, pp, pc, sum, kgt, kl);
@@ -577,7 +583,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
                 PV<T, D, NW, QB>::template run<1>(vb, vlane, pp, o);
             }
         } else {
-            fetch_k();
+            load_k(kt, t & 1);
             if (has_pv) {
                 PV<T, D, NW, QB>::template run<0>(vb, vlane, pp, o);
                 PV<T, D, NW, QB>::template run<1>(vb, vlane, pp, o);
@@ -632,7 +638,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
                 qk_block<T, D, NW, QB>(kb, 1, i, h, sw, qf, sn);
             }
         } else {
-            fetch_v();
+            load_v(vt, (t + 1) & 1);
             if (has_next) {
                 qk_block<T, D, NW, QB>(kb, 0, i, h, sw, qf, sn);
                 qk_block<T, D, NW, QB>(kb, 1, i, h, sw, qf, sn);
@@ -706,7 +712,7 @@ size_t prefill_workspace_bytes(const zipvl_dims& d) {
 
 template <typename T, int D, int NW, int QB>
 static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
-                        float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, int whole_tiles, void* O, hipStream_t st)
+                        float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, void* O, hipStream_t st)
 {
     using C = AttnCfg<T, D, NW, QB>;
     static std::atomic<bool> attr_done{false};       // raising the dynamic-LDS cap is idempotent
@@ -737,7 +743,7 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
             skip_k ? d.k_strides[1] : (int64_t)npad * D,
             skip_v ? (const T*)V : Vp, skip_v ? d.v_strides[0] : (int64_t)d.Hkv * npad * D,
             skip_v ? d.v_strides[1] : (int64_t)npad * D, idx, k, (T*)O, d.n, npad, ntq, ug, BH, d.Hq, d.Hkv,
-            scale * kLog2e, out_compact, (int)blocks, t_per_batch, skip_v, Kp, Vp, whole_tiles);
+            scale * kLog2e, out_compact, (int)blocks, t_per_batch, skip_k, skip_v);
     }
     return check_launch("flash_kept");
 }
@@ -755,31 +761,23 @@ static int launch_prefill_t(const void* Q, const void* K, const void* V, const z
     const int rows_are_kept = (flags & ZIPVL_KV_ALREADY_COMPACT) ? 1 : 0;
     const int t_per_batch = (flags & ZIPVL_T_PER_BATCH) ? 1 : 0;
 
-    // An evicted cache with contiguous rows is read in place (K always, V when the transposing LDS read applies), but for
-    // a last tile that the n rows do not fill: that one is packed (it holds kept rows only when nearly all are kept), and
-    // only where both tensors are read in place.  32 heads, n = 2933: packing all of it took 8.5 us of 64.
-    // Rows between k and the end of the last tile may hold anything: K rows there are masked, V rows there are cleared
-    // once they are in LDS.
-    const bool k_rows = rows_are_kept && d.k_strides[2] == D, v_rows = rows_are_kept && Elem<T>::kBytes == 2 && d.v_strides[2] == D;
-    const bool whole = d.n % kBN == 0;
-    const int skip_k = (k_rows && (whole || v_rows)) ? 1 : 0, skip_v = (v_rows && (whole || k_rows)) ? 1 : 0;
-    const bool tail_only = skip_k && skip_v && !whole;
-    const int whole_tiles = tail_only ? d.n / kBN : npad / kBN;
-    if (tail_only) VTp = Kp + (size_t)units * kBN * D;
-    if (!(skip_k && skip_v) || tail_only) {
+    // An evicted cache with contiguous rows is read in place (K always, V when the transposing LDS read applies: then
+    // nothing is packed), whatever its length: no row at or beyond k is read.  32 heads, n = 2933: packing all of it took 8.5 us of 64.
+    const int skip_k = (rows_are_kept && d.k_strides[2] == D) ? 1 : 0;
+    const int skip_v = (rows_are_kept && Elem<T>::kBytes == 2 && d.v_strides[2] == D) ? 1 : 0;
+    if (!(skip_k && skip_v)) {
         KernelTimer tm(ZIPVL_K_PACK_KV, st);
-        hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(tail_only ? 1 : npad / kBN, units), dim3(256), 0, st,
+        hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(npad / kBN, units), dim3(256), 0, st,
             (const T*)K, (const T*)V, d.k_strides[0], d.k_strides[1], d.k_strides[2],
-            d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, Kp, VTp, d.n, tail_only ? kBN : npad, d.Hkv, rows_are_kept,
-            tail_only ? 0 : skip_k, t_per_batch, tail_only ? whole_tiles : 0);
+            d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, Kp, VTp, d.n, npad, d.Hkv, rows_are_kept, skip_k, t_per_batch);
         int rc = check_launch("pack_kv");
         if (rc) return rc;
     }
 
     if constexpr (Elem<T>::kBytes == 2)
-        return launch_flash<T, D, kFlashWavesBf16, kFlashBlocksBf16>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, whole_tiles, O, st);
+        return launch_flash<T, D, kFlashWavesBf16, kFlashBlocksBf16>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, O, st);
     else
-        return launch_flash<T, D, 4, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, whole_tiles, O, st);
+        return launch_flash<T, D, 4, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, O, st);
 }
 
 int launch_sparse_prefill(const void* Q, const void* K, const void* V, const zipvl_dims& d,

@@ -355,8 +355,8 @@ def test_attention_compact_output_rows():
 @pytest.mark.parametrize("n,d,ks", [(40, 128, [40, 39]), (65, 128, [65, 64]), (129, 64, [129, 1]), (333, 128, [333, 320]), (333, 128, [321, 319]),
                                     (447, 64, [447, 446])])
 def test_attention_reads_a_ragged_cache_up_to_its_last_row(n, d, ks):
-    """Evicted caches whose last 64-row tile is not full, with kept counts in and next to that tile: everything before it
-    is read in place, NaN beyond k.  Bit for bit the attention that gathers from the whole K, V."""
+    """Evicted caches whose last 64-row tile is not full, with kept counts in and next to that tile, read in place; NaN
+    beyond k.  Bit for bit the attention that gathers from the whole K, V."""
     say(f"attention KV_ALREADY_COMPACT ragged n={n} d={d} k={ks}")
     B, Hq, Hkv, dtype = 1, 4, 2, "bf16"
     w = make_custom(B, Hq, Hkv, n, d, dtype, seed=10, m=min(64, n))
@@ -377,9 +377,36 @@ def test_attention_reads_a_ragged_cache_up_to_its_last_row(n, d, ks):
         assert torch.equal(O1, O2) and not torch.isnan(O2.float()).any()
 
 
+@pytest.mark.parametrize("n,d,dtype,ks,gain", [(448, 128, "bf16", [211, 77], 1.0), (333, 128, "bf16", [130, 129], 1.0), (1000, 128, "bf16", [833, 640], 1.0),
+                                               (1024, 64, "bf16", [577, 831], 1.0), (1000, 128, "bf16", [705, 1], 40.0), (129, 64, "f32", [65, 63], 1.0),
+                                               (640, 128, "f32", [449, 320], 1.0)])
+def test_attention_reads_no_row_at_or_beyond_k(n, d, dtype, ks, gain):
+    """An evicted cache of exactly max k rows inside a larger allocation of NaN (rows past a unit's k included): a V row
+    read at or beyond k would weigh in as 0 * NaN.  The tile with row k - 1 is the first of its workgroup, a later one,
+    one in the kernel's steady state, or whole; gain 40: the pass with running maxima.  Bit for bit the attention that
+    gathers from the whole K, V."""
+    say(f"attention on a cache of max k rows n={n} d={d} {dtype} k={ks} gain={gain}")
+    B, Hq, Hkv, cap, guard = 1, 4, 2, max(ks), 128
+    w = make_custom(B, Hq, Hkv, n, d, dtype, seed=12, m=min(64, n))
+    Q, K, V = dev(w.Q * np.float32(gain), dtype), dev(w.K, dtype), dev(w.V, dtype)
+    r = np.random.Generator(np.random.PCG64(13))
+    idx = np.zeros((2, n), dtype=np.int32)
+    for u in range(2):
+        idx[u, :ks[u]] = np.sort(r.choice(n, ks[u], replace=False))
+    idx_d, k_d = torch.from_numpy(idx).to(DEV), torch.tensor(ks, dtype=torch.int32, device=DEV)
+    pools = [torch.full(((Hkv * cap + 2 * guard) * d,), float("nan"), dtype=K.dtype, device=DEV) for _ in range(2)]
+    Kc, Vc = (p[guard * d:guard * d + Hkv * cap * d].view(Hkv, cap, d) for p in pools)
+    z.zipvl_compact_kv(K, V, idx_d, k_d, cap, Kc=Kc, Vc=Vc)
+    O1, O2 = torch.zeros_like(Q), torch.zeros_like(Q)
+    z.zipvl_sparse_prefill(Q, K, V, idx_d, k_d, w.scale, O=O1)
+    z.zipvl_sparse_prefill(Q, Kc.view(B, Hkv, cap, d), Vc.view(B, Hkv, cap, d), idx_d, k_d, w.scale, z.KV_ALREADY_COMPACT, O=O2)
+    torch.cuda.synchronize()
+    assert torch.equal(O1, O2) and not torch.isnan(O2.float()).any()
+
+
 @pytest.mark.parametrize("n,gain", [(400, 1.0), (448, 1.0), (448, 40.0)])
 def test_attention_on_already_compacted_cache(n, gain):
-    # n = 448 (whole 64-row tiles, contiguous rows) reads the evicted cache in place; n = 400 packs its last tile;
+    # the evicted cache is read in place, for n a multiple of the 64-row tile and not;
     # gain 40: logits far outside the range the offset-free pass accepts, so every workgroup repeats its keys
     say(f"attention KV_ALREADY_COMPACT n={n} gain={gain}")
     B, Hq, Hkv, d, dtype = 1, 4, 2, 128, "bf16"
