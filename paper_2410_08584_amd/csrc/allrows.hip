@@ -135,14 +135,13 @@ __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 ? 3 : 2) void a
     };
     // acc[r]: streamed row jb + acc_row(r, h), register-side row `my`
     auto accumulate = [&](floatx16& acc, const float (&rb)[16], int jb) {
-        if (PASS == 1 ? jb + 31 > wrow0 : (jb < wrow0 + 31 || jb + 32 > n)) {           // wave-uniform
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int j = jb + acc_row(r, h);
-                if (PASS == 1 ? j > my : (j < my || j >= n)) acc[r] = -INFINITY;
-            }
-        }
+        const bool masked = PASS == 1 ? jb + 31 > wrow0 : (jb < wrow0 + 31 || jb + 32 > n);      // wave-uniform
         if (PASS == 1) {
+            if (masked) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (jb + acc_row(r, h) > my) acc[r] = -INFINITY;
+            }
             float mx = -INFINITY;
 #pragma unroll
             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
@@ -155,12 +154,18 @@ __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 ? 3 : 2) void a
                 m_run = m_new;
             }
         } else {
-            float s0 = 0.f, s1 = 0.f;
+            float p[16], s0 = 0.f, s1 = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                s0 += fast_exp2(fmaf(acc[r], c, -rb[r]));
-                s1 += fast_exp2(fmaf(acc[r + 1], c, -rb[r + 1]));
+            for (int r = 0; r < 16; ++r) p[r] = fast_exp2(fmaf(acc[r], c, -rb[r]));
+            if (masked) {                                                // on the result: the lse of a row that does not see this key may be no number
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int j = jb + acc_row(r, h);
+                    if (j < my || j >= n) p[r] = 0.f;
+                }
             }
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) { s0 += p[r]; s1 += p[r + 1]; }
             recent += s0 + s1;
         }
     };

@@ -577,6 +577,25 @@ def test_all_rows_scores_with_logits_that_outgrow_the_first_block(n, d, dtype, g
         assert (np.abs(host64(got) - ref) <= 1e-9 + (1e-5 + 1e-6 * big) * np.abs(ref)).all()
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_all_rows_scores_keep_a_row_without_numbers_to_the_keys_it_sees(dtype, d, bad):
+    """A query row that is not finite has no softmax; the scores of later keys, which it does not see, are those without it."""
+    say(f"score_all_rows with a {bad} row {dtype} d={d}")
+    n, rows = 203, (70, 192)                                 # inside a 32-row block; the first row of the last chunk
+    w = make_custom(1, 4, 2, n, d, dtype, seed=73, m=64)
+    Q, K = dev(w.Q, dtype), dev(w.K, dtype)
+    mass, rank = z.zipvl_score_all_rows(Q, K, w.scale)
+    for i in rows:
+        Qb = Q.clone()
+        Qb[0, 3, i, 5] = bad                                 # query head 3 = unit 1
+        mass_b, rank_b = z.zipvl_score_all_rows(Qb, K, w.scale)
+        torch.cuda.synchronize()
+        for a, b in ((mass, mass_b), (rank, rank_b)):
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1, i + 1:], b[1, i + 1:])
+            assert torch.isnan(b[1, :i + 1]).any()
+
+
 def test_all_rows_scores_at_cfg2_shape_against_sampled_columns():
     say("score_all_rows at n=3072, 32 heads (sampled heads)")
     w = make_workload(2)
