@@ -43,14 +43,14 @@ struct ArCfg {
 
 // Which (head, block of register-side rows) a workgroup takes.  Workgroups go round-robin over the 8 XCDs; every XCD
 // gets whole heads (or 1 / split of the blocks of one, where the heads do not divide by 8) so that the rows it streams
-// stay in its own L2, the blocks with the most visible pairs first.
-struct ArMap { int split, per, share; };   // parts per head, blocks per part, parts per XCD
+// stay in its own L2, the blocks with the most visible pairs first.  Grid: x = (block of the part, XCD), y = part of the XCD;
+// neither dimension reaches the launch limits (2^32 threads, 65535) for any dims that are accepted.
 
 template <typename T, int D, int PASS>
 __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 ? 3 : 2) void allrows_pass_kernel(
     const T* __restrict__ R, int64_t rs0, int64_t rs1, int64_t rs2,     // register side: Q (pass 1) / K (pass 2)
     const T* __restrict__ S, int64_t ss0, int64_t ss1, int64_t ss2,     // streamed side: K (pass 1) / Q (pass 2)
-    int n, float c, float* __restrict__ lse, float* __restrict__ colsum_out, int Hq, int Hkv, ArMap map)
+    int n, float c, float* __restrict__ lse, float* __restrict__ colsum_out, int Hq, int Hkv, int split)
 {
     using C = ArCfg<T, D>;
     constexpr int CH = C::CH, RB = C::RB, NLD = C::NLD, STG = C::STG;
@@ -59,10 +59,10 @@ __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 ? 3 : 2) void a
     const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nblk = (n + C::ROWS - 1) / C::ROWS;
-    const int y = blockIdx.x >> 3, part = __builtin_amdgcn_readfirstlane((blockIdx.x & 7) * map.share + y / map.per);
-    const int order = __builtin_amdgcn_readfirstlane((y % map.per) * map.split + part % map.split);     // scalar from here on
+    const int part = (blockIdx.x & 7) * gridDim.y + blockIdx.y;           // split parts per head
+    const int order = __builtin_amdgcn_readfirstlane((blockIdx.x >> 3) * split + part % split);        // scalar from here on
     if (order >= nblk) return;
-    const int bh = __builtin_amdgcn_readfirstlane(part / map.split), b = __builtin_amdgcn_readfirstlane(bh / Hq), head = bh - b * Hq;
+    const int bh = __builtin_amdgcn_readfirstlane(part / split), b = __builtin_amdgcn_readfirstlane(bh / Hq), head = bh - b * Hq;
     const int g = __builtin_amdgcn_readfirstlane(head / G);
     // heavy blocks first: late queries in pass 1, early keys in pass 2
     const int row0 = (PASS == 1 ? nblk - 1 - order : order) * C::ROWS, wrow0 = row0 + 32 * w;
@@ -246,8 +246,7 @@ static int launch_allrows_t(const void* Q, const void* K, const zipvl_dims& d, f
     const float c = scale * kLog2e;
     const int nblk = (d.n + C::ROWS - 1) / C::ROWS, heads = d.B * d.Hq;
     const int split = 8 / std::gcd(heads, 8);
-    const ArMap map{split, (nblk + split - 1) / split, heads * split / 8};
-    const dim3 grid(heads * split * map.per);
+    const dim3 grid(8 * ((nblk + split - 1) / split), heads * split / 8);
     float* lse = (float*)ws;
     float* colsum = lse + (size_t)heads * d.n;
     {
@@ -255,7 +254,7 @@ static int launch_allrows_t(const void* Q, const void* K, const zipvl_dims& d, f
         hipLaunchKernelGGL((allrows_pass_kernel<T, D, 1>), grid, dim3(64 * kArWaves), C::LDS, st,
             (const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
             (const T*)K, d.k_strides[0], d.k_strides[1], d.k_strides[2],
-            d.n, c, lse, (float*)nullptr, d.Hq, d.Hkv, map);
+            d.n, c, lse, (float*)nullptr, d.Hq, d.Hkv, split);
     }
     int rc = check_launch("allrows_lse");
     if (rc) return rc;
@@ -263,7 +262,7 @@ static int launch_allrows_t(const void* Q, const void* K, const zipvl_dims& d, f
     hipLaunchKernelGGL((allrows_pass_kernel<T, D, 2>), grid, dim3(64 * kArWaves), C::LDS, st,
         (const T*)K, d.k_strides[0], d.k_strides[1], d.k_strides[2],
         (const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
-        d.n, c, lse, colsum, d.Hq, d.Hkv, map);
+        d.n, c, lse, colsum, d.Hq, d.Hkv, split);
     rc = check_launch("allrows_colsum");
     if (rc) return rc;
     hipLaunchKernelGGL(allrows_finish_kernel, dim3((d.n + 255) / 256, d.B * d.Hkv), dim3(256), 0, st,
