@@ -42,7 +42,7 @@ __device__ __forceinline__ void load_kib_to_lds(const char* gbase, int goff, uns
                  :: "s"(m0v), "v"(goff), "s"(gbase) : "memory", "m0");
 }
 
-// The same with a 64-bit address per lane, for rows that lie 4 GiB and more apart.
+// The same with a 64-bit address per lane, for rows further apart than the 32-bit offsets of a load reach.
 __device__ __forceinline__ void load_kib_to_lds_at(const char* lane_ptr, unsigned lds_base) {
     const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_base);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"

@@ -578,6 +578,22 @@ def test_all_rows_scores_with_logits_that_outgrow_the_first_block(n, d, dtype, g
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+def test_all_rows_scores_of_rows_32_mib_apart(dtype, d):
+    """64 streamed rows that span 2 GiB and more are addressed with 64 bits per lane; bit for bit the contiguous result."""
+    say(f"score_all_rows strides above 32 MiB {dtype} d={d}")
+    n = 65
+    w = make_custom(1, 1, 1, n, d, dtype, seed=74, m=64)
+    Q, K = dev(w.Q, dtype), dev(w.K, dtype)
+    stride = (32 << 20) // K.element_size() + 64
+    pool = torch.empty((n * stride,), dtype=K.dtype, device=DEV)
+    Qs, Ks = (pool.as_strided((1, 1, n, d), (0, 0, stride, 1), off) for off in (0, d))
+    Qs.copy_(Q)
+    Ks.copy_(K)
+    for a, b in zip(z.zipvl_score_all_rows(Q, K, w.scale), z.zipvl_score_all_rows(Qs, Ks, w.scale)):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 def test_all_rows_scores_keep_a_row_without_numbers_to_the_keys_it_sees(dtype, d, bad):
     """A query row that is not finite has no softmax; the scores of later keys, which it does not see, are those without it."""
