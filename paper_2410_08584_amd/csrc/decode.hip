@@ -1,9 +1,10 @@
 // Decode-phase attention against the (evicted) KV cache (Eq. (5); Algorithm 2).
 // Memory-bound: one query per head, every cached row read exactly once, all
 // query heads of a KV group served from the same read.
-// Split-KV: grid = (splits, units).  The number of splits is chosen on the host
-// (from the units and the capacity); a split's rows are the unit's device-resident
-// length over that number, so every workgroup has work on short and full caches.
+// Split-KV: a unit's device-resident length is cut into equal splits, as many as fill
+// the chip when all units are alike (from the units, on the host) and more where the
+// unit is long (from its length; SplitRule), so that short and full caches as well as
+// batches of unequal lengths keep the workgroups busy.
 // Groups of two and more heads run on the matrix cores, 16 cached rows per wave
 // step (attend_split); a single head runs on the vector units, where 16 lanes
 // cover one cached row (16 bytes each at d = 128 bf16), reduce the dot product with
@@ -213,6 +214,9 @@ constexpr float kDecLazyLog2 = 8.f;
 template <int GT> constexpr bool kDecMfma = GT > 1;
 template <int GT> constexpr int kDecWaves = kDecMfma<GT> ? 8 : 4;        // waves per workgroup (8: 14.0 us, 4: 18.5 us at the shape above)
 constexpr int kDecTile = 16;          // cached rows per wave step
+// Tiles of a split that is called long (SplitRule).  Such a split takes about 85 us (one head, 3072 rows) and 100 us (groups,
+// 6144 rows) on one workgroup; for shorter ones more workgroups mostly add launching and merging.
+constexpr int kDecLongOne = 192, kDecLongGroups = 384;
 
 template <typename T, int EPL> struct alignas(sizeof(T) * EPL > 16 ? 16 : sizeof(T) * EPL) RawChunk { T v[EPL]; };
 
@@ -281,9 +285,25 @@ __device__ __forceinline__ void attend_rows(const T* Kb, const T* Vb, T* Kw, T* 
     }
 }
 
-// rows of the cache that split `split` of nsplit takes (multiples of a tile)
-__device__ __forceinline__ int rows_per_split(int L, int nsplit) {
-    return max(kDecTile, ((L + nsplit - 1) / nsplit + kDecTile - 1) / kDecTile * kDecTile);
+// Splits of a unit: `least`, which fill the chip together with the other units' when all are alike; `more` where those would
+// be longer than `tiles`, and `most` where these would be (split_rule).  A unit goes by its own length: a long one among
+// short ones is not left to few workgroups, and units that are all long make whole rounds of workgroups.  One conversation of
+// 8192 rows among 31 of 200, 32 heads: 228 us with equal splits, 92 so; 8 KV heads of four heads: 132, 80; 32 conversations of
+// 8192 rows as before (737 and 198).
+// Workgroups are dealt to XCDs and CUs in turn.  Without idle ones the splits of a unit follow each other; where a short unit
+// leaves some idle the units do, each row of units turned by `turn`, so that neither the busy workgroups of short units nor
+// those of a long one fall on the same CUs (one conversation of 32768 rows among three of 500, 32 heads: 213 us without the
+// turn, 145 with it, 16 splits either way).
+struct SplitRule {
+    int least, more, most, tiles, units, turn;               // turn 0: nothing is left idle
+    dim3 grid() const { return turn ? dim3(units, most) : dim3(most, units); }
+    __device__ __forceinline__ int split() const { return turn ? blockIdx.y : blockIdx.x; }
+    __device__ __forceinline__ int unit() const { return turn ? (blockIdx.x + blockIdx.y * (unsigned)turn) % (unsigned)units : blockIdx.y; }
+};
+__device__ __forceinline__ int tiles_of(int L) { return (L + kDecTile - 1) / kDecTile; }
+__device__ __forceinline__ int tiles_per_split(int T, const SplitRule& rule) {
+    const int s = T <= rule.least * rule.tiles ? rule.least : T <= rule.more * rule.tiles ? rule.more : rule.most;
+    return max(1, (T + s - 1) / s);
 }
 
 // Rows [r_begin, r_end) of one unit against heads gbase .. gbase + GT - 1 of its group; the workgroup's state goes to
@@ -418,35 +438,37 @@ __device__ __forceinline__ void attend_one(A&&... a) {
 template <typename T, int D, int GT>
 __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_partial_kernel(
     const T* __restrict__ q, const T* __restrict__ Kc, const T* __restrict__ Vc,
-    const int32_t* __restrict__ len, int cap, int Hq, int Hkv, int gbase, float c, float* __restrict__ part)
+    const int32_t* __restrict__ len, int cap, int Hq, int Hkv, int gbase, float c, SplitRule rule, float* __restrict__ part)
 {
     __shared__ float red[kDecWaves<GT>][GT][D + 2];
     const int G = Hq / Hkv;
-    const int split = blockIdx.x, u = blockIdx.y;
+    const int u = rule.unit(), split = rule.split();
     const int L = max(0, min(len[u], cap));
-    const int rows = rows_per_split(L, gridDim.x);
+    const int rows = tiles_per_split(tiles_of(L), rule) * kDecTile;
     const int r_begin = split * rows, r_end = min(L, r_begin + rows);
     if (split > 0 && r_begin >= L) return;                  // split 0 always reports (an empty state when L = 0)
-    const PartialOut po(part, D, u, G, gridDim.x, gridDim.y);
+    const PartialOut po(part, D, u, G, rule.most, rule.units);
     attend_one<T, D, GT, false>(q + ((int64_t)u * G + gbase) * D, min(GT, G - gbase), c, const_cast<T*>(Kc) + (int64_t)u * cap * D,
                                   const_cast<T*>(Vc) + (int64_t)u * cap * D, nullptr, nullptr, -1, r_begin, r_end, red, po, gbase, split);
 }
 
-// Splits of unit u that hold rows: from the device-resident length when `len` is given, else all of them.
-__device__ __forceinline__ int unit_splits(const int32_t* len, int u, int cap, int nsplit) {
-    if (!len) return nsplit;
-    const int L = max(0, min(len[u], cap)), rows = rows_per_split(L, nsplit);
-    return max(1, (L + rows - 1) / rows);
-}
+struct Lengths { const int32_t* len[3]; int cap[3]; };     // row counts of a unit's parts (NULL: no such part), on the device
 
+// Merges the splits of a unit that hold rows (all of them when no lengths are given).
 template <typename T, int D, int THREADS>
-__global__ __launch_bounds__(THREADS) void decode_combine_kernel(const float* __restrict__ part, const int32_t* __restrict__ len,
-                                                             int cap, int nsplit, int G, T* __restrict__ o)
+__global__ __launch_bounds__(THREADS) void decode_combine_kernel(const float* __restrict__ part, Lengths parts, SplitRule rule, int G, T* __restrict__ o)
 {
     __shared__ MergeLds lds;
     const int u = blockIdx.x;
-    merge_splits<T, D, THREADS, false>(PartialOut(const_cast<float*>(part), D, u, G, nsplit, gridDim.x), G, unit_splits(len, u, cap, nsplit), lds,
-                                   o + (int64_t)u * G * D);
+    int nsplit = rule.most;
+    if (parts.len[0]) {
+        int tiles = 0;
+        for (int p = 0; p < 3; ++p)
+            if (parts.len[p]) tiles += tiles_of(max(0, min(parts.len[p][u], parts.cap[p])));
+        const int per = tiles_per_split(tiles, rule);
+        nsplit = max(1, (tiles + per - 1) / per);
+    }
+    merge_splits<T, D, THREADS, false>(PartialOut(const_cast<float*>(part), D, u, G, rule.most, rule.units), G, nsplit, lds, o + (int64_t)u * G * D);
 }
 
 // ---------------------------------------------------------------- one launch per decode step
@@ -460,21 +482,21 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(const float* __
 template <typename T, int D, int GT>
 __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_step_kernel(
     const T* __restrict__ q, T* __restrict__ Kc, T* __restrict__ Vc, int32_t* __restrict__ len, int cap,
-    const T* __restrict__ k_new, const T* __restrict__ v_new, int Hq, int Hkv, float c,
+    const T* __restrict__ k_new, const T* __restrict__ v_new, int Hq, int Hkv, float c, SplitRule rule,
     float* __restrict__ part, unsigned* __restrict__ arrived, T* __restrict__ out)
 {
     __shared__ union { float red[kDecWaves<GT>][GT][D + 2]; MergeLds merge; } lds;
     __shared__ int is_last;
     const int G = Hq / Hkv;
-    const int split = blockIdx.x, u = blockIdx.y, tid = threadIdx.x;
+    const int u = rule.unit(), split = rule.split(), tid = threadIdx.x;
     const int Lraw = len[u];
     const bool room = Lraw >= 0 && Lraw < cap;               // a full cache is left unchanged, as by the append call
     const int L0 = max(0, min(Lraw, cap));
     const int L = L0 + (room ? 1 : 0);                       // rows attended: the new one included
-    const int rows = rows_per_split(L, gridDim.x);
+    const int rows = tiles_per_split(tiles_of(L), rule) * kDecTile;
     const int r_begin = split * rows, r_end = min(L, r_begin + rows);
     const int nsplit = max(1, (L + rows - 1) / rows);
-    const PartialOut po(part, D, u, G, gridDim.x, gridDim.y);
+    const PartialOut po(part, D, u, G, rule.most, rule.units);
 
     if (split < nsplit)
         attend_one<T, D, GT, true>(q + (int64_t)u * G * D, G, c, Kc + (int64_t)u * cap * D, Vc + (int64_t)u * cap * D,
@@ -485,7 +507,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_step_kernel(
     // would do the same by writing back the whole L2, 150 us per launch here.
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (tid == 0) is_last = atomicAdd(&arrived[u], 1u) == gridDim.x - 1u;
+    if (tid == 0) is_last = atomicAdd(&arrived[u], 1u) == rule.most - 1u;
     __syncthreads();
     if (!is_last) return;
     merge_splits<T, D, 64 * kDecWaves<GT>, true>(po, G, nsplit, lds.merge, out + (int64_t)u * G * D);
@@ -554,17 +576,18 @@ template <typename T, int D, int GT>
 __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
     const T* __restrict__ q, QTensor Kq, QTensor Vq, const int32_t* __restrict__ len_hi, const int32_t* __restrict__ len_lo,
     int cap_hi, int cap_lo, const T* __restrict__ Kt, const T* __restrict__ Vt, const int32_t* __restrict__ len_t, int cap_t,
-    int Hq, int Hkv, int gbase, float c, float* __restrict__ part, int nsplit)
+    int Hq, int Hkv, int gbase, float c, float* __restrict__ part, SplitRule rule)
 {
     constexpr bool kExact = sizeof(T) == 2;                              // codes meet the queries in bf16
     constexpr int EPL = D / 16, QE = D / 4, E16 = 16 / (int)sizeof(T), NK = QE / E16, NP = kExact ? 4 : 1, NW4 = QE / 8, NW2 = QE / 16;
     __shared__ float red[kDecWaves<GT>][GT][D + 2];
     const int G = Hq / Hkv, heads = min(GT, G - gbase);
-    const int split = blockIdx.x, u = blockIdx.y;
+    const int u = rule.unit(), split = rule.split();
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 15, kk = lane >> 4;
     const int L4 = max(0, min(len_hi[u], cap_hi)), L2 = max(0, min(len_lo[u], cap_lo)), Lt = Kt ? max(0, min(len_t[u], cap_t)) : 0;
-    const int T4 = (L4 + kDecTile - 1) / kDecTile, T2 = (L2 + kDecTile - 1) / kDecTile, Tt = (Lt + kDecTile - 1) / kDecTile;
-    const int per = (T4 + T2 + Tt + nsplit - 1) / nsplit;
+    const int T4 = tiles_of(L4), T2 = tiles_of(L2), Tt = tiles_of(Lt);
+    const int per = tiles_per_split(T4 + T2 + Tt, rule);
+    if (split > 0 && split * per >= T4 + T2 + Tt) return;                // split 0 always reports
     const int t_end = min(T4 + T2 + Tt, (split + 1) * per), t_codes = min(t_end, T4 + T2);
 
     struct Codes { uint32_t k[NW4], kp[NP], v[4], vp[4]; };
@@ -718,7 +741,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
         if (kk == 0) { red[w][j][D] = m; red[w][j][D + 1] = l; }
     }
     __syncthreads();
-    combine_waves<D, GT, kDecWaves<GT>>(red, heads, PartialOut(part, D, u, G, nsplit, gridDim.y), gbase, split);
+    combine_waves<D, GT, kDecWaves<GT>>(red, heads, PartialOut(part, D, u, G, rule.most, rule.units), gbase, split);
 }
 
 // ---- the same, for one head per group: 4 lanes per row.
@@ -762,12 +785,12 @@ template <typename T, int D, int GT>
 __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
     const T* __restrict__ q, QTensor Kq, QTensor Vq, const int32_t* __restrict__ len_hi, const int32_t* __restrict__ len_lo,
     int cap_hi, int cap_lo, const T* __restrict__ Kt, const T* __restrict__ Vt, const int32_t* __restrict__ len_t, int cap_t,
-    int Hq, int Hkv, int gbase, float c, float* __restrict__ part, int nsplit)
+    int Hq, int Hkv, int gbase, float c, float* __restrict__ part, SplitRule rule)
 {
     constexpr int EPL = D / 4;                               // elements per lane
     __shared__ float red[4][GT][D + 2];
     const int G = Hq / Hkv;
-    const int split = blockIdx.x, u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
+    const int u = blockIdx.y, split = blockIdx.x, nsplit = rule.most, b = u / Hkv, g = u - b * Hkv;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 3, rg = lane >> 2;   // 16 rows per wave step
     float qv[GT][EPL], qsum[GT];
 #pragma unroll
@@ -970,7 +993,7 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
         }
     }
     __syncthreads();
-    combine_waves<D, GT, 4>(red, min(GT, G - gbase), PartialOut(part, D, u, G, nsplit, gridDim.y), gbase, split);
+    combine_waves<D, GT, 4>(red, min(GT, G - gbase), PartialOut(part, D, u, G, nsplit, rule.units), gbase, split);
 }
 
 static int decode_splits(const zipvl_dims& d, int cap) {
@@ -987,12 +1010,19 @@ static int workspace_splits(const zipvl_dims& d, int cap) {
     return std::max(decode_splits(d, cap), (cap + per - 1) / per);
 }
 
-// Workgroups per unit of the kernels over a cache as stored: all of them have work whatever the lengths are (a split is
-// the unit's rows over this number).  256 of 8 waves (one per CU: 512 is 3-10 % slower from 32 units on, and as fast below)
-// or 1024 of 4 waves (512: 151 us for four layers of 128 units, 1024: 131, 2048: 142), never more than the workspace has room for.
-static int attend_splits(const zipvl_dims& d, int cap) {
-    const int units = d.B * d.Hkv;
-    return std::max(1, std::min(workspace_splits(d, cap), ((d.Hq / d.Hkv > 1 ? 256 : 1024) + units - 1) / units));
+// One head: 1024 workgroups of 4 waves (512: 151 us for four layers of 128 units, 1024: 131, 2048: 142), then 1792: seven per CU
+// are resident together, and a few more would run alone at the end (four conversations of 32768 rows, 32 heads: 1024 387 us,
+// 1792 382, 2048 424).  Groups: 256 of 8 waves (one per CU: 512 is 3-10 % slower from 32 units on, and as fast below), then twice.
+static SplitRule split_rule(const zipvl_dims& d, int cap) {
+    const int units = d.B * d.Hkv, room = workspace_splits(d, cap);
+    const bool groups = d.Hq / d.Hkv > 1;
+    const int tiles = groups ? kDecLongGroups : kDecLongOne;
+    const int least = std::max(1, std::min(room, ((groups ? 256 : 1024) + units - 1) / units));
+    const int most = std::min(room, 4 * least), more = std::min(most, groups ? 2 * least : std::max(least, 1792 / units));
+    const int64_t longest = (int64_t)tiles * kDecTile;       // what no unit reaches is not launched
+    const int launched = cap <= least * longest ? least : cap <= more * longest ? more : most;
+    const int turn = launched > least ? std::max(1, (int)(units * 0.618)) : 0;       // rows of any number of units start all over the chip
+    return {least, std::min(more, launched), launched, tiles, units, turn};
 }
 
 size_t decode_workspace_bytes(const zipvl_dims& d, int cap) {
@@ -1003,11 +1033,13 @@ template <typename T, int D>
 static int launch_decode_t(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
                            const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
-    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, nsplit = attend_splits(d, cap);
+    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv;
+    const SplitRule rule = split_rule(d, cap);
+    const Lengths lengths{{len, nullptr, nullptr}, {cap, 0, 0}};
     const float c = scale * kLog2e;
 #define ZIPVL_DEC(GT)                                                                                \
-    hipLaunchKernelGGL((decode_partial_kernel<T, D, GT>), dim3(nsplit, units), dim3(64 * kDecWaves<GT>), 0, st, \
-        (const T*)q, (const T*)Kc, (const T*)Vc, len, cap, d.Hq, d.Hkv, gb, c, (float*)ws)
+    hipLaunchKernelGGL((decode_partial_kernel<T, D, GT>), rule.grid(), dim3(64 * kDecWaves<GT>), 0, st, \
+        (const T*)q, (const T*)Kc, (const T*)Vc, len, cap, d.Hq, d.Hkv, gb, c, rule, (float*)ws)
     for (int gb = 0; gb < G; gb += 8) {
         KernelTimer tm(ZIPVL_K_DECODE_PARTIAL, st);
         if (G > 1) ZIPVL_DEC(8);
@@ -1020,10 +1052,10 @@ static int launch_decode_t(const void* q, const void* Kc, const void* Vc, const 
     // as many threads as in the fused step, which makes the two paths add the splits in the same order
     if (G > 1)
         hipLaunchKernelGGL((decode_combine_kernel<T, D, 64 * kDecWaves<8>>), dim3(units), dim3(64 * kDecWaves<8>), 0, st,
-            (const float*)ws, len, cap, nsplit, G, (T*)o);
+            (const float*)ws, lengths, rule, G, (T*)o);
     else
         hipLaunchKernelGGL((decode_combine_kernel<T, D, 64 * kDecWaves<1>>), dim3(units), dim3(64 * kDecWaves<1>), 0, st,
-            (const float*)ws, len, cap, nsplit, G, (T*)o);
+            (const float*)ws, lengths, rule, G, (T*)o);
     return check_launch("decode_combine");
 }
 
@@ -1033,13 +1065,16 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
                              const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
     const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, cap = cap_hi + cap_lo + cap_t;
-    const int nsplit = G > 1 ? attend_splits(d, cap) : decode_splits(d, cap);
+    // one head: decode_splits(d, cap) splits whatever the lengths are, each with its share of every part
+    const SplitRule rule = G > 1 ? split_rule(d, cap) : SplitRule{1, 1, decode_splits(d, cap), 0, units, 0};
+    Lengths lengths{{nullptr, nullptr, nullptr}, {0, 0, 0}};
+    if (G > 1) lengths = {{len_hi, len_lo, len_t}, {cap_hi, cap_lo, cap_t}};
     const float c = scale * kLog2e;
     const QTensor kq{(const uint8_t*)Kq.hi_codes, (const uint32_t*)Kq.hi_params, (const uint8_t*)Kq.lo_codes, (const uint32_t*)Kq.lo_params};
     const QTensor vq{(const uint8_t*)Vq.hi_codes, (const uint32_t*)Vq.hi_params, (const uint8_t*)Vq.lo_codes, (const uint32_t*)Vq.lo_params};
 #define ZIPVL_DECQ(KERNEL, GT, THREADS)                                                              \
-    hipLaunchKernelGGL((KERNEL<T, D, GT>), dim3(nsplit, units), dim3(THREADS), 0, st, (const T*)q, kq, vq, \
-        len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t, d.Hq, d.Hkv, gb, c, (float*)ws, nsplit)
+    hipLaunchKernelGGL((KERNEL<T, D, GT>), rule.grid(), dim3(THREADS), 0, st, (const T*)q, kq, vq, \
+        len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t, d.Hq, d.Hkv, gb, c, (float*)ws, rule)
     for (int gb = 0; gb < G; gb += 8) {
         KernelTimer tm(ZIPVL_K_DECODE_Q_PARTIAL, st);
         // one head: the vector units, as over a cache as stored (four layers of 128 units x 8192 rows 160 us, 440 on the matrix
@@ -1052,7 +1087,7 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
 #undef ZIPVL_DECQ
     KernelTimer tm(ZIPVL_K_DECODE_COMBINE, st);
     hipLaunchKernelGGL((decode_combine_kernel<T, D, 256>), dim3(units), dim3(256), 0, st,
-        (const float*)ws, (const int32_t*)nullptr, 0, nsplit, G, (T*)o);
+        (const float*)ws, lengths, rule, G, (T*)o);
     return check_launch("decode_combine");
 }
 
@@ -1066,7 +1101,7 @@ template <typename T, int D>
 static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,
                                 const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
-    const int G = d.Hq / d.Hkv, units = d.B * d.Hkv;
+    const int G = d.Hq / d.Hkv;
     unsigned* arrived = (unsigned*)ws;
     float* part = (float*)((char*)ws + step_counter_bytes(d));
     if (G > 8) {                                            // several passes over the cache per step: not fused
@@ -1075,11 +1110,11 @@ static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len,
         return launch_decode_attn(q, Kc, Vc, len, cap, d, scale, o, part, st);
     }
     const float c = scale * kLog2e;
-    const dim3 grid(attend_splits(d, cap), units);
+    const SplitRule rule = split_rule(d, cap);
     KernelTimer tm(ZIPVL_K_DECODE_STEP, st);
 #define ZIPVL_STEP(GT)                                                                               \
-    hipLaunchKernelGGL((decode_step_kernel<T, D, GT>), grid, dim3(64 * kDecWaves<GT>), 0, st, (const T*)q, (T*)Kc, (T*)Vc, len, cap, \
-        (const T*)k_new, (const T*)v_new, d.Hq, d.Hkv, c, part, arrived, (T*)o)
+    hipLaunchKernelGGL((decode_step_kernel<T, D, GT>), rule.grid(), dim3(64 * kDecWaves<GT>), 0, st, (const T*)q, (T*)Kc, (T*)Vc, len, cap, \
+        (const T*)k_new, (const T*)v_new, d.Hq, d.Hkv, c, rule, part, arrived, (T*)o)
     if (G > 1) ZIPVL_STEP(8);
     else ZIPVL_STEP(1);
 #undef ZIPVL_STEP

@@ -1126,6 +1126,66 @@ def test_decode_256_fused_steps_bit_identical_to_append_then_attention_at_the_st
         assert np.abs(oh[u] - ref).max() <= 2e-2
 
 
+# B, Hq, Hkv, cap, long length, splits the long units get at least (of at most 3072 rows for one head, 6144 for groups)
+UNEQUAL = [(32, 32, 32, 8456, 8192, 3), (16, 32, 32, 8456, 8000, 3), (32, 16, 8, 8456, 8192, 2), (128, 8, 4, 6200, 6145, 2), (1100, 1, 1, 3100, 3073, 2)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,cap,longest,splits", UNEQUAL)
+def test_decode_of_unequal_conversations_splits_the_long_one(B, Hq, Hkv, cap, longest, splits):
+    """One long conversation (the last of the batch) among short ones and an empty one: its units are shared by several
+    workgroups (counted by the partial states that the call leaves in its workspace), the outputs meet the oracle, and
+    the fused step gives the same bits, lengths and caches over three steps."""
+    say(f"unequal decode B={B} Hq={Hq} Hkv={Hkv} cap={cap}")
+    units, d, G = B * Hkv, 64, Hq // Hkv
+    g = torch.Generator(device=DEV); g.manual_seed(91)
+    Ka = torch.empty((units, cap, d), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    Va = torch.empty((units, cap, d), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    lens = np.full(units, 10, dtype=np.int32)
+    lens[0], lens[units - Hkv:] = 0, longest
+    la, scale = torch.from_numpy(lens).to(DEV), 1.0 / math.sqrt(d)
+    q = torch.randn((B * Hq, d), generator=g, device=DEV).to(torch.bfloat16)
+    ws = torch.full((z.workspace_bytes(z.OP_DECODE, z.dims_of(None, None, None, B=B, Hq=Hq, Hkv=Hkv, n=cap, d=d, dtype=1)),), 0xFF, dtype=torch.uint8, device=DEV)
+    o = z.zipvl_decode_attn(q, Ka, Va, la, scale, B=B, Hq=Hq, Hkv=Hkv, ws=ws)
+    torch.cuda.synchronize()
+    states = int((ws.view(torch.int32) != -1).sum()) / (G * (d + 2))
+    assert states >= (units - Hkv) + Hkv * splits, f"{states} partial states for {units} units"
+    oh = host64(o)
+    for u in (0, 1, units - Hkv, units - 1):
+        ref = oz.decode_attention(host64(q[u * G]), host64(Ka[u]), host64(Va[u]), int(lens[u]), scale) if lens[u] else 0.0
+        assert np.abs(oh[u * G] - ref).max() <= 2e-2
+    Kb, Vb, lb = Ka.clone(), Va.clone(), la.clone()
+    step_ws = z.decode_step_workspace(B, Hq, Hkv, cap, d, Ka)
+    for _ in range(3):
+        q = torch.randn((B * Hq, d), generator=g, device=DEV).to(torch.bfloat16)
+        kn, vn = (torch.randn((units, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2))
+        oa = z.zipvl_decode_step(q, Ka, Va, la, kn, vn, scale, B=B, Hq=Hq, Hkv=Hkv, ws=step_ws)
+        z.zipvl_kv_append(Kb, Vb, lb, kn, vn, B=B, Hkv=Hkv)
+        ob = z.zipvl_decode_attn(q, Kb, Vb, lb, scale, B=B, Hq=Hq, Hkv=Hkv)
+        assert torch.equal(oa, ob) and torch.equal(la, lb)
+    assert torch.equal(Ka, Kb) and torch.equal(Va, Vb)
+    assert int(step_ws[:4 * units].view(torch.int32).abs().sum().item()) == 0
+
+
+def test_decode_over_quantised_caches_of_unequal_conversations():
+    """Grouped heads: a conversation in a batch where it is by far the longest, against the same conversation alone."""
+    say("unequal decode over quantised caches")
+    B, Hq, Hkv, n, d, k = 32, 16, 8, 6300, 64, 1500
+    g = torch.Generator(device=DEV); g.manual_seed(92)
+    K, V = (torch.empty((B, Hkv, n, d), dtype=torch.bfloat16, device=DEV).normal_(generator=g) for _ in range(2))
+    idx = torch.arange(n, dtype=torch.int32, device=DEV).repeat(B * Hkv, 1) * 4 % n
+    idx[:, :k] = idx[:, :k].sort(dim=1).values
+    kc = torch.full((B * Hkv,), k, dtype=torch.int32, device=DEV)
+    q = torch.randn((B * Hq, d), generator=g, device=DEV).to(torch.bfloat16)
+    all_, one = z.zipvl_quantize_kv(K, V, idx, kc, k, n - k), z.zipvl_quantize_kv(K[:1], V[:1], idx[:Hkv], kc[:Hkv], k, n - k)
+    all_.len_hi[Hkv:], all_.len_lo[Hkv:] = 20, 33
+    oa = z.zipvl_decode_attn_q(q, all_, 0.125, B=B, Hq=Hq, Hkv=Hkv)
+    ob = z.zipvl_decode_attn_q(q[:Hq].contiguous(), one, 0.125, B=1, Hq=Hq, Hkv=Hkv)
+    torch.cuda.synchronize()
+    # fp32 sums of either split order, rounded to bf16 once: half an ulp of the largest output apart, twice
+    assert (oa[:Hq].float() - ob.float()).abs().max() <= 2 ** -8 * ob.float().abs().max()
+    assert not torch.isnan(oa.float()).any()
+
+
 @pytest.mark.parametrize("dtype,d,G", [("bf16", 128, 7), ("bf16", 64, 2), ("f32", 64, 4), ("f32", 128, 8)])
 def test_decode_of_head_groups_at_tile_edges(dtype, d, G):
     """Groups of several heads on the matrix cores (16 cached rows per wave step): lengths on both sides of a tile, of a
