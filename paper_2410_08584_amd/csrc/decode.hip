@@ -587,7 +587,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
     const int L4 = max(0, min(len_hi[u], cap_hi)), L2 = max(0, min(len_lo[u], cap_lo)), Lt = Kt ? max(0, min(len_t[u], cap_t)) : 0;
     const int T4 = tiles_of(L4), T2 = tiles_of(L2), Tt = tiles_of(Lt);
     const int per = tiles_per_split(T4 + T2 + Tt, rule);
-    if (split > 0 && split * per >= T4 + T2 + Tt) return;                // split 0 always reports
+    if (rule.turn && split > 0 && split * per >= T4 + T2 + Tt) return;   // equal splits all report, and are all merged
     const int t_end = min(T4 + T2 + Tt, (split + 1) * per), t_codes = min(t_end, T4 + T2);
 
     struct Codes { uint32_t k[NW4], kp[NP], v[4], vp[4]; };
@@ -1065,10 +1065,10 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
                              const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
     const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, cap = cap_hi + cap_lo + cap_t;
-    // one head: decode_splits(d, cap) splits whatever the lengths are, each with its share of every part
+    // one head: decode_splits(d, cap) splits whatever the lengths are, each with its share of every part of the cache
     const SplitRule rule = G > 1 ? split_rule(d, cap) : SplitRule{1, 1, decode_splits(d, cap), 0, units, 0};
     Lengths lengths{{nullptr, nullptr, nullptr}, {0, 0, 0}};
-    if (G > 1) lengths = {{len_hi, len_lo, len_t}, {cap_hi, cap_lo, cap_t}};
+    if (rule.turn) lengths = {{len_hi, len_lo, Kt ? len_t : nullptr}, {cap_hi, cap_lo, cap_t}};      // else every split reports: 0.5 us less
     const float c = scale * kLog2e;
     const QTensor kq{(const uint8_t*)Kq.hi_codes, (const uint32_t*)Kq.hi_params, (const uint8_t*)Kq.lo_codes, (const uint32_t*)Kq.lo_params};
     const QTensor vq{(const uint8_t*)Vq.hi_codes, (const uint32_t*)Vq.hi_params, (const uint8_t*)Vq.lo_codes, (const uint32_t*)Vq.lo_params};
