@@ -604,7 +604,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
             uint32_t lo[NW2];
             load_words<NW2>(Kq.lo_codes + rk * (D / 4) + kk * (QE / 4), lo);
 #pragma unroll
-            for (int i = 0; i < NW2; ++i) x.k[i] = lo[i];
+            for (int i = 0; i < NW4; ++i) x.k[i] = i < NW2 ? lo[i % NW2] : 0u;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
