@@ -25,24 +25,21 @@ template <typename T> __device__ __forceinline__ T to_out(float x);
 template <> __device__ __forceinline__ float to_out<float>(float x) { return x; }
 template <> __device__ __forceinline__ __bf16 to_out<__bf16>(float x) { return (__bf16)x; }
 
-// One cached row against the GT queries of the group: kf / vf are this lane's EPL elements of the row.
-template <int EPL, int GT>
+// One cached row against a query: kf / vf are this lane's EPL elements of the row.
+template <int EPL>
 __device__ __forceinline__ void attend_row(bool valid, const float (&kf)[EPL], const float (&vf)[EPL],
-                                           const float (&qv)[GT][EPL], float (&m)[GT], float (&l)[GT], float (&o)[GT][EPL]) {
+                                           const float (&qv)[EPL], float& m, float& l, float (&o)[EPL]) {
+    float s = 0.f;
 #pragma unroll
-    for (int t = 0; t < GT; ++t) {
-        float s = 0.f;
+    for (int e = 0; e < EPL; ++e) s += qv[e] * kf[e];
+    s += __shfl_xor(s, 1); s += __shfl_xor(s, 2); s += __shfl_xor(s, 4); s += __shfl_xor(s, 8);
+    if (valid) {
+        const float m_new = fmaxf(m, s);
+        const float a = fast_exp2(m - m_new), p = fast_exp2(s - m_new);
+        l = l * a + p;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) s += qv[t][e] * kf[e];
-        s += __shfl_xor(s, 1); s += __shfl_xor(s, 2); s += __shfl_xor(s, 4); s += __shfl_xor(s, 8);
-        if (valid) {
-            const float m_new = fmaxf(m[t], s);
-            const float a = fast_exp2(m[t] - m_new), p = fast_exp2(s - m_new);
-            l[t] = l[t] * a + p;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) o[t][e] = o[t][e] * a + p * vf[e];
-            m[t] = m_new;
-        }
+        for (int e = 0; e < EPL; ++e) o[e] = o[e] * a + p * vf[e];
+        m = m_new;
     }
 }
 
@@ -162,30 +159,26 @@ __device__ __forceinline__ void merge_splits(const PartialOut& po, int G, int ns
     }
 }
 
-// Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state.
-template <int D, int GT, bool COHERENT = false>
-__device__ __forceinline__ void write_partial(float (&m)[GT], float (&l)[GT], float (&o)[GT][D / 16], float (&red)[4][GT][D + 2],
-                                              int heads, const PartialOut& po, int gbase, int split) {
+// Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state (one head).
+template <int D, bool COHERENT>
+__device__ __forceinline__ void write_partial(float m, float l, float (&o)[D / 16], float (&red)[4][1][D + 2], const PartialOut& po, int split) {
     constexpr int EPL = D / 16;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
 #pragma unroll
-    for (int t = 0; t < GT; ++t) {
+    for (int off = 16; off <= 32; off <<= 1) {
+        const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
+        float o2[EPL];
 #pragma unroll
-        for (int off = 16; off <= 32; off <<= 1) {
-            const float m2 = __shfl_xor(m[t], off), l2 = __shfl_xor(l[t], off);
-            float o2[EPL];
+        for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[e], off);
+        merge_state<EPL>(m, l, o, m2, l2, o2);
+    }
+    if (rg == 0) {
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[t][e], off);
-            merge_state<EPL>(m[t], l[t], o[t], m2, l2, o2);
-        }
-        if (rg == 0) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) red[w][t][sub * EPL + e] = o[t][e];
-            if (sub == 0) { red[w][t][D] = m[t]; red[w][t][D + 1] = l[t]; }
-        }
+        for (int e = 0; e < EPL; ++e) red[w][0][sub * EPL + e] = o[e];
+        if (sub == 0) { red[w][0][D] = m; red[w][0][D + 1] = l; }
     }
     __syncthreads();
-    combine_waves<D, GT, 4, COHERENT>(red, heads, po, gbase, split);
+    combine_waves<D, 1, 4, COHERENT>(red, 1, po, 0, split);
 }
 
 // rows [r_begin, r_end) of a segment of L rows that split `split` of nsplit handles (multiples of 64 rows: 16 per wave step)
@@ -249,14 +242,13 @@ __device__ __forceinline__ void raw_to_floats(const RawChunk<T, EPL>& r, float (
     RowChunk<T, EPL>::load(r.v, f);
 }
 
-// Rows [r_begin, r_end) of one unit against the GT queries in qv.  Row r comes from the cache, except row
+// Rows [r_begin, r_end) of one unit against the query in qv.  Row r comes from the cache, except row
 // `new_row` (>= 0 only in the fused step), which comes from k_new / v_new and is also written to the cache.
 // The 16 row groups of the workgroup take rows r_begin + g, r_begin + g + 16, ...; the loads of a group's next
 // row are in flight while the current one is consumed.
-template <typename T, int D, int GT>
+template <typename T, int D>
 __device__ __forceinline__ void attend_rows(const T* Kb, const T* Vb, T* Kw, T* Vw, const T* kn, const T* vn, int new_row,
-                                            int r_begin, int r_end, int group, const float (&qv)[GT][D / 16],
-                                            float (&m)[GT], float (&l)[GT], float (&o)[GT][D / 16]) {
+                                            int r_begin, int r_end, int group, const float (&qv)[D / 16], float& m, float& l, float (&o)[D / 16]) {
     constexpr int EPL = D / 16;
     using Raw = RawChunk<T, EPL>;
     auto fetch = [&](int r, Raw& kr, Raw& vr) {
@@ -280,7 +272,7 @@ __device__ __forceinline__ void attend_rows(const T* Kb, const T* Vb, T* Kw, T* 
         float kf[EPL], vf[EPL];
         raw_to_floats<T, EPL>(kc, kf);
         raw_to_floats<T, EPL>(vc, vf);
-        attend_row<EPL, GT>(valid, kf, vf, qv, m, l, o);
+        attend_row<EPL>(valid, kf, vf, qv, m, l, o);
         kc = kx; vc = vx;
     }
 }
@@ -408,31 +400,30 @@ __device__ __forceinline__ void attend_split(const T* q0, int heads, float c, T*
     combine_waves<D, GT, kDecWaves<GT>, COHERENT>(red, heads, po, gbase, split);
 }
 
-template <typename T, int D, int GT, bool COHERENT>
-__device__ __forceinline__ void attend_split_valu(const T* q0, int heads, float c, T* Kb, T* Vb, const T* kn, const T* vn, int new_row,
-                                                  int r_begin, int r_end, float (&red)[4][GT][D + 2],
-                                                  const PartialOut& po, int gbase, int split)
+// The same for a group of one head.
+template <typename T, int D, bool COHERENT>
+__device__ __forceinline__ void attend_split_one(const T* q, float c, T* Kb, T* Vb, const T* kn, const T* vn, int new_row,
+                                                 int r_begin, int r_end, float (&red)[4][1][D + 2], const PartialOut& po, int split)
 {
     constexpr int EPL = D / 16;
     const int tid = threadIdx.x, sub = tid & 15;
-    float qv[GT][EPL], m[GT], l[GT], o[GT][EPL];
+    float qv[EPL], m = -INFINITY, l = 0.f, o[EPL];
+    RowChunk<T, EPL>::load(q + sub * EPL, qv);
 #pragma unroll
-    for (int t = 0; t < GT; ++t) {
-        m[t] = -INFINITY; l[t] = 0.f;
-        if (t < heads) RowChunk<T, EPL>::load(q0 + (int64_t)t * D + sub * EPL, qv[t]);
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) { qv[t][e] = t < heads ? qv[t][e] * c : 0.f; o[t][e] = 0.f; }
-    }
+    for (int e = 0; e < EPL; ++e) { qv[e] *= c; o[e] = 0.f; }
     Kb += sub * EPL; Vb += sub * EPL;
     if constexpr (COHERENT) { kn += sub * EPL; vn += sub * EPL; }         // the fused step: the only caller with a new row
-    attend_rows<T, D, GT>(Kb, Vb, Kb, Vb, kn, vn, new_row, r_begin, r_end, tid >> 4, qv, m, l, o);
-    write_partial<D, GT, COHERENT>(m, l, o, red, heads, po, gbase, split);
+    attend_rows<T, D>(Kb, Vb, Kb, Vb, kn, vn, new_row, r_begin, r_end, tid >> 4, qv, m, l, o);
+    write_partial<D, COHERENT>(m, l, o, red, po, split);
 }
 
-template <typename T, int D, int GT, bool COHERENT, typename... A>
-__device__ __forceinline__ void attend_one(A&&... a) {
-    if constexpr (kDecMfma<GT>) attend_split<T, D, GT, COHERENT>(a...);
-    else attend_split_valu<T, D, GT, COHERENT>(a...);
+template <typename T, int D, int GT, bool COHERENT>
+__device__ __forceinline__ void attend_one(const T* q0, int heads, float c, T* Kb, T* Vb, const T* kn, const T* vn, int new_row,
+                                           int r_begin, int r_end, float (&red)[kDecWaves<GT>][GT][D + 2],
+                                           const PartialOut& po, int gbase, int split)
+{
+    if constexpr (kDecMfma<GT>) attend_split<T, D, GT, COHERENT>(q0, heads, c, Kb, Vb, kn, vn, new_row, r_begin, r_end, red, po, gbase, split);
+    else attend_split_one<T, D, COHERENT>(q0, c, Kb, Vb, kn, vn, new_row, r_begin, r_end, red, po, split);
 }
 
 template <typename T, int D, int GT>
@@ -781,58 +772,45 @@ template <int BITS> struct MixCodes {
 };
 static_assert(MixCodes<4>::PAIRS <= 2 * MixCodes<4>::KEPT && MixCodes<2>::PAIRS <= 2 * MixCodes<2>::KEPT, "one shift reaches every field");
 
-template <typename T, int D, int GT>
+template <typename T, int D>
 __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
     const T* __restrict__ q, QTensor Kq, QTensor Vq, const int32_t* __restrict__ len_hi, const int32_t* __restrict__ len_lo,
     int cap_hi, int cap_lo, const T* __restrict__ Kt, const T* __restrict__ Vt, const int32_t* __restrict__ len_t, int cap_t,
-    int Hq, int Hkv, int gbase, float c, float* __restrict__ part, SplitRule rule)
+    float c, float* __restrict__ part, SplitRule rule)
 {
     constexpr int EPL = D / 4;                               // elements per lane
-    __shared__ float red[4][GT][D + 2];
-    const int G = Hq / Hkv;
-    const int u = blockIdx.y, split = blockIdx.x, nsplit = rule.most, b = u / Hkv, g = u - b * Hkv;
+    __shared__ float red[4][1][D + 2];
+    const int u = blockIdx.y, split = blockIdx.x, nsplit = rule.most;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 3, rg = lane >> 2;   // 16 rows per wave step
-    float qv[GT][EPL], qsum[GT];
+    float qv[EPL], part_sum = 0.f;
 #pragma unroll
-    for (int t = 0; t < GT; ++t) {
-        const int hh = gbase + t;
-        float part_sum = 0.f;
+    for (int e8 = 0; e8 < EPL / 8; ++e8) {
+        float f[8];
+        RowChunk<T, 8>::load(q + (int64_t)u * D + sub * EPL + 8 * e8, f);
 #pragma unroll
-        for (int e8 = 0; e8 < EPL / 8; ++e8) {
-            float f[8];
-            if (hh < G) RowChunk<T, 8>::load(q + ((int64_t)(b * Hq + g * G + hh)) * D + sub * EPL + 8 * e8, f);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) { qv[t][8 * e8 + e] = hh < G ? f[e] * c : 0.f; part_sum += qv[t][8 * e8 + e]; }
-        }
-        qsum[t] = quad_sum(part_sum);                        // sum over the whole row of the scaled query
+        for (int e = 0; e < 8; ++e) { qv[8 * e8 + e] = f[e] * c; part_sum += qv[8 * e8 + e]; }
     }
-    float m[GT], l[GT], zacc[GT], o[GT][EPL];
+    const float qsum = quad_sum(part_sum);                   // sum over the whole row of the scaled query
+    float m = -INFINITY, l = 0.f, zacc = 0.f, o[EPL];
 #pragma unroll
-    for (int t = 0; t < GT; ++t) {
-        m[t] = -INFINITY; l[t] = 0.f; zacc[t] = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) o[t][e] = 0.f;
-    }
-    // one cached row: dsum[t] = q_t . (this lane's part of the K row); then o += (p * vs) (V codes), zacc += p * vz
+    for (int e = 0; e < EPL; ++e) o[e] = 0.f;
+    // one cached row: dot(qv) = q . (this lane's part of the K row); then o += (p * vs) (V codes), zacc += p * vz
     auto attend = [&](bool valid, auto&& dot, float ks, float kz, auto&& axpy, float vs, float vz) {
+        const float dsum = quad_sum(dot(qv));
+        const float sc = valid ? fmaf(ks, dsum, kz * qsum) : -INFINITY;
+        const bool grow = sc > m + kDecLazyLog2;
+        if (__any(grow)) {
+            const float m_new = grow ? sc : m;
+            const float a = grow ? fast_exp2(m - m_new) : 1.f;      // 0 on a row group's first row (m = -inf)
+            l *= a; zacc *= a;
 #pragma unroll
-        for (int t = 0; t < GT; ++t) {
-            const float dsum = quad_sum(dot(qv[t]));
-            const float sc = valid ? fmaf(ks, dsum, kz * qsum[t]) : -INFINITY;
-            const bool grow = sc > m[t] + kDecLazyLog2;
-            if (__any(grow)) {
-                const float m_new = grow ? sc : m[t];
-                const float a = grow ? fast_exp2(m[t] - m_new) : 1.f;   // 0 on a row group's first row (m = -inf)
-                l[t] *= a; zacc[t] *= a;
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) o[t][e] *= a;
-                m[t] = m_new;
-            }
-            const float p = valid ? fast_exp2(sc - m[t]) : 0.f;
-            l[t] += p;
-            zacc[t] = fmaf(p, vz, zacc[t]);
-            axpy(p * vs, o[t]);
+            for (int e = 0; e < EPL; ++e) o[e] *= a;
+            m = m_new;
         }
+        const float p = valid ? fast_exp2(sc - m) : 0.f;
+        l += p;
+        zacc = fmaf(p, vz, zacc);
+        axpy(p * vs, o);
     };
     // a row's codes (BITS wide, NW words per lane): dot with the queries, whose elements carry 1 / MixCodes::field, and
     // weighted sum into the outputs
@@ -869,9 +847,7 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
     // the queries' elements carry the factor of the codes they meet: powers of two, exact
     auto rescale_queries = [&](auto&& factor) {
 #pragma unroll
-        for (int t = 0; t < GT; ++t)
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) qv[t][e] *= factor(e);
+        for (int e = 0; e < EPL; ++e) qv[e] *= factor(e);
     };
     using Four = std::integral_constant<int, 4>;
     using Two = std::integral_constant<int, 2>;
@@ -973,27 +949,24 @@ __global__ __launch_bounds__(256) void decode_q4_partial_kernel(
             }, 1.f, 0.f);
         }
     }
-    // fold the zero-point sums into the outputs, merge the 16 row groups of the wave, then the 4 waves
+    // fold the zero-point sum into the outputs, merge the 16 row groups of the wave, then the 4 waves
 #pragma unroll
-    for (int t = 0; t < GT; ++t) {
+    for (int e = 0; e < EPL; ++e) o[e] += zacc;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) o[t][e] += zacc[t];
+    for (int off = 4; off <= 32; off <<= 1) {
+        const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
+        float o2[EPL];
 #pragma unroll
-        for (int off = 4; off <= 32; off <<= 1) {
-            const float m2 = __shfl_xor(m[t], off), l2 = __shfl_xor(l[t], off);
-            float o2[EPL];
+        for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[e], off);
+        merge_state<EPL>(m, l, o, m2, l2, o2);
+    }
+    if (rg == 0) {
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[t][e], off);
-            merge_state<EPL>(m[t], l[t], o[t], m2, l2, o2);
-        }
-        if (rg == 0) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) red[w][t][sub * EPL + e] = o[t][e];
-            if (sub == 0) { red[w][t][D] = m[t]; red[w][t][D + 1] = l[t]; }
-        }
+        for (int e = 0; e < EPL; ++e) red[w][0][sub * EPL + e] = o[e];
+        if (sub == 0) { red[w][0][D] = m; red[w][0][D + 1] = l; }
     }
     __syncthreads();
-    combine_waves<D, GT, 4>(red, min(GT, G - gbase), PartialOut(part, D, u, G, nsplit, rule.units), gbase, split);
+    combine_waves<D, 1, 4>(red, 1, PartialOut(part, D, u, 1, nsplit, rule.units), 0, split);
 }
 
 static int decode_splits(const zipvl_dims& d, int cap) {
@@ -1072,19 +1045,20 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
     const float c = scale * kLog2e;
     const QTensor kq{(const uint8_t*)Kq.hi_codes, (const uint32_t*)Kq.hi_params, (const uint8_t*)Kq.lo_codes, (const uint32_t*)Kq.lo_params};
     const QTensor vq{(const uint8_t*)Vq.hi_codes, (const uint32_t*)Vq.hi_params, (const uint8_t*)Vq.lo_codes, (const uint32_t*)Vq.lo_params};
-#define ZIPVL_DECQ(KERNEL, GT, THREADS)                                                              \
-    hipLaunchKernelGGL((KERNEL<T, D, GT>), rule.grid(), dim3(THREADS), 0, st, (const T*)q, kq, vq, \
-        len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t, d.Hq, d.Hkv, gb, c, (float*)ws, rule)
+#define ZIPVL_DECQ_ARGS (const T*)q, kq, vq, len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t
     for (int gb = 0; gb < G; gb += 8) {
         KernelTimer tm(ZIPVL_K_DECODE_Q_PARTIAL, st);
         // one head: the vector units, as over a cache as stored (four layers of 128 units x 8192 rows 160 us, 440 on the matrix
         // cores); two and more: the matrix cores (two heads, 32 units x 4000: 122 -> 100 us)
-        if (G > 1) ZIPVL_DECQ(decode_q_partial_kernel, 8, 64 * kDecWaves<8>);
-        else ZIPVL_DECQ(decode_q4_partial_kernel, 1, 256);
+        if (G > 1)
+            hipLaunchKernelGGL((decode_q_partial_kernel<T, D, 8>), rule.grid(), dim3(64 * kDecWaves<8>), 0, st, ZIPVL_DECQ_ARGS,
+                d.Hq, d.Hkv, gb, c, (float*)ws, rule);
+        else
+            hipLaunchKernelGGL((decode_q4_partial_kernel<T, D>), rule.grid(), dim3(256), 0, st, ZIPVL_DECQ_ARGS, c, (float*)ws, rule);
         int rc = check_launch("decode_q_partial");
         if (rc) return rc;
     }
-#undef ZIPVL_DECQ
+#undef ZIPVL_DECQ_ARGS
     KernelTimer tm(ZIPVL_K_DECODE_COMBINE, st);
     hipLaunchKernelGGL((decode_combine_kernel<T, D, 256>), dim3(units), dim3(256), 0, st,
         (const float*)ws, lengths, rule, G, (T*)o);
