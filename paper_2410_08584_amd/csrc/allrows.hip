@@ -25,8 +25,8 @@ constexpr int kArWaves = 4;       // waves per workgroup; 8 (half the streaming 
 
 // What bounds it: a 32x32x128 bf16 tile is 256 matrix cycles and, per lane, 16 x (fma + exp2 + add) (pass 1: + max),
 // about 400 vector cycles, and waves overlap the two only in part.  So: staging that needs no registers (three to four
-// waves per SIMD) and no barrier but one per 64 rows.  28 heads on 4, n = 18432, d = 128, both passes: 5.0 ms (staged through
-// registers, 128-row blocks in no XCD order) -> 2.94 ms.  32 heads, n = 2933: 232 -> 138 us.  Measured and not taken: two row
+// waves per SIMD) and no barrier but one per 64 rows.  28 heads on 4, n = 18432, d = 128, both passes: 4.97 ms (staged through
+// registers, 128-row blocks in no XCD order) -> 2.86 ms.  32 heads, n = 2933: 232 -> 138 us.  Measured and not taken: two row
 // groups per wave (each fragment read from LDS feeds two MFMAs; same time, and 1.1-1.5 times slower below 2000
 // workgroups), three chunks in flight (52 KiB of LDS, 5 % slower), MFMAs and exponentials interleaved by hand (3-8 %
 // slower), a lazily moved offset instead of the running maximum (4 % faster, other roundings).

@@ -742,7 +742,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
 //   q . (zero + scale * code) = zero * sum(q) + scale * (q . code),
 //   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j zero_j + sum_j (p_j scale_j) code_j,
 // i.e. one FMA and 0.6 instructions of unpacking per element and side (MixCodes; 1.25 to 1.5 with conversions to fp32:
-// 174 us instead of 160 for four layers of 128 units x 8192 rows).  The softmax offset follows the running maximum lazily
+// 170 us instead of 152 for four layers of 128 units x 8192 rows).  The softmax offset follows the running maximum lazily
 // (moves only when exceeded by 2^kDecLazyLog2), so the accumulators are rescaled on few rows.
 
 // sum over the 4 lanes of a quad (lanes 4i .. 4i+3), result in all four, by two in-register lane permutes
@@ -1048,7 +1048,7 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
 #define ZIPVL_DECQ_ARGS (const T*)q, kq, vq, len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t
     for (int gb = 0; gb < G; gb += 8) {
         KernelTimer tm(ZIPVL_K_DECODE_Q_PARTIAL, st);
-        // one head: the vector units, as over a cache as stored (four layers of 128 units x 8192 rows 160 us, 440 on the matrix
+        // one head: the vector units, as over a cache as stored (four layers of 128 units x 8192 rows 152 us, 440 on the matrix
         // cores); two and more: the matrix cores (two heads, 32 units x 4000: 122 -> 100 us)
         if (G > 1)
             hipLaunchKernelGGL((decode_q_partial_kernel<T, D, 8>), rule.grid(), dim3(64 * kDecWaves<8>), 0, st, ZIPVL_DECQ_ARGS,
