@@ -146,9 +146,9 @@ int zipvl_score_all_rows(const void* Q, const void* K, const zipvl_dims* dims, f
  * is read back and the selection runs either way (validation that needs device data cannot be an error code of a
  * call that does not synchronise).
  * ws [device] may be NULL: one kernel, one workgroup per unit.  With a workspace of
- * zipvl_workspace_bytes(ZIPVL_OP_SELECT, dims with B * Hkv = units, 0) bytes (16-byte aligned) the first,
- * widest digit of the search is histogrammed by the whole chip and one workgroup per unit finishes (two
- * kernels; faster for long vectors on few units).  That workspace must be ZERO before the first call that uses
+ * zipvl_workspace_bytes(ZIPVL_OP_SELECT, dims with B * Hkv = units, 0) bytes (16-byte aligned) and n > 32768 the
+ * first, widest digit of the search is histogrammed by the whole chip and one workgroup per unit finishes (two
+ * kernels; a quarter less time; shorter vectors fit the registers of one workgroup and do not use it).  That workspace must be ZERO before the first call that uses
  * it; every call leaves it zero; two calls that overlap on one workspace race.  Same results either way.
  */
 int zipvl_select(const float* mass, const float* rank, int units, int n, double tau,

@@ -1,5 +1,4 @@
-// Device code of the selection (Eq. (7), Eq. (9)) that is shared by the stand-alone select kernels and by
-// the score kernel that ends with the selection of its unit.
+// Device code of the selection (Eq. (7), Eq. (9)): what its kernels share, and the two-kernel form for long vectors.
 //
 // Two-level form of the radix descent.  The first digit is 12 bits wide (exponent byte and four mantissa
 // bits of the order-preserving key: 4096 bins) and its histograms - element count packed over the exact
@@ -63,21 +62,6 @@ __device__ __forceinline__ unsigned long long fixed40(float x) {
 
 __device__ __forceinline__ unsigned long long fixed40_of_key(uint32_t key) { return fixed40(__uint_as_float(key)); }
 
-// Loads of data that other workgroups of the same launch may have written (COH): device-scope, so that they
-// are served from the coherence point and not from this XCD's L2.
-template <bool COH> __device__ __forceinline__ float sel_ld(const float* p) {
-    if constexpr (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else return *p;
-}
-template <bool COH> __device__ __forceinline__ uint32_t sel_ld(const uint32_t* p) {
-    if constexpr (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else return *p;
-}
-template <bool COH> __device__ __forceinline__ unsigned long long sel_ld(const unsigned long long* p) {
-    if constexpr (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else return *p;
-}
-
 struct TailShared {
     unsigned long long hist[128];            // histogram of one digit of the list descent (packed, or counts)
     uint32_t list[kSelMaxCand];              // the gathered elements of the crossing bin
@@ -109,22 +93,15 @@ __device__ __forceinline__ void block_scan(uint32_t lc, unsigned long long ls, T
     __syncthreads();
 }
 
-// Where the keys of the vector in use live: n order-preserving keys in LDS, or (longer vectors) the fp32
-// values in memory, re-read by every sweep.
-template <int NTH, bool COH>
+// Order-preserving keys of a vector, read from memory by every sweep.
+template <int NTH>
 struct KeySrc {
-    const uint32_t* lds;
     const float* x;
     int n;
     template <typename F>
     __device__ __forceinline__ void for_each(F&& f) const {
-        if (lds) {
 #pragma unroll 4
-            for (int j = threadIdx.x; j < n; j += NTH) f(lds[j]);
-        } else {
-#pragma unroll 4
-            for (int j = threadIdx.x; j < n; j += NTH) f(orderable(sel_ld<COH>(x + j)));
-        }
+        for (int j = threadIdx.x; j < n; j += NTH) f(orderable(x[j]));
     }
 };
 
@@ -147,13 +124,13 @@ template <int NTH> struct TableRegs {
     unsigned long long v[BPT];      // packed slots, or plain counts
 };
 
-template <int NTH, bool COH>
+template <int NTH>
 __device__ __forceinline__ void table_load(const unsigned long long* __restrict__ hm, const uint32_t* __restrict__ hr, TableRegs<NTH>& r) {
     constexpr int BPT = kSelBins / NTH;
 #pragma unroll
     for (int t = 0; t < BPT; ++t) {
         const int bin = kSelBins - 1 - ((int)threadIdx.x * BPT + t);
-        r.v[t] = hr ? (unsigned long long)sel_ld<COH>(hr + bin) : sel_ld<COH>(hm + bin);
+        r.v[t] = hr ? (unsigned long long)hr[bin] : hm[bin];
     }
 }
 
@@ -197,11 +174,10 @@ __device__ void table_cross(const TableRegs<NTH>& r, bool packed, double tau, ui
 }
 
 // The elements whose first digit is `bin`, gathered into sh.list (any order); at most kSelMaxCand of them exist.
-// cnt: how many of them this thread will meet in its sweep (counted by the caller, or -1: counted here).
 template <int NTH, typename Src>
-__device__ int gather_bin(const Src& src, uint32_t bin, int cnt_known, TailShared& sh) {
-    uint32_t cnt = cnt_known >= 0 ? (uint32_t)cnt_known : 0u;
-    if (cnt_known < 0) src.for_each([&](uint32_t key) { cnt += (key >> kSelBinShift) == bin ? 1u : 0u; });
+__device__ int gather_bin(const Src& src, uint32_t bin, TailShared& sh) {
+    uint32_t cnt = 0u;
+    src.for_each([&](uint32_t key) { cnt += (key >> kSelBinShift) == bin ? 1u : 0u; });
     uint32_t ec, tc;
     unsigned long long es, ts;
     block_scan<NTH>(cnt, 0ull, sh, ec, es, tc, ts);
@@ -279,10 +255,10 @@ __device__ void descend_low(const Src& src, unsigned long long target, TailShare
 }
 
 // After table_cross: the key at which the descending cumulative sum (WITH_SUM) or count crosses the target, with the
-// count / sum strictly above it.  my_cnt: elements of the crossing bin in this thread's sweep, or -1 if not counted.
+// count / sum strictly above it.
 // Returns false when all scores are zero (WITH_SUM only).
-template <int NTH, bool COH, bool WITH_SUM>
-__device__ bool crossing_key(const KeySrc<NTH, COH>& keys, uint32_t cnt_target, int my_cnt, TailShared& sh, uint32_t& key_out,
+template <int NTH, bool WITH_SUM>
+__device__ bool crossing_key(const KeySrc<NTH>& keys, uint32_t cnt_target, TailShared& sh, uint32_t& key_out,
                              uint32_t& base_cnt, unsigned long long& base_sum, unsigned long long& target) {
     target = WITH_SUM ? sh.target : (unsigned long long)cnt_target;
     if (WITH_SUM && target == 0ull) return false;
@@ -296,7 +272,7 @@ __device__ bool crossing_key(const KeySrc<NTH, COH>& keys, uint32_t cnt_target, 
         __syncthreads();
         prefix = sh.sole_key;
     } else if (in_bin <= (uint32_t)kSelMaxCand) {
-        const int nl = gather_bin<NTH>(keys, bin, my_cnt, sh);
+        const int nl = gather_bin<NTH>(keys, bin, sh);
         descend_low<NTH, WITH_SUM>(ListSrc<NTH>{sh.list, nl}, target, sh, prefix, base_cnt, base_sum);
     } else {
         descend_low<NTH, WITH_SUM>(keys, target, sh, prefix, base_cnt, base_sum);
@@ -393,7 +369,7 @@ __device__ uint32_t input_flags(const float* __restrict__ mass, const float* __r
 
 // One unit, one workgroup of NTH threads: k from (mass, hm), T from (rank, hr) -> idx, k_out.
 // lds_keys: key_cap words of LDS (key_cap a multiple of 32).  rank == mass (and hr null): one vector for both steps.
-template <int NTH, bool COH>
+template <int NTH>
 __device__ void select_tail(const float* __restrict__ mass, const float* __restrict__ rank, int n, double tau,
                             const unsigned long long* __restrict__ hm, const uint32_t* __restrict__ hr,
                             int32_t* __restrict__ idx, int32_t* __restrict__ k_out, uint32_t* lds_keys, int key_cap,
@@ -404,41 +380,17 @@ __device__ void select_tail(const float* __restrict__ mass, const float* __restr
         for (int j = tid; j < n; j += NTH) idx[j] = j;
         return;
     }
-    const bool in_lds = n <= key_cap;
     const bool two = rank != mass;
-    constexpr int kPre = 8;                                  // values of the second vector a thread holds while the first is in use
-    const bool pre_rank = in_lds && two && n <= kPre * NTH;
-    // everything the first step needs from memory is requested at once: both tables, the first vector, and (short
-    // vectors) the second vector, which waits in registers
-    TableRegs<NTH> tm, tr;
-    table_load<NTH, COH>(hm, nullptr, tm);
-    if (two) table_load<NTH, COH>(hm, hr, tr);
-    float pre[kPre];
-    if (pre_rank) {
-#pragma unroll
-        for (int q = 0; q < kPre; ++q) pre[q] = sel_ld<COH>(rank + min(tid + q * NTH, n - 1));
-    }
+    TableRegs<NTH> tm, tr;                                   // both tables are requested at once
+    table_load<NTH>(hm, nullptr, tm);
+    if (two) table_load<NTH>(hm, hr, tr);
     // ---- how many (Eq. (7)) ----
     table_cross<NTH, true>(tm, true, tau, 0u, sh);
-    const uint32_t bin_m = sh.sel_digit;                     // garbage when every score is zero: unused then
-    int my_cnt = -1;
-    if (in_lds) {
-        // keys into LDS; the elements of the crossing bin are counted on the way
-        my_cnt = 0;
-#pragma unroll 8
-        for (int j = tid; j < n; j += NTH) {
-            const uint32_t key = orderable(sel_ld<COH>(mass + j));
-            lds_keys[j] = key;
-            my_cnt += (key >> kSelBinShift) == bin_m ? 1 : 0;
-        }
-        __syncthreads();
-    }
     int k = 1;
     {
         uint32_t key, base_cnt;
         unsigned long long base_sum, target;
-        const KeySrc<NTH, COH> mk{in_lds ? lds_keys : nullptr, mass, n};
-        if (crossing_key<NTH, COH, true>(mk, 0u, my_cnt, sh, key, base_cnt, base_sum, target)) {
+        if (crossing_key<NTH, true>(KeySrc<NTH>{mass, n}, 0u, sh, key, base_cnt, base_sum, target)) {
             const unsigned long long qv = fixed40_of_key(key);
             const unsigned long long need = target - base_sum;              // >= 1
             k = (int)(base_cnt + (qv ? (need + qv - 1) / qv : 1ull));
@@ -453,36 +405,10 @@ __device__ void select_tail(const float* __restrict__ mass, const float* __restr
     __syncthreads();
     // ---- which (Eq. (9)): k-th largest normalised score v*, ties to the lower index ----
     table_cross<NTH, false>(two ? tr : tm, !two, tau, (uint32_t)k, sh);
-    const uint32_t bin_r = sh.sel_digit;
-    if (in_lds && two) {
-        my_cnt = 0;
-        if (pre_rank) {
-#pragma unroll
-            for (int q = 0; q < kPre; ++q) {
-                const int j = tid + q * NTH;
-                if (j < n) {
-                    const uint32_t key = orderable(pre[q]);
-                    lds_keys[j] = key;
-                    my_cnt += (key >> kSelBinShift) == bin_r ? 1 : 0;
-                }
-            }
-        } else {
-#pragma unroll 8
-            for (int j = tid; j < n; j += NTH) {
-                const uint32_t key = orderable(sel_ld<COH>(rank + j));
-                lds_keys[j] = key;
-                my_cnt += (key >> kSelBinShift) == bin_r ? 1 : 0;
-            }
-        }
-        __syncthreads();
-    } else {
-        my_cnt = -1;                                         // one vector for both steps: other bin, counted in the gather
-    }
     uint32_t vstar, cnt_gt;
     {
         unsigned long long unused, target;
-        const KeySrc<NTH, COH> rk{in_lds ? lds_keys : nullptr, rank, n};
-        crossing_key<NTH, COH, false>(rk, (uint32_t)k, my_cnt, sh, vstar, cnt_gt, unused, target);
+        crossing_key<NTH, false>(KeySrc<NTH>{rank, n}, (uint32_t)k, sh, vstar, cnt_gt, unused, target);
     }
     const uint32_t need_eq = (uint32_t)k - cnt_gt;           // ties at v* that are kept (>= 1)
     __syncthreads();
@@ -491,13 +417,11 @@ __device__ void select_tail(const float* __restrict__ mass, const float* __restr
     const int blk = min(key_cap, 32 * NTH);
     for (int b0 = 0; b0 < n; b0 += blk) {
         const int bn = min(blk, n - b0);
-        if (!in_lds) {
-            __syncthreads();
+        __syncthreads();
 #pragma unroll 8
-            for (int j = tid; j < bn; j += NTH) lds_keys[j] = orderable(sel_ld<COH>(rank + b0 + j));
-            __syncthreads();
-        }
-        emit_block<NTH>(in_lds ? lds_keys + b0 : lds_keys, b0, bn, vstar, need_eq, gt_run, eq_run, sh, idx);
+        for (int j = tid; j < bn; j += NTH) lds_keys[j] = orderable(rank[b0 + j]);
+        __syncthreads();
+        emit_block<NTH>(lds_keys, b0, bn, vstar, need_eq, gt_run, eq_run, sh, idx);
     }
 }
 

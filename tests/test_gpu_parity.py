@@ -154,6 +154,24 @@ def test_select_exact_on_synthetic_distributions():
     _select_case("blocks-of-equal-values", dup, dup[:, ::-1].copy(), 0.8)
 
 
+@pytest.mark.parametrize("n", [1, 2, 64, 1023, 1024, 1025, 2048, 3073, 6144, 6145, 12289, 20480, 24577, 28673, 32767, 32768, 32769])
+def test_select_with_keys_in_registers_at_the_edges_of_its_sizes(n):
+    """Either side of every number of keys per thread, and of the largest; scores far above and far below the octaves that
+    the first digit covers, more equal or nearly equal scores than the list of candidates holds, and ranks of zero that
+    the set has to reach down to."""
+    r = np.random.Generator(np.random.PCG64(n))
+    x = np.exp(r.normal(0, 2.2, (2, n)))
+    x = (x / x.sum(axis=1, keepdims=True)).astype(np.float32)
+    rk = (x * (1 + r.random((2, n)))).astype(np.float32)
+    _select_case(f"registers-n{n}", x, rk, 0.975)
+    _select_case(f"registers-low-n{n}", (x * np.float32(2.0 ** -12)).astype(np.float32), (rk * np.float32(2.0 ** -40)).astype(np.float32), 0.9)
+    _select_case(f"registers-high-n{n}", x, (rk * np.float32(2.0 ** 60)).astype(np.float32), 0.5)
+    near = (np.float32(1.0 / n) * (1 + r.integers(0, 50, (2, n)) * 2.0 ** -20)).astype(np.float32)
+    _select_case(f"registers-near-n{n}", near, near[:, ::-1].copy(), 0.6)
+    holes = np.where(r.random((2, n)) < 0.9, 0, rk).astype(np.float32)
+    _select_case(f"registers-holes-n{n}", x, holes, 0.975)
+
+
 def test_select_status_word_reports_inputs_outside_the_contract():
     """The optional status word: 0 for valid input, and one bit each for a sign-bit entry, a non-finite entry and a
     mass that sums to 2 or more; both forms of the call; the selection itself still runs (and, for the sign-bit
