@@ -2,8 +2,10 @@
 purely as device memory; the stream is torch's current stream."""
 from __future__ import annotations
 
+import array
 import ctypes as C
 import os
+import struct
 from typing import Optional, Sequence, Tuple
 
 import torch
@@ -119,30 +121,45 @@ def _dtype_code(t: torch.Tensor) -> int:
 def _strides3(t: Optional[torch.Tensor]) -> Tuple[int, int, int]:
     if t is None:
         return (0, 0, 0)
-    if t.dim() != 4 or t.stride(3) != 1:
+    st = t.stride()
+    if len(st) != 4 or st[3] != 1:
         raise ZipvlError(-1, "expected a [B,H,n,d] view with a contiguous last dimension")
-    return (t.stride(0), t.stride(1), t.stride(2))
+    return st[:3]
+
+
+_pack_dims = struct.Struct("6i9q").pack      # the layout of Dims; one packed copy is 5 us cheaper than filling the fields
 
 
 def dims_of(Q: Optional[torch.Tensor], K: Optional[torch.Tensor], V: Optional[torch.Tensor] = None, *,
             B=None, Hq=None, Hkv=None, n=None, d=None, dtype=None) -> Dims:
     """Fill a zipvl_dims from [B,H,n,d] tensors (any memory order with d contiguous)."""
     ref = Q if Q is not None else K
-    dm = Dims()
-    dm.B = B if B is not None else ref.shape[0]
-    dm.Hq = Hq if Hq is not None else (Q.shape[1] if Q is not None else K.shape[1])
-    dm.Hkv = Hkv if Hkv is not None else (K.shape[1] if K is not None else dm.Hq)
-    dm.n = n if n is not None else ref.shape[2]
-    dm.d = d if d is not None else ref.shape[3]
-    dm.dtype = dtype if dtype is not None else _dtype_code(ref)
-    dm.q_strides = (C.c_int64 * 3)(*_strides3(Q))
-    dm.k_strides = (C.c_int64 * 3)(*_strides3(K))
-    dm.v_strides = (C.c_int64 * 3)(*_strides3(V))
-    return dm
+    if ref is not None:
+        sh = ref.shape
+        if B is None:
+            B = sh[0]
+        if n is None:
+            n = sh[2]
+        if d is None:
+            d = sh[3]
+    if Hq is None:
+        Hq = Q.shape[1] if Q is not None else K.shape[1]
+    if Hkv is None:
+        Hkv = K.shape[1] if K is not None else Hq
+    if dtype is None:
+        dtype = _dtype_code(ref)
+    qs, ks, vs = _strides3(Q), _strides3(K), _strides3(V)
+    try:
+        return Dims.from_buffer_copy(_pack_dims(B, Hq, Hkv, n, d, dtype, *qs, *ks, *vs))
+    except struct.error:                                  # out of a field's range: ctypes wraps it, and the library refuses it
+        dm = Dims()
+        dm.B, dm.Hq, dm.Hkv, dm.n, dm.d, dm.dtype = B, Hq, Hkv, n, d, dtype
+        dm.q_strides, dm.k_strides, dm.v_strides = (C.c_int64 * 3)(*qs), (C.c_int64 * 3)(*ks), (C.c_int64 * 3)(*vs)
+        return dm
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
 def _dense(*tensors):
@@ -152,8 +169,23 @@ def _dense(*tensors):
             raise ZipvlError(-1, f"expected a contiguous tensor, got strides {tuple(t.stride())} for shape {tuple(t.shape)}")
 
 
-def _stream() -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """Handle of torch's current stream on the current device (without building a torch.cuda.Stream for it)."""
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
+
+
+def _int32_array(values: Sequence[int]):
+    """`values` as a C array of int32."""
+    if type(values) in (list, tuple):
+        try:
+            a = array.array("i", values)
+            return (C.c_int32 * len(a)).from_buffer(a), len(a)
+        except (TypeError, OverflowError, ValueError):   # no plain int32 numbers, or none at all
+            pass
+    v = [int(p) for p in values]
+    return (C.c_int32 * max(len(v), 1))(*v), len(v)
 
 
 def workspace_bytes(op: int, dims: Dims, m: int = 0) -> int:
@@ -171,16 +203,15 @@ def zipvl_score(Q: torch.Tensor, K: torch.Tensor, probe_pos: Sequence[int], soft
     lib = load_library()
     dm = dims_of(Q, K)
     units = dm.B * (dm.Hq if flags & SCORE_PER_QHEAD else dm.Hkv)
-    pp = [int(p) for p in probe_pos]
-    arr = (C.c_int32 * max(len(pp), 1))(*pp)
+    probes, m = _int32_array(probe_pos)
     if mass is None:
         mass = torch.empty((units, dm.n), dtype=torch.float32, device=Q.device)
     if rank is None and want_rank:
         rank = torch.empty((units, dm.n), dtype=torch.float32, device=Q.device)
     if ws is None:
-        ws = _workspace(workspace_bytes(OP_SCORE, dm, len(pp)), Q.device)
+        ws = _workspace(workspace_bytes(OP_SCORE, dm, m), Q.device)
     _dense(mass, rank)
-    _check(lib.zipvl_score(_ptr(Q), _ptr(K), C.byref(dm), arr, len(pp), float(softmax_scale), int(flags),
+    _check(lib.zipvl_score(_ptr(Q), _ptr(K), C.byref(dm), probes, m, float(softmax_scale), int(flags),
                            _ptr(mass), _ptr(rank), _ptr(ws), ws.numel(), _stream()))
     return mass, rank
 
