@@ -83,7 +83,6 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     if (tid < ZIPVL_MAX_PROBES) sp[tid] = probes.pos[tid];           // -1 beyond m
     __syncthreads();
     const int Pmin = sp[0];
-    const bool has_pad = m < np;
 
     // waves -> tasks.  Fewer tasks than waves: KS waves share a task and take the key blocks slot, slot + KS, ...
     const bool few = NT < NWV;
@@ -147,27 +146,49 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             for (int cc = 0; cc < CH; ++cc) qf[cc] = load16(qp + cc * Elem<T>::kPerChunk);
         }
         const int Pm = sp[nb * 32 + i];                              // PASS 1: position of this lane's probe (-1: padding)
+        // the first and last probe of this wave's block (sp ascends): its tiles up to the first need no mask, those past the
+        // last are empty.  64 random probes put the first of all 128 near token 0, and every tile was masked.
+        const int Pfirst = __builtin_amdgcn_readfirstlane(nb * 32 + 32 <= m ? sp[nb * 32] : -1);
+        const int Plast = __builtin_amdgcn_readfirstlane(sp[min(nb * 32 + 31, m - 1)]);
 
         if (PASS == 2) {
-            // merge the chunk statistics of this task's 32 rows: lane = (row, half of the chunks)
-            float M = -INFINITY, L = 0.f;
-            const float2* p = partial + (int64_t)bh * nsplit * np + nb * 32;     // wave-uniform base; the rest fits 32 bits (host check)
-            for (int s0 = h; s0 < nsplit; s0 += 16) {                // 8 independent loads per lane and round (16: 47 -> 53 us for the 18432-token pass pair, 32 spills)
-                float2 v[8];
+            // Merge the chunk statistics of this task's 32 rows: lane = (pair of rows, quarter of the chunks), 16 bytes a load, eight
+            // loads in flight, one exponential per statistic.  28 heads on 4, n = 18432: a workgroup reads 229 KB of them, the
+            // prologue took 9.9 of pass 2's 23 us with 8-byte loads and pairwise merges, 7.0 so (a CU takes in some 40 GB/s).
+            const floatx4* p = reinterpret_cast<const floatx4*>(partial + (int64_t)bh * nsplit * np + nb * 32);   // wave-uniform base; the rest fits 32 bits (host check)
+            const int pr = lane & 15, cg = lane >> 4;
+            float M[2] = {-INFINITY, -INFINITY}, L[2] = {0.f, 0.f};
+            for (int s0 = cg; s0 < nsplit; s0 += 32) {
+                floatx4 v[8];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    const int s = s0 + 2 * q;
-                    v[q] = s < nsplit ? p[s * np + i] : make_float2(-INFINITY, 0.f);
+                for (int q = 0; q < 8; ++q) v[q] = p[min(s0 + 4 * q, nsplit - 1) * (np / 2) + pr];
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    float top = M[r];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) top = fmaxf(top, v[q][2 * r]);             // a chunk read twice changes nothing
+                    const float off = top > -INFINITY ? top : 0.f;
+                    float sum = L[r] * fast_exp2((M[r] - off) * c);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        sum = fmaf(s0 + 4 * q < nsplit ? v[q][2 * r + 1] : 0.f, fast_exp2((v[q][2 * r] - off) * c), sum);
+                    M[r] = top; L[r] = sum;
                 }
-#pragma unroll
-                for (int q = 0; q < 8; ++q) merge_stats(M, L, v[q].x, v[q].y, c);
             }
-            merge_stats(M, L, __shfl_xor(M, 32), __shfl_xor(L, 32), c);
-            if (active && slot == 0 && h == 0)
-                row_bias[ts][i] = (nb * 32 + i < m && L > 0.f) ? M * c + __log2f(L) : INFINITY;
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                merge_stats(M[r], L[r], __shfl_xor(M[r], 16), __shfl_xor(L[r], 16), c);
+                merge_stats(M[r], L[r], __shfl_xor(M[r], 32), __shfl_xor(L[r], 32), c);
+                if (active && slot == 0 && cg == 0)
+                    row_bias[ts][2 * pr + r] = (nb * 32 + 2 * pr + r < m && L[r] > 0.f) ? M[r] * c + __log2f(L[r]) : INFINITY;
+            }
             __syncthreads();
         }
 
+        // The probe rows have to be here now.  Left to the tile loop, the compiler's wait for them stands in front of every
+        // tile's first product and, not knowing of the stage loads, waits for those just requested too.
+#pragma unroll
+        for (int cc = 0; cc < CH; ++cc) asm volatile("" : "+v"(qf[cc]));
         float m_run = -INFINITY, l_run = 0.f;                        // PASS 1
         // add the tasks' column sums of stage s (PASS 2) in task order and write the scores of its keys
         // (taken by the workgroup's last threads first: with more waves than tasks those waves are otherwise idle)
@@ -177,7 +198,11 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             const int keys = min(min(blk1 * 32, n) - row0, SK);
             for (int t = kThreads - 1 - tid; t < keys; t += kThreads) {
                 const int j = row0 + t;
-                float a = (rd && j < n_eff) ? mass[(int64_t)u * n + j] : 0.f;     // tasks of earlier rounds
+                float a = 0.f;
+                if (rd && j < n_eff) {                               // tasks of earlier rounds
+                    a = mass[(int64_t)u * n + j];
+                    asm volatile("" : "+v"(a));                      // waited for here and not, with the stages in flight, on every path
+                }
                 if (j < n_eff)
                     for (int q = 0; q < ntr; ++q) a += colbuf[buf][q][t];
                 if (rd + 1 < rounds) {
@@ -215,17 +240,27 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
 #pragma unroll 1
                 for (int kb = slot; kb < KBS && sblk + kb < blk1; kb += KS) {
                     const int jb = (sblk + kb) * 32;
-                    if (PASS == 2 && jb >= n_eff) {                  // no probe row sees these keys
-                        if (h == 0) colbuf[buf][ts][kb * 32 + i] = 0.f;
+                    if (jb > Plast) {                                // no probe row of the block sees these keys
+                        if (PASS == 2 && h == 0) colbuf[buf][ts][kb * 32 + i] = 0.f;
                         continue;
                     }
                     const char* krow = kb0 + (kb * 32 + i) * RB;
                     auto kfrag = [&](int cc) { return *reinterpret_cast<const uintx4*>(krow + swz_chunk(2 * cc + h, k_row_swizzle<RB>(i))); };
                     floatx16 acc = {0};
-                    const bool masked = has_pad || jb + 31 > Pmin;  // wave-uniform
-                    if (PASS == 1) {
+                    // bf16: the fragments of the key block are read ahead of the products (six while 128 registers hold no more; two at
+                    // a time: 14 heads on 2, n = 33000, m = 128 84.7 -> 80.3 us); an fp32 one feeds four products of 64 cycles
+                    constexpr int kReads = C::E == 4 ? 1 : CH == 8 && PASS == 2 && NWV == 16 ? 6 : CH;
+                    uintx4 kf[CH];
 #pragma unroll
-                        for (int cc = 0; cc < CH; ++cc) acc = mma_frag<T>(kfrag(cc), qf[cc], acc);
+                    for (int cc = 0; cc < kReads; ++cc) kf[cc] = kfrag(cc);
+                    if (C::E == 2) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int cc = 0; cc < CH; ++cc) {
+                        if (cc + kReads < CH) kf[cc + kReads] = kfrag(cc + kReads);
+                        acc = PASS == 1 ? mma_frag<T>(kf[cc], qf[cc], acc) : mma_frag<T>(qf[cc], kf[cc], acc);
+                    }
+                    const bool masked = jb + 31 > Pfirst;            // wave-uniform
+                    if (PASS == 1) {
                         // acc[r]: key jb + acc_row(r, h), probe column nb*32 + i  (raw logit)
                         float sv[16], mx = -INFINITY;
 #pragma unroll
@@ -247,8 +282,6 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                             m_run = m_new;
                         }
                     } else {
-#pragma unroll
-                        for (int cc = 0; cc < CH; ++cc) acc = mma_frag<T>(qf[cc], kfrag(cc), acc);
                         // acc[r]: probe row nb*32 + acc_row(r, h), key column jb + i; rb[r]: exponent offset of that row
                         float rb[16];
 #pragma unroll

@@ -282,6 +282,26 @@ def test_scores_match_oracle(case):
     say(f"  worst relative score error so far {WORST_SCORE_ERR['rel']:.2e} (bound 1e-5)")
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("name", ["first-rows", "block-ends-early", "one-past-a-block", "straddling", "last-row-only"])
+def test_scores_where_blocks_of_probes_end(name, dtype):
+    """Blocks of 32 probes that see few keys, all keys, none of most tiles, or end on the edge of a 32-key tile; the same
+    bound as above."""
+    n, tail = 1111, list(range(1111 - 40, 1111))
+    pp = {"first-rows": list(range(32)) + [n - 1],                      # a block wholly at the start, one probe in the next
+          "block-ends-early": list(range(0, 320, 10)) + list(range(400, 432)) + tail,
+          "one-past-a-block": list(range(31, 64)) + list(range(95, 128)),   # nothing past token 127 is seen
+          "straddling": [0, 31, 32, 33, 63, 64, 500] + list(range(512, 512 + 64)) + tail,
+          "last-row-only": [n - 1]}[name]
+    say(f"score blocks case={name} dtype={dtype}")
+    w = make_custom(1, 6, 2, n, 128, dtype, seed=len(pp), m=len(pp), probe_pos=np.array(pp, dtype=np.int32))
+    mass, rank = z.zipvl_score(dev(w.Q, dtype), dev(w.K, dtype), w.probe_pos, w.scale)
+    torch.cuda.synchronize()
+    mo, ro = oz.token_scores(w.Q[0], w.K[0], w.probe_pos, w.scale)
+    assert_scores_close(host64(mass), mo, dtype, "mass")
+    assert_scores_close(host64(rank), ro, dtype, "rank")
+
+
 # ------------------------------------------------------------------ attention
 def _attention_case(B, Hq, Hkv, n, d, dtype, ks, seed=0, flags=0, dense=False, reshape_inputs=None):
     G = Hq // Hkv
