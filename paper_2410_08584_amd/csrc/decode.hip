@@ -159,11 +159,9 @@ __device__ __forceinline__ void merge_splits(const PartialOut& po, int G, int ns
     }
 }
 
-// Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state (one head).
-template <int D, bool COHERENT>
-__device__ __forceinline__ void write_partial(float m, float l, float (&o)[D / 16], float (&red)[4][1][D + 2], const PartialOut& po, int split) {
-    constexpr int EPL = D / 16;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
+// Merge the states of a wave's four row groups (16 lanes each), result in all four.
+template <int EPL>
+__device__ __forceinline__ void merge_row_groups(float& m, float& l, float (&o)[EPL]) {
 #pragma unroll
     for (int off = 16; off <= 32; off <<= 1) {
         const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
@@ -172,6 +170,14 @@ __device__ __forceinline__ void write_partial(float m, float l, float (&o)[D / 1
         for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[e], off);
         merge_state<EPL>(m, l, o, m2, l2, o2);
     }
+}
+
+// Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state (one head).
+template <int D, bool COHERENT>
+__device__ __forceinline__ void write_partial(float m, float l, float (&o)[D / 16], float (&red)[4][1][D + 2], const PartialOut& po, int split) {
+    constexpr int EPL = D / 16;
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
+    merge_row_groups<EPL>(m, l, o);
     if (rg == 0) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) red[w][0][sub * EPL + e] = o[e];
@@ -735,238 +741,286 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
     combine_waves<D, GT, kDecWaves<GT>>(red, heads, PartialOut(part, D, u, G, rule.most, rule.units), gbase, split);
 }
 
-// ---- the same, for one head per group: 4 lanes per row.
-// A 4-bit row of d = 128 is 64 bytes: with 16 lanes per row a lane would hold 4 bytes and the per-row work
-// (cross-lane sums, softmax update) would dominate.  Here a lane holds d/4 consecutive elements (16 bytes of 4-bit
-// codes, 8 bytes of 2-bit codes), a wave covers 16 rows per step, and the arithmetic runs on the codes:
-//   q . (zero + scale * code) = zero * sum(q) + scale * (q . code),
-//   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j zero_j + sum_j (p_j scale_j) code_j,
-// i.e. one FMA and 0.6 instructions of unpacking per element and side (MixCodes; 1.25 to 1.5 with conversions to fp32:
-// 170 us instead of 152 for four layers of 128 units x 8192 rows).  The softmax offset follows the running maximum lazily
-// (moves only when exceeded by 2^kDecLazyLog2), so the accumulators are rescaled on few rows.
+// ---- the same, for one head per group: integer matrix products on the codes.
+// A group of one head leaves 15 of 16 columns of a floating-point tile empty, and the vector units need 1.6 instructions per
+// element and side.  The codes are small integers, so both products run on v_mfma_i32_16x16x64_i8, the other operand cut
+// into four signed bytes of a 30-bit fixed-point number (the columns that one head leaves empty): every product and sum is
+// exact, the only rounding is that of a query element to 2^-29 of the largest and of a weight to 2^-27 of the largest.
+// The codes enter about their middle, 2 code - 15 or 2 code - 3 (in the integer sums, with the sums of the bytes alone):
+//   q . (zero + scale * code) = (zero + scale * mid) * sum(q) + scale / 2 * (q . (2 code - 2 mid)),
+//   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j (zero_j + scale_j * mid) + sum_j (p_j scale_j) / 2 (2 code_j - 2 mid),
+// either term of the size of the result; with plain codes they cancel (1.8e-6 of the output instead of 0.39e-6).
+// A wave takes 64 rows at a time:
+//   scores   A = the bytes of q (row m of the tile: byte m % 4), B = 16 cached rows, lane (n, kk) unpacking a quarter kk of the
+//            codes of row n (1.5 instructions per 4 codes): the lane's accumulators are the four bytes' sums of row n, and
+//            lane L keeps those of row L.
+//   weights  one row per lane: exponential, p * scale rounded to fixed point, its bytes to LDS.
+//   output   A = the bytes of the 64 weights, B = codes of 16 channels x 64 rows, from the row-major codes in LDS through the
+//            transposing 4-bit read (2-bit codes: two channels a nibble).
+// The exponent offset is the wave's and moves lazily; it and the fixed-point scale of the weights are fixed until a row
+// outgrows them, and then the integer sums go over to fp32.
+// Four layers of 128 units x 8192 rows: 115 us a step, some 20 us a layer in this kernel (151 and 33 on the vector units).
+// Error of the output against float64, fp32 queries, n = 300 to 30000: 3.9e-7 in the mean (2.4e-6 on the vector units).
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef int intx2 __attribute__((ext_vector_type(2)));
 
-// sum over the 4 lanes of a quad (lanes 4i .. 4i+3), result in all four, by two in-register lane permutes
-__device__ __forceinline__ float quad_sum(float v) {
-    int x = __float_as_int(v);
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
-    x = __float_as_int(v);
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
-    return v;
+// Over the wave by lane permutes in registers (a shuffle through LDS takes some 100 clocks a step): shifts inside rows of 16
+// lanes, then across the rows; the last lane has it all.
+template <typename F>
+__device__ __forceinline__ float wave_reduce(float v, float none, F&& f) {
+    auto moved = [&](auto ctrl, auto rows) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), decltype(ctrl)::value, decltype(rows)::value, 0xF, false));
+    };
+    using std::integral_constant;
+    v = f(v, moved(integral_constant<int, 0x111>(), integral_constant<int, 0xF>()));
+    v = f(v, moved(integral_constant<int, 0x112>(), integral_constant<int, 0xF>()));
+    v = f(v, moved(integral_constant<int, 0x114>(), integral_constant<int, 0xF>()));
+    v = f(v, moved(integral_constant<int, 0x118>(), integral_constant<int, 0xF>()));
+    v = f(v, moved(integral_constant<int, 0x142>(), integral_constant<int, 0xA>()));
+    v = f(v, moved(integral_constant<int, 0x143>(), integral_constant<int, 0xC>()));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, -INFINITY, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, 0.f, [](float a, float b) { return a + b; }); }
 
-// Codes as fp16 numbers without a conversion: a masked field of a word is, in either half, the subnormal
-// code * 2^(shift - 24), which v_fma_mix_f32 multiplies as it is; the other factor makes up for the powers of two, exactly.
-// Pair k of a word: elements k and k + PER / 2 in its low and high half.
-typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
-template <int BITS> struct MixCodes {
-    static constexpr int PER = 32 / BITS, PAIRS = PER / 2;
-    static constexpr int FIT = 10 / BITS;                                // fields that lie inside the ten mantissa bits
-    static constexpr int MOVE = BITS == 4 ? 8 : FIT * BITS;              // the others are shifted down by this
-    static constexpr int KEPT = MOVE / BITS;                             // pairs taken before the shift
-    __host__ __device__ static constexpr int shift(int k) { return BITS * (k % KEPT); }
-    __device__ static __forceinline__ halfx2 pair(uint32_t w, int k) {
-        const uint32_t x = k < KEPT ? w : w >> MOVE;
-        return __builtin_bit_cast(halfx2, x & ((uint32_t)((1u << BITS) - 1u) * 0x00010001u << shift(k)));
+// |x| < 2^30 as four signed bytes of weight 256^i, byte i in bits 8 i ...
+__device__ __forceinline__ uint32_t signed_bytes(int x) { return ((uint32_t)x + 0x00808080u) ^ 0x00808080u; }
+// and back, from sums over each byte
+__device__ __forceinline__ float from_bytes(const intx4& s) {
+    return fmaf(fmaf(fmaf((float)s[3], 256.f, (float)s[2]), 256.f, (float)s[1]), 256.f, (float)s[0]);
+}
+// exponent e of a power of two with |x| * 2^e in [2^(bits - 1), 2^bits); 0 for x = 0
+__device__ __forceinline__ int fixed_exponent(float x, int bits) {
+    return x > 0.f ? max(-100, min(100, bits - (int)((__float_as_uint(x) >> 23) & 255u) + 126)) : 0;
+}
+__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
+
+// Rows of BITS-bit codes as a wave of decode_q1_partial_kernel takes them.
+template <int D, int BITS> struct CodeRows {
+    static constexpr int RB = D * BITS / 8;                  // bytes of a row
+    static constexpr int CPR = RB / 16;                      // 16-byte chunks of a row = V loads per lane for 64 rows
+    static constexpr int NW = RB / 16;                       // dwords of a quarter of a row
+    static constexpr int ND = D / 16;                        // dwords of one code per byte that they unpack to
+    // chunk swizzle of the rows in LDS: 16 rows read at one 8-byte piece fall on different banks, or on the two halves of one chunk
+    __device__ static __forceinline__ int swizzle(int row) { return CPR == 4 ? (row >> 2) & 3 : CPR == 2 ? (row >> 3) & 1 : 0; }
+    // one code per byte; the same order of channels as query_operand
+    __device__ static __forceinline__ void unpack(const uint32_t (&w)[NW], uint32_t (&b)[ND]) {
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int s = 0; s < 8 / BITS; ++s) b[s * NW + i] = (w[i] >> (BITS * s)) & (BITS == 4 ? 0x0F0F0F0Fu : 0x03030303u);
     }
-    __host__ __device__ static constexpr float field(int e) { return (float)(1u << shift(e % PAIRS)); }   // of element e of a word
+    // d: the bytes of this lane's quarter of the channels in their own order
+    __device__ static __forceinline__ void query_operand(const uint32_t (&d)[ND], uint32_t (&a)[ND]) {
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int s = 0; s < 8 / BITS; ++s) {
+                if constexpr (BITS == 4) {
+                    a[s * NW + i] = __builtin_amdgcn_perm(d[2 * i + 1], d[2 * i], 0x06040200u + 0x01010101u * s);
+                } else {
+                    const uint32_t sel = (uint32_t)s | (uint32_t)(4 + s) << 8;
+                    const uint32_t lo = __builtin_amdgcn_perm(d[4 * i + 1], d[4 * i], sel), hi = __builtin_amdgcn_perm(d[4 * i + 3], d[4 * i + 2], sel);
+                    a[s * NW + i] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+                }
+            }
+    }
 };
-static_assert(MixCodes<4>::PAIRS <= 2 * MixCodes<4>::KEPT && MixCodes<2>::PAIRS <= 2 * MixCodes<2>::KEPT, "one shift reaches every field");
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_q4_partial_kernel(
+__global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kernel(
     const T* __restrict__ q, QTensor Kq, QTensor Vq, const int32_t* __restrict__ len_hi, const int32_t* __restrict__ len_lo,
     int cap_hi, int cap_lo, const T* __restrict__ Kt, const T* __restrict__ Vt, const int32_t* __restrict__ len_t, int cap_t,
     float c, float* __restrict__ part, SplitRule rule)
 {
-    constexpr int EPL = D / 4;                               // elements per lane
-    __shared__ float red[4][1][D + 2];
+    constexpr int NG = D / 16, ND = D / 16, NM = D / 64;     // output blocks of 16 channels; dwords and products of an operand
+    __shared__ __attribute__((aligned(16))) uint8_t vrows[4][64 * D / 2];    // per wave: V codes of its 64 rows
+    __shared__ __attribute__((aligned(16))) uint8_t wbytes[4][4 * 64];       // per wave: byte i of the 64 weights at 64 i
+    __shared__ __attribute__((aligned(16))) uint8_t qbytes[4][4 * D];        // per wave: byte i of the query at D i
+    __shared__ float red[12][1][D + 2];                      // per wave: states of the 4-bit, the 2-bit and the appended rows
     const int u = blockIdx.y, split = blockIdx.x, nsplit = rule.most;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 3, rg = lane >> 2;   // 16 rows per wave step
-    float qv[EPL], part_sum = 0.f;
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, n = lane & 15, kk = lane >> 4;
+    const int L4 = max(0, min(len_hi[u], cap_hi)), L2 = max(0, min(len_lo[u], cap_lo));
+    // blocks of 64 rows, the 4-bit ones first, dealt to the splits in equal shares and to their waves in turn
+    const int B4 = (L4 + 63) >> 6, B2 = (L2 + 63) >> 6, per = (B4 + B2 + nsplit - 1) / nsplit;
+    const int b0 = split * per, b1 = min(B4 + B2, b0 + per);
+
+    float qsum = 0.f, q_inv = 1.f;                           // sum of the scaled query; 1 / its fixed-point scale
+    auto prepare_query = [&]() {
+        float f[D / 64], mx = 0.f;
 #pragma unroll
-    for (int e8 = 0; e8 < EPL / 8; ++e8) {
-        float f[8];
-        RowChunk<T, 8>::load(q + (int64_t)u * D + sub * EPL + 8 * e8, f);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { qv[8 * e8 + e] = f[e] * c; part_sum += qv[8 * e8 + e]; }
-    }
-    const float qsum = quad_sum(part_sum);                   // sum over the whole row of the scaled query
-    float m = -INFINITY, l = 0.f, zacc = 0.f, o[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) o[e] = 0.f;
-    // one cached row: dot(qv) = q . (this lane's part of the K row); then o += (p * vs) (V codes), zacc += p * vz
-    auto attend = [&](bool valid, auto&& dot, float ks, float kz, auto&& axpy, float vs, float vz) {
-        const float dsum = quad_sum(dot(qv));
-        const float sc = valid ? fmaf(ks, dsum, kz * qsum) : -INFINITY;
-        const bool grow = sc > m + kDecLazyLog2;
-        if (__any(grow)) {
-            const float m_new = grow ? sc : m;
-            const float a = grow ? fast_exp2(m - m_new) : 1.f;      // 0 on a row group's first row (m = -inf)
-            l *= a; zacc *= a;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) o[e] *= a;
-            m = m_new;
+        for (int e = 0; e < D / 64; ++e) {
+            f[e] = (float)q[(int64_t)u * D + 64 * e + lane] * c;
+            qsum += f[e];
+            mx = fmaxf(mx, fabsf(f[e]));
         }
-        const float p = valid ? fast_exp2(sc - m) : 0.f;
-        l += p;
-        zacc = fmaf(p, vz, zacc);
-        axpy(p * vs, o);
+        qsum = wave_sum(qsum);
+        const int ex = fixed_exponent(wave_max(mx), 29);
+        q_inv = power_of_two(-ex);
+#pragma unroll
+        for (int e = 0; e < D / 64; ++e) {
+            const uint32_t z = signed_bytes(__float2int_rn(f[e] * power_of_two(ex)));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qbytes[w][i * D + 64 * e + lane] = (uint8_t)(z >> (8 * i));
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
-    // a row's codes (BITS wide, NW words per lane): dot with the queries, whose elements carry 1 / MixCodes::field, and
-    // weighted sum into the outputs
-    auto attend_codes = [&](auto bits, bool valid, const auto& kw, float ks, float kz, const auto& vw, float vs, float vz) {
-        using M = MixCodes<decltype(bits)::value>;
-        constexpr int NW = EPL / M::PER;
-        attend(valid, [&](const float (&qt)[EPL]) {
-            float d = 0.f;
+
+    // One part of the cache: blocks first, first + 4, ... below last (of 64 rows) of L rows -> the state red[out].
+    bool have_query = false;
+    auto attend_codes = [&](auto bits, const uint8_t* kc, const uint32_t* kp, const uint8_t* vc, const uint32_t* vp, int64_t base,
+                            int L, int first, int last, float* out) {
+        constexpr int BITS = decltype(bits)::value, kTwoMid = (1 << BITS) - 1;
+        using R = CodeRows<D, BITS>;
+        struct Block { uint32_t k[4][R::NW]; uintx4 v[R::CPR]; uint32_t kp, vp; };
+        auto fetch = [&](int blk, Block& x) {
+            const int r0 = blk * 64;                         // rows past the end re-read the last one and weigh nothing
 #pragma unroll
-            for (int i = 0; i < NW; ++i)
+            for (int t = 0; t < 4; ++t) load_words<R::NW>(kc + (base + min(r0 + 16 * t + n, L - 1)) * R::RB + kk * (R::RB / 4), x.k[t]);
 #pragma unroll
-                for (int k = 0; k < M::PAIRS; ++k) {
-                    const halfx2 x = M::pair(kw[i], k);
-                    d = fmaf(qt[i * M::PER + k], (float)x[0], d);
-                    d = fmaf(qt[i * M::PER + M::PAIRS + k], (float)x[1], d);
-                }
-            return d;
-        }, ks * 0x1p24f, kz, [&](float pv, float (&ot)[EPL]) {
-            float pk[M::KEPT];                                           // pv * 2^(24 - shift)
-#pragma unroll
-            for (int k = 0; k < M::KEPT; ++k) pk[k] = pv * (0x1p24f / M::field(k));
-#pragma unroll
-            for (int i = 0; i < NW; ++i)
-#pragma unroll
-                for (int k = 0; k < M::PAIRS; ++k) {
-                    const halfx2 x = M::pair(vw[i], k);
-                    float& a0 = ot[i * M::PER + k];
-                    float& a1 = ot[i * M::PER + M::PAIRS + k];
-                    a0 = fmaf(pk[k % M::KEPT], (float)x[0], a0);
-                    a1 = fmaf(pk[k % M::KEPT], (float)x[1], a1);
-                }
-        }, vs, vz);
-    };
-    // the queries' elements carry the factor of the codes they meet: powers of two, exact
-    auto rescale_queries = [&](auto&& factor) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) qv[e] *= factor(e);
-    };
-    using Four = std::integral_constant<int, 4>;
-    using Two = std::integral_constant<int, 2>;
-    rescale_queries([](int e) { return 1.f / MixCodes<4>::field(e % 8); });
-    int r_begin, r_end;
-    {   // important tokens, 4 bits
-        constexpr int NW = EPL * 4 / 32;
-        const int L = max(0, min(len_hi[u], cap_hi));
-        split_range64(L, split, nsplit, r_begin, r_end);
-        const int64_t base = (int64_t)u * cap_hi;
-        // the loads of the next 16 rows are issued before the current ones are consumed
-        uint32_t kw[NW], vw[NW], kp, vp;
-        auto fetch = [&](int r, uint32_t (&kw_)[NW], uint32_t (&vw_)[NW], uint32_t& kp_, uint32_t& vp_) {
-            const int64_t row = base + (r < r_end ? r : r_begin);
-            load_words<NW>(Kq.hi_codes + row * (D / 2) + sub * (NW * 4), kw_);
-            load_words<NW>(Vq.hi_codes + row * (D / 2) + sub * (NW * 4), vw_);
-            kp_ = Kq.hi_params[row];
-            vp_ = Vq.hi_params[row];
+            for (int p = 0; p < R::CPR; ++p) {
+                const int piece = p * 64 + lane;
+                x.v[p] = load16(vc + (base + min(r0 + piece / R::CPR, L - 1)) * R::RB + (piece % R::CPR) * 16);
+            }
+            const int64_t row = base + min(r0 + lane, L - 1);
+            x.kp = kp[row];
+            x.vp = vp[row];
         };
-        int r = r_begin + w * 16 + rg;
-        if (r - rg - w * 16 < r_end) fetch(r, kw, vw, kp, vp);
-        for (; r - rg - w * 16 < r_end; r += 64) {
-            const bool valid = r < r_end;
-            uint32_t kw2[NW], vw2[NW], kp2 = 0, vp2 = 0;
-            const bool more = r + 64 - rg - w * 16 < r_end;
-            if (more) fetch(r + 64, kw2, vw2, kp2, vp2);
-            float ks, kz, vs, vz;
-            unpack_params(kp, ks, kz);
-            unpack_params(vp, vs, vz);
-            attend_codes(Four(), valid, kw, ks, kz, vw, vs, vz);
-            if (more) {
+        float m = -INFINITY, l = 0.f, zacc = 0.f, ws = INFINITY, w_inv = 0.f, of[NG];     // m, ws, w_inv: of the wave
+        intx4 o[NG], ow = {0, 0, 0, 0};                       // sums of weight bytes times codes, and of the weight bytes
+        const intx4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 #pragma unroll
-                for (int i = 0; i < NW; ++i) { kw[i] = kw2[i]; vw[i] = vw2[i]; }
-                kp = kp2; vp = vp2;
+        for (int g = 0; g < NG; ++g) { of[g] = 0.f; o[g] = intx4{0, 0, 0, 0}; }
+        auto flush = [&](float a) {                          // integer sums -> fp32, which are then scaled by a
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                of[g] = fmaf(from_bytes(2 * o[g] - kTwoMid * ow), 0.5f * w_inv, of[g]) * a;
+                o[g] = intx4{0, 0, 0, 0};
             }
-        }
-    }
-    rescale_queries([](int e) { return MixCodes<4>::field(e % 8) / MixCodes<2>::field(e % 16); });
-    {   // the other tokens, 2 bits
-        constexpr int NW = EPL * 2 / 32;
-        const int L = max(0, min(len_lo[u], cap_lo));
-        split_range64(L, split, nsplit, r_begin, r_end);
-        const int64_t base = (int64_t)u * cap_lo;
-        // the loads of the next 16 rows are issued before the current ones are consumed
-        uint32_t kw[NW], vw[NW], kp, vp;
-        auto fetch = [&](int r, uint32_t (&kw_)[NW], uint32_t (&vw_)[NW], uint32_t& kp_, uint32_t& vp_) {
-            const int64_t row = base + (r < r_end ? r : r_begin);
-            load_words<NW>(Kq.lo_codes + row * (D / 4) + sub * (NW * 4), kw_);
-            load_words<NW>(Vq.lo_codes + row * (D / 4) + sub * (NW * 4), vw_);
-            kp_ = Kq.lo_params[row];
-            vp_ = Vq.lo_params[row];
+            ow = intx4{0, 0, 0, 0};
         };
-        int r = r_begin + w * 16 + rg;
-        if (r - rg - w * 16 < r_end) fetch(r, kw, vw, kp, vp);
-        for (; r - rg - w * 16 < r_end; r += 64) {
-            const bool valid = r < r_end;
-            uint32_t kw2[NW], vw2[NW], kp2 = 0, vp2 = 0;
-            const bool more = r + 64 - rg - w * 16 < r_end;
-            if (more) fetch(r + 64, kw2, vw2, kp2, vp2);
-            float ks, kz, vs, vz;
-            unpack_params(kp, ks, kz);
-            unpack_params(vp, vs, vz);
-            attend_codes(Two(), valid, kw, ks, kz, vw, vs, vz);
-            if (more) {
+        if (first < last) {
+            Block cur;
+            fetch(first, cur);
+            if (!have_query) prepare_query();
+            have_query = true;
+            uint32_t qa[ND];
+            {
+                uint32_t d[ND];
 #pragma unroll
-                for (int i = 0; i < NW; ++i) { kw[i] = kw2[i]; vw[i] = vw2[i]; }
-                kp = kp2; vp = vp2;
+                for (int i = 0; i < ND; ++i) d[i] = *reinterpret_cast<const uint32_t*>(&qbytes[w][(n & 3) * D + kk * (D / 4) + 4 * i]);
+                R::query_operand(d, qa);
             }
-        }
-    }
-    rescale_queries([](int e) { return MixCodes<2>::field(e % 16); });
-    if (Kt) {   // rows appended during decoding, as stored: "codes" are the values, scale 1, zero 0
-        const int L = max(0, min(len_t[u], cap_t));
-        split_range64(L, split, nsplit, r_begin, r_end);
-        const T* Kb = Kt + (int64_t)u * cap_t * D + sub * EPL;
-        const T* Vb = Vt + (int64_t)u * cap_t * D + sub * EPL;
-        for (int r = r_begin + w * 16 + rg; r - rg - w * 16 < r_end; r += 64) {
-            const bool valid = r < r_end;
-            const int rr = valid ? r : r_begin;
-            float kc[EPL], vc[EPL];
+            auto query = [&](int h) { return intx4{(int)qa[4 * h], (int)qa[4 * h + 1], (int)qa[4 * h + 2], (int)qa[4 * h + 3]}; };
+            intx4 qw = {0, 0, 0, 0};                         // sums of the query's bytes
 #pragma unroll
-            for (int e8 = 0; e8 < EPL / 8; ++e8) {
-                float f[8];
-                RowChunk<T, 8>::load(Kb + (int64_t)rr * D + 8 * e8, f);
+            for (int h = 0; h < NM; ++h) qw = __builtin_amdgcn_mfma_i32_16x16x64_i8(query(h), ones, qw, 0, 0, 0);
+            qw *= kTwoMid;
+            uint8_t* vb = vrows[w];
+            for (int blk = first; blk < last; blk += 4) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) kc[8 * e8 + e] = f[e];
-                RowChunk<T, 8>::load(Vb + (int64_t)rr * D + 8 * e8, f);
+                for (int p = 0; p < R::CPR; ++p) {
+                    const int piece = p * 64 + lane, r = piece / R::CPR;
+                    store16(vb + r * R::RB + ((piece % R::CPR) ^ R::swizzle(r)) * 16, cur.v[p]);
+                }
+                intx4 mine;                                  // lane L: of row L
 #pragma unroll
-                for (int e = 0; e < 8; ++e) vc[8 * e8 + e] = f[e];
+                for (int t = 0; t < 4; ++t) {
+                    uint32_t b[ND];
+                    R::unpack(cur.k[t], b);
+                    intx4 s = {0, 0, 0, 0};
+#pragma unroll
+                    for (int h = 0; h < NM; ++h)
+                        s = __builtin_amdgcn_mfma_i32_16x16x64_i8(query(h), intx4{(int)b[4 * h], (int)b[4 * h + 1], (int)b[4 * h + 2], (int)b[4 * h + 3]}, s, 0, 0, 0);
+                    if (t == 0 || kk == t) mine = s;
+                }
+                float ks, kz, vs, vz;
+                unpack_params(cur.kp, ks, kz);
+                unpack_params(cur.vp, vs, vz);
+                if (blk + 4 < last) fetch(blk + 4, cur);     // in flight while this block is worked on
+                const bool valid = blk * 64 + lane < L;
+                const float sc = valid ? fmaf(0.5f * ks * q_inv, from_bytes(2 * mine - qw), fmaf(0.5f * kTwoMid, ks, kz) * qsum) : -INFINITY;
+                if (__any(sc > m + kDecLazyLog2)) {
+                    const float top = wave_max(sc), a = m > -INFINITY ? fast_exp2(m - top) : 0.f;
+                    flush(a);
+                    l *= a; zacc *= a;
+                    m = top;
+                }
+                const float p = valid ? fast_exp2(sc - (m > -INFINITY ? m : 0.f)) : 0.f, wt = p * vs;
+                l += p;
+                zacc = fmaf(p, fmaf(0.5f * kTwoMid, vs, vz), zacc) + (wt - wt);      // NaN where a weight is no number
+                if (__any(fabsf(wt) * ws >= 0x1p30f)) {
+                    flush(1.f);
+                    const int ex = fixed_exponent(wave_max(fabsf(wt)), 28);
+                    ws = power_of_two(ex);
+                    w_inv = power_of_two(-ex);
+                }
+                const uint32_t z = signed_bytes(__float2int_rn(wt * ws));
+                // byte i of row `lane`, where the unpacked nibbles of a transposed read have that row
+                const int pos = 16 * kk + 8 * (n >> 3) + 4 * (n & 1) + ((n & 7) >> 1);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) wbytes[w][64 * i + pos] = (uint8_t)(z >> (8 * i));
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const uintx4 wa = load16(&wbytes[w][64 * (n & 3) + 16 * kk]);
+                const intx4 a4 = __builtin_bit_cast(intx4, wa);
+                ow = __builtin_amdgcn_mfma_i32_16x16x64_i8(a4, ones, ow, 0, 0, 0);
+                const int vrow = 16 * kk + n;
+#pragma unroll
+                for (int g = 0; g < R::RB / 8; ++g) {        // an 8-byte piece of 64 rows
+                    using lds_ptr = __attribute__((address_space(3))) intx2*;
+                    const uint8_t* at = vb + vrow * R::RB + ((g >> 1) ^ R::swizzle(vrow)) * 16 + (g & 1) * 8;
+                    const intx2 t2 = __builtin_amdgcn_ds_read_tr4_b64_v2i32((lds_ptr)at);
+                    const uint32_t x0 = (uint32_t)t2[0], x1 = (uint32_t)t2[1];
+                    constexpr uint32_t M = BITS == 4 ? 0x0F0F0F0Fu : 0x03030303u;
+                    if constexpr (BITS == 4) {
+                        o[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a4, intx4{(int)(x0 & M), (int)(x0 >> 4 & M), (int)(x1 & M), (int)(x1 >> 4 & M)}, o[g], 0, 0, 0);
+                    } else {
+                        o[2 * g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a4, intx4{(int)(x0 & M), (int)(x0 >> 4 & M), (int)(x1 & M), (int)(x1 >> 4 & M)}, o[2 * g], 0, 0, 0);
+                        o[2 * g + 1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a4, intx4{(int)(x0 >> 2 & M), (int)(x0 >> 6 & M), (int)(x1 >> 2 & M), (int)(x1 >> 6 & M)}, o[2 * g + 1], 0, 0, 0);
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
-            attend(valid, [&](const float (&qt)[EPL]) {
-                float d = 0.f;
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) d = fmaf(qt[e], kc[e], d);
-                return d;
-            }, 1.f, 0.f, [&](float pv, float (&ot)[EPL]) {
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) ot[e] = fmaf(pv, vc[e], ot[e]);
-            }, 1.f, 0.f);
+            flush(1.f);
+            l = wave_sum(l);
+            zacc = wave_sum(zacc);
         }
-    }
-    // fold the zero-point sum into the outputs, merge the 16 row groups of the wave, then the 4 waves
+        // all four quarters of the wave hold the same sums: each writes a quarter of the blocks
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) o[e] += zacc;
+        for (int g = 0; g < NG; ++g)
+            if (g % 4 == kk) out[BITS == 4 ? 16 * g + n : 32 * (g >> 1) + 2 * n + (g & 1)] = of[g] + zacc;
+        if (lane == 0) { out[D] = m; out[D + 1] = l; }
+    };
+    // this wave's first block at or after `from`
+    auto next_block = [&](int from) { const int behind = from - (b0 + w); return b0 + w + (behind > 0 ? (behind + 3) / 4 * 4 : 0); };
+    attend_codes(std::integral_constant<int, 4>(), Kq.hi_codes, Kq.hi_params, Vq.hi_codes, Vq.hi_params, (int64_t)u * cap_hi,
+                 L4, b0 + w, min(b1, B4), red[3 * w][0]);
+    attend_codes(std::integral_constant<int, 2>(), Kq.lo_codes, Kq.lo_params, Vq.lo_codes, Vq.lo_params, (int64_t)u * cap_lo,
+                 L2, next_block(B4) - B4, b1 - B4, red[3 * w + 1][0]);
+
+    // rows appended during decoding, as stored: 16 lanes per row, as in a cache without codes
+    float* out = red[3 * w + 2][0];
+    int r_begin = 0, r_end = 0;
+    if (Kt) split_range64(max(0, min(len_t[u], cap_t)), split, nsplit, r_begin, r_end);
+    if (r_begin < r_end) {
+        constexpr int EPL = D / 16;
+        float qv[EPL], m = -INFINITY, l = 0.f, o[EPL];
+        RowChunk<T, EPL>::load(q + (int64_t)u * D + n * EPL, qv);
 #pragma unroll
-    for (int off = 4; off <= 32; off <<= 1) {
-        const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
-        float o2[EPL];
+        for (int e = 0; e < EPL; ++e) { qv[e] *= c; o[e] = 0.f; }
+        const int64_t base = (int64_t)u * cap_t * D + n * EPL;
+        attend_rows<T, D>(Kt + base, Vt + base, nullptr, nullptr, nullptr, nullptr, -1, r_begin, r_end, tid >> 4, qv, m, l, o);
+        merge_row_groups<EPL>(m, l, o);
+        if (kk == 0) {
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[e], off);
-        merge_state<EPL>(m, l, o, m2, l2, o2);
-    }
-    if (rg == 0) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) red[w][0][sub * EPL + e] = o[e];
-        if (sub == 0) { red[w][0][D] = m; red[w][0][D + 1] = l; }
+            for (int e = 0; e < EPL; ++e) out[n * EPL + e] = o[e];
+            if (n == 0) { out[D] = m; out[D + 1] = l; }
+        }
+    } else {
+        for (int e = lane; e < D + 2; e += 64) out[e] = e == D ? -INFINITY : 0.f;
     }
     __syncthreads();
-    combine_waves<D, 1, 4>(red, 1, PartialOut(part, D, u, 1, nsplit, rule.units), 0, split);
+    combine_waves<D, 1, 12>(red, 1, PartialOut(part, D, u, 1, nsplit, rule.units), 0, split);
 }
 
 static int decode_splits(const zipvl_dims& d, int cap) {
@@ -1038,8 +1092,9 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
                              const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
 {
     const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, cap = cap_hi + cap_lo + cap_t;
-    // one head: decode_splits(d, cap) splits whatever the lengths are, each with its share of every part of the cache
-    const SplitRule rule = G > 1 ? split_rule(d, cap) : SplitRule{1, 1, decode_splits(d, cap), 0, units, 0};
+    // one head: as many splits as are resident together (three workgroups of four waves per CU), whatever the lengths are; each
+    // takes its share of the cache (four layers of 128 units x 8192 rows: 1024 workgroups 153 us, 768 123, 512 137, 384 134)
+    const SplitRule rule = G > 1 ? split_rule(d, cap) : SplitRule{1, 1, std::min(decode_splits(d, cap), std::max(1, 768 / units)), 0, units, 0};
     Lengths lengths{{nullptr, nullptr, nullptr}, {0, 0, 0}};
     if (rule.turn) lengths = {{len_hi, len_lo, Kt ? len_t : nullptr}, {cap_hi, cap_lo, cap_t}};      // else every split reports: 0.5 us less
     const float c = scale * kLog2e;
@@ -1054,7 +1109,7 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
             hipLaunchKernelGGL((decode_q_partial_kernel<T, D, 8>), rule.grid(), dim3(64 * kDecWaves<8>), 0, st, ZIPVL_DECQ_ARGS,
                 d.Hq, d.Hkv, gb, c, (float*)ws, rule);
         else
-            hipLaunchKernelGGL((decode_q4_partial_kernel<T, D>), rule.grid(), dim3(256), 0, st, ZIPVL_DECQ_ARGS, c, (float*)ws, rule);
+            hipLaunchKernelGGL((decode_q1_partial_kernel<T, D>), rule.grid(), dim3(256), 0, st, ZIPVL_DECQ_ARGS, c, (float*)ws, rule);
         int rc = check_launch("decode_q_partial");
         if (rc) return rc;
     }

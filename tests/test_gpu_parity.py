@@ -909,6 +909,37 @@ def test_decode_over_quantised_cache_at_tile_edges(dtype, d, G):
     assert worst <= (2e-2 if dtype == "bf16" else 5e-5)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_one_head_decode_over_quantised_cache_in_blocks_of_64_rows(d):
+    """Integer products: both parts around multiples of 64 rows; value rows from 1e-4 to 1e4, small ones first and last (the
+    fixed-point scale of the weights moves); logits that rise along the sequence (the exponent offset moves); query elements
+    six orders of magnitude apart, and a query of zeros.  Bound: a score of |s| is off by up to 4 * 2^-24 |s| in fp32, a
+    weight by that relative amount; |s| < 80 here, so 2e-5 of the largest value that a head weighs."""
+    say(f"decode_attn_q one head, blocks of 64, d={d}")
+    n = 400
+    kept = [0, 1, 63, 64, 65, 127, 128, 129, 192, 336, 399, 400]
+    units = len(kept)
+    r = np.random.Generator(np.random.PCG64(71))
+    w = make_custom(1, units, units, n, d, "f32", seed=72)
+    q = r.standard_normal((units, d)).astype(np.float32)
+    q[1] *= np.float32(10.0) ** r.uniform(-6, 0, d).astype(np.float32)
+    q[2] = 0
+    mag = np.concatenate([np.full(100, 1e-4), 10.0 ** r.uniform(-4, 4, 200), np.full(100, 1e-4)]).astype(np.float32)
+    V = (w.V * mag[None, None, :, None]).astype(np.float32)
+    K = (w.K + 0.06 * np.arange(n, dtype=np.float32)[None, None, :, None] * q[None, :, None, :] / np.maximum(np.linalg.norm(q, axis=1), 1e-3)[None, :, None, None]).astype(np.float32)
+    idx = np.zeros((units, n), dtype=np.int32)
+    for u, k in enumerate(kept):
+        idx[u, :k] = np.sort(r.choice(n, k, replace=False))
+    cache = z.zipvl_quantize_kv(dev(K, "f32"), dev(V, "f32"), torch.from_numpy(idx).to(DEV), torch.tensor(kept, dtype=torch.int32, device=DEV), n, n)
+    o = z.zipvl_decode_attn_q(dev(q, "f32"), cache, w.scale, B=1, Hq=units, Hkv=units)
+    torch.cuda.synchronize()
+    for u, k in enumerate(kept):
+        qc = oz.quantize_kv(K[0, u], V[0, u], idx[u, :k])
+        ref = oz.decode_attention_quantized(q[u].astype(np.float64), qc, w.scale)
+        err = np.abs(host64(o[u]) - ref).max()
+        assert err <= 2e-5 * np.abs(V[0, u]).max(), f"unit {u}: {err:.3e}"
+
+
 def test_quantize_kv_with_one_set_per_batch_element_and_without_T():
     say("quantize_kv T_PER_BATCH / idx=NULL")
     B, Hq, Hkv, n, d, dtype = 2, 4, 4, 1000, 128, "bf16"
