@@ -3,10 +3,9 @@
 //
 // Two kernels:
 //   pack   gathers K[T] and V[T] into the workspace, once per KV head, zero-filling
-//          the ragged tail.  bf16: both row-major (the P.V operand is fetched from
-//          LDS with the transposing read, so an evicted cache with contiguous rows is
-//          read in place and nothing is packed at all); fp32: V[T] transposed
-//          ([d][64 keys] tiles), so that both MFMA operands are contiguous fragments.
+//          the ragged tail.  An evicted cache with contiguous rows is read in place and
+//          nothing is packed at all (the P.V operand comes from row-major V tiles in LDS:
+//          bf16 through the transposing read, fp32 one element per lane and product).
 //   flash  one workgroup = 128 kept queries of one query head (4 waves x 32
 //          rows).  K / V tiles of 64 keys are loaded straight into LDS (double
 //          buffered) and shared by the four waves.  S^T = K Q^T and O^T = V^T P^T
@@ -65,10 +64,7 @@ struct AttnCfg {
     // LDS tiles are unpadded; the 16-byte chunks of a row are XOR-swizzled with the row index instead, so
     // that 16 consecutive rows read at the same logical chunk hit 16 different bank groups.
     static constexpr int KRB = D * E;                        // bytes per K row
-    // bf16: V tiles stay row-major ([64 keys][d], like K) and the P.V operand is fetched with the LDS
-    // transposing read; fp32 (no such read for 32-bit elements): V^T tiles ([d][64 keys]) packed beforehand.
-    static constexpr bool VROWS = E == 2;
-    static constexpr int VRB = VROWS ? D * E : kBN * E;      // bytes per row of a V tile
+    static constexpr int VRB = D * E;                        // bytes per V row
     static constexpr int TILE_BYTES = kBN * D * E;           // one K tile = one V tile
     static constexpr int NLD = TILE_BYTES / 1024 / NW;       // 1-KiB direct-to-LDS loads per wave per tile
     static constexpr int LDS_BYTES = 4 * TILE_BYTES;         // two K and two V buffers
@@ -78,21 +74,15 @@ struct AttnCfg {
 };
 
 // ------------------------------------------------------------------ pack
-// Key held at element e of 16-byte chunk kc of a V^T tile row (fp32 path): natural order.
-__device__ __forceinline__ int vt_key(int kc, int e) { return kc * 4 + e; }
-
 template <typename T, int D>
 __global__ __launch_bounds__(256) void pack_kv_kernel(
     const T* __restrict__ K, const T* __restrict__ V,
     int64_t ks0, int64_t ks1, int64_t ks2, int64_t vs0, int64_t vs1, int64_t vs2,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
-    T* __restrict__ Kp, T* __restrict__ Vp, int n, int npad, int Hkv, int rows_are_kept, int skip_k, int t_per_batch)
+    T* __restrict__ Kp, T* __restrict__ Vp, int n, int npad, int Hkv, int rows_are_kept, int skip_k, int skip_v, int t_per_batch)
 {
     constexpr int EPF = Elem<T>::kPerFrag;
     constexpr int CPR = D / EPF;
-    constexpr int LS = D + EPF;                 // padded LDS row (elements)
-    constexpr bool VROWS = Elem<T>::kBytes == 2;
-    __shared__ __attribute__((aligned(16))) T tile[VROWS ? EPF : kBN * LS];
     const int u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
     const int t0 = blockIdx.x * kBN;
     const int ut = t_per_batch ? b : u;                   // row of idx / k that holds this unit's T
@@ -107,21 +97,10 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
         if (row < kk) {
             const int src = (idx && !rows_are_kept) ? idx[(int64_t)ut * n + row] : row;
             if (!skip_k) kv = load16(Kb + (int64_t)src * ks2 + cc * EPF);
-            vv = load16(Vb + (int64_t)src * vs2 + cc * EPF);
+            if (!skip_v) vv = load16(Vb + (int64_t)src * vs2 + cc * EPF);
         }
-        if (!skip_k) store16(Kp + ((int64_t)u * npad + row) * D + cc * EPF, kv);
-        if (VROWS) store16(Vp + ((int64_t)u * npad + row) * D + cc * EPF, vv);      // rows past k are zero rows
-        else store16(tile + r * LS + cc * EPF, vv);
-    }
-    if (VROWS) return;
-    __syncthreads();
-    T* VT = Vp + ((int64_t)u * (npad / kBN) + blockIdx.x) * (D * kBN);
-    for (int wi = threadIdx.x; wi < D * (kBN / EPF); wi += 256) {
-        const int dd = wi % D, kc = wi / D;
-        T v[EPF];
-#pragma unroll
-        for (int e = 0; e < EPF; ++e) v[e] = tile[vt_key(kc, e) * LS + dd];
-        store16(VT + dd * kBN + kc * EPF, *reinterpret_cast<const uintx4*>(v));
+        if (!skip_k) store16(Kp + ((int64_t)u * npad + row) * D + cc * EPF, kv);    // rows past k are zero rows
+        if (!skip_v) store16(Vp + ((int64_t)u * npad + row) * D + cc * EPF, vv);
     }
 }
 
@@ -134,17 +113,19 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
 // per-lane source offsets for tile_to_lds (rows of RB bytes)
 // Row swizzle of a row-major bf16 V tile (rows of RB bytes): the transposing read of a 16-lane group
 // touches 4 consecutive keys x 4 consecutive 16-byte chunks, so the key index goes into chunk bits 2..3
-// (one bit of it is already an address bit when two rows share a 256-byte bank period).
-template <int RB>
-__device__ __forceinline__ int v_row_swizzle(int row) { return ((row & 3) >> (RB == 128 ? 1 : 0)) << 2; }
+// (one bit of it is already an address bit when two rows share a 256-byte bank period).  fp32: a wave reads 32
+// consecutive elements of two rows 4 apart, which go to the two halves of the bank period.
+template <int RB, int E>
+__device__ __forceinline__ int v_row_swizzle(int row) { return E == 4 ? ((row >> 2) & 1) << 3 : ((row & 3) >> (RB == 128 ? 1 : 0)) << 2; }
 
-template <int RB, int NW, int NLD, bool VSWZ = false>
+// VE: 0 for K tiles, bytes per element for V tiles
+template <int RB, int NW, int NLD, int VE = 0>
 __device__ __forceinline__ void lds_fill_offsets(int w, int lane, int (&off)[NLD]) {
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
         const int o = (q * NW + w) * 1024 + lane * 16;
         const int r = o / RB, p = (o % RB) >> 4;
-        off[q] = r * RB + ((p ^ (VSWZ ? v_row_swizzle<RB>(r) : k_row_swizzle<RB>(r))) << 4);
+        off[q] = r * RB + ((p ^ (VE ? v_row_swizzle<RB, VE>(r) : k_row_swizzle<RB>(r))) << 4);
     }
 }
 
@@ -168,7 +149,7 @@ __device__ __forceinline__ void tile_load_pinned(const char* gtile, int q, const
 // Only the first `rows` rows of the tile may be read: fewer than kBN happens once per head, at its last tile, and the
 // rows after them are then filled from the last one, chunk for chunk.  That form derives its offsets again from the
 // thread index, so that the key loop carries nothing for it.
-template <int RB, int NW, int NLD, bool VSWZ = false>
+template <int RB, int NW, int NLD, int VE = 0>
 __device__ __forceinline__ void tile_to_lds(const char* gtile, unsigned lds_dst, const int (&off)[NLD], int rows) {
     if (rows >= kBN) {
 #pragma unroll
@@ -179,7 +160,7 @@ __device__ __forceinline__ void tile_to_lds(const char* gtile, unsigned lds_dst,
 #pragma unroll 1
         for (int q = 0; q < NLD; ++q) {
             const int o = q * NW * 1024 + tid * 16, r = o / RB, p = (o % RB) >> 4;
-            const int chunk = (p ^ (VSWZ ? v_row_swizzle<RB>(r) : k_row_swizzle<RB>(r))) << 4;
+            const int chunk = (p ^ (VE ? v_row_swizzle<RB, VE>(r) : k_row_swizzle<RB>(r))) << 4;
             load_kib_to_lds(gtile, min(r, rows - 1) * RB + chunk, lds_dst + q * NW * 1024);
         }
     }
@@ -222,7 +203,7 @@ template <int D, int NW, int QB> struct PV<__bf16, D, NW, QB> {
         const int row = 4 * h + e;                           // key inside its group of 8 = swizzle of the row
 #pragma unroll
         for (int db = 0; db < C::ODB; ++db)
-            lane_off[db] = row * C::VRB + swz_chunk(4 * db + 2 * grp + (q >> 1), v_row_swizzle<C::VRB>(row)) + (q & 1) * 8;
+            lane_off[db] = row * C::VRB + swz_chunk(4 * db + 2 * grp + (q >> 1), v_row_swizzle<C::VRB, 2>(row)) + (q & 1) * 8;
     }
     template <int HALF>
     __device__ static __forceinline__ void run(const char* vb, const int (&lane_off)[C::ODB], const Probs& p,
@@ -247,28 +228,29 @@ template <int D, int NW, int QB> struct PV<__bf16, D, NW, QB> {
 template <int D, int NW, int QB> struct PV<float, D, NW, QB> {
     using C = AttnCfg<float, D, NW, QB>;
     using Probs = floatx16[QB][2];                           // p[qb][blk][r]: as the S^T accumulators
-    // lane_off[0] = V^T row of this lane inside a channel block and [1] = its swizzle (i, i & 7)
+    // lane_off[db]: this lane's element of channel block db in a row whose swizzle is 0 (rows 4 h + ... of a group of 8 have h)
     __device__ static __forceinline__ void lane_offsets(int lane, int (&lane_off)[C::ODB]) {
-        lane_off[0] = lane & 31;
-        lane_off[1] = lane >> 5;
+        const int i = lane & 31, h = lane >> 5;
+#pragma unroll
+        for (int db = 0; db < C::ODB; ++db)
+            lane_off[db] = 4 * h * C::VRB + swz_chunk(8 * db + (i >> 2), v_row_swizzle<C::VRB, 4>(4 * h)) + (i & 3) * 4;
     }
     template <int HALF>
     __device__ static __forceinline__ void run(const char* vb, const int (&lane_off)[C::ODB], const Probs& p, floatx16 (&o)[QB][C::ODB]) {
-        const int i = lane_off[0], h = lane_off[1], sw = k_row_swizzle<C::VRB>(i);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
+        for (int a = 0; a < 4; ++a)
             // step (a, t): this lane contributes key 32*HALF + 8*a + 4*h + t
-            const int chunk = swz_chunk(8 * HALF + 2 * a + h, sw);
 #pragma unroll
             for (int db = 0; db < C::ODB; ++db) {
-                const floatx4 v = *reinterpret_cast<const floatx4*>(vb + (db * 32 + i) * C::VRB + chunk);
+                float v[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const float*>(vb + lane_off[db] + (32 * HALF + 8 * a + t) * C::VRB);
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
                     for (int qb = 0; qb < QB; ++qb)
                         o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[t], p[qb][HALF][4 * a + t], o[qb][db], 0, 0, 0);
             }
-        }
     }
 };
 
@@ -363,12 +345,12 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     const int ntiles = (min(i0 + kBM, kk) + kBN - 1) / kBN;
     const int wave_first_row = i0 + kRW * w, wave_last_row = wave_first_row + kRW - 1;
     const int my_tiles = min(ntiles, wave_last_row / kBN + 1);   // later tiles lie wholly in this wave's future
-    const char* kg = reinterpret_cast<const char*>(Kp + b * kp0 + g * kp1);   // row-major kept K rows of this unit
-    const char* vg = reinterpret_cast<const char*>(Vp + b * vp0 + g * vp1);   // V tiles of this unit (V^T tiles for fp32)
+    const char* kg = reinterpret_cast<const char*>(Kp + b * kp0 + g * kp1);   // row-major kept rows of this unit
+    const char* vg = reinterpret_cast<const char*>(Vp + b * vp0 + g * vp1);
     // An evicted cache that is read in place need not hold a row at or beyond k: the tile with row k - 1 is loaded as far
     // as that row (what stands for later rows is masked and weighs nothing).  Packed tiles are whole.  The steps that
     // request it run outside the steady state: at most 1 us of 289 at 128 heads x 8192 tokens.
-    const int krows = k_in_place ? kk : npad, vrows = C::VROWS && v_in_place ? kk : npad;
+    const int krows = k_in_place ? kk : npad, vrows = v_in_place ? kk : npad;
     const int whole_tiles = min(krows, vrows) / kBN;
     const int steady_end = ntiles <= whole_tiles ? ntiles : whole_tiles - 2;   // the steps before this request whole tiles only
     char* const Kb0 = smem;
@@ -376,7 +358,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     const int sw = k_row_swizzle<C::KRB>(i);
     int koff[C::NLD], voff[C::NLD];
     lds_fill_offsets<C::KRB, NW, C::NLD>(w, lane, koff);
-    lds_fill_offsets<C::VRB, NW, C::NLD, C::VROWS>(w, lane, voff);
+    lds_fill_offsets<C::VRB, NW, C::NLD, C::E>(w, lane, voff);
     int vlane[C::ODB];
     PV<T, D, NW, QB>::lane_offsets(lane, vlane);
 
@@ -385,8 +367,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         tile_to_lds<C::KRB, NW, C::NLD>(kg + (int64_t)t * C::TILE_BYTES, klds + buf * C::TILE_BYTES, koff, krows - t * kBN);
     };
     auto load_v = [&](int t, int buf) {
-        const int rows = C::VROWS ? vrows - t * kBN : kBN;
-        tile_to_lds<C::VRB, NW, C::NLD, C::VROWS>(vg + (int64_t)t * C::TILE_BYTES, vlds + buf * C::TILE_BYTES, voff, rows);
+        tile_to_lds<C::VRB, NW, C::NLD, C::E>(vg + (int64_t)t * C::TILE_BYTES, vlds + buf * C::TILE_BYTES, voff, vrows - t * kBN);
     };
     // The first tiles are requested before anything else is loaded: their addresses need only scalars, while the
     // query rows below wait for their positions first (two round trips).
@@ -532,6 +513,8 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
                 }
         };
         const bool has_pv = t >= 1 && t - 1 < my_tiles, has_s = t < my_tiles, has_next = t + 1 < my_tiles;
+        // fp32: the second block of a tile is left out where all its keys lie past the wave's last row (64 products of 64 cycles)
+        auto second = [&](int tile) { return Elem<T>::kBytes == 2 || tile * kBN + 32 <= min(wave_last_row, kk - 1); };
         const char* kb = Kb0 + ((t + 1) & 1) * C::TILE_BYTES;
         const char* vb = Vb0 + ((t + 1) & 1) * C::TILE_BYTES;          // V tile t-1
         float mc[QB], sum[QB];
@@ -574,6 +557,13 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
             }
         };
         const bool steady = has_pv && has_next && t < steady_end && !SAFE;
+        auto next_second = [&]() {
+            if (second(t + 1)) qk_block<T, D, NW, QB>(kb, 1, i, h, sw, qf, sn);
+            else {
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) sn[qb][1] = floatx16{0};      // masked for every row that exists
+            }
+        };
         // ---- first half: P.V of tile t-1 | exponentials of key block 0 of tile t | requests for K tile t+2
         if (steady) {
             if constexpr (kExplicit) steady_half(std::integral_constant<int, 0>{}, vb, sc, sn, pp, pc, sum, kgt, kl);
@@ -586,7 +576,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
             load_k(kt, t & 1);
             if (has_pv) {
                 PV<T, D, NW, QB>::template run<0>(vb, vlane, pp, o);
-                PV<T, D, NW, QB>::template run<1>(vb, vlane, pp, o);
+                if (second(t - 1)) PV<T, D, NW, QB>::template run<1>(vb, vlane, pp, o);
             }
             if (has_s) {
                 if constexpr (SAFE) {
@@ -635,15 +625,15 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
             else {
                 exps(1, true);
                 qk_block<T, D, NW, QB>(kb, 0, i, h, sw, qf, sn);
-                qk_block<T, D, NW, QB>(kb, 1, i, h, sw, qf, sn);
+                next_second();
             }
         } else {
             load_v(vt, (t + 1) & 1);
             if (has_next) {
                 qk_block<T, D, NW, QB>(kb, 0, i, h, sw, qf, sn);
-                qk_block<T, D, NW, QB>(kb, 1, i, h, sw, qf, sn);
+                next_second();
             }
-            if (has_s) exps(1, false);
+            if (has_s && second(t)) exps(1, false);
         }
         if (has_s) {
 #pragma unroll
@@ -756,28 +746,29 @@ static int launch_prefill_t(const void* Q, const void* K, const void* V, const z
     const int npad = (d.n + kBN - 1) / kBN * kBN;
     const int units = d.B * d.Hkv;
     T* Kp = (T*)ws;
-    T* VTp = Kp + (size_t)units * npad * D;
+    T* Vp = Kp + (size_t)units * npad * D;
     const int out_compact = (flags & ZIPVL_OUT_COMPACT) ? 1 : 0;
-    const int rows_are_kept = (flags & ZIPVL_KV_ALREADY_COMPACT) ? 1 : 0;
+    const int rows_are_kept = ((flags & ZIPVL_KV_ALREADY_COMPACT) || !idx) ? 1 : 0;      // row i of K, V is kept token i
     const int t_per_batch = (flags & ZIPVL_T_PER_BATCH) ? 1 : 0;
 
-    // An evicted cache with contiguous rows is read in place (K always, V when the transposing LDS read applies: then
-    // nothing is packed), whatever its length: no row at or beyond k is read.  32 heads, n = 2933: packing all of it took 8.5 us of 64.
+    // An evicted cache (or, with every token kept, K and V themselves) with contiguous rows is read in place, whatever its length:
+    // no row at or beyond k is read.  All of 28 heads on 4, n = 18432: the copy took 15 us of 2200.  32 heads,
+    // n = 2933: packing all of it took 8.5 us of 64; fp32, 4 heads, n = 576: the launch that transposed V 3.8 of 45.
     const int skip_k = (rows_are_kept && d.k_strides[2] == D) ? 1 : 0;
-    const int skip_v = (rows_are_kept && Elem<T>::kBytes == 2 && d.v_strides[2] == D) ? 1 : 0;
+    const int skip_v = (rows_are_kept && d.v_strides[2] == D) ? 1 : 0;
     if (!(skip_k && skip_v)) {
         KernelTimer tm(ZIPVL_K_PACK_KV, st);
         hipLaunchKernelGGL((pack_kv_kernel<T, D>), dim3(npad / kBN, units), dim3(256), 0, st,
             (const T*)K, (const T*)V, d.k_strides[0], d.k_strides[1], d.k_strides[2],
-            d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, Kp, VTp, d.n, npad, d.Hkv, rows_are_kept, skip_k, t_per_batch);
+            d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, Kp, Vp, d.n, npad, d.Hkv, rows_are_kept, skip_k, skip_v, t_per_batch);
         int rc = check_launch("pack_kv");
         if (rc) return rc;
     }
 
     if constexpr (Elem<T>::kBytes == 2)
-        return launch_flash<T, D, kFlashWavesBf16, kFlashBlocksBf16>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, O, st);
+        return launch_flash<T, D, kFlashWavesBf16, kFlashBlocksBf16>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
     else
-        return launch_flash<T, D, 4, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, VTp, npad, O, st);
+        return launch_flash<T, D, 4, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
 }
 
 int launch_sparse_prefill(const void* Q, const void* K, const void* V, const zipvl_dims& d,

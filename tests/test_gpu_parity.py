@@ -338,6 +338,40 @@ def _attention_case(B, Hq, Hkv, n, d, dtype, ks, seed=0, flags=0, dense=False, r
     assert worst <= ATOL_OUT[dtype]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [1, 31, 33, 64, 65, 129, 200])
+def test_attention_in_place_is_attention_over_packed_rows(dtype, d, n):
+    """Contiguous rows are read where they are, others through the workspace: the same sums in the same order, so the same
+    bits.  Every token kept, and an evicted cache whose rows from k on are NaN; then against the oracle."""
+    say(f"attention in place dtype={dtype} d={d} n={n}")
+    w = make_custom(1, 4, 2, n, d, dtype, seed=n + d)
+    Q, K, V = dev(w.Q, dtype), dev(w.K, dtype), dev(w.V, dtype)
+
+    def spread(x):                                          # the same rows, 16 bytes apart
+        wide = torch.zeros(x.shape[:-1] + (d + 16 // x.element_size(),), dtype=x.dtype, device=DEV)
+        wide[..., :d] = x
+        return wide[..., :d]
+
+    dense, packed = z.zipvl_sparse_prefill(Q, K, V, None, None, w.scale), z.zipvl_sparse_prefill(Q, spread(K), spread(V), None, None, w.scale)
+    mixed = z.zipvl_sparse_prefill(Q, K, spread(V), None, None, w.scale)
+    assert torch.equal(dense, packed) and torch.equal(dense, mixed)
+    k = max(1, n - 7)
+    Kc, Vc = K.clone(), V.clone()
+    Kc[:, :, k:] = float("nan")
+    Vc[:, :, k:] = float("nan")
+    idx = torch.arange(n, dtype=torch.int32, device=DEV).repeat(2, 1)
+    kc = torch.full((2,), k, dtype=torch.int32, device=DEV)
+    args = (idx, kc, w.scale, z.OUT_FULL | z.KV_ALREADY_COMPACT)
+    evicted = z.zipvl_sparse_prefill(Q, Kc, Vc, *args)
+    assert torch.equal(evicted, z.zipvl_sparse_prefill(Q, spread(Kc), spread(Vc), *args))
+    torch.cuda.synchronize()
+    for h in range(4):
+        for got, T in ((dense, np.arange(n)), (evicted, np.arange(k))):
+            ref = oz.kept_token_attention(w.Q[0, h], w.K[0, h // 2], w.V[0, h // 2], T, w.scale)
+            assert np.abs(host64(got[0, h]) - ref).max() <= ATOL_OUT[dtype]
+
+
 def test_attention_fp32_small_ragged():
     say("attention fp32 d=64 ragged k")
     _attention_case(1, 4, 4, 576, 64, "f32", [576, 1, 130, 67], seed=1)
