@@ -41,11 +41,9 @@
 namespace zipvl {
 
 constexpr int kBN = 64;      // keys per tile
-// bf16 launch shape: 4 waves x 32 queries.  Measured alternatives: 8 waves per workgroup (half the L2 -> LDS
-// traffic per query) is 3 % slower; 64 queries per wave (QB = 2, half the LDS operand reads per MFMA) does
-// not fit the register file with the S^T double buffer and spills.
-constexpr int kFlashWavesBf16 = 4;
-constexpr int kFlashBlocksBf16 = 1;
+// Launch shape: 4 waves x 32 queries, or (launch_prefill_t) 2 x 32 queries x 2 key blocks.  Measured alternatives: 8 waves per
+// workgroup (half the L2 -> LDS traffic per query) is 3 % slower; 64 queries per wave (QB = 2, half the LDS operand reads per
+// MFMA) does not fit the register file with the S^T double buffer and spills.
 constexpr int kFillSpan = 512;       // positions per workgroup that clears dropped output rows
 constexpr float kLazyLog2 = 8.f;     // slack of the running softmax offset below the running maximum (log2 domain)
 constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p64f;   // row sums of the offset-free pass that need no second pass
@@ -54,10 +52,12 @@ constexpr int kSchedAhead = 3;       // LDS operand reads in flight ahead of the
 // NW = waves per workgroup, QB = 32-query blocks per wave: a workgroup covers 32 QB NW kept queries, its
 // K / V^T tiles are fetched from L2 once per that many queries, and every LDS operand fragment a wave
 // reads feeds QB matrix instructions.
-template <typename T, int D, int NW = 4, int QB = 1>
+// KS = 2: two waves share 32 queries and take one 32-key block of every tile each (their sums meet at the end).
+template <typename T, int D, int NW = 4, int QB = 1, int KS = 1>
 struct AttnCfg {
     static constexpr int E = Elem<T>::kBytes;
-    static constexpr int BM = 32 * QB * NW;                  // queries per workgroup
+    static constexpr int BM = 32 * QB * NW / KS;             // queries per workgroup
+    static constexpr int NBK = 2 / KS;                       // 32-key blocks of a tile per wave
     static constexpr int NT = 64 * NW;                       // threads per workgroup
     static constexpr int CH = D / Elem<T>::kPerChunk;       // Q/K fragments per row per lane
     static constexpr int ODB = D / 32;                       // 32-row blocks of O^T
@@ -168,10 +168,10 @@ __device__ __forceinline__ void tile_to_lds(const char* gtile, unsigned lds_dst,
 
 // S^T = K Q^T for 32 keys (block blk of the 64-key tile in LDS buffer kb) and the wave's QB query blocks:
 // acc[qb][blk][r] = key 32*blk + acc_row(r, h), this lane's query of block qb.  A K fragment is read once for all QB.
-template <typename T, int D, int NW, int QB>
+template <typename T, int D, int NW, int QB, int KS>
 __device__ __forceinline__ void qk_block(const char* kb, int blk, int i, int h, int sw,
-                                         const uintx4 (&qf)[QB][AttnCfg<T, D, NW, QB>::CH], floatx16 (&acc)[QB][2]) {
-    using C = AttnCfg<T, D, NW, QB>;
+                                         const uintx4 (&qf)[QB][AttnCfg<T, D, NW, QB, KS>::CH], floatx16 (&acc)[QB][AttnCfg<T, D, NW, QB, KS>::NBK]) {
+    using C = AttnCfg<T, D, NW, QB, KS>;
     floatx16 a[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) a[qb] = floatx16{0};
@@ -186,13 +186,13 @@ __device__ __forceinline__ void qk_block(const char* kb, int blk, int i, int h, 
 }
 
 // O^T += V^T P^T for the 32 keys of half HALF: p[qb][HALF] holds the probabilities of S^T block HALF of query block qb.
-template <typename T, int D, int NW, int QB> struct PV;
+template <typename T, int D, int NW, int QB, int KS> struct PV;
 
-template <int D, int NW, int QB> struct PV<__bf16, D, NW, QB> {
-    using C = AttnCfg<__bf16, D, NW, QB>;
+template <int D, int NW, int QB, int KS> struct PV<__bf16, D, NW, QB, KS> {
+    using C = AttnCfg<__bf16, D, NW, QB, KS>;
     // p[qb][blk][s2]: the probabilities of S^T block blk as P^T operand fragments.  Contraction slot t of
     // this lane <-> key 16*s2 + 8*(t/4) + 4*h + t%4 of the block = accumulator register 8*s2 + t.
-    using Probs = uintx4[QB][2][2];
+    using Probs = uintx4[QB][C::NBK][2];
     // The matching V^T operand (lane = channel 32 db + lane % 32, slots = those 8 keys) comes from the
     // row-major V tile through ds_read_b64_tr_b16: in every group of 16 lanes, lane 4e + q supplies the
     // address of 4 consecutive channels of key e, and lane l receives channel l of keys 0..3.  Two reads
@@ -225,9 +225,9 @@ template <int D, int NW, int QB> struct PV<__bf16, D, NW, QB> {
     }
 };
 
-template <int D, int NW, int QB> struct PV<float, D, NW, QB> {
-    using C = AttnCfg<float, D, NW, QB>;
-    using Probs = floatx16[QB][2];                           // p[qb][blk][r]: as the S^T accumulators
+template <int D, int NW, int QB, int KS> struct PV<float, D, NW, QB, KS> {
+    using C = AttnCfg<float, D, NW, QB, KS>;
+    using Probs = floatx16[QB][C::NBK];                           // p[qb][blk][r]: as the S^T accumulators
     // lane_off[db]: this lane's element of channel block db in a row whose swizzle is 0 (rows 4 h + ... of a group of 8 have h)
     __device__ static __forceinline__ void lane_offsets(int lane, int (&lane_off)[C::ODB]) {
         const int i = lane & 31, h = lane >> 5;
@@ -275,15 +275,15 @@ template <> __device__ __forceinline__ void store_out4<__bf16>(__bf16* dst, floa
     *reinterpret_cast<uintx2*>(dst) = uintx2{pack_bf16x2(a, b), pack_bf16x2(c, d)};
 }
 
-template <typename T, int D, int NW, int QB>
-__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void flash_kept_kernel(
+template <typename T, int D, int NW, int QB, int KS>
+__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS>::MIN_WGS)) void flash_kept_kernel(
     const T* __restrict__ Q, int64_t qs0, int64_t qs1, int64_t qs2,
     const T* __restrict__ Kp, int64_t kp0, int64_t kp1, const T* __restrict__ Vp, int64_t vp0, int64_t vp1,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
     T* __restrict__ O, int n, int npad, int ntq, int ug, int BH, int Hq, int Hkv, float c, int out_compact, int compute_blocks,
     int t_per_batch, int k_in_place, int v_in_place)
 {
-    using C = AttnCfg<T, D, NW, QB>;
+    using C = AttnCfg<T, D, NW, QB, KS>;
     constexpr int kBM = C::BM, kNT = C::NT, kRW = 32 * QB;   // queries per workgroup, threads, queries per wave
     extern __shared__ __attribute__((aligned(16))) char smem[];
     // Workgroup -> (unit group, query tile, unit in group, head of the KV group), in that order of
@@ -295,6 +295,8 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     // chip's resident workgroups for that one not to end alone.
     const int G = Hq / Hkv, NU = BH / G;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, i = lane & 31, h = lane >> 5;
+    // KS = 2: wave w has the queries of wave qw and key block kw of every tile
+    const int qw = KS == 1 ? w : w % (NW / KS), kw = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(w / (NW / KS));
     if (blockIdx.x >= (unsigned)compute_blocks) {
         // Outputs of dropped tokens are zero rows.  The workgroups after the last attention workgroup
         // each clear the dropped rows of one head inside one span of kFillSpan positions; they are
@@ -343,8 +345,10 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     float m_run[QB], l_run[QB];
 
     const int ntiles = (min(i0 + kBM, kk) + kBN - 1) / kBN;
-    const int wave_first_row = i0 + kRW * w, wave_last_row = wave_first_row + kRW - 1;
-    const int my_tiles = min(ntiles, wave_last_row / kBN + 1);   // later tiles lie wholly in this wave's future
+    const int wave_first_row = i0 + kRW * qw, wave_last_row = wave_first_row + kRW - 1;
+    const int key_room = min(wave_last_row, kk - 1) - 32 * kw;
+    // later tiles lie wholly in this wave's future
+    const int my_tiles = KS == 1 ? min(ntiles, wave_last_row / kBN + 1) : key_room >= 0 ? min(ntiles, key_room / kBN + 1) : 0;
     const char* kg = reinterpret_cast<const char*>(Kp + b * kp0 + g * kp1);   // row-major kept rows of this unit
     const char* vg = reinterpret_cast<const char*>(Vp + b * vp0 + g * vp1);
     // An evicted cache that is read in place need not hold a row at or beyond k: the tile with row k - 1 is loaded as far
@@ -360,7 +364,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     lds_fill_offsets<C::KRB, NW, C::NLD>(w, lane, koff);
     lds_fill_offsets<C::VRB, NW, C::NLD, C::E>(w, lane, voff);
     int vlane[C::ODB];
-    PV<T, D, NW, QB>::lane_offsets(lane, vlane);
+    PV<T, D, NW, QB, KS>::lane_offsets(lane, vlane);
 
     const unsigned klds = lds_address(Kb0) + w * 1024, vlds = lds_address(Vb0) + w * 1024;
     auto load_k = [&](int t, int buf) {
@@ -382,7 +386,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     uintx4 qf[QB][C::CH];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        qrow[qb] = i0 + kRW * w + 32 * qb + i;
+        qrow[qb] = i0 + kRW * qw + 32 * qb + i;
         const int qclamp = min(qrow[qb], kk - 1);
         qpos[qb] = tidx ? tidx[qclamp] : qclamp;
         const T* qp = Q + b * qs0 + head * qs1 + (int64_t)qpos[qb] * qs2;
@@ -395,7 +399,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     // fp32 range, which is checked afterwards.  SAFE = true: the offset follows the running maximum.
     auto pass = [&](auto safe_tag) {
     constexpr bool SAFE = decltype(safe_tag)::value;
-    using Probs = typename PV<T, D, NW, QB>::Probs;
+    using Probs = typename PV<T, D, NW, QB, KS>::Probs;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         m_run[qb] = -INFINITY;
@@ -413,10 +417,10 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     if constexpr (SAFE) request_first_tiles();                  // the first pass requested them before the query rows
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    floatx16 sa[QB][2], sb[QB][2];
+    floatx16 sa[QB][C::NBK], sb[QB][C::NBK];
     Probs pa, pb;
-    qk_block<T, D, NW, QB>(Kb0, 0, i, h, sw, qf, sa);       // tile 0 is visible to every row
-    qk_block<T, D, NW, QB>(Kb0, 1, i, h, sw, qf, sa);
+    qk_block<T, D, NW, QB, KS>(Kb0 + kw * 32 * C::KRB, 0, i, h, sw, qf, sa);       // tile 0 is visible to every row
+    if constexpr (KS == 1) qk_block<T, D, NW, QB, KS>(Kb0, 1, i, h, sw, qf, sa);
     __syncthreads();                                         // step 0 overwrites K tile 0
 
     // wait until at most `pending` of this wave's tile requests (NLD loads each) are outstanding, and for its LDS reads
@@ -431,12 +435,13 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     // HALF 0: P.V of the previous tile (src = its V tile), exponentials of key block 0, requests for a K tile.
     // HALF 1: S^T of the next tile (src = its K tile), exponentials of key block 1, requests for a V tile.
     constexpr bool kExplicit = Elem<T>::kBytes == 2 && QB == 1;
-    auto steady_half = [&](auto half_tag, const char* src, floatx16 (&sc)[QB][2], floatx16 (&sn)[QB][2], Probs& pp, Probs& pc,
+    auto steady_half = [&](auto half_tag, const char* src, floatx16 (&sc)[QB][C::NBK], floatx16 (&sn)[QB][C::NBK], Probs& pp, Probs& pc,
                            float (&sum)[QB], const char* gt, unsigned lt) {
         if constexpr (kExplicit) {
         constexpr int HALF = decltype(half_tag)::value;
-        constexpr int NM = HALF == 0 ? 4 * C::ODB : 2 * C::CH;     // matrix instructions of the half
-        constexpr int PPM = 16 / NM;                                // vector pieces per matrix instruction
+        constexpr int NM = (HALF == 0 ? 4 * C::ODB : 2 * C::CH) / KS;  // matrix instructions of the half
+        constexpr int PPM = 16 / KS / NM;                           // vector pieces per matrix instruction
+        constexpr int BLK = KS == 1 ? HALF : 0;                     // key block whose exponentials these are
         typedef short shortx4 __attribute__((ext_vector_type(4)));
         using lds_ptr = __attribute__((address_space(3))) shortx4*;
         uintx4 frag[NM];
@@ -449,28 +454,28 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
                 const uintx2 hi = __builtin_bit_cast(uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(a0 + 8 * C::VRB)));
                 frag[j] = uintx4{lo[0], lo[1], hi[0], hi[1]};
             } else {
-                const int blk = j & 1, cc = j >> 1;
+                const int blk = KS == 1 ? j & 1 : 0, cc = KS == 1 ? j >> 1 : j;
                 frag[j] = *reinterpret_cast<const uintx4*>(src + (blk * 32 + i) * C::KRB + swz_chunk(2 * cc + h, sw));
             }
         };
-        auto piece = [&](int q) {                                   // q = 0..15: half a pair of keys
+        auto piece = [&](int q) {                                   // q = 0..15 (KS = 2: 0..7 and 8..15): half a pair of keys
             const int r = 2 * (q >> 1);
             if ((q & 1) == 0) {
-                pe[r] = sc[0][HALF][r] * c;
-                pe[r + 1] = sc[0][HALF][r + 1] * c;
+                pe[r] = sc[0][BLK][r] * c;
+                pe[r + 1] = sc[0][BLK][r + 1] * c;
                 pe[r] = fast_exp2(pe[r]);
             } else {
                 pe[r + 1] = fast_exp2(pe[r + 1]);
 #pragma unroll
                 for (int L = 0; L < C::NLD; ++L)
-                    if (q == ((2 * L + 1) * 16) / (2 * C::NLD) + 1) {          // request L rides on this piece
+                    if (q - (KS == 2 ? 8 * HALF : 0) == ((((2 * L + 1) * 16 / KS) / (2 * C::NLD)) | 1)) {     // request L rides on this piece
                         unsigned pin = __float_as_uint(pe[r + 1]);
                         if constexpr (HALF == 0) tile_load_pinned<C::KRB, NW, C::NLD>(gt, L, koff, lt + L * NW * 1024, pin);
                         else tile_load_pinned<C::VRB, NW, C::NLD>(gt, L, voff, lt + L * NW * 1024, pin);
                         pe[r + 1] = __uint_as_float(pin);
                     }
                 const uint32_t pk = pack_bf16x2(pe[r], pe[r + 1]);
-                pc[0][HALF][r >> 3][(r & 7) >> 1] = pk;
+                pc[0][BLK][r >> 3][(r & 7) >> 1] = pk;
                 sum[0] = add_bf16x2(pk, sum[0]);
             }
         };
@@ -483,16 +488,16 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
                 const int hf = j / (2 * C::ODB), s2 = (j / C::ODB) & 1, db = j % C::ODB;
                 o[0][db] = mma_frag<__bf16>(frag[j], pp[0][hf][s2], o[0][db]);
             } else {
-                const int blk = j & 1, cc = j >> 1;
+                const int blk = KS == 1 ? j & 1 : 0, cc = KS == 1 ? j >> 1 : j;
                 sn[0][blk] = mma_frag<__bf16>(frag[j], qf[0][cc], cc == 0 ? floatx16{0} : sn[0][blk]);
             }
 #pragma unroll
-            for (int q = 0; q < PPM; ++q) piece(j * PPM + q);
+            for (int q = 0; q < PPM; ++q) piece((KS == 2 ? 8 * HALF : 0) + j * PPM + q);
             __builtin_amdgcn_sched_barrier(0);
         }
         }
     };
-    auto step = [&](int t, floatx16 (&sc)[QB][2], floatx16 (&sn)[QB][2], Probs& pp, Probs& pc) {
+    auto step = [&](int t, floatx16 (&sc)[QB][C::NBK], floatx16 (&sn)[QB][C::NBK], Probs& pp, Probs& pc) {
         // requests of this step: K tile t+2 into the buffer tile t has left (first half), V tile t+1 into the
         // one tile t-1 leaves at the middle barrier (second half).  In the steady state they are issued one
         // at a time, each tied to one exponential (a burst of them stalls every wave of the workgroup at the
@@ -514,20 +519,20 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         };
         const bool has_pv = t >= 1 && t - 1 < my_tiles, has_s = t < my_tiles, has_next = t + 1 < my_tiles;
         // fp32: the second block of a tile is left out where all its keys lie past the wave's last row (64 products of 64 cycles)
-        auto second = [&](int tile) { return Elem<T>::kBytes == 2 || tile * kBN + 32 <= min(wave_last_row, kk - 1); };
-        const char* kb = Kb0 + ((t + 1) & 1) * C::TILE_BYTES;
-        const char* vb = Vb0 + ((t + 1) & 1) * C::TILE_BYTES;          // V tile t-1
+        auto second = [&](int tile) { return KS == 1 && (Elem<T>::kBytes == 2 || tile * kBN + 32 <= min(wave_last_row, kk - 1)); };
+        const char* kb = Kb0 + ((t + 1) & 1) * C::TILE_BYTES + kw * 32 * C::KRB;
+        const char* vb = Vb0 + ((t + 1) & 1) * C::TILE_BYTES + kw * 32 * C::VRB;      // V tile t-1
         float mc[QB], sum[QB];
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) { mc[qb] = 0.f; sum[qb] = 0.f; }
-        if (has_s && t * kBN + kBN - 1 > wave_first_row) {       // tile touches the diagonal (wave-uniform)
+        if (has_s && t * kBN + (KS == 1 ? kBN : 32 * kw + 32) - 1 > wave_first_row) {       // tile touches the diagonal (wave-uniform)
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-                for (int blk = 0; blk < 2; ++blk)
+                for (int blk = 0; blk < C::NBK; ++blk)
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
-                        if (t * kBN + 32 * blk + acc_row(r, h) > qrow[qb]) sc[qb][blk][r] = -INFINITY;
+                        if (t * kBN + 32 * (KS == 1 ? blk : kw) + acc_row(r, h) > qrow[qb]) sc[qb][blk][r] = -INFINITY;
         }
         // Probabilities of this tile.  bf16: packed once into P^T operand fragments, and the row sums are
         // taken over the values as rounded to bf16, so that numerator and denominator of the output use
@@ -558,7 +563,8 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         };
         const bool steady = has_pv && has_next && t < steady_end && !SAFE;
         auto next_second = [&]() {
-            if (second(t + 1)) qk_block<T, D, NW, QB>(kb, 1, i, h, sw, qf, sn);
+            if constexpr (KS == 2) return;
+            else if (second(t + 1)) qk_block<T, D, NW, QB, KS>(kb, 1, i, h, sw, qf, sn);
             else {
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) sn[qb][1] = floatx16{0};      // masked for every row that exists
@@ -569,14 +575,15 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
             if constexpr (kExplicit) steady_half(std::integral_constant<int, 0>{}, vb, sc, sn, pp, pc, sum, kgt, kl);
             else {
                 exps(0, true);
-                PV<T, D, NW, QB>::template run<0>(vb, vlane, pp, o);
-                PV<T, D, NW, QB>::template run<1>(vb, vlane, pp, o);
+                PV<T, D, NW, QB, KS>::template run<0>(vb, vlane, pp, o);
+                if constexpr (KS == 1) PV<T, D, NW, QB, KS>::template run<1>(vb, vlane, pp, o);
             }
         } else {
             load_k(kt, t & 1);
             if (has_pv) {
-                PV<T, D, NW, QB>::template run<0>(vb, vlane, pp, o);
-                if (second(t - 1)) PV<T, D, NW, QB>::template run<1>(vb, vlane, pp, o);
+                PV<T, D, NW, QB, KS>::template run<0>(vb, vlane, pp, o);
+                if constexpr (KS == 1)
+                    if (second(t - 1)) PV<T, D, NW, QB, KS>::template run<1>(vb, vlane, pp, o);
             }
             if (has_s) {
                 if constexpr (SAFE) {
@@ -592,19 +599,19 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
                     for (int qb = 0; qb < QB; ++qb) {
                         float mx = -INFINITY;
 #pragma unroll
-                        for (int blk = 0; blk < 2; ++blk)
+                        for (int blk = 0; blk < C::NBK; ++blk)
 #pragma unroll
                             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[qb][blk][r]);
                         mx = xhalf_max(mx);
                         const bool grow = mx > m_run[qb] + lazy;
                         m_new[qb] = grow ? mx : m_run[qb];
-                        mc[qb] = m_new[qb] * c;
+                        mc[qb] = KS == 1 || m_new[qb] > -INFINITY ? m_new[qb] * c : 0.f;      // KS = 2: a wave's keys may all lie in a row's future
                         moved |= grow;
                     }
                     if (__any(moved)) {
 #pragma unroll
                         for (int qb = 0; qb < QB; ++qb) {
-                            const float alpha = fast_exp2(m_run[qb] * c - mc[qb]);   // 1 where the maximum stayed
+                            const float alpha = KS == 1 || m_run[qb] > -INFINITY ? fast_exp2(m_run[qb] * c - mc[qb]) : 0.f;   // 1 where the maximum stayed
                             l_run[qb] *= alpha;
 #pragma unroll
                             for (int db = 0; db < C::ODB; ++db)
@@ -623,14 +630,18 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         if (steady) {
             if constexpr (kExplicit) steady_half(std::integral_constant<int, 1>{}, kb, sc, sn, pp, pc, sum, vgt, vl);
             else {
-                exps(1, true);
-                qk_block<T, D, NW, QB>(kb, 0, i, h, sw, qf, sn);
+                if constexpr (KS == 1) exps(1, true);
+                else {
+#pragma unroll
+                    for (int L = 0; L < C::NLD; ++L) tile_load<C::VRB, NW, C::NLD>(vgt, L, voff, vl + L * NW * 1024);
+                }
+                qk_block<T, D, NW, QB, KS>(kb, 0, i, h, sw, qf, sn);
                 next_second();
             }
         } else {
             load_v(vt, (t + 1) & 1);
             if (has_next) {
-                qk_block<T, D, NW, QB>(kb, 0, i, h, sw, qf, sn);
+                qk_block<T, D, NW, QB, KS>(kb, 0, i, h, sw, qf, sn);
                 next_second();
             }
             if (has_s && second(t)) exps(1, false);
@@ -655,13 +666,26 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
     // scarce); the positions are requested now and arrive during the check below.
     int tid_out = threadIdx.x;
     asm volatile("" : "+v"(tid_out));
-    const int w_out = tid_out >> 6, i_out = tid_out & 31, h_out = (tid_out >> 5) & 1;
+    const int w_out = KS == 1 ? tid_out >> 6 : (tid_out >> 6) % (NW / KS), i_out = tid_out & 31, h_out = (tid_out >> 5) & 1;
     int qr_out[QB], orow_out[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         qr_out[qb] = i0 + kRW * w_out + 32 * qb + i_out;
         orow_out[qb] = (out_compact || !tidx) ? qr_out[qb] : tidx[min(qr_out[qb], kk - 1)];
     }
+    // KS = 2: a query's sums lie in two waves.  A per-lane value of the partner wave (same queries, other keys), through LDS: the
+    // tile buffers are free once every wave has waited for its last requests.
+    float* const meet = reinterpret_cast<float*>(smem);
+    auto partner = [&](float v) {
+        const int lane_out = tid_out & 63, w_all = tid_out >> 6;
+        __syncthreads();
+        meet[w_all * 64 + lane_out] = v;
+        __syncthreads();
+        return meet[((w_all + NW / KS) % NW) * 64 + lane_out];
+    };
+    if constexpr (KS == 2)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) l_run[qb] += partner(l_run[qb]);
     {
         // the offset-free pass stands if every row sum of the workgroup is finite and far from both ends of the
         // fp32 range (no exponential overflowed, the dominant terms did not underflow); otherwise the whole
@@ -672,7 +696,51 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
             const float l_tot = xhalf_sum(l_run[qb]);
             bad |= qrow[qb] < kk && !(l_tot >= kSumLow && l_tot <= kSumHigh);   // rows past k are never stored
         }
-        if (__syncthreads_or(bad)) pass(std::true_type{});
+        if (__syncthreads_or(bad)) {
+            pass(std::true_type{});
+            if constexpr (KS == 2)
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {            // to the larger of the two offsets (key 0 is visible to every row: finite)
+                    const float m_all = fmaxf(m_run[qb], partner(m_run[qb]));
+                    const float a = m_run[qb] > -INFINITY ? fast_exp2((m_run[qb] - m_all) * c) : 0.f;
+                    l_run[qb] *= a;
+#pragma unroll
+                    for (int db = 0; db < C::ODB; ++db)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) o[qb][db][r] *= a;
+                    l_run[qb] += partner(l_run[qb]);
+                }
+        }
+    }
+    // KS = 2: either wave keeps half of the channel blocks, o[.][0 .. ODB / 2), and hands over the others
+    constexpr int kOut = C::ODB / KS;
+    if constexpr (KS == 2) {
+        const int w_all = tid_out >> 6, lane_out = tid_out & 63;
+        if (kw) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int db = 0; db < kOut; ++db) {
+                    const floatx16 x = o[qb][db];
+                    o[qb][db] = o[qb][db + kOut];
+                    o[qb][db + kOut] = x;
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int db = 0; db < kOut; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) meet[(((w_all * QB + qb) * kOut + db) * 16 + r) * 64 + lane_out] = o[qb][db + kOut][r];
+        __syncthreads();
+        const int w2 = (w_all + NW / KS) % NW;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int db = 0; db < kOut; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[qb][db][r] += meet[(((w2 * QB + qb) * kOut + db) * 16 + r) * 64 + lane_out];
     }
 
 #pragma unroll
@@ -682,9 +750,9 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB>::MIN_WGS)) void fla
         if (qr < kk) {
             const float inv = 1.f / l_tot;
             const int orow = orow_out[qb];
-            T* op = O + ((int64_t)bh * n + orow) * D;
+            T* op = O + ((int64_t)bh * n + orow) * D + (KS == 2 ? kw * (D / 2) : 0);
 #pragma unroll
-            for (int db = 0; db < C::ODB; ++db)
+            for (int db = 0; db < kOut; ++db)
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
                     store_out4<T>(op + 32 * db + 8 * a + 4 * h_out, o[qb][db][4 * a] * inv, o[qb][db][4 * a + 1] * inv,
@@ -700,14 +768,14 @@ size_t prefill_workspace_bytes(const zipvl_dims& d) {
     return 2 * (size_t)d.B * d.Hkv * npad * d.d * e;
 }
 
-template <typename T, int D, int NW, int QB>
+template <typename T, int D, int NW, int QB, int KS>
 static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                         float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, void* O, hipStream_t st)
 {
-    using C = AttnCfg<T, D, NW, QB>;
+    using C = AttnCfg<T, D, NW, QB, KS>;
     static std::atomic<bool> attr_done{false};       // raising the dynamic-LDS cap is idempotent
     if (!attr_done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kept_kernel<T, D, NW, QB>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kept_kernel<T, D, NW, QB, KS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES) != hipSuccess)
             return set_error(ZIPVL_EHIP, "sparse_prefill: cannot reserve %d bytes of LDS", C::LDS_BYTES);
         attr_done = true;
@@ -727,7 +795,7 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
         // full-size output of a sparse call: one more workgroup per (head, span of positions) clears dropped rows
         const int64_t fill = (!out_compact && idx) ? (int64_t)BH * ((d.n + kFillSpan - 1) / kFillSpan) : 0;
         if (blocks + fill > 0x7fffffffLL) return set_error(ZIPVL_ESHAPE, "sparse_prefill: %lld workgroups exceed the grid limit", (long long)blocks);
-        hipLaunchKernelGGL((flash_kept_kernel<T, D, NW, QB>), dim3((unsigned)(blocks + fill)), dim3(C::NT),
+        hipLaunchKernelGGL((flash_kept_kernel<T, D, NW, QB, KS>), dim3((unsigned)(blocks + fill)), dim3(C::NT),
             C::LDS_BYTES, st, (const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
             skip_k ? (const T*)K : Kp, skip_k ? d.k_strides[0] : (int64_t)d.Hkv * npad * D,
             skip_k ? d.k_strides[1] : (int64_t)npad * D,
@@ -765,10 +833,19 @@ static int launch_prefill_t(const void* Q, const void* K, const void* V, const z
         if (rc) return rc;
     }
 
-    if constexpr (Elem<T>::kBytes == 2)
-        return launch_flash<T, D, kFlashWavesBf16, kFlashBlocksBf16>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
-    else
-        return launch_flash<T, D, 4, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
+    // A call with few query tiles lasts as long as the one with the most keys: about 1 us per 64 keys (a SIMD's products and
+    // exponentials one after the other) while most CUs are idle.  Tiles of 64 queries whose waves split the keys put the same
+    // work on twice the workgroups: half the work per step on every SIMD, and long tiles share a CU with short ones.  With
+    // enough tiles to fill the chip it only doubles the K / V traffic per query.  The lines (tiles of 128 queries; k is not
+    // known here, a set keeps a third or so), bf16, us, 128 -> 64: every token kept, 32 heads, n = 1500 (384 tiles)
+    // 46 -> 40, 28 heads on 4, n = 2933 (644) 83 -> 89; a third kept, 32 heads, n = 2933 (736) 55 -> 47, n = 5000 (1280)
+    // 78 -> 82; 60 % kept 70.3 -> 69.9 (736), 94 -> 99 (28 heads, n = 4500, 1008).  Below n = 1000 the chains are short:
+    // every token kept, 3 x 28 heads, n = 400 (336) 22.5 -> 25.6, 2 x 32 heads, n = 500 (256) 24 -> 22.  fp32: 2 x 8 heads,
+    // n = 1500, every token (192) 203 -> 119, 512 tiles 170 -> 182; a third kept, 768 tiles 184 -> 181, 1536 241 -> 242.
+    const int64_t tiles = (int64_t)((d.n + 127) / 128) * d.B * d.Hq;
+    if (tiles <= (d.n >= 1000 ? 384 : 256) * (idx ? 2 : 1))
+        return launch_flash<T, D, 4, 1, 2>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
+    return launch_flash<T, D, 4, 1, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
 }
 
 int launch_sparse_prefill(const void* Q, const void* K, const void* V, const zipvl_dims& d,

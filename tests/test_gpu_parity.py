@@ -419,6 +419,36 @@ def test_attention_logits_far_from_zero():
         _attention_case(1, 4, 4, 450, d, dtype, ks, seed=seed + 6, reshape_inputs=mixed)
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("gain", [1.0, 16.0])
+def test_attention_with_either_query_tile(dtype, d, gain):
+    """The same heads in a small call (query tiles of 64, the keys of a tile split over two waves) and repeated in a batch large
+    enough for tiles of 128: kept counts around 32-key blocks and both tiles, dropped rows, and logits (gain 16) that take the
+    pass with running maxima.  Both against the oracle with the bounds used above."""
+    say(f"attention query tiles dtype={dtype} d={d} gain={gain}")
+    n, ks = 330, [1, 31, 32, 33, 63, 64, 65, 96, 97, 128, 129, 161, 192, 193, 257, 330]
+    Hkv = len(ks)
+    w = make_custom(1, Hkv, Hkv, n, d, dtype, seed=51)
+    rnd = (lambda x: torch.from_numpy(x).bfloat16().float().numpy()) if dtype == "bf16" else (lambda x: x)
+    Qh = rnd((w.Q * np.float32(gain)).astype(np.float32))
+    Q, K, V = dev(Qh, dtype), dev(w.K, dtype), dev(w.V, dtype)
+    r = np.random.Generator(np.random.PCG64(52))
+    idx = np.zeros((Hkv, n), dtype=np.int32)
+    for u, k in enumerate(ks):
+        idx[u, :k] = np.sort(r.choice(n, k, replace=False))
+    idx_d, k_d = torch.from_numpy(idx).to(DEV), torch.tensor(ks, dtype=torch.int32, device=DEV)
+    copies = 512 // (3 * Hkv) + 1                            # 3 tiles of 128 per head: beyond 512 tiles
+    for B in (1, copies):
+        O = torch.full((B, Hkv, n, d), 7.0, dtype=Q.dtype, device=DEV)
+        z.zipvl_sparse_prefill(Q.repeat(B, 1, 1, 1), K.repeat(B, 1, 1, 1), V.repeat(B, 1, 1, 1), idx_d.repeat(B, 1), k_d.repeat(B), w.scale, O=O)
+        torch.cuda.synchronize()
+        assert torch.equal(O, O[:1].expand_as(O))            # every copy the same bits
+        for u in range(Hkv):
+            ref = oz.kept_token_attention(Qh[0, u], w.K[0, u], w.V[0, u], idx[u, :ks[u]], w.scale)
+            worst = np.abs(host64(O[0, u]) - ref).max()
+            assert worst <= ATOL_OUT[dtype], f"B={B} k={ks[u]}: {worst:.3e}"
+
+
 def test_attention_compact_output_rows():
     say("attention OUT_COMPACT")
     _attention_case(1, 4, 2, 500, 128, "bf16", [333, 128], seed=7, flags=z.OUT_COMPACT)
