@@ -226,7 +226,7 @@ def zipvl_select(mass: torch.Tensor, rank: Optional[torch.Tensor], tau: float, *
                  idx: Optional[torch.Tensor] = None, k: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None,
                  status: Optional[torch.Tensor] = None):
     """(idx [units,n] int32 with the first k entries valid and ascending, k [units] int32).  ws: select_workspace(units)
-    for the two-kernel form, None for the one-kernel form.  status: int32 [units] tensor that receives the SELECT_* bits."""
+    for the two-kernel form (taken for n > 32768), None for the one-kernel form.  status: int32 [units] tensor that receives the SELECT_* bits."""
     lib = load_library()
     _dense(mass, rank, idx, k)
     units, n = mass.shape

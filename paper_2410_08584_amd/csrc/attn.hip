@@ -7,7 +7,8 @@
 //          nothing is packed at all (the P.V operand comes from row-major V tiles in LDS:
 //          bf16 through the transposing read, fp32 one element per lane and product).
 //   flash  one workgroup = 128 kept queries of one query head (4 waves x 32
-//          rows).  K / V tiles of 64 keys are loaded straight into LDS (double
+//          rows; 64 where there are few, two waves then share 32 rows and halve
+//          the keys of every tile).  K / V tiles of 64 keys are loaded straight into LDS (double
 //          buffered) and shared by the four waves.  S^T = K Q^T and O^T = V^T P^T
 //          are taken on 32x32 MFMA tiles, so a lane owns one query column and the
 //          softmax statistics are per-lane scalars.  The key loop is a pipeline
