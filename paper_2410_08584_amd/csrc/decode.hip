@@ -159,9 +159,11 @@ __device__ __forceinline__ void merge_splits(const PartialOut& po, int G, int ns
     }
 }
 
-// Merge the states of a wave's four row groups (16 lanes each), result in all four.
-template <int EPL>
-__device__ __forceinline__ void merge_row_groups(float& m, float& l, float (&o)[EPL]) {
+// Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state (one head).
+template <int D, bool COHERENT>
+__device__ __forceinline__ void write_partial(float m, float l, float (&o)[D / 16], float (&red)[4][1][D + 2], const PartialOut& po, int split) {
+    constexpr int EPL = D / 16;
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
 #pragma unroll
     for (int off = 16; off <= 32; off <<= 1) {
         const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
@@ -170,14 +172,6 @@ __device__ __forceinline__ void merge_row_groups(float& m, float& l, float (&o)[
         for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[e], off);
         merge_state<EPL>(m, l, o, m2, l2, o2);
     }
-}
-
-// Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state (one head).
-template <int D, bool COHERENT>
-__device__ __forceinline__ void write_partial(float m, float l, float (&o)[D / 16], float (&red)[4][1][D + 2], const PartialOut& po, int split) {
-    constexpr int EPL = D / 16;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, sub = lane & 15, rg = lane >> 4;
-    merge_row_groups<EPL>(m, l, o);
     if (rg == 0) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) red[w][0][sub * EPL + e] = o[e];
@@ -1010,7 +1004,14 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
         for (int e = 0; e < EPL; ++e) { qv[e] *= c; o[e] = 0.f; }
         const int64_t base = (int64_t)u * cap_t * D + n * EPL;
         attend_rows<T, D>(Kt + base, Vt + base, nullptr, nullptr, nullptr, nullptr, -1, r_begin, r_end, tid >> 4, qv, m, l, o);
-        merge_row_groups<EPL>(m, l, o);
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            const float m2 = __shfl_xor(m, off), l2 = __shfl_xor(l, off);
+            float o2[EPL];
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) o2[e] = __shfl_xor(o[e], off);
+            merge_state<EPL>(m, l, o, m2, l2, o2);
+        }
         if (kk == 0) {
 #pragma unroll
             for (int e = 0; e < EPL; ++e) out[n * EPL + e] = o[e];
