@@ -739,7 +739,8 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
 // A group of one head leaves 15 of 16 columns of a floating-point tile empty, and the vector units need 1.6 instructions per
 // element and side.  The codes are small integers, so both products run on v_mfma_i32_16x16x64_i8, the other operand cut
 // into four signed bytes of a 30-bit fixed-point number (the columns that one head leaves empty): every product and sum is
-// exact, the only rounding is that of a query element to 2^-29 of the largest and of a weight to 2^-27 of the largest.
+// exact, the only rounding is that of a query element to 2^-29 of the largest and of a weight to 2^-27 of the largest that the
+// wave has met under the present exponent offset.
 // The codes enter about their middle, 2 code - 15 or 2 code - 3 (in the integer sums, with the sums of the bytes alone):
 //   q . (zero + scale * code) = (zero + scale * mid) * sum(q) + scale / 2 * (q . (2 code - 2 mid)),
 //   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j (zero_j + scale_j * mid) + sum_j (p_j scale_j) / 2 (2 code_j - 2 mid),
@@ -752,7 +753,8 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
 //   output   A = the bytes of the 64 weights, B = codes of 16 channels x 64 rows, from the row-major codes in LDS through the
 //            transposing 4-bit read (2-bit codes: two channels a nibble).
 // The exponent offset is the wave's and moves lazily; it and the fixed-point scale of the weights are fixed until a row
-// outgrows them, and then the integer sums go over to fp32.
+// outgrows them, and then the integer sums go over to fp32.  A new offset takes a new scale: rows of V a thousand times larger
+// than the others, which then turn out to weigh nothing, would leave the others 10 bits less (with 1e4 and 1e-3, 3 % off).
 // Four layers of 128 units x 8192 rows: 115 us a step, some 20 us a layer in this kernel (151 and 33 on the vector units).
 // Error of the output against float64, fp32 queries, n = 300 to 30000: 3.9e-7 in the mean (2.4e-6 on the vector units).
 typedef int intx4 __attribute__((ext_vector_type(4)));
@@ -939,6 +941,7 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
                     flush(a);
                     l *= a; zacc *= a;
                     m = top;
+                    ws = INFINITY;                           // weights under the new offset: the rows that set the scale may not count any more
                 }
                 const float p = valid ? fast_exp2(sc - (m > -INFINITY ? m : 0.f)) : 0.f, wt = p * vs;
                 l += p;

@@ -973,6 +973,61 @@ def test_decode_over_quantised_cache_at_tile_edges(dtype, d, G):
     assert worst <= (2e-2 if dtype == "bf16" else 5e-5)
 
 
+def _one_head_cache(K, V, kept, copies):
+    """The mixed-precision cache of a few heads K, V [heads, n, d], `copies` times over: with 300 units and more a launch
+    splits a unit's rows two or three ways, so that every wave takes several blocks of 64 rows of either part."""
+    heads, n, d = K.shape
+    r = np.random.Generator(np.random.PCG64(n + d))
+    idx = np.zeros((heads, n), dtype=np.int32)
+    for h in range(heads):
+        idx[h, :kept] = np.sort(r.choice(n, kept, replace=False))
+    grow = lambda x: dev(x, "f32")[None].expand(copies, -1, -1, -1)
+    cache = z.zipvl_quantize_kv(grow(K), grow(V), torch.from_numpy(idx).to(DEV).repeat(copies, 1),
+                                torch.full((copies * heads,), kept, dtype=torch.int32, device=DEV), kept, n - kept)
+    return cache, idx
+
+
+def _check_one_head(name, q, K, V, kept, bound, copies=110):
+    """|do| of every channel against `bound` times what the channel's rows weigh in all, sum_j p_j |v_j| (float64, from the codes)."""
+    heads, n, d = K.shape
+    scale = 1.0 / math.sqrt(d)
+    cache, idx = _one_head_cache(K, V, kept, copies)
+    o = z.zipvl_decode_attn_q(dev(np.tile(q, (copies, 1)), "f32"), cache, scale, B=copies, Hq=heads, Hkv=heads)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o[:heads].repeat(copies, 1))       # every copy the same bits
+    worst = 0.0
+    for h in range(heads):
+        qc = oz.quantize_kv(K[h], V[h], idx[h, :kept])
+        ref = oz.decode_attention_quantized(q[h].astype(np.float64), qc, scale)
+        s = np.concatenate([oz.dequantize_rows(*qc["K_hi"]), oz.dequantize_rows(*qc["K_lo"])]) @ q[h].astype(np.float64) * scale
+        p = np.exp(s - s.max())
+        v = np.concatenate([oz.dequantize_rows(*qc["V_hi"]), oz.dequantize_rows(*qc["V_lo"])])
+        worst = max(worst, float((np.abs(host64(o[h]) - ref) / (p @ np.abs(v) / p.sum())).max()))
+    say(f"  {name}: worst |do| / sum p |v| = {worst:.2e} (bound {bound:.1e})")
+    assert worst <= bound, f"{name}: {worst:.3e}"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_one_head_decode_over_quantised_cache_keeps_its_precision_as_the_offset_moves(d):
+    """Rows of V that get smaller by seven orders of magnitude while the logits rise by 60, and large rows that later ones
+    outweigh: whatever was summed before, the rows that count are weighed in full.  Bound: log2-domain scores up to s = 90 in
+    fp32, two roundings of each and one of their sum: 3 * 2^-24 * 90 * ln 2 = 1.1e-5 of a weight, 2 to 3 times that with the
+    query's and the exponential's: 3e-5."""
+    say(f"decode_attn_q one head, offset and scale move, d={d}")
+    n, heads = 4000, 3
+    r = np.random.Generator(np.random.PCG64(81))
+    q = (r.standard_normal((heads, d)) + 1).astype(np.float32)
+    K, V = (r.standard_normal((heads, n, d)).astype(np.float32) for _ in range(2))
+    at = np.arange(n) / n
+    rise = np.stack([60 * at, 35 * (at > 0.7), 40 * (at * 8 % 1)])                   # logits of the three heads along the sequence
+    size = np.stack([10.0 ** (4 - 7 * at), np.where(at > 0.7, 1e-3, 1e4), np.where(at * 8 % 1 > 0.8, 1e-2, 1e3)])
+    unit = q / (q * q).sum(1, keepdims=True) * math.sqrt(d)                          # adds one to a head's logits
+    K += (rise[:, :, None] * unit[:, None, :]).astype(np.float32)
+    V *= size[:, :, None].astype(np.float32)
+    for kept in (1000, 4000 - 64, 64):
+        _check_one_head(f"kept {kept}", q, K, V, kept, 3e-5)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_one_head_decode_over_quantised_cache_in_blocks_of_64_rows(d):
     """Integer products: both parts around multiples of 64 rows; value rows from 1e-4 to 1e4, small ones first and last (the
