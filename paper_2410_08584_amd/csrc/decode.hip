@@ -741,10 +741,15 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
 // into four signed bytes of a 30-bit fixed-point number (the columns that one head leaves empty): every product and sum is
 // exact, the only rounding is that of a query element to 2^-29 of the largest and of a weight to 2^-27 of the largest that the
 // wave has met under the present exponent offset.
-// The codes enter about their middle, 2 code - 15 or 2 code - 3 (in the integer sums, with the sums of the bytes alone):
+// The K codes enter about their middle, 2 code - 15 or 2 code - 3 (in the integer sums, with the sums of the bytes alone):
 //   q . (zero + scale * code) = (zero + scale * mid) * sum(q) + scale / 2 * (q . (2 code - 2 mid)),
-//   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j (zero_j + scale_j * mid) + sum_j (p_j scale_j) / 2 (2 code_j - 2 mid),
-// either term of the size of the result; with plain codes they cancel (1.8e-6 of the output instead of 0.39e-6).
+// The output is the sum of two terms that may cancel,
+//   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j zero_j + sum_j w_j code_j,   w_j = p_j scale_j in fixed point,
+// whichever number of a row's codes is taken for the middle one: at the lowest code where a row has an outlier, in the middle of
+// the codes where it has none.  So they meet in double precision: the first is summed in it (one row per lane, 64 rows a step),
+// the second is exact, and what the fixed point leaves of p_j scale_j is weighed with the code that stands for the value 0,
+// which leaves the output with a slightly other weight of the whole row.  fp32, added about the middle: single channels up to
+// 1.1e-5 off beside an outlier of 1000 in the row (now 1e-7); from the lowest code: 1.8e-6 of ordinary outputs (0.3e-6).
 // A wave takes 64 rows at a time:
 //   scores   A = the bytes of q (row m of the tile: byte m % 4), B = 16 cached rows, lane (n, kk) unpacking a quarter kk of the
 //            codes of row n (1.5 instructions per 4 codes): the lane's accumulators are the four bytes' sums of row n, and
@@ -762,22 +767,32 @@ typedef int intx2 __attribute__((ext_vector_type(2)));
 
 // Over the wave by lane permutes in registers (a shuffle through LDS takes some 100 clocks a step): shifts inside rows of 16
 // lanes, then across the rows; the last lane has it all.
-template <typename F>
-__device__ __forceinline__ float wave_reduce(float v, float none, F&& f) {
-    auto moved = [&](auto ctrl, auto rows) {
-        return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), decltype(ctrl)::value, decltype(rows)::value, 0xF, false));
-    };
-    using std::integral_constant;
-    v = f(v, moved(integral_constant<int, 0x111>(), integral_constant<int, 0xF>()));
-    v = f(v, moved(integral_constant<int, 0x112>(), integral_constant<int, 0xF>()));
-    v = f(v, moved(integral_constant<int, 0x114>(), integral_constant<int, 0xF>()));
-    v = f(v, moved(integral_constant<int, 0x118>(), integral_constant<int, 0xF>()));
-    v = f(v, moved(integral_constant<int, 0x142>(), integral_constant<int, 0xA>()));
-    v = f(v, moved(integral_constant<int, 0x143>(), integral_constant<int, 0xC>()));
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float lane_moved(float v, float none) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), CTRL, ROWS, 0xF, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_moved(double v, double none) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(__double2hiint(none), __double2hiint(v), CTRL, ROWS, 0xF, false),
+                            __builtin_amdgcn_update_dpp(__double2loint(none), __double2loint(v), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ float last_lane(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); }
+__device__ __forceinline__ double last_lane(double v) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+template <typename N, typename F>
+__device__ __forceinline__ N wave_reduce(N v, N none, F&& f) {
+    v = f(v, lane_moved<0x111, 0xF>(v, none));
+    v = f(v, lane_moved<0x112, 0xF>(v, none));
+    v = f(v, lane_moved<0x114, 0xF>(v, none));
+    v = f(v, lane_moved<0x118, 0xF>(v, none));
+    v = f(v, lane_moved<0x142, 0xA>(v, none));
+    v = f(v, lane_moved<0x143, 0xC>(v, none));
+    return last_lane(v);
 }
 __device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, -INFINITY, [](float a, float b) { return fmaxf(a, b); }); }
-__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, 0.f, [](float a, float b) { return a + b; }); }
+template <typename N>
+__device__ __forceinline__ N wave_sum(N v) { return wave_reduce(v, N(0), [](N a, N b) { return a + b; }); }
 
 // |x| < 2^30 as four signed bytes of weight 256^i, byte i in bits 8 i ...
 __device__ __forceinline__ uint32_t signed_bytes(int x) { return ((uint32_t)x + 0x00808080u) ^ 0x00808080u; }
@@ -785,11 +800,16 @@ __device__ __forceinline__ uint32_t signed_bytes(int x) { return ((uint32_t)x + 
 __device__ __forceinline__ float from_bytes(const intx4& s) {
     return fmaf(fmaf(fmaf((float)s[3], 256.f, (float)s[2]), 256.f, (float)s[1]), 256.f, (float)s[0]);
 }
+__device__ __forceinline__ double exact_from_bytes(const intx4& s) {
+    return fma(fma(fma((double)s[3], 256.0, (double)s[2]), 256.0, (double)s[1]), 256.0, (double)s[0]);
+}
 // exponent e of a power of two with |x| * 2^e in [2^(bits - 1), 2^bits); 0 for x = 0
 __device__ __forceinline__ int fixed_exponent(float x, int bits) {
     return x > 0.f ? max(-100, min(100, bits - (int)((__float_as_uint(x) >> 23) & 255u) + 126)) : 0;
 }
 __device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
+
+constexpr float kNoScale = 0x1p100f;      // fixed-point scale until a weight is met: the largest that fixed_exponent gives
 
 // Rows of BITS-bit codes as a wave of decode_q1_partial_kernel takes them.
 template <int D, int BITS> struct CodeRows {
@@ -866,7 +886,7 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
     bool have_query = false;
     auto attend_codes = [&](auto bits, const uint8_t* kc, const uint32_t* kp, const uint8_t* vc, const uint32_t* vp, int64_t base,
                             int L, int first, int last, float* out) {
-        constexpr int BITS = decltype(bits)::value, kTwoMid = (1 << BITS) - 1;
+        constexpr int BITS = decltype(bits)::value, kTop = (1 << BITS) - 1, kTwoMid = kTop;
         using R = CodeRows<D, BITS>;
         struct Block { uint32_t k[4][R::NW]; uintx4 v[R::CPR]; uint32_t kp, vp; };
         auto fetch = [&](int blk, Block& x) {
@@ -882,18 +902,24 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
             x.kp = kp[row];
             x.vp = vp[row];
         };
-        float m = -INFINITY, l = 0.f, zacc = 0.f, ws = INFINITY, w_inv = 0.f, of[NG];     // m, ws, w_inv: of the wave
-        intx4 o[NG], ow = {0, 0, 0, 0};                       // sums of weight bytes times codes, and of the weight bytes
+        // of the wave: m, ws, w_inv (the scale of the weights and its reciprocal), any (integer sums other than 0)
+        float m = -INFINITY, l = 0.f, ws = kNoScale, w_inv = 1.f / kNoScale, of[NG];
+        double zacc = 0.0;                                    // this lane's rows: what their weight has besides the integer sums
+        bool any = false;
+        intx4 o[NG];                                          // sums of weight bytes times codes
         const intx4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 #pragma unroll
         for (int g = 0; g < NG; ++g) { of[g] = 0.f; o[g] = intx4{0, 0, 0, 0}; }
-        auto flush = [&](float a) {                          // integer sums -> fp32, which are then scaled by a
+        auto flush = [&](float a) {                           // all sums -> fp32, which are then scaled by a
+            const double z = any ? wave_sum(zacc) : 0.0;
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
-                of[g] = fmaf(from_bytes(2 * o[g] - kTwoMid * ow), 0.5f * w_inv, of[g]) * a;
+                if (any) of[g] = (float)fma(exact_from_bytes(o[g]), (double)w_inv, z + (double)of[g]);
+                of[g] *= a;
                 o[g] = intx4{0, 0, 0, 0};
             }
-            ow = intx4{0, 0, 0, 0};
+            zacc = 0.0;
+            any = false;
         };
         if (first < last) {
             Block cur;
@@ -939,20 +965,25 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
                 if (__any(sc > m + kDecLazyLog2)) {
                     const float top = wave_max(sc), a = m > -INFINITY ? fast_exp2(m - top) : 0.f;
                     flush(a);
-                    l *= a; zacc *= a;
+                    l *= a;
                     m = top;
-                    ws = INFINITY;                           // weights under the new offset: the rows that set the scale may not count any more
+                    ws = kNoScale;                           // weights under the new offset: the rows that set the scale may not count any more
                 }
                 const float p = valid ? fast_exp2(sc - (m > -INFINITY ? m : 0.f)) : 0.f, wt = p * vs;
                 l += p;
-                zacc = fmaf(p, fmaf(0.5f * kTwoMid, vs, vz), zacc) + (wt - wt);      // NaN where a weight is no number
                 if (__any(fabsf(wt) * ws >= 0x1p30f)) {
                     flush(1.f);
                     const int ex = fixed_exponent(wave_max(fabsf(wt)), 28);
                     ws = power_of_two(ex);
                     w_inv = power_of_two(-ex);
                 }
-                const uint32_t z = signed_bytes(__float2int_rn(wt * ws));
+                const float wf = rintf(wt * ws);
+                // the rest of p * scale, exact, times the code of the value 0 (NaN where a weight is no number)
+                const float rest = fmaf(-wf, w_inv, wt) + fmaf(p, vs, -wt);
+                const float code0 = fminf(fmaxf(-vz * __builtin_amdgcn_rcpf(vs), 0.f), (float)kTop);
+                zacc = fma((double)p, (double)vz, zacc) + (double)(rest * code0);
+                any = true;
+                const uint32_t z = signed_bytes(__float2int_rn(wf));
                 // byte i of row `lane`, where the unpacked nibbles of a transposed read have that row
                 const int pos = 16 * kk + 8 * (n >> 3) + 4 * (n & 1) + ((n & 7) >> 1);
 #pragma unroll
@@ -960,7 +991,6 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 const uintx4 wa = load16(&wbytes[w][64 * (n & 3) + 16 * kk]);
                 const intx4 a4 = __builtin_bit_cast(intx4, wa);
-                ow = __builtin_amdgcn_mfma_i32_16x16x64_i8(a4, ones, ow, 0, 0, 0);
                 const int vrow = 16 * kk + n;
 #pragma unroll
                 for (int g = 0; g < R::RB / 8; ++g) {        // an 8-byte piece of 64 rows
@@ -980,12 +1010,11 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
             }
             flush(1.f);
             l = wave_sum(l);
-            zacc = wave_sum(zacc);
         }
         // all four quarters of the wave hold the same sums: each writes a quarter of the blocks
 #pragma unroll
         for (int g = 0; g < NG; ++g)
-            if (g % 4 == kk) out[BITS == 4 ? 16 * g + n : 32 * (g >> 1) + 2 * n + (g & 1)] = of[g] + zacc;
+            if (g % 4 == kk) out[BITS == 4 ? 16 * g + n : 32 * (g >> 1) + 2 * n + (g & 1)] = of[g];
         if (lane == 0) { out[D] = m; out[D + 1] = l; }
     };
     // this wave's first block at or after `from`

@@ -1029,6 +1029,23 @@ def test_one_head_decode_over_quantised_cache_keeps_its_precision_as_the_offset_
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_one_head_decode_over_quantised_cache_with_outliers_in_v(d):
+    """One channel of V far above or far below the others, which then share the lowest or the highest code of their rows, and
+    rows that are nearly constant: every channel to fp32 accuracy, not only the large one.  Bound: log2-domain scores up to
+    s = 12 in fp32, three roundings, 3 * 2^-24 * 12 * ln 2 = 1.5e-6 of a weight, and 2^-23 of its exponential: 2e-6."""
+    say(f"decode_attn_q one head, outliers in V, d={d}")
+    n, heads = 4000, 4
+    r = np.random.Generator(np.random.PCG64(83))
+    q = (r.standard_normal((heads, d)) + 1).astype(np.float32)
+    K, V = (r.standard_normal((heads, n, d)).astype(np.float32) for _ in range(2))
+    V[0, :, 7] += 1000
+    V[1, :, 9] -= 1000
+    V[2, ::3] = 100 + 1e-2 * V[2, ::3]
+    for kept in (1000, 4000 - 64):
+        _check_one_head(f"kept {kept}", q, K, V, kept, 2e-6)
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_one_head_decode_over_quantised_cache_in_blocks_of_64_rows(d):
     """Integer products: both parts around multiples of 64 rows; value rows from 1e-4 to 1e4, small ones first and last (the
     fixed-point scale of the weights moves); logits that rise along the sequence (the exponent offset moves); query elements
