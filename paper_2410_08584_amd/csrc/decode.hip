@@ -741,15 +741,15 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
 // into four signed bytes of a 30-bit fixed-point number (the columns that one head leaves empty): every product and sum is
 // exact, the only rounding is that of a query element to 2^-29 of the largest and of a weight to 2^-27 of the largest that the
 // wave has met under the present exponent offset.
-// The K codes enter about their middle, 2 code - 15 or 2 code - 3 (in the integer sums, with the sums of the bytes alone):
-//   q . (zero + scale * code) = (zero + scale * mid) * sum(q) + scale / 2 * (q . (2 code - 2 mid)),
-// The output is the sum of two terms that may cancel,
+// Scores and outputs are sums of two terms that may cancel,
+//   q . (zero + scale * code) = zero * sum(q) + scale * (q . code),
 //   sum_j p_j (zero_j + scale_j * code_j) = sum_j p_j zero_j + sum_j w_j code_j,   w_j = p_j scale_j in fixed point,
 // whichever number of a row's codes is taken for the middle one: at the lowest code where a row has an outlier, in the middle of
 // the codes where it has none.  So they meet in double precision: the first is summed in it (one row per lane, 64 rows a step),
 // the second is exact, and what the fixed point leaves of p_j scale_j is weighed with the code that stands for the value 0,
-// which leaves the output with a slightly other weight of the whole row.  fp32, added about the middle: single channels up to
-// 1.1e-5 off beside an outlier of 1000 in the row (now 1e-7); from the lowest code: 1.8e-6 of ordinary outputs (0.3e-6).
+// which leaves the output with a slightly other weight of the whole row.  fp32, added about the middle: scores up to 1e-3 off
+// beside an outlier of 1000 in rows of K (now by their own rounding), single channels up to 1.1e-5 beside one in V (now 1e-7);
+// from the lowest code: 1e-3 beside an outlier of -1000 in K, 1.8e-6 of ordinary outputs (0.3e-6).
 // A wave takes 64 rows at a time:
 //   scores   A = the bytes of q (row m of the tile: byte m % 4), B = 16 cached rows, lane (n, kk) unpacking a quarter kk of the
 //            codes of row n (1.5 instructions per 4 codes): the lane's accumulators are the four bytes' sums of row n, and
@@ -796,12 +796,12 @@ __device__ __forceinline__ N wave_sum(N v) { return wave_reduce(v, N(0), [](N a,
 
 // |x| < 2^30 as four signed bytes of weight 256^i, byte i in bits 8 i ...
 __device__ __forceinline__ uint32_t signed_bytes(int x) { return ((uint32_t)x + 0x00808080u) ^ 0x00808080u; }
-// and back, from sums over each byte
-__device__ __forceinline__ float from_bytes(const intx4& s) {
-    return fmaf(fmaf(fmaf((float)s[3], 256.f, (float)s[2]), 256.f, (float)s[1]), 256.f, (float)s[0]);
-}
-__device__ __forceinline__ double exact_from_bytes(const intx4& s) {
+// and back, from sums over each byte (of one row's channels: below 2^18, two of them fit an integer)
+__device__ __forceinline__ double from_bytes(const intx4& s) {
     return fma(fma(fma((double)s[3], 256.0, (double)s[2]), 256.0, (double)s[1]), 256.0, (double)s[0]);
+}
+__device__ __forceinline__ double from_row_bytes(const intx4& s) {
+    return fma((double)(s[3] * 256 + s[2]), 65536.0, (double)(s[1] * 256 + s[0]));
 }
 // exponent e of a power of two with |x| * 2^e in [2^(bits - 1), 2^bits); 0 for x = 0
 __device__ __forceinline__ int fixed_exponent(float x, int bits) {
@@ -861,13 +861,14 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
     const int B4 = (L4 + 63) >> 6, B2 = (L2 + 63) >> 6, per = (B4 + B2 + nsplit - 1) / nsplit;
     const int b0 = split * per, b1 = min(B4 + B2, b0 + per);
 
-    float qsum = 0.f, q_inv = 1.f;                           // sum of the scaled query; 1 / its fixed-point scale
+    double qsum = 0.0;                                       // sum of the scaled query
+    float q_inv = 1.f;                                       // 1 / its fixed-point scale
     auto prepare_query = [&]() {
         float f[D / 64], mx = 0.f;
 #pragma unroll
         for (int e = 0; e < D / 64; ++e) {
             f[e] = (float)q[(int64_t)u * D + 64 * e + lane] * c;
-            qsum += f[e];
+            qsum += (double)f[e];
             mx = fmaxf(mx, fabsf(f[e]));
         }
         qsum = wave_sum(qsum);
@@ -886,7 +887,7 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
     bool have_query = false;
     auto attend_codes = [&](auto bits, const uint8_t* kc, const uint32_t* kp, const uint8_t* vc, const uint32_t* vp, int64_t base,
                             int L, int first, int last, float* out) {
-        constexpr int BITS = decltype(bits)::value, kTop = (1 << BITS) - 1, kTwoMid = kTop;
+        constexpr int BITS = decltype(bits)::value, kTop = (1 << BITS) - 1;
         using R = CodeRows<D, BITS>;
         struct Block { uint32_t k[4][R::NW]; uintx4 v[R::CPR]; uint32_t kp, vp; };
         auto fetch = [&](int blk, Block& x) {
@@ -907,14 +908,13 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
         double zacc = 0.0;                                    // this lane's rows: what their weight has besides the integer sums
         bool any = false;
         intx4 o[NG];                                          // sums of weight bytes times codes
-        const intx4 ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
 #pragma unroll
         for (int g = 0; g < NG; ++g) { of[g] = 0.f; o[g] = intx4{0, 0, 0, 0}; }
         auto flush = [&](float a) {                           // all sums -> fp32, which are then scaled by a
             const double z = any ? wave_sum(zacc) : 0.0;
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
-                if (any) of[g] = (float)fma(exact_from_bytes(o[g]), (double)w_inv, z + (double)of[g]);
+                if (any) of[g] = (float)fma(from_bytes(o[g]), (double)w_inv, z + (double)of[g]);
                 of[g] *= a;
                 o[g] = intx4{0, 0, 0, 0};
             }
@@ -934,10 +934,6 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
                 R::query_operand(d, qa);
             }
             auto query = [&](int h) { return intx4{(int)qa[4 * h], (int)qa[4 * h + 1], (int)qa[4 * h + 2], (int)qa[4 * h + 3]}; };
-            intx4 qw = {0, 0, 0, 0};                         // sums of the query's bytes
-#pragma unroll
-            for (int h = 0; h < NM; ++h) qw = __builtin_amdgcn_mfma_i32_16x16x64_i8(query(h), ones, qw, 0, 0, 0);
-            qw *= kTwoMid;
             uint8_t* vb = vrows[w];
             for (int blk = first; blk < last; blk += 4) {
 #pragma unroll
@@ -961,7 +957,7 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
                 unpack_params(cur.vp, vs, vz);
                 if (blk + 4 < last) fetch(blk + 4, cur);     // in flight while this block is worked on
                 const bool valid = blk * 64 + lane < L;
-                const float sc = valid ? fmaf(0.5f * ks * q_inv, from_bytes(2 * mine - qw), fmaf(0.5f * kTwoMid, ks, kz) * qsum) : -INFINITY;
+                const float sc = valid ? (float)fma((double)(ks * q_inv), from_row_bytes(mine), (double)kz * qsum) : -INFINITY;
                 if (__any(sc > m + kDecLazyLog2)) {
                     const float top = wave_max(sc), a = m > -INFINITY ? fast_exp2(m - top) : 0.f;
                     flush(a);

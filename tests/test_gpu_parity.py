@@ -1046,6 +1046,26 @@ def test_one_head_decode_over_quantised_cache_with_outliers_in_v(d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_one_head_decode_over_quantised_cache_with_outliers_in_k(d):
+    """One channel of K far above or far below the others, which the query hardly looks at, and one of the query where all K are
+    0: the scores are the small sum of large terms.  Bound: log2-domain scores up to s = 128 in fp32, a rounding of each and one
+    of the difference to the largest: 2 * 2^-24 * 128 * ln 2 = 1.1e-5 of a weight, as much for its exponential: 2.2e-5."""
+    say(f"decode_attn_q one head, outliers in K, d={d}")
+    n, heads = 4000, 4
+    r = np.random.Generator(np.random.PCG64(85))
+    q = (r.standard_normal((heads, d)) + 1).astype(np.float32)
+    K, V = (r.standard_normal((heads, n, d)).astype(np.float32) for _ in range(2))
+    K[0, :, 7] += 1000
+    K[1, :, 9] -= 1000
+    q[0, 7] = q[1, 9] = 1e-3
+    K[2] = np.abs(K[2])
+    K[2, :, 11] = 0
+    q[2, 11] = 1000
+    for kept in (1000, 4000 - 64):
+        _check_one_head(f"kept {kept}", q, K, V, kept, 2.2e-5)
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_one_head_decode_over_quantised_cache_in_blocks_of_64_rows(d):
     """Integer products: both parts around multiples of 64 rows; value rows from 1e-4 to 1e4, small ones first and last (the
     fixed-point scale of the weights moves); logits that rise along the sequence (the exponent offset moves); query elements
