@@ -511,7 +511,11 @@ __global__ __launch_bounds__(kSelThreads, KPT <= 4 ? 8 : 4) void select_reg_kern
     auto collect = [&](uint32_t (&key)[KPT], auto with_sum) {
         constexpr bool WITH_SUM = decltype(with_sum)::value;
         Span s = get();
-        while (s.in_bin > (uint32_t)kRegCand && s.hi - s.lo > 1u) {
+        // A bin that holds a sixteenth of the vector or more (and more than 256 keys) holds close or equal scores: one wave would
+        // add 64 of them to one counter after the other, all waves do better although a list would take them.  Two vectors of
+        // 1000 scores, 4 units: all equal 22.0 us -> 11.6, within 1e-3 18.0 -> 9.0; 2933 of three values 22.8 -> 13.2.
+        const uint32_t most = (uint32_t)min(kRegCand, max(256, n >> 4));
+        while (s.in_bin > most && s.hi - s.lo > 1u) {
             const int shift = span_shift(s, 9);
             for (int i = tid; i < kRegRep * kRegStride; i += kSelThreads) { if (WITH_SUM) sh.hm[i] = 0ull; else sh.hr[i] = 0u; }
             __syncthreads();
