@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
     T* __restrict__ Kp, T* __restrict__ Vp, int n, int npad, int Hkv, int rows_are_kept, int skip_k, int skip_v, int t_per_batch)
 {
     constexpr int EPF = Elem<T>::kPerFrag;
-    constexpr int CPR = D / EPF;
+    constexpr int CPR = D / EPF, kPass = 256 / CPR, kPasses = kBN / kPass;
     const int u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
     const int t0 = blockIdx.x * kBN;
     const int ut = t_per_batch ? b : u;                   // row of idx / k that holds this unit's T
@@ -92,17 +92,29 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
     if (t0 >= kk) return;
     const T* Kb = K + b * ks0 + g * ks1;
     const T* Vb = V + b * vs0 + g * vs1;
-    for (int wi = threadIdx.x; wi < kBN * CPR; wi += 256) {
-        const int r = wi / CPR, cc = wi - r * CPR, row = t0 + r;
-        uintx4 kv = {0, 0, 0, 0}, vv = {0, 0, 0, 0};
-        if (row < kk) {
-            const int src = (idx && !rows_are_kept) ? idx[(int64_t)ut * n + row] : row;
-            if (!skip_k) kv = load16(Kb + (int64_t)src * ks2 + cc * EPF);
-            if (!skip_v) vv = load16(Vb + (int64_t)src * vs2 + cc * EPF);
-        }
-        if (!skip_k) store16(Kp + ((int64_t)u * npad + row) * D + cc * EPF, kv);    // rows past k are zero rows
-        if (!skip_v) store16(Vp + ((int64_t)u * npad + row) * D + cc * EPF, vv);
+    // Positions, then rows: all of a thread's are requested at once, as in compact_kv.  One after the other (each behind a branch on
+    // whether it is packed at all): 4 x 32 heads on 8, bf16, d = 128, n = 1500, a tenth kept 23.1 us a call (20.6 so), fp32 60.4 (55.7).
+    const int cc = threadIdx.x % CPR, r1 = t0 + threadIdx.x / CPR;
+    int src[kPasses];
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        const int row = min(r1 + p * kPass, kk - 1);
+        src[p] = (idx && !rows_are_kept) ? idx[(int64_t)ut * n + row] : row;
     }
+    uintx4 kr[kPasses] = {}, vr[kPasses] = {};
+    if (!skip_k)
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) kr[p] = load16(Kb + (int64_t)src[p] * ks2 + cc * EPF);
+    if (!skip_v)
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) vr[p] = load16(Vb + (int64_t)src[p] * vs2 + cc * EPF);
+    const int64_t out = ((int64_t)u * npad + r1) * D + cc * EPF;
+    if (!skip_k)
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) store16(Kp + out + p * kPass * D, r1 + p * kPass < kk ? kr[p] : uintx4{0, 0, 0, 0});   // rows past k are zero rows
+    if (!skip_v)
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) store16(Vp + out + p * kPass * D, r1 + p * kPass < kk ? vr[p] : uintx4{0, 0, 0, 0});
 }
 
 // ------------------------------------------------------------------ flash
