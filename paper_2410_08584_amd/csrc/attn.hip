@@ -288,72 +288,18 @@ template <> __device__ __forceinline__ void store_out4<__bf16>(__bf16* dst, floa
     *reinterpret_cast<uintx2*>(dst) = uintx2{pack_bf16x2(a, b), pack_bf16x2(c, d)};
 }
 
+// The kept queries i0 ... i0 + BM - 1 of one head by one workgroup.  Q: rows of the head; Kp, Vp: rows of its unit; O: of the head.
 template <typename T, int D, int NW, int QB, int KS>
-__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS>::MIN_WGS)) void flash_kept_kernel(
-    const T* __restrict__ Q, int64_t qs0, int64_t qs1, int64_t qs2,
-    const T* __restrict__ Kp, int64_t kp0, int64_t kp1, const T* __restrict__ Vp, int64_t vp0, int64_t vp1,
-    const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
-    T* __restrict__ O, int n, int npad, int ntq, int ug, int BH, int Hq, int Hkv, float c, int out_compact, int compute_blocks,
-    int t_per_batch, int k_in_place, int v_in_place)
+__device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t qs2, const T* __restrict__ Kp, const T* __restrict__ Vp,
+                                              const int32_t* __restrict__ tidx, T* __restrict__ O, int i0, int kk, int npad, float c,
+                                              int out_compact, int k_in_place, int v_in_place)
 {
     using C = AttnCfg<T, D, NW, QB, KS>;
-    constexpr int kBM = C::BM, kNT = C::NT, kRW = 32 * QB;   // queries per workgroup, threads, queries per wave
+    constexpr int kBM = C::BM, kRW = 32 * QB;                // queries per workgroup, queries per wave
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    // Workgroup -> (unit group, query tile, unit in group, head of the KV group), in that order of
-    // significance; heavy (late) query tiles first inside a group.  A group holds enough KV heads to
-    // fill the chip several times over (a few for long GQA sequences, many for short MHA ones): the
-    // chip then works through few KV heads at a time, so the caches hold little more than the K / V
-    // in use, while the light tail of one group overlaps the heavy start of the next.  The last query
-    // tile of a head runs for as long as all its kept keys take; a group must hold many times the
-    // chip's resident workgroups for that one not to end alone.
-    const int G = Hq / Hkv, NU = BH / G;
     const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, i = lane & 31, h = lane >> 5;
     // KS = 2: wave w has the queries of wave qw and key block kw of every tile
     const int qw = KS == 1 ? w : w % (NW / KS), kw = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(w / (NW / KS));
-    if (blockIdx.x >= (unsigned)compute_blocks) {
-        // Outputs of dropped tokens are zero rows.  The workgroups after the last attention workgroup
-        // each clear the dropped rows of one head inside one span of kFillSpan positions; they are
-        // dispatched last, into the slots that the light end of the attention work leaves idle.
-        const int f = blockIdx.x - compute_blocks, s = f / BH, fbh = f - s * BH;
-        const int fb = fbh / Hq, fu = fb * Hkv + (fbh - fb * Hq) / G;
-        const int32_t* ft = idx + (int64_t)(t_per_batch ? fb : fu) * n;
-        const int fk = kcnt ? max(0, min(kcnt[t_per_batch ? fb : fu], n)) : n;
-        const int p0 = s * kFillSpan, p1 = min(n, p0 + kFillSpan);
-        int* kept = reinterpret_cast<int*>(smem);            // [kFillSpan]
-        for (int e = tid; e < kFillSpan; e += kNT) kept[e] = 0;
-        int lo = 0, hi = fk;                                 // first kept row at or after p0 (T ascends)
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (ft[mid] < p0) lo = mid + 1; else hi = mid;
-        }
-        __syncthreads();
-        for (int e = lo + tid; e < min(fk, lo + kFillSpan); e += kNT) {
-            const int pos = ft[e];
-            if (pos >= p0 && pos < p1) kept[pos - p0] = 1;
-        }
-        __syncthreads();
-        constexpr int CPR = D * Elem<T>::kBytes / 16;
-        const uintx4 z = {0, 0, 0, 0};
-        char* base = reinterpret_cast<char*>(O + ((int64_t)fbh * n + p0) * D);
-        for (int q = tid; q < (p1 - p0) * CPR; q += kNT)
-            // whole rows, written once and not read again by this path: streaming stores, so that they do not stay
-            // behind as dirty lines in the last-level cache, to be written back under the next kernel's reads
-            if (!kept[q / CPR]) __builtin_nontemporal_store(z, reinterpret_cast<uintx4*>(base + (int64_t)q * 16));
-        return;
-    }
-    const int full = ug * ntq * G;                           // workgroups of a full group
-    const int ngroups = (NU + ug - 1) / ug;
-    const int grp = min((int)(blockIdx.x / full), ngroups - 1);
-    const int r = blockIdx.x - grp * full;
-    const int nu_g = min(ug, NU - grp * ug);
-    const int tile_rev = r / (nu_g * G), rr = r - tile_rev * (nu_g * G);
-    const int u = grp * ug + rr / G, hg = rr % G;
-    const int b = u / Hkv, g = u - b * Hkv, head = g * G + hg, bh = b * Hq + head;
-    const int i0 = (ntq - 1 - tile_rev) * kBM;
-    const int32_t* tidx = idx ? idx + (int64_t)(t_per_batch ? b : u) * n : nullptr;   // this unit's T
-    int kk = kcnt ? kcnt[t_per_batch ? b : u] : n;
-    kk = max(0, min(kk, n));
-    if (i0 >= kk) return;
     floatx16 o[QB][C::ODB];
     float m_run[QB], l_run[QB];
 
@@ -362,8 +308,8 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS>::MIN_WGS)) void
     const int key_room = min(wave_last_row, kk - 1) - 32 * kw;
     // later tiles lie wholly in this wave's future
     const int my_tiles = KS == 1 ? min(ntiles, wave_last_row / kBN + 1) : key_room >= 0 ? min(ntiles, key_room / kBN + 1) : 0;
-    const char* kg = reinterpret_cast<const char*>(Kp + b * kp0 + g * kp1);   // row-major kept rows of this unit
-    const char* vg = reinterpret_cast<const char*>(Vp + b * vp0 + g * vp1);
+    const char* kg = reinterpret_cast<const char*>(Kp);   // row-major kept rows of this unit
+    const char* vg = reinterpret_cast<const char*>(Vp);
     // An evicted cache that is read in place need not hold a row at or beyond k: the tile with row k - 1 is loaded as far
     // as that row (what stands for later rows is masked and weighs nothing).  Packed tiles are whole.  The steps that
     // request it run outside the steady state: at most 1 us of 289 at 128 heads x 8192 tokens.
@@ -402,7 +348,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS>::MIN_WGS)) void
         qrow[qb] = i0 + kRW * qw + 32 * qb + i;
         const int qclamp = min(qrow[qb], kk - 1);
         qpos[qb] = tidx ? tidx[qclamp] : qclamp;
-        const T* qp = Q + b * qs0 + head * qs1 + (int64_t)qpos[qb] * qs2;
+        const T* qp = Q + (int64_t)qpos[qb] * qs2;
 #pragma unroll
         for (int cc = 0; cc < C::CH; ++cc) qf[qb][cc] = load16(qp + cc * Elem<T>::kPerChunk + h * Elem<T>::kPerFrag);
     }
@@ -763,7 +709,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS>::MIN_WGS)) void
         if (qr < kk) {
             const float inv = 1.f / l_tot;
             const int orow = orow_out[qb];
-            T* op = O + ((int64_t)bh * n + orow) * D + (KS == 2 ? kw * (D / 2) : 0);
+            T* op = O + (int64_t)orow * D + (KS == 2 ? kw * (D / 2) : 0);
 #pragma unroll
             for (int db = 0; db < kOut; ++db)
 #pragma unroll
@@ -775,6 +721,90 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS>::MIN_WGS)) void
 }
 
 // ------------------------------------------------------------------ host
+// Whether a head's queries are taken 64 at a time with the keys split over two waves, where both are possible (KS = 0): k kept
+// tokens, BH heads alike, so many live tiles of 128.  bf16, d = 128, rows in place, us, 128 -> 64: k >= 1000: 448 live tiles (32 heads,
+// k = 1759) 44 -> 42, 532 (28 on 4, k = 2346) 57.1 -> 57.4, 576 (2 x 32 on 8, k = 1100) 35 -> 43, 688 (8, k = 11000) 258 -> 268; shorter:
+// 256 (4 x 32, k = 230) 14.7 -> 14.4, 252 (3 x 28 on 4, k = 300) 14.1 -> 12.9, 320 (2 x 32, k = 599) 22.1 -> 22.5, 384 (4 x 32, k = 300) 15.7 -> 18.6.
+__device__ __forceinline__ bool splits_keys(int k, int BH) { return ((k + 127) >> 7) * BH <= (k >= 1000 ? 512 : 288); }
+
+template <typename T, int D, int NW, int QB, int KS>
+__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, 1>::MIN_WGS)) void flash_kept_kernel(
+    const T* __restrict__ Q, int64_t qs0, int64_t qs1, int64_t qs2,
+    const T* __restrict__ Kp, int64_t kp0, int64_t kp1, const T* __restrict__ Vp, int64_t vp0, int64_t vp1,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
+    T* __restrict__ O, int n, int npad, int ntq, int ug, int BH, int Hq, int Hkv, float c, int out_compact, int compute_blocks,
+    int t_per_batch, int k_in_place, int v_in_place)
+{
+    using C = AttnCfg<T, D, NW, QB, KS == 1 ? 1 : 2>;
+    constexpr int kBM = C::BM, kNT = C::NT;                  // queries per workgroup, threads
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    // Workgroup -> (unit group, query tile, unit in group, head of the KV group), in that order of
+    // significance; heavy (late) query tiles first inside a group.  A group holds enough KV heads to
+    // fill the chip several times over (a few for long GQA sequences, many for short MHA ones): the
+    // chip then works through few KV heads at a time, so the caches hold little more than the K / V
+    // in use, while the light tail of one group overlaps the heavy start of the next.  The last query
+    // tile of a head runs for as long as all its kept keys take; a group must hold many times the
+    // chip's resident workgroups for that one not to end alone.
+    const int G = Hq / Hkv, NU = BH / G;
+    const int tid = threadIdx.x;
+    if (blockIdx.x >= (unsigned)compute_blocks) {
+        // Outputs of dropped tokens are zero rows.  The workgroups after the last attention workgroup
+        // each clear the dropped rows of one head inside one span of kFillSpan positions; they are
+        // dispatched last, into the slots that the light end of the attention work leaves idle.
+        const int f = blockIdx.x - compute_blocks, s = f / BH, fbh = f - s * BH;
+        const int fb = fbh / Hq, fu = fb * Hkv + (fbh - fb * Hq) / G;
+        const int32_t* ft = idx + (int64_t)(t_per_batch ? fb : fu) * n;
+        const int fk = kcnt ? max(0, min(kcnt[t_per_batch ? fb : fu], n)) : n;
+        const int p0 = s * kFillSpan, p1 = min(n, p0 + kFillSpan);
+        int* kept = reinterpret_cast<int*>(smem);            // [kFillSpan]
+        for (int e = tid; e < kFillSpan; e += kNT) kept[e] = 0;
+        int lo = 0, hi = fk;                                 // first kept row at or after p0 (T ascends)
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (ft[mid] < p0) lo = mid + 1; else hi = mid;
+        }
+        __syncthreads();
+        for (int e = lo + tid; e < min(fk, lo + kFillSpan); e += kNT) {
+            const int pos = ft[e];
+            if (pos >= p0 && pos < p1) kept[pos - p0] = 1;
+        }
+        __syncthreads();
+        constexpr int CPR = D * Elem<T>::kBytes / 16;
+        const uintx4 z = {0, 0, 0, 0};
+        char* base = reinterpret_cast<char*>(O + ((int64_t)fbh * n + p0) * D);
+        for (int q = tid; q < (p1 - p0) * CPR; q += kNT)
+            // whole rows, written once and not read again by this path: streaming stores, so that they do not stay
+            // behind as dirty lines in the last-level cache, to be written back under the next kernel's reads
+            if (!kept[q / CPR]) __builtin_nontemporal_store(z, reinterpret_cast<uintx4*>(base + (int64_t)q * 16));
+        return;
+    }
+    const int full = ug * ntq * G;                           // workgroups of a full group
+    const int ngroups = (NU + ug - 1) / ug;
+    const int grp = min((int)(blockIdx.x / full), ngroups - 1);
+    const int r = blockIdx.x - grp * full;
+    const int nu_g = min(ug, NU - grp * ug);
+    const int tile_rev = r / (nu_g * G), rr = r - tile_rev * (nu_g * G);
+    const int u = grp * ug + rr / G, hg = rr % G;
+    const int b = u / Hkv, g = u - b * Hkv, head = g * G + hg, bh = b * Hq + head;
+    const int32_t* tidx = idx ? idx + (int64_t)(t_per_batch ? b : u) * n : nullptr;   // this unit's T
+    int kk = kcnt ? kcnt[t_per_batch ? b : u] : n;
+    kk = max(0, min(kk, n));
+    // KS = 0: ntq tiles of 64 queries, or the first half as many workgroups take 128 each (every other one would leave an XCD idle)
+    const bool wide = KS == 1 || (KS == 0 && !splits_keys(kk, BH));
+    const int i0 = KS == 0 && wide ? ((ntq + 1) / 2 - 1 - tile_rev) * (2 * kBM) : (ntq - 1 - tile_rev) * kBM;
+    if (i0 < 0 || i0 >= kk) return;
+    Q += b * qs0 + head * qs1;
+    Kp += b * kp0 + g * kp1;
+    Vp += b * vp0 + g * vp1;
+    O += (int64_t)bh * n * D;
+    auto queries = [&](auto ks) {
+        flash_queries<T, D, NW, QB, decltype(ks)::value>(Q, qs2, Kp, Vp, tidx, O, i0, kk, npad, c, out_compact, k_in_place, v_in_place);
+    };
+    if constexpr (KS != 0) queries(std::integral_constant<int, KS>{});
+    else if (wide) queries(std::integral_constant<int, 1>{});
+    else queries(std::integral_constant<int, 2>{});
+}
+
 size_t prefill_workspace_bytes(const zipvl_dims& d) {
     const int e = d.dtype == ZIPVL_BF16 ? 2 : 4;
     const size_t npad = ((size_t)d.n + kBN - 1) / kBN * kBN;
@@ -785,7 +815,7 @@ template <typename T, int D, int NW, int QB, int KS>
 static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                         float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, void* O, hipStream_t st)
 {
-    using C = AttnCfg<T, D, NW, QB, KS>;
+    using C = AttnCfg<T, D, NW, QB, KS == 1 ? 1 : 2>;
     static std::atomic<bool> attr_done{false};       // raising the dynamic-LDS cap is idempotent
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kept_kernel<T, D, NW, QB, KS>),
@@ -849,14 +879,20 @@ static int launch_prefill_t(const void* Q, const void* K, const void* V, const z
     // A call with few query tiles lasts as long as the one with the most keys: about 1 us per 64 keys (a SIMD's products and
     // exponentials one after the other) while most CUs are idle.  Tiles of 64 queries whose waves split the keys put the same
     // work on twice the workgroups: half the work per step on every SIMD, and long tiles share a CU with short ones.  With
-    // enough tiles to fill the chip it only doubles the K / V traffic per query.  The lines (tiles of 128 queries; k is not
-    // known here, a set keeps a third or so), bf16, us, 128 -> 64: every token kept, 32 heads, n = 1500 (384 tiles)
-    // 46 -> 40, 28 heads on 4, n = 2933 (644) 83 -> 89; a third kept, 32 heads, n = 2933 (736) 55 -> 47, n = 5000 (1280)
-    // 78 -> 82; 60 % kept 70.3 -> 69.9 (736), 94 -> 99 (28 heads, n = 4500, 1008).  Below n = 1000 the chains are short:
-    // every token kept, 3 x 28 heads, n = 400 (336) 22.5 -> 25.6, 2 x 32 heads, n = 500 (256) 24 -> 22.  fp32: 2 x 8 heads,
-    // n = 1500, every token (192) 203 -> 119, 512 tiles 170 -> 182; a third kept, 768 tiles 184 -> 181, 1536 241 -> 242.
-    const int64_t tiles = (int64_t)((d.n + 127) / 128) * d.B * d.Hq;
-    if (tiles <= (d.n >= 1000 ? 384 : 256) * (idx ? 2 : 1))
+    // enough tiles to fill the chip it only doubles the K / V traffic per query.  The line (tiles of 128 queries), bf16, d = 128,
+    // us, 128 -> 64: every token kept, 32 heads, n = 1500 (384 tiles) 42 -> 37, 28 heads on 4, n = 2933 (644) 74 -> 82; below
+    // n = 1000 the chains are short: 3 x 28 heads on 4, n = 500 (336) 20.2 -> 21.6, 2 x 32 heads, n = 500 (256) 24 -> 22.
+    // Of a set only some tiles are live, and k is on the device.  Up to twice the line, bf16 at d = 128 decides there, head by
+    // head (splits_keys; the kernel of both needs no more registers than that of 128): 32 heads, n = 2933, a third kept 29.5 us (128)
+    // and 22.0 (64), 22.0 so, all of a set kept 80, 91 and 79; 4 x 32 heads, n = 500, 60 % kept 15.4, 18.5 and 15.3, all 21.4, 27.1 and
+    // 22.4.  At d = 64 it would take the kernel of 64 a third of its waves: with up to 60 % kept 64 is
+    // faster or equal (2 x 32 heads, n = 960, 512 tiles 12.5 -> 11.4), with all of a set kept up to 17 % slower.  fp32: a third kept,
+    // 736 tiles 138 -> 136, 1536 241 -> 242; 60 %, 512 tiles 69 -> 60 (n = 500), 736 349 -> 293.
+    const int64_t tiles = (int64_t)((d.n + 127) / 128) * d.B * d.Hq, line = d.n >= 1000 ? 384 : 256;
+    if constexpr (Elem<T>::kBytes == 2 && D == 128)
+        if (tiles > line && tiles <= 2 * line && idx)
+            return launch_flash<T, D, 4, 1, 0>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
+    if (tiles <= line * (idx ? 2 : 1))
         return launch_flash<T, D, 4, 1, 2>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
     return launch_flash<T, D, 4, 1, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
 }

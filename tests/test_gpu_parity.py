@@ -449,6 +449,39 @@ def test_attention_with_either_query_tile(dtype, d, gain):
             assert worst <= ATOL_OUT[dtype], f"B={B} k={ks[u]}: {worst:.3e}"
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,gain", [(900, 1.0), (900, 16.0), (1100, 1.0)])
+def test_attention_query_tile_chosen_by_kept_tokens(d, n, gain):
+    """A call whose heads may take either query tile, each by its own count: 64 heads alike in fours, counts around 64-row and
+    128-row tiles and around the counts where the choice turns (n = 900: four tiles of 128, 1100: 999 and eight tiles); rows packed,
+    and in place in an evicted cache that is NaN from row k on; gain 16: logits that take the pass with running maxima."""
+    say(f"attention query tile by kept tokens d={d} n={n} gain={gain}")
+    ks = [0, 1, 63, 64, 65, 127, 129, 300, 511, 512, 513, 575, 640, 700, n - 1, n] if n < 1000 else [1, 64, 129, 300, 511, 512, 513, 641, 769, 895, 999, 1000, 1023, 1025, n - 1, n]
+    units, B = len(ks), 4
+    w = make_custom(1, units, units, n, d, "bf16", seed=53)
+    Qh = torch.from_numpy((w.Q * np.float32(gain)).astype(np.float32)).bfloat16().float().numpy()
+    Q, K, V = (dev(x, "bf16").repeat(B, 1, 1, 1) for x in (Qh, w.K, w.V))
+    r = np.random.Generator(np.random.PCG64(54))
+    idx = np.zeros((units, n), dtype=np.int32)
+    for u, k in enumerate(ks):
+        idx[u, :k] = np.sort(r.choice(n, k, replace=False))
+    idx_d, k_d = torch.from_numpy(idx).to(DEV).repeat(B, 1), torch.tensor(ks, dtype=torch.int32, device=DEV).repeat(B)
+    packed, inplace = (torch.full((B, units, n, d), 7.0, dtype=Q.dtype, device=DEV) for _ in range(2))
+    z.zipvl_sparse_prefill(Q, K, V, idx_d, k_d, w.scale, O=packed)
+    Kc, Vc, _ = z.zipvl_compact_kv(K, V, idx_d, k_d, n)
+    Kc, Vc = Kc.view(B, units, n, d), Vc.view(B, units, n, d)
+    for u, k in enumerate(ks):
+        Kc[:, u, k:] = float("nan")
+        Vc[:, u, k:] = float("nan")
+    z.zipvl_sparse_prefill(Q, Kc, Vc, idx_d, k_d, w.scale, z.OUT_FULL | z.KV_ALREADY_COMPACT, O=inplace)
+    torch.cuda.synchronize()
+    assert torch.equal(packed, inplace) and torch.equal(packed, packed[:1].expand_as(packed))
+    for u, k in enumerate(ks):
+        ref = oz.kept_token_attention(Qh[0, u], w.K[0, u], w.V[0, u], idx[u, :k], w.scale)
+        worst = np.abs(host64(packed[0, u]) - ref).max()
+        assert worst <= ATOL_OUT["bf16"], f"k={k}: {worst:.3e}"
+
+
 def test_attention_compact_output_rows():
     say("attention OUT_COMPACT")
     _attention_case(1, 4, 2, 500, 128, "bf16", [333, 128], seed=7, flags=z.OUT_COMPACT)
