@@ -22,6 +22,7 @@
 // the result does not depend on scheduling).
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "launch.h"
 #include "ldsload.h"
@@ -152,28 +153,41 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
         const int Plast = __builtin_amdgcn_readfirstlane(sp[min(nb * 32 + 31, m - 1)]);
 
         if (PASS == 2) {
-            // Merge the chunk statistics of this task's 32 rows: lane = (pair of rows, quarter of the chunks), 16 bytes a load, eight
-            // loads in flight, one exponential per statistic.  28 heads on 4, n = 18432: a workgroup reads 229 KB of them, the
+            // Merge the chunk statistics of this task's 32 rows: lane = (pair of rows, quarter of the chunks), 16 bytes a load, up to
+            // eight in flight, one exponential per statistic.  28 heads on 4, n = 18432: a workgroup reads 229 KB of them, the
             // prologue took 9.9 of pass 2's 23 us with 8-byte loads and pairwise merges, 7.0 so (a CU takes in some 40 GB/s).
             const floatx4* p = reinterpret_cast<const floatx4*>(partial + (int64_t)bh * nsplit * np + nb * 32);   // wave-uniform base; the rest fits 32 bits (host check)
             const int pr = lane & 15, cg = lane >> 4;
             float M[2] = {-INFINITY, -INFINITY}, L[2] = {0.f, 0.f};
-            for (int s0 = cg; s0 < nsplit; s0 += 32) {
-                floatx4 v[8];
+            auto take = [&](int first, auto loads) {
+                constexpr int N = decltype(loads)::value;
+                const int s0 = first + cg;
+                floatx4 v[N];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = p[min(s0 + 4 * q, nsplit - 1) * (np / 2) + pr];
+                for (int q = 0; q < N; ++q) v[q] = p[min(s0 + 4 * q, nsplit - 1) * (np / 2) + pr];
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
                     float top = M[r];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) top = fmaxf(top, v[q][2 * r]);             // a chunk read twice changes nothing
+                    for (int q = 0; q < N; ++q) top = fmaxf(top, v[q][2 * r]);             // a chunk read twice changes nothing
                     const float off = top > -INFINITY ? top : 0.f;
                     float sum = L[r] * fast_exp2((M[r] - off) * c);
 #pragma unroll
-                    for (int q = 0; q < 8; ++q)
+                    for (int q = 0; q < N; ++q)
                         sum = fmaf(s0 + 4 * q < nsplit ? v[q][2 * r + 1] : 0.f, fast_exp2((v[q][2 * r] - off) * c), sum);
                     M[r] = top; L[r] = sum;
                 }
+            };
+            // no more loads than there are chunks for: a short sequence reads few (28 heads on 4, n = 100, m = 64: 18.6 us with eight,
+            // 17.8; fp32 at d = 128 with 16 waves holds 64 registers of probe rows: four at a time, 140 bytes of scratch and not 176)
+            if constexpr (C::E == 4 && D == 128 && NWV == 16) {
+                for (int first = 0; first < nsplit; first += 16) take(first, std::integral_constant<int, 4>{});
+            } else if (nsplit <= 4) {
+                take(0, std::integral_constant<int, 1>{});
+            } else if (nsplit <= 16) {
+                take(0, std::integral_constant<int, 4>{});
+            } else {
+                for (int first = 0; first < nsplit; first += 32) take(first, std::integral_constant<int, 8>{});
             }
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
