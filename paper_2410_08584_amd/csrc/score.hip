@@ -199,10 +199,13 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             __syncthreads();
         }
 
-        // The probe rows have to be here now.  Left to the tile loop, the compiler's wait for them stands in front of every
-        // tile's first product and, not knowing of the stage loads, waits for those just requested too.
+        // The probe rows have to be here now.  Left to the tile loop, the compiler's wait for them stands in front of every tile's
+        // first product and, not knowing of the stage loads, waits for those just requested too.  PASS 1 waits for its first stages
+        // here, which costs more than it gives where K is read once (d = 128, 40 heads, n = 18432, m = 64: 66.5 -> 67.7 us, 4 x 32
+        // heads, n = 4096 54.4 -> 55.9); at d = 64 it gives (40 heads, n = 18432, 64 recent and 64 random 67.9 -> 66.0).
+        if (PASS == 2 || D == 64)
 #pragma unroll
-        for (int cc = 0; cc < CH; ++cc) asm volatile("" : "+v"(qf[cc]));
+            for (int cc = 0; cc < CH; ++cc) asm volatile("" : "+v"(qf[cc]));
         float m_run = -INFINITY, l_run = 0.f;                        // PASS 1
         // add the tasks' column sums of stage s (PASS 2) in task order and write the scores of its keys
         // (taken by the workgroup's last threads first: with more waves than tasks those waves are otherwise idle)
