@@ -97,7 +97,8 @@ def _select_case(name, mass, rank, tau):
     units = mass.shape[0]
     ws = SELECT_WS.setdefault(units, z.select_workspace(units, DEV))      # reused across cases: every call must leave it zero
     ref = [oz.select(mass[u], None if rank is None else rank[u], tau) for u in range(units)]
-    for form, w_ in (("one kernel", None), ("two kernels", ws)):
+    long = mass.shape[1] > 32768                              # shorter vectors: keys in registers, and the workspace is not used
+    for form, w_ in (("one kernel" if long else "registers", None), ("two kernels" if long else "registers, workspace given", ws)):
         idx, k = z.zipvl_select(m_d, r_d, tau, ws=w_)
         torch.cuda.synchronize()
         idx, k = idx.cpu().numpy(), k.cpu().numpy()
@@ -119,7 +120,7 @@ def test_select_exact_on_synthetic_distributions():
         rk = (skew * (1 + 0.5 * r.random((3, n)))).astype(np.float32)
         _select_case(f"skew-n{n}", skew, rk, 0.975)
         _select_case(f"skew-single-n{n}", skew, None, 0.9)
-    # beyond the LDS-resident key count (27648): keys are re-read from memory on every digit pass
+    # around the block of keys that the kernels for long vectors stage in LDS (27648), and such vectors themselves (> 32768)
     for n in (27648, 27649, 131072):
         big = norm(r.random((2, n)) ** 6 + 1e-9)
         _select_case(f"long-n{n}", big, (big * (1 + r.random((2, n)))).astype(np.float32), 0.975)
@@ -143,8 +144,9 @@ def test_select_exact_on_synthetic_distributions():
     tail = norm(np.concatenate([r.random((2, 40)) * 50, r.random((2, 18392)) * 0.01], axis=1))
     rk = tail.copy(); rk[:, -64:] *= np.linspace(1, 64, 64, dtype=np.float32)
     _select_case("heavy+tail", tail, rk, 0.975)
-    # one first-digit bin (a sixteenth of a binade) holding more elements than the gathered list takes, and exactly as many
-    for cnt in (2048, 2049, 5000):
+    # one first-digit bin (a sixteenth of a binade) holding more elements than the list of candidates takes (1024 of keys in
+    # registers; the 2048 of the two-kernel form: below, at its sizes)
+    for cnt in (1024, 1025, 2048, 2049, 5000):
         band = (1.0 + r.random((2, cnt)) / 17.0).astype(np.float32)        # all in [1, 1 + 1/16): one bin
         rest = (r.random((2, 3000)) * 0.9).astype(np.float32)
         x = norm(np.concatenate([rest, band], axis=1)[:, r.permutation(3000 + cnt)])
@@ -172,13 +174,46 @@ def test_select_with_keys_in_registers_at_the_edges_of_its_sizes(n):
     _select_case(f"registers-holes-n{n}", x, holes, 0.975)
 
 
-def test_select_status_word_reports_inputs_outside_the_contract():
+@pytest.mark.parametrize("n", [32769, 33000, 60000])
+def test_select_of_long_vectors(n):
+    """n > 32768: one kernel that re-reads the vectors, and two kernels with a workspace.  Nothing to sum, every token, one token, few
+    values, close values, a first-digit bin that holds as many keys as the gathered list takes (2048) and more, scores far
+    outside the octaves of a softmax."""
+    r = np.random.Generator(np.random.PCG64(n))
+    norm = lambda x: (x / x.sum(axis=1, keepdims=True)).astype(np.float32)
+    x = norm(np.exp(r.normal(0, 2.2, (2, n))))
+    rk = (x * (1 + r.random((2, n)))).astype(np.float32)
+    for tau in (1e-9, 0.5, 0.99999, 1.0):
+        _select_case(f"long-tau-n{n}", x, rk, tau)
+    zeros = np.zeros((2, n), dtype=np.float32)
+    _select_case(f"long-zeros-n{n}", zeros, None, 0.9)
+    _select_case(f"long-zeros-ranked-n{n}", zeros, rk, 0.9)
+    _select_case(f"long-rank-zeros-n{n}", x, zeros, 0.9)
+    onehot = zeros.copy()
+    onehot[0, n - 1] = onehot[1, 0] = 1.0
+    _select_case(f"long-onehot-n{n}", onehot, None, 0.99)
+    _select_case(f"long-uniform-n{n}", np.full((2, n), 2.0 ** -17, dtype=np.float32), None, 0.5)
+    few = norm(np.round(r.random((2, n)) * 6) + 1.0)
+    _select_case(f"long-few-values-n{n}", few, few[:, ::-1].copy(), 0.7)
+    near = (np.float32(1.0 / n) * (1 + r.integers(0, 50, (2, n)) * 2.0 ** -20)).astype(np.float32)
+    _select_case(f"long-near-n{n}", near, near[:, ::-1].copy(), 0.6)
+    holes = np.where(r.random((2, n)) < 0.9, 0, rk).astype(np.float32)
+    _select_case(f"long-holes-n{n}", x, holes, 0.975)
+    _select_case(f"long-wide-n{n}", (x * np.float32(2.0 ** -12)).astype(np.float32), (rk * np.float32(2.0 ** 60)).astype(np.float32), 0.9)
+    for cnt in (2047, 2048, 2049, 5000):
+        band = (1.0 + r.random((2, cnt)) / 17.0).astype(np.float32)        # all in [1, 1 + 1/16): one bin
+        y = norm(np.concatenate([r.random((2, n - cnt)) * 0.02, band], axis=1)[:, r.permutation(n)])
+        _select_case(f"long-crowded-bin-{cnt}-n{n}", y, (y * (1 + 0.01 * r.random(y.shape))).astype(np.float32), 0.6)
+        _select_case(f"long-crowded-bin-single-{cnt}-n{n}", y, None, 0.5)
+
+
+@pytest.mark.parametrize("n", [5000, 33000])
+def test_select_status_word_reports_inputs_outside_the_contract(n):
     """The optional status word: 0 for valid input, and one bit each for a sign-bit entry, a non-finite entry and a
-    mass that sums to 2 or more; both forms of the call; the selection itself still runs (and, for the sign-bit
-    case, treats the entry as zero: the result equals the oracle's on the cleaned vector)."""
-    say("select status word")
+    mass that sums to 2 or more; with and without a workspace, at a size of either dispatch; the selection itself still runs
+    (and, for the sign-bit case, treats the entry as zero: the result equals the oracle's on the cleaned vector)."""
+    say(f"select status word n={n}")
     r = np.random.Generator(np.random.PCG64(23))
-    n = 5000
     good = r.random((5, n)).astype(np.float32) ** 4
     good /= good.sum(axis=1, keepdims=True)
     x = np.ascontiguousarray(good.astype(np.float32))
@@ -369,6 +404,44 @@ def test_attention_in_place_is_attention_over_packed_rows(dtype, d, n):
     for h in range(4):
         for got, T in ((dense, np.arange(n)), (evicted, np.arange(k))):
             ref = oz.kept_token_attention(w.Q[0, h], w.K[0, h // 2], w.V[0, h // 2], T, w.scale)
+            assert np.abs(host64(got[0, h]) - ref).max() <= ATOL_OUT[dtype]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,gain", [(1, 1.0), (33, 1.0), (65, 1.0), (129, 1.0), (200, 1.0), (330, 16.0)])
+def test_attention_in_place_with_query_tiles_of_128(dtype, d, n, gain):
+    """The same in a batch large enough for tiles of 128 queries (more than 512 of them): every token kept, sequences and kept
+    counts that are no multiple of 64, rows from k on NaN; gain 16: logits that take the pass with running maxima."""
+    Hq, Hkv, k = 4, 2, max(1, n - 7)
+    B = 512 // ((n + 127) // 128 * Hq) + 1
+    say(f"attention in place, tiles of 128, dtype={dtype} d={d} n={n} B={B}")
+    w = make_custom(1, Hq, Hkv, n, d, dtype, seed=n + d + 1)
+    Qh = (w.Q * np.float32(gain)).astype(np.float32)
+    if dtype == "bf16":
+        Qh = torch.from_numpy(Qh).bfloat16().float().numpy()
+    Q, K, V = (dev(x, dtype).repeat(B, 1, 1, 1) for x in (Qh, w.K, w.V))
+
+    def spread(x):                                          # the same rows, 16 bytes apart
+        wide = torch.zeros(x.shape[:-1] + (d + 16 // x.element_size(),), dtype=x.dtype, device=DEV)
+        wide[..., :d] = x
+        return wide[..., :d]
+
+    dense = z.zipvl_sparse_prefill(Q, K, V, None, None, w.scale)
+    assert torch.equal(dense, z.zipvl_sparse_prefill(Q, spread(K), spread(V), None, None, w.scale))
+    Kc, Vc = K.clone(), V.clone()
+    Kc[:, :, k:] = float("nan")
+    Vc[:, :, k:] = float("nan")
+    idx = torch.arange(n, dtype=torch.int32, device=DEV).repeat(B * Hkv, 1)
+    kc = torch.full((B * Hkv,), k, dtype=torch.int32, device=DEV)
+    args = (idx, kc, w.scale, z.OUT_FULL | z.KV_ALREADY_COMPACT)
+    evicted = z.zipvl_sparse_prefill(Q, Kc, Vc, *args)
+    assert torch.equal(evicted, z.zipvl_sparse_prefill(Q, spread(Kc), spread(Vc), *args))
+    torch.cuda.synchronize()
+    for got, T in ((dense, np.arange(n)), (evicted, np.arange(k))):
+        assert torch.equal(got, got[:1].expand_as(got))      # every copy the same bits
+        for h in range(Hq):
+            ref = oz.kept_token_attention(Qh[0, h], w.K[0, h // 2], w.V[0, h // 2], T, w.scale)
             assert np.abs(host64(got[0, h]) - ref).max() <= ATOL_OUT[dtype]
 
 
@@ -1100,10 +1173,10 @@ def test_one_head_decode_over_quantised_cache_with_outliers_in_k(d):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_one_head_decode_over_quantised_cache_in_blocks_of_64_rows(d):
-    """Integer products: both parts around multiples of 64 rows; value rows from 1e-4 to 1e4, small ones first and last (the
-    fixed-point scale of the weights moves); logits that rise along the sequence (the exponent offset moves); query elements
+    """Integer products: both parts around multiples of 64 rows, in few units (a wave takes one block of either part; several
+    blocks, whose scale and offset move: above); value rows from 1e-4 to 1e4; logits that rise along the sequence; query elements
     six orders of magnitude apart, and a query of zeros.  Bound: a score of |s| is off by up to 4 * 2^-24 |s| in fp32, a
-    weight by that relative amount; |s| < 80 here, so 2e-5 of the largest value that a head weighs."""
+    weight by that relative amount; |s| < 80 here, so 2e-5 of the largest value of the head."""
     say(f"decode_attn_q one head, blocks of 64, d={d}")
     n = 400
     kept = [0, 1, 63, 64, 65, 127, 128, 129, 192, 336, 399, 400]
