@@ -9,8 +9,9 @@ namespace zipvl {
 constexpr int kCompactRows = 64;   // kept rows handled by one workgroup
 
 // CPR = 16-byte chunks per row.  A workgroup's life is a chain of two round trips to memory, positions -> rows: all of its
-// positions, then all of its rows are requested at once.  With one pass of 256 threads after the other 32 units x 970 of
-// 2933 rows of 256 bytes took 6.9 us (6.1 so), 128 x 2048 of 8192 49.7 (46.2: 5.8 TB/s), 4 x 69 of 576 3.5 (2.7).
+// positions, then all of its rows are requested at once.  With one pass of 256 threads after the other, the same call again
+// and again, 32 units x 970 of 2933 rows of 256 bytes took 6.9 us (6.1 so), 128 x 2048 of 8192 49.7 (46.2: 5.8 TB/s), 4 x 69 of 576 3.5
+// (2.7); inside a layer, where the rows come from memory, 9.7 (10.2; shortest 8.4 and 7.8), 54.1 (53.9) and 3.8 (3.2).
 template <int CPR>
 __global__ __launch_bounds__(256) void compact_kv_kernel(
     const char* __restrict__ K, const char* __restrict__ V,

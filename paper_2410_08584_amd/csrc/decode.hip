@@ -6,9 +6,10 @@
 // unit is long (from its length; SplitRule), so that short and full caches as well as
 // batches of unequal lengths keep the workgroups busy.
 // Groups of two and more heads run on the matrix cores, 16 cached rows per wave
-// step (attend_split); a single head runs on the vector units, where 16 lanes
-// cover one cached row (16 bytes each at d = 128 bf16), reduce the dot product with
-// shuffles and keep an online-softmax state per row group (attend_rows).  Waves and
+// step (attend_split); a single head runs on the vector units over rows as stored,
+// where 16 lanes cover one cached row (16 bytes each at d = 128 bf16), reduce the dot
+// product with shuffles and keep an online-softmax state per row group (attend_rows),
+// and in integer matrix products over codes (decode_q1_partial_kernel).  Waves and
 // finally splits are merged with the usual (max, sum, weighted output) rule.
 #include <algorithm>
 #include <mutex>
@@ -760,8 +761,8 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
 // The exponent offset is the wave's and moves lazily; it and the fixed-point scale of the weights are fixed until a row
 // outgrows them, and then the integer sums go over to fp32.  A new offset takes a new scale: rows of V a thousand times larger
 // than the others, which then turn out to weigh nothing, would leave the others 10 bits less (with 1e4 and 1e-3, 3 % off).
-// Four layers of 128 units x 8192 rows: 115 us a step, some 20 us a layer in this kernel (151 and 33 on the vector units).
-// Error of the output against float64, fp32 queries, n = 300 to 30000: 3.9e-7 in the mean (2.4e-6 on the vector units).
+// Four layers of 128 units x 8192 rows: 116 us a step, 23 us a layer in this kernel (151 and 33 on the vector units).
+// Error of the output against float64, fp32 queries, n = 300 to 30000: 2.0e-7 in the mean (2.3e-6 on the vector units).
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef int intx2 __attribute__((ext_vector_type(2)));
 
@@ -1132,8 +1133,9 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
 #define ZIPVL_DECQ_ARGS (const T*)q, kq, vq, len_hi, len_lo, cap_hi, cap_lo, (const T*)Kt, (const T*)Vt, len_t, cap_t
     for (int gb = 0; gb < G; gb += 8) {
         KernelTimer tm(ZIPVL_K_DECODE_Q_PARTIAL, st);
-        // one head: the vector units, as over a cache as stored (four layers of 128 units x 8192 rows 152 us, 440 on the matrix
-        // cores); two and more: the matrix cores (two heads, 32 units x 4000: 122 -> 100 us)
+        // one head: integer products on the codes (four layers of 128 units x 8192 rows 116 us; 152 on the vector units, 440 in
+        // floating-point tiles of which one column in 16 is used); two and more: floating-point tiles (two heads, 32 units x 4000:
+        // 122 us on the vector units, 100)
         if (G > 1)
             hipLaunchKernelGGL((decode_q_partial_kernel<T, D, 8>), rule.grid(), dim3(64 * kDecWaves<8>), 0, st, ZIPVL_DECQ_ARGS,
                 d.Hq, d.Hkv, gb, c, (float*)ws, rule);
