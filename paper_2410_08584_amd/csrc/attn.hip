@@ -28,10 +28,11 @@
 //          by extra workgroups at the end of the same grid (one per head and span
 //          of positions), which run in the slots the thinning end of the
 //          attention work leaves idle.
-// The kept count k lives on the device: the grid covers the worst case (k = n)
-// and workgroups beyond a unit's k exit at once; heavy (late) query tiles are
-// scheduled first, over all KV heads of a schedule group, because the longest
-// workgroup (all k keys) lasts a large part of the whole launch.
+// The kept count k lives on the device: the grid covers the worst case (k = n),
+// but every workgroup knows the tiles of the longest head, so that those without
+// work stand at the end of the grid; heavy (late) query tiles are scheduled first,
+// over all KV heads of a schedule group, because the longest workgroup (all k keys)
+// lasts a large part of the whole launch.
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -46,6 +47,13 @@ constexpr int kBN = 64;      // keys per tile
 // workgroup (half the L2 -> LDS traffic per query) is 3 % slower; 64 queries per wave (QB = 2, half the LDS operand reads per
 // MFMA) does not fit the register file with the S^T double buffer and spills.
 constexpr int kFillSpan = 512;       // positions per workgroup that clears dropped output rows
+// Every workgroup reads all kept counts of a call (64 a load) unless they are more than kScanSets; a call of up to kScanBlocks
+// workgroups is on the chip at once in whatever order, and the reading costs it 0.3 us of 11.
+constexpr int kScanSets = 512, kScanBlocks = 512;
+// Workgroups of the grid above which a head gets fewer of them than it has tiles if all is kept (half at least; the others are
+// taken in a second round).  us, a row for every tile -> so: 4 x 32 heads, n = 8192, a quarter kept 209 -> 204, half kept 611 -> 612;
+// 2 x 32, n = 12000, 15 % kept 92.6 -> 90.4; with half as many workgroups 207, 639 and 89.9.
+constexpr int kSecondRound = 4096;
 constexpr float kLazyLog2 = 8.f;     // slack of the running softmax offset below the running maximum (log2 domain)
 constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p64f;   // row sums of the offset-free pass that need no second pass
 constexpr int kSchedAhead = 3;       // LDS operand reads in flight ahead of the consuming MFMA
@@ -297,7 +305,9 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     using C = AttnCfg<T, D, NW, QB, KS>;
     constexpr int kBM = C::BM, kRW = 32 * QB;                // queries per workgroup, queries per wave
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, i = lane & 31, h = lane >> 5;
+    int tid = threadIdx.x;
+    if constexpr (KS == 1) asm volatile("" : "+v"(tid));     // nothing of a lane is kept from one tile of queries for the next
+    const int w = tid >> 6, lane = tid & 63, i = lane & 31, h = lane >> 5;
     // KS = 2: wave w has the queries of wave qw and key block kw of every tile
     const int qw = KS == 1 ? w : w % (NW / KS), kw = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(w / (NW / KS));
     floatx16 o[QB][C::ODB];
@@ -727,88 +737,165 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
 // 256 (4 x 32, k = 230) 14.7 -> 14.4, 252 (3 x 28 on 4, k = 300) 14.1 -> 12.9, 320 (2 x 32, k = 599) 22.1 -> 22.5, 384 (4 x 32, k = 300) 15.7 -> 18.6.
 __device__ __forceinline__ bool splits_keys(int k, int BH) { return ((k + 127) >> 7) * BH <= (k >= 1000 ? 512 : 288); }
 
+// Clears the rows of one head at the positions of [p0, p1), up to kFillSpan of them, that are not among its fk kept ones (ft,
+// ascending).
+template <typename T, int D, int NT>
+__device__ __forceinline__ void clear_dropped(T* __restrict__ O, const int32_t* __restrict__ ft, int fk, int p0, int p1, int* kept) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int e = tid; e < kFillSpan; e += NT) kept[e] = 0;
+    int lo = 0, len = fk;                                    // the first kept row at or after p0 is in [lo, lo + len]: 64 probes a round
+    while (len > 0) {
+        const int step = (len + 63) >> 6, blocks = (len + step - 1) / step;
+        const bool below = lane < blocks && ft[lo + min((lane + 1) * step, len) - 1] < p0;
+        const int cnt = __popcll(__ballot(below));           // blocks that end before p0
+        lo += min(cnt * step, len);
+        len = cnt == blocks ? 0 : min(step, len - cnt * step) - 1;
+    }
+    __syncthreads();
+    for (int e = lo + tid; e < min(fk, lo + kFillSpan); e += NT) {
+        const int pos = ft[e];
+        if (pos < p1) kept[pos - p0] = 1;
+    }
+    __syncthreads();
+    constexpr int CPR = D * Elem<T>::kBytes / 16;
+    const uintx4 z = {0, 0, 0, 0};
+    char* base = reinterpret_cast<char*>(O + (int64_t)p0 * D);
+    for (int q = tid; q < (p1 - p0) * CPR; q += NT)
+        // whole rows, written once and not read again by this path: streaming stores, so that they do not stay
+        // behind as dirty lines in the last-level cache, to be written back under the next kernel's reads
+        if (!kept[q / CPR]) __builtin_nontemporal_store(z, reinterpret_cast<uintx4*>(base + (int64_t)q * 16));
+}
+
+// kp, vp: of batch element, KV head.  slots: rows of attention workgroups in the grid, BH each; fill: workgroups after them that clear
+// rows; scan: whether the kept counts are read for the longest head; ug: KV heads of a scheduling group.
+template <typename T> struct FlashArgs {
+    const T* Q; int64_t qs0, qs1, qs2;
+    const T* Kp; int64_t kp0, kp1;
+    const T* Vp; int64_t vp0, vp1;
+    const int32_t* idx; const int32_t* kcnt;
+    T* O;
+    int n, npad, slots, fill, scan, ug, G, BH, Hq, Hkv;
+    float c;
+    int out_compact, t_per_batch, k_in_place, v_in_place;
+};
+
 template <typename T, int D, int NW, int QB, int KS>
-__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, 1>::MIN_WGS)) void flash_kept_kernel(
-    const T* __restrict__ Q, int64_t qs0, int64_t qs1, int64_t qs2,
-    const T* __restrict__ Kp, int64_t kp0, int64_t kp1, const T* __restrict__ Vp, int64_t vp0, int64_t vp1,
-    const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
-    T* __restrict__ O, int n, int npad, int ntq, int ug, int BH, int Hq, int Hkv, float c, int out_compact, int compute_blocks,
-    int t_per_batch, int k_in_place, int v_in_place)
+__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, 1>::MIN_WGS)) void flash_kept_kernel(FlashArgs<T> args)
 {
     using C = AttnCfg<T, D, NW, QB, KS == 1 ? 1 : 2>;
-    constexpr int kBM = C::BM, kNT = C::NT;                  // queries per workgroup, threads
+    constexpr int kBM = C::BM;                               // queries per tile
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    // Workgroup -> (unit group, query tile, unit in group, head of the KV group), in that order of
-    // significance; heavy (late) query tiles first inside a group.  A group holds enough KV heads to
-    // fill the chip several times over (a few for long GQA sequences, many for short MHA ones): the
-    // chip then works through few KV heads at a time, so the caches hold little more than the K / V
-    // in use, while the light tail of one group overlaps the heavy start of the next.  The last query
-    // tile of a head runs for as long as all its kept keys take; a group must hold many times the
-    // chip's resident workgroups for that one not to end alone.
-    const int G = Hq / Hkv, NU = BH / G;
-    const int tid = threadIdx.x;
-    if (blockIdx.x >= (unsigned)compute_blocks) {
+    int block = blockIdx.x;
+    // All arguments at once: the compiler would load each where it is first used, 0.2 us apart.
+    auto fetch = [](const auto& a) {
+        const FlashArgs<T> x = {a.Q, a.qs0, a.qs1, a.qs2, a.Kp, a.kp0, a.kp1, a.Vp, a.vp0, a.vp1, a.idx, a.kcnt, a.O, a.n, a.npad, a.slots, a.fill, a.scan,
+                                a.ug, a.G, a.BH, a.Hq, a.Hkv, a.c, a.out_compact, a.t_per_batch, a.k_in_place, a.v_in_place};
+        asm volatile("" :: "s"(x.Q), "s"(x.qs0), "s"(x.qs1), "s"(x.qs2), "s"(x.Kp), "s"(x.kp0), "s"(x.kp1), "s"(x.Vp), "s"(x.vp0), "s"(x.vp1), "s"(x.idx),
+                     "s"(x.kcnt), "s"(x.O), "s"(x.n), "s"(x.npad), "s"(x.fill), "s"(x.ug), "s"(x.G), "s"(x.BH), "s"(x.Hq), "s"(x.Hkv), "s"(x.c),
+                     "s"(x.out_compact), "s"(x.t_per_batch), "s"(x.k_in_place), "s"(x.v_in_place));
+        return x;
+    };
+    const FlashArgs<T> a0 = fetch(args);
+    // The query tiles of the longest head.  k is on the device and the grid is for k = n, so that most workgroups of a sparse call have
+    // nothing to do; dispatched among the others, in their order and 1.5 us each in a slot of the chip, they kept a fifth of the slots
+    // empty (4 x 32 heads, n = 8192, a quarter kept).  With this every workgroup knows them, and they are the last of the grid.
+    int lmax = (a0.n + kBM - 1) / kBM, lane_k = 0, sets = 0;
+    if (a0.scan) {
+        sets = a0.t_per_batch ? a0.BH / a0.Hq : a0.BH / a0.G;
+        const int lane = threadIdx.x & 63;
+        lane_k = a0.kcnt[min(lane, sets - 1)];
+        int most = max(lane_k, 0);
+        for (int x = lane + 64; x < sets; x += 64) most = max(most, a0.kcnt[x]);
+        lmax = min(lmax, (wave_reduce(most, 0, [](int x, int y) { return max(x, y); }) + kBM - 1) / kBM);
+    }
+    const int rows = min(lmax, a0.slots);
+    // Workgroup -> (group of KV heads, row, KV head in group, head of the KV head), in that order of significance; heavy (late) query
+    // tiles first inside a group (units_per_group), so that the light tail of one overlaps the heavy start of the next.
+    struct Place { int row, b, g, head, set; };
+    auto place = [&](const FlashArgs<T>& a) {
+        const int heads = a.ug * a.G;                        // of a group
+        const int grp = block / (heads * rows), r = block - grp * (heads * rows);
+        const int row = r / heads, rr = r - row * heads;
+        const int u = grp * a.ug + rr / a.G, b = u / a.Hkv, g = u - b * a.Hkv;
+        return Place{row, b, g, g * a.G + rr % a.G, a.t_per_batch ? b : u};
+    };
+    auto kept = [&](const FlashArgs<T>& a, int set) { return a.kcnt ? a.kcnt[set] : a.n; };
+    auto tile = [&](const FlashArgs<T>& a, const Place& at, int kk, int round) {
+        kk = max(0, min(kk, a.n));
+        const int x = round * rows + (round & 1 ? rows - 1 - at.row : at.row);
+        // KS = 0: heads that take 128 queries at a time have half as many tiles, and start with the last one
+        const bool wide = KS == 1 || (KS == 0 && !splits_keys(kk, a.BH));
+        const int i0 = KS == 0 && wide ? ((kk + 2 * kBM - 1) / (2 * kBM) - 1 - x) * 2 * kBM : (lmax - 1 - x) * kBM;
+        if (i0 < 0 || i0 >= kk) return;
+        const int32_t* tidx = a.idx ? a.idx + (int64_t)at.set * a.n : nullptr;       // this unit's T
+        const T* q = a.Q + at.b * a.qs0 + at.head * a.qs1;
+        const T* kp = a.Kp + at.b * a.kp0 + at.g * a.kp1;
+        const T* vp = a.Vp + at.b * a.vp0 + at.g * a.vp1;
+        T* Oh = a.O + (int64_t)(at.b * a.Hq + at.head) * a.n * D;
+        auto queries = [&](auto ks) {
+            flash_queries<T, D, NW, QB, decltype(ks)::value>(q, a.qs2, kp, vp, tidx, Oh, i0, kk, a.npad, a.c, a.out_compact, a.k_in_place, a.v_in_place);
+        };
+        if constexpr (KS != 0) queries(std::integral_constant<int, KS>{});
+        else if (wide) queries(std::integral_constant<int, 1>{});
+        else queries(std::integral_constant<int, 2>{});
+    };
+    if (block >= a0.BH * rows) {
         // Outputs of dropped tokens are zero rows.  The workgroups after the last attention workgroup
         // each clear the dropped rows of one head inside one span of kFillSpan positions; they are
         // dispatched last, into the slots that the light end of the attention work leaves idle.
-        const int f = blockIdx.x - compute_blocks, s = f / BH, fbh = f - s * BH;
-        const int fb = fbh / Hq, fu = fb * Hkv + (fbh - fb * Hq) / G;
-        const int32_t* ft = idx + (int64_t)(t_per_batch ? fb : fu) * n;
-        const int fk = kcnt ? max(0, min(kcnt[t_per_batch ? fb : fu], n)) : n;
-        const int p0 = s * kFillSpan, p1 = min(n, p0 + kFillSpan);
-        int* kept = reinterpret_cast<int*>(smem);            // [kFillSpan]
-        for (int e = tid; e < kFillSpan; e += kNT) kept[e] = 0;
-        int lo = 0, hi = fk;                                 // first kept row at or after p0 (T ascends)
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (ft[mid] < p0) lo = mid + 1; else hi = mid;
-        }
-        __syncthreads();
-        for (int e = lo + tid; e < min(fk, lo + kFillSpan); e += kNT) {
-            const int pos = ft[e];
-            if (pos >= p0 && pos < p1) kept[pos - p0] = 1;
-        }
-        __syncthreads();
-        constexpr int CPR = D * Elem<T>::kBytes / 16;
-        const uintx4 z = {0, 0, 0, 0};
-        char* base = reinterpret_cast<char*>(O + ((int64_t)fbh * n + p0) * D);
-        for (int q = tid; q < (p1 - p0) * CPR; q += kNT)
-            // whole rows, written once and not read again by this path: streaming stores, so that they do not stay
-            // behind as dirty lines in the last-level cache, to be written back under the next kernel's reads
-            if (!kept[q / CPR]) __builtin_nontemporal_store(z, reinterpret_cast<uintx4*>(base + (int64_t)q * 16));
+        const int f = block - a0.BH * rows, s = f / a0.BH, bh = f - s * a0.BH;
+        if (f >= a0.fill) return;
+        const int b = bh / a0.Hq, set = a0.t_per_batch ? b : b * a0.Hkv + (bh - b * a0.Hq) / a0.G;
+        clear_dropped<T, D, C::NT>(a0.O + (int64_t)bh * a0.n * D, a0.idx + (int64_t)set * a0.n, max(0, min(kept(a0, set), a0.n)),
+                                   s * kFillSpan, min(a0.n, (s + 1) * kFillSpan), reinterpret_cast<int*>(smem));
         return;
     }
-    const int full = ug * ntq * G;                           // workgroups of a full group
-    const int ngroups = (NU + ug - 1) / ug;
-    const int grp = min((int)(blockIdx.x / full), ngroups - 1);
-    const int r = blockIdx.x - grp * full;
-    const int nu_g = min(ug, NU - grp * ug);
-    const int tile_rev = r / (nu_g * G), rr = r - tile_rev * (nu_g * G);
-    const int u = grp * ug + rr / G, hg = rr % G;
-    const int b = u / Hkv, g = u - b * Hkv, head = g * G + hg, bh = b * Hq + head;
-    const int32_t* tidx = idx ? idx + (int64_t)(t_per_batch ? b : u) * n : nullptr;   // this unit's T
-    int kk = kcnt ? kcnt[t_per_batch ? b : u] : n;
-    kk = max(0, min(kk, n));
-    // KS = 0: ntq tiles of 64 queries, or the first half as many workgroups take 128 each (every other one would leave an XCD idle)
-    const bool wide = KS == 1 || (KS == 0 && !splits_keys(kk, BH));
-    const int i0 = KS == 0 && wide ? ((ntq + 1) / 2 - 1 - tile_rev) * (2 * kBM) : (ntq - 1 - tile_rev) * kBM;
-    if (i0 < 0 || i0 >= kk) return;
-    Q += b * qs0 + head * qs1;
-    Kp += b * kp0 + g * kp1;
-    Vp += b * vp0 + g * vp1;
-    O += (int64_t)bh * n * D;
-    auto queries = [&](auto ks) {
-        flash_queries<T, D, NW, QB, decltype(ks)::value>(Q, qs2, Kp, Vp, tidx, O, i0, kk, npad, c, out_compact, k_in_place, v_in_place);
-    };
-    if constexpr (KS != 0) queries(std::integral_constant<int, KS>{});
-    else if (wide) queries(std::integral_constant<int, 1>{});
-    else queries(std::integral_constant<int, 2>{});
+    const Place at0 = place(a0);
+    const int k0 = at0.set < min(sets, 64) ? __builtin_amdgcn_readlane(lane_k, at0.set) : kept(a0, at0.set);
+    if constexpr (KS != 1) {
+        tile(a0, at0, k0, 0);
+    } else {
+        // A workgroup of a grid that has fewer rows than tiles takes a second one, from the light end.  What a round needs is
+        // read from the arguments and derived again (the empty asm): carried through the key loop it would take more scalar
+        // registers than there are.
+        using ArgPtr = const __attribute__((address_space(4))) FlashArgs<T>*;
+        ArgPtr again = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+        FlashArgs<T> a = a0;
+        Place at = at0;
+        int k = k0;
+#pragma unroll 1
+        for (int round = 0;;) {
+            tile(a, at, k, round);
+            if (++round * rows >= lmax) break;
+            __syncthreads();
+            asm volatile("" : "+s"(block), "+s"(again));
+            a = fetch(*again);
+            at = place(a);
+            k = kept(a, at.set);
+        }
+    }
 }
 
 size_t prefill_workspace_bytes(const zipvl_dims& d) {
     const int e = d.dtype == ZIPVL_BF16 ? 2 : 4;
     const size_t npad = ((size_t)d.n + kBN - 1) / kBN * kBN;
     return 2 * (size_t)d.B * d.Hkv * npad * d.d * e;
+}
+
+// KV heads per scheduling group: all of equal size, as near as the KV heads divide to 20 heads of queries, or to 800 tiles of 128
+// for shorter sequences.  Larger groups take K / V beyond what the caches hold at a time, smaller ones leave too few light tiles under
+// the heavy ones of the next, and an uneven last one runs on alone.  us, groups by bytes of K / V (32 and 8 heads, 42 and 22, ...) -> so:
+// every token kept, 40 heads, n = 4096 195 -> 172; a third kept, 4 x 32 on 8, n = 5000 120 -> 109; d = 64, 2 x 32, n = 6000 59 -> 54;
+// 15 %, 40 heads, n = 16000 97 -> 88; 20 %, 4 x 4, n = 20000 110 -> 105.  fp32 products take 16 times as long as the loads under them: one group
+// (2 x 32 on 8, n = 3000, a third kept 180; in two 211).
+template <typename T>
+static int units_per_group(int units, int G, int tiles) {
+    if (Elem<T>::kBytes == 4) return units;
+    const double want = units * G / (double)std::max(20, 800 / tiles);
+    int best = 1;
+    for (int groups = 2; groups <= units; ++groups)
+        if (units % groups == 0 && std::max(groups / want, want / groups) < std::max(best / want, want / best)) best = groups;
+    return units / best;
 }
 
 template <typename T, int D, int NW, int QB, int KS>
@@ -826,25 +913,19 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
     {
         KernelTimer tm(ZIPVL_K_FLASH_KEPT, st);
         const int BH = d.B * d.Hq;
-        const int ntq = (d.n + C::BM - 1) / C::BM;
-        const int64_t blocks = (int64_t)ntq * BH;
-        const int G = d.Hq / d.Hkv;
-        // KV heads per scheduling group (see the kernel): about eight waves of workgroups on the chip, so
-        // that the longest workgroup (the last query tile) is a small part of a group even when only a
-        // fraction of the tiles is kept, but no more K / V than a quarter of the 256 MiB last-level cache
-        const int64_t unit_bytes = 2 * (int64_t)npad * D * Elem<T>::kBytes;
-        int ug = (int)std::min<int64_t>((16384 / (NW * QB)) / ((int64_t)ntq * G), (64ll << 20) / unit_bytes);
-        ug = ug < 1 ? 1 : ug;
+        const int ntq = (d.n + C::BM - 1) / C::BM, G = d.Hq / d.Hkv;
+        const int slots = KS == 1 && idx ? std::max((ntq + 1) / 2, std::min(ntq, (kSecondRound + BH - 1) / BH)) : ntq;
+        const int64_t blocks = (int64_t)slots * BH;
         // full-size output of a sparse call: one more workgroup per (head, span of positions) clears dropped rows
         const int64_t fill = (!out_compact && idx) ? (int64_t)BH * ((d.n + kFillSpan - 1) / kFillSpan) : 0;
-        if (blocks + fill > 0x7fffffffLL) return set_error(ZIPVL_ESHAPE, "sparse_prefill: %lld workgroups exceed the grid limit", (long long)blocks);
+        const int ug = units_per_group<T>(d.B * d.Hkv, G, (d.n + 127) / 128);
+        const int scan = k && blocks > kScanBlocks && (t_per_batch ? d.B : d.B * d.Hkv) <= kScanSets;
+        if (blocks + fill > 0x7fffffffLL) return set_error(ZIPVL_ESHAPE, "sparse_prefill: %lld workgroups exceed the grid limit", (long long)(blocks + fill));
         hipLaunchKernelGGL((flash_kept_kernel<T, D, NW, QB, KS>), dim3((unsigned)(blocks + fill)), dim3(C::NT),
-            C::LDS_BYTES, st, (const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
-            skip_k ? (const T*)K : Kp, skip_k ? d.k_strides[0] : (int64_t)d.Hkv * npad * D,
-            skip_k ? d.k_strides[1] : (int64_t)npad * D,
-            skip_v ? (const T*)V : Vp, skip_v ? d.v_strides[0] : (int64_t)d.Hkv * npad * D,
-            skip_v ? d.v_strides[1] : (int64_t)npad * D, idx, k, (T*)O, d.n, npad, ntq, ug, BH, d.Hq, d.Hkv,
-            scale * kLog2e, out_compact, (int)blocks, t_per_batch, skip_k, skip_v);
+            C::LDS_BYTES, st, FlashArgs<T>{(const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
+                skip_k ? (const T*)K : Kp, skip_k ? d.k_strides[0] : (int64_t)d.Hkv * npad * D, skip_k ? d.k_strides[1] : (int64_t)npad * D,
+                skip_v ? (const T*)V : Vp, skip_v ? d.v_strides[0] : (int64_t)d.Hkv * npad * D, skip_v ? d.v_strides[1] : (int64_t)npad * D,
+                idx, k, (T*)O, d.n, npad, slots, (int)fill, scan, ug, G, BH, d.Hq, d.Hkv, scale * kLog2e, out_compact, t_per_batch, skip_k, skip_v});
     }
     return check_launch("flash_kept");
 }

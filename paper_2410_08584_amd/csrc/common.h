@@ -79,4 +79,33 @@ __device__ __forceinline__ float add_bf16x2(uint32_t packed, float acc) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, packed), ones, acc, false);
 }
 
+// Over the wave by lane permutes in registers (a shuffle through LDS takes some 100 clocks a step): shifts inside rows of 16
+// lanes, then across the rows; the last lane has it all.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float lane_moved(float v, float none) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(none), __float_as_int(v), CTRL, ROWS, 0xF, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int lane_moved(int v, int none) { return __builtin_amdgcn_update_dpp(none, v, CTRL, ROWS, 0xF, false); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_moved(double v, double none) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(__double2hiint(none), __double2hiint(v), CTRL, ROWS, 0xF, false),
+                            __builtin_amdgcn_update_dpp(__double2loint(none), __double2loint(v), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63); }
+__device__ __forceinline__ float last_lane(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); }
+__device__ __forceinline__ double last_lane(double v) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63), __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+template <typename N, typename F>
+__device__ __forceinline__ N wave_reduce(N v, N none, F&& f) {
+    v = f(v, lane_moved<0x111, 0xF>(v, none));
+    v = f(v, lane_moved<0x112, 0xF>(v, none));
+    v = f(v, lane_moved<0x114, 0xF>(v, none));
+    v = f(v, lane_moved<0x118, 0xF>(v, none));
+    v = f(v, lane_moved<0x142, 0xA>(v, none));
+    v = f(v, lane_moved<0x143, 0xC>(v, none));
+    return last_lane(v);
+}
+
 }  // namespace zipvl

@@ -555,6 +555,46 @@ def test_attention_query_tile_chosen_by_kept_tokens(d, n, gain):
         assert worst <= ATOL_OUT["bf16"], f"k={k}: {worst:.3e}"
 
 
+@pytest.mark.parametrize("copies,Hq,Hkv,n,d,dtype,shared", [(8, 64, 64, 1100, 64, "bf16", False), (74, 56, 8, 129, 128, "bf16", True), (40, 64, 16, 257, 64, "f32", False),
+                                                           (5, 40, 10, 1030, 128, "bf16", True), (3, 14, 7, 700, 128, "bf16", False)])
+def test_attention_schedule(copies, Hq, Hkv, n, d, dtype, shared):
+    """Which workgroup takes which tile: more tiles than workgroups (the first three: 9, 2 and 3 tiles of 128 a head), more sets than a
+    workgroup reads the counts of (the third), several scheduling groups, a KV head without a token, heads that keep all; one set per
+    KV head and one per batch element, full and compact outputs.  Repeated batch elements give the same bits, the first one agrees
+    with the oracle."""
+    say(f"attention schedule {copies}x{Hq}/{Hkv} n={n} d={d} {dtype} shared={shared}")
+    r = np.random.Generator(np.random.PCG64(61))
+    few = min(Hkv, 4)                                        # heads that are computed for the oracle; the others repeat them
+    w = make_custom(1, few * Hq // Hkv, few, n, d, dtype, seed=62)
+    Q, K, V = dev(w.Q, dtype), dev(w.K, dtype), dev(w.V, dtype)
+    reps = (Hkv + few - 1) // few
+    Q, K, V = (x.repeat(copies, reps, 1, 1)[:, :h].contiguous() for x, h in ((Q, Hq), (K, Hkv), (V, Hkv)))
+    ks = [[n, 1, n // 3, 0], [n // 2], [128, n - 1, 64, n // 5]][1 if shared else copies % 2 * 2][:1 if shared else few]
+    idx = np.zeros((len(ks), n), dtype=np.int32)
+    for u, k in enumerate(ks):
+        idx[u, :k] = np.sort(r.choice(n, k, replace=False))
+    times = copies if shared else copies * reps
+    idx_d = torch.from_numpy(idx).to(DEV).repeat(times, 1).view(copies, -1, n)[:, :1 if shared else Hkv].reshape(-1, n).contiguous()
+    k_d = torch.tensor(ks, dtype=torch.int32, device=DEV).repeat(times).view(copies, -1)[:, :1 if shared else Hkv].reshape(-1).contiguous()
+    flag = z.T_PER_BATCH if shared else 0
+    O, C = (torch.full((copies, Hq, n, d), 7.0, dtype=Q.dtype, device=DEV) for _ in range(2))
+    z.zipvl_sparse_prefill(Q, K, V, idx_d, k_d, w.scale, flag, O=O)
+    z.zipvl_sparse_prefill(Q, K, V, idx_d, k_d, w.scale, flag | z.OUT_COMPACT, O=C)
+    torch.cuda.synchronize()
+    assert torch.equal(O, O[:1].expand_as(O)) and torch.equal(C, C[:1].expand_as(C))
+    G = Hq // Hkv
+    for h in range(Hq):
+        u, f = 0 if shared else h // G % few, h // G % few
+        k = ks[u]
+        if h >= few * G:
+            assert torch.equal(O[0, h], O[0, h % (few * G)])
+            continue
+        ref = oz.kept_token_attention(w.Q[0, h], w.K[0, f], w.V[0, f], idx[u, :k], w.scale)
+        worst = np.abs(host64(O[0, h]) - ref).max()
+        assert worst <= ATOL_OUT[dtype], f"head {h}, k={k}: {worst:.3e}"
+        assert torch.equal(C[0, h, :k], O[0, h][torch.from_numpy(idx[u, :k]).long().to(DEV)])
+
+
 def test_attention_compact_output_rows():
     say("attention OUT_COMPACT")
     _attention_case(1, 4, 2, 500, 128, "bf16", [333, 128], seed=7, flags=z.OUT_COMPACT)
