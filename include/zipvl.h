@@ -238,15 +238,16 @@ int zipvl_decode_attn_static(const void* q, const void* Kc, const void* Vc, cons
                              int32_t cap, const zipvl_dims* dims, float softmax_scale, void* o, void* stream);
 
 /*
- * One decode step in one launch: zipvl_kv_append followed by zipvl_decode_attn (Eq. (4), Eq. (5) /
+ * One decode step in one call: zipvl_kv_append followed by zipvl_decode_attn (Eq. (4), Eq. (5) /
  * Algorithm 2), with the same results: the new row is written at row len[u] and takes part in the
  * attention, len[u] is incremented afterwards; a full cache (len == cap) is left unchanged and attended
  * as it is.  Arguments as in those two calls.
  * ws [device]: zipvl_workspace_bytes(ZIPVL_OP_DECODE_STEP, dims (n = cap), 0) bytes, 16-byte aligned.  Its
  * first 4 * B * Hkv bytes are per-unit arrival counters: they must be zero before the first call that
  * uses this workspace, every call leaves them zero, and nothing else may write there between calls
- * (two calls that overlap on one workspace race).  Groups larger than 8 query heads per KV head run the
- * two separate kernels inside this call.
+ * (two calls that overlap on one workspace race).  One launch; two (attention with the new row, then the merge of its
+ * parts) for groups of heads over caches that are cut into more than 16; groups larger than 8 query heads per KV head
+ * run the separate kernels inside this call.
  */
 int zipvl_decode_step(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,
                       const void* v_new, const zipvl_dims* dims, float softmax_scale, void* o,

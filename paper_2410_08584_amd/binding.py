@@ -351,7 +351,7 @@ def decode_step_workspace(B: int, Hq: int, Hkv: int, cap: int, d: int, dtype_lik
 def zipvl_decode_step(q: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, length: torch.Tensor,
                       k_new: torch.Tensor, v_new: torch.Tensor, softmax_scale: float, *, B: int, Hq: int, Hkv: int,
                       ws: torch.Tensor, o: Optional[torch.Tensor] = None):
-    """Append k_new / v_new and attend, one launch; ws from decode_step_workspace (kept between steps)."""
+    """Append k_new / v_new and attend in one call; ws from decode_step_workspace (kept between steps)."""
     lib = load_library()
     units, cap, d = Kc.shape
     dm = dims_of(None, None, None, B=B, Hq=Hq, Hkv=Hkv, n=cap, d=d, dtype=_dtype_code(Kc))

@@ -107,5 +107,8 @@ __device__ __forceinline__ N wave_reduce(N v, N none, F&& f) {
     v = f(v, lane_moved<0x143, 0xC>(v, none));
     return last_lane(v);
 }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, -INFINITY, [](float a, float b) { return fmaxf(a, b); }); }
+template <typename N>
+__device__ __forceinline__ N wave_sum(N v) { return wave_reduce(v, N(0), [](N a, N b) { return a + b; }); }
 
 }  // namespace zipvl

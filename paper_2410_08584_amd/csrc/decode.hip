@@ -90,75 +90,63 @@ __device__ __forceinline__ void combine_waves(float (&red)[WAVES][GT][D + 2], in
     }
 }
 
-// The partial states of one unit's splits -> its output rows, by a workgroup of THREADS threads.  One wave per head
-// first turns the splits' (max, sum) pairs into weights a_s / sum_s(a_s l_s), a_s = exp2(m_s - max), one split per
-// lane; then every thread accumulates four output elements over every SG-th split, eight independent 16-byte loads at a
-// time, and the SG partial sums of an element meet in LDS (added in a fixed order).
+// The partial states of one head's splits -> its output row, by a workgroup of THREADS threads: every wave turns the splits'
+// (max, sum) pairs into weights a_s / sum_s(a_s l_s), a_s = exp2(m_s - max), one split per lane; every thread has four output
+// elements of every kGroups-th split on the way meanwhile, and the partial sums of an element meet in LDS, added in a fixed order.
 // nsplit <= 64.  COHERENT: the states were written by other workgroups of the same launch.
-struct MergeLds { float wgt[8][64]; floatx4 sum[1024]; };
-
-template <typename T, int D, int THREADS, bool COHERENT>
-__device__ __forceinline__ void merge_splits(const PartialOut& po, int G, int nsplit, MergeLds& lds, T* __restrict__ out) {
-    static_assert(THREADS <= 1024 && 8 * (D / 4) <= 256 && THREADS >= 256, "eight heads fit one pass");
-    auto get = [](const float* p) {
-        if constexpr (COHERENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else return *p;
-    };
-    auto get4 = [](const float* p, int off) {
-        if constexpr (COHERENT) return load16_coherent(p, off);
-        else return *reinterpret_cast<const floatx4*>(reinterpret_cast<const char*>(p) + off);
-    };
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-    for (int t0 = 0; t0 < G; t0 += 8) {                      // groups larger than 8 heads: 8 at a time
-        const int gt = min(8, G - t0), cols = gt * (D / 4);  // four output elements each
-        const int SG = min(THREADS / cols, nsplit);          // >= 1; fewer, longer chains were 1-3 us a launch slower at 8 splits
-        const int sg = tid / cols, col = tid - sg * cols, t = col / (D / 4);
-        const int off = (t0 + t) * po.nsplit * (D * 4) + (col - t * (D / 4)) * 16;   // the unit's base is wave-uniform
-        constexpr int kBatch = 8;                            // 16: 140 VGPRs, and 168 us instead of 139 for four one-head layers
-        floatx4 v[kBatch];
-        auto fetch = [&](int s0) {
+template <int D, int THREADS, bool COHERENT>
+struct HeadStates {
+    static constexpr int kCols = D / 4, kGroups = THREADS / kCols, N = 64 / kGroups;
+    float m, l;                                              // of split `lane`
+    floatx4 v[N];
+    // the states of splits [from, nsplit), from a multiple of kGroups
+    __device__ __forceinline__ void fetch_outputs(const PartialOut& po, int head, int from, int nsplit) {
+        const int tid = threadIdx.x, sg = tid / kCols, col = tid - sg * kCols;
+        const int off = head * po.nsplit * (D * 4) + col * 16;                        // the unit's base is wave-uniform
 #pragma unroll
-            for (int q = 0; q < kBatch; ++q)
-                if (q * SG < nsplit) v[q] = get4(po.o, off + min(s0 + q * SG, nsplit - 1) * (D * 4));   // uniform over the workgroup
-        };
-        if (sg < SG) fetch(sg);                              // on their way while the weights are formed
-        __syncthreads();
-        for (int h = w; h < gt; h += THREADS / 64) {
-            const float* p = po.ml + (int64_t)(t0 + h) * po.nsplit * 2;
-            const float ms = lane < nsplit ? get(p + 2 * lane) : -INFINITY;
-            const float ls = lane < nsplit ? get(p + 2 * lane + 1) : 0.f;
-            float M = ms;
-#pragma unroll
-            for (int x = 32; x; x >>= 1) M = fmaxf(M, __shfl_xor(M, x));
-            const float a = M > -INFINITY ? fast_exp2(ms - M) : 0.f;
-            float tot = a * ls;
-#pragma unroll
-            for (int x = 32; x; x >>= 1) tot += __shfl_xor(tot, x);
-            lds.wgt[h][lane] = tot > 0.f ? a / tot : 0.f;
-        }
-        __syncthreads();
-        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-        if (sg < SG) {
-            for (int s0 = sg; s0 < nsplit; s0 += kBatch * SG) {
-                if (s0 != sg) fetch(s0);
-#pragma unroll
-                for (int q = 0; q < kBatch; ++q)
-                    if (s0 + q * SG < nsplit) acc += lds.wgt[t][s0 + q * SG] * v[q];
+        for (int q = 0; q < N; ++q)
+            if (q * kGroups >= from && q * kGroups < nsplit) {                        // uniform over the workgroup
+                const int at = off + min(sg + q * kGroups, nsplit - 1) * (D * 4);
+                if constexpr (COHERENT) v[q] = load16_coherent(po.o, at);
+                else v[q] = *reinterpret_cast<const floatx4*>(reinterpret_cast<const char*>(po.o) + at);
             }
-        }
-        if (SG > 1) {
-            if (sg < SG) lds.sum[tid] = acc;
-            __syncthreads();
-            if (sg == 0)
-                for (int x = 1; x < SG; ++x) acc += lds.sum[x * cols + col];
-        }
+    }
+    __device__ __forceinline__ void fetch_sums(const PartialOut& po, int head, int nsplit) {
+        const int lane = threadIdx.x & 63;
+        const float* p = po.ml + ((int64_t)head * po.nsplit + min(lane, nsplit - 1)) * 2;
+        if constexpr (COHERENT) {
+            m = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            l = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else { m = p[0]; l = p[1]; }
+        if (lane >= nsplit) { m = -INFINITY; l = 0.f; }
+    }
+    __device__ __forceinline__ float weight() const {        // of split `lane`
+        const float M = wave_max(m);
+        const float a = M > -INFINITY ? fast_exp2(m - M) : 0.f;
+        const float tot = wave_sum(a * l);
+        return tot > 0.f ? a / tot : 0.f;
+    }
+    template <typename T>
+    __device__ __forceinline__ void finish(int nsplit, floatx4 (&sum)[THREADS], T* __restrict__ out) const {
+        const int tid = threadIdx.x, sg = tid / kCols, col = tid - sg * kCols;
+        const float w = weight();
+        floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if (q * kGroups < nsplit) {
+                const float ws = __shfl(w, min(sg + q * kGroups, 63));
+                if (sg + q * kGroups < nsplit) acc += ws * v[q];
+            }
+        sum[tid] = acc;
+        __syncthreads();
         if (sg == 0) {
-            T* dst = out + (int64_t)t0 * D + col * 4;
+            for (int x = 1; x < min(kGroups, nsplit); ++x) acc += sum[x * kCols + col];
+            T* dst = out + col * 4;
 #pragma unroll
             for (int e = 0; e < 4; ++e) dst[e] = to_out<T>(acc[e]);
         }
     }
-}
+};
 
 // Merge the 4 row groups of every wave, then the 4 waves, and write the workgroup's partial state (one head).
 template <int D, bool COHERENT>
@@ -210,6 +198,10 @@ template <int GT> constexpr int kDecWaves = kDecMfma<GT> ? 8 : 4;        // wave
 constexpr int kDecTile = 16;          // cached rows per wave step
 // Tiles of a split that is called long (SplitRule).  Such a split takes about 85 us (one head, 3072 rows) and 100 us (groups,
 // 6144 rows) on one workgroup; for shorter ones more workgroups mostly add launching and merging.
+// Splits of a group of heads that the step kernel merges itself.  us, one launch and two: 8 x 32 heads on 8, 4 splits 26.7, 28.0; 8 x 28
+// on 4, 8 splits 13.6, 14.8; 4 x 28 on 4, 16 splits 19.3, 20.2; 28 on 4, 41 splits 14.4, 12.2; 14 on 2, 17 splits 11.6, 10.9.  With room for 32
+// states in registers 14.0, 20.1 and 11.2.
+constexpr int kMergeSplits = 16;
 constexpr int kDecLongOne = 192, kDecLongGroups = 384;
 
 template <typename T, int EPL> struct alignas(sizeof(T) * EPL > 16 ? 16 : sizeof(T) * EPL) RawChunk { T v[EPL]; };
@@ -446,12 +438,13 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_partial_kernel(
 
 struct Lengths { const int32_t* len[3]; int cap[3]; };     // row counts of a unit's parts (NULL: no such part), on the device
 
-// Merges the splits of a unit that hold rows (all of them when no lengths are given).
+// Merges the splits of a unit that hold rows (all of them when no lengths are given), one workgroup per unit and head: a CU takes in
+// 42 GB/s, and the 41 states of seven heads are 147 KB.
 template <typename T, int D, int THREADS>
 __global__ __launch_bounds__(THREADS) void decode_combine_kernel(const float* __restrict__ part, Lengths parts, SplitRule rule, int G, T* __restrict__ o)
 {
-    __shared__ MergeLds lds;
-    const int u = blockIdx.x;
+    __shared__ floatx4 sum[THREADS];
+    const int u = blockIdx.x, head = blockIdx.y;
     int nsplit = rule.most;
     if (parts.len[0]) {
         int tiles = 0;
@@ -460,24 +453,72 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(const float* __
         const int per = tiles_per_split(tiles, rule);
         nsplit = max(1, (tiles + per - 1) / per);
     }
-    merge_splits<T, D, THREADS, false>(PartialOut(const_cast<float*>(part), D, u, G, rule.most, rule.units), G, nsplit, lds, o + (int64_t)u * G * D);
+    const PartialOut po(const_cast<float*>(part), D, u, G, rule.most, rule.units);
+    HeadStates<D, THREADS, false> x;
+    x.fetch_outputs(po, head, 0, nsplit);
+    x.fetch_sums(po, head, nsplit);
+    x.template finish<T>(nsplit, sum, o + ((int64_t)u * G + head) * D);
 }
 
-// ---------------------------------------------------------------- one launch per decode step
-// Append and attention of Algorithm 2 in one kernel.  The new row (k_new / v_new) becomes row len of the
+// ---------------------------------------------------------------- a decode step
+// Append and attention of Algorithm 2 together.  The new row (k_new / v_new) becomes row len of the
 // cache: the workgroup whose split contains that row takes it from k_new / v_new in its place in the row
-// order (the arithmetic is that of the two separate calls) and stores it in the cache.  Every workgroup
-// of a unit - those without rows too - reads len and then arrives at a per-unit counter; the one that
-// arrives last merges the unit's partial states, writes the output, advances len and clears the counter.
-// Since all workgroups have read len before the last one arrives, the update cannot be seen by a reader of
-// the old value.
-template <typename T, int D, int GT>
+// order (the arithmetic is that of the two separate calls) and stores it in the cache.
+// One launch (kMerge): every workgroup of a unit - those without rows too - reads len and then arrives at a
+// per-unit counter; the one that arrives last merges the unit's partial states, writes the output, advances len and
+// clears the counter.  Since all workgroups have read len before the last one arrives, the update cannot be seen by
+// a reader of the old value.
+// Groups of heads with many splits: a second launch merges, a workgroup per unit and head, and advances len.  Every split leaves a
+// state, those without rows one that says so (kNoRows), because len is about to change and cannot be read for their number.
+// 28 heads on 4, 7200 rows, 41 splits: 12.3 us a layer, 14.4 with one launch (the last workgroup alone takes 4.3 us for the 147 KB of a
+// unit's states); the merge shared by the last workgroups to arrive, each waiting for the counter a bounded number of times: 19.5.
+constexpr float kNoRows = -1.f;                              // instead of a sum
+
+// One wave per head, all of at most kMergeSplits states on the way at once; the sums are those of HeadStates, bit for bit.
+template <typename T, int D>
+__device__ __forceinline__ void merge_few_states(const PartialOut& po, int head, int nsplit, T* __restrict__ out) {
+    constexpr int EPL = D / 64;
+    const int lane = threadIdx.x & 63;
+    HeadStates<D, 512, true> x;
+    float v[kMergeSplits][EPL];
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(po.o, 0, 0x7FFFFFFF, 0x00020000);
+#pragma unroll
+    for (int s = 0; s < kMergeSplits; ++s)
+        if (s < nsplit) {
+            const int at = (head * po.nsplit + s) * (D * 4) + lane * (EPL * 4);
+            if constexpr (EPL == 2) {
+                const uintx2 r = __builtin_bit_cast(uintx2, __builtin_amdgcn_raw_buffer_load_b64(rs, at, 0, 16));      // sc1, as load16_coherent
+                v[s][0] = __uint_as_float(r[0]);
+                v[s][EPL - 1] = __uint_as_float(r[1]);
+            } else v[s][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, at, 0, 16));
+        }
+    x.fetch_sums(po, head, nsplit);
+    const float w = x.weight();
+    static_assert(kMergeSplits <= HeadStates<D, 512, true>::kGroups, "one state in each partial sum");
+    float acc[EPL] = {};
+#pragma unroll
+    for (int s = 0; s < kMergeSplits; ++s)
+        if (s < nsplit) {
+            const float ws = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), s));
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) {
+                float p = fmaf(ws, v[s][e], 0.f);
+                asm volatile("" : "+v"(p));                  // rounded before it is added
+                acc[e] = s == 0 ? p : acc[e] + p;
+            }
+        }
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) out[lane * EPL + e] = to_out<T>(acc[e]);
+}
+
+template <typename T, int D, int GT, bool kMerge>
 __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_step_kernel(
     const T* __restrict__ q, T* __restrict__ Kc, T* __restrict__ Vc, int32_t* __restrict__ len, int cap,
     const T* __restrict__ k_new, const T* __restrict__ v_new, int Hq, int Hkv, float c, SplitRule rule,
     float* __restrict__ part, unsigned* __restrict__ arrived, T* __restrict__ out)
 {
-    __shared__ union { float red[kDecWaves<GT>][GT][D + 2]; MergeLds merge; } lds;
+    constexpr int kThreads = 64 * kDecWaves<GT>;
+    __shared__ __attribute__((aligned(16))) union { float red[kDecWaves<GT>][GT][D + 2]; floatx4 sum[GT == 1 ? kThreads : 1]; } lds;
     __shared__ int is_last;
     const int G = Hq / Hkv;
     const int u = rule.unit(), split = rule.split(), tid = threadIdx.x;
@@ -491,22 +532,60 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_step_kernel(
     const PartialOut po(part, D, u, G, rule.most, rule.units);
 
     if (split < nsplit)
-        attend_one<T, D, GT, true>(q + (int64_t)u * G * D, G, c, Kc + (int64_t)u * cap * D, Vc + (int64_t)u * cap * D,
+        attend_one<T, D, GT, kMerge>(q + (int64_t)u * G * D, G, c, Kc + (int64_t)u * cap * D, Vc + (int64_t)u * cap * D,
                                      k_new + (int64_t)u * D, v_new + (int64_t)u * D, room ? L0 : -1, r_begin, r_end, lds.red, po, 0, split);
-
-    // The partial state went out with device-scope (write-through) stores: once they have completed
-    // (vmcnt 0) it is visible to every XCD, and only then is this workgroup counted.  A release fence
-    // would do the same by writing back the whole L2, 150 us per launch here.
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (tid == 0) is_last = atomicAdd(&arrived[u], 1u) == rule.most - 1u;
-    __syncthreads();
-    if (!is_last) return;
-    merge_splits<T, D, 64 * kDecWaves<GT>, true>(po, G, nsplit, lds.merge, out + (int64_t)u * G * D);
-    if (tid == 0) {
-        if (room) len[u] = Lraw + 1;
-        arrived[u] = 0u;                                     // ready for the next step
+    else if (!kMerge && tid < G) {
+        po.ml[2 * ((int64_t)tid * po.nsplit + split)] = -INFINITY;
+        po.ml[2 * ((int64_t)tid * po.nsplit + split) + 1] = kNoRows;
     }
+    if constexpr (kMerge) {
+        // The partial state went out with device-scope (write-through) stores: once they have completed
+        // (vmcnt 0) it is visible to every XCD, and only then is this workgroup counted.  A release fence
+        // would do the same by writing back the whole L2, 150 us per launch here.
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (tid == 0) is_last = atomicAdd(&arrived[u], 1u) == rule.most - 1u;
+        __syncthreads();
+        if (!is_last) return;
+        if (tid == 0) {
+            if (room) len[u] = Lraw + 1;
+            arrived[u] = 0u;                                 // ready for the next step
+        }
+        T* const o = out + (int64_t)u * G * D;
+        if constexpr (GT == 1) {
+            HeadStates<D, kThreads, true> x;
+            x.fetch_outputs(po, 0, 0, nsplit);
+            x.fetch_sums(po, 0, nsplit);
+            x.template finish<T>(nsplit, lds.sum, o);
+        } else {
+            static_assert(GT <= kDecWaves<GT>, "a wave per head");
+            const int head = __builtin_amdgcn_readfirstlane(tid >> 6);
+            if (head < G) merge_few_states<T, D>(po, head, nsplit, o + head * D);
+        }
+    }
+}
+
+template <typename T, int D, int THREADS>
+__global__ __launch_bounds__(THREADS) void decode_step_combine_kernel(const float* __restrict__ part, int32_t* __restrict__ len, int cap, SplitRule rule,
+                                                                      int G, T* __restrict__ o)
+{
+    __shared__ floatx4 sum[THREADS];
+    using States = HeadStates<D, THREADS, false>;
+    const int u = blockIdx.x, head = blockIdx.y;
+    const PartialOut po(const_cast<float*>(part), D, u, G, rule.most, rule.units);
+    States x;
+    const int first = (rule.least + States::kGroups - 1) / States::kGroups * States::kGroups;      // states that most likely hold rows: not waited for the sums
+    x.fetch_outputs(po, head, 0, min(first, rule.most));
+    x.fetch_sums(po, head, rule.most);
+    const bool none = x.l == kNoRows || (int)(threadIdx.x & 63) >= rule.most;
+    const int nsplit = 64 - __popcll(__ballot(none));
+    if (none) x.l = 0.f;
+    x.fetch_outputs(po, head, first, nsplit);
+    if (head == 0 && threadIdx.x == 0) {
+        const int L = len[u];
+        if (L >= 0 && L < cap) len[u] = L + 1;
+    }
+    x.template finish<T>(nsplit, sum, o + ((int64_t)u * G + head) * D);
 }
 
 // ---------------------------------------------------------------- mixed-precision cache
@@ -765,10 +844,6 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
 // Error of the output against float64, fp32 queries, n = 300 to 30000: 2.0e-7 in the mean (2.3e-6 on the vector units).
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef int intx2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, -INFINITY, [](float a, float b) { return fmaxf(a, b); }); }
-template <typename N>
-__device__ __forceinline__ N wave_sum(N v) { return wave_reduce(v, N(0), [](N a, N b) { return a + b; }); }
 
 // |x| < 2^30 as four signed bytes of weight 256^i, byte i in bits 8 i ...
 __device__ __forceinline__ uint32_t signed_bytes(int x) { return ((uint32_t)x + 0x00808080u) ^ 0x00808080u; }
@@ -1083,7 +1158,7 @@ static int launch_decode_t(const void* q, const void* Kc, const void* Vc, const 
     KernelTimer tm(ZIPVL_K_DECODE_COMBINE, st);
     // as many threads as in the fused step, which makes the two paths add the splits in the same order
     if (G > 1)
-        hipLaunchKernelGGL((decode_combine_kernel<T, D, 64 * kDecWaves<8>>), dim3(units), dim3(64 * kDecWaves<8>), 0, st,
+        hipLaunchKernelGGL((decode_combine_kernel<T, D, 64 * kDecWaves<8>>), dim3(units, G), dim3(64 * kDecWaves<8>), 0, st,
             (const float*)ws, lengths, rule, G, (T*)o);
     else
         hipLaunchKernelGGL((decode_combine_kernel<T, D, 64 * kDecWaves<1>>), dim3(units), dim3(64 * kDecWaves<1>), 0, st,
@@ -1121,7 +1196,7 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
     }
 #undef ZIPVL_DECQ_ARGS
     KernelTimer tm(ZIPVL_K_DECODE_COMBINE, st);
-    hipLaunchKernelGGL((decode_combine_kernel<T, D, 256>), dim3(units), dim3(256), 0, st,
+    hipLaunchKernelGGL((decode_combine_kernel<T, D, 256>), dim3(units, G), dim3(256), 0, st,
         (const float*)ws, lengths, rule, G, (T*)o);
     return check_launch("decode_combine");
 }
@@ -1146,14 +1221,23 @@ static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len,
     }
     const float c = scale * kLog2e;
     const SplitRule rule = split_rule(d, cap);
-    KernelTimer tm(ZIPVL_K_DECODE_STEP, st);
-#define ZIPVL_STEP(GT)                                                                               \
-    hipLaunchKernelGGL((decode_step_kernel<T, D, GT>), rule.grid(), dim3(64 * kDecWaves<GT>), 0, st, (const T*)q, (T*)Kc, (T*)Vc, len, cap, \
+    const bool one_launch = G == 1 || rule.most <= kMergeSplits;
+    {
+        KernelTimer tm(ZIPVL_K_DECODE_STEP, st);
+#define ZIPVL_STEP(GT, MERGE)                                                                        \
+    hipLaunchKernelGGL((decode_step_kernel<T, D, GT, MERGE>), rule.grid(), dim3(64 * kDecWaves<GT>), 0, st, (const T*)q, (T*)Kc, (T*)Vc, len, cap, \
         (const T*)k_new, (const T*)v_new, d.Hq, d.Hkv, c, rule, part, arrived, (T*)o)
-    if (G > 1) ZIPVL_STEP(8);
-    else ZIPVL_STEP(1);
+        if (G == 1) ZIPVL_STEP(1, true);
+        else if (one_launch) ZIPVL_STEP(8, true);
+        else ZIPVL_STEP(8, false);
 #undef ZIPVL_STEP
-    return check_launch("decode_step");
+    }
+    int rc = check_launch("decode_step");
+    if (rc || one_launch) return rc;
+    KernelTimer tm(ZIPVL_K_DECODE_COMBINE, st);
+    constexpr int kThreads = 64 * kDecWaves<8>;
+    hipLaunchKernelGGL((decode_step_combine_kernel<T, D, kThreads>), dim3(d.B * d.Hkv, G), dim3(kThreads), 0, st, (const float*)part, len, cap, rule, G, (T*)o);
+    return check_launch("decode_combine");
 }
 
 int launch_decode_step(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,

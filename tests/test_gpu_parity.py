@@ -1454,6 +1454,43 @@ def test_decode_step_one_launch_matches_append_then_attention(dtype, d, Hq, Hkv)
     assert worst <= ATOL_OUT[dtype]
 
 
+@pytest.mark.parametrize("dtype,d,units,G,cap,splits", [("bf16", 128, 4, 7, 3900, 16), ("bf16", 128, 2, 7, 4200, 17), ("f32", 128, 3, 2, 8300, 33), ("bf16", 64, 1, 8, 17000, 64),
+                                                        ("f32", 64, 1, 5, 300, 2), ("bf16", 64, 64, 2, 24700, 16), ("bf16", 64, 32, 3, 49300, 32)])
+def test_decode_step_of_head_groups_with_few_and_many_splits(dtype, d, units, G, cap, splits):
+    """The step that merges its splits itself (16 of them at most) and the one that leaves it to a second launch, also where a long
+    unit has more splits than the others (the last two): empty, short, nearly full and full caches, three steps.  The same bits as
+    append and attention one after the other, whose outputs agree with the oracle."""
+    say(f"decode_step of groups dtype={dtype} d={d} units={units} G={G} cap={cap}")
+    Hq = units * G
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(71)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device=DEV, dtype=torch.float32).to(dt)
+    Ka, Va = torch.zeros((units, cap, d), dtype=dt, device=DEV), torch.zeros((units, cap, d), dtype=dt, device=DEV)
+    lens = ([cap - 2, 0, 17, cap] + [15, 63, 64, 200] * (units // 4))[:units]
+    for u, n in enumerate(lens):
+        Ka[u, :n], Va[u, :n] = rnd(n, d), rnd(n, d)
+    Kb, Vb, la = Ka.clone(), Va.clone(), torch.tensor(lens, dtype=torch.int32, device=DEV)
+    lb = la.clone()
+    ws = z.decode_step_workspace(1, Hq, units, cap, d, Ka)
+    assert ws.numel() >= units * G * splits * (d + 2) * 4
+    scale = 1.0 / math.sqrt(d)
+    for step in range(3):
+        q, kn, vn = rnd(Hq, d) * 2, rnd(units, d), rnd(units, d)
+        oa = z.zipvl_decode_step(q, Ka, Va, la, kn, vn, scale, B=1, Hq=Hq, Hkv=units, ws=ws)
+        z.zipvl_kv_append(Kb, Vb, lb, kn, vn, B=1, Hkv=units)
+        ob = z.zipvl_decode_attn(q, Kb, Vb, lb, scale, B=1, Hq=Hq, Hkv=units)
+        torch.cuda.synchronize()
+        assert torch.equal(la, lb) and la.tolist() == [min(cap, n + 1) for n in lens]
+        assert torch.equal(oa, ob) and torch.equal(Ka, Kb) and torch.equal(Va, Vb)
+        lens = la.tolist()
+        for u in range(min(units, 4)):
+            for h in (0, G - 1):
+                ref = oz.decode_attention(host64(q[u * G + h]), host64(Kb[u]), host64(Vb[u]), lens[u], scale)
+                assert np.abs(host64(oa[u * G + h]) - ref).max() <= ATOL_OUT[dtype]
+    assert int(ws[:4 * units].view(torch.int32).abs().sum().item()) == 0      # counters left at zero
+
+
 def test_decode_256_fused_steps_bit_identical_to_append_then_attention_at_the_stack_shape():
     """zipvl_decode_step against zipvl_kv_append + zipvl_decode_attn over 256 consecutive steps at the 32-head,
     batch-4 stack shape: outputs, lengths and caches must agree bit for bit at every step (the fused kernel
