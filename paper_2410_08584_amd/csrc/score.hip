@@ -14,8 +14,9 @@
 // wave owns one (query head, block of 32 probe rows) - its "task" - for the
 // whole kernel: the probe rows' fragments stay in its registers, and the key
 // fragments of a tile come from LDS.  With few tasks (one query head per KV
-// head) several waves share a task and split the key blocks of a stage; with
-// more tasks than waves the chunk is streamed once per round of tasks.
+// head) several waves share a task and split the key blocks of a stage; more
+// tasks are dealt to several workgroups in pass 1 (task_groups), and taken in
+// rounds, the chunk streamed once for each, in pass 2.
 // Pass 1 computes K Q^T (lane = probe column: row statistics stay in the
 // lane); pass 2 computes Q K^T (lane = key column: column sums stay in the
 // lane, the tasks' sums of a stage meet in LDS and are added in task order, so
@@ -55,12 +56,12 @@ __device__ __forceinline__ void merge_stats(float& m, float& l, float m2, float 
 // PASS 1: partial[((b*Hq + head) * nsplit + chunk) * np + probe] = (raw-logit maximum, sum of exp2((s - max) * c))
 // PASS 2: mass / rank of the workgroup's keys; nsplit = chunks of pass 1
 // np = probe rows rounded up to a multiple of 32 (NB blocks); rows beyond m are masked out.
-// bpc = 32-key blocks per chunk of this pass.
+// bpc = 32-key blocks per chunk of this pass; tpg = tasks per workgroup of pass 1, at most NWV.
 template <typename T, int D, int PASS, int NWV>
 __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV == 8) ? 2 : 4) void score_kernel(
     const T* __restrict__ Q, const T* __restrict__ K,
     int64_t qs0, int64_t qs1, int64_t qs2, int64_t ks0, int64_t ks1, int64_t ks2,
-    ProbeList probes, int m, int NB, int n, int n_eff, float c, float2* __restrict__ partial, int nsplit, int bpc,
+    ProbeList probes, int m, int NB, int n, int n_eff, float c, float2* __restrict__ partial, int nsplit, int bpc, int tpg,
     float* __restrict__ mass, float* __restrict__ rank, int Hq, int Hkv, int kv_div)
 {
     using C = ScoreCfg<T, D, NWV>;
@@ -72,7 +73,9 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     __shared__ __attribute__((aligned(16))) float row_bias[PASS == 2 ? NWV : 1][32];
     __shared__ float colbuf[PASS == 2 ? 2 : 1][PASS == 2 ? NWV : 1][PASS == 2 ? SK : 1];
 
-    const int G = Hq / Hkv, np = NB * 32, NT = G * NB;
+    const int G = Hq / Hkv, np = NB * 32;
+    const int task0 = PASS == 1 ? blockIdx.z * tpg : 0;
+    const int NT = PASS == 1 ? min(tpg, G * NB - task0) : G * NB;    // tasks of this workgroup
     const int u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
     const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);          // wave-uniform: everything derived from it lives in scalar registers
@@ -88,7 +91,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     // waves -> tasks.  Fewer tasks than waves: KS waves share a task and take the key blocks slot, slot + KS, ...
     const bool few = NT < NWV;
     const int KS = few ? NWV / NT : 1;
-    const int rounds = few ? 1 : (NT + NWV - 1) / NWV;
+    const int rounds = PASS == 1 || few ? 1 : (NT + NWV - 1) / NWV;
     const int ts = few ? w % NT : w;                                 // task slot inside a round
     const int slot = few ? w / NT : 0;
 
@@ -130,7 +133,8 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
         const int task = rd * NWV + ts;
         const bool active = few ? w < NT * KS : task < NT;
         const int ntr = few ? NT : min(NWV, NT - rd * NWV);          // tasks of this round
-        const int head = active ? task / NB : 0, nb = active ? task - (task / NB) * NB : 0;
+        const int tk = PASS == 1 ? task0 + task : task;              // of the KV head's
+        const int head = active ? tk / NB : 0, nb = active ? tk - (tk / NB) * NB : 0;
         const int bh = b * Hq + g * G + head;
 
         if (rd) __syncthreads();                                     // the stage buffers of the previous round are free
@@ -344,7 +348,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                     const float2 v = wstat[few ? sl * NT + q : q][pc];
                     merge_stats(M, L, v.x, v.y, c);
                 }
-                const int tk = rd * NWV + q, hd = tk / NB, nbk = tk - hd * NB;
+                const int tk = task0 + rd * NWV + q, hd = tk / NB, nbk = tk - hd * NB;
                 partial[((int64_t)(b * Hq + g * G + hd) * nsplit + blockIdx.x) * np + nbk * 32 + pc] = make_float2(M, L);
             }
         }
@@ -378,40 +382,64 @@ size_t score_workspace_bytes(const zipvl_dims& d, int m) {
     return (size_t)d.B * d.Hq * max_chunks * probe_rows(m) * sizeof(float2);
 }
 
-template <typename T, int D, int NWV>
+// Pass 1: groups of tasks, a workgroup each, per KV head and chunk.  A task for each of the 8 waves, or half as many tasks
+// and two waves for each: a chunk of as many workgroups is twice as long, so that pass 2 has half of the statistics to read and
+// pass 1 reads K twice as often.  The two together, bytes per CU, decide (kKeyCost: a byte of K against one of the statistics, from
+// where the two cost the same: 28 heads on 4, m = 64 n = 13000, 14 on 2 n = 33000).  us, all tasks of a KV head in one workgroup of 16 waves, in
+// rounds of 16 where there are more -> 8 a workgroup, 4 a workgroup: 28 heads on 4, m = 64, n = 4096 22.4 -> 21.5, 20.0; n = 18432 37.3 -> 35.3, 36.4;
+// m = 128 n = 4096 39.5 -> 30.3, 29.8; n = 18432 69.4 -> 62.1, 62.0; 32 on 2, n = 4096 40.8 -> 29.1, 26.7; 32 on 8, n = 4096 21.0 (8), 19.7.
+constexpr double kKeyCost = 1.2;
+
+static int task_groups(int NT, int units, int nblk, int row_bytes, int waves2) {
+    const int full = (NT + 7) / 8, half = (NT + 3) / 4, slots = resident_slots(8), cus = resident_slots(16);
+    auto cost = [&](int groups) {
+        const int bpc = blocks_per_chunk(nblk, units * groups, slots), chunks = (nblk + bpc - 1) / bpc;
+        return kKeyCost * groups * units * nblk * 32.0 * row_bytes / cus + (double)chunks * NT * 32 * sizeof(float2) * (16 / waves2);
+    };
+    return cost(half) < cost(full) ? half : full;
+}
+
+template <typename T, int D, int PASS, int NWV>
+static int reserve_lds() {
+    static std::atomic<bool> done{false};                            // raising the dynamic-LDS cap is idempotent
+    if (!done) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&score_kernel<T, D, PASS, NWV>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, kStageBufs * ScoreCfg<T, D, NWV>::STG) != hipSuccess)
+            return set_error(ZIPVL_EHIP, "score: cannot reserve LDS for the key stages");
+        done = true;
+    }
+    return ZIPVL_OK;
+}
+
+// NW2: waves per workgroup of pass 2 (pass 1: 8)
+template <typename T, int D, int NW2>
 static int launch_score_w(const void* Q, const void* K, const zipvl_dims& d, const ProbeList& pl, int m,
                           int n_eff, float scale, float* mass, float* rank, void* ws, int kv_div, hipStream_t st)
 {
-    using C = ScoreCfg<T, D, NWV>;
     const float c = scale * kLog2e;
     float2* partial = (float2*)ws;
-    const int units = d.B * d.Hkv, NB = probe_rows(m) / 32;
-    const size_t lds = (size_t)kStageBufs * C::STG;
-    static std::atomic<bool> attr_done{false};
-    if (!attr_done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&score_kernel<T, D, 1, NWV>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(&score_kernel<T, D, 2, NWV>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return set_error(ZIPVL_EHIP, "score: cannot reserve LDS for the key stages");
-        attr_done = true;
-    }
-    const int slots = resident_slots(NWV);
-    const int nblk1 = (n_eff + 31) / 32, bpc1 = blocks_per_chunk(nblk1, units, slots), nsplit = (nblk1 + bpc1 - 1) / bpc1;
-    const int nblk2 = (d.n + 31) / 32, bpc2 = blocks_per_chunk(nblk2, units, slots), chunks2 = (nblk2 + bpc2 - 1) / bpc2;
+    const int units = d.B * d.Hkv, NB = probe_rows(m) / 32, NT = d.Hq / d.Hkv * NB;
+    constexpr size_t lds1 = (size_t)kStageBufs * ScoreCfg<T, D, 8>::STG, lds2 = (size_t)kStageBufs * ScoreCfg<T, D, NW2>::STG;
+    int rc = reserve_lds<T, D, 1, 8>();
+    if (rc) return rc;
+    rc = reserve_lds<T, D, 2, NW2>();
+    if (rc) return rc;
+    const int nblk1 = (n_eff + 31) / 32, groups = task_groups(NT, units, nblk1, D * (int)sizeof(T), NW2), tpg = (NT + groups - 1) / groups;
+    const int bpc1 = blocks_per_chunk(nblk1, units * groups, resident_slots(8)), nsplit = (nblk1 + bpc1 - 1) / bpc1;
+    const int nblk2 = (d.n + 31) / 32, bpc2 = blocks_per_chunk(nblk2, units, resident_slots(NW2)), chunks2 = (nblk2 + bpc2 - 1) / bpc2;
     {
         KernelTimer tm(ZIPVL_K_SCORE_ROWSTATS, st);
-        hipLaunchKernelGGL((score_kernel<T, D, 1, NWV>), dim3(nsplit, units), dim3(64 * NWV), lds, st,
+        hipLaunchKernelGGL((score_kernel<T, D, 1, 8>), dim3(nsplit, units, groups), dim3(512), lds1, st,
             (const T*)Q, (const T*)K, d.q_strides[0], d.q_strides[1], d.q_strides[2],
-            d.k_strides[0], d.k_strides[1], d.k_strides[2], pl, m, NB, d.n, n_eff, c, partial, nsplit, bpc1,
+            d.k_strides[0], d.k_strides[1], d.k_strides[2], pl, m, NB, d.n, n_eff, c, partial, nsplit, bpc1, tpg,
             (float*)nullptr, (float*)nullptr, d.Hq, d.Hkv, kv_div);
     }
-    int rc = check_launch("score_rowstats");
+    rc = check_launch("score_rowstats");
     if (rc) return rc;
     KernelTimer tm(ZIPVL_K_SCORE_COLSUM, st);
-    hipLaunchKernelGGL((score_kernel<T, D, 2, NWV>), dim3(chunks2, units), dim3(64 * NWV), lds, st,
+    hipLaunchKernelGGL((score_kernel<T, D, 2, NW2>), dim3(chunks2, units), dim3(64 * NW2), lds2, st,
         (const T*)Q, (const T*)K, d.q_strides[0], d.q_strides[1], d.q_strides[2],
-        d.k_strides[0], d.k_strides[1], d.k_strides[2], pl, m, NB, d.n, n_eff, c, partial, nsplit, bpc2,
+        d.k_strides[0], d.k_strides[1], d.k_strides[2], pl, m, NB, d.n, n_eff, c, partial, nsplit, bpc2, NT,
         mass, rank, d.Hq, d.Hkv, kv_div);
     return check_launch("score_colsum");
 }

@@ -317,6 +317,22 @@ def test_scores_match_oracle(case):
     say(f"  worst relative score error so far {WORST_SCORE_ERR['rel']:.2e} (bound 1e-5)")
 
 
+@pytest.mark.parametrize("dtype,d,G,Hkv,n,m", [("bf16", 128, 5, 1, 90, 40), ("bf16", 128, 8, 2, 40, 40), ("f32", 64, 9, 1, 1000, 64), ("bf16", 64, 11, 1, 700, 96),
+                                               ("bf16", 128, 16, 1, 150, 128), ("f32", 128, 16, 1, 500, 65), ("bf16", 128, 8, 1, 17000, 33), ("bf16", 64, 13, 1, 9000, 128)])
+def test_scores_of_wide_groups(dtype, d, G, Hkv, n, m):
+    """More (head, block of 32 probes) tasks than one workgroup of the row statistics takes, 8 or 4 a workgroup, in even and uneven
+    shares, over few and many keys: the oracle's scores with the bound above, for probes over the whole sequence."""
+    say(f"scores of wide groups dtype={dtype} d={d} G={G} n={n} m={m}")
+    r = np.random.Generator(np.random.PCG64(81))
+    pp = np.sort(np.append(r.choice(n - 1, m - 1, replace=False), n - 1)).astype(np.int32)
+    w = make_custom(1, G * Hkv, Hkv, n, d, dtype, seed=82, m=m, probe_pos=pp)
+    mass, rank = z.zipvl_score(dev(w.Q, dtype), dev(w.K, dtype), w.probe_pos, w.scale)
+    torch.cuda.synchronize()
+    mo, ro = oz.token_scores(w.Q[0], w.K[0], w.probe_pos, w.scale)
+    assert_scores_close(host64(mass), mo, dtype, "mass")
+    assert_scores_close(host64(rank), ro, dtype, "rank")
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("name", ["first-rows", "block-ends-early", "one-past-a-block", "straddling", "last-row-only"])
 def test_scores_where_blocks_of_probes_end(name, dtype):
