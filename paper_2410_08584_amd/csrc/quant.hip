@@ -4,249 +4,253 @@
 // fp16 (scale, zero) pair:
 //   zero = fp16(min), scale = fp16((max - min) * fp32(1 / (2^bits - 1))),
 //   code = clamp(rint((x - zero) / scale), 0, 2^bits - 1)   (0 when scale = 0), all in fp32.
-// Two kernels: `token_slots` turns T (ascending positions) into, for every token,
-// its row in the 4-bit group (rank among the kept tokens) or in the 2-bit group
-// (rank among the others, Eq. (10)), with an LDS bitmap and a prefix count;
-// `quantize_rows` then handles 16 rows per wave pass, 16 lanes per row like the
-// decode kernels, so every code row is written as one contiguous store per lane.
-#include <atomic>
+// One kernel: a workgroup takes 64 tokens, 8 lanes per row, each with 8 (d = 64) or 2 x 8 (d = 128) of its elements.  A token's row in the 4-bit group (rank among the kept tokens) or in the 2-bit
+// group (rank among the others, Eq. (10)) comes from a bisection of T (ascending positions) by every wave, while the
+// rows are on their way.
 #include <type_traits>
 
 #include "launch.h"
-#include "rowops.h"
 
 namespace zipvl {
 
-constexpr int kQuantMaxTokens = 262144;      // bitmap + prefix counts of one unit fit in 64 KB of LDS
-constexpr int kSlotThreads = 1024;
-constexpr int kQuantRows = 64;               // rows per workgroup of quantize_rows
+constexpr int kQuantMaxTokens = 262144;
+constexpr int kQuantRows = 64;               // rows per workgroup: a bit each of a 64-bit mask
+constexpr int kLanes = 8, kPass = 256 / kLanes, kPasses = kQuantRows / kPass;      // lanes per row, rows per pass
 
-// slot[ut, j] = i >= 0: token j is T_i (4-bit row i);  slot = ~i < 0: token j is the i-th other token (2-bit row i)
-__global__ __launch_bounds__(kSlotThreads) void token_slots_kernel(
-    const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt, int n, int32_t* __restrict__ slot)
-{
-    extern __shared__ uint32_t lds[];
-    const int nwords = (n + 31) >> 5;
-    uint32_t* bm = lds;                      // [nwords] bit j set <=> token j is in T
-    uint32_t* pre = lds + nwords;            // [nwords] number of kept tokens before word w
-    __shared__ uint32_t wave_tot[kSlotThreads / 64];
-    const int ut = blockIdx.x, tid = threadIdx.x;
-    int kk = kcnt ? kcnt[ut] : n;
-    kk = max(0, min(kk, n));
-    for (int w = tid; w < nwords; w += kSlotThreads) bm[w] = 0u;
-    __syncthreads();
-    for (int i = tid; i < kk; i += kSlotThreads) {
-        const int t = idx ? idx[(int64_t)ut * n + i] : i;
-        if (t >= 0 && t < n) atomicOr(&bm[t >> 5], 1u << (t & 31));
-    }
-    __syncthreads();
-    // exclusive prefix of the word popcounts: every thread owns a contiguous run of words
-    const int per = (nwords + kSlotThreads - 1) / kSlotThreads;
-    const int w0 = min(tid * per, nwords), w1 = min(w0 + per, nwords);
-    uint32_t mine = 0;
-    for (int w = w0; w < w1; ++w) mine += __popc(bm[w]);
-    uint32_t incl = mine;                    // inclusive scan inside the wave
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_up(incl, off);
-        if ((tid & 63) >= off) incl += v;
-    }
-    if ((tid & 63) == 63) wave_tot[tid >> 6] = incl;
-    __syncthreads();
-    uint32_t before = incl - mine;
-    for (int ww = 0; ww < (tid >> 6); ++ww) before += wave_tot[ww];
-    for (int w = w0; w < w1; ++w) { pre[w] = before; before += __popc(bm[w]); }
-    __syncthreads();
-    for (int j = tid; j < n; j += kSlotThreads) {
-        const uint32_t word = bm[j >> 5], bit = j & 31;
-        const int kept_before = (int)(pre[j >> 5] + __popc(word & ((1u << bit) - 1u)));
-        slot[(int64_t)ut * n + j] = ((word >> bit) & 1u) ? kept_before : ~(j - kept_before);
-    }
+// Minimum and maximum over the 8 lanes of a row, of a row of K and one of V at a time, result in all of them.  One instruction a step
+// and value, where the compiler takes three (a lane permute, a quieting, the minimum); a lane permute may not read what the two
+// instructions before it wrote, and here three others always lie between.
+__device__ __forceinline__ void row8_extremes(float& klo, float& khi, float& vlo, float& vhi) {
+#define ZIPVL_STEP(CTRL)                                                            \
+    "v_min_f32_dpp %0, %0, %0 " CTRL " row_mask:0xf bank_mask:0xf\n\t"              \
+    "v_max_f32_dpp %1, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf\n\t"              \
+    "v_min_f32_dpp %2, %2, %2 " CTRL " row_mask:0xf bank_mask:0xf\n\t"              \
+    "v_max_f32_dpp %3, %3, %3 " CTRL " row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t" ZIPVL_STEP("quad_perm:[1,0,3,2]") ZIPVL_STEP("quad_perm:[2,3,0,1]") ZIPVL_STEP("row_half_mirror")
+        : "+v"(klo), "+v"(khi), "+v"(vlo), "+v"(vhi));
+#undef ZIPVL_STEP
 }
 
-// minimum / maximum over the 16 lanes of a row, result in all of them (lane permutes inside the row, no LDS)
-template <bool MAX>
-__device__ __forceinline__ float row16_extreme(float v) {
-    auto step = [&](auto ctrl) {
-        const float o = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
-        v = MAX ? fmaxf(v, o) : fminf(v, o);
-    };
-    step(std::integral_constant<int, 0xB1>());       // quad_perm [1,0,3,2]
-    step(std::integral_constant<int, 0x4E>());       // quad_perm [2,3,0,1]
-    step(std::integral_constant<int, 0x141>());      // mirror of 8: the other quad
-    step(std::integral_constant<int, 0x140>());      // mirror of 16: the other 8
-    return v;
-}
+// 8 elements of a row as loaded
+template <typename T> struct RawPiece;
+template <> struct RawPiece<__bf16> {
+    uintx4 v;
+    __device__ __forceinline__ void load(const __bf16* p) { v = load16(p); }
+    __device__ __forceinline__ float operator[](int e) const { return __uint_as_float(e & 1 ? v[e >> 1] & 0xFFFF0000u : v[e >> 1] << 16); }
+};
+template <> struct RawPiece<float> {
+    floatx4 v[2];
+    __device__ __forceinline__ void load(const float* p) { v[0] = *reinterpret_cast<const floatx4*>(p); v[1] = *reinterpret_cast<const floatx4*>(p + 4); }
+    __device__ __forceinline__ float operator[](int e) const { return v[e >> 2][e & 3]; }
+};
 
-// Codes and parameters of one row (EPL elements in each of its 16 lanes) at 4 or 2 bits, chosen per row: one
-// instruction stream serves the rows of both widths that share a wave.
-// The code is rint of the correctly rounded (x - zero) / scale.  The product with a reciprocal lies within 1e-5 of that
-// quotient wherever it is below 16, so the two round to the same code unless it comes that close to a half; only
-// then (about one wave step in a hundred) are the divisions taken.
-template <int EPL>
-__device__ __forceinline__ uint32_t quantize_chunk(const float (&x)[EPL], bool wide, uint32_t& params) {
-    float lo = x[0], hi = x[0];
-#pragma unroll
-    for (int e = 1; e < EPL; ++e) { lo = fminf(lo, x[e]); hi = fmaxf(hi, x[e]); }
-    lo = row16_extreme<false>(lo);
-    hi = row16_extreme<true>(hi);
-    const float qmax = wide ? 15.f : 3.f;
+// Codes (8 to a word) and parameters of one row, P pieces of 8 elements in each of its lanes, lo and hi its extremes, at 4 or 2
+// bits, chosen per row: one instruction stream serves the rows of both widths that share a wave.
+// The code is rint of the correctly rounded (x - zero) / scale, clamped.  One correction of the product with a reciprocal gives that
+// quotient: the remainder it takes is exact, and as scale has 11 bits no quotient lies closer than 2^-12 of its last place to the
+// middle of two floats, where what is left of the error (2^-22 of a last place) could turn the rounding.  bf16 rows meet exact halves in every fifth
+// wave step, so that a division only near them, as it was, took a fifth of the instructions.  The products of the row's extremes
+// say whether a code needs the clamp; only then, or where an element is not a number, divisions and clamps are taken.
+// Four codes are put together by fused multiply-adds (below 2^16: exact).
+template <typename T, int P>
+__device__ __forceinline__ void quantize_chunk(const RawPiece<T> (&x)[P], float lo, float hi, bool wide, uint32_t (&word)[P], uint32_t& params) {
+    const float qmax = wide ? 15.f : 3.f, base = wide ? 16.f : 4.f;
+    const int bits = wide ? 4 : 2;
     const _Float16 zero_h = (_Float16)lo;
     float step = (hi - lo) * (wide ? (float)(1.0 / 15.0) : (float)(1.0 / 3.0));
     asm volatile("" : "+v"(step));            // the product is rounded to fp32 first: no fused multiply-convert
     const _Float16 scale_h = (_Float16)step;
     const float zero = (float)zero_h, scale = (float)scale_h;
     const float inv = scale > 0.f ? __builtin_amdgcn_rcpf(scale) : 0.f;
-    const int bits = wide ? 4 : 2;
-    uint32_t word = 0;
-    float off = 0.f;                                         // largest distance from the nearest integer
+    float sum = 0.f;
 #pragma unroll
-    for (int e = EPL - 1; e >= 0; --e) {
-        const float t = (x[e] - zero) * inv, q = __builtin_rintf(t);
-        off = fmaxf(off, fabsf(t - q));
-        word = (word << bits) | (uint32_t)fminf(fmaxf(q, 0.f), qmax);
+    for (int p = 0; p < P; ++p) {
+        float four[2];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+#pragma unroll
+            for (int e = 3; e >= 0; --e) {
+                const float d = x[p][4 * f + e] - zero, t = d * inv, q = __builtin_rintf(fmaf(fmaf(-t, scale, d), inv, t));
+                four[f] = e == 3 ? q : fmaf(four[f], base, q);
+            }
+            sum += four[f];
+        }
+        word[p] = ((uint32_t)four[1] << (4 * bits)) | (uint32_t)four[0];
     }
-    if (__any(off > 0.49999f)) {
-        word = 0;
+    const bool plain = ((lo - zero) * inv >= -0.499f) & ((hi - zero) * inv <= qmax + 0.499f) & (sum >= 0.f);
+    if (__any(!plain)) {
 #pragma unroll
-        for (int e = EPL - 1; e >= 0; --e) {
-            float t = scale > 0.f ? (x[e] - zero) / scale : 0.f;
-            t = fminf(fmaxf(__builtin_rintf(t), 0.f), qmax);
-            word = (word << bits) | (uint32_t)t;
+        for (int p = 0; p < P; ++p) {
+            word[p] = 0;
+#pragma unroll
+            for (int e = 7; e >= 0; --e) {
+                float t = scale > 0.f ? (x[p][e] - zero) / scale : 0.f;
+                t = fminf(fmaxf(__builtin_rintf(t), 0.f), qmax);
+                word[p] = (word[p] << bits) | (uint32_t)t;
+            }
         }
     }
     params = (uint32_t)__builtin_bit_cast(uint16_t, scale_h) | ((uint32_t)__builtin_bit_cast(uint16_t, zero_h) << 16);
-    return word;
 }
 
-// one lane's EPL elements of a row as loaded
-template <typename T, int EPL>
-struct RawRow {
-    T v[EPL];
-    __device__ __forceinline__ void load(const T* p) {
-        struct alignas(sizeof(T) * EPL > 16 ? 16 : sizeof(T) * EPL) Raw { T v[EPL]; };
-        const Raw r = *reinterpret_cast<const Raw*>(p);
+template <typename T, int P>
+__device__ __forceinline__ void chunk_extremes(const RawPiece<T> (&x)[P], float& lo, float& hi) {
+    lo = hi = x[0][0];
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) v[e] = r.v[e];
-    }
-    __device__ __forceinline__ void floats(float (&f)[EPL]) const {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) f[e] = (float)v[e];
-    }
-};
+    for (int e = 1; e < 8 * P; ++e) { lo = fminf(lo, x[e >> 3][e & 7]); hi = fmaxf(hi, x[e >> 3][e & 7]); }
+}
 
 struct QTensorOut {
     uint8_t* hi_codes; uint32_t* hi_params;
     uint8_t* lo_codes; uint32_t* lo_params;
 };
 
+// Bound by vector instructions and memory alike: 807 instructions a wave for 64 elements a lane, 74 % of a SIMD's cycles, under 630 MB in
+// 128 us (4.9 TB/s) at 128 units x 8192 rows of 256 bytes.  With 16 lanes a row, a division near every half and a launch before it that
+// wrote every token's slot: 1246, all of the cycles, 143 + 6 us.  us a call, so -> now: that shape 164 -> 133, 4 x 18432 28.7 -> 18.8,
+// 32 x 2933 29.7 -> 19.7; d = 64, 64 x 9000 60.6 -> 43.5; fp32, 40 x 4097 40.5 -> 34.9.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(
     const T* __restrict__ K, const T* __restrict__ V,
     int64_t ks0, int64_t ks1, int64_t ks2, int64_t vs0, int64_t vs1, int64_t vs2,
-    const int32_t* __restrict__ slot, const int32_t* __restrict__ kcnt,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
     QTensorOut Kq, QTensorOut Vq, int cap_hi, int cap_lo, int32_t* __restrict__ len_hi, int32_t* __restrict__ len_lo,
     int n, int Hkv, int t_per_batch)
 {
-    constexpr int EPL = D / 16;
+    constexpr int P = D / 64;
     const int u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
     const int ut = t_per_batch ? b : u;
-    const int tid = threadIdx.x, sub = tid & 15, rl = tid >> 4;         // 16 rows per pass
+    const int tid = threadIdx.x, lane = tid & 63, sub = tid % kLanes, rl = tid / kLanes;
+    int kk = kcnt ? kcnt[ut] : n;
+    kk = max(0, min(kk, n));
     if (blockIdx.x == 0 && tid == 0) {
-        int kk = kcnt ? kcnt[ut] : n;
-        kk = max(0, min(kk, n));
         len_hi[u] = min(kk, cap_hi);
         len_lo[u] = min(n - kk, cap_lo);
     }
-    const T* Kb = K + b * ks0 + g * ks1 + sub * EPL;
-    const T* Vb = V + b * vs0 + g * vs1 + sub * EPL;
-    const int32_t* slots = slot + (int64_t)ut * n;
-    const int j0 = blockIdx.x * kQuantRows + rl;
-    constexpr int kPasses = kQuantRows / 16;
-    // rows past the end are loaded from the last one and dropped
-    RawRow<T, EPL> kr, vr;
-    int s = slots[min(j0, n - 1)];
-    kr.load(Kb + (int64_t)min(j0, n - 1) * ks2);
-    vr.load(Vb + (int64_t)min(j0, n - 1) * vs2);
-    using W4 = typename CodeWord<EPL, 4>::type;
-    using W2 = typename CodeWord<EPL, 2>::type;
+    // All rows of the workgroup are requested at once.  Rows past the end are loaded from the last one and dropped.
+    const int j0 = blockIdx.x * kQuantRows, left = n - 1 - j0;
+    const T* Kb = K + b * ks0 + g * ks1 + (int64_t)j0 * ks2;
+    const T* Vb = V + b * vs0 + g * vs1 + (int64_t)j0 * vs2;
+    const T* kl = Kb + rl * ks2;
+    const T* vl = Vb + rl * vs2;
+    RawPiece<T> kr[kPasses][P], vr[kPasses][P];
+    auto request = [&](auto whole) {
 #pragma unroll
-    for (int p = 0; p < kPasses; ++p) {
-        const int j = j0 + p * 16, jn = min(j + 16, n - 1);             // uniform over the 16 lanes of a row
-        RawRow<T, EPL> kx, vx;
-        int sx = 0;
-        if (p + 1 < kPasses) {                                          // the next rows are on their way while these are coded
-            sx = slots[jn];
-            kx.load(Kb + (int64_t)jn * ks2);
-            vx.load(Vb + (int64_t)jn * vs2);
-        }
-        const bool wide = s >= 0;
-        const int i = wide ? s : ~s;
-        float f[EPL];
-        uint32_t kp, vp;
-        kr.floats(f);
-        const uint32_t kw = quantize_chunk<EPL>(f, wide, kp);
-        vr.floats(f);
-        const uint32_t vw = quantize_chunk<EPL>(f, wide, vp);
-        if (j < n) {
-            if (wide) {
-                if (i < cap_hi) {
-                    const int64_t row = (int64_t)u * cap_hi + i;
-                    reinterpret_cast<W4*>(Kq.hi_codes + row * (D / 2))[sub] = (W4)kw;
-                    reinterpret_cast<W4*>(Vq.hi_codes + row * (D / 2))[sub] = (W4)vw;
-                    if (sub == 0) { Kq.hi_params[row] = kp; Vq.hi_params[row] = vp; }
-                }
-            } else if (i < cap_lo) {
-                const int64_t row = (int64_t)u * cap_lo + i;
-                reinterpret_cast<W2*>(Kq.lo_codes + row * (D / 4))[sub] = (W2)kw;
-                reinterpret_cast<W2*>(Vq.lo_codes + row * (D / 4))[sub] = (W2)vw;
-                if (sub == 0) { Kq.lo_params[row] = kp; Vq.lo_params[row] = vp; }
+        for (int p = 0; p < kPasses; ++p) {
+            const int r = min(rl + kPass * p, left);
+            const T* kp = whole ? kl + kPass * p * ks2 : Kb + r * ks2;
+            const T* vp = whole ? vl + kPass * p * vs2 : Vb + r * vs2;
+#pragma unroll
+            for (int c = 0; c < P; ++c) {
+                kr[p][c].load(kp + 64 * c + 8 * sub);
+                vr[p][c].load(vp + 64 * c + 8 * sub);
             }
         }
-        kr = kx; vr = vx; s = sx;
+    };
+    // The kept tokens before the workgroup's first, and which of its 64 are kept.  The first kept token at or after j0 is entry
+    // [lo, lo + len] of T: 64 probes a round, the first of them requested before the rows and the entries after them.
+    const int32_t* const T_u = idx ? idx + (int64_t)ut * n : nullptr;
+    int lo = 0, len = T_u ? kk : 0, probe = 0;
+    auto step_of = [&]() { return (len + 63) >> 6; };
+    auto ask = [&]() { if (len > kQuantRows) probe = T_u[lo + min((lane + 1) * step_of(), len) - 1]; };
+    ask();
+    if (left >= kQuantRows - 1) request(std::true_type{});
+    else request(std::false_type{});
+    auto narrow = [&]() {
+        const int step = step_of(), blocks = (len + step - 1) / step;
+        const int below = __popcll(__ballot(lane < blocks && probe < j0));                   // blocks that end before j0
+        lo += min(below * step, len);
+        len = below == blocks ? 0 : min(step, len - below * step);
+    };
+    if (len > kQuantRows) {                                  // apart from the loop: its wait is for the first request alone
+        narrow();
+        while (len > kQuantRows) { ask(); narrow(); }
+    }
+    int before = min(j0, kk);                                                               // without T: the first kk tokens
+    uint64_t mask = ~0ull >> (kQuantRows - max(1, min(kk - j0, kQuantRows)));
+    if (kk <= j0) mask = 0;
+    if (T_u) {
+        const int e0 = lo + lane, e1 = e0 + 64;
+        const int last = max(kk - 1, 0), t0 = T_u[min(e0, last)], t1 = T_u[min(e1, last)];
+        const unsigned b0 = e0 < kk ? t0 - j0 : ~0u, b1 = e1 < kk ? t1 - j0 : ~0u;
+        before = lo + __popcll(__ballot(e0 < kk && t0 < j0));
+        auto bits = [&](unsigned first) {
+            const int mine = (b0 - first < 32u ? 1u << (b0 - first) : 0u) | (b1 - first < 32u ? 1u << (b1 - first) : 0u);
+            return (uint32_t)wave_reduce(mine, 0, [](int x, int y) { return x | y; });
+        };
+        mask = bits(0) | (uint64_t)bits(32) << 32;
+    }
+    // of this unit: a row's offset in bytes fits 32 bits
+    const int64_t hi0 = (int64_t)u * cap_hi, lo0 = (int64_t)u * cap_lo;
+    auto put = [](auto* first, unsigned bytes, auto v) {
+        *reinterpret_cast<decltype(v)*>(reinterpret_cast<char*>(first) + bytes) = v;
+    };
+    const uint64_t mine = mask >> rl;                                   // bit kPass p: this lane's row of pass p
+    int kept_before = before + __popcll(mask & ((1ull << rl) - 1));
+#pragma unroll
+    for (int p = 0; p < kPasses; ++p) {
+        const int r = rl + kPass * p;
+        const bool wide = (uint32_t)(mine >> (kPass * p)) & 1u;
+        const unsigned i = wide ? kept_before : j0 + r - kept_before;
+        kept_before += __popc((uint32_t)(mine >> (kPass * p)));
+        float klo, khi, vlo, vhi;
+        chunk_extremes(kr[p], klo, khi);
+        chunk_extremes(vr[p], vlo, vhi);
+        row8_extremes(klo, khi, vlo, vhi);
+        uint32_t kp, vp, kw[P], vw[P];
+        quantize_chunk(kr[p], klo, khi, wide, kw, kp);
+        quantize_chunk(vr[p], vlo, vhi, wide, vw, vp);
+        if (r <= left) {
+            if (wide) {
+                if (i < (unsigned)cap_hi) {
+                    const unsigned at = i * (D / 2) + sub * 4;
+#pragma unroll
+                    for (int c = 0; c < P; ++c) {
+                        put(Kq.hi_codes + hi0 * (D / 2), at + 32 * c, kw[c]);
+                        put(Vq.hi_codes + hi0 * (D / 2), at + 32 * c, vw[c]);
+                    }
+                    if (sub == 0) { put(Kq.hi_params + hi0, i * 4, kp); put(Vq.hi_params + hi0, i * 4, vp); }
+                }
+            } else if (i < (unsigned)cap_lo) {
+                const unsigned at = i * (D / 4) + sub * 2;
+#pragma unroll
+                for (int c = 0; c < P; ++c) {
+                    put(Kq.lo_codes + lo0 * (D / 4), at + 16 * c, (uint16_t)kw[c]);
+                    put(Vq.lo_codes + lo0 * (D / 4), at + 16 * c, (uint16_t)vw[c]);
+                }
+                if (sub == 0) { put(Kq.lo_params + lo0, i * 4, kp); put(Vq.lo_params + lo0, i * 4, vp); }
+            }
+        }
     }
 }
+static_assert(kPass == 32, "a pass takes one half of the mask");
 
+// Not written by the kernel above; callers of the ABI hold it.
 size_t quantize_workspace_bytes(const zipvl_dims& d) { return (size_t)d.B * d.Hkv * d.n * sizeof(int32_t); }
 
 template <typename T, int D>
 static int launch_quantize_t(const void* K, const void* V, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                              const zipvl_qtensor& Kq, const zipvl_qtensor& Vq, int32_t cap_hi, int32_t cap_lo,
-                             int32_t* len_hi, int32_t* len_lo, int flags, void* ws, hipStream_t st)
+                             int32_t* len_hi, int32_t* len_lo, int flags, hipStream_t st)
 {
     const int units = d.B * d.Hkv;
     const int t_per_batch = (flags & ZIPVL_T_PER_BATCH) ? 1 : 0;
-    int32_t* slot = (int32_t*)ws;
-    const size_t lds = 2 * (size_t)((d.n + 31) / 32) * sizeof(uint32_t);
-    static std::atomic<bool> attr_done{false};
-    if (!attr_done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&token_slots_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024) != hipSuccess)
-            return set_error(ZIPVL_EHIP, "quantize_kv: cannot reserve LDS for the token bitmap");
-        attr_done = true;
-    }
-    {
-        KernelTimer tm(ZIPVL_K_TOKEN_SLOTS, st);
-        hipLaunchKernelGGL(token_slots_kernel, dim3(t_per_batch ? d.B : units), dim3(kSlotThreads), lds, st, idx, k, d.n, slot);
-    }
-    int rc = check_launch("token_slots");
-    if (rc) return rc;
     const QTensorOut kq{(uint8_t*)Kq.hi_codes, (uint32_t*)Kq.hi_params, (uint8_t*)Kq.lo_codes, (uint32_t*)Kq.lo_params};
     const QTensorOut vq{(uint8_t*)Vq.hi_codes, (uint32_t*)Vq.hi_params, (uint8_t*)Vq.lo_codes, (uint32_t*)Vq.lo_params};
     KernelTimer tm(ZIPVL_K_QUANTIZE_ROWS, st);
     hipLaunchKernelGGL((quantize_rows_kernel<T, D>), dim3((d.n + kQuantRows - 1) / kQuantRows, units), dim3(256), 0, st,
         (const T*)K, (const T*)V, d.k_strides[0], d.k_strides[1], d.k_strides[2],
-        d.v_strides[0], d.v_strides[1], d.v_strides[2], (const int32_t*)slot, k, kq, vq, cap_hi, cap_lo, len_hi, len_lo,
+        d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, kq, vq, cap_hi, cap_lo, len_hi, len_lo,
         d.n, d.Hkv, t_per_batch);
     return check_launch("quantize_rows");
 }
 
 int launch_quantize_kv(const void* K, const void* V, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                        const zipvl_qtensor& Kq, const zipvl_qtensor& Vq, int32_t cap_hi, int32_t cap_lo,
-                       int32_t* len_hi, int32_t* len_lo, int flags, void* ws, hipStream_t st)
+                       int32_t* len_hi, int32_t* len_lo, int flags, hipStream_t st)
 {
     if (d.n > kQuantMaxTokens) return set_error(ZIPVL_ESHAPE, "quantize_kv: n = %d exceeds %d", d.n, kQuantMaxTokens);
-#define ZIPVL_ARGS K, V, d, idx, k, Kq, Vq, cap_hi, cap_lo, len_hi, len_lo, flags, ws, st
+#define ZIPVL_ARGS K, V, d, idx, k, Kq, Vq, cap_hi, cap_lo, len_hi, len_lo, flags, st
     if (d.dtype == ZIPVL_BF16) {
         if (d.d == 128) return launch_quantize_t<__bf16, 128>(ZIPVL_ARGS);
         return launch_quantize_t<__bf16, 64>(ZIPVL_ARGS);

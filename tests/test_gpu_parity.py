@@ -8,6 +8,7 @@ compaction bit-exact.
 """
 import math
 import sys
+import types
 
 import numpy as np
 import pytest
