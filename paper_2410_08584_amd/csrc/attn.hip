@@ -4,8 +4,8 @@
 // Two kernels:
 //   pack   gathers K[T] and V[T] into the workspace, once per KV head, zero-filling
 //          the ragged tail.  An evicted cache with contiguous rows is read in place and
-//          nothing is packed at all (the P.V operand comes from row-major V tiles in LDS:
-//          bf16 through the transposing read, fp32 one element per lane and product).
+//          nothing is packed at all (the P.V operand comes from row-major V tiles in LDS
+//          through the transposing read).
 //   flash  one workgroup = 128 kept queries of one query head (4 waves x 32
 //          rows; 64 where there are few, two waves then share 32 rows and halve
 //          the keys of every tile).  K / V tiles of 64 keys are loaded straight into LDS (double
@@ -28,6 +28,8 @@
 //          by extra workgroups at the end of the same grid (one per head and span
 //          of positions), which run in the slots the thinning end of the
 //          attention work leaves idle.
+//          fp32 rows are split into three bf16 planes on their way into LDS, and a product
+//          is taken as six of planes (flash_queries_f32).
 // The kept count k lives on the device: the grid covers the worst case (k = n),
 // but every workgroup knows the tiles of the longest head, so that those without
 // work stand at the end of the grid; heavy (late) query tiles are scheduled first,
@@ -56,7 +58,26 @@ constexpr int kScanSets = 512, kScanBlocks = 512;
 constexpr int kSecondRound = 4096;
 constexpr float kLazyLog2 = 8.f;     // slack of the running softmax offset below the running maximum (log2 domain)
 constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p64f;   // row sums of the offset-free pass that need no second pass
+template <int D> constexpr int kPlanesLine = D == 64 ? 900 : 600;   // fp32: live tiles up to which a head's keys are split (splits_keys)
 constexpr int kSchedAhead = 3;       // LDS operand reads in flight ahead of the consuming MFMA
+
+// fp32 (flash_queries_f32): K and V as three bf16 planes each in LDS
+template <int D, int KS>
+struct SplitCfg {
+    static constexpr int NW = KS == 4 ? 8 : 4;               // waves; 32 NW / KS queries
+    static constexpr int TK = 32 * KS;                       // keys per tile: a 32-key block for every wave
+    static constexpr int RB = 2 * D;                         // bytes per row of a plane
+    static constexpr int PLANE = TK * RB;
+    // Three planes of K and three of V, or (d = 128, KS > 1) three that K and V take in turns.  The pass in fp32 products has a tile
+    // of K and one of V.
+    static constexpr bool kShared = D == 128 && KS > 1;
+    static constexpr int LDS_BYTES = kShared ? 2 * TK * D * 4 : 6 * PLANE;
+    static_assert(KS == 1 || 64 * NW * D * 2 <= LDS_BYTES, "room for the sums of all waves");
+    static_assert(!kShared || 3 * PLANE + 32 * NW / KS * RB <= LDS_BYTES, "room for a plane of Q");
+    static constexpr int LPR = D / 8;                        // lanes per row when a tile is converted (8 elements each)
+    static constexpr int RPP = 64 * NW / LPR, NP = TK / RPP;     // rows per pass of the workgroup, passes
+    static constexpr int CH = D / 16, ODB = D / 32;
+};
 
 // NW = waves per workgroup, QB = 32-query blocks per wave: a workgroup covers 32 QB NW kept queries, its
 // K / V^T tiles are fetched from L2 once per that many queries, and every LDS operand fragment a wave
@@ -76,10 +97,10 @@ struct AttnCfg {
     static constexpr int VRB = D * E;                        // bytes per V row
     static constexpr int TILE_BYTES = kBN * D * E;           // one K tile = one V tile
     static constexpr int NLD = TILE_BYTES / 1024 / NW;       // 1-KiB direct-to-LDS loads per wave per tile
-    static constexpr int LDS_BYTES = 4 * TILE_BYTES;         // two K and two V buffers
-    // bf16, QB = 1: two waves per SIMD (<= 256 registers, accumulators stay in VGPRs); otherwise one
-    // wave per SIMD with the whole 512-entry register file
-    static constexpr int MIN_WGS = (E == 2 && QB == 1) ? 8 / NW : 1;
+    static constexpr int LDS_BYTES = E == 4 ? SplitCfg<D, KS>::LDS_BYTES : 4 * TILE_BYTES;     // two K and two V buffers
+    // QB = 1: two waves per SIMD (<= 256 registers, accumulators stay in VGPRs), three for fp32 at d = 64 in workgroups of four;
+    // otherwise one wave per SIMD with the whole 512-entry register file
+    static constexpr int MIN_WGS = QB == 1 ? E == 4 ? (D == 64 && NW == 4 ? 3 : 2) : 8 / NW : 1;
 };
 
 // ------------------------------------------------------------------ pack
@@ -134,19 +155,17 @@ __global__ __launch_bounds__(256) void pack_kv_kernel(
 // per-lane source offsets for tile_to_lds (rows of RB bytes)
 // Row swizzle of a row-major bf16 V tile (rows of RB bytes): the transposing read of a 16-lane group
 // touches 4 consecutive keys x 4 consecutive 16-byte chunks, so the key index goes into chunk bits 2..3
-// (one bit of it is already an address bit when two rows share a 256-byte bank period).  fp32: a wave reads 32
-// consecutive elements of two rows 4 apart, which go to the two halves of the bank period.
-template <int RB, int E>
-__device__ __forceinline__ int v_row_swizzle(int row) { return E == 4 ? ((row >> 2) & 1) << 3 : ((row & 3) >> (RB == 128 ? 1 : 0)) << 2; }
+// (one bit of it is already an address bit when two rows share a 256-byte bank period).
+template <int RB>
+__device__ __forceinline__ int v_row_swizzle(int row) { return ((row & 3) >> (RB == 128 ? 1 : 0)) << 2; }
 
-// VE: 0 for K tiles, bytes per element for V tiles
-template <int RB, int NW, int NLD, int VE = 0>
+template <int RB, int NW, int NLD, bool V = false>
 __device__ __forceinline__ void lds_fill_offsets(int w, int lane, int (&off)[NLD]) {
 #pragma unroll
     for (int q = 0; q < NLD; ++q) {
         const int o = (q * NW + w) * 1024 + lane * 16;
         const int r = o / RB, p = (o % RB) >> 4;
-        off[q] = r * RB + ((p ^ (VE ? v_row_swizzle<RB, VE>(r) : k_row_swizzle<RB>(r))) << 4);
+        off[q] = r * RB + ((p ^ (V ? v_row_swizzle<RB>(r) : k_row_swizzle<RB>(r))) << 4);
     }
 }
 
@@ -170,7 +189,7 @@ __device__ __forceinline__ void tile_load_pinned(const char* gtile, int q, const
 // Only the first `rows` rows of the tile may be read: fewer than kBN happens once per head, at its last tile, and the
 // rows after them are then filled from the last one, chunk for chunk.  That form derives its offsets again from the
 // thread index, so that the key loop carries nothing for it.
-template <int RB, int NW, int NLD, int VE = 0>
+template <int RB, int NW, int NLD, bool V = false>
 __device__ __forceinline__ void tile_to_lds(const char* gtile, unsigned lds_dst, const int (&off)[NLD], int rows) {
     if (rows >= kBN) {
 #pragma unroll
@@ -181,7 +200,7 @@ __device__ __forceinline__ void tile_to_lds(const char* gtile, unsigned lds_dst,
 #pragma unroll 1
         for (int q = 0; q < NLD; ++q) {
             const int o = q * NW * 1024 + tid * 16, r = o / RB, p = (o % RB) >> 4;
-            const int chunk = (p ^ (VE ? v_row_swizzle<RB, VE>(r) : k_row_swizzle<RB>(r))) << 4;
+            const int chunk = (p ^ (V ? v_row_swizzle<RB>(r) : k_row_swizzle<RB>(r))) << 4;
             load_kib_to_lds(gtile, min(r, rows - 1) * RB + chunk, lds_dst + q * NW * 1024);
         }
     }
@@ -224,7 +243,7 @@ template <int D, int NW, int QB, int KS> struct PV<__bf16, D, NW, QB, KS> {
         const int row = 4 * h + e;                           // key inside its group of 8 = swizzle of the row
 #pragma unroll
         for (int db = 0; db < C::ODB; ++db)
-            lane_off[db] = row * C::VRB + swz_chunk(4 * db + 2 * grp + (q >> 1), v_row_swizzle<C::VRB, 2>(row)) + (q & 1) * 8;
+            lane_off[db] = row * C::VRB + swz_chunk(4 * db + 2 * grp + (q >> 1), v_row_swizzle<C::VRB>(row)) + (q & 1) * 8;
     }
     template <int HALF>
     __device__ static __forceinline__ void run(const char* vb, const int (&lane_off)[C::ODB], const Probs& p,
@@ -243,35 +262,6 @@ template <int D, int NW, int QB, int KS> struct PV<__bf16, D, NW, QB, KS> {
                 for (int qb = 0; qb < QB; ++qb) o[qb][db] = mma_frag<__bf16>(vf, p[qb][HALF][s2], o[qb][db]);
             }
         }
-    }
-};
-
-template <int D, int NW, int QB, int KS> struct PV<float, D, NW, QB, KS> {
-    using C = AttnCfg<float, D, NW, QB, KS>;
-    using Probs = floatx16[QB][C::NBK];                           // p[qb][blk][r]: as the S^T accumulators
-    // lane_off[db]: this lane's element of channel block db in a row whose swizzle is 0 (rows 4 h + ... of a group of 8 have h)
-    __device__ static __forceinline__ void lane_offsets(int lane, int (&lane_off)[C::ODB]) {
-        const int i = lane & 31, h = lane >> 5;
-#pragma unroll
-        for (int db = 0; db < C::ODB; ++db)
-            lane_off[db] = 4 * h * C::VRB + swz_chunk(8 * db + (i >> 2), v_row_swizzle<C::VRB, 4>(4 * h)) + (i & 3) * 4;
-    }
-    template <int HALF>
-    __device__ static __forceinline__ void run(const char* vb, const int (&lane_off)[C::ODB], const Probs& p, floatx16 (&o)[QB][C::ODB]) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-            // step (a, t): this lane contributes key 32*HALF + 8*a + 4*h + t
-#pragma unroll
-            for (int db = 0; db < C::ODB; ++db) {
-                float v[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const float*>(vb + lane_off[db] + (32 * HALF + 8 * a + t) * C::VRB);
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int qb = 0; qb < QB; ++qb)
-                        o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[t], p[qb][HALF][4 * a + t], o[qb][db], 0, 0, 0);
-            }
     }
 };
 
@@ -331,7 +321,7 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     const int sw = k_row_swizzle<C::KRB>(i);
     int koff[C::NLD], voff[C::NLD];
     lds_fill_offsets<C::KRB, NW, C::NLD>(w, lane, koff);
-    lds_fill_offsets<C::VRB, NW, C::NLD, C::E>(w, lane, voff);
+    lds_fill_offsets<C::VRB, NW, C::NLD, true>(w, lane, voff);
     int vlane[C::ODB];
     PV<T, D, NW, QB, KS>::lane_offsets(lane, vlane);
 
@@ -340,7 +330,7 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         tile_to_lds<C::KRB, NW, C::NLD>(kg + (int64_t)t * C::TILE_BYTES, klds + buf * C::TILE_BYTES, koff, krows - t * kBN);
     };
     auto load_v = [&](int t, int buf) {
-        tile_to_lds<C::VRB, NW, C::NLD, C::E>(vg + (int64_t)t * C::TILE_BYTES, vlds + buf * C::TILE_BYTES, voff, vrows - t * kBN);
+        tile_to_lds<C::VRB, NW, C::NLD, true>(vg + (int64_t)t * C::TILE_BYTES, vlds + buf * C::TILE_BYTES, voff, vrows - t * kBN);
     };
     // The first tiles are requested before anything else is loaded: their addresses need only scalars, while the
     // query rows below wait for their positions first (two round trips).
@@ -403,10 +393,9 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     // of the operand kSchedAhead matrix instructions ahead; nothing moves across the fences between them.
     // HALF 0: P.V of the previous tile (src = its V tile), exponentials of key block 0, requests for a K tile.
     // HALF 1: S^T of the next tile (src = its K tile), exponentials of key block 1, requests for a V tile.
-    constexpr bool kExplicit = Elem<T>::kBytes == 2 && QB == 1;
+    static_assert(Elem<T>::kBytes == 2 && QB == 1, "the order below is for one query block of bf16");
     auto steady_half = [&](auto half_tag, const char* src, floatx16 (&sc)[QB][C::NBK], floatx16 (&sn)[QB][C::NBK], Probs& pp, Probs& pc,
                            float (&sum)[QB], const char* gt, unsigned lt) {
-        if constexpr (kExplicit) {
         constexpr int HALF = decltype(half_tag)::value;
         constexpr int NM = (HALF == 0 ? 4 * C::ODB : 2 * C::CH) / KS;  // matrix instructions of the half
         constexpr int PPM = 16 / KS / NM;                           // vector pieces per matrix instruction
@@ -464,7 +453,6 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
             for (int q = 0; q < PPM; ++q) piece((KS == 2 ? 8 * HALF : 0) + j * PPM + q);
             __builtin_amdgcn_sched_barrier(0);
         }
-        }
     };
     auto step = [&](int t, floatx16 (&sc)[QB][C::NBK], floatx16 (&sn)[QB][C::NBK], Probs& pp, Probs& pc) {
         // requests of this step: K tile t+2 into the buffer tile t has left (first half), V tile t+1 into the
@@ -475,20 +463,7 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         const char* kgt = kg + (int64_t)kt * C::TILE_BYTES;
         const char* vgt = vg + (int64_t)vt * C::TILE_BYTES;
         const unsigned kl = klds + (t & 1) * C::TILE_BYTES, vl = vlds + ((t + 1) & 1) * C::TILE_BYTES;
-        // load L of a half rides on exponential (2L+1) * 16 / (2 NLD) of that half's key block
-        auto fetch_after_exp = [&](int blk, int r, float& pinned) {
-#pragma unroll
-            for (int L = 0; L < C::NLD; ++L)
-                if (r == ((2 * L + 1) * 16) / (2 * C::NLD)) {
-                    unsigned pin = __float_as_uint(pinned);
-                    if (blk == 0) tile_load_pinned<C::KRB, NW, C::NLD>(kgt, L, koff, kl + L * NW * 1024, pin);
-                    else tile_load_pinned<C::VRB, NW, C::NLD>(vgt, L, voff, vl + L * NW * 1024, pin);
-                    pinned = __uint_as_float(pin);
-                }
-        };
         const bool has_pv = t >= 1 && t - 1 < my_tiles, has_s = t < my_tiles, has_next = t + 1 < my_tiles;
-        // fp32: the second block of a tile is left out where all its keys lie past the wave's last row (64 products of 64 cycles)
-        auto second = [&](int tile) { return KS == 1 && (Elem<T>::kBytes == 2 || tile * kBN + 32 <= min(wave_last_row, kk - 1)); };
         const char* kb = Kb0 + ((t + 1) & 1) * C::TILE_BYTES + kw * 32 * C::KRB;
         const char* vb = Vb0 + ((t + 1) & 1) * C::TILE_BYTES + kw * 32 * C::VRB;      // V tile t-1
         float mc[QB], sum[QB];
@@ -503,56 +478,29 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
                     for (int r = 0; r < 16; ++r)
                         if (t * kBN + 32 * (KS == 1 ? blk : kw) + acc_row(r, h) > qrow[qb]) sc[qb][blk][r] = -INFINITY;
         }
-        // Probabilities of this tile.  bf16: packed once into P^T operand fragments, and the row sums are
-        // taken over the values as rounded to bf16, so that numerator and denominator of the output use
-        // the same weights.  fp32: in place.
-        auto exps = [&](int blk, bool spread_loads) {
+        // Probabilities of this tile, packed once into P^T operand fragments; the row sums are taken over the values as rounded
+        // to bf16, so that numerator and denominator of the output use the same weights.
+        auto exps = [&](int blk) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                if constexpr (Elem<T>::kBytes == 2) {
+            for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-                    for (int r = 0; r < 16; r += 2) {
-                        float p0 = fast_exp2(SAFE ? fmaf(sc[qb][blk][r], c, -mc[qb]) : sc[qb][blk][r] * c);
-                        float p1 = fast_exp2(SAFE ? fmaf(sc[qb][blk][r + 1], c, -mc[qb]) : sc[qb][blk][r + 1] * c);
-                        if (spread_loads && qb == 0) { fetch_after_exp(blk, r, p0); fetch_after_exp(blk, r + 1, p1); }
-                        const uint32_t pk = pack_bf16x2(p0, p1);
-                        pc[qb][blk][r >> 3][(r & 7) >> 1] = pk;
-                        sum[qb] = add_bf16x2(pk, sum[qb]);
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        float p = fast_exp2(SAFE ? fmaf(sc[qb][blk][r], c, -mc[qb]) : sc[qb][blk][r] * c);
-                        if (spread_loads && qb == 0) fetch_after_exp(blk, r, p);
-                        pc[qb][blk][r] = p;
-                        sum[qb] += p;
-                    }
+                for (int r = 0; r < 16; r += 2) {
+                    const float p0 = fast_exp2(SAFE ? fmaf(sc[qb][blk][r], c, -mc[qb]) : sc[qb][blk][r] * c);
+                    const float p1 = fast_exp2(SAFE ? fmaf(sc[qb][blk][r + 1], c, -mc[qb]) : sc[qb][blk][r + 1] * c);
+                    const uint32_t pk = pack_bf16x2(p0, p1);
+                    pc[qb][blk][r >> 3][(r & 7) >> 1] = pk;
+                    sum[qb] = add_bf16x2(pk, sum[qb]);
                 }
-            }
         };
         const bool steady = has_pv && has_next && t < steady_end && !SAFE;
-        auto next_second = [&]() {
-            if constexpr (KS == 2) return;
-            else if (second(t + 1)) qk_block<T, D, NW, QB, KS>(kb, 1, i, h, sw, qf, sn);
-            else {
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb) sn[qb][1] = floatx16{0};      // masked for every row that exists
-            }
-        };
         // ---- first half: P.V of tile t-1 | exponentials of key block 0 of tile t | requests for K tile t+2
         if (steady) {
-            if constexpr (kExplicit) steady_half(std::integral_constant<int, 0>{}, vb, sc, sn, pp, pc, sum, kgt, kl);
-            else {
-                exps(0, true);
-                PV<T, D, NW, QB, KS>::template run<0>(vb, vlane, pp, o);
-                if constexpr (KS == 1) PV<T, D, NW, QB, KS>::template run<1>(vb, vlane, pp, o);
-            }
+            steady_half(std::integral_constant<int, 0>{}, vb, sc, sn, pp, pc, sum, kgt, kl);
         } else {
             load_k(kt, t & 1);
             if (has_pv) {
                 PV<T, D, NW, QB, KS>::template run<0>(vb, vlane, pp, o);
-                if constexpr (KS == 1)
-                    if (second(t - 1)) PV<T, D, NW, QB, KS>::template run<1>(vb, vlane, pp, o);
+                if constexpr (KS == 1) PV<T, D, NW, QB, KS>::template run<1>(vb, vlane, pp, o);
             }
             if (has_s) {
                 if constexpr (SAFE) {
@@ -590,30 +538,22 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
                         }
                     }
                 }
-                exps(0, false);
+                exps(0);
             }
         }
         wait_tiles(2);                                        // K tile t+1 has landed (this wave's part)
         __syncthreads();
         // ---- second half: S^T of tile t+1 | exponentials of key block 1 of tile t | requests for V tile t+1
         if (steady) {
-            if constexpr (kExplicit) steady_half(std::integral_constant<int, 1>{}, kb, sc, sn, pp, pc, sum, vgt, vl);
-            else {
-                if constexpr (KS == 1) exps(1, true);
-                else {
-#pragma unroll
-                    for (int L = 0; L < C::NLD; ++L) tile_load<C::VRB, NW, C::NLD>(vgt, L, voff, vl + L * NW * 1024);
-                }
-                qk_block<T, D, NW, QB, KS>(kb, 0, i, h, sw, qf, sn);
-                next_second();
-            }
+            steady_half(std::integral_constant<int, 1>{}, kb, sc, sn, pp, pc, sum, vgt, vl);
         } else {
             load_v(vt, (t + 1) & 1);
             if (has_next) {
                 qk_block<T, D, NW, QB, KS>(kb, 0, i, h, sw, qf, sn);
-                next_second();
+                if constexpr (KS == 1) qk_block<T, D, NW, QB, KS>(kb, 1, i, h, sw, qf, sn);
             }
-            if (has_s && second(t)) exps(1, false);
+            if constexpr (KS == 1)
+                if (has_s) exps(1);
         }
         if (has_s) {
 #pragma unroll
@@ -730,12 +670,338 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     }
 }
 
+// ---------------------------------------------------------------- fp32
+// Eight fp32 values as three bf16 planes, x = hi + mid + lo exactly (8 significant bits and a sign each, rounded to nearest, so
+// that a plane holds at most 2^-9 of the one before).  An infinity, a NaN or a value that rounds to one leaves a NaN in mid.
+struct Planes { uintx4 hi, mid, lo; };
+// x - the low (high) half of a packed pair, in one instruction
+// (the factors through a register: as a constant 0xBF800000 is taken for the float -1)
+__device__ __forceinline__ float less_half(float x, uint32_t pair, uint32_t factors) {
+    asm("" : "+s"(factors));
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), __builtin_bit_cast(bf16x2, factors), x, false);
+}
+__device__ __forceinline__ float less_low(float x, uint32_t pair) { return less_half(x, pair, 0x0000BF80u); }
+__device__ __forceinline__ float less_high(float x, uint32_t pair) { return less_half(x, pair, 0xBF800000u); }
+__device__ __forceinline__ Planes split8(const uintx4& a, const uintx4& b) {
+    Planes s;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float x0 = __uint_as_float(e < 2 ? a[2 * e] : b[2 * e - 4]), x1 = __uint_as_float(e < 2 ? a[2 * e + 1] : b[2 * e - 3]);
+        const uint32_t hi = pack_bf16x2(x0, x1);
+        const float r0 = less_low(x0, hi), r1 = less_high(x1, hi);
+        const uint32_t mid = pack_bf16x2(r0, r1);
+        s.hi[e] = hi;
+        s.mid[e] = mid;
+        s.lo[e] = pack_bf16x2(less_low(r0, mid), less_high(r1, mid));
+    }
+    return s;
+}
+// acc + a b in six products, the small ones first; what is left out (mid lo, lo mid, lo lo) is below 2^-26 of |a| |b|.
+__device__ __forceinline__ floatx16 mma_planes(const Planes& a, const Planes& b, floatx16 acc) {
+    acc = mma_frag<__bf16>(a.lo, b.hi, acc);
+    acc = mma_frag<__bf16>(a.hi, b.lo, acc);
+    acc = mma_frag<__bf16>(a.mid, b.mid, acc);
+    acc = mma_frag<__bf16>(a.mid, b.hi, acc);
+    acc = mma_frag<__bf16>(a.hi, b.mid, acc);
+    return mma_frag<__bf16>(a.hi, b.hi, acc);
+}
+
+// flash_queries for fp32.  A product of fp32 numbers on the matrix cores takes 16 times as long as one of bf16; here it is six of bf16.
+// K and V rows go through registers into LDS, split there by the workgroup once for all its waves (7 vector instructions for two elements,
+// a quarter of the time of the products of a 32-key tile); the queries' planes stay in registers, the weights are split where they
+// are taken.  Against 64 bits the outputs are nearer than with fp32 products (48 sums in a logit of d = 128 and not 64; 2-norm at 9000 rows
+// 9.4e-7, was 1.14e-6; at 300 6.2e-7, was 7.5e-7).  Bound: large calls by the rate of bf16 products (28 heads on 4, 4485 of 20 000 kept: 610 us,
+// 1.08 PFLOP/s of them), small ones by the chain of a workgroup's tiles: split, product, weights, product, between barriers.  Next rows are
+// requested after a tile's first product, where no operand of it waits for registers.  us, fp32 products -> so, every token kept: 28 heads on 4,
+// n = 3000 601 -> 350; 14 on 2, n = 3000 321 -> 207; d = 64, 32 on 8, n = 2000 161 -> 107; 4 heads, n = 576 26.8 -> 19.0; a third kept,
+// 32 heads, n = 2933 147 -> 76; 4485 of 20 000 1262 -> 607.
+template <int D, int KS>
+__device__ __forceinline__ void flash_queries_f32(const float* __restrict__ Q, int64_t qs2, const float* __restrict__ Kp, const float* __restrict__ Vp,
+                                                  const int32_t* __restrict__ tidx, float* __restrict__ O, int i0, int kk, float c, int out_compact)
+{
+    using C = SplitCfg<D, KS>;
+    constexpr int NW = C::NW, BM = 32 * NW / KS, TK = C::TK, RB = C::RB;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int qw = KS == 1 ? w : w % (NW / KS), kw = KS == 1 ? 0 : w / (NW / KS);        // wave w has the queries of wave qw, key block kw
+    const int ntiles = (min(i0 + BM, kk) + TK - 1) / TK;
+    // Derived again wherever it is used (the empty asm): carried through the key loop these would go to scratch, and so would what is
+    // kept from one tile of queries for the next.
+    struct Lane { int tid, lane, i, h, qrow, crow, ccol; };  // crow, ccol: its row and 8 elements of every pass over a tile of rows
+    auto this_lane = [&]() {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        return Lane{tid, tid & 63, tid & 31, (tid >> 5) & 1, i0 + 32 * qw + (tid & 31), tid / C::LPR, tid % C::LPR};
+    };
+    const int first_row = i0 + 32 * qw, last_row = min(first_row + 31, kk - 1);          // of the wave
+    floatx16 o[C::ODB];
+    float m_run = 0.f, l_run = 0.f;
+
+    auto load_rows = [&](const float* base, int t, const Lane& L, uintx4 (&raw)[C::NP][2]) {      // rows at and past k repeat row k - 1 and are masked
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p) {
+            const float* src = base + (int64_t)min(t * TK + p * C::RPP + L.crow, kk - 1) * D + L.ccol * 8;
+            raw[p][0] = load16(src);
+            raw[p][1] = load16(src + 4);
+        }
+    };
+    auto store_planes = [&](char* dst, const Lane& L, const uintx4 (&raw)[C::NP][2], auto swizzle) {
+#pragma unroll
+        for (int p = 0; p < C::NP; ++p) {
+            const int r = p * C::RPP + L.crow;
+            const Planes x = split8(raw[p][0], raw[p][1]);
+            char* const a = dst + r * RB + swz_chunk(L.ccol, swizzle(r));
+            store16(a, x.hi);
+            store16(a + C::PLANE, x.mid);
+            store16(a + 2 * C::PLANE, x.lo);
+        }
+    };
+    char* const kpl = smem;
+    char* const vpl = smem + (C::kShared ? 0 : 3 * C::PLANE);
+    auto mask = [&](int jb, const Lane& L, floatx16& s) {
+        if (jb + 31 > first_row) {                           // touches the diagonal (wave-uniform)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (jb + acc_row(r, L.h) > L.qrow) s[r] = -INFINITY;
+        }
+    };
+    auto pass_planes = [&]() {
+        const Lane L = this_lane();
+        const int lane = L.lane, i = L.i, h = L.h, qrow = L.qrow;
+        uintx4 kr[C::NP][2], vr[C::NP][2];
+        load_rows(Kp, 0, L, kr);
+        if constexpr (!C::kShared) load_rows(Vp, 0, L, vr);
+        Planes qf[C::CH];
+        char* const qlo = smem + 3 * C::PLANE + qw * (C::CH * 1024) + lane * 16;     // kShared: the last plane of Q stands in LDS (32 registers)
+        {
+            const int qc = min(qrow, kk - 1), pos = tidx ? tidx[qc] : qc;
+            const float* qp = Q + (int64_t)pos * qs2 + 8 * h;
+#pragma unroll
+            for (int cc = 0; cc < C::CH; ++cc) {
+                qf[cc] = split8(load16(qp + 16 * cc), load16(qp + 16 * cc + 4));
+                if constexpr (C::kShared) store16(qlo + cc * 1024, qf[cc].lo);       // both waves of the queries store the same
+            }
+        }
+#pragma unroll
+        for (int db = 0; db < C::ODB; ++db) o[db] = floatx16{0};
+        // V^T operands through the transposing read, as for bf16
+        int vlane[C::ODB];
+        {
+            const int grp = (lane >> 4) & 1, e = (lane >> 2) & 3, q = lane & 3, row = 4 * h + e;
+#pragma unroll
+            for (int db = 0; db < C::ODB; ++db)
+                vlane[db] = (32 * kw + row) * RB + swz_chunk(4 * db + 2 * grp + (q >> 1), v_row_swizzle<RB>(row)) + (q & 1) * 8;
+        }
+        const int krow = (32 * kw + i) * RB, sw = k_row_swizzle<RB>(i);
+#pragma unroll 1
+        for (int t = 0; t < ntiles; ++t) {
+            if (t) __syncthreads();                          // everyone is done with tile t - 1
+            store_planes(kpl, L, kr, [](int r) { return k_row_swizzle<RB>(r); });
+            if constexpr (C::kShared) {
+                load_rows(Vp, t, L, vr);
+            } else {
+                store_planes(vpl, L, vr, [](int r) { return v_row_swizzle<RB>(r); });
+            }
+            __syncthreads();
+            const int jb = t * TK + 32 * kw;
+            const bool live = jb <= last_row;                // wave-uniform: not all of the keys in the future
+            floatx16 s = {0};
+            if (live) {
+#pragma unroll
+                for (int cc = 0; cc < C::CH; ++cc) {
+                    const char* a = kpl + krow + swz_chunk(2 * cc + h, sw);
+                    if constexpr (C::kShared) qf[cc].lo = load16(qlo + cc * 1024);
+                    s = mma_planes(Planes{load16(a), load16(a + C::PLANE), load16(a + 2 * C::PLANE)}, qf[cc], s);
+                }
+            }
+            if constexpr (C::kShared) {
+                __syncthreads();
+                store_planes(vpl, L, vr, [](int r) { return v_row_swizzle<RB>(r); });
+                load_rows(Kp, min(t + 1, ntiles - 1), L, kr);
+                __syncthreads();
+            } else {
+                load_rows(Kp, min(t + 1, ntiles - 1), L, kr);
+                load_rows(Vp, min(t + 1, ntiles - 1), L, vr);
+            }
+            if (!live) continue;
+            mask(jb, L, s);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) s[r] = fast_exp2(s[r] * c);
+            float sum = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum += s[r];
+            l_run += sum;
+            typedef short shortx4 __attribute__((ext_vector_type(4)));
+            using lds_ptr = __attribute__((address_space(3))) shortx4*;
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2) {
+                uintx4 pa, pb;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { pa[e] = __float_as_uint(s[8 * s2 + e]); pb[e] = __float_as_uint(s[8 * s2 + 4 + e]); }
+                const Planes pp = split8(pa, pb);
+#pragma unroll
+                for (int db = 0; db < C::ODB; ++db) {
+                    auto operand = [&](int plane) {
+                        const char* a = vpl + plane * C::PLANE + vlane[db] + 16 * s2 * RB;
+                        const uintx2 lo = __builtin_bit_cast(uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)a));
+                        const uintx2 hi = __builtin_bit_cast(uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(a + 8 * RB)));
+                        return uintx4{lo[0], lo[1], hi[0], hi[1]};
+                    };
+                    o[db] = mma_planes(Planes{operand(0), operand(1), operand(2)}, pp, o[db]);
+                }
+            }
+        }
+    };
+    // The same in fp32 products, the offset following the running maximum: for row sums near the ends of the fp32 range, and
+    // for infinities, which the planes do not hold.
+    auto pass_fp32 = [&]() {
+        const Lane L = this_lane();
+        const int i = L.i, h = L.h, qrow = L.qrow, crow = L.crow, ccol = L.ccol;
+        constexpr int FRB = 4 * D;
+        char* const kt = smem;
+        char* const vt = smem + TK * FRB;
+        uintx4 qf[D / 8];
+        {
+            const int qc = min(qrow, kk - 1), pos = tidx ? tidx[qc] : qc;
+            const float* qp = Q + (int64_t)pos * qs2 + 4 * h;
+#pragma unroll
+            for (int cc = 0; cc < D / 8; ++cc) qf[cc] = load16(qp + 8 * cc);
+        }
+#pragma unroll
+        for (int db = 0; db < C::ODB; ++db) o[db] = floatx16{0};
+        m_run = -INFINITY;
+        l_run = 0.f;
+#pragma unroll 1
+        for (int t = 0; t < ntiles; ++t) {
+            __syncthreads();
+#pragma unroll
+            for (int p = 0; p < C::NP; ++p) {
+                const int r = p * C::RPP + crow, sw = k_row_swizzle<FRB>(r);
+                const int64_t src = (int64_t)min(t * TK + r, kk - 1) * D + ccol * 8;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    store16(kt + r * FRB + swz_chunk(2 * ccol + e, sw), load16(Kp + src + 4 * e));
+                    store16(vt + r * FRB + (2 * ccol + e) * 16, load16(Vp + src + 4 * e));
+                }
+            }
+            __syncthreads();
+            const int jb = t * TK + 32 * kw;
+            if (jb > last_row) continue;
+            floatx16 s = {0};
+#pragma unroll
+            for (int cc = 0; cc < D / 8; ++cc)
+                s = mma_frag<float>(load16(kt + (32 * kw + i) * FRB + swz_chunk(2 * cc + h, k_row_swizzle<FRB>(i))), qf[cc], s);
+            mask(jb, L, s);
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+            mx = xhalf_max(mx);
+            const float m_new = mx > m_run + kLazyLog2 / c ? mx : m_run, mc = m_new > -INFINITY ? m_new * c : 0.f;
+            const float alpha = m_run > -INFINITY ? fast_exp2(m_run * c - mc) : 0.f;     // 1 where the maximum stayed
+            if (__any(m_new != m_run)) {
+                l_run *= alpha;
+#pragma unroll
+                for (int db = 0; db < C::ODB; ++db)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+                m_run = m_new;
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                s[r] = fast_exp2(fmaf(s[r], c, -mc));
+                l_run += s[r];
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float* v = reinterpret_cast<const float*>(vt + (32 * kw + acc_row(r, h)) * FRB) + i;
+#pragma unroll
+                for (int db = 0; db < C::ODB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[32 * db], s[r], o[db], 0, 0, 0);
+            }
+        }
+    };
+
+    // over the waves of a query (its keys lie in KS of them), through LDS; the same in all of them
+    float* const meet = reinterpret_cast<float*>(smem);
+    auto over_waves = [&](float v, auto f) {
+        if constexpr (KS == 1) return v;
+        const Lane L = this_lane();
+        __syncthreads();
+        meet[L.tid] = v;
+        __syncthreads();
+        v = meet[qw * 64 + L.lane];
+#pragma unroll
+        for (int x = 1; x < KS; ++x) v = f(v, meet[(qw + x * (NW / KS)) * 64 + L.lane]);
+        return v;
+    };
+    auto plus = [](float x, float y) { return x + y; };
+    pass_planes();
+    const Lane out = this_lane();
+    const int lane = out.lane, h = out.h, qrow = out.qrow;
+    l_run = over_waves(l_run, plus);
+    float probe = 0.f;                                       // NaN if any of the sums is no finite number
+#pragma unroll
+    for (int db = 0; db < C::ODB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) probe = fmaf(o[db][r], 0.f, probe);
+    const float l_once = xhalf_sum(l_run);
+    if (__syncthreads_or(qrow < kk && !(l_once >= kSumLow && l_once <= kSumHigh && probe == 0.f))) {
+        pass_fp32();
+        if constexpr (KS > 1) {                              // to the largest of the offsets (key 0 is visible to every row: finite)
+            const float m_all = over_waves(m_run, [](float x, float y) { return fmaxf(x, y); });
+            const float a = m_run > -INFINITY ? fast_exp2((m_run - m_all) * c) : 0.f;
+            l_run *= a;
+#pragma unroll
+            for (int db = 0; db < C::ODB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[db][r] *= a;
+            l_run = over_waves(l_run, plus);
+        }
+    }
+    if constexpr (KS > 1) {                                  // a wave stores the channels of 4 / KS of a block's four register groups
+        __syncthreads();
+#pragma unroll
+        for (int db = 0; db < C::ODB; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) meet[((w * C::ODB + db) * 16 + r) * 64 + lane] = o[db][r];
+        __syncthreads();
+    }
+    const float inv = 1.f / xhalf_sum(l_run);
+    if (qrow < kk) {
+        const int orow = (out_compact || !tidx) ? qrow : tidx[qrow];
+        float* op = O + (int64_t)orow * D + 4 * h;
+#pragma unroll
+        for (int db = 0; db < C::ODB; ++db)
+#pragma unroll
+            for (int a = 0; a < 4 / KS; ++a) {
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if constexpr (KS == 1) {
+                        v[e] = o[db][4 * a + e];
+                    } else {
+                        const float* x = meet + ((qw * C::ODB + db) * 16 + 4 * (kw * (4 / KS) + a) + e) * 64 + lane;
+                        v[e] = x[0];
+#pragma unroll
+                        for (int y = 1; y < KS; ++y) v[e] += x[y * (NW / KS) * C::ODB * 1024];
+                    }
+                }
+                store_out4<float>(op + 32 * db + 8 * (kw * (4 / KS) + a), v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
+            }
+    }
+}
+
 // ------------------------------------------------------------------ host
 // Whether a head's queries are taken 64 at a time with the keys split over two waves, where both are possible (KS = 0): k kept
 // tokens, BH heads alike, so many live tiles of 128.  bf16, d = 128, rows in place, us, 128 -> 64: k >= 1000: 448 live tiles (32 heads,
 // k = 1759) 44 -> 42, 532 (28 on 4, k = 2346) 57.1 -> 57.4, 576 (2 x 32 on 8, k = 1100) 35 -> 43, 688 (8, k = 11000) 258 -> 268; shorter:
 // 256 (4 x 32, k = 230) 14.7 -> 14.4, 252 (3 x 28 on 4, k = 300) 14.1 -> 12.9, 320 (2 x 32, k = 599) 22.1 -> 22.5, 384 (4 x 32, k = 300) 15.7 -> 18.6.
-__device__ __forceinline__ bool splits_keys(int k, int BH) { return ((k + 127) >> 7) * BH <= (k >= 1000 ? 512 : 288); }
+// fp32 (planes), every token kept: d = 128: 336 (2 x 28 on 4, k = 700) 71.9 -> 54.5, 480 (40, k = 1500) 159 -> 156, 512 (4 x 32 on 8, k = 400)
+// 53 -> 52, 672 (28 on 4, k = 3000) 352 -> 369; d = 64: 512 (32 on 8, k = 2000) 116 -> 105, 896 (28 on 4, k = 4000) 317 -> 317, 728 (k = 3265 of 12 000) 223 -> 205; d = 128: 608 (32 on 8, k = 2400) 267 -> 267.
+template <typename T, int D>
+__device__ __forceinline__ bool splits_keys(int k, int BH) {
+    const int line = Elem<T>::kBytes == 4 ? kPlanesLine<D> : k >= 1000 ? 512 : 288;
+    return ((k + 127) >> 7) * BH <= line;
+}
 
 // Clears the rows of one head at the positions of [p0, p1), up to kFillSpan of them, that are not among its fk kept ones (ft,
 // ascending).
@@ -780,9 +1046,9 @@ template <typename T> struct FlashArgs {
 };
 
 template <typename T, int D, int NW, int QB, int KS>
-__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, 1>::MIN_WGS)) void flash_kept_kernel(FlashArgs<T> args)
+__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::MIN_WGS)) void flash_kept_kernel(FlashArgs<T> args)
 {
-    using C = AttnCfg<T, D, NW, QB, KS == 1 ? 1 : 2>;
+    using C = AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>;
     constexpr int kBM = C::BM;                               // queries per tile
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int block = blockIdx.x;
@@ -824,7 +1090,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, 1>::MIN_WGS)) void 
         kk = max(0, min(kk, a.n));
         const int x = round * rows + (round & 1 ? rows - 1 - at.row : at.row);
         // KS = 0: heads that take 128 queries at a time have half as many tiles, and start with the last one
-        const bool wide = KS == 1 || (KS == 0 && !splits_keys(kk, a.BH));
+        const bool wide = KS == 1 || (KS == 0 && !splits_keys<T, D>(kk, a.BH));
         const int i0 = KS == 0 && wide ? ((kk + 2 * kBM - 1) / (2 * kBM) - 1 - x) * 2 * kBM : (lmax - 1 - x) * kBM;
         if (i0 < 0 || i0 >= kk) return;
         const int32_t* tidx = a.idx ? a.idx + (int64_t)at.set * a.n : nullptr;       // this unit's T
@@ -833,7 +1099,9 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, 1>::MIN_WGS)) void 
         const T* vp = a.Vp + at.b * a.vp0 + at.g * a.vp1;
         T* Oh = a.O + (int64_t)(at.b * a.Hq + at.head) * a.n * D;
         auto queries = [&](auto ks) {
-            flash_queries<T, D, NW, QB, decltype(ks)::value>(q, a.qs2, kp, vp, tidx, Oh, i0, kk, a.npad, a.c, a.out_compact, a.k_in_place, a.v_in_place);
+            constexpr int S = decltype(ks)::value;
+            if constexpr (Elem<T>::kBytes == 4) flash_queries_f32<D, S>(q, a.qs2, kp, vp, tidx, Oh, i0, kk, a.c, a.out_compact);
+            else flash_queries<T, D, NW, QB, S>(q, a.qs2, kp, vp, tidx, Oh, i0, kk, a.npad, a.c, a.out_compact, a.k_in_place, a.v_in_place);
         };
         if constexpr (KS != 0) queries(std::integral_constant<int, KS>{});
         else if (wide) queries(std::integral_constant<int, 1>{});
@@ -886,8 +1154,8 @@ size_t prefill_workspace_bytes(const zipvl_dims& d) {
 // for shorter sequences.  Larger groups take K / V beyond what the caches hold at a time, smaller ones leave too few light tiles under
 // the heavy ones of the next, and an uneven last one runs on alone.  us, groups by bytes of K / V (32 and 8 heads, 42 and 22, ...) -> so:
 // every token kept, 40 heads, n = 4096 195 -> 172; a third kept, 4 x 32 on 8, n = 5000 120 -> 109; d = 64, 2 x 32, n = 6000 59 -> 54;
-// 15 %, 40 heads, n = 16000 97 -> 88; 20 %, 4 x 4, n = 20000 110 -> 105.  fp32 products take 16 times as long as the loads under them: one group
-// (2 x 32 on 8, n = 3000, a third kept 180; in two 211).
+// 15 %, 40 heads, n = 16000 97 -> 88; 20 %, 4 x 4, n = 20000 110 -> 105.  fp32, six products for one, hides the loads: one
+// group (40 heads, n = 4000 829 us, in two 898; a third of 4 x 32 heads, d = 64, n = 3000 113, in groups 125).
 template <typename T>
 static int units_per_group(int units, int G, int tiles) {
     if (Elem<T>::kBytes == 4) return units;
@@ -902,7 +1170,7 @@ template <typename T, int D, int NW, int QB, int KS>
 static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                         float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, void* O, hipStream_t st)
 {
-    using C = AttnCfg<T, D, NW, QB, KS == 1 ? 1 : 2>;
+    using C = AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>;
     static std::atomic<bool> attr_done{false};       // raising the dynamic-LDS cap is idempotent
     if (!attr_done) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kept_kernel<T, D, NW, QB, KS>),
@@ -967,15 +1235,30 @@ static int launch_prefill_t(const void* Q, const void* K, const void* V, const z
     // head (splits_keys; the kernel of both needs no more registers than that of 128): 32 heads, n = 2933, a third kept 29.5 us (128)
     // and 22.0 (64), 22.0 so, all of a set kept 80, 91 and 79; 4 x 32 heads, n = 500, 60 % kept 15.4, 18.5 and 15.3, all 21.4, 27.1 and
     // 22.4.  At d = 64 it would take the kernel of 64 a third of its waves: with up to 60 % kept 64 is
-    // faster or equal (2 x 32 heads, n = 960, 512 tiles 12.5 -> 11.4), with all of a set kept up to 17 % slower.  fp32: a third kept,
-    // 736 tiles 138 -> 136, 1536 241 -> 242; 60 %, 512 tiles 69 -> 60 (n = 500), 736 349 -> 293.
+    // faster or equal (2 x 32 heads, n = 960, 512 tiles 12.5 -> 11.4), with all of a set kept up to 17 % slower.
     const int64_t tiles = (int64_t)((d.n + 127) / 128) * d.B * d.Hq, line = d.n >= 1000 ? 384 : 256;
-    if constexpr (Elem<T>::kBytes == 2 && D == 128)
-        if (tiles > line && tiles <= 2 * line && idx)
-            return launch_flash<T, D, 4, 1, 0>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
-    if (tiles <= line * (idx ? 2 : 1))
-        return launch_flash<T, D, 4, 1, 2>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
-    return launch_flash<T, D, 4, 1, 1>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
+    auto launch = [&](auto waves, auto ks) {
+        return launch_flash<T, D, decltype(waves)::value, 1, decltype(ks)::value>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
+    };
+    constexpr std::integral_constant<int, 0> chosen{};
+    constexpr std::integral_constant<int, 1> whole{};
+    constexpr std::integral_constant<int, 2> half{};
+    constexpr std::integral_constant<int, 4> four{};
+    constexpr std::integral_constant<int, 8> eight{};
+    // fp32.  Fewer tiles than CUs: eight waves on 64 queries, two for every SIMD of a CU that has only this workgroup, take four key blocks of a
+    // tile.  us, 64 queries by four waves -> by eight: 8 on 2, n = 700, d = 128 (48 tiles) 42 -> 39, 8 heads, n = 2933, d = 64 (184) 93 -> 70, 4 heads,
+    // n = 8000 (252) 485 -> 380, 32 on 8, n = 1100 (288) 80 -> 86, 2 x 32 on 8, n = 500, d = 64 (256) 21 -> 24.  Of a set half is taken to be
+    // live; above, the form is chosen by what is (splits_keys), until a quarter kept is past that line too.
+    if constexpr (Elem<T>::kBytes == 4) {
+        const int64_t few = (d.n >= 1000 ? 256 : 128) * (idx ? 2 : 1);
+        if (tiles <= few) return launch(eight, four);
+        if (idx && tiles <= 4 * kPlanesLine<D>) return launch(four, chosen);
+        return tiles <= kPlanesLine<D> ? launch(four, half) : launch(four, whole);
+    } else {
+        if constexpr (D == 128)
+            if (tiles > line && tiles <= 2 * line && idx) return launch(four, chosen);
+        return tiles <= line * (idx ? 2 : 1) ? launch(four, half) : launch(four, whole);
+    }
 }
 
 int launch_sparse_prefill(const void* Q, const void* K, const void* V, const zipvl_dims& d,

@@ -612,6 +612,63 @@ def test_attention_schedule(copies, Hq, Hkv, n, d, dtype, shared):
         assert torch.equal(C[0, h, :k], O[0, h][torch.from_numpy(idx[u, :k]).long().to(DEV)])
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,n,ks", [(1, 97, [97, 33]), (1, 257, [256, 129]), (20, 130, None), (300, 130, None), (100, 161, [100, 1]), (160, 161, [161, 129]), (400, 260, [95, 32])])
+def test_attention_fp32_in_three_planes(d, B, n, ks):
+    """fp32 attention in all its forms (64 queries by eight waves, by four, 128; chosen by the host and by the kept count), at tiles that
+    end early: within 4e-6 of the outputs in 64 bits (2-norm).  A logit of size 5 is a chain of 3 d / 8 sums and rounds by some
+    2^-25 sqrt(3 d / 8) of it each, 1e-6 in all, its weight by as much; without one of the last planes it would be 2e-5."""
+    say(f"attention fp32 in planes d={d} B={B} n={n} k={ks}")
+    w = make_custom(1, 4, 2, n, d, "f32", seed=d + n)
+    Q, K, V = (dev(x, "f32").repeat(B, 1, 1, 1) for x in (w.Q, w.K, w.V))
+    idx = k = None
+    T = [np.arange(n)] * 2
+    if ks:
+        r = np.random.Generator(np.random.PCG64(n))
+        T = [np.sort(r.choice(n, x, replace=False)) for x in ks]
+        rows = np.zeros((2, n), dtype=np.int32)
+        for g in range(2):
+            rows[g, :ks[g]] = T[g]
+        idx, k = torch.from_numpy(rows).to(DEV).repeat(B, 1), torch.tensor(ks, dtype=torch.int32, device=DEV).repeat(B)
+    O = z.zipvl_sparse_prefill(Q, K, V, idx, k, w.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(O, O[:1].expand_as(O))
+    for h in range(4):
+        ref = oz.kept_token_attention(w.Q[0, h], w.K[0, h // 2], w.V[0, h // 2], T[h // 2], w.scale)
+        err = np.linalg.norm(host64(O[0, h]) - ref) / np.linalg.norm(ref)
+        assert err <= 4e-6, f"head {h}: {err:.2e}"
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B", [1, 20, 120])
+def test_attention_fp32_beyond_the_range_of_the_planes(d, B):
+    """Values that three bf16 planes do not hold: a key that no query can see (an infinity, logit -inf), an infinity in V, and one just
+    below the largest fp32 number, which rounds to an infinity; in all three forms."""
+    n, key, inf_row, big_row = 260, 40, 200, 70
+    say(f"attention fp32 beyond the planes d={d} B={B}")
+    w = make_custom(1, 4, 2, n, d, "f32", seed=d)
+    Qh, Kh, Vh = w.Q.copy(), w.K.copy(), w.V.copy()
+    Qh[..., 0] = -np.abs(Qh[..., 0]) - np.float32(0.1)
+    Kh[:, :, key, 0] = np.inf
+    Vh[:, :, inf_row, 3] = np.inf
+    Vh[:, :, big_row, 5] = 3.4e38
+    O = z.zipvl_sparse_prefill(*(dev(x, "f32").repeat(B, 1, 1, 1) for x in (Qh, Kh, Vh)), None, None, w.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(O[1:].isnan(), O[:1].expand_as(O)[1:].isnan()) and torch.equal(O.nan_to_num(), O[:1].expand_as(O).nan_to_num())
+    for h in range(4):
+        q, k, v = (x.astype(np.float64) for x in (Qh[0, h], Kh[0, h // 2], Vh[0, h // 2]))
+        got = host64(O[0, h])
+        k[key], v[inf_row, 3] = 0.0, 0.0
+        s = np.where(np.tril(np.ones((n, n), dtype=bool)), q @ k.T * w.scale, -np.inf)
+        s[:, key] = -np.inf
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        ref = p @ v / p.sum(axis=1, keepdims=True)
+        assert np.all(got[inf_row:, 3] == np.inf)            # rows before it in its block of 32 keys weigh it with 0: no number
+        got[inf_row:, 3], ref[inf_row // 32 * 32:, 3] = 0.0, 0.0
+        got[inf_row // 32 * 32:inf_row, 3] = 0.0
+        assert np.all(np.abs(got - ref) <= ATOL_OUT["f32"] * np.maximum(1.0, np.abs(ref)))
+
+
 def test_attention_compact_output_rows():
     say("attention OUT_COMPACT")
     _attention_case(1, 4, 2, 500, 128, "bf16", [333, 128], seed=7, flags=z.OUT_COMPACT)
