@@ -1668,6 +1668,30 @@ def test_decode_over_quantised_caches_of_unequal_conversations():
     assert not torch.isnan(oa.float()).any()
 
 
+@pytest.mark.parametrize("d,G", [(128, 7), (64, 2)])
+@pytest.mark.parametrize("n", [1, 15, 17, 129, 700])
+def test_decode_of_head_groups_with_an_infinity_in_v(d, G, n):
+    """bf16 groups weigh V with three planes of a weight, of which an infinity makes no number where one is 0: the channel is infinite,
+    of its sign, the others agree with the oracle, for a row in the first, the last and a middle tile."""
+    say(f"decode of groups with an infinity d={d} G={G} n={n}")
+    r = np.random.Generator(np.random.PCG64(n + d))
+    K, V, q = (torch.from_numpy(r.standard_normal(s).astype(np.float32)).bfloat16() for s in ((3, n, d), (3, n, d), (3 * G, d)))
+    rows = [0, n - 1, n // 2]
+    for u in range(3):
+        V[u, rows[u], u] = float("inf") if u else -float("inf")
+    ln = torch.full((3,), n, dtype=torch.int32, device=DEV)
+    o = z.zipvl_decode_attn(q.to(DEV), K.to(DEV), V.to(DEV), ln, d ** -0.5, B=1, Hq=3 * G, Hkv=3)
+    torch.cuda.synchronize()
+    for u in range(3):
+        V[u, rows[u], u] = 0.0
+        for h in range(G):
+            got = host64(o[u * G + h])
+            assert got[u] == (np.inf if u else -np.inf)
+            ref = oz.decode_attention(host64(q[u * G + h]), host64(K[u]), host64(V[u]), n, d ** -0.5)
+            got[u] = ref[u] = 0.0
+            assert np.abs(got - ref).max() <= ATOL_OUT["bf16"]
+
+
 @pytest.mark.parametrize("dtype,d,G", [("bf16", 128, 7), ("bf16", 64, 2), ("f32", 64, 4), ("f32", 128, 8)])
 def test_decode_of_head_groups_at_tile_edges(dtype, d, G):
     """Groups of several heads on the matrix cores (16 cached rows per wave step): lengths on both sides of a tile, of a
