@@ -1151,15 +1151,16 @@ size_t prefill_workspace_bytes(const zipvl_dims& d) {
 }
 
 // KV heads per scheduling group: all of equal size, as near as the KV heads divide to 20 heads of queries, or to 800 tiles of 128
-// for shorter sequences.  Larger groups take K / V beyond what the caches hold at a time, smaller ones leave too few light tiles under
+// for shorter sequences; 1280 of a set, of which some are live (800: 2 x 32 on 8, n = 3000, a third kept 41 us, so 36; 32 heads, n = 6000 55, 48;
+// 4 x 8, n = 5000 59, 52; 2 x 32 on 8, n = 3000, 60 % kept 73, 74.5; 1600: 4 x 32, n = 8192 2 % slower, the others as with 1280).  Larger groups take K / V beyond what the caches hold at a time, smaller ones leave too few light tiles under
 // the heavy ones of the next, and an uneven last one runs on alone.  us, groups by bytes of K / V (32 and 8 heads, 42 and 22, ...) -> so:
 // every token kept, 40 heads, n = 4096 195 -> 172; a third kept, 4 x 32 on 8, n = 5000 120 -> 109; d = 64, 2 x 32, n = 6000 59 -> 54;
 // 15 %, 40 heads, n = 16000 97 -> 88; 20 %, 4 x 4, n = 20000 110 -> 105.  fp32, six products for one, hides the loads: one
 // group (40 heads, n = 4000 829 us, in two 898; a third of 4 x 32 heads, d = 64, n = 3000 113, in groups 125).
 template <typename T>
-static int units_per_group(int units, int G, int tiles) {
+static int units_per_group(int units, int G, int tiles, bool set) {
     if (Elem<T>::kBytes == 4) return units;
-    const double want = units * G / (double)std::max(20, 800 / tiles);
+    const double want = units * G / (double)std::max(20, (set ? 1280 : 800) / tiles);
     int best = 1;
     for (int groups = 2; groups <= units; ++groups)
         if (units % groups == 0 && std::max(groups / want, want / groups) < std::max(best / want, want / best)) best = groups;
@@ -1186,7 +1187,7 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
         const int64_t blocks = (int64_t)slots * BH;
         // full-size output of a sparse call: one more workgroup per (head, span of positions) clears dropped rows
         const int64_t fill = (!out_compact && idx) ? (int64_t)BH * ((d.n + kFillSpan - 1) / kFillSpan) : 0;
-        const int ug = units_per_group<T>(d.B * d.Hkv, G, (d.n + 127) / 128);
+        const int ug = units_per_group<T>(d.B * d.Hkv, G, (d.n + 127) / 128, idx != nullptr);
         const int scan = k && blocks > kScanBlocks && (t_per_batch ? d.B : d.B * d.Hkv) <= kScanSets;
         if (blocks + fill > 0x7fffffffLL) return set_error(ZIPVL_ESHAPE, "sparse_prefill: %lld workgroups exceed the grid limit", (long long)(blocks + fill));
         hipLaunchKernelGGL((flash_kept_kernel<T, D, NW, QB, KS>), dim3((unsigned)(blocks + fill)), dim3(C::NT),
