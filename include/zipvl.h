@@ -183,7 +183,9 @@ int zipvl_share_scores(const float* mass, const float* rank, int B, int Hkv, int
  * O [device] [B,Hq,n,d] contiguous, dtype as the inputs.
  * ws [device] zipvl_workspace_bytes(ZIPVL_OP_SPARSE_PREFILL, dims, 0) bytes, 256-byte aligned.
  * Numerics: accumulation in fp32; probabilities of a bf16 call are rounded to bf16 before they weigh V and before
- * they are summed.  Logits of any finite magnitude are handled: rows whose scaled logits all lie within about
+ * they are summed.  A product of two numbers of an fp32 call is taken as six products of their three bf16 parts, to
+ * 2^-26 of it; a workgroup with a query element outside [2^-100, 2^90] or an output below 2^-80 (0 apart), where parts would
+ * be cut short, repeats its keys in fp32 products.  Logits of any finite magnitude are handled: rows whose scaled logits all lie within about
  * +-44 of zero are exponentiated without an offset, a workgroup with any other row repeats its keys with running
  * maxima (twice the time for that workgroup, the same result up to rounding).  Inputs must be finite.
  */

@@ -58,6 +58,8 @@ constexpr int kScanSets = 512, kScanBlocks = 512;
 constexpr int kSecondRound = 4096;
 constexpr float kLazyLog2 = 8.f;     // slack of the running softmax offset below the running maximum (log2 domain)
 constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p64f;   // row sums of the offset-free pass that need no second pass
+// fp32 in planes: magnitudes (other than 0) of outputs, and of queries, outside which the tiles are repeated in fp32 products
+constexpr float kOutLow = 0x1p-80f, kQueryLow = 0x1p-100f, kQueryHigh = 0x1p90f;
 template <int D> constexpr int kPlanesLine = D == 64 ? 900 : 600;   // fp32: live tiles up to which a head's keys are split (splits_keys)
 constexpr int kSchedAhead = 3;       // LDS operand reads in flight ahead of the consuming MFMA
 
@@ -671,9 +673,16 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
 }
 
 // ---------------------------------------------------------------- fp32
-// Eight fp32 values as three bf16 planes, x = hi + mid + lo exactly (8 significant bits and a sign each, rounded to nearest, so
-// that a plane holds at most 2^-9 of the one before).  An infinity, a NaN or a value that rounds to one leaves a NaN in mid.
+// Eight fp32 values as three bf16 planes, x = hi + mid + lo (8 significant bits and a sign each, rounded to nearest, so
+// that a plane holds at most 2^-9 of the one before): exactly from 2^-109 on; below, the last plane ends at bf16's smallest number and
+// the sum is off by up to 2^-134.  An infinity, a NaN or a value that rounds to one leaves a NaN in mid or lo.
 struct Planes { uintx4 hi, mid, lo; };
+// The smallest magnitude other than 0 of some fp32 values, as 2 |x| - 1 of the bits: 0 is the largest of all.
+struct Least {
+    uint32_t key = ~0u;
+    __device__ __forceinline__ void add(uint32_t x) { key = min(key, 2 * x - 1); }
+    __device__ __forceinline__ bool below(float x) const { return key < 2 * __float_as_uint(x) - 1; }        // x > 0
+};
 // x - the low (high) half of a packed pair, in one instruction
 // (the factors through a register: as a constant 0xBF800000 is taken for the float -1)
 __device__ __forceinline__ float less_half(float x, uint32_t pair, uint32_t factors) {
@@ -710,7 +719,9 @@ __device__ __forceinline__ floatx16 mma_planes(const Planes& a, const Planes& b,
 // K and V rows go through registers into LDS, split there by the workgroup once for all its waves (7 vector instructions for two elements,
 // a quarter of the time of the products of a 32-key tile); the queries' planes stay in registers, the weights are split where they
 // are taken.  Against 64 bits the outputs are nearer than with fp32 products (48 sums in a logit of d = 128 and not 64; 2-norm at 9000 rows
-// 9.4e-7, was 1.14e-6; at 300 6.2e-7, was 7.5e-7).  Bound: large calls by the rate of bf16 products (28 heads on 4, 4485 of 20 000 kept: 610 us,
+// 9.4e-7, was 1.14e-6; at 300 6.2e-7, was 7.5e-7).  That an input of the planes is off by up to 2^-134 where it is small is nothing beside outputs
+// of 2^-80 and more and queries between 2^-100 and 2^90; outside of that (and where a sum is no number) the workgroup repeats its tiles in fp32
+// products.  Bound: large calls by the rate of bf16 products (28 heads on 4, 4485 of 20 000 kept: 610 us,
 // 1.08 PFLOP/s of them), small ones by the chain of a workgroup's tiles: split, product, weights, product, between barriers.  Next rows are
 // requested after a tile's first product, where no operand of it waits for registers.  us, fp32 products -> so, every token kept: 28 heads on 4,
 // n = 3000 601 -> 350; 14 on 2, n = 3000 321 -> 207; d = 64, 32 on 8, n = 2000 161 -> 107; 4 heads, n = 576 26.8 -> 19.0; a third kept,
@@ -765,7 +776,7 @@ __device__ __forceinline__ void flash_queries_f32(const float* __restrict__ Q, i
                 if (jb + acc_row(r, L.h) > L.qrow) s[r] = -INFINITY;
         }
     };
-    auto pass_planes = [&]() {
+    auto pass_planes = [&]() {                               // returns whether its queries are in range
         const Lane L = this_lane();
         const int lane = L.lane, i = L.i, h = L.h, qrow = L.qrow;
         uintx4 kr[C::NP][2], vr[C::NP][2];
@@ -773,14 +784,26 @@ __device__ __forceinline__ void flash_queries_f32(const float* __restrict__ Q, i
         if constexpr (!C::kShared) load_rows(Vp, 0, L, vr);
         Planes qf[C::CH];
         char* const qlo = smem + 3 * C::PLANE + qw * (C::CH * 1024) + lane * 16;     // kShared: the last plane of Q stands in LDS (32 registers)
+        bool in_range;
         {
+            Least least;
+            float most = 0.f;
             const int qc = min(qrow, kk - 1), pos = tidx ? tidx[qc] : qc;
             const float* qp = Q + (int64_t)pos * qs2 + 8 * h;
 #pragma unroll
             for (int cc = 0; cc < C::CH; ++cc) {
-                qf[cc] = split8(load16(qp + 16 * cc), load16(qp + 16 * cc + 4));
+                const uintx4 q0 = load16(qp + 16 * cc), q1 = load16(qp + 16 * cc + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    least.add(q0[e]);
+                    least.add(q1[e]);
+                    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(q0[e]), "v"(q1[e]));
+                }
+                asm volatile("" : "+v"(least.key), "+v"(most));      // now, not with all rows held for it: 248 bytes of scratch in the form of two kinds
+                qf[cc] = split8(q0, q1);
                 if constexpr (C::kShared) store16(qlo + cc * 1024, qf[cc].lo);       // both waves of the queries store the same
             }
+            in_range = !__any(least.below(kQueryLow) || most >= kQueryHigh);
         }
 #pragma unroll
         for (int db = 0; db < C::ODB; ++db) o[db] = floatx16{0};
@@ -851,10 +874,12 @@ __device__ __forceinline__ void flash_queries_f32(const float* __restrict__ Q, i
                 }
             }
         }
+        return in_range;
     };
-    // The same in fp32 products, the offset following the running maximum: for row sums near the ends of the fp32 range, and
-    // for infinities, which the planes do not hold.
-    auto pass_fp32 = [&]() {
+    // The same in fp32 products, for what the planes do not hold: infinities, and what is small enough to be cut short.  maxima: the
+    // offset follows the running maximum, for row sums near the ends of the fp32 range; otherwise it stays 0.
+    auto pass_fp32 = [&](bool maxima) {
+        const float lazy = maxima ? kLazyLog2 / c : INFINITY;
         const Lane L = this_lane();
         const int i = L.i, h = L.h, qrow = L.qrow, crow = L.crow, ccol = L.ccol;
         constexpr int FRB = 4 * D;
@@ -869,7 +894,7 @@ __device__ __forceinline__ void flash_queries_f32(const float* __restrict__ Q, i
         }
 #pragma unroll
         for (int db = 0; db < C::ODB; ++db) o[db] = floatx16{0};
-        m_run = -INFINITY;
+        m_run = maxima ? -INFINITY : 0.f;
         l_run = 0.f;
 #pragma unroll 1
         for (int t = 0; t < ntiles; ++t) {
@@ -896,7 +921,7 @@ __device__ __forceinline__ void flash_queries_f32(const float* __restrict__ Q, i
 #pragma unroll
             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
             mx = xhalf_max(mx);
-            const float m_new = mx > m_run + kLazyLog2 / c ? mx : m_run, mc = m_new > -INFINITY ? m_new * c : 0.f;
+            const float m_new = mx > m_run + lazy ? mx : m_run, mc = m_new > -INFINITY ? m_new * c : 0.f;
             const float alpha = m_run > -INFINITY ? fast_exp2(m_run * c - mc) : 0.f;     // 1 where the maximum stayed
             if (__any(m_new != m_run)) {
                 l_run *= alpha;
@@ -934,18 +959,25 @@ __device__ __forceinline__ void flash_queries_f32(const float* __restrict__ Q, i
         return v;
     };
     auto plus = [](float x, float y) { return x + y; };
-    pass_planes();
+    const bool in_range = pass_planes();
     const Lane out = this_lane();
     const int lane = out.lane, h = out.h, qrow = out.qrow;
     l_run = over_waves(l_run, plus);
     float probe = 0.f;                                       // NaN if any of the sums is no finite number
+    Least least;
 #pragma unroll
     for (int db = 0; db < C::ODB; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) probe = fmaf(o[db][r], 0.f, probe);
+        for (int r = 0; r < 16; ++r) {
+            probe = fmaf(o[db][r], 0.f, probe);
+            least.add(__float_as_uint(o[db][r]));
+        }
     const float l_once = xhalf_sum(l_run);
-    if (__syncthreads_or(qrow < kk && !(l_once >= kSumLow && l_once <= kSumHigh && probe == 0.f))) {
-        pass_fp32();
+    const bool sums = l_once >= kSumLow && l_once <= kSumHigh && probe == 0.f;
+    // outputs may be small because of V or of their weights, and one wave has a part of them
+    const bool stands = sums && in_range && !least.below(kOutLow * fmaxf(l_once, 1.f));
+    if (__syncthreads_or(qrow < kk && !stands)) {
+        pass_fp32(__syncthreads_or(qrow < kk && !sums));
         if constexpr (KS > 1) {                              // to the largest of the offsets (key 0 is visible to every row: finite)
             const float m_all = over_waves(m_run, [](float x, float y) { return fmaxf(x, y); });
             const float a = m_run > -INFINITY ? fast_exp2((m_run - m_all) * c) : 0.f;

@@ -669,6 +669,39 @@ def test_attention_fp32_beyond_the_range_of_the_planes(d, B):
         assert np.all(np.abs(got - ref) <= ATOL_OUT["f32"] * np.maximum(1.0, np.abs(ref)))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B", [1, 20, 120])
+def test_attention_fp32_keeps_its_precision_at_small_and_large_magnitudes(d, B):
+    """Magnitudes at which the last of three bf16 planes ends at bf16's smallest number (2^-133): V small as a whole or in one channel,
+    a channel that lives by one key of weight 2^-121, queries small against large keys and the other way round; every output within 4e-6
+    of its value in 64 bits, channel by channel (as for ordinary values; the weight: an exponent of -121 and its factor are rounded to
+    24 bits, 5e-6 of it).  All three forms."""
+    n, key = 260, 40
+    say(f"attention fp32 at small and large magnitudes d={d} B={B}")
+    w = make_custom(1, 4, 2, n, d, "f32", seed=d + 1)
+    mul = lambda x, f: (x.astype(np.float64) * f).astype(np.float32)
+    one = w.V.copy()
+    one[..., 5] = mul(one[..., 5], 1e-36)
+    Qk, Kk, Vk = w.Q.copy(), w.K.copy(), w.V.copy()
+    Qk, Kk[..., 0] = mul(Qk, 0.05), 0.0
+    Qk[..., 0] = -1.0
+    Kk[:, :, key] = 0.0
+    Kk[:, :, key, 0] = 84.0 / w.scale
+    Vk[..., 7] = 0.0
+    Vk[:, :, key, 7] = 1024.0
+    cases = [(f"V * {f}", w.Q, w.K, mul(w.V, f), 4e-6) for f in (1e-30, 1e-34, 1e-36, 1e-37)]
+    cases += [("one channel of V * 1e-36", w.Q, w.K, one, 4e-6), ("Q * 1e-36, K * 1e36", mul(w.Q, 1e-36), mul(w.K, 1e36), w.V, 4e-6),
+              ("Q * 1e36, K * 1e-36", mul(w.Q, 1e36), mul(w.K, 1e-36), w.V, 4e-6), ("one key of weight 2^-121", Qk, Kk, Vk, 1.2e-5)]
+    for what, Q, K, V, tol in cases:
+        O = z.zipvl_sparse_prefill(*(dev(x, "f32").repeat(B, 1, 1, 1) for x in (Q, K, V)), None, None, w.scale)
+        torch.cuda.synchronize()
+        assert torch.equal(O, O[:1].expand_as(O))
+        for h in range(4):
+            ref = oz.kept_token_attention(Q[0, h].astype(np.float64), K[0, h // 2].astype(np.float64), V[0, h // 2].astype(np.float64), np.arange(n), w.scale)
+            err = np.linalg.norm(host64(O[0, h]) - ref, axis=0) / np.linalg.norm(ref, axis=0)
+            assert err.max() <= tol, f"{what}, head {h}, channel {err.argmax()}: {err.max():.2e}"
+
+
 def test_attention_compact_output_rows():
     say("attention OUT_COMPACT")
     _attention_case(1, 4, 2, 500, 128, "bf16", [333, 128], seed=7, flags=z.OUT_COMPACT)
