@@ -275,7 +275,7 @@ typedef struct zipvl_qtensor {
  * Builds the cache from the prefill K, V [B,Hkv,n,d]: row i of the 4-bit group of unit u is token T_i,
  * row i of the 2-bit group is the i-th token not in T (Eq. (10), ascending position).
  * len_hi[u] = min(k, cap_hi), len_lo[u] = min(n - k, cap_lo) [device, units]; rows beyond a cap are not written.
- * idx, k as written by zipvl_select (strictly ascending; NULL = every token important); flags: 0 or ZIPVL_T_PER_BATCH.
+ * idx, k as written by zipvl_select (in any order here; NULL = every token important); flags: 0 or ZIPVL_T_PER_BATCH.
  * ws [device]: zipvl_workspace_bytes(ZIPVL_OP_QUANTIZE_KV, dims, 0) bytes, 4-byte aligned.  n <= 262144.
  * All eight arrays 16-byte aligned.
  */

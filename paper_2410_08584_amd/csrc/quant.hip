@@ -4,18 +4,69 @@
 // fp16 (scale, zero) pair:
 //   zero = fp16(min), scale = fp16((max - min) * fp32(1 / (2^bits - 1))),
 //   code = clamp(rint((x - zero) / scale), 0, 2^bits - 1)   (0 when scale = 0), all in fp32.
-// One kernel: a workgroup takes 64 tokens, 8 lanes per row, each with 8 (d = 64) or 2 x 8 (d = 128) of its elements.  A token's row in the 4-bit group (rank among the kept tokens) or in the 2-bit
-// group (rank among the others, Eq. (10)) comes from a bisection of T (ascending positions) by every wave, while the
-// rows are on their way.
+// Two kernels.  `kept_masks` turns T (in any order) into a bit per token and, for every 64 tokens, the number of kept ones before them: a token's
+// row in the 4-bit group (rank among the kept tokens) or in the 2-bit group (rank among the others, Eq. (10)).  `quantize_rows`: a
+// workgroup takes 64 tokens, 8 lanes per row, each with 8 (d = 64) or 2 x 8 (d = 128) of its elements.
 #include <type_traits>
 
 #include "launch.h"
 
 namespace zipvl {
 
-constexpr int kQuantMaxTokens = 262144;
+constexpr int kQuantMaxTokens = 262144;      // the bits of a set fit 32 KB of LDS
+constexpr int kSetThreads = 1024;
 constexpr int kQuantRows = 64;               // rows per workgroup: a bit each of a 64-bit mask
 constexpr int kLanes = 8, kPass = 256 / kLanes, kPasses = kQuantRows / kPass;      // lanes per row, rows per pass
+
+// Of one set, in its n words of the workspace: a bit per token (words 0 ... W - 1, W = ceil(n / 32)), then the number of kept tokens before
+// token 64 x for x = 1, 2, ...  Positions outside [0, n) are passed over, a position that comes twice counts once.
+// Latency: the count, the positions, the bits in LDS, their sums; 1.5 to 5 us of a call (4 sets of 60 000 positions 22).  A bisection of T by every wave
+// of quantize_rows takes no launch, and gives two tokens one row wherever T does not ascend.
+__global__ __launch_bounds__(kSetThreads) void kept_masks_kernel(const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt, int n,
+                                                                 uint32_t* __restrict__ masks)
+{
+    extern __shared__ uint32_t words[];
+    __shared__ int wave_total[kSetThreads / 64];
+    const int set = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int blocks = (n + 63) >> 6, W = (n + 31) >> 5;
+    const int32_t* T = idx + (int64_t)set * n;
+    uint32_t* out = masks + (int64_t)set * n;
+    const int kk = max(0, min(kcnt[set], n));
+    for (int i = tid; i < 2 * blocks; i += kSetThreads) words[i] = 0;
+    __syncthreads();
+    constexpr int kAhead = 4;                                // positions of a thread on the way at once
+    for (int i0 = tid; i0 < kk; i0 += kAhead * kSetThreads) {
+        int t[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) t[a] = T[min(i0 + a * kSetThreads, kk - 1)];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+            if (i0 + a * kSetThreads < kk && (unsigned)t[a] < (unsigned)n) atomicOr(&words[t[a] >> 5], 1u << (t[a] & 31));
+    }
+    __syncthreads();
+    for (int i = tid; i < W; i += kSetThreads) out[i] = words[i];
+    // every thread has a run of blocks: their sum, the sums before it in the wave, the waves before
+    const int per = (blocks + kSetThreads - 1) / kSetThreads, x0 = min(tid * per, blocks), x1 = min(x0 + per, blocks);
+    auto count = [&](int x) { return __popc(words[2 * x]) + __popc(words[2 * x + 1]); };
+    int mine = 0;
+    for (int x = x0; x < x1; ++x) mine += count(x);
+    int upto = mine;
+    upto += lane_moved<0x111, 0xF>(upto, 0);
+    upto += lane_moved<0x112, 0xF>(upto, 0);
+    upto += lane_moved<0x114, 0xF>(upto, 0);
+    upto += lane_moved<0x118, 0xF>(upto, 0);
+    upto += lane_moved<0x142, 0xA>(upto, 0);
+    upto += lane_moved<0x143, 0xC>(upto, 0);
+    if (lane == 63) wave_total[w] = upto;
+    __syncthreads();
+    if (x0 == x1) return;
+    int before = upto - mine;
+    for (int x = 0; x < w; ++x) before += wave_total[x];
+    for (int x = x0; x < x1; ++x) {
+        if (x) out[W + x - 1] = before;
+        before += count(x);
+    }
+}
 
 // Minimum and maximum over the 8 lanes of a row, of a row of K and one of V at a time, result in all of them.  One instruction a step
 // and value, where the compiler takes three (a lane permute, a quieting, the minimum); a lane permute may not read what the two
@@ -105,30 +156,29 @@ struct QTensorOut {
     uint8_t* lo_codes; uint32_t* lo_params;
 };
 
-// Bound by vector instructions and memory alike: 807 instructions a wave for 64 elements a lane, 74 % of a SIMD's cycles, under 630 MB in
-// 128 us (4.9 TB/s) at 128 units x 8192 rows of 256 bytes.  With 16 lanes a row, a division near every half and a launch before it that
-// wrote every token's slot: 1246, all of the cycles, 143 + 6 us.  us a call, so -> now: that shape 164 -> 133, 4 x 18432 28.7 -> 18.8,
-// 32 x 2933 29.7 -> 19.7; d = 64, 64 x 9000 60.6 -> 43.5; fp32, 40 x 4097 40.5 -> 34.9.
+// Bound by memory and vector instructions alike: 630 MB at 128 units x 8192 rows of 256 bytes.  us a call (with kept_masks), 16 lanes a row, a
+// division near every half and a launch before that wrote every token's row -> now: that shape 154 -> 131, 4 x 18432 23.4 -> 16.5,
+// 32 x 2933 24.2 -> 15.9; d = 64, 64 x 9000 53.7 -> 37.4; fp32, 40 x 4097 34.7 -> 31.8.
 template <typename T, int D>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(
     const T* __restrict__ K, const T* __restrict__ V,
     int64_t ks0, int64_t ks1, int64_t ks2, int64_t vs0, int64_t vs1, int64_t vs2,
-    const int32_t* __restrict__ idx, const int32_t* __restrict__ kcnt,
+    const uint32_t* __restrict__ masks, const int32_t* __restrict__ kcnt,
     QTensorOut Kq, QTensorOut Vq, int cap_hi, int cap_lo, int32_t* __restrict__ len_hi, int32_t* __restrict__ len_lo,
     int n, int Hkv, int t_per_batch)
 {
     constexpr int P = D / 64;
     const int u = blockIdx.y, b = u / Hkv, g = u - b * Hkv;
     const int ut = t_per_batch ? b : u;
-    const int tid = threadIdx.x, lane = tid & 63, sub = tid % kLanes, rl = tid / kLanes;
+    const int tid = threadIdx.x, sub = tid % kLanes, rl = tid / kLanes;
     int kk = kcnt ? kcnt[ut] : n;
     kk = max(0, min(kk, n));
     if (blockIdx.x == 0 && tid == 0) {
         len_hi[u] = min(kk, cap_hi);
         len_lo[u] = min(n - kk, cap_lo);
     }
-    // All rows of the workgroup are requested at once.  Rows past the end are loaded from the last one and dropped.
     const int j0 = blockIdx.x * kQuantRows, left = n - 1 - j0;
+    // All rows of the workgroup are requested at once.  Rows past the end are loaded from the last one and dropped.
     const T* Kb = K + b * ks0 + g * ks1 + (int64_t)j0 * ks2;
     const T* Vb = V + b * vs0 + g * vs1 + (int64_t)j0 * vs2;
     const T* kl = Kb + rl * ks2;
@@ -147,38 +197,17 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(
             }
         }
     };
-    // The kept tokens before the workgroup's first, and which of its 64 are kept.  The first kept token at or after j0 is entry
-    // [lo, lo + len] of T: 64 probes a round, the first of them requested before the rows and the entries after them.
-    const int32_t* const T_u = idx ? idx + (int64_t)ut * n : nullptr;
-    int lo = 0, len = T_u ? kk : 0, probe = 0;
-    auto step_of = [&]() { return (len + 63) >> 6; };
-    auto ask = [&]() { if (len > kQuantRows) probe = T_u[lo + min((lane + 1) * step_of(), len) - 1]; };
-    ask();
     if (left >= kQuantRows - 1) request(std::true_type{});
     else request(std::false_type{});
-    auto narrow = [&]() {
-        const int step = step_of(), blocks = (len + step - 1) / step;
-        const int below = __popcll(__ballot(lane < blocks && probe < j0));                   // blocks that end before j0
-        lo += min(below * step, len);
-        len = below == blocks ? 0 : min(step, len - below * step);
-    };
-    if (len > kQuantRows) {                                  // apart from the loop: its wait is for the first request alone
-        narrow();
-        while (len > kQuantRows) { ask(); narrow(); }
-    }
-    int before = min(j0, kk);                                                               // without T: the first kk tokens
-    uint64_t mask = ~0ull >> (kQuantRows - max(1, min(kk - j0, kQuantRows)));
-    if (kk <= j0) mask = 0;
-    if (T_u) {
-        const int e0 = lo + lane, e1 = e0 + 64;
-        const int last = max(kk - 1, 0), t0 = T_u[min(e0, last)], t1 = T_u[min(e1, last)];
-        const unsigned b0 = e0 < kk ? t0 - j0 : ~0u, b1 = e1 < kk ? t1 - j0 : ~0u;
-        before = lo + __popcll(__ballot(e0 < kk && t0 < j0));
-        auto bits = [&](unsigned first) {
-            const int mine = (b0 - first < 32u ? 1u << (b0 - first) : 0u) | (b1 - first < 32u ? 1u << (b1 - first) : 0u);
-            return (uint32_t)wave_reduce(mine, 0, [](int x, int y) { return x | y; });
-        };
-        mask = bits(0) | (uint64_t)bits(32) << 32;
+    // which of the workgroup's tokens are kept, and how many before them (without T all are)
+    uint64_t mask = ~0ull;
+    int before = j0;
+    if (masks) {
+        const uint32_t* of_set = masks + (int64_t)ut * n;
+        const int x = blockIdx.x, W = (n + 31) >> 5;
+        mask = of_set[2 * x];
+        if (2 * x + 1 < W) mask |= (uint64_t)of_set[2 * x + 1] << 32;
+        before = x ? of_set[W + x - 1] : 0;
     }
     // of this unit: a row's offset in bytes fits 32 bits
     const int64_t hi0 = (int64_t)u * cap_hi, lo0 = (int64_t)u * cap_lo;
@@ -225,32 +254,40 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(
 }
 static_assert(kPass == 32, "a pass takes one half of the mask");
 
-// Not written by the kernel above; callers of the ABI hold it.
 size_t quantize_workspace_bytes(const zipvl_dims& d) { return (size_t)d.B * d.Hkv * d.n * sizeof(int32_t); }
 
 template <typename T, int D>
 static int launch_quantize_t(const void* K, const void* V, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                              const zipvl_qtensor& Kq, const zipvl_qtensor& Vq, int32_t cap_hi, int32_t cap_lo,
-                             int32_t* len_hi, int32_t* len_lo, int flags, hipStream_t st)
+                             int32_t* len_hi, int32_t* len_lo, int flags, void* ws, hipStream_t st)
 {
     const int units = d.B * d.Hkv;
     const int t_per_batch = (flags & ZIPVL_T_PER_BATCH) ? 1 : 0;
     const QTensorOut kq{(uint8_t*)Kq.hi_codes, (uint32_t*)Kq.hi_params, (uint8_t*)Kq.lo_codes, (uint32_t*)Kq.lo_params};
     const QTensorOut vq{(uint8_t*)Vq.hi_codes, (uint32_t*)Vq.hi_params, (uint8_t*)Vq.lo_codes, (uint32_t*)Vq.lo_params};
+    uint32_t* masks = idx ? (uint32_t*)ws : nullptr;
+    if (masks) {
+        {
+            KernelTimer tm(ZIPVL_K_TOKEN_SLOTS, st);
+            hipLaunchKernelGGL(kept_masks_kernel, dim3(t_per_batch ? d.B : units), dim3(kSetThreads), (d.n + 63) / 64 * 8, st, idx, k, d.n, masks);
+        }
+        const int rc = check_launch("kept_masks");
+        if (rc) return rc;
+    }
     KernelTimer tm(ZIPVL_K_QUANTIZE_ROWS, st);
     hipLaunchKernelGGL((quantize_rows_kernel<T, D>), dim3((d.n + kQuantRows - 1) / kQuantRows, units), dim3(256), 0, st,
         (const T*)K, (const T*)V, d.k_strides[0], d.k_strides[1], d.k_strides[2],
-        d.v_strides[0], d.v_strides[1], d.v_strides[2], idx, k, kq, vq, cap_hi, cap_lo, len_hi, len_lo,
+        d.v_strides[0], d.v_strides[1], d.v_strides[2], masks, k, kq, vq, cap_hi, cap_lo, len_hi, len_lo,
         d.n, d.Hkv, t_per_batch);
     return check_launch("quantize_rows");
 }
 
 int launch_quantize_kv(const void* K, const void* V, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                        const zipvl_qtensor& Kq, const zipvl_qtensor& Vq, int32_t cap_hi, int32_t cap_lo,
-                       int32_t* len_hi, int32_t* len_lo, int flags, hipStream_t st)
+                       int32_t* len_hi, int32_t* len_lo, int flags, void* ws, hipStream_t st)
 {
     if (d.n > kQuantMaxTokens) return set_error(ZIPVL_ESHAPE, "quantize_kv: n = %d exceeds %d", d.n, kQuantMaxTokens);
-#define ZIPVL_ARGS K, V, d, idx, k, Kq, Vq, cap_hi, cap_lo, len_hi, len_lo, flags, st
+#define ZIPVL_ARGS K, V, d, idx, k, Kq, Vq, cap_hi, cap_lo, len_hi, len_lo, flags, ws, st
     if (d.dtype == ZIPVL_BF16) {
         if (d.d == 128) return launch_quantize_t<__bf16, 128>(ZIPVL_ARGS);
         return launch_quantize_t<__bf16, 64>(ZIPVL_ARGS);

@@ -327,7 +327,7 @@ int zipvl_quantize_kv(const void* K, const void* V, const zipvl_dims* dims, cons
     const size_t need = quantize_workspace_bytes(*dims);
     if (!ws || ws_bytes < need) return set_error(ZIPVL_EWORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need, ws ? ws_bytes : (size_t)0);
     if (reinterpret_cast<uintptr_t>(ws) & 3u) return set_error(ZIPVL_EALIGN, "%s: ws is not 4-byte aligned", fn);
-    return launch_quantize_kv(K, V, *dims, idx, k, *Kq, *Vq, cap_hi, cap_lo, len_hi, len_lo, flags, (hipStream_t)stream);
+    return launch_quantize_kv(K, V, *dims, idx, k, *Kq, *Vq, cap_hi, cap_lo, len_hi, len_lo, flags, ws, (hipStream_t)stream);
 }
 
 int zipvl_decode_attn_q(const void* q, const zipvl_qtensor* Kq, const zipvl_qtensor* Vq,

@@ -1368,6 +1368,55 @@ def test_quantize_kv_with_one_set_per_batch_element_and_without_T():
     _check_qcache_against_oracle(allhi, w, dtype, [np.arange(n)] * (B * Hkv), Hkv)
 
 
+@pytest.mark.parametrize("n,k,shared", [(1, 1, False), (2, 1, False), (33, 32, True), (64, 20, False), (65, 64, False), (129, 1, False), (4160, 4097, True),
+                                        (20001, 9000, False), (70001, 5000, True)])
+def test_quantize_kv_takes_positions_in_any_order(n, k, shared):
+    """T shuffled, and shuffled among positions that are none: the cache of T in ascending order, with a workspace of no more bytes than
+    asked for; the ascending one against the oracle's ranks.  At both edges of a block of 64 tokens and of a word of 32, with more kept tokens
+    than are taken at a time, and with more blocks than threads."""
+    say(f"quantize_kv positions in any order n={n} k={k} shared={shared}")
+    B, Hkv, d = 2, 2, 64
+    r = np.random.Generator(np.random.PCG64(n))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    K, V = (torch.randn((B, Hkv, n, d), generator=g, device=DEV) for _ in range(2))
+    sets = B if shared else B * Hkv
+    T = [np.sort(r.choice(n, max(1, k - s), replace=False)) for s in range(sets)]
+    none = [-1, n, n + 70, -2**31, 2**31 - 1][:n - k]
+    flag = z.T_PER_BATCH if shared else 0
+    need = z.workspace_bytes(z.OP_QUANTIZE_KV, z.dims_of(None, K, V, Hq=Hkv))
+
+    def cache(order):
+        rows = [order(t) for t in T]
+        idx = np.zeros((sets, n), dtype=np.int32)
+        for s, t in enumerate(rows):
+            idx[s, :len(t)] = t
+        c = z.QCache(B * Hkv, n, n, d, DEV)
+        for t in (c.K, c.V):
+            for x in t.values():
+                x.zero_()
+        ws = torch.full((need + 64,), 0x5A, dtype=torch.uint8, device=DEV)
+        z.zipvl_quantize_kv(K, V, torch.from_numpy(idx).to(DEV), torch.tensor([len(t) for t in rows], dtype=torch.int32, device=DEV), n, n, flag,
+                            cache=c, ws=ws[:need])
+        torch.cuda.synchronize()
+        assert bool((ws[need:] == 0x5A).all())
+        return c
+
+    plain = cache(lambda t: t)
+    for order in (lambda t: r.permutation(t), lambda t: r.permutation(np.concatenate([t, none]))):
+        other = cache(order)
+        for a, b in ((plain.K, other.K), (plain.V, other.V)):
+            assert all(torch.equal(a[x].view(torch.uint8), b[x].view(torch.uint8)) for x in a)
+    for u in (0, B * Hkv - 1):
+        t = T[u // Hkv if shared else u]
+        qc = oz.quantize_kv(K.view(B * Hkv, n, d)[u].cpu().numpy(), V.view(B * Hkv, n, d)[u].cpu().numpy(), t)
+        for name, x in (("K", plain.K), ("V", plain.V)):
+            for part, rows in (("hi", len(t)), ("lo", n - len(t))):
+                scale, zero = qc[f"{name}_{part}"][1:]
+                params = x[f"{part}_params"][u, :rows].cpu().numpy()
+                assert np.array_equal(params[:, 0], scale) and np.array_equal(params[:, 1], zero)
+
+
 def test_quantised_cache_at_stack_shape_sampled_units():
     say("quantize_kv + decode_attn_q at B4 H32 n8192 (sampled units)")
     from workloads import make_stack_layer_device
