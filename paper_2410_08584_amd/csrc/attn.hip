@@ -1065,14 +1065,14 @@ __device__ __forceinline__ void clear_dropped(T* __restrict__ O, const int32_t* 
 }
 
 // kp, vp: of batch element, KV head.  slots: rows of attention workgroups in the grid, BH each; fill: workgroups after them that clear
-// rows; scan: whether the kept counts are read for the longest head; ug: KV heads of a scheduling group.
+// rows; scan: whether the kept counts are read for the longest head; ug: KV heads of a scheduling group, one more in the first `extra` ones.
 template <typename T> struct FlashArgs {
     const T* Q; int64_t qs0, qs1, qs2;
     const T* Kp; int64_t kp0, kp1;
     const T* Vp; int64_t vp0, vp1;
     const int32_t* idx; const int32_t* kcnt;
     T* O;
-    int n, npad, slots, fill, scan, ug, G, BH, Hq, Hkv;
+    int n, npad, slots, fill, scan, ug, extra, G, BH, Hq, Hkv;
     float c;
     int out_compact, t_per_batch, k_in_place, v_in_place;
 };
@@ -1087,9 +1087,9 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
     // All arguments at once: the compiler would load each where it is first used, 0.2 us apart.
     auto fetch = [](const auto& a) {
         const FlashArgs<T> x = {a.Q, a.qs0, a.qs1, a.qs2, a.Kp, a.kp0, a.kp1, a.Vp, a.vp0, a.vp1, a.idx, a.kcnt, a.O, a.n, a.npad, a.slots, a.fill, a.scan,
-                                a.ug, a.G, a.BH, a.Hq, a.Hkv, a.c, a.out_compact, a.t_per_batch, a.k_in_place, a.v_in_place};
+                                a.ug, a.extra, a.G, a.BH, a.Hq, a.Hkv, a.c, a.out_compact, a.t_per_batch, a.k_in_place, a.v_in_place};
         asm volatile("" :: "s"(x.Q), "s"(x.qs0), "s"(x.qs1), "s"(x.qs2), "s"(x.Kp), "s"(x.kp0), "s"(x.kp1), "s"(x.Vp), "s"(x.vp0), "s"(x.vp1), "s"(x.idx),
-                     "s"(x.kcnt), "s"(x.O), "s"(x.n), "s"(x.npad), "s"(x.fill), "s"(x.ug), "s"(x.G), "s"(x.BH), "s"(x.Hq), "s"(x.Hkv), "s"(x.c),
+                     "s"(x.kcnt), "s"(x.O), "s"(x.n), "s"(x.npad), "s"(x.fill), "s"(x.ug), "s"(x.extra), "s"(x.G), "s"(x.BH), "s"(x.Hq), "s"(x.Hkv), "s"(x.c),
                      "s"(x.out_compact), "s"(x.t_per_batch), "s"(x.k_in_place), "s"(x.v_in_place));
         return x;
     };
@@ -1108,13 +1108,15 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
     }
     const int rows = min(lmax, a0.slots);
     // Workgroup -> (group of KV heads, row, KV head in group, head of the KV head), in that order of significance; heavy (late) query
-    // tiles first inside a group (units_per_group), so that the light tail of one overlaps the heavy start of the next.
+    // tiles first inside a group (scheduling_groups), so that the light tail of one overlaps the heavy start of the next.
     struct Place { int row, b, g, head, set; };
     auto place = [&](const FlashArgs<T>& a) {
-        const int heads = a.ug * a.G;                        // of a group
-        const int grp = block / (heads * rows), r = block - grp * (heads * rows);
+        const int per = a.G * rows, wide = a.extra * (a.ug + 1);      // workgroups of a KV head; KV heads of the larger groups
+        const bool large = block < wide * per;
+        const int from = large ? 0 : wide, size = a.ug + large, heads = size * a.G;
+        const int first = from + (block - from * per) / (heads * rows) * size, r = block - first * per;
         const int row = r / heads, rr = r - row * heads;
-        const int u = grp * a.ug + rr / a.G, b = u / a.Hkv, g = u - b * a.Hkv;
+        const int u = first + rr / a.G, b = u / a.Hkv, g = u - b * a.Hkv;
         return Place{row, b, g, g * a.G + rr % a.G, a.t_per_batch ? b : u};
     };
     auto kept = [&](const FlashArgs<T>& a, int set) { return a.kcnt ? a.kcnt[set] : a.n; };
@@ -1182,21 +1184,32 @@ size_t prefill_workspace_bytes(const zipvl_dims& d) {
     return 2 * (size_t)d.B * d.Hkv * npad * d.d * e;
 }
 
-// KV heads per scheduling group: all of equal size, as near as the KV heads divide to 20 heads of queries, or to 800 tiles of 128
+// Scheduling groups of KV heads: as near as their number comes to 20 heads of queries each, or to 800 tiles of 128
 // for shorter sequences; 1280 of a set, of which some are live (800: 2 x 32 on 8, n = 3000, a third kept 41 us, so 36; 32 heads, n = 6000 55, 48;
 // 4 x 8, n = 5000 59, 52; 2 x 32 on 8, n = 3000, 60 % kept 73, 74.5; 1600: 4 x 32, n = 8192 2 % slower, the others as with 1280).  Larger groups take K / V beyond what the caches hold at a time, smaller ones leave too few light tiles under
 // the heavy ones of the next, and an uneven last one runs on alone.  us, groups by bytes of K / V (32 and 8 heads, 42 and 22, ...) -> so:
 // every token kept, 40 heads, n = 4096 195 -> 172; a third kept, 4 x 32 on 8, n = 5000 120 -> 109; d = 64, 2 x 32, n = 6000 59 -> 54;
 // 15 %, 40 heads, n = 16000 97 -> 88; 20 %, 4 x 4, n = 20000 110 -> 105.  fp32, six products for one, hides the loads: one
 // group (40 heads, n = 4000 829 us, in two 898; a third of 4 x 32 heads, d = 64, n = 3000 113, in groups 125).
+// Where every head has its own K / V, groups of a multiple of 8 heads within a factor of 2 of that (1.5 of a set): workgroups go to the 8 XCDs in turn,
+// and a head's tiles then meet on one L2.  The nearest count (20, 20 and 15 heads) -> so: every token kept, 40 heads, n = 15000 2056 -> 2020 us,
+// 2 x 40, n = 9000 1549 -> 1499, 4 x 40, n = 4200 717 -> 699; 40 % kept, 3 x 40, n = 5000 173 -> 159; a factor of 2 of a set: 40 heads, 30 % of 33000 957 -> 976.
+// Otherwise groups of one size where their number divides the KV heads within sqrt(2) of the wanted one, which some number always is; if not, sizes
+// differ by one (one group -> two: every token kept, 37 heads, n = 9000 855 -> 767, 31, n = 14000 1672 -> 1476, 29, n = 9000 643 -> 594).
 template <typename T>
-static int units_per_group(int units, int G, int tiles, bool set) {
-    if (Elem<T>::kBytes == 4) return units;
+static int scheduling_groups(int units, int G, int tiles, bool set) {
+    if (Elem<T>::kBytes == 4) return 1;
     const double want = units * G / (double)std::max(20, (set ? 1280 : 800) / tiles);
-    int best = 1;
-    for (int groups = 2; groups <= units; ++groups)
-        if (units % groups == 0 && std::max(groups / want, want / groups) < std::max(best / want, want / best)) best = groups;
-    return units / best;
+    auto off = [&](int groups) { return std::max(groups / want, want / groups); };
+    int whole = 0, equal = 1, any = 1;
+    for (int groups = 1; groups <= units; ++groups) {
+        if (off(groups) < off(any)) any = groups;
+        if (units % groups) continue;
+        if (off(groups) < off(equal)) equal = groups;
+        if (G == 1 && units / groups % 8 == 0 && off(groups) <= (set ? 1.5 : 2.0) && (!whole || off(groups) < off(whole))) whole = groups;
+    }
+    if (whole) return whole;
+    return off(equal) <= 1.4143 ? equal : any;
 }
 
 template <typename T, int D, int NW, int QB, int KS>
@@ -1219,14 +1232,14 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
         const int64_t blocks = (int64_t)slots * BH;
         // full-size output of a sparse call: one more workgroup per (head, span of positions) clears dropped rows
         const int64_t fill = (!out_compact && idx) ? (int64_t)BH * ((d.n + kFillSpan - 1) / kFillSpan) : 0;
-        const int ug = units_per_group<T>(d.B * d.Hkv, G, (d.n + 127) / 128, idx != nullptr);
+        const int units = d.B * d.Hkv, groups = scheduling_groups<T>(units, G, (d.n + 127) / 128, idx != nullptr);
         const int scan = k && blocks > kScanBlocks && (t_per_batch ? d.B : d.B * d.Hkv) <= kScanSets;
         if (blocks + fill > 0x7fffffffLL) return set_error(ZIPVL_ESHAPE, "sparse_prefill: %lld workgroups exceed the grid limit", (long long)(blocks + fill));
         hipLaunchKernelGGL((flash_kept_kernel<T, D, NW, QB, KS>), dim3((unsigned)(blocks + fill)), dim3(C::NT),
             C::LDS_BYTES, st, FlashArgs<T>{(const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
                 skip_k ? (const T*)K : Kp, skip_k ? d.k_strides[0] : (int64_t)d.Hkv * npad * D, skip_k ? d.k_strides[1] : (int64_t)npad * D,
                 skip_v ? (const T*)V : Vp, skip_v ? d.v_strides[0] : (int64_t)d.Hkv * npad * D, skip_v ? d.v_strides[1] : (int64_t)npad * D,
-                idx, k, (T*)O, d.n, npad, slots, (int)fill, scan, ug, G, BH, d.Hq, d.Hkv, scale * kLog2e, out_compact, t_per_batch, skip_k, skip_v});
+                idx, k, (T*)O, d.n, npad, slots, (int)fill, scan, units / groups, units % groups, G, BH, d.Hq, d.Hkv, scale * kLog2e, out_compact, t_per_batch, skip_k, skip_v});
     }
     return check_launch("flash_kept");
 }
