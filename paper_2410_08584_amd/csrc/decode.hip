@@ -388,15 +388,15 @@ __device__ __forceinline__ void attend_split(const T* q0, int heads, float c, T*
 #pragma unroll
                 for (int r = 0; r < 4; ++r) p[r] -= __uint_as_float(r & 1 ? h[r >> 1] & 0xFFFF0000u : h[r >> 1] << 16);
             }
+            struct Pairs { uint32_t of[EPL / 2]; } row[4];   // the rows' pieces, two elements each
+#pragma unroll
+            for (int r = 0; r < 4; ++r) row[r] = __builtin_bit_cast(Pairs, cur.v[r]);
 #pragma unroll
             for (int x = 2; x >= 0; --x)
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) {
-                    uint32_t row[4];                         // the pair of elements e is in
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) row[r] = reinterpret_cast<const uint32_t*>(cur.v[r].v)[e >> 1];
                     const uint32_t pick = e & 1 ? 0x07060302u : 0x05040100u;
-                    const uintx2 v = {__builtin_amdgcn_perm(row[1], row[0], pick), __builtin_amdgcn_perm(row[3], row[2], pick)};
+                    const uintx2 v = {__builtin_amdgcn_perm(row[1].of[e >> 1], row[0].of[e >> 1], pick), __builtin_amdgcn_perm(row[3].of[e >> 1], row[2].of[e >> 1], pick)};
                     o[e] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, v), pp[x], o[e], 0, 0, 0);
                 }
         } else {
