@@ -8,7 +8,6 @@ compaction bit-exact.
 """
 import math
 import sys
-import types
 
 import numpy as np
 import pytest
@@ -1611,12 +1610,14 @@ def test_decode_step_one_launch_matches_append_then_attention(dtype, d, Hq, Hkv)
     assert worst <= ATOL_OUT[dtype]
 
 
-@pytest.mark.parametrize("dtype,d,units,G,cap,splits", [("bf16", 128, 4, 7, 3900, 16), ("bf16", 128, 2, 7, 4200, 17), ("f32", 128, 3, 2, 8300, 33), ("bf16", 64, 1, 8, 17000, 64),
-                                                        ("f32", 64, 1, 5, 300, 2), ("bf16", 64, 64, 2, 24700, 16), ("bf16", 64, 32, 3, 49300, 32)])
-def test_decode_step_of_head_groups_with_few_and_many_splits(dtype, d, units, G, cap, splits):
+@pytest.mark.parametrize("dtype,d,units,G,cap,least,splits", [("bf16", 128, 4, 7, 3900, 16, 16), ("bf16", 128, 2, 7, 4200, 17, 17), ("f32", 128, 3, 2, 8300, 33, 33),
+                                                              ("bf16", 64, 1, 8, 17000, 64, 64), ("f32", 64, 1, 5, 300, 2, 2), ("bf16", 64, 64, 2, 24700, 4, 8),
+                                                              ("bf16", 64, 32, 3, 49300, 8, 16), ("bf16", 64, 15, 2, 110700, 18, 36)])
+def test_decode_step_of_head_groups_with_few_and_many_splits(dtype, d, units, G, cap, least, splits):
     """The step that merges its splits itself (16 of them at most) and the one that leaves it to a second launch, also where a long
-    unit has more splits than the others (the last two): empty, short, nearly full and full caches, three steps.  The same bits as
-    append and attention one after the other, whose outputs agree with the oracle."""
+    unit has more splits than the others (the last three: 8 and not 4, 16 and not 8, and in two launches 36 and not 18): empty, short, nearly
+    full and full caches, three steps.  The same bits as append and attention one after the other, whose outputs agree with the oracle.
+    Which form it was shows in the workspace: of a split with rows a state, of two launches a pair of sums of every split besides."""
     say(f"decode_step of groups dtype={dtype} d={d} units={units} G={G} cap={cap}")
     Hq = units * G
     gen = torch.Generator(device=DEV)
@@ -1630,11 +1631,20 @@ def test_decode_step_of_head_groups_with_few_and_many_splits(dtype, d, units, G,
     Kb, Vb, la = Ka.clone(), Va.clone(), torch.tensor(lens, dtype=torch.int32, device=DEV)
     lb = la.clone()
     ws = z.decode_step_workspace(1, Hq, units, cap, d, Ka)
-    assert ws.numel() >= units * G * splits * (d + 2) * 4
+    states = ws[(4 * units + 255) // 256 * 256:].view(torch.int32)
+
+    def splits_of(rows):
+        tiles = (rows + 15) // 16
+        per = max(1, -(-tiles // (least if tiles <= 384 * least else splits)))
+        return max(1, -(-tiles // per))
+
     scale = 1.0 / math.sqrt(d)
     for step in range(3):
         q, kn, vn = rnd(Hq, d) * 2, rnd(units, d), rnd(units, d)
+        states.fill_(-1)
         oa = z.zipvl_decode_step(q, Ka, Va, la, kn, vn, scale, B=1, Hq=Hq, Hkv=units, ws=ws)
+        held = sum(splits_of(min(cap, n + 1)) for n in lens)
+        assert int((states != -1).sum()) == G * (d * held + 2 * (units * splits if splits > 16 else held))
         z.zipvl_kv_append(Kb, Vb, lb, kn, vn, B=1, Hkv=units)
         ob = z.zipvl_decode_attn(q, Kb, Vb, lb, scale, B=1, Hq=Hq, Hkv=units)
         torch.cuda.synchronize()
