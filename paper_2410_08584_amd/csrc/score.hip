@@ -15,7 +15,7 @@
 // whole kernel: the probe rows' fragments stay in its registers, and the key
 // fragments of a tile come from LDS.  With few tasks (one query head per KV
 // head) several waves share a task and split the key blocks of a stage; more
-// tasks are dealt to several workgroups in pass 1 (task_groups), and taken in
+// tasks are dealt to several workgroups in pass 1 (row_stats_plan), and taken in
 // rounds, the chunk streamed once for each, in pass 2.
 // Pass 1 computes K Q^T (lane = probe column: row statistics stay in the
 // lane); pass 2 computes Q K^T (lane = key column: column sums stay in the
@@ -388,15 +388,35 @@ size_t score_workspace_bytes(const zipvl_dims& d, int m) {
 // where the two cost the same: 28 heads on 4, m = 64 n = 13000, 14 on 2 n = 33000).  us, all tasks of a KV head in one workgroup of 16 waves, in
 // rounds of 16 where there are more -> 8 a workgroup, 4 a workgroup: 28 heads on 4, m = 64, n = 4096 22.4 -> 21.5, 20.0; n = 18432 37.3 -> 35.3, 36.4;
 // m = 128 n = 4096 39.5 -> 30.3, 29.8; n = 18432 69.4 -> 62.1, 62.0; 32 on 2, n = 4096 40.8 -> 29.1, 26.7; 32 on 8, n = 4096 21.0 (8), 19.7.
+// fp32 is bound by its products: there the tiles that the busiest SIMD takes decide first (7 of 8 waves with a task leave one SIMD with fewer),
+// and chunks may be twice as many, taken in two turns, where one turn leaves slots empty (kTurnTiles: a turn costs 4.5 us at d = 64 and
+// 10 at 128, as long as so many tiles).  28 heads on 4, m = 128, fp32, 16 waves in rounds, bytes
+// alone -> so: batch 1 n = 33000 546, 554, 531; 3, n = 12000 572, 606, 566; 4, n = 12000 741, 764, 742; d = 64, batch 4, n = 25000 760, 802, 762.
 constexpr double kKeyCost = 1.2;
+constexpr int kTurnTiles = 5;
 
-static int task_groups(int NT, int units, int nblk, int row_bytes, int waves2) {
+struct RowStatsPlan { int groups, bpc; };                        // groups of tasks, 32-key blocks of a chunk
+
+static RowStatsPlan row_stats_plan(int NT, int units, int nblk, int row_bytes, int waves2, bool products) {
     const int full = (NT + 7) / 8, half = (NT + 3) / 4, slots = resident_slots(8), cus = resident_slots(16);
-    auto cost = [&](int groups) {
-        const int bpc = blocks_per_chunk(nblk, units * groups, slots), chunks = (nblk + bpc - 1) / bpc;
-        return kKeyCost * groups * units * nblk * 32.0 * row_bytes / cus + (double)chunks * NT * 32 * sizeof(float2) * (16 / waves2);
+    auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    auto plan = [&](int groups, int turns) { return RowStatsPlan{groups, blocks_per_chunk(nblk, units * groups, turns * slots)}; };
+    auto bytes = [&](const RowStatsPlan& p) {
+        return kKeyCost * p.groups * units * nblk * 32.0 * row_bytes / cus + (double)ceil_div(nblk, p.bpc) * NT * 32 * sizeof(float2) * (16 / waves2);
     };
-    return cost(half) < cost(full) ? half : full;
+    auto tiles = [&](const RowStatsPlan& p) {
+        const int64_t tpg = ceil_div(NT, p.groups), shared = std::max<int64_t>(1, 8 / tpg), wgs = (int64_t)units * p.groups * ceil_div(nblk, p.bpc);
+        const int64_t turns = ceil_div(wgs, slots);
+        return turns * ceil_div(std::min<int64_t>(wgs, slots), cus) * ceil_div(tpg * shared, 4) * ceil_div(p.bpc, shared) + (turns - 1) * kTurnTiles;
+    };
+    RowStatsPlan best = plan(full, 1);
+    auto look_at = [&](const RowStatsPlan& p) {
+        const int64_t more = products ? tiles(p) - tiles(best) : 0;
+        if (more < 0 || (more == 0 && bytes(p) < bytes(best))) best = p;
+    };
+    look_at(plan(half, 1));
+    if (products && half > 1) look_at(plan(half, 2));            // (the workspace has room for slots / units chunks)
+    return best;
 }
 
 template <typename T, int D, int PASS, int NWV>
@@ -424,8 +444,9 @@ static int launch_score_w(const void* Q, const void* K, const zipvl_dims& d, con
     if (rc) return rc;
     rc = reserve_lds<T, D, 2, NW2>();
     if (rc) return rc;
-    const int nblk1 = (n_eff + 31) / 32, groups = task_groups(NT, units, nblk1, D * (int)sizeof(T), NW2), tpg = (NT + groups - 1) / groups;
-    const int bpc1 = blocks_per_chunk(nblk1, units * groups, resident_slots(8)), nsplit = (nblk1 + bpc1 - 1) / bpc1;
+    const int nblk1 = (n_eff + 31) / 32;
+    const RowStatsPlan plan = row_stats_plan(NT, units, nblk1, D * (int)sizeof(T), NW2, Elem<T>::kBytes == 4);
+    const int groups = plan.groups, tpg = (NT + groups - 1) / groups, bpc1 = plan.bpc, nsplit = (nblk1 + bpc1 - 1) / bpc1;
     const int nblk2 = (d.n + 31) / 32, bpc2 = blocks_per_chunk(nblk2, units, resident_slots(NW2)), chunks2 = (nblk2 + bpc2 - 1) / bpc2;
     {
         KernelTimer tm(ZIPVL_K_SCORE_ROWSTATS, st);

@@ -318,10 +318,12 @@ def test_scores_match_oracle(case):
 
 
 @pytest.mark.parametrize("dtype,d,G,Hkv,n,m", [("bf16", 128, 5, 1, 90, 40), ("bf16", 128, 8, 2, 40, 40), ("f32", 64, 9, 1, 1000, 64), ("bf16", 64, 11, 1, 700, 96),
-                                               ("bf16", 128, 16, 1, 150, 128), ("f32", 128, 16, 1, 500, 65), ("bf16", 128, 8, 1, 17000, 33), ("bf16", 64, 13, 1, 9000, 128)])
+                                               ("bf16", 128, 16, 1, 150, 128), ("f32", 128, 16, 1, 500, 65), ("bf16", 128, 8, 1, 17000, 33), ("bf16", 64, 13, 1, 9000, 128),
+                                               ("f32", 64, 7, 16, 2880, 128), ("f32", 128, 5, 60, 360, 128), ("f32", 128, 7, 2, 500, 128)])
 def test_scores_of_wide_groups(dtype, d, G, Hkv, n, m):
     """More (head, block of 32 probes) tasks than one workgroup of the row statistics takes, 8 or 4 a workgroup, in even and uneven
-    shares, over few and many keys: the oracle's scores with the bound above, for probes over the whole sequence."""
+    shares, over few and many keys, in one turn of the chip and (fp32, 16 and 60 KV heads) in two: the oracle's scores with the bound above, for
+    probes over the whole sequence."""
     say(f"scores of wide groups dtype={dtype} d={d} G={G} n={n} m={m}")
     r = np.random.Generator(np.random.PCG64(81))
     pp = np.sort(np.append(r.choice(n - 1, m - 1, replace=False), n - 1)).astype(np.int32)
