@@ -56,6 +56,12 @@ constexpr int kScanSets = 512, kScanBlocks = 512;
 // taken in a second round).  us, a row for every tile -> so: 4 x 32 heads, n = 8192, a quarter kept 209 -> 204, half kept 611 -> 612;
 // 2 x 32, n = 12000, 15 % kept 92.6 -> 90.4; with half as many workgroups 207, 639 and 89.9.
 constexpr int kSecondRound = 4096;
+// Rows of workgroups from which a group of a multiple of 8 heads of a set, each with its own K / V, is turned by a head every kTurnRows rows.
+// Workgroups go to the 8 XCDs in turn, so that a head is one XCD's, and heads keep different numbers of tokens.  us, every row alike -> so:
+// 15 % more and less than half kept, 2 x 4 heads, n = 28000 407 -> 370, 4 x 4, d = 64 504 -> 437, 32, n = 25000, 40 % 838 -> 793, 3 x 8, n = 25000, 40 %
+// 613 -> 590; by a head every row 374, 460, 833, 644; short ones lose the rows of a head that share its K / V on the way: 4 x 32, n = 8192, a
+// quarter 195 -> 214, 32, n = 2933 22 -> 25 by a head every row.
+constexpr int kTurnFrom = 64, kTurnRows = 4;
 constexpr float kLazyLog2 = 8.f;     // slack of the running softmax offset below the running maximum (log2 domain)
 constexpr float kSumLow = 0x1p-64f, kSumHigh = 0x1p64f;   // row sums of the offset-free pass that need no second pass
 // fp32 in planes: magnitudes (other than 0) of outputs, and of queries, outside which the tiles are repeated in fp32 products
@@ -1115,7 +1121,9 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
         const bool large = block < wide * per;
         const int from = large ? 0 : wide, size = a.ug + large, heads = size * a.G;
         const int first = from + (block - from * per) / (heads * rows) * size, r = block - first * per;
-        const int row = r / heads, rr = r - row * heads;
+        const int row = r / heads;
+        int rr = r - row * heads;
+        if (rows >= kTurnFrom && a.kcnt && a.G == 1 && heads % 8 == 0) rr = (rr + row / kTurnRows) % heads;
         const int u = first + rr / a.G, b = u / a.Hkv, g = u - b * a.Hkv;
         return Place{row, b, g, g * a.G + rr % a.G, a.t_per_batch ? b : u};
     };
@@ -1191,14 +1199,20 @@ size_t prefill_workspace_bytes(const zipvl_dims& d) {
 // every token kept, 40 heads, n = 4096 195 -> 172; a third kept, 4 x 32 on 8, n = 5000 120 -> 109; d = 64, 2 x 32, n = 6000 59 -> 54;
 // 15 %, 40 heads, n = 16000 97 -> 88; 20 %, 4 x 4, n = 20000 110 -> 105.  fp32, six products for one, hides the loads: one
 // group (40 heads, n = 4000 829 us, in two 898; a third of 4 x 32 heads, d = 64, n = 3000 113, in groups 125).
-// Where every head has its own K / V, groups of a multiple of 8 heads within a factor of 2 of that (1.5 of a set): workgroups go to the 8 XCDs in turn,
-// and a head's tiles then meet on one L2.  The nearest count (20, 20 and 15 heads) -> so: every token kept, 40 heads, n = 15000 2056 -> 2020 us,
-// 2 x 40, n = 9000 1549 -> 1499, 4 x 40, n = 4200 717 -> 699; 40 % kept, 3 x 40, n = 5000 173 -> 159; a factor of 2 of a set: 40 heads, 30 % of 33000 957 -> 976.
+// One group of up to 40 heads (32 of a set) where the tiles are few.  us, in two -> one: every token kept, d = 64, 32 heads, n = 5000 132 -> 126; a quarter
+// kept, 32 on 8, n = 8000 57.3 -> 52.1; past the lines: half kept, 32 on 8, n = 11 098 151 -> 161, 40, n = 6326 131 -> 138, 3 x 32 on 8, n = 2538 70 -> 75,
+// every token kept, 2 x 32 on 8, n = 2239 96 -> 101.
+// Every token kept and own K / V for every head: groups of a multiple of 8 heads within a factor of 2 of that: workgroups go to the 8 XCDs in turn,
+// and a head's tiles then meet on one L2.  The nearest count (20, 20 and 20 heads) -> so: 40 heads, n = 15000 2056 -> 2020 us, 2 x 40, n = 9000
+// 1549 -> 1499, 4 x 40, n = 4200 717 -> 699; of a set, whose heads keep different numbers: 2 x 40, half kept, n = 10 180 343 -> 360.
 // Otherwise groups of one size where their number divides the KV heads within sqrt(2) of the wanted one, which some number always is; if not, sizes
 // differ by one (one group -> two: every token kept, 37 heads, n = 9000 855 -> 767, 31, n = 14000 1672 -> 1476, 29, n = 9000 643 -> 594).
+constexpr int64_t kOneGroup = 3600, kOneGroupOfSet = 2048;
+
 template <typename T>
 static int scheduling_groups(int units, int G, int tiles, bool set) {
-    if (Elem<T>::kBytes == 4) return 1;
+    const int64_t heads = (int64_t)units * G;
+    if (Elem<T>::kBytes == 4 || (heads <= (set ? 32 : 40) && heads * tiles <= (set ? kOneGroupOfSet : kOneGroup))) return 1;
     const double want = units * G / (double)std::max(20, (set ? 1280 : 800) / tiles);
     auto off = [&](int groups) { return std::max(groups / want, want / groups); };
     int whole = 0, equal = 1, any = 1;
@@ -1206,7 +1220,7 @@ static int scheduling_groups(int units, int G, int tiles, bool set) {
         if (off(groups) < off(any)) any = groups;
         if (units % groups) continue;
         if (off(groups) < off(equal)) equal = groups;
-        if (G == 1 && units / groups % 8 == 0 && off(groups) <= (set ? 1.5 : 2.0) && (!whole || off(groups) < off(whole))) whole = groups;
+        if (!set && G == 1 && units / groups % 8 == 0 && off(groups) <= 2 && (!whole || off(groups) < off(whole))) whole = groups;
     }
     if (whole) return whole;
     return off(equal) <= 1.4143 ? equal : any;

@@ -575,10 +575,10 @@ def test_attention_query_tile_chosen_by_kept_tokens(d, n, gain):
 
 @pytest.mark.parametrize("copies,Hq,Hkv,n,d,dtype,shared", [(8, 64, 64, 1100, 64, "bf16", False), (74, 56, 8, 129, 128, "bf16", True), (40, 64, 16, 257, 64, "f32", False),
                                                            (5, 40, 10, 1030, 128, "bf16", True), (3, 14, 7, 700, 128, "bf16", False),
-                                                           (71, 3, 3, 1100, 64, "bf16", False), (31, 14, 7, 700, 128, "bf16", False)])
+                                                           (71, 3, 3, 1100, 64, "bf16", False), (31, 14, 7, 700, 128, "bf16", False), (2, 8, 8, 8300, 64, "bf16", False)])
 def test_attention_schedule(copies, Hq, Hkv, n, d, dtype, shared):
     """Which workgroup takes which tile: more tiles than workgroups (the first three: 9, 2 and 3 tiles of 128 a head), more sets than a
-    workgroup reads the counts of (the third), several scheduling groups (the last two: of 107 and 106, 109 and 108 KV heads), a KV head without a token, heads that keep all; one set per
+    workgroup reads the counts of (the third), several scheduling groups (of 107 and 106, 109 and 108 KV heads), heads that go round the XCDs (the last), a KV head without a token, heads that keep all; one set per
     KV head and one per batch element, full and compact outputs.  Repeated batch elements give the same bits, the first one agrees
     with the oracle."""
     say(f"attention schedule {copies}x{Hq}/{Hkv} n={n} d={d} {dtype} shared={shared}")
