@@ -248,7 +248,7 @@ int zipvl_decode_attn_static(const void* q, const void* Kc, const void* Vc, cons
  * first 4 * B * Hkv bytes are per-unit arrival counters: they must be zero before the first call that
  * uses this workspace, every call leaves them zero, and nothing else may write there between calls
  * (two calls that overlap on one workspace race).  One launch; two (attention with the new row, then the merge of its
- * parts) for groups of heads over caches that are cut into more than 16; groups larger than 8 query heads per KV head
+ * parts) for groups of heads over caches that are cut into more than 16 (24 for bf16 at d = 64); groups larger than 8 query heads per KV head
  * run the separate kernels inside this call.
  */
 int zipvl_decode_step(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,

@@ -203,11 +203,12 @@ template <int GT> constexpr int kDecWaves = kDecMfma<GT> ? 8 : 4;        // wave
 constexpr int kDecTile = 16;          // cached rows per wave step
 // Tiles of a split that is called long (SplitRule).  Such a split takes about 85 us (one head, 3072 rows) and 100 us (groups,
 // 6144 rows) on one workgroup; for shorter ones more workgroups mostly add launching and merging.
+constexpr int kDecLongOne = 192, kDecLongGroups = 384;
 // Splits of a group of heads that the step kernel merges itself.  us, one launch and two: 8 x 32 heads on 8, 4 splits 26.7, 28.0; 8 x 28
 // on 4, 8 splits 13.6, 14.8; 4 x 28 on 4, 16 splits 19.3, 20.2; 28 on 4, 41 splits 14.4, 12.2; 14 on 2, 17 splits 11.6, 10.9.  With room for 32
-// states in registers 14.0, 20.1 and 11.2.
-constexpr int kMergeSplits = 16;
-constexpr int kDecLongOne = 192, kDecLongGroups = 384;
+// states in registers 14.0, 20.1 and 11.2.  bf16 at d = 64, half the bytes: 28 on 4, 17 splits 9.0, 10.5, 22 splits 9.4, 10.5 (two launches cost the
+// host more than the GPU there), 47 splits 11.1, 9.7; fp32, 17 splits 11.2, 10.4.
+template <typename T, int D> constexpr int kMergeSplits = D == 64 && sizeof(T) == 2 ? 24 : 16;
 
 template <typename T, int EPL> struct alignas(sizeof(T) * EPL > 16 ? 16 : sizeof(T) * EPL) RawChunk { T v[EPL]; };
 
@@ -522,13 +523,13 @@ constexpr float kNoRows = -1.f;                              // instead of a sum
 // One wave per head, all of at most kMergeSplits states on the way at once; the sums are those of HeadStates, bit for bit.
 template <typename T, int D>
 __device__ __forceinline__ void merge_few_states(const PartialOut& po, int head, int nsplit, T* __restrict__ out) {
-    constexpr int EPL = D / 64;
+    constexpr int EPL = D / 64, kMost = kMergeSplits<T, D>;
     const int lane = threadIdx.x & 63;
     HeadStates<D, 512, true> x;
-    float v[kMergeSplits][EPL];
+    float v[kMost][EPL];
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(po.o, 0, 0x7FFFFFFF, 0x00020000);
 #pragma unroll
-    for (int s = 0; s < kMergeSplits; ++s)
+    for (int s = 0; s < kMost; ++s)
         if (s < nsplit) {
             const int at = (head * po.nsplit + s) * (D * 4) + lane * (EPL * 4);
             if constexpr (EPL == 2) {
@@ -539,10 +540,10 @@ __device__ __forceinline__ void merge_few_states(const PartialOut& po, int head,
         }
     x.fetch_sums(po, head, nsplit);
     const float w = x.weight();
-    static_assert(kMergeSplits <= HeadStates<D, 512, true>::kGroups, "one state in each partial sum");
+    static_assert(kMost <= HeadStates<D, 512, true>::kGroups, "one state in each partial sum");
     float acc[EPL] = {};
 #pragma unroll
-    for (int s = 0; s < kMergeSplits; ++s)
+    for (int s = 0; s < kMost; ++s)
         if (s < nsplit) {
             const float ws = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), s));
 #pragma unroll
@@ -1266,7 +1267,7 @@ static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len,
     }
     const float c = scale * kLog2e;
     const SplitRule rule = split_rule(d, cap);
-    const bool one_launch = G == 1 || rule.most <= kMergeSplits;
+    const bool one_launch = G == 1 || rule.most <= kMergeSplits<T, D>;
     {
         KernelTimer tm(ZIPVL_K_DECODE_STEP, st);
 #define ZIPVL_STEP(GT, MERGE)                                                                        \
