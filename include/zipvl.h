@@ -187,7 +187,7 @@ int zipvl_share_scores(const float* mass, const float* rank, int B, int Hkv, int
  * 2^-26 of it; a workgroup with a query element outside [2^-100, 2^90] or an output below 2^-80 (0 apart), where parts would
  * be cut short, repeats its keys in fp32 products.  Logits of any finite magnitude are handled: rows whose scaled logits all lie within about
  * +-44 of zero are exponentiated without an offset, a workgroup with any other row repeats its keys with running
- * maxima (twice the time for that workgroup, the same result up to rounding).  Inputs must be finite.
+ * maxima (twice the time for that workgroup, up to three times for fp32; the same result up to rounding).  Inputs must be finite.
  */
 int zipvl_sparse_prefill(const void* Q, const void* K, const void* V, const zipvl_dims* dims,
                          const int32_t* idx, const int32_t* k, float softmax_scale, int flags,

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
 
         if (PASS == 2) {
             // Merge the chunk statistics of this task's 32 rows: lane = (pair of rows, quarter of the chunks), 16 bytes a load, up to
-            // eight in flight, one exponential per statistic.  28 heads on 4, n = 18432: a workgroup reads 229 KB of them, the
+            // eight in flight, one exponential per statistic.  28 heads on 4, n = 18432: a workgroup reads 229 KB of them (14 tasks, 64 chunks), the
             // prologue took 9.9 of pass 2's 23 us with 8-byte loads and pairwise merges, 7.0 so (a CU takes in some 40 GB/s).
             const floatx4* p = reinterpret_cast<const floatx4*>(partial + (int64_t)bh * nsplit * np + nb * 32);   // wave-uniform base; the rest fits 32 bits (host check)
             const int pr = lane & 15, cg = lane >> 4;
