@@ -983,6 +983,27 @@ def test_all_rows_scores_at_cfg2_shape_against_sampled_columns():
         assert_scores_close(rank[u].cpu().numpy().astype(np.float64)[None], ro, spec.dtype, "rank")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,n,d,dtype", [(4, 26, 26, 2560, 128, "bf16"), (4, 28, 4, 2561, 64, "bf16"), (4, 28, 4, 2559, 128, "bf16"),
+                                                (2, 20, 4, 2051, 128, "bf16"), (1, 16, 4, 2049, 64, "f32"), (1, 41, 41, 2048, 128, "bf16")])
+def test_all_rows_scores_of_many_blocks(B, Hq, Hkv, n, d, dtype):
+    """32 and 64 rows a wave on both sides of the line between them, blocks dealt in turned rounds and not, against a softmax in float64."""
+    say(f"score_all_rows B={B} Hq={Hq} Hkv={Hkv} n={n} d={d} {dtype}")
+    w = make_custom(B, Hq, Hkv, n, d, dtype, seed=75, m=64)
+    Q, K = dev(w.Q, dtype), dev(w.K, dtype)
+    mass, rank = z.zipvl_score_all_rows(Q, K, w.scale)
+    G = Hq // Hkv
+    hidden = torch.ones((n, n), dtype=torch.bool, device=DEV).triu(1)
+    for b, g in {(0, 0), (B - 1, Hkv - 1), (0, Hkv // 2)}:
+        a = torch.zeros((n,), dtype=torch.float64, device=DEV)
+        for h in range(g * G, (g + 1) * G):
+            logits = Q[b, h].double() @ K[b, g].double().t().contiguous() * w.scale
+            a += torch.softmax(logits.masked_fill_(hidden, -math.inf), dim=1).sum(dim=0)
+        a /= G
+        u = b * Hkv + g
+        assert_scores_close(host64(mass[u]), (a / n).cpu().numpy(), dtype, "mass")
+        assert_scores_close(host64(rank[u]), (a / torch.arange(n, 0, -1, device=DEV)).cpu().numpy(), dtype, "rank")
+
+
 # ------------------------------------------------------------------ one T per layer
 def test_share_scores_bit_exact():
     say("share_scores")
