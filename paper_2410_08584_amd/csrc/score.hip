@@ -1,15 +1,15 @@
 // Probe-token importance scores (supplementary Eq. (A); Eq. (6), Eq. (8);
 // Algorithm 1 steps 2-4).  The m x n probe attention matrix is never stored:
-//   pass 1  row statistics: for each (head, probe row) the maximum and the
-//           exp-sum of the masked, scaled logits over the chunk of keys a
-//           workgroup owns (one partial pair per row and chunk);
-//   pass 2  merges the partial pairs of its rows into one exponent offset per
+//   pass 1  row statistics: for each (head, probe row) the sum of exp2 of the
+//           masked, scaled logits over the chunk of keys a workgroup owns (one
+//           number per row and chunk, or two where it is out of range);
+//   pass 2  merges the numbers of its rows into one exponent offset per
 //           row (in its prologue: no launch in between), recomputes the
 //           logits, normalises them with that offset, sums them down the probe
 //           rows and over the query heads of the group, and writes mass / rank.
 // Both passes share one kernel body.  A workgroup owns a chunk of keys of one
-// KV head and streams it through LDS in stages of 32 KiB, loaded straight from
-// global memory (no staging registers), double buffered.  The work of a stage
+// KV head and streams it through LDS in stages of 16 or 32 KiB, loaded straight from
+// global memory (no staging registers), three stages ahead.  The work of a stage
 // is a grid of 32-key x 32-probe tiles, one 32x32 MFMA accumulator each.  A
 // wave owns one (query head, block of 32 probe rows) - its "task" - for the
 // whole kernel: the probe rows' fragments stay in its registers, and the key
@@ -23,6 +23,7 @@
 // the result does not depend on scheduling).
 #include <algorithm>
 #include <atomic>
+#include <cfloat>
 #include <type_traits>
 
 #include "launch.h"
@@ -31,8 +32,16 @@
 namespace zipvl {
 
 constexpr int kMaxGroup = 16;
+constexpr int kSumStages = 8;               // stages whose scores are written at a time
 constexpr int kStageBufs = 4;               // stage buffers in LDS: three stages are in flight while one is worked on
 
+// What bounds it: long chunks of one query head per KV head memory; the others a chain (positions, probe rows and statistics, first keys: 4 to 7 of
+// the 12 to 19 us of a launch) and then about 600 cycles a tile, products and vector work one after the other (done between the products of the
+// next tile instead, as in the exact scores, a tile took 15 % longer: four waves a SIMD, a barrier every one to four tiles).  us, rows gathered by
+// lanes behind three stages of keys, pairs of statistics, scores made by the last waves -> now: 40 heads, n = 4096, 64 recent and 64 random
+// probes 37.2 -> 31.8; 28 on 4, n = 18432 35.0 -> 32.6; 32, n = 3072 19.7 -> 17.0; 32, n = 20000, m = 128 78.6 -> 67.5; 28 on 4, fp32, n = 12000,
+// m = 128 224 -> 201; 4, fp32, d = 64, n = 576 14.4 -> 12.4; bound by memory, 40, n = 18432 67.4 -> 67.0; 28 tasks at d = 64, n = 4096 22.6 -> 23.1.
+//
 // NWV waves per workgroup.  16 waves (one workgroup per CU): stages of 32 KiB; 8 waves (two per CU): 16 KiB;
 // never more than 128 keys (the column-sum buffers grow with the keys of a stage).
 template <typename T, int D, int NWV>
@@ -46,14 +55,19 @@ struct ScoreCfg {
     static constexpr int NLD = STG / 1024 / NWV;            // 1-KiB loads per wave per stage
 };
 
-// The statistics (maximum m, exp-sum l relative to m, log2 domain scale c) of two disjoint key sets of one row.
-__device__ __forceinline__ void merge_stats(float& m, float& l, float m2, float l2, float c) {
-    const float M = fmaxf(m, m2);
-    if (M > -INFINITY) l = l * fast_exp2((m - M) * c) + l2 * fast_exp2((m2 - M) * c);
-    m = M;
+// The statistics of a row over some keys: the sum l of exp2(s c - e) about an offset e that is a whole number (the largest s c, rounded
+// up), so that a change of offset scales l by a power of two and costs no rounding.  No key yet: l = 0, e = -FLT_MAX.
+__device__ __forceinline__ void merge_stats(float& e, float& l, float e2, float l2) {
+    const float E = fmaxf(e, e2);
+    l = l * fast_exp2(e - E) + l2 * fast_exp2(e2 - E);
+    e = E;
 }
+// A chunk's statistics of a row in one number, l 2^e, which fp32 holds exactly for offsets up to this and sums of 2^24 keys; beyond
+// (and where l is no number) in two, -l and e.
+constexpr float kWholeOffset = 100.f;
 
-// PASS 1: partial[((b*Hq + head) * nsplit + chunk) * np + probe] = (raw-logit maximum, sum of exp2((s - max) * c))
+// PASS 1: partial[((b*Hq + head) * nsplit + chunk) * np + probe] = the sum over the chunk's keys of exp2(s c), or, where that is out of range
+// (the sign tells), what is said above, the offset in a second plane of as many numbers
 // PASS 2: mass / rank of the workgroup's keys; nsplit = chunks of pass 1
 // np = probe rows rounded up to a multiple of 32 (NB blocks); rows beyond m are masked out.
 // bpc = 32-key blocks per chunk of this pass; tpg = tasks per workgroup of pass 1, at most NWV.
@@ -61,16 +75,18 @@ template <typename T, int D, int PASS, int NWV>
 __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV == 8) ? 2 : 4) void score_kernel(
     const T* __restrict__ Q, const T* __restrict__ K,
     int64_t qs0, int64_t qs1, int64_t qs2, int64_t ks0, int64_t ks1, int64_t ks2,
-    ProbeList probes, int m, int NB, int n, int n_eff, float c, float2* __restrict__ partial, int nsplit, int bpc, int tpg,
+    ProbeList probes, int m, int NB, int n, int n_eff, float c, float* __restrict__ partial, int nsplit, int bpc, int tpg,
     float* __restrict__ mass, float* __restrict__ rank, int Hq, int Hkv, int kv_div)
 {
     using C = ScoreCfg<T, D, NWV>;
     constexpr int CH = C::CH, RB = C::RB, SK = C::SK, KBS = C::KBS, NLD = C::NLD, kStageBytes = C::STG;
     constexpr int kThreads = 64 * NWV;
-    extern __shared__ __attribute__((aligned(16))) char kstage[];   // kStageBufs stage buffers
+    extern __shared__ __attribute__((aligned(512))) char kstage[];   // kStageBufs stage buffers
     __shared__ __attribute__((aligned(16))) int sp[ZIPVL_MAX_PROBES];
     __shared__ float2 wstat[PASS == 1 ? NWV : 1][32];                // pass 1: per-wave row statistics
     __shared__ __attribute__((aligned(16))) float row_bias[PASS == 2 ? NWV : 1][32];
+    __shared__ unsigned char marks[PASS == 2 ? NWV : 1][64];        // pass 2: which of a wave's 64 keys are probes
+    __shared__ float keysum[PASS == 2 ? (kSumStages - 1) * SK : 1];  // pass 2: sums of up to kSumStages - 1 stages
     __shared__ float colbuf[PASS == 2 ? 2 : 1][PASS == 2 ? NWV : 1][PASS == 2 ? SK : 1];
 
     const int G = Hq / Hkv, np = NB * 32;
@@ -86,7 +102,6 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
 
     if (tid < ZIPVL_MAX_PROBES) sp[tid] = probes.pos[tid];           // -1 beyond m
     __syncthreads();
-    const int Pmin = sp[0];
 
     // waves -> tasks.  Fewer tasks than waves: KS waves share a task and take the key blocks slot, slot + KS, ...
     const bool few = NT < NWV;
@@ -94,19 +109,18 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     const int rounds = PASS == 1 || few ? 1 : (NT + NWV - 1) / NWV;
     const int ts = few ? w % NT : w;                                 // task slot inside a round
     const int slot = few ? w / NT : 0;
+    const int w_last_slot = (NWV - 1) / NT;                          // the last wave's, if it has a task
 
     // where this lane's NLD 16-byte pieces of a stage come from: row inside the stage and chunk under the row swizzle
     const char* Ku = reinterpret_cast<const char*>(K + b * ks0 + (g / kv_div) * ks1);   // kv_div > 1: every query head is its own unit
     const int row_stride = (int)ks2 * C::E;                          // bytes; a stage spans less than 2 GiB (checked on the host)
     const unsigned lds0 = lds_address(kstage);
     // where this lane's NLD 16-byte pieces of a stage come from: byte offset of (row inside the stage, chunk under the row swizzle)
-    int ld_off[NLD];
-#pragma unroll
-    for (int q = 0; q < NLD; ++q) {
-        const int o = (q * NWV + w) * 1024 + lane * 16;              // LDS byte of the piece: row r, position p of the row
-        const int r = o / RB, p = (o % RB) >> 4;
-        ld_off[q] = r * row_stride + ((p ^ k_row_swizzle<RB>(r)) << 4);
-    }
+    // (the loads of a wave are a multiple of 16 rows apart: one swizzle and one lane offset, the rest in the scalar base)
+    constexpr int kLoadRows = NWV * 1024 / RB;
+    static_assert(kLoadRows % 16 == 0, "one swizzle for all loads");
+    const int ld_row = (w * 1024 + lane * 16) / RB;
+    const int ld_off = ld_row * row_stride + ((((lane * 16) % RB >> 4) ^ k_row_swizzle<RB>(ld_row)) << 4);
     // Every wave issues exactly NLD loads per stage (pieces past the chunk's or the sequence's last row re-read
     // the stage's first row and are never used), so that "all but the newest p stages have landed" is a count.
     auto issue_stage = [&](int s) {
@@ -114,10 +128,15 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
         const int rows = min(min(blk1 * 32, n) - row0, SK);           // rows of this stage that exist and belong to the chunk
         const char* gbase = Ku + (int64_t)row0 * row_stride;
         const unsigned dst = lds0 + (s % kStageBufs) * kStageBytes;
+        if (rows == SK) {
 #pragma unroll
-        for (int q = 0; q < NLD; ++q) {
-            const int r = ((q * NWV + w) * 1024 + lane * 16) / RB;
-            load_kib_to_lds(gbase, r < rows ? ld_off[q] : 0, dst + (q * NWV + w) * 1024);
+            for (int q = 0; q < NLD; ++q) load_kib_to_lds(gbase + (int64_t)(q * kLoadRows) * row_stride, ld_off, dst + (q * NWV + w) * 1024);
+        } else {
+            int l = lane;                                            // derived again: nothing is carried for it
+            asm volatile("" : "+v"(l));
+            const int r0 = (w * 1024 + l * 16) / RB, off = r0 * row_stride + ((((l * 16) % RB >> 4) ^ k_row_swizzle<RB>(r0)) << 4);
+#pragma unroll
+            for (int q = 0; q < NLD; ++q) load_kib_to_lds(gbase, q * kLoadRows + r0 < rows ? q * kLoadRows * row_stride + off : 0, dst + (q * NWV + w) * 1024);
         }
     };
     // wait until at most `pending` stages (NLD loads each) of this wave are still on their way
@@ -137,18 +156,131 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
         const int head = active ? tk / NB : 0, nb = active ? tk - (tk / NB) * NB : 0;
         const int bh = b * Hq + g * G + head;
 
+        // chunk 2 cc + h of a row of the buffers, from where its chunk h is (rows are aligned to their size)
+        using LdsFrag = const __attribute__((address_space(3))) uintx4*;
+        auto fragment = [&](unsigned row, int cc) { return *(LdsFrag)(uintptr_t)(row ^ (32 * cc)); };
         if (rd) __syncthreads();                                     // the stage buffers of the previous round are free
+        // This wave's probe rows: fragments of row nb*32 + i, held for the whole round.  Gathered lane by lane (a row each) a load touches 64
+        // lines, and the 112 of a workgroup of 14 tasks kept the address unit busy for 3 us.  So they take the way of the keys: whole
+        // rows to the end of the stage buffers, once for the waves of a task, and from there into registers.  The stages whose
+        // buffers they leave free are on the way meanwhile.
+        constexpr int kEnd = kStageBufs * kStageBytes;
+        constexpr int kRows = NWV * 32 * RB <= kStageBufs * kStageBytes ? 32 : 16;       // rows of a task at a time
+        static_assert(NWV * kRows * RB <= kStageBufs * kStageBytes, "room for the probe rows of all tasks of a round");
+        const int rows_at = kEnd - (ts + 1) * kRows * RB;
+        const int early = min(min(kStageBufs - 1, S), (kEnd - ntr * kRows * RB) / kStageBytes);
+        const bool merges = PASS == 2 && active && slot == 0;
+        const float* stats = partial + (int64_t)bh * nsplit * np + nb * 32;                     // wave-uniform base; the rest fits 32 bits (host check)
+        // PASS 2: the statistics of a task's rows over pass 1's chunks, merged by one of its waves: lane = (4 rows, eighth of the chunks), 16
+        // bytes a load, no more loads than there are chunks for; as a rule plain sums
+        auto merge_chunks = [&]() {
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            const int st_row = 4 * (l & 7), st_chunk = l >> 3;
+            float L[4] = {0.f, 0.f, 0.f, 0.f}, E[4] = {0.f, 0.f, 0.f, 0.f};
+            uint32_t signs = 0;
+#pragma unroll 1
+            for (int from = 0; from < nsplit; from += 64) {
+                floatx4 v[8];
 #pragma unroll
-        for (int s = 0; s < kStageBufs - 1; ++s)
-            if (s < S) issue_stage(s);
-
-        // this wave's probe rows: fragments of row nb*32 + i, held for the whole round
+                for (int q = 0; q < 8; ++q) {
+                    v[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    if (from + 8 * q < nsplit) v[q] = *reinterpret_cast<const floatx4*>(stats + min(from + st_chunk + 8 * q, nsplit - 1) * np + st_row);
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const float there = from + st_chunk + 8 * q < nsplit ? 1.f : 0.f;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) L[r] = fmaf(v[q][r], there, L[r]);
+                    signs |= __float_as_uint(v[q][0]) | __float_as_uint(v[q][1]);
+                    signs |= __float_as_uint(v[q][2]) | __float_as_uint(v[q][3]);
+                }
+            }
+            if (__any((int)signs < 0)) {
+                const float* offsets = stats + (int64_t)gridDim.y * G * nsplit * np;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { L[r] = 0.f; E[r] = -FLT_MAX; }
+#pragma unroll 1
+                for (int s = st_chunk; s < nsplit; s += 8)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float v = stats[s * np + st_row + r];
+                        if ((int)__float_as_uint(v) >= 0) merge_stats(E[r], L[r], v > 0.f ? 0.f : -FLT_MAX, v);
+                        else merge_stats(E[r], L[r], offsets[s * np + st_row + r], -v);
+                    }
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int x = 8; x <= 32; x *= 2) merge_stats(E[r], L[r], __shfl_xor(E[r], x), __shfl_xor(L[r], x));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    L[r] += lane_moved<0x128, 0xF>(L[r], 0.f);                             // the other eight lanes of 16
+                    const auto by16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(L[r]), __float_as_uint(L[r]), false, false);
+                    L[r] = __uint_as_float(by16[0]) + __uint_as_float(by16[1]);
+                    const auto by32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(L[r]), __float_as_uint(L[r]), false, false);
+                    L[r] = __uint_as_float(by32[0]) + __uint_as_float(by32[1]);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (st_chunk == 0) row_bias[ts][st_row + r] = (nb * 32 + st_row + r < m && L[r] > 0.f) ? E[r] + __log2f(L[r]) : INFINITY;
+        };
         uintx4 qf[CH];
-        {
-            const int prow = sp[min(nb * 32 + i, m - 1)];
-            const T* qp = Q + b * qs0 + (int64_t)(g * G + head) * qs1 + (int64_t)prow * qs2 + h * Elem<T>::kPerFrag;
+        auto request_stages = [&](int from, int to) {
+            for (int s = from; s < to; ++s) issue_stage(s);
+        };
+        if constexpr (D == 64 && C::E == 2 && NWV == 16) {
+            // rows of 128 bytes: four loads a wave, gathered behind the first stages
+            request_stages(0, min(kStageBufs - 1, S));
+            const T* qp = Q + b * qs0 + (int64_t)(g * G + head) * qs1 + (int64_t)sp[min(nb * 32 + i, m - 1)] * qs2 + h * Elem<T>::kPerFrag;
 #pragma unroll
             for (int cc = 0; cc < CH; ++cc) qf[cc] = load16(qp + cc * Elem<T>::kPerChunk);
+            if (merges) merge_chunks();
+#pragma unroll
+            for (int cc = 0; cc < CH; ++cc) asm volatile("" : "+v"(qf[cc]));      // here now, and not waited for in front of every tile
+            if (PASS == 2) __syncthreads();
+        } else {
+#pragma unroll
+        for (int r0 = 0; r0 < 32; r0 += kRows) {
+            // (long chunks of few tasks: the keys first, they are what such a call waits for)
+            if (r0 == 0 && early == kStageBufs - 1) request_stages(0, early);
+            int l = lane;                                            // (through the empty asm: none of the addresses is kept from round to round)
+            asm volatile("" : "+v"(l));
+            if (active) {
+                // lane: row l / (RB / 16) of each load's 1024 / RB, piece l % (RB / 16) under the swizzle
+                const int lr = l * 16 / RB, lp = (l * 16 % RB >> 4), r1 = nb * 32 + r0 + lr;
+                const char* Qh = reinterpret_cast<const char*>(Q + b * qs0 + (int64_t)(g * G + head) * qs1);
+                const int64_t stride = qs2 * C::E;
+                auto request = [&](auto narrow) {
+                    for (int q = slot; q < kRows * RB / 1024; q += KS) {
+                        const int r = q * (1024 / RB), prow = sp[min(r1 + r, m - 1)], piece = (lp ^ k_row_swizzle<RB>(r + lr)) << 4;
+                        const unsigned dst = lds0 + rows_at + q * 1024;
+                        if constexpr (decltype(narrow)::value) load_kib_to_lds(Qh, (int)(__umul24(prow, (unsigned)stride) + piece), dst);
+                        else load_kib_to_lds_at(Qh + prow * stride + piece, dst);
+                    }
+                };
+                if (stride < 1 << 24 && n * stride < (int64_t)1 << 32) request(std::true_type{});       // offsets of 32 bits: a sixth of the address arithmetic
+                else request(std::false_type{});
+            }
+            if (r0 == 0 && early < kStageBufs - 1) request_stages(0, early);
+            if (r0 == 0 && merges) merge_chunks();
+            // all but the stages requested after them
+            if (r0 == 0 && early == 1) __builtin_amdgcn_s_waitcnt(0x0F70 | NLD);
+            else if (r0 == 0 && early == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * NLD));
+            else __builtin_amdgcn_s_waitcnt(0x0F70);
+            __syncthreads();
+            const int li = l & 31;
+            const unsigned row = lds0 + rows_at + (kRows == 32 ? li : li & 15) * RB + (((l >> 5) ^ k_row_swizzle<RB>(li)) << 4);
+            if (kRows == 32 || (li >> 4) == (r0 >> 4))
+#pragma unroll
+                for (int cc = 0; cc < CH; ++cc) qf[cc] = fragment(row, cc);
+            if (r0 + kRows < 32 || early < min(kStageBufs - 1, S)) {
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                __syncthreads();                                     // every wave has read its rows
+            }
+        }
+        request_stages(early, min(kStageBufs - 1, S));
         }
         const int Pm = sp[nb * 32 + i];                              // PASS 1: position of this lane's probe (-1: padding)
         // the first and last probe of this wave's block (sp ascends): its tiles up to the first need no mask, those past the
@@ -156,96 +288,77 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
         const int Pfirst = __builtin_amdgcn_readfirstlane(nb * 32 + 32 <= m ? sp[nb * 32] : -1);
         const int Plast = __builtin_amdgcn_readfirstlane(sp[min(nb * 32 + 31, m - 1)]);
 
-        if (PASS == 2) {
-            // Merge the chunk statistics of this task's 32 rows: lane = (pair of rows, quarter of the chunks), 16 bytes a load, up to
-            // eight in flight, one exponential per statistic.  28 heads on 4, n = 18432: a workgroup reads 229 KB of them (14 tasks, 64 chunks), the
-            // prologue took 9.9 of pass 2's 23 us with 8-byte loads and pairwise merges, 7.0 so (a CU takes in some 40 GB/s).
-            const floatx4* p = reinterpret_cast<const floatx4*>(partial + (int64_t)bh * nsplit * np + nb * 32);   // wave-uniform base; the rest fits 32 bits (host check)
-            const int pr = lane & 15, cg = lane >> 4;
-            float M[2] = {-INFINITY, -INFINITY}, L[2] = {0.f, 0.f};
-            auto take = [&](int first, auto loads) {
-                constexpr int N = decltype(loads)::value;
-                const int s0 = first + cg;
-                floatx4 v[N];
+        float e_run = -FLT_MAX, l_run = 0.f;                         // PASS 1
+        // PASS 2: exponent offsets of this lane's probe rows nb*32 + acc_row(r, h); in LDS where registers are short
+        constexpr bool kHeldBias = PASS == 2 && !(C::E == 4 && D == 128 && NWV == 16);
+        float rb[16];
+        auto load_bias = [&]() {
 #pragma unroll
-                for (int q = 0; q < N; ++q) v[q] = p[min(s0 + 4 * q, nsplit - 1) * (np / 2) + pr];
-#pragma unroll
-                for (int r = 0; r < 2; ++r) {
-                    float top = M[r];
-#pragma unroll
-                    for (int q = 0; q < N; ++q) top = fmaxf(top, v[q][2 * r]);             // a chunk read twice changes nothing
-                    const float off = top > -INFINITY ? top : 0.f;
-                    float sum = L[r] * fast_exp2((M[r] - off) * c);
-#pragma unroll
-                    for (int q = 0; q < N; ++q)
-                        sum = fmaf(s0 + 4 * q < nsplit ? v[q][2 * r + 1] : 0.f, fast_exp2((v[q][2 * r] - off) * c), sum);
-                    M[r] = top; L[r] = sum;
-                }
-            };
-            // no more loads than there are chunks for: a short sequence reads few (28 heads on 4, n = 100, m = 64: 18.6 us with eight,
-            // 17.8; fp32 at d = 128 with 16 waves holds 64 registers of probe rows: four at a time, 140 bytes of scratch and not 176)
-            if constexpr (C::E == 4 && D == 128 && NWV == 16) {
-                for (int first = 0; first < nsplit; first += 16) take(first, std::integral_constant<int, 4>{});
-            } else if (nsplit <= 4) {
-                take(0, std::integral_constant<int, 1>{});
-            } else if (nsplit <= 16) {
-                take(0, std::integral_constant<int, 4>{});
-            } else {
-                for (int first = 0; first < nsplit; first += 32) take(first, std::integral_constant<int, 8>{});
+            for (int a = 0; a < 4; ++a) {
+                const floatx4 v = *reinterpret_cast<const floatx4*>(&row_bias[ts][8 * a + 4 * h]);
+                rb[4 * a] = v[0]; rb[4 * a + 1] = v[1]; rb[4 * a + 2] = v[2]; rb[4 * a + 3] = v[3];
             }
+        };
+        if (kHeldBias) load_bias();
+        // PASS 2: the scores of a stage's keys.  Every wave waits for them at the next barrier.  Where the last waves have no tile they make them
+        // meanwhile, stage by stage; else these add up the tasks' sums only, and what makes scores of them is left for kSumStages stages
+        // at a time, to all waves.
+        const bool idle = few && (w_last_slot >= KBS || NWV > NT * KS);
+        // The tasks' column sums, in task order.
+        auto key_sum = [&](int s, int t) {
+            const float* col = &colbuf[s & 1][0][t];
+            float a = 0.f;
+            for (int q = 0; q < ntr; q += 4) {
+                float v[4];
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                merge_stats(M[r], L[r], __shfl_xor(M[r], 16), __shfl_xor(L[r], 16), c);
-                merge_stats(M[r], L[r], __shfl_xor(M[r], 32), __shfl_xor(L[r], 32), c);
-                if (active && slot == 0 && cg == 0)
-                    row_bias[ts][2 * pr + r] = (nb * 32 + 2 * pr + r < m && L[r] > 0.f) ? M[r] * c + __log2f(L[r]) : INFINITY;
+                for (int e = 0; e < 4; ++e) v[e] = col[min(q + e, ntr - 1) * SK];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a += q + e < ntr ? v[e] : 0.f;
             }
-            __syncthreads();
-        }
-
-        // The probe rows have to be here now.  Left to the tile loop, the compiler's wait for them stands in front of every tile's
-        // first product and, not knowing of the stage loads, waits for those just requested too.  PASS 1 waits for its first stages
-        // here, which costs more than it gives where K is read once (d = 128, 40 heads, n = 18432, m = 64: 66.5 -> 67.7 us, 4 x 32
-        // heads, n = 4096 54.4 -> 55.9); at d = 64 it gives (40 heads, n = 18432, 64 recent and 64 random 67.9 -> 66.0).
-        if (PASS == 2 || D == 64)
-#pragma unroll
-            for (int cc = 0; cc < CH; ++cc) asm volatile("" : "+v"(qf[cc]));
-        float m_run = -INFINITY, l_run = 0.f;                        // PASS 1
-        // add the tasks' column sums of stage s (PASS 2) in task order and write the scores of its keys
-        // (taken by the workgroup's last threads first: with more waves than tasks those waves are otherwise idle)
-        auto reduce_stage = [&](int s) {
-            const int buf = s & 1;
-            const int row0 = (blk0 + s * KBS) * 32;
-            const int keys = min(min(blk1 * 32, n) - row0, SK);
-            for (int t = kThreads - 1 - tid; t < keys; t += kThreads) {
-                const int j = row0 + t;
+            return a;
+        };
+        // by the workgroup's last threads (with more waves than tasks those waves are otherwise idle)
+        auto sum_stage = [&](int s) {
+            for (int t = kThreads - 1 - tid; t < SK; t += kThreads) keysum[(s % kSumStages) * SK + t] = key_sum(s, t);
+        };
+        // The scores of the keys of stages s0 .. s1 - 1; the last of them is still in the tasks' sums
+        auto write_scores = [&](int s0, int s1) {
+            const int row0 = (blk0 + s0 * KBS) * 32, last = (s1 - 1 - s0) * SK, keys = min(min(blk1 * 32, n) - row0, last + SK);
+            for (int t0 = (NWV - 1 - w) * 64; t0 < keys; t0 += kThreads) {       // 64 keys of the wave
+                const int t = t0 + lane, j = row0 + t;
+                const bool mine = t < keys, seen = mine && j < n_eff;
                 float a = 0.f;
-                if (rd && j < n_eff) {                               // tasks of earlier rounds
+                if (rd && seen) {                                    // tasks of earlier rounds
                     a = mass[(int64_t)u * n + j];
                     asm volatile("" : "+v"(a));                      // waited for here and not, with the stages in flight, on every path
                 }
-                if (j < n_eff)
-                    for (int q = 0; q < ntr; ++q) a += colbuf[buf][q][t];
+                if (seen) a += t < last ? keysum[t] : key_sum(s1 - 1, t - last);
                 if (rd + 1 < rounds) {
-                    mass[(int64_t)u * n + j] = a;
+                    if (mine) mass[(int64_t)u * n + j] = a;
                 } else {
-                    a /= (float)G;
-                    // probes at or after j: m less those before it (sp ascends).  By bisection: counting all 128 one by one
-                    // took half of pass 2 with random probes (40 heads, n = 4096, m = 128: 53 -> 22 us).
-                    int cnt = m;
-                    if (j > Pmin) {
-                        int before = 0;
+                    // Probes at or after j: m less those before it, of which two ballots count those before the 64 keys, and the others are marks
+                    // among the keys (a bisection over the list in LDS is seven reads one after the other).
+                    static_assert(ZIPVL_MAX_PROBES == 128, "two probes a lane");
+                    const int j0 = row0 + t0;
+                    int before = 0;
+                    marks[w][lane] = 0;
 #pragma unroll
-                        for (int step = ZIPVL_MAX_PROBES / 2; step; step >>= 1)
-                            if (before + step <= m && sp[before + step - 1] < j) before += step;
-                        if (before < m && sp[before] < j) ++before;          // all ZIPVL_MAX_PROBES of them
-                        cnt = m - before;
+                    for (int e = 0; e < ZIPVL_MAX_PROBES; e += 64) {
+                        const int pos = e + lane < m ? sp[e + lane] - j0 : 64;
+                        before += __popcll(__ballot(pos < 0));
+                        if (pos >= 0 && pos < 64) marks[w][pos] = 1;
                     }
-                    mass[(int64_t)u * n + j] = a / (float)m;
-                    if (rank) rank[(int64_t)u * n + j] = cnt > 0 ? a / (float)cnt : 0.f;
+                    const uint64_t bits = __ballot(marks[w][lane]);
+                    before += __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0));
+                    const int cnt = m - before;
+                    if (mine) {
+                        mass[(int64_t)u * n + j] = a / (float)(G * m);
+                        if (rank) rank[(int64_t)u * n + j] = cnt > 0 ? a / (float)(G * cnt) : 0.f;
+                    }
                 }
             }
         };
+        const unsigned frag0 = lds0 + i * RB + ((h ^ k_row_swizzle<RB>(i)) << 4);
 #pragma unroll 1
         for (int s = 0; s < S; ++s) {
             // stage s has landed (this wave's pieces, then everyone's); everyone is done with stage s - 1, whose
@@ -253,9 +366,12 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             wait_stages(min(kStageBufs - 2, S - 1 - s));
             __syncthreads();
             if (s + kStageBufs - 1 < S) issue_stage(s + kStageBufs - 1);
-            if (PASS == 2 && s > 0) reduce_stage(s - 1);
+            if (PASS == 2 && s > 0) {
+                if (idle || s % kSumStages == 0) write_scores(idle ? s - 1 : s - kSumStages, s);
+                else sum_stage(s - 1);
+            }
             const int buf = s & 1;                                   // column-sum buffer of the stage
-            const char* kb0 = kstage + (s % kStageBufs) * kStageBytes;
+            const unsigned kb0 = frag0 + (s % kStageBufs) * kStageBytes;
             const int sblk = blk0 + s * KBS;                         // first key block of the stage
             if (active) {
 #pragma unroll 1
@@ -265,12 +381,15 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                         if (PASS == 2 && h == 0) colbuf[buf][ts][kb * 32 + i] = 0.f;
                         continue;
                     }
-                    const char* krow = kb0 + (kb * 32 + i) * RB;
-                    auto kfrag = [&](int cc) { return *reinterpret_cast<const uintx4*>(krow + swz_chunk(2 * cc + h, k_row_swizzle<RB>(i))); };
+                    const unsigned krow = kb0 + kb * 32 * RB;
+                    auto kfrag = [&](int cc) { return fragment(krow, cc); };
                     floatx16 acc = {0};
-                    // bf16: the fragments of the key block are read ahead of the products (six while 128 registers hold no more; two at
+                    // long chunks of few tasks are bound by memory, and faster where a wave with a tile waits for all stages on their way (40
+                    // heads, n = 18432, m = 64 68.8 -> 67.4 us)
+                    if (PASS == 1 && early == kStageBufs - 1 && S > 4 * (kStageBufs - 1)) __builtin_amdgcn_s_waitcnt(0x0F70);
+                    // bf16: the fragments of the key block are read ahead of the products (four while 128 registers hold no more; two at
                     // a time: 14 heads on 2, n = 33000, m = 128 84.7 -> 80.3 us); an fp32 one feeds four products of 64 cycles
-                    constexpr int kReads = C::E == 4 ? 1 : CH == 8 && PASS == 2 && NWV == 16 ? 6 : CH;
+                    constexpr int kReads = C::E == 4 ? 1 : CH;
                     uintx4 kf[CH];
 #pragma unroll
                     for (int cc = 0; cc < kReads; ++cc) kf[cc] = kfrag(cc);
@@ -283,33 +402,24 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                     const bool masked = jb + 31 > Pfirst;            // wave-uniform
                     if (PASS == 1) {
                         // acc[r]: key jb + acc_row(r, h), probe column nb*32 + i  (raw logit)
-                        float sv[16], mx = -INFINITY;
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) sv[r] = acc[r];
                         if (masked) {
+                            const int own = Pm - jb - 4 * h;
 #pragma unroll
                             for (int r = 0; r < 16; ++r)
-                                if (jb + acc_row(r, h) > Pm) sv[r] = -INFINITY;
+                                if (acc_row(r, 0) > own) acc[r] = -INFINITY;
                         }
+                        float mx = acc[0];
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sv[r]);
-                        const float m_new = fmaxf(m_run, mx);
-                        if (m_new > -INFINITY) {
-                            const float mc = m_new * c;
-                            float sum = l_run * fast_exp2(m_run * c - mc);      // 0 while m_run = -inf
+                        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, acc[r]);
+                        const float e_new = fmaxf(e_run, ceilf(mx * c));     // a number also where the lane has seen no key yet: it adds zeros
+                        float sum = l_run * fast_exp2(e_run - e_new);
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(sv[r], c, -mc));
-                            l_run = sum;
-                            m_run = m_new;
-                        }
+                        for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[r], c, -e_new));
+                        l_run = sum;
+                        e_run = e_new;
                     } else {
-                        // acc[r]: probe row nb*32 + acc_row(r, h), key column jb + i; rb[r]: exponent offset of that row
-                        float rb[16];
-#pragma unroll
-                        for (int a = 0; a < 4; ++a) {
-                            const floatx4 v = *reinterpret_cast<const floatx4*>(&row_bias[ts][8 * a + 4 * h]);
-                            rb[4 * a] = v[0]; rb[4 * a + 1] = v[1]; rb[4 * a + 2] = v[2]; rb[4 * a + 3] = v[3];
-                        }
+                        // acc[r]: probe row nb*32 + acc_row(r, h), key column jb + i
+                        if (!kHeldBias) load_bias();
                         float sum = 0.f;
                         if (masked) {
 #pragma unroll
@@ -325,31 +435,37 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
 #pragma unroll
                             for (int r = 0; r < 16; ++r) sum += fast_exp2(fmaf(acc[r], c, -rb[r]));
                         }
-                        sum += __shfl_xor(sum, 32);
-                        if (h == 0) colbuf[buf][ts][kb * 32 + i] = sum;
+                        const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+                        if (h == 0) colbuf[buf][ts][kb * 32 + i] = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
                     }
                 }
             }
         }
         if (PASS == 2) {
             __syncthreads();                                         // the last stage's column sums are in LDS
-            reduce_stage(S - 1);
+            write_scores(idle ? S - 1 : (S - 1) / kSumStages * kSumStages, S);
         }
 
         if (PASS == 1) {
             // the two half-waves saw different keys of the same rows; waves that share a task saw different key blocks
-            merge_stats(m_run, l_run, __shfl_xor(m_run, 32), __shfl_xor(l_run, 32), c);
-            if (h == 0) wstat[w][i] = active ? make_float2(m_run, l_run) : make_float2(-INFINITY, 0.f);
+            merge_stats(e_run, l_run, __shfl_xor(e_run, 32), __shfl_xor(l_run, 32));
+            if (h == 0) wstat[w][i] = active ? make_float2(e_run, l_run) : make_float2(-FLT_MAX, 0.f);
             __syncthreads();
             for (int t = tid; t < ntr * 32; t += kThreads) {
                 const int q = t >> 5, pc = t & 31;                   // task slot, probe row of its block
-                float M = -INFINITY, L = 0.f;
+                float E = -FLT_MAX, L = 0.f;
                 for (int sl = 0; sl < KS; ++sl) {
                     const float2 v = wstat[few ? sl * NT + q : q][pc];
-                    merge_stats(M, L, v.x, v.y, c);
+                    merge_stats(E, L, v.x, v.y);
                 }
                 const int tk = task0 + rd * NWV + q, hd = tk / NB, nbk = tk - hd * NB;
-                partial[((int64_t)(b * Hq + g * G + hd) * nsplit + blockIdx.x) * np + nbk * 32 + pc] = make_float2(M, L);
+                float* out = partial + ((int64_t)(b * Hq + g * G + hd) * nsplit + blockIdx.x) * np + nbk * 32 + pc;
+                if (L == 0.f || (L > 0.f && fabsf(E) <= kWholeOffset)) {
+                    *out = L > 0.f ? __builtin_amdgcn_ldexpf(L, (int)E) : 0.f;
+                } else {
+                    *out = __uint_as_float(__float_as_uint(L) | 0x80000000u);
+                    out[(int64_t)gridDim.y * G * nsplit * np] = E;
+                }
             }
         }
     }
@@ -377,7 +493,7 @@ static int blocks_per_chunk(int nblk, int units, int slots) {
 }
 
 size_t score_workspace_bytes(const zipvl_dims& d, int m) {
-    // one (max, sum) pair per head, probe row and pass-1 chunk; chunks per unit never exceed the resident slots
+    // one pair (sum, offset; the offsets in a plane of their own) per head, probe row and pass-1 chunk; chunks per unit never exceed the resident slots
     const int max_chunks = std::max(1, resident_slots(8) / std::max(1, d.B * d.Hkv));
     return (size_t)d.B * d.Hq * max_chunks * probe_rows(m) * sizeof(float2);
 }
@@ -402,7 +518,7 @@ static RowStatsPlan row_stats_plan(int NT, int units, int nblk, int row_bytes, i
     auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     auto plan = [&](int groups, int turns) { return RowStatsPlan{groups, blocks_per_chunk(nblk, units * groups, turns * slots)}; };
     auto bytes = [&](const RowStatsPlan& p) {
-        return kKeyCost * p.groups * units * nblk * 32.0 * row_bytes / cus + (double)ceil_div(nblk, p.bpc) * NT * 32 * sizeof(float2) * (16 / waves2);
+        return kKeyCost * p.groups * units * nblk * 32.0 * row_bytes / cus + (double)ceil_div(nblk, p.bpc) * NT * 32 * sizeof(float) * (16 / waves2);
     };
     auto tiles = [&](const RowStatsPlan& p) {
         const int64_t tpg = ceil_div(NT, p.groups), shared = std::max<int64_t>(1, 8 / tpg), wgs = (int64_t)units * p.groups * ceil_div(nblk, p.bpc);
@@ -437,7 +553,7 @@ static int launch_score_w(const void* Q, const void* K, const zipvl_dims& d, con
                           int n_eff, float scale, float* mass, float* rank, void* ws, int kv_div, hipStream_t st)
 {
     const float c = scale * kLog2e;
-    float2* partial = (float2*)ws;
+    float* partial = (float*)ws;
     const int units = d.B * d.Hkv, NB = probe_rows(m) / 32, NT = d.Hq / d.Hkv * NB;
     constexpr size_t lds1 = (size_t)kStageBufs * ScoreCfg<T, D, 8>::STG, lds2 = (size_t)kStageBufs * ScoreCfg<T, D, NW2>::STG;
     int rc = reserve_lds<T, D, 1, 8>();

@@ -335,6 +335,34 @@ def test_scores_of_wide_groups(dtype, d, G, Hkv, n, m):
     assert_scores_close(host64(rank), ro, dtype, "rank")
 
 
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,n", [("bf16", 128, 4, 4, 1500), ("bf16", 64, 28, 4, 700), ("f32", 64, 4, 2, 333), ("f32", 128, 20, 2, 200)])
+def test_scores_of_rows_whose_sums_do_not_fit_one_number(dtype, d, Hq, Hkv, n):
+    """Sums of exp2 beyond 2^100 and below 2^-100, in some chunks, rows and heads and not in others, and a row that is not a number.
+    A log2-domain exponent x carries sqrt(d) 2^-24 |x| < 1e-6 |x| from the fp32 product sum and its roundings."""
+    say(f"score {dtype} d={d} Hq={Hq} Hkv={Hkv} n={n}, large logits")
+    w = make_custom(1, Hq, Hkv, n, d, dtype, seed=77, m=64)
+    G, K32, Q32 = Hq // Hkv, w.K.copy(), w.Q.copy()
+    last = Q32[:, ::G, n - 1] / np.linalg.norm(Q32[:, ::G, n - 1], axis=-1, keepdims=True)
+    K32[:, :, n // 3] += 60 * last                             # one key far above the others, in one chunk
+    K32[:, 0] -= 40 * last[:, :1]                              # the first KV head: all of them far below zero
+    Q32[:, 1::2, n - 64 : n - 40] *= 3
+    if Hq > 2:
+        Q32[:, 2, n - 20] = 0
+    Q, K = dev(Q32, dtype), dev(K32, dtype)
+    mass, rank = z.zipvl_score(Q, K, w.probe_pos, w.scale)
+    torch.cuda.synchronize()
+    Qh, Kh = host64(Q)[0], host64(K)[0]
+    big = max(np.abs(Qh[h, n - 64:] @ Kh[h // G].T).max() for h in range(Hq)) * w.scale * 1.4427
+    say(f"  largest log2-domain logit {big:.0f}")
+    assert big > 200
+    mo, ro = oz.token_scores(Qh, Kh, w.probe_pos, w.scale)
+    for got, ref in ((mass, mo), (rank, ro)):
+        assert (np.abs(host64(got) - ref) <= 1e-9 + (1e-5 + 1e-6 * big) * np.abs(ref)).all()
+    Q[0, 0, n - 9] = float("nan")                              # a probe row of head 0 only: the other KV heads do not see it
+    nan_mass, _ = z.zipvl_score(Q, K, w.probe_pos, w.scale)
+    assert torch.equal(nan_mass[1:], mass[1:]) and torch.isnan(nan_mass[0]).any()
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("name", ["first-rows", "block-ends-early", "one-past-a-block", "straddling", "last-row-only"])
 def test_scores_where_blocks_of_probes_end(name, dtype):
