@@ -41,6 +41,7 @@ class QTensor(C.Structure):
 
 
 _lib = None
+_native = None               # the extension module _pycall: see _called
 
 
 def library_path() -> str:
@@ -49,7 +50,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libzipvl.so from the package directory; raise if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     path = library_path()
@@ -57,6 +58,10 @@ def load_library():
         raise ZipvlError(-100, f"{path} is missing: build it with `python -m paper_2410_08584_amd.build` "
                                "(there is no CPU fallback)")
     lib = C.CDLL(path)
+    try:
+        from . import _pycall
+    except ImportError as e:
+        raise ZipvlError(-100, f"the extension module beside {path} does not load ({e}): build it with `python -m paper_2410_08584_amd.build`")
     vp, i32p, f32p = C.c_void_p, C.c_void_p, C.c_void_p
     lib.zipvl_version.restype = C.c_int
     lib.zipvl_last_error.restype = C.c_char_p
@@ -93,6 +98,7 @@ def load_library():
                  "zipvl_decode_attn_q", "zipvl_sparse_prefill", "zipvl_compact_kv", "zipvl_kv_append", "zipvl_decode_attn",
                  "zipvl_decode_step"):
         getattr(lib, name).restype = C.c_int
+    _native = _pycall
     _lib = lib
     return lib
 
@@ -108,6 +114,14 @@ def zipvl_last_error() -> str:
 def _check(rc: int):
     if rc != 0:
         raise ZipvlError(rc, zipvl_last_error())
+
+
+def _called(rc: Optional[int]) -> bool:
+    """Whether _pycall took the call (plain tensors and numbers, nothing to allocate); if not, nothing has been launched and the
+    general way below it in each function handles the call, or says what is wrong with it.  Raises on an error code."""
+    if rc:
+        raise ZipvlError(rc, zipvl_last_error())
+    return rc is not None
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -201,6 +215,9 @@ def zipvl_score(Q: torch.Tensor, K: torch.Tensor, probe_pos: Sequence[int], soft
                 want_rank: bool = True, ws: Optional[torch.Tensor] = None, flags: int = 0):
     """(mass, rank) fp32 [B*Hkv, n] from the probe rows of Q against K ([B*Hq, n] with flags=SCORE_PER_QHEAD)."""
     lib = load_library()
+    if mass is not None and ws is not None and (rank is not None or not want_rank) and _called(
+            _native.score(Q, K, probe_pos, softmax_scale, flags, mass, rank, ws)):
+        return mass, rank
     dm = dims_of(Q, K)
     units = dm.B * (dm.Hq if flags & SCORE_PER_QHEAD else dm.Hkv)
     probes, m = _int32_array(probe_pos)
@@ -228,6 +245,8 @@ def zipvl_select(mass: torch.Tensor, rank: Optional[torch.Tensor], tau: float, *
     """(idx [units,n] int32 with the first k entries valid and ascending, k [units] int32).  ws: select_workspace(units)
     for the two-kernel form (taken for n > 32768), None for the one-kernel form.  status: int32 [units] tensor that receives the SELECT_* bits."""
     lib = load_library()
+    if idx is not None and k is not None and _called(_native.select(mass, rank, tau, idx, k, status, ws)):
+        return idx, k
     _dense(mass, rank, idx, k)
     units, n = mass.shape
     if idx is None:
@@ -277,6 +296,8 @@ def zipvl_sparse_prefill(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, idx:
                          O: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None):
     """O [B,Hq,n,d]: causal attention over the kept tokens (idx=k=None: all tokens)."""
     lib = load_library()
+    if O is not None and ws is not None and _called(_native.sparse_prefill(Q, K, V, idx, k, softmax_scale, flags, O, ws)):
+        return O
     dm = dims_of(Q, K, V)
     if O is None:
         O = torch.empty((dm.B, dm.Hq, dm.n, dm.d), dtype=Q.dtype, device=Q.device)
@@ -292,6 +313,8 @@ def zipvl_compact_kv(K: torch.Tensor, V: torch.Tensor, idx: Optional[torch.Tenso
                      length: Optional[torch.Tensor] = None):
     """(Kc, Vc [B*Hkv, cap, d], len [B*Hkv] int32): the evicted cache (flags: 0 or T_PER_BATCH)."""
     lib = load_library()
+    if Kc is not None and Vc is not None and length is not None and _called(_native.compact_kv(K, V, idx, k, cap, flags, Kc, Vc, length)):
+        return Kc, Vc, length
     dm = dims_of(None, K, V, Hq=K.shape[1])
     units = dm.B * dm.Hkv
     if Kc is None:
@@ -308,6 +331,8 @@ def zipvl_compact_kv(K: torch.Tensor, V: torch.Tensor, idx: Optional[torch.Tenso
 def zipvl_kv_append(Kc: torch.Tensor, Vc: torch.Tensor, length: torch.Tensor, k_new: torch.Tensor,
                     v_new: torch.Tensor, *, B: int, Hkv: int):
     lib = load_library()
+    if _called(_native.kv_append(Kc, Vc, length, k_new, v_new, B, Hkv)):
+        return length
     units, cap, d = Kc.shape
     dm = dims_of(None, None, None, B=B, Hq=Hkv, Hkv=Hkv, n=cap, d=d, dtype=_dtype_code(Kc))
     _check(lib.zipvl_kv_append(_ptr(Kc), _ptr(Vc), _ptr(length), int(cap), _ptr(k_new), _ptr(v_new),
@@ -353,6 +378,8 @@ def zipvl_decode_step(q: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor, lengt
                       ws: torch.Tensor, o: Optional[torch.Tensor] = None):
     """Append k_new / v_new and attend in one call; ws from decode_step_workspace (kept between steps)."""
     lib = load_library()
+    if o is not None and _called(_native.decode_step(q, Kc, Vc, length, k_new, v_new, softmax_scale, B, Hq, Hkv, ws, o)):
+        return o
     units, cap, d = Kc.shape
     dm = dims_of(None, None, None, B=B, Hq=Hq, Hkv=Hkv, n=cap, d=d, dtype=_dtype_code(Kc))
     if o is None:
@@ -411,6 +438,9 @@ def zipvl_decode_attn_q(q: torch.Tensor, cache: QCache, softmax_scale: float, *,
                         o: Optional[torch.Tensor] = None, ws: Optional[torch.Tensor] = None):
     """o [B*Hq, d]: one query per head against the dequantised cache followed by the appended rows."""
     lib = load_library()
+    if o is not None and ws is not None and _called(
+            _native.decode_attn_q(q, cache, softmax_scale, B, Hq, Hkv, K_tail, V_tail, len_tail, o, ws)):
+        return o
     cap_tail = 0 if K_tail is None else K_tail.shape[1]
     dm = dims_of(None, None, None, B=B, Hq=Hq, Hkv=Hkv, n=cache.cap_hi + cache.cap_lo + cap_tail, d=cache.d,
                  dtype=_dtype_code(q))

@@ -1871,3 +1871,74 @@ def test_decode_of_head_groups_at_tile_edges(dtype, d, G):
             worst = max(worst, np.abs(host64(o[h]) - oz.decode_attention(host64(q[h]), Kh, Vh, L1, w.scale)).max())
     say(f"  worst |do| = {worst:.3e}")
     assert worst <= ATOL_OUT[dtype]
+
+
+# ------------------------------------------------------------------ calls without ctypes
+def test_calls_of_the_extension_module_are_the_general_ones(monkeypatch):
+    """Every call that _pycall takes, then the same call the general way: the same bits.  Calls that it leaves to the general way, and
+    calls that the library refuses: the same errors."""
+    say("extension module against ctypes")
+    from paper_2410_08584_amd import binding
+    B, Hq, Hkv, n, d = 2, 4, 2, 500, 64
+    w = make_custom(B, Hq, Hkv, n, d, "bf16", seed=81, m=64)
+    Q, K, V = (dev(x, "bf16") for x in (w.Q, w.K, w.V))
+    units, probes = B * Hkv, [int(p) for p in w.probe_pos]
+    new = lambda *shape, dtype=torch.float32: torch.zeros(shape, dtype=dtype, device=DEV)
+    byte_ws = lambda nbytes: new(nbytes, dtype=torch.uint8)
+
+    def calls():
+        mass, rank, idx, k = new(units, n), new(units, n), new(units, n, dtype=torch.int32), new(units, dtype=torch.int32)
+        z.zipvl_score(Q, K, probes, w.scale, mass=mass, rank=rank, ws=byte_ws(z.workspace_bytes(z.OP_SCORE, z.dims_of(Q, K), 64)))
+        z.zipvl_select(mass, rank, 0.975, idx=idx, k=k)
+        cap = n + 8
+        Kc, Vc, ln = new(units, cap, d, dtype=Q.dtype), new(units, cap, d, dtype=Q.dtype), new(units, dtype=torch.int32)
+        z.zipvl_compact_kv(K, V, idx, k, cap, Kc=Kc, Vc=Vc, length=ln)
+        O = new(B, Hq, n, d, dtype=Q.dtype)
+        z.zipvl_sparse_prefill(Q, K, V, idx, k, w.scale, O=O, ws=byte_ws(z.workspace_bytes(z.OP_SPARSE_PREFILL, z.dims_of(Q, K, V))))
+        q, kn, vn = Q[:, :, 3].reshape(B * Hq, d).contiguous(), K[:, :, 3].reshape(units, d).contiguous(), V[:, :, 3].reshape(units, d).contiguous()
+        o = new(B * Hq, d, dtype=Q.dtype)
+        z.zipvl_decode_step(q, Kc, Vc, ln, kn, vn, w.scale, B=B, Hq=Hq, Hkv=Hkv, ws=z.decode_step_workspace(B, Hq, Hkv, cap, d, Kc), o=o)
+        cache = z.zipvl_quantize_kv(K, V, idx, k, n, n)
+        Kt, Vt, lt, oq = new(units, 9, d, dtype=Q.dtype), new(units, 9, d, dtype=Q.dtype), new(units, dtype=torch.int32), new(B * Hq, d, dtype=Q.dtype)
+        z.zipvl_kv_append(Kt, Vt, lt, kn, vn, B=B, Hkv=Hkv)
+        dq = z.dims_of(None, None, None, B=B, Hq=Hq, Hkv=Hkv, n=2 * n + 9, d=d, dtype=1)
+        z.zipvl_decode_attn_q(q, cache, w.scale, B=B, Hq=Hq, Hkv=Hkv, K_tail=Kt, V_tail=Vt, len_tail=lt, o=oq, ws=byte_ws(z.workspace_bytes(z.OP_DECODE_Q, dq)))
+        torch.cuda.synchronize()
+        kept = [idx[u, : int(k[u])] for u in range(units)]
+        return [mass, rank, k, ln, O, o, Kt, Vt, lt, oq, *kept, *(Kc[u, : int(ln[u])] for u in range(units))]
+
+    def refusals():
+        ws, mass = byte_ws(1 << 20), new(units, n)
+        cap = 16
+        Kc, ln, o, x = new(units, cap, d, dtype=Q.dtype), new(units, dtype=torch.int32), new(B * Hq, d, dtype=Q.dtype), new(units, d, dtype=Q.dtype)
+        bad = [lambda: z.zipvl_score(Q, K, probes[::-1], w.scale, mass=mass, rank=mass, ws=ws),
+               lambda: z.zipvl_score(Q, K, probes, w.scale, mass=mass, rank=mass, ws=ws[:256]),
+               lambda: z.zipvl_score(Q, K, probes, -1.0, mass=mass, rank=mass, ws=ws),
+               lambda: z.zipvl_score(Q.half(), K, probes, w.scale, mass=mass, rank=mass, ws=ws),
+               lambda: z.zipvl_score(Q.transpose(2, 3), K, probes, w.scale, mass=mass, rank=mass, ws=ws),
+               lambda: z.zipvl_score(Q, K, probes, w.scale, mass=mass.t(), rank=mass, ws=ws),
+               lambda: z.zipvl_select(mass, mass, 2.0, idx=new(units, n, dtype=torch.int32), k=ln, ws=ws[:8]),
+               lambda: z.zipvl_sparse_prefill(Q, K, V, None, ln, w.scale, O=torch.empty_like(Q), ws=ws),
+               lambda: z.zipvl_compact_kv(K, V, None, ln, 0, Kc=Kc, Vc=Kc, length=ln),
+               lambda: z.zipvl_kv_append(Kc, Kc, ln, x, x, B=-1, Hkv=Hkv),
+               lambda: z.zipvl_decode_step(o, Kc, Kc, ln, x, x, w.scale, B=B, Hq=3, Hkv=2, ws=ws, o=o),
+               lambda: z.zipvl_decode_step(o, Kc[0], Kc, ln, x, x, w.scale, B=B, Hq=Hq, Hkv=Hkv, ws=ws, o=o)]
+        out = []
+        for call in bad:
+            with pytest.raises(Exception) as e:
+                call()
+            out.append((type(e.value), str(e.value)))
+        return out
+
+    direct, refused = calls(), refusals()
+    took = []
+
+    class General:
+        def __getattr__(self, name):
+            return lambda *a: took.append(name)
+
+    monkeypatch.setattr(binding, "_native", General())
+    for a, b in zip(direct, calls()):
+        assert torch.equal(a, b)
+    assert sorted(set(took)) == ["compact_kv", "decode_attn_q", "decode_step", "kv_append", "score", "select", "sparse_prefill"]
+    assert refused == refusals()
