@@ -105,7 +105,7 @@ struct AttnCfg {
     static constexpr int VRB = D * E;                        // bytes per V row
     static constexpr int TILE_BYTES = kBN * D * E;           // one K tile = one V tile
     static constexpr int NLD = TILE_BYTES / 1024 / NW;       // 1-KiB direct-to-LDS loads per wave per tile
-    static constexpr int LDS_BYTES = E == 4 ? SplitCfg<D, KS>::LDS_BYTES : 4 * TILE_BYTES;     // two K and two V buffers
+    static constexpr int LDS_BYTES = E == 4 ? SplitCfg<D, KS>::LDS_BYTES : 4 * TILE_BYTES + 256 * NW;     // two K and two V buffers, positions of a wave's queries
     // QB = 1: two waves per SIMD (<= 256 registers, accumulators stay in VGPRs), three for fp32 at d = 64 in workgroups of four;
     // otherwise one wave per SIMD with the whole 512-entry register file
     static constexpr int MIN_WGS = QB == 1 ? E == 4 ? (D == 64 && NW == 4 ? 3 : 2) : 8 / NW : 1;
@@ -340,26 +340,39 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     auto load_v = [&](int t, int buf) {
         tile_to_lds<C::VRB, NW, C::NLD, true>(vg + (int64_t)t * C::TILE_BYTES, vlds + buf * C::TILE_BYTES, voff, vrows - t * kBN);
     };
-    // The first tiles are requested before anything else is loaded: their addresses need only scalars, while the
-    // query rows below wait for their positions first (two round trips).
+    // Positions, then the first key tiles, then query rows, all straight into LDS: the rows wait for the positions only (a load into
+    // registers would wait for the tiles too), and a load asks for whole rows (fragment by fragment, 16 bytes of a row a lane, a wave's
+    // took the address unit 64 clocks a load).  The rows lie where V tiles go from the first step on, in the swizzle of K rows.  A workgroup of
+    // 17 steps had its rows 3.2 us after it asked for tiles, 3.0 so; with the rows of the output (below), calls with their sets and caches,
+    // us: 4 x 32 heads, a third kept, n = 4000 120 -> 115, 32, n = 2933 39.7 -> 38.6, 28 on 4, n = 18432, 39 % 358 -> 353, d = 64, 3 x 40, n = 8000, a fifth 109.5 -> 107.
+    static_assert(QB == 1, "32 queries a wave");
+    constexpr int kRowLanes = C::KRB / 16, kRowsAtOnce = 64 / kRowLanes, kQueryLoads = 32 / kRowsAtOnce;
+    char* const held = smem + 4 * C::TILE_BYTES + w * 256;
+    char* const rows_lds = Vb0 + w * 32 * C::KRB;
     auto request_first_tiles = [&]() {
         load_k(0, 0);
-        load_v(0, 0);
         if (ntiles > 1) load_k(1, 1);
     };
+    const int first = i0 + kRW * qw;
+    if (tidx) load_dwords_to_lds(reinterpret_cast<const char*>(tidx), min(first + i, kk - 1) * 4, lds_address(held));
     request_first_tiles();
-    // kept-token coordinates of this lane's QB queries, their positions, their Q fragments
-    int qrow[QB], qpos[QB];
-    uintx4 qf[QB][C::CH];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        qrow[qb] = i0 + kRW * qw + 32 * qb + i;
-        const int qclamp = min(qrow[qb], kk - 1);
-        qpos[qb] = tidx ? tidx[qclamp] : qclamp;
-        const T* qp = Q + (int64_t)qpos[qb] * qs2;
-#pragma unroll
-        for (int cc = 0; cc < C::CH; ++cc) qf[qb][cc] = load16(qp + cc * Elem<T>::kPerChunk + h * Elem<T>::kPerFrag);
+    if (tidx) {
+        if (ntiles > 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::NLD) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(C::NLD) : "memory");
     }
+#pragma unroll
+    for (int q = 0; q < kQueryLoads; ++q) {
+        const int r = q * kRowsAtOnce + lane / kRowLanes;
+        const int pos = tidx ? *reinterpret_cast<const int*>(held + 4 * r) : min(first + r, kk - 1);
+        load_kib_to_lds_at(reinterpret_cast<const char*>(Q + (int64_t)pos * qs2) + swz_chunk(lane % kRowLanes, k_row_swizzle<C::KRB>(r)),
+                           lds_address(rows_lds) + q * 1024);
+    }
+    int qrow[QB] = {first + i};                              // kept-token coordinate of this lane's query
+    uintx4 qf[QB][C::CH];
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int cc = 0; cc < C::CH; ++cc) qf[0][cc] = *reinterpret_cast<const uintx4*>(rows_lds + i * C::KRB + swz_chunk(2 * cc + h, sw));
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     // One pass over the key tiles.  SAFE = false: the exponent offset stays 0 (softmax is shift invariant, and
     // floating point keeps its relative precision at any magnitude), so there is no running maximum, no
     // exchange between lanes and no rescaling in the loop; valid as long as the row sums stay far inside the
@@ -384,6 +397,7 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     if constexpr (SAFE) request_first_tiles();                  // the first pass requested them before the query rows
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    load_v(0, 0);
     floatx16 sa[QB][C::NBK], sb[QB][C::NBK];
     Probs pa, pb;
     qk_block<T, D, NW, QB, KS>(Kb0 + kw * 32 * C::KRB, 0, i, h, sw, qf, sa);       // tile 0 is visible to every row
@@ -580,16 +594,10 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     pass(std::false_type{});
     // Output rows.  Everything the stores need is derived again from the thread index here (the empty asm
     // keeps the compiler from carrying row numbers and pointers through the key loop, where registers are
-    // scarce); the positions are requested now and arrive during the check below.
+    // scarce).
     int tid_out = threadIdx.x;
     asm volatile("" : "+v"(tid_out));
-    const int w_out = KS == 1 ? tid_out >> 6 : (tid_out >> 6) % (NW / KS), i_out = tid_out & 31, h_out = (tid_out >> 5) & 1;
-    int qr_out[QB], orow_out[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        qr_out[qb] = i0 + kRW * w_out + 32 * qb + i_out;
-        orow_out[qb] = (out_compact || !tidx) ? qr_out[qb] : tidx[min(qr_out[qb], kk - 1)];
-    }
+    const int i_out = tid_out & 31, h_out = (tid_out >> 5) & 1;
     // KS = 2: a query's sums lie in two waves.  A per-lane value of the partner wave (same queries, other keys), through LDS: the
     // tile buffers are free once every wave has waited for its last requests.
     float* const meet = reinterpret_cast<float*>(smem);
@@ -615,6 +623,7 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         }
         if (__syncthreads_or(bad)) {
             pass(std::true_type{});
+            if constexpr (KS == 1) __syncthreads();              // the last requests of all waves have landed
             if constexpr (KS == 2)
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) {            // to the larger of the two offsets (key 0 is visible to every row: finite)
@@ -660,21 +669,26 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
                 for (int r = 0; r < 16; ++r) o[qb][db][r] += meet[(((w2 * QB + qb) * kOut + db) * 16 + r) * 64 + lane_out];
     }
 
+    // Rows leave through LDS (a wave's own part of the V buffers), 16 bytes a lane and whole rows a store: from the accumulators a lane has 8 bytes of
+    // a row at a time, 32 rows a store.  A workgroup ended 2.9 us after its last step (stores included), 2.1 so.
+    constexpr int kOutBytes = D * Elem<T>::kBytes / KS, kOutLanes = kOutBytes / 16, kOutRows = 64 / kOutLanes;
+    char* const mine = Vb0 + (tid_out >> 6) * 32 * kOutBytes;
+    auto out_chunk = [](int row, int c) { return row * kOutBytes + ((c ^ (row / (256 / kOutBytes) & (kOutLanes - 1))) << 4); };
+    const float inv = 1.f / xhalf_sum(l_run[0]);
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const float l_tot = xhalf_sum(l_run[qb]);
-        const int qr = qr_out[qb];
-        if (qr < kk) {
-            const float inv = 1.f / l_tot;
-            const int orow = orow_out[qb];
-            T* op = O + (int64_t)orow * D + (KS == 2 ? kw * (D / 2) : 0);
+    for (int db = 0; db < kOut; ++db)
 #pragma unroll
-            for (int db = 0; db < kOut; ++db)
+        for (int a = 0; a < 4; ++a)
+            store_out4<T>(reinterpret_cast<T*>(mine + out_chunk(i_out, 4 * db + a) + 8 * h_out), o[0][db][4 * a] * inv, o[0][db][4 * a + 1] * inv,
+                          o[0][db][4 * a + 2] * inv, o[0][db][4 * a + 3] * inv);
+    const int w_out = KS == 1 ? tid_out >> 6 : (tid_out >> 6) % (NW / KS), lane_row = (tid_out & 63) / kOutLanes, c_out = tid_out % kOutLanes;
+    const char* const held_out = smem + 4 * C::TILE_BYTES + (tid_out >> 6) * 256;
 #pragma unroll
-                for (int a = 0; a < 4; ++a)
-                    store_out4<T>(op + 32 * db + 8 * a + 4 * h_out, o[qb][db][4 * a] * inv, o[qb][db][4 * a + 1] * inv,
-                                  o[qb][db][4 * a + 2] * inv, o[qb][db][4 * a + 3] * inv);
-        }
+    for (int q = 0; q < 32 / kOutRows; ++q) {
+        const int r = q * kOutRows + lane_row, qr = i0 + kRW * w_out + r;
+        const uintx4 x = *reinterpret_cast<const uintx4*>(mine + out_chunk(r, c_out));
+        const int orow = out_compact || !tidx ? qr : *reinterpret_cast<const int*>(held_out + 4 * r);
+        if (qr < kk) store16(O + (int64_t)orow * D + (KS == 2 ? kw * (D / 2) : 0) + c_out * 8, x);
     }
 }
 
@@ -1109,7 +1123,12 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
         const int lane = threadIdx.x & 63;
         lane_k = a0.kcnt[min(lane, sets - 1)];
         int most = max(lane_k, 0);
-        for (int x = lane + 64; x < sets; x += 64) most = max(most, a0.kcnt[x]);
+        for (int x = 64; x < sets; x += 256) {                   // loads of four at a time
+            int k4[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k4[j] = a0.kcnt[min(x + 64 * j + lane, sets - 1)];
+            most = max(max(most, max(k4[0], k4[1])), max(k4[2], k4[3]));
+        }
         lmax = min(lmax, (wave_reduce(most, 0, [](int x, int y) { return max(x, y); }) + kBM - 1) / kBM);
     }
     const int rows = min(lmax, a0.slots);

@@ -643,6 +643,34 @@ def test_attention_schedule(copies, Hq, Hkv, n, d, dtype, shared):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("copies,n,ks", [(1, 1, (1, 1)), (1, 33, (32, 33)), (1, 300, (31, 130)), (1, 300, (0, 300)), (24, 1090, (65, 1089)), (24, 1090, (1, 700))])
+@pytest.mark.parametrize("gain", [1.0, 60.0])
+def test_attention_of_queries_in_any_rows(copies, n, ks, d, gain):
+    """Query rows at any distance from each other ([B, n, Hq, 2 d] and half of it), in tiles of 64 and of 128 queries with 1 to 128 of them, kept and all;
+    with rows that repeat their tiles (gain 60).  The same bits as from contiguous queries, which agree with the oracle."""
+    say(f"attention strided queries {copies} n={n} ks={ks} d={d} gain={gain}")
+    w = make_custom(1, 4, 2, n, d, "bf16", seed=66)
+    Qh, Kh = (torch.from_numpy(x * g).bfloat16().float().numpy() for x, g in ((w.Q, gain), (w.K, 1.0)))
+    Q, K, V = (dev(x, "bf16").repeat(copies, 1, 1, 1) for x in (Qh, Kh, w.V))
+    far = torch.full((copies, n, 4, 2 * d), float("nan"), dtype=Q.dtype, device=DEV)[..., :d].transpose(1, 2)
+    far.copy_(Q)
+    r = np.random.Generator(np.random.PCG64(67))
+    idx = np.zeros((2, n), dtype=np.int32)
+    for u, k in enumerate(ks):
+        idx[u, :k] = np.sort(r.choice(n, k, replace=False))
+    args = torch.from_numpy(idx).to(DEV).repeat(copies, 1), torch.tensor(ks, dtype=torch.int32, device=DEV).repeat(copies), w.scale
+    for a in (args, (None, None, w.scale)):
+        O = z.zipvl_sparse_prefill(Q, K, V, *a)
+        assert torch.equal(O, z.zipvl_sparse_prefill(far, K, V, *a))
+        assert torch.equal(O, O[:1].expand_as(O))
+        for h in range(4):
+            T = np.arange(n) if a[0] is None else idx[h // 2, :ks[h // 2]]
+            ref = oz.kept_token_attention(Qh[0, h], Kh[0, h // 2], w.V[0, h // 2], T, w.scale)
+            worst = np.abs(host64(O[0, h]) - ref).max()
+            assert worst <= ATOL_OUT["bf16"], f"head {h}: {worst:.3e}"
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("B,n,ks", [(1, 97, [97, 33]), (1, 257, [256, 129]), (20, 130, None), (300, 130, None), (100, 161, [100, 1]), (160, 161, [161, 129]), (400, 260, [95, 32])])
 def test_attention_fp32_in_three_planes(d, B, n, ks):
     """fp32 attention in all its forms (64 queries by eight waves, by four, 128; chosen by the host and by the kept count), at tiles that
