@@ -1086,6 +1086,15 @@ __device__ __forceinline__ void clear_dropped(T* __restrict__ O, const int32_t* 
 
 // kp, vp: of batch element, KV head.  slots: rows of attention workgroups in the grid, BH each; fill: workgroups after them that clear
 // rows; scan: whether the kept counts are read for the longest head; ug: KV heads of a scheduling group, one more in the first `extra` ones.
+// n / d of whole numbers below 2^31, inv = inverse(d) from the host: the high half of the product is the quotient or one less.  The compiler's own division by
+// a number it does not know is some 20 dependent vector instructions, and a workgroup needs five of them to know its place: 0.8 us, 0.3 so.  Attention with
+// its set and cache, us: d = 64, 3 x 40 heads, n = 8000, a fifth kept 107.0 -> 104.1, 4 x 32, n = 4000, a third 115.2 -> 113.5, long tiles as before.
+static uint32_t inverse(int d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)d); }
+__device__ __forceinline__ int divided(int n, int d, uint32_t inv) {
+    const uint32_t q = (uint32_t)((uint64_t)(uint32_t)n * inv >> 32);
+    return (int)(q + ((uint32_t)n - q * d >= (uint32_t)d));
+}
+
 template <typename T> struct FlashArgs {
     const T* Q; int64_t qs0, qs1, qs2;
     const T* Kp; int64_t kp0, kp1;
@@ -1095,6 +1104,7 @@ template <typename T> struct FlashArgs {
     int n, npad, slots, fill, scan, ug, extra, G, BH, Hq, Hkv;
     float c;
     int out_compact, t_per_batch, k_in_place, v_in_place;
+    uint32_t inv_larger, inv_smaller, inv_g, inv_hkv;        // of (ug + 1) G, ug G, G, Hkv
 };
 
 template <typename T, int D, int NW, int QB, int KS>
@@ -1107,28 +1117,25 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
     // All arguments at once: the compiler would load each where it is first used, 0.2 us apart.
     auto fetch = [](const auto& a) {
         const FlashArgs<T> x = {a.Q, a.qs0, a.qs1, a.qs2, a.Kp, a.kp0, a.kp1, a.Vp, a.vp0, a.vp1, a.idx, a.kcnt, a.O, a.n, a.npad, a.slots, a.fill, a.scan,
-                                a.ug, a.extra, a.G, a.BH, a.Hq, a.Hkv, a.c, a.out_compact, a.t_per_batch, a.k_in_place, a.v_in_place};
+                                a.ug, a.extra, a.G, a.BH, a.Hq, a.Hkv, a.c, a.out_compact, a.t_per_batch, a.k_in_place, a.v_in_place,
+                                a.inv_larger, a.inv_smaller, a.inv_g, a.inv_hkv};
         asm volatile("" :: "s"(x.Q), "s"(x.qs0), "s"(x.qs1), "s"(x.qs2), "s"(x.Kp), "s"(x.kp0), "s"(x.kp1), "s"(x.Vp), "s"(x.vp0), "s"(x.vp1), "s"(x.idx),
                      "s"(x.kcnt), "s"(x.O), "s"(x.n), "s"(x.npad), "s"(x.fill), "s"(x.ug), "s"(x.extra), "s"(x.G), "s"(x.BH), "s"(x.Hq), "s"(x.Hkv), "s"(x.c),
-                     "s"(x.out_compact), "s"(x.t_per_batch), "s"(x.k_in_place), "s"(x.v_in_place));
+                     "s"(x.out_compact), "s"(x.t_per_batch), "s"(x.k_in_place), "s"(x.v_in_place), "s"(x.inv_larger), "s"(x.inv_smaller), "s"(x.inv_g), "s"(x.inv_hkv));
         return x;
     };
     const FlashArgs<T> a0 = fetch(args);
     // The query tiles of the longest head.  k is on the device and the grid is for k = n, so that most workgroups of a sparse call have
     // nothing to do; dispatched among the others, in their order and 1.5 us each in a slot of the chip, they kept a fifth of the slots
     // empty (4 x 32 heads, n = 8192, a quarter kept).  With this every workgroup knows them, and they are the last of the grid.
-    int lmax = (a0.n + kBM - 1) / kBM, lane_k = 0, sets = 0;
+    int lmax = (a0.n + kBM - 1) / kBM, lane_k = 0, lane_k2 = 0, sets = 0;
     if (a0.scan) {
-        sets = a0.t_per_batch ? a0.BH / a0.Hq : a0.BH / a0.G;
+        sets = a0.t_per_batch ? divided(divided(a0.BH, a0.G, a0.inv_g), a0.Hkv, a0.inv_hkv) : divided(a0.BH, a0.G, a0.inv_g);
         const int lane = threadIdx.x & 63;
         lane_k = a0.kcnt[min(lane, sets - 1)];
-        int most = max(lane_k, 0);
-        for (int x = 64; x < sets; x += 256) {                   // loads of four at a time
-            int k4[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) k4[j] = a0.kcnt[min(x + 64 * j + lane, sets - 1)];
-            most = max(max(most, max(k4[0], k4[1])), max(k4[2], k4[3]));
-        }
+        lane_k2 = a0.kcnt[min(lane + 64, sets - 1)];
+        int most = max(max(lane_k, lane_k2), 0);
+        for (int x = lane + 128; x < sets; x += 64) most = max(most, a0.kcnt[x]);
         lmax = min(lmax, (wave_reduce(most, 0, [](int x, int y) { return max(x, y); }) + kBM - 1) / kBM);
     }
     const int rows = min(lmax, a0.slots);
@@ -1136,15 +1143,19 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
     // tiles first inside a group (scheduling_groups), so that the light tail of one overlaps the heavy start of the next.
     struct Place { int row, b, g, head, set; };
     auto place = [&](const FlashArgs<T>& a) {
-        const int per = a.G * rows, wide = a.extra * (a.ug + 1);      // workgroups of a KV head; KV heads of the larger groups
-        const bool large = block < wide * per;
-        const int from = large ? 0 : wide, size = a.ug + large, heads = size * a.G;
-        const int first = from + (block - from * per) / (heads * rows) * size, r = block - first * per;
-        const int row = r / heads;
-        int rr = r - row * heads;
-        if (rows >= kTurnFrom && a.kcnt && a.G == 1 && heads % 8 == 0) rr = (rr + row / kTurnRows) % heads;
-        const int u = first + rr / a.G, b = u / a.Hkv, g = u - b * a.Hkv;
-        return Place{row, b, g, g * a.G + rr % a.G, a.t_per_batch ? b : u};
+        const int wide = a.extra * (a.ug + 1);                   // KV heads of the larger groups
+        const bool large = block < wide * a.G * rows;
+        const int from = large ? 0 : wide, size = a.ug + large, heads = size * a.G, past = block - from * a.G * rows;
+        const uint32_t inv = large ? a.inv_larger : a.inv_smaller;
+        const int line = divided(past, heads, inv);        // row, counted from the first of these groups
+        const int group = (unsigned)line / (unsigned)rows, row = line - group * rows;
+        int rr = past - line * heads;
+        if (rows >= kTurnFrom && a.kcnt && a.G == 1 && heads % 8 == 0) {
+            rr += row / kTurnRows;
+            rr -= divided(rr, heads, inv) * heads;
+        }
+        const int j = divided(rr, a.G, a.inv_g), u = from + group * size + j, b = divided(u, a.Hkv, a.inv_hkv), g = u - b * a.Hkv;
+        return Place{row, b, g, g * a.G + rr - j * a.G, a.t_per_batch ? b : u};
     };
     auto kept = [&](const FlashArgs<T>& a, int set) { return a.kcnt ? a.kcnt[set] : a.n; };
     auto tile = [&](const FlashArgs<T>& a, const Place& at, int kk, int round) {
@@ -1180,7 +1191,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
         return;
     }
     const Place at0 = place(a0);
-    const int k0 = at0.set < min(sets, 64) ? __builtin_amdgcn_readlane(lane_k, at0.set) : kept(a0, at0.set);
+    const int k0 = at0.set < min(sets, 128) ? __builtin_amdgcn_readlane(at0.set < 64 ? lane_k : lane_k2, at0.set & 63) : kept(a0, at0.set);
     if constexpr (KS != 1) {
         tile(a0, at0, k0, 0);
     } else {
@@ -1272,7 +1283,8 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
             C::LDS_BYTES, st, FlashArgs<T>{(const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
                 skip_k ? (const T*)K : Kp, skip_k ? d.k_strides[0] : (int64_t)d.Hkv * npad * D, skip_k ? d.k_strides[1] : (int64_t)npad * D,
                 skip_v ? (const T*)V : Vp, skip_v ? d.v_strides[0] : (int64_t)d.Hkv * npad * D, skip_v ? d.v_strides[1] : (int64_t)npad * D,
-                idx, k, (T*)O, d.n, npad, slots, (int)fill, scan, units / groups, units % groups, G, BH, d.Hq, d.Hkv, scale * kLog2e, out_compact, t_per_batch, skip_k, skip_v});
+                idx, k, (T*)O, d.n, npad, slots, (int)fill, scan, units / groups, units % groups, G, BH, d.Hq, d.Hkv, scale * kLog2e, out_compact, t_per_batch, skip_k, skip_v,
+                inverse((units / groups + 1) * G), inverse(units / groups * G), inverse(G), inverse(d.Hkv)});
     }
     return check_launch("flash_kept");
 }
