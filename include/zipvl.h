@@ -219,6 +219,7 @@ int zipvl_kv_append(void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k
  * q, o [device] [B*Hq, d] contiguous; Kc, Vc [device] [B*Hkv, cap, d]; len [device] [B*Hkv].
  * Memory-bound: each cached row is read once per call.  G = Hq/Hkv <= 8.
  * ws [device] zipvl_workspace_bytes(ZIPVL_OP_DECODE, dims (n = cap), 0) bytes.
+ * A smaller one is taken as long as it holds splits of 256 rows; few heads then leave part of the chip idle.
  */
 int zipvl_decode_attn(const void* q, const void* Kc, const void* Vc, const int32_t* len,
                       int32_t cap, const zipvl_dims* dims, float softmax_scale,
@@ -229,7 +230,7 @@ int zipvl_decode_attn(const void* q, const void* Kc, const void* Vc, const int32
  * HIP-graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels
  * and same results as zipvl_decode_attn, without ws / ws_bytes: the partial states of the split-KV kernels
  * live in a fixed array of ZIPVL_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until the
- * process ends).  The call allocates and frees nothing.  Dims whose zipvl_workspace_bytes(ZIPVL_OP_DECODE)
+ * process ends).  The call allocates and frees nothing.  Dims whose smallest workspace (splits of 256 rows)
  * exceeds ZIPVL_STATIC_SCRATCH_BYTES are rejected with ZIPVL_ESHAPE before anything is launched.
  * Every call on a GPU uses that GPU's one array: calls that overlap in time on one GPU (two streams, two
  * threads) race on it; calls ordered on one stream do not.  The array keeps the last call's contents;

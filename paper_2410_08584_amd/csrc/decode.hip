@@ -1156,25 +1156,39 @@ __global__ __launch_bounds__(256, D == 128 ? 3 : 4) void decode_q1_partial_kerne
     combine_waves<D, 1, 12>(red, 1, PartialOut(part, D, u, 1, nsplit, rule.units), 0, split);
 }
 
-static int decode_splits(const zipvl_dims& d, int cap) {
+static int decode_splits(const zipvl_dims& d, int cap, int rows = 256) {       // at least `rows` rows per split
     const int units = d.B * d.Hkv;
     int s = (1024 + units - 1) / units;
-    const int by_len = (cap + 255) / 256;                   // at least 256 rows per split
+    const int by_len = (cap + rows - 1) / rows;
     s = s < by_len ? s : by_len;
     return s < 1 ? 1 : (s > kDecMaxSplit ? kDecMaxSplit : s);
 }
 
-// Partial states that the workspace of a cache of `cap` rows holds per head.
-static int workspace_splits(const zipvl_dims& d, int cap) {
+// Partial states that the smallest workspace of a cache of `cap` rows holds per head.
+static int least_splits(const zipvl_dims& d, int cap) {
     const int per = std::max(256, ((cap + 15) / 16 + 15) / 16 * 16);
     return std::max(decode_splits(d, cap), (cap + per - 1) / per);
 }
 
+// Partial states that a call makes use of.  Where splits of 256 rows leave the chip idle, one head (fewer than 512 workgroups of 4 waves) has splits of
+// 128, in fp32 64, and groups of bf16 at d = 128 (fewer than 256 of 8 waves) of 128 where two launches merge them in any case.  us a step of all layers,
+// 256 rows -> so: 28 layers of 28 heads on 4, cap 10 500 316 -> 301; 16 of 14 on 2, cap 9200 163 -> 146; 8 of 32 heads, cap 2700 107 -> 92; 8 of 8,
+// d = 64, cap 1900 72 -> 63; fp32, d = 64, 8 of 4 heads, cap 350 51 -> 44; with as many as 1024 workgroups of one head 96, and 32 heads, d = 64,
+// cap 5500 118 for 110.  Groups with shorter caches and in fp32 would gain too (16 layers of 32 on 8, cap 700 121 -> 112; fp32, 28 on 4, cap 2300 213 -> 157),
+// but the tests of the merge fix how many states those leave; at d = 64 bf16 gains nothing (28 on 4, cap 2900 7.9 us a layer, 8.1 in two launches).
+constexpr int kFineGroups = 24;                              // splits of 256 rows above which groups have finer ones
+static int useful_splits(const zipvl_dims& d, int cap) {
+    const bool groups = d.Hq > d.Hkv, bf16 = d.dtype == ZIPVL_BF16;
+    if (groups && (!bf16 || d.d == 64 || decode_splits(d, cap) <= kFineGroups)) return least_splits(d, cap);
+    return std::max(least_splits(d, cap), std::min(decode_splits(d, cap, bf16 ? 128 : 64), (groups ? 256 : 512) / (d.B * d.Hkv)));
+}
+static size_t state_bytes(const zipvl_dims& d) { return (size_t)d.B * d.Hq * (d.d + 2) * sizeof(float); }       // of a split of every unit
+
 // One head: 1024 workgroups of 4 waves (512: 151 us for four layers of 128 units, 1024: 131, 2048: 142), then 1792: seven per CU
 // are resident together, and a few more would run alone at the end (four conversations of 32768 rows, 32 heads: 1024 387 us,
 // 1792 382, 2048 424).  Groups: 256 of 8 waves (one per CU: 512 is 3-10 % slower from 32 units on, and as fast below), then twice.
-static SplitRule split_rule(const zipvl_dims& d, int cap) {
-    const int units = d.B * d.Hkv, room = workspace_splits(d, cap);
+static SplitRule split_rule(const zipvl_dims& d, int cap, size_t ws_bytes) {
+    const int units = d.B * d.Hkv, room = (int)std::min<size_t>(useful_splits(d, cap), ws_bytes / state_bytes(d));
     const bool groups = d.Hq / d.Hkv > 1;
     const int tiles = groups ? kDecLongGroups : kDecLongOne;
     const int least = std::max(1, std::min(room, ((groups ? 256 : 1024) + units - 1) / units));
@@ -1185,16 +1199,15 @@ static SplitRule split_rule(const zipvl_dims& d, int cap) {
     return {least, std::min(more, launched), launched, tiles, units, turn};
 }
 
-size_t decode_workspace_bytes(const zipvl_dims& d, int cap) {
-    return (size_t)d.B * d.Hq * workspace_splits(d, cap) * (d.d + 2) * sizeof(float);
-}
+size_t decode_workspace_bytes(const zipvl_dims& d, int cap) { return useful_splits(d, cap) * state_bytes(d); }
+size_t decode_workspace_least(const zipvl_dims& d, int cap) { return least_splits(d, cap) * state_bytes(d); }
 
 template <typename T, int D>
 static int launch_decode_t(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
-                           const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
+                           const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st)
 {
     const int G = d.Hq / d.Hkv, units = d.B * d.Hkv;
-    const SplitRule rule = split_rule(d, cap);
+    const SplitRule rule = split_rule(d, cap, ws_bytes);
     const Lengths lengths{{len, nullptr, nullptr}, {cap, 0, 0}};
     const float c = scale * kLog2e;
 #define ZIPVL_DEC(GT)                                                                                \
@@ -1222,12 +1235,12 @@ static int launch_decode_t(const void* q, const void* Kc, const void* Vc, const 
 template <typename T, int D>
 static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl_qtensor& Vq, const int32_t* len_hi,
                              const int32_t* len_lo, int32_t cap_hi, int32_t cap_lo, const void* Kt, const void* Vt,
-                             const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
+                             const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st)
 {
     const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, cap = cap_hi + cap_lo + cap_t;
     // one head: as many splits as are resident together (three workgroups of four waves per CU), whatever the lengths are; each
     // takes its share of the cache (four layers of 128 units x 8192 rows: 1024 workgroups 153 us, 768 123, 512 137, 384 134)
-    const SplitRule rule = G > 1 ? split_rule(d, cap) : SplitRule{1, 1, std::min(decode_splits(d, cap), std::max(1, 768 / units)), 0, units, 0};
+    const SplitRule rule = G > 1 ? split_rule(d, cap, ws_bytes) : SplitRule{1, 1, std::min(decode_splits(d, cap), std::max(1, 768 / units)), 0, units, 0};
     Lengths lengths{{nullptr, nullptr, nullptr}, {0, 0, 0}};
     if (rule.turn) lengths = {{len_hi, len_lo, Kt ? len_t : nullptr}, {cap_hi, cap_lo, cap_t}};      // else every split reports: 0.5 us less
     const float c = scale * kLog2e;
@@ -1259,10 +1272,11 @@ static size_t step_counter_bytes(const zipvl_dims& d) { return ((size_t)d.B * d.
 size_t decode_step_workspace_bytes(const zipvl_dims& d, int cap) {
     return step_counter_bytes(d) + decode_workspace_bytes(d, cap);
 }
+size_t decode_step_workspace_least(const zipvl_dims& d, int cap) { return step_counter_bytes(d) + decode_workspace_least(d, cap); }
 
 template <typename T, int D>
 static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,
-                                const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
+                                const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st)
 {
     const int G = d.Hq / d.Hkv;
     unsigned* arrived = (unsigned*)ws;
@@ -1270,10 +1284,10 @@ static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len,
     if (G > 8) {                                            // several passes over the cache per step: not fused
         int rc = launch_kv_append(Kc, Vc, len, cap, k_new, v_new, d, st);
         if (rc) return rc;
-        return launch_decode_attn(q, Kc, Vc, len, cap, d, scale, o, part, st);
+        return launch_decode_attn(q, Kc, Vc, len, cap, d, scale, o, part, ws_bytes - step_counter_bytes(d), st);
     }
     const float c = scale * kLog2e;
-    const SplitRule rule = split_rule(d, cap);
+    const SplitRule rule = split_rule(d, cap, ws_bytes - step_counter_bytes(d));
     const bool one_launch = G == 1 || rule.most <= kMergeSplits<T, D>;
     {
         KernelTimer tm(ZIPVL_K_DECODE_STEP, st);
@@ -1294,21 +1308,21 @@ static int launch_decode_step_t(const void* q, void* Kc, void* Vc, int32_t* len,
 }
 
 int launch_decode_step(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,
-                       const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
+                       const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st)
 {
     if (d.dtype == ZIPVL_BF16) {
-        if (d.d == 128) return launch_decode_step_t<__bf16, 128>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, st);
-        return launch_decode_step_t<__bf16, 64>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, st);
+        if (d.d == 128) return launch_decode_step_t<__bf16, 128>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, ws_bytes, st);
+        return launch_decode_step_t<__bf16, 64>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, ws_bytes, st);
     }
-    if (d.d == 128) return launch_decode_step_t<float, 128>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, st);
-    return launch_decode_step_t<float, 64>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, st);
+    if (d.d == 128) return launch_decode_step_t<float, 128>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, ws_bytes, st);
+    return launch_decode_step_t<float, 64>(q, Kc, Vc, len, cap, k_new, v_new, d, scale, o, ws, ws_bytes, st);
 }
 
 int launch_decode_attn_q(const void* q, const zipvl_qtensor& Kq, const zipvl_qtensor& Vq, const int32_t* len_hi,
                          const int32_t* len_lo, int32_t cap_hi, int32_t cap_lo, const void* Kt, const void* Vt,
-                         const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
+                         const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st)
 {
-#define ZIPVL_ARGS q, Kq, Vq, len_hi, len_lo, cap_hi, cap_lo, Kt, Vt, len_t, cap_t, d, scale, o, ws, st
+#define ZIPVL_ARGS q, Kq, Vq, len_hi, len_lo, cap_hi, cap_lo, Kt, Vt, len_t, cap_t, d, scale, o, ws, ws_bytes, st
     if (d.dtype == ZIPVL_BF16) {
         if (d.d == 128) return launch_decode_q_t<__bf16, 128>(ZIPVL_ARGS);
         return launch_decode_q_t<__bf16, 64>(ZIPVL_ARGS);
@@ -1349,25 +1363,25 @@ static int static_scratch(void** out) {
 int launch_decode_attn_static(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
                               const zipvl_dims& d, float scale, void* o, hipStream_t st)
 {
-    const size_t need = decode_workspace_bytes(d, cap);
+    const size_t need = decode_workspace_least(d, cap);
     if (need > kStaticScratchBytes)
         return set_error(ZIPVL_ESHAPE, "decode_attn_static: these dims need %zu bytes of partial states, the built-in scratch holds %zu "
                                        "(use zipvl_decode_attn with a workspace)", need, kStaticScratchBytes);
     void* ws = nullptr;
     const int rc = static_scratch(&ws);
     if (rc) return rc;
-    return launch_decode_attn(q, Kc, Vc, len, cap, d, scale, o, ws, st);
+    return launch_decode_attn(q, Kc, Vc, len, cap, d, scale, o, ws, kStaticScratchBytes, st);
 }
 
 int launch_decode_attn(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
-                       const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st)
+                       const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st)
 {
     if (d.dtype == ZIPVL_BF16) {
-        if (d.d == 128) return launch_decode_t<__bf16, 128>(q, Kc, Vc, len, cap, d, scale, o, ws, st);
-        return launch_decode_t<__bf16, 64>(q, Kc, Vc, len, cap, d, scale, o, ws, st);
+        if (d.d == 128) return launch_decode_t<__bf16, 128>(q, Kc, Vc, len, cap, d, scale, o, ws, ws_bytes, st);
+        return launch_decode_t<__bf16, 64>(q, Kc, Vc, len, cap, d, scale, o, ws, ws_bytes, st);
     }
-    if (d.d == 128) return launch_decode_t<float, 128>(q, Kc, Vc, len, cap, d, scale, o, ws, st);
-    return launch_decode_t<float, 64>(q, Kc, Vc, len, cap, d, scale, o, ws, st);
+    if (d.d == 128) return launch_decode_t<float, 128>(q, Kc, Vc, len, cap, d, scale, o, ws, ws_bytes, st);
+    return launch_decode_t<float, 64>(q, Kc, Vc, len, cap, d, scale, o, ws, ws_bytes, st);
 }
 
 }  // namespace zipvl

@@ -36,16 +36,18 @@ int launch_share_scores(const float* mass, const float* rank, int B, int Hkv, in
 int launch_kv_append(void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,
                      const void* v_new, const zipvl_dims& d, hipStream_t st);
 
-size_t decode_workspace_bytes(const zipvl_dims& d, int cap);
+size_t decode_workspace_bytes(const zipvl_dims& d, int cap);        // of as many splits as a call makes use of
+size_t decode_workspace_least(const zipvl_dims& d, int cap);        // fewer are enough
 int launch_decode_attn(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
-                       const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st);
+                       const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st);
 
 int launch_decode_attn_static(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
                               const zipvl_dims& d, float scale, void* o, hipStream_t st);
 
 size_t decode_step_workspace_bytes(const zipvl_dims& d, int cap);
+size_t decode_step_workspace_least(const zipvl_dims& d, int cap);
 int launch_decode_step(const void* q, void* Kc, void* Vc, int32_t* len, int32_t cap, const void* k_new,
-                       const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st);
+                       const void* v_new, const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st);
 
 size_t allrows_workspace_bytes(const zipvl_dims& d);
 int launch_score_all_rows(const void* Q, const void* K, const zipvl_dims& d, float scale,
@@ -57,7 +59,7 @@ int launch_quantize_kv(const void* K, const void* V, const zipvl_dims& d, const 
                        int32_t* len_hi, int32_t* len_lo, int flags, void* ws, hipStream_t st);
 int launch_decode_attn_q(const void* q, const zipvl_qtensor& Kq, const zipvl_qtensor& Vq, const int32_t* len_hi,
                          const int32_t* len_lo, int32_t cap_hi, int32_t cap_lo, const void* Kt, const void* Vt,
-                         const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, hipStream_t st);
+                         const int32_t* len_t, int32_t cap_t, const zipvl_dims& d, float scale, void* o, void* ws, size_t ws_bytes, hipStream_t st);
 
 int launch_probe_mfma(int iters, int workgroups, float* out, hipStream_t st);
 int launch_probe_read(const void* src, size_t bytes, int workgroups, uint32_t* out, hipStream_t st);

@@ -256,10 +256,10 @@ int zipvl_decode_attn(const void* q, const void* Kc, const void* Vc, const int32
     if (!len) return set_error(ZIPVL_EINVAL, "%s: len is NULL", fn);
     if (cap < 1) return set_error(ZIPVL_EINVAL, "%s: cap = %d must be positive", fn, cap);
     if (!(softmax_scale > 0.f) || !(softmax_scale < 1e30f)) return set_error(ZIPVL_EINVAL, "%s: softmax_scale must be positive and finite", fn);
-    const size_t need = decode_workspace_bytes(*dims, cap);
+    const size_t need = decode_workspace_least(*dims, cap);
     if (!ws || ws_bytes < need) return set_error(ZIPVL_EWORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need, ws ? ws_bytes : (size_t)0);
     if (!aligned16(ws)) return set_error(ZIPVL_EALIGN, "%s: ws is not 16-byte aligned", fn);
-    return launch_decode_attn(q, Kc, Vc, len, cap, *dims, softmax_scale, o, ws, (hipStream_t)stream);
+    return launch_decode_attn(q, Kc, Vc, len, cap, *dims, softmax_scale, o, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int zipvl_decode_attn_static(const void* q, const void* Kc, const void* Vc, const int32_t* len, int32_t cap,
@@ -294,10 +294,10 @@ int zipvl_decode_step(const void* q, void* Kc, void* Vc, int32_t* len, int32_t c
     if (!len) return set_error(ZIPVL_EINVAL, "%s: len is NULL", fn);
     if (cap < 1) return set_error(ZIPVL_EINVAL, "%s: cap = %d must be positive", fn, cap);
     if (!(softmax_scale > 0.f) || !(softmax_scale < 1e30f)) return set_error(ZIPVL_EINVAL, "%s: softmax_scale must be positive and finite", fn);
-    const size_t need = decode_step_workspace_bytes(*dims, cap);
+    const size_t need = decode_step_workspace_least(*dims, cap);
     if (!ws || ws_bytes < need) return set_error(ZIPVL_EWORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need, ws ? ws_bytes : (size_t)0);
     if (!aligned16(ws)) return set_error(ZIPVL_EALIGN, "%s: ws is not 16-byte aligned", fn);
-    return launch_decode_step(q, Kc, Vc, len, cap, k_new, v_new, *dims, softmax_scale, o, ws, (hipStream_t)stream);
+    return launch_decode_step(q, Kc, Vc, len, cap, k_new, v_new, *dims, softmax_scale, o, ws, ws_bytes, (hipStream_t)stream);
 }
 
 static int check_qtensor(const char* fn, const char* what, const zipvl_qtensor* t) {
@@ -352,11 +352,11 @@ int zipvl_decode_attn_q(const void* q, const zipvl_qtensor* Kq, const zipvl_qten
         cap_tail = 0;
     }
     if (!(softmax_scale > 0.f) || !(softmax_scale < 1e30f)) return set_error(ZIPVL_EINVAL, "%s: softmax_scale must be positive and finite", fn);
-    const size_t need = decode_workspace_bytes(*dims, cap_hi + cap_lo + cap_tail);
+    const size_t need = decode_workspace_least(*dims, cap_hi + cap_lo + cap_tail);
     if (!ws || ws_bytes < need) return set_error(ZIPVL_EWORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need, ws ? ws_bytes : (size_t)0);
     if (!aligned16(ws)) return set_error(ZIPVL_EALIGN, "%s: ws is not 16-byte aligned", fn);
     return launch_decode_attn_q(q, *Kq, *Vq, len_hi, len_lo, cap_hi, cap_lo, K_tail, V_tail, len_tail, cap_tail,
-                                *dims, softmax_scale, o, ws, (hipStream_t)stream);
+                                *dims, softmax_scale, o, ws, ws_bytes, (hipStream_t)stream);
 }
 
 int zipvl_probe_mfma(int iters, int workgroups, float* out, void* stream)

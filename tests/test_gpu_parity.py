@@ -1641,6 +1641,44 @@ def test_decode_append_and_attention(dtype, d, Hq, Hkv):
     assert worst <= ATOL_OUT[dtype]
 
 
+@pytest.mark.parametrize("dtype,d,B,Hq,Hkv", [("bf16", 128, 1, 28, 4), ("bf16", 128, 2, 4, 4), ("f32", 128, 1, 7, 1), ("f32", 64, 1, 4, 4), ("bf16", 64, 1, 8, 1),
+                                              ("bf16", 128, 1, 18, 2), ("bf16", 128, 9, 7, 7)])
+@pytest.mark.parametrize("cap", [1, 64, 65, 129, 1000, 6400])
+def test_decode_splits_by_what_the_workspace_holds(dtype, d, B, Hq, Hkv, cap):
+    """Splits of fewer rows where few heads leave the chip idle: a workspace of the size asked for, and the smallest one (splits of 256 rows), in both
+    entry points, against the oracle; nothing is written past the end of either, and one byte less than the smallest is refused."""
+    say(f"decode splits {dtype} d={d} {B}x{Hq}/{Hkv} cap={cap}")
+    G, units = Hq // Hkv, B * Hkv
+    w = make_custom(B, Hq, Hkv, cap, d, dtype, seed=33)
+    Kc, Vc = (dev(x, dtype).reshape(units, cap, d) for x in (w.K, w.V))
+    lens = [max(0, cap - 1 - 37 * u) for u in range(units)]
+    r = np.random.Generator(np.random.PCG64(34))
+    cast = (lambda x: torch.from_numpy(x).bfloat16().float().numpy()) if dtype == "bf16" else (lambda x: x)
+    q, kn, vn = (cast(r.standard_normal((rows, d)).astype(np.float32)) for rows in (B * Hq, units, units))
+    refs = [oz.decode_step(q[i], kn[i // G], vn[i // G], Kc[i // G].float().cpu().numpy(), Vc[i // G].float().cpu().numpy(), lens[i // G], w.scale)[0]
+            for i in range(B * Hq)]
+    dm = z.dims_of(None, None, None, B=B, Hq=Hq, Hkv=Hkv, n=cap, d=d, dtype=1 if dtype == "bf16" else 0)
+    per = max(256, ((cap + 15) // 16 + 15) // 16 * 16)
+    least = max(min(-(-1024 // units), -(-cap // 256)), -(-cap // per)) * B * Hq * (d + 2) * 4
+    full, counters = z.workspace_bytes(z.OP_DECODE, dm), z.workspace_bytes(z.OP_DECODE_STEP, dm) - z.workspace_bytes(z.OP_DECODE, dm)
+    assert full >= least
+    for size in {full, least}:
+        K1, V1, ln = Kc.clone(), Vc.clone(), torch.tensor(lens, dtype=torch.int32, device=DEV)
+        room = torch.zeros(counters + size + 256, dtype=torch.uint8, device=DEV)
+        room[counters + size:] = 0xA5
+        args = dict(B=B, Hq=Hq, Hkv=Hkv)
+        step = z.zipvl_decode_step(dev(q, dtype), K1, V1, ln, dev(kn, dtype), dev(vn, dtype), w.scale, ws=room[:counters + size], **args)
+        assert ln.cpu().tolist() == [x + 1 for x in lens]
+        attn = z.zipvl_decode_attn(dev(q, dtype), K1, V1, ln, w.scale, ws=room[counters:counters + size], **args)
+        torch.cuda.synchronize()
+        assert torch.equal(step, attn)
+        assert bool((room[counters + size:] == 0xA5).all()) and not room[:counters].any()
+        worst = max(np.abs(host64(step[i]) - refs[i]).max() for i in range(B * Hq))
+        assert worst <= ATOL_OUT[dtype], f"{size} bytes: {worst:.3e}"
+    with pytest.raises(z.ZipvlError):
+        z.zipvl_decode_attn(dev(q, dtype), Kc, Vc, ln, w.scale, ws=room[counters:counters + least - 1], **args)
+
+
 @pytest.mark.parametrize("dtype,d,Hq,Hkv", [("bf16", 128, 4, 4), ("bf16", 128, 14, 2), ("f32", 64, 4, 2), ("bf16", 64, 3, 1),
                                             ("f32", 128, 8, 1), ("bf16", 128, 18, 2)])
 def test_decode_step_one_launch_matches_append_then_attention(dtype, d, Hq, Hkv):
