@@ -342,12 +342,14 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                     const int j0 = row0 + t0;
                     int before = 0;
                     marks[w][lane] = 0;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");       // other lanes' marks are neither before this nor behind the read below
 #pragma unroll
                     for (int e = 0; e < ZIPVL_MAX_PROBES; e += 64) {
                         const int pos = e + lane < m ? sp[e + lane] - j0 : 64;
                         before += __popcll(__ballot(pos < 0));
                         if (pos >= 0 && pos < 64) marks[w][pos] = 1;
                     }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     const uint64_t bits = __ballot(marks[w][lane]);
                     before += __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0));
                     const int cnt = m - before;

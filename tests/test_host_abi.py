@@ -123,6 +123,19 @@ def test_decode_attn_static_rejects_dims_beyond_its_scratch(lib):
     assert lib.zipvl_decode_attn_static(FAKE, FAKE, FAKE, None, 4096, C.byref(_dims()), C.c_float(0.1), FAKE, None) == -1
 
 
+@pytest.mark.parametrize("source,stored,taken", [
+    ("score.hip", "marks[w][lane] = 0;", "marks[w][pos] = 1;"),
+    ("score.hip", "marks[w][pos] = 1;", "__ballot(marks[w][lane])"),
+])
+def test_lds_between_lanes_of_a_wave_is_fenced(source, stored, taken):
+    """What a lane leaves in LDS for other lanes of its wave: without a fence between, the compiler may keep the order of one lane only, and
+    hand a lane what it stored itself."""
+    text = open(os.path.join(ROOT, "paper_2410_08584_amd", "csrc", source)).read()
+    assert text.count(stored) == 1 and text.count(taken) == 1
+    between = text[text.index(stored):text.index(taken)]
+    assert '__builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront")' in between
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     import paper_2410_08584_amd.binding as b
     monkeypatch.setattr(b, "_lib", None)
