@@ -683,6 +683,7 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         for (int a = 0; a < 4; ++a)
             store_out4<T>(reinterpret_cast<T*>(mine + out_chunk(i_out, 4 * db + a) + 8 * h_out), o[0][db][4 * a] * inv, o[0][db][4 * a + 1] * inv,
                           o[0][db][4 * a + 2] * inv, o[0][db][4 * a + 3] * inv);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the rows below are other lanes' stores
     const int w_out = KS == 1 ? tid_out >> 6 : (tid_out >> 6) % (NW / KS), lane_row = (tid_out & 63) / kOutLanes, c_out = tid_out % kOutLanes;
     const char* const held_out = smem + 4 * C::TILE_BYTES + (tid_out >> 6) * 256;
 #pragma unroll

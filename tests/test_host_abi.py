@@ -126,6 +126,7 @@ def test_decode_attn_static_rejects_dims_beyond_its_scratch(lib):
 @pytest.mark.parametrize("source,stored,taken", [
     ("score.hip", "marks[w][lane] = 0;", "marks[w][pos] = 1;"),
     ("score.hip", "marks[w][pos] = 1;", "__ballot(marks[w][lane])"),
+    ("attn.hip", "store_out4<T>(reinterpret_cast<T*>(mine + out_chunk(", "*reinterpret_cast<const uintx4*>(mine + out_chunk("),
 ])
 def test_lds_between_lanes_of_a_wave_is_fenced(source, stored, taken):
     """What a lane leaves in LDS for other lanes of its wave: without a fence between, the compiler may keep the order of one lane only, and
