@@ -1,11 +1,12 @@
-"""ctypes binding of include/zipvl.h.  Tensors are torch CUDA(HIP) tensors used
-purely as device memory; the stream is torch's current stream."""
+"""Binding of include/zipvl.h: ctypes, and before it the extension module _pycall for the calls that a layer and a decode
+step repeat.  Tensors are torch CUDA(HIP) tensors used purely as device memory; the stream is torch's current stream."""
 from __future__ import annotations
 
 import array
 import ctypes as C
 import os
 import struct
+import warnings
 from typing import Optional, Sequence, Tuple
 
 import torch
@@ -41,7 +42,14 @@ class QTensor(C.Structure):
 
 
 _lib = None
-_native = None               # the extension module _pycall: see _called
+_native = None               # the extension module _pycall, or _NoExtension: see _called
+
+
+class _NoExtension:
+    """In the place of _pycall where it does not load: takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
 
 
 def library_path() -> str:
@@ -59,9 +67,11 @@ def load_library():
                                "(there is no CPU fallback)")
     lib = C.CDLL(path)
     try:
-        from . import _pycall
-    except ImportError as e:
-        raise ZipvlError(-100, f"the extension module beside {path} does not load ({e}): build it with `python -m paper_2410_08584_amd.build`")
+        from . import _pycall as native
+    except Exception as e:                                   # not built, for another Python, a torch without what it looks up
+        warnings.warn(f"_pycall beside {path} does not load ({e!r}): every call goes through ctypes, 3 to 5 us slower; "
+                      "`python -m paper_2410_08584_amd.build` builds it", RuntimeWarning, stacklevel=2)
+        native = _NoExtension()
     vp, i32p, f32p = C.c_void_p, C.c_void_p, C.c_void_p
     lib.zipvl_version.restype = C.c_int
     lib.zipvl_last_error.restype = C.c_char_p
@@ -98,7 +108,7 @@ def load_library():
                  "zipvl_decode_attn_q", "zipvl_sparse_prefill", "zipvl_compact_kv", "zipvl_kv_append", "zipvl_decode_attn",
                  "zipvl_decode_step"):
         getattr(lib, name).restype = C.c_int
-    _native = _pycall
+    _native = native
     _lib = lib
     return lib
 

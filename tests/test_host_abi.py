@@ -145,6 +145,35 @@ def test_missing_library_fails_loudly(monkeypatch):
         b.load_library()
 
 
+@pytest.mark.parametrize("missing", [
+    "class Hidden:\n    def find_spec(self, name, path=None, target=None):\n        if name.endswith('._pycall'): raise ImportError('hidden')\nsys.meta_path.insert(0, Hidden())",
+    "del torch._C._cuda_getDevice",
+])
+def test_the_library_loads_without_the_extension_module(lib, missing):
+    """Where _pycall is absent, or torch lacks what it looks up, a warning says so and every call goes the general way: here to the library's own refusal."""
+    import subprocess
+    import sys
+    code = f"""
+import sys, warnings
+import torch
+{missing}
+import paper_2410_08584_amd as z
+from paper_2410_08584_amd import binding
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    assert z.zipvl_version() >= 100
+assert any("ctypes" in str(w.message) for w in seen)
+binding._stream = lambda: 0                      # no call below is launched
+x = torch.zeros(2, 16, 64)
+try:
+    z.zipvl_kv_append(x, x, x, x, x, B=-1, Hkv=2)
+except z.ZipvlError as e:
+    print("refused", e.code)
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120, cwd=ROOT)
+    assert r.stdout.split() == ["refused", "-1"], r.stderr
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU: any other count ends with a message and a non-zero status, before any GPU work."""
     import subprocess
