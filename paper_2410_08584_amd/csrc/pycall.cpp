@@ -132,7 +132,9 @@ struct Args {
     }
 };
 
+// What an argument raised the general way raises again; an interrupt (the calls into torch run Python code) would be lost.
 PyObject* general_way() {
+    if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_Exception)) return nullptr;
     PyErr_Clear();
     Py_RETURN_NONE;
 }

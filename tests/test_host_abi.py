@@ -174,6 +174,30 @@ except z.ZipvlError as e:
     assert r.stdout.split() == ["refused", "-1"], r.stderr
 
 
+def test_an_interrupt_inside_the_extension_module_reaches_the_caller(lib):
+    """Ctrl-C while _pycall asks torch for its stream, which runs Python code: not taken for an argument that the general way handles."""
+    import subprocess
+    import sys
+    code = """
+import torch
+def interrupted():
+    torch.cuda.is_initialized = lambda: True
+    raise KeyboardInterrupt
+torch.cuda.is_initialized = interrupted
+import paper_2410_08584_amd as z
+from paper_2410_08584_amd import binding
+z.load_library()
+binding._stream = lambda: 0                      # no call below is launched
+x = torch.zeros(2, 16, 64)
+try:
+    z.zipvl_kv_append(x, x, x, x, x, B=-1, Hkv=2)
+except BaseException as e:
+    print(type(e).__name__)
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120, cwd=ROOT)
+    assert r.stdout.split() == ["KeyboardInterrupt"], r.stdout + r.stderr
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py measures one GPU: any other count ends with a message and a non-zero status, before any GPU work."""
     import subprocess
