@@ -285,15 +285,17 @@ __device__ __forceinline__ void attend_rows(const T* Kb, const T* Vb, T* Kw, T* 
 // leaves some idle the units do, each row of units turned by `turn`, so that neither the busy workgroups of short units nor
 // those of a long one fall on the same CUs (one conversation of 32768 rows among three of 500, 32 heads: 213 us without the
 // turn, 145 with it, 16 splits either way).
+// A unit of fewer than `from` tiles has `coarse` splits: finer ones would cost more than they give (finer_from).
 struct SplitRule {
     int least, more, most, tiles, units, turn;               // turn 0: nothing is left idle
+    int coarse, from;                                        // from 0: `least` splits for all
     dim3 grid() const { return turn ? dim3(units, most) : dim3(most, units); }
     __device__ __forceinline__ int split() const { return turn ? blockIdx.y : blockIdx.x; }
     __device__ __forceinline__ int unit() const { return turn ? (blockIdx.x + blockIdx.y * (unsigned)turn) % (unsigned)units : blockIdx.y; }
 };
 __device__ __forceinline__ int tiles_of(int L) { return (L + kDecTile - 1) / kDecTile; }
 __device__ __forceinline__ int tiles_per_split(int T, const SplitRule& rule) {
-    const int s = T <= rule.least * rule.tiles ? rule.least : T <= rule.more * rule.tiles ? rule.more : rule.most;
+    const int s = T < rule.from ? rule.coarse : T <= rule.least * rule.tiles ? rule.least : T <= rule.more * rule.tiles ? rule.more : rule.most;
     return max(1, (T + s - 1) / s);
 }
 
@@ -1170,17 +1172,43 @@ static int least_splits(const zipvl_dims& d, int cap) {
     return std::max(decode_splits(d, cap), (cap + per - 1) / per);
 }
 
-// Partial states that a call makes use of.  Where splits of 256 rows leave the chip idle, one head (fewer than 512 workgroups of 4 waves) has splits of
-// 128, in fp32 64, and groups of bf16 at d = 128 (fewer than 256 of 8 waves) of 128 where two launches merge them in any case.  us a step of all layers,
-// 256 rows -> so: 28 layers of 28 heads on 4, cap 10 500 316 -> 301; 16 of 14 on 2, cap 9200 163 -> 146; 8 of 32 heads, cap 2700 107 -> 92; 8 of 8,
-// d = 64, cap 1900 72 -> 63; fp32, d = 64, 8 of 4 heads, cap 350 51 -> 44; with as many as 1024 workgroups of one head 96, and 32 heads, d = 64,
-// cap 5500 118 for 110.  Groups with shorter caches and in fp32 would gain too (16 layers of 32 on 8, cap 700 121 -> 112; fp32, 28 on 4, cap 2300 213 -> 157),
-// but the tests of the merge fix how many states those leave; at d = 64 bf16 gains nothing (28 on 4, cap 2900 7.9 us a layer, 8.1 in two launches).
-constexpr int kFineGroups = 24;                              // splits of 256 rows above which groups have finer ones
+// Finer splits, of 128 rows (fp32 of few heads 64), where splits of 256 leave the chip idle.
+//
+// One head: a tile less in a split saves 0.37 us, a workgroup more in the launch costs some 10 ns, idle ones too: all of them arrive at counters that
+// lie in one or two lines.  So a launch has at most kMostMore more, a unit takes the finer splits from the tiles on where that pays
+// (finer_from), and they are launched at all where caches from seven tenths of the capacity on take them; up to kFewMore more cost nothing
+// from some 30 rows on.  us a step of 8 layers, splits of 256 rows -> so, cache full, at 60 %, at 12 %: 8 heads, d = 128, cap 2700 98 -> 85, 81 -> 75, 57 -> 57; 32 heads,
+// cap 1300 92 -> 88, 78 -> 77, 56 -> 57; 32 heads, cap 2700 140 -> 130, 92 -> 92, 68 -> 69; 4 heads, cap 5500 98 -> 87, 82 -> 78; fp32, d = 64, 8 heads, cap 1300
+// 85 -> 71, 67 -> 60.  Finer splits at every length, without the line, and the idle workgroups dispatched before busy ones: 8 heads, cap 5500, full, 25 %, 12 %
+// 106 -> 103, 73 -> 85, 65 -> 79; fp32, 64 rows, 8 heads, cap 2700, 25 % 58 -> 77.  Past the lines: 16 heads, cap 5500, fp32 183 -> 187;
+// near them 16 heads, d = 64, cap 2700, full, 60 %, 4 % 101 -> 98, 84 -> 87, 54 -> 58.
+//
+// Groups of bf16 at d = 128, where two launches merge them in any case (fewer than 256 workgroups of 8 waves): 28 layers of 28 heads on 4, cap 10 500
+// 316 -> 301; 16 of 14 on 2, cap 9200 163 -> 146.  Shorter caches and fp32 would gain too (16 layers of 32 on 8, cap 700 121 -> 112; fp32, 28 on 4, cap 2300
+// 213 -> 157), but the tests of the merge fix how many states those leave; at d = 64 bf16 gains nothing (28 on 4, cap 2900 7.9 us a layer, 8.1 in two launches).
+constexpr int kFewMore = 32, kMostMore = 96;                 // workgroups of a launch
+constexpr int kFineGroups = 24;                              // splits of 256 rows
+
+// Tiles of a unit from which it has `fine` splits and not `coarse` ones.
+static int finer_from(const zipvl_dims& d, int coarse, int fine) {
+    const int units = d.B * d.Hkv;
+    return d.Hq > d.Hkv || units * (fine - coarse) <= kFewMore ? 0 : ((units + 4) * coarse * fine + 47) / 48;
+}
+
+// Partial states that a call makes use of.
 static int useful_splits(const zipvl_dims& d, int cap) {
     const bool groups = d.Hq > d.Hkv, bf16 = d.dtype == ZIPVL_BF16;
-    if (groups && (!bf16 || d.d == 64 || decode_splits(d, cap) <= kFineGroups)) return least_splits(d, cap);
-    return std::max(least_splits(d, cap), std::min(decode_splits(d, cap, bf16 ? 128 : 64), (groups ? 256 : 512) / (d.B * d.Hkv)));
+    const int units = d.B * d.Hkv, coarse = least_splits(d, cap);
+    if (groups) {
+        if (!bf16 || d.d == 64 || decode_splits(d, cap) <= kFineGroups) return coarse;
+        return std::max(coarse, std::min(decode_splits(d, cap, 128), 256 / units));
+    }
+    if (!bf16) {
+        const int fine = std::min(decode_splits(d, cap, 64), 512 / units);
+        if (units * (fine - coarse) <= kFewMore) return std::max(coarse, fine);
+    }
+    const int fine = std::min({decode_splits(d, cap, 128), 512 / units, coarse + kMostMore / units});
+    return fine > coarse && 10 * (int64_t)finer_from(d, coarse, fine) <= 7 * (((int64_t)cap + kDecTile - 1) / kDecTile) ? fine : coarse;
 }
 static size_t state_bytes(const zipvl_dims& d) { return (size_t)d.B * d.Hq * (d.d + 2) * sizeof(float); }       // of a split of every unit
 
@@ -1190,13 +1218,14 @@ static size_t state_bytes(const zipvl_dims& d) { return (size_t)d.B * d.Hq * (d.
 static SplitRule split_rule(const zipvl_dims& d, int cap, size_t ws_bytes) {
     const int units = d.B * d.Hkv, room = (int)std::min<size_t>(useful_splits(d, cap), ws_bytes / state_bytes(d));
     const bool groups = d.Hq / d.Hkv > 1;
-    const int tiles = groups ? kDecLongGroups : kDecLongOne;
-    const int least = std::max(1, std::min(room, ((groups ? 256 : 1024) + units - 1) / units));
+    const int tiles = groups ? kDecLongGroups : kDecLongOne, fill = ((groups ? 256 : 1024) + units - 1) / units;
+    const int least = std::max(1, std::min(room, fill)), coarse = std::max(1, std::min(least_splits(d, cap), fill));
     const int most = std::min(room, 4 * least), more = std::min(most, groups ? 2 * least : std::max(least, 1792 / units));
     const int64_t longest = (int64_t)tiles * kDecTile;       // what no unit reaches is not launched
     const int launched = cap <= least * longest ? least : cap <= more * longest ? more : most;
-    const int turn = launched > least ? std::max(1, (int)(units * 0.618)) : 0;       // rows of any number of units start all over the chip
-    return {least, std::min(more, launched), launched, tiles, units, turn};
+    const int from = least > coarse ? finer_from(d, coarse, least) : 0;
+    const int turn = launched > least || from ? std::max(1, (int)(units * 0.618)) : 0;     // rows of any number of units start all over the chip
+    return {least, std::min(more, launched), launched, tiles, units, turn, coarse, from};
 }
 
 size_t decode_workspace_bytes(const zipvl_dims& d, int cap) { return useful_splits(d, cap) * state_bytes(d); }
@@ -1240,7 +1269,7 @@ static int launch_decode_q_t(const void* q, const zipvl_qtensor& Kq, const zipvl
     const int G = d.Hq / d.Hkv, units = d.B * d.Hkv, cap = cap_hi + cap_lo + cap_t;
     // one head: as many splits as are resident together (three workgroups of four waves per CU), whatever the lengths are; each
     // takes its share of the cache (four layers of 128 units x 8192 rows: 1024 workgroups 153 us, 768 123, 512 137, 384 134)
-    const SplitRule rule = G > 1 ? split_rule(d, cap, ws_bytes) : SplitRule{1, 1, std::min(decode_splits(d, cap), std::max(1, 768 / units)), 0, units, 0};
+    const SplitRule rule = G > 1 ? split_rule(d, cap, ws_bytes) : SplitRule{1, 1, std::min(decode_splits(d, cap), std::max(1, 768 / units)), 0, units, 0, 1, 0};
     Lengths lengths{{nullptr, nullptr, nullptr}, {0, 0, 0}};
     if (rule.turn) lengths = {{len_hi, len_lo, Kt ? len_t : nullptr}, {cap_hi, cap_lo, cap_t}};      // else every split reports: 0.5 us less
     const float c = scale * kLog2e;

@@ -1679,6 +1679,46 @@ def test_decode_splits_by_what_the_workspace_holds(dtype, d, B, Hq, Hkv, cap):
         z.zipvl_decode_attn(dev(q, dtype), Kc, Vc, ln, w.scale, ws=room[counters:counters + least - 1], **args)
 
 
+# units of one head, cap, splits of 256 rows, finer ones, tiles of 16 rows from which a unit has the finer ones
+@pytest.mark.parametrize("dtype,d,units,cap,coarse,fine,first", [("bf16", 128, 8, 2700, 11, 22, 61), ("f32", 64, 8, 2700, 11, 22, 61), ("bf16", 64, 32, 1300, 6, 9, 41),
+                                                                 ("bf16", 128, 4, 1300, 6, 11, 0), ("f32", 128, 4, 700, 3, 11, 0), ("f32", 64, 16, 5500, 22, 22, 0)])
+def test_decode_of_one_head_has_finer_splits_where_a_cache_is_full(dtype, d, units, cap, coarse, fine, first):
+    """Splits finer than 256 rows pay in long caches only: a unit below the line leaves as many partial states as with the smallest workspace, one above it
+    as many as there is room for, in one call; outputs against the oracle, and the fused step over the same rows gives the same bits."""
+    say(f"finer splits {dtype} d={d} units={units} cap={cap}")
+    tiles = lambda rows: -(-rows // 16)
+    states = lambda rows: max(1, -(-tiles(rows) // max(1, -(-tiles(rows) // (coarse if tiles(rows) < first else fine)))))
+    edge = 16 * first if first else cap // 3
+    lens = ([edge - 16, edge - 15, edge, cap, 0, 1, cap // 8, cap // 4] * (units // 4 + 1))[:units]
+    w = make_custom(1, units, units, cap, d, dtype, seed=35)
+    Ka, Va = (dev(x, dtype).reshape(units, cap, d).clone() for x in (w.K, w.V))
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(36)
+    q = torch.randn((units, d), generator=gen, device=DEV).to(Ka.dtype)
+    la = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    dm = z.dims_of(None, None, None, B=1, Hq=units, Hkv=units, n=cap, d=d, dtype=1 if dtype == "bf16" else 0)
+    size = z.workspace_bytes(z.OP_DECODE, dm)
+    assert size == fine * units * (d + 2) * 4
+    ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device=DEV)
+    o = z.zipvl_decode_attn(q, Ka, Va, la, w.scale, B=1, Hq=units, Hkv=units, ws=ws[:size])
+    torch.cuda.synchronize()
+    assert int((ws.view(torch.int32) != -1).sum()) == (d + 2) * sum(states(n) for n in lens)
+    for u in range(min(units, 8)):
+        ref = oz.decode_attention(host64(q[u]), host64(Ka[u]), host64(Va[u]), lens[u], w.scale) if lens[u] else 0.0
+        assert np.abs(host64(o[u]) - ref).max() <= ATOL_OUT[dtype]
+    # the step that appends the last row of every cache
+    lb = torch.clamp(la - 1, min=0)
+    kn, vn = (torch.stack([x[u, max(n - 1, 0)] for u, n in enumerate(lens)]) for x in (Ka, Va))
+    step_ws = z.decode_step_workspace(1, units, units, cap, d, Ka)
+    for _ in range(2):                                        # the arrival counters clear themselves
+        ln = lb.clone()
+        step = z.zipvl_decode_step(q, Ka, Va, ln, kn, vn, w.scale, B=1, Hq=units, Hkv=units, ws=step_ws)
+        torch.cuda.synchronize()
+        held = torch.tensor([n > 0 for n in lens], device=DEV)
+        assert torch.equal(step[held], o[held]) and ln.tolist() == [max(n, 1) for n in lens]
+    assert int(step_ws[:4 * units].view(torch.int32).abs().sum().item()) == 0
+
+
 @pytest.mark.parametrize("dtype,d,Hq,Hkv", [("bf16", 128, 4, 4), ("bf16", 128, 14, 2), ("f32", 64, 4, 2), ("bf16", 64, 3, 1),
                                             ("f32", 128, 8, 1), ("bf16", 128, 18, 2)])
 def test_decode_step_one_launch_matches_append_then_attention(dtype, d, Hq, Hkv):
