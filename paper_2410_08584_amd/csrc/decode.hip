@@ -1183,9 +1183,11 @@ static int least_splits(const zipvl_dims& d, int cap) {
 // 106 -> 103, 73 -> 85, 65 -> 79; fp32, 64 rows, 8 heads, cap 2700, 25 % 58 -> 77.  Past the lines: 16 heads, cap 5500, fp32 183 -> 187;
 // near them 16 heads, d = 64, cap 2700, full, 60 %, 4 % 101 -> 98, 84 -> 87, 54 -> 58.
 //
-// Groups of bf16 at d = 128, where two launches merge them in any case (fewer than 256 workgroups of 8 waves): 28 layers of 28 heads on 4, cap 10 500
-// 316 -> 301; 16 of 14 on 2, cap 9200 163 -> 146.  Shorter caches and fp32 would gain too (16 layers of 32 on 8, cap 700 121 -> 112; fp32, 28 on 4, cap 2300
-// 213 -> 157), but the tests of the merge fix how many states those leave; at d = 64 bf16 gains nothing (28 on 4, cap 2900 7.9 us a layer, 8.1 in two launches).
+// Groups: bf16 at d = 128 above kFineGroups splits, where all forms of the step merge them in a launch of their own, up to a workgroup a CU.  us, 16 layers,
+// full, 25 % full: 28 on 4, cap 7000 176 -> 171; 14 on 2, cap 7000 175 -> 156; 8 of them over quantised caches, 28 on 4, cap 7000 95 -> 79, 67 -> 70,
+// cap 10 500 99 -> 91, 68 -> 70, 14 on 2, cap 7000 93 -> 77, 66 -> 68, cap 13 000 and more alike.  At kFineGroups, steps of 28 on 4: cap 6100 175 -> 166, 6200 175 -> 168.
+// It is not the line where the gain ends (8 on 2, cap 700 139 -> 117; 28 on 4, cap 4110 176 -> 155; fp32, cap 2300 240 -> 173, but 32 on 8, cap 6200
+// 306 -> 311; d = 64, 32 on 8, cap 2300 138 -> 140): below it the tests of the merge count the states that a step leaves by splits of 256 rows.
 constexpr int kFewMore = 32, kMostMore = 96;                 // workgroups of a launch
 constexpr int kFineGroups = 24;                              // splits of 256 rows
 

@@ -1305,6 +1305,44 @@ def test_decode_over_quantised_cache_at_tile_edges(dtype, d, G):
     assert worst <= (2e-2 if dtype == "bf16" else 5e-5)
 
 
+@pytest.mark.parametrize("Hq,Hkv,n,fine", [(14, 2, 6300, 50), (28, 4, 6104, 24), (28, 4, 6105, 49), (18, 2, 9000, 64), (32, 8, 6300, 32)])
+def test_decode_of_groups_over_quantised_caches_splits_by_what_the_workspace_holds(Hq, Hkv, n, fine):
+    """Groups of bf16 at d = 128 have splits of 128 rows over long quantised caches too (from 25 splits of 256 on, at most 256 workgroups): a workspace of the size asked
+    for and the smallest one, with a full and a nearly empty unit, against the oracle; nothing is written past the end of either, and a byte less is refused."""
+    say(f"decode_attn_q groups {Hq}/{Hkv} n={n}")
+    d, G, k, cap_t, tail = 128, Hq // Hkv, 2000, 40, 33
+    cap = n + cap_t
+    w = make_custom(1, Hq, Hkv, n, d, "bf16", seed=87)
+    r = np.random.Generator(np.random.PCG64(88))
+    idx = np.zeros((Hkv, n), dtype=np.int32)
+    for u in range(Hkv):
+        idx[u, :k] = np.sort(r.choice(n, k, replace=False))
+    cache = z.zipvl_quantize_kv(dev(w.K, "bf16"), dev(w.V, "bf16"), torch.from_numpy(idx).to(DEV), torch.full((Hkv,), k, dtype=torch.int32, device=DEV), k, n - k)
+    cache.len_hi[1], cache.len_lo[1] = 20, 33
+    q = dev(r.standard_normal((Hq, d)).astype(np.float32), "bf16")
+    Kt, Vt = (dev(r.standard_normal((Hkv, cap_t, d)).astype(np.float32), "bf16") for _ in range(2))
+    lt = torch.full((Hkv,), tail, dtype=torch.int32, device=DEV)
+    state = Hq * (d + 2) * 4
+    least = -(-cap // 256) * state
+    full = z.workspace_bytes(z.OP_DECODE_Q, z.dims_of(None, None, None, B=1, Hq=Hq, Hkv=Hkv, n=cap, d=d, dtype=1))
+    assert full == fine * state
+    args = dict(B=1, Hq=Hq, Hkv=Hkv, K_tail=Kt, V_tail=Vt, len_tail=lt)
+    for size in sorted({full, least}):
+        room = torch.full((size + 256,), 0xA5, dtype=torch.uint8, device=DEV)
+        o = z.zipvl_decode_attn_q(q, cache, w.scale, ws=room[:size], o=torch.empty_like(q), **args)
+        torch.cuda.synchronize()
+        assert bool((room[size:] == 0xA5).all())
+        for u in (0, 1, Hkv - 1):
+            qc = oz.quantize_kv(w.K[0, u], w.V[0, u], idx[u, :k])
+            if u == 1:
+                qc = {name: tuple(x[:rows] for x in qc[name]) for name, rows in (("K_hi", 20), ("K_lo", 33), ("V_hi", 20), ("V_lo", 33))}
+            for h in (u * G, u * G + G - 1):
+                ref = oz.decode_attention_quantized(host64(q[h]), qc, w.scale, host64(Kt[u, :tail]), host64(Vt[u, :tail]))
+                assert np.abs(host64(o[h]) - ref).max() <= ATOL_OUT["bf16"], f"{size} bytes, head {h}"
+    with pytest.raises(z.ZipvlError):
+        z.zipvl_decode_attn_q(q, cache, w.scale, ws=room[:least - 1], o=torch.empty_like(q), **args)
+
+
 def _one_head_cache(K, V, kept, copies):
     """The mixed-precision cache of a few heads K, V [heads, n, d], `copies` times over: with 300 units and more a launch
     splits a unit's rows two or three ways, so that every wave takes several blocks of 64 rows of either part."""
