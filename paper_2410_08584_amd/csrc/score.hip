@@ -387,8 +387,8 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                     auto kfrag = [&](int cc) { return fragment(krow, cc); };
                     floatx16 acc = {0};
                     // long chunks of few tasks are bound by memory, and faster where a wave with a tile waits for all stages on their way (40
-                    // heads, n = 18432, m = 64 68.8 -> 67.4 us)
-                    if (PASS == 1 && early == kStageBufs - 1 && S > 4 * (kStageBufs - 1)) __builtin_amdgcn_s_waitcnt(0x0F70);
+                    // heads, n = 18432, m = 64 68.8 -> 67.4 us; at d = 64 4 x 32 heads 111.5 -> 118)
+                    if (PASS == 1 && D == 128 && early == kStageBufs - 1 && S > 4 * (kStageBufs - 1)) __builtin_amdgcn_s_waitcnt(0x0F70);
                     // bf16: the fragments of the key block are read ahead of the products (four while 128 registers hold no more; two at
                     // a time: 14 heads on 2, n = 33000, m = 128 84.7 -> 80.3 us); an fp32 one feeds four products of 64 cycles
                     constexpr int kReads = C::E == 4 ? 1 : CH;
