@@ -40,7 +40,8 @@ constexpr int kStageBufs = 4;               // stage buffers in LDS: three stage
 // next tile instead, as in the exact scores, a tile took 15 % longer: four waves a SIMD, a barrier every one to four tiles).  us, rows gathered by
 // lanes behind three stages of keys, pairs of statistics, scores made by the last waves -> now: 40 heads, n = 4096, 64 recent and 64 random
 // probes 37.2 -> 31.8; 28 on 4, n = 18432 35.0 -> 32.6; 32, n = 3072 19.7 -> 17.0; 32, n = 20000, m = 128 78.6 -> 67.5; 28 on 4, fp32, n = 12000,
-// m = 128 224 -> 201; 4, fp32, d = 64, n = 576 14.4 -> 12.4; bound by memory, 40, n = 18432 67.4 -> 67.0; 28 tasks at d = 64, n = 4096 22.6 -> 23.1.
+// m = 128 224 -> 201; 4, fp32, d = 64, n = 576 14.4 -> 12.4; bound by memory, 40, n = 18432 67.4 -> 67.0; at d = 64 28 on 4, n = 4096,
+// m = 128 22.5 -> 22.1, 4 x 32, n = 18432 112.5 -> 110.5, 32 on 2, n = 1000, m = 128 28.6 -> 28.9.
 //
 // NWV waves per workgroup.  16 waves (one workgroup per CU): stages of 32 KiB; 8 waves (two per CU): 16 KiB;
 // never more than 128 keys (the column-sum buffers grow with the keys of a stage).
@@ -71,7 +72,8 @@ constexpr float kWholeOffset = 100.f;
 // PASS 2: mass / rank of the workgroup's keys; nsplit = chunks of pass 1
 // np = probe rows rounded up to a multiple of 32 (NB blocks); rows beyond m are masked out.
 // bpc = 32-key blocks per chunk of this pass; tpg = tasks per workgroup of pass 1, at most NWV.
-template <typename T, int D, int PASS, int NWV>
+// BY_STAGE (pass 2): scores are made stage by stage (scores_by_stage; known to the compiler: 2 to 3 % of short calls).
+template <typename T, int D, int PASS, int NWV, bool BY_STAGE>
 __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV == 8) ? 2 : 4) void score_kernel(
     const T* __restrict__ Q, const T* __restrict__ K,
     int64_t qs0, int64_t qs1, int64_t qs2, int64_t ks0, int64_t ks1, int64_t ks2,
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     __shared__ float2 wstat[PASS == 1 ? NWV : 1][32];                // pass 1: per-wave row statistics
     __shared__ __attribute__((aligned(16))) float row_bias[PASS == 2 ? NWV : 1][32];
     __shared__ unsigned char marks[PASS == 2 ? NWV : 1][64];        // pass 2: which of a wave's 64 keys are probes
-    __shared__ float keysum[PASS == 2 ? (kSumStages - 1) * SK : 1];  // pass 2: sums of up to kSumStages - 1 stages
+    __shared__ float keysum[PASS == 2 && !BY_STAGE ? (kSumStages - 1) * SK : 1];     // pass 2: sums of up to kSumStages - 1 stages
     __shared__ float colbuf[PASS == 2 ? 2 : 1][PASS == 2 ? NWV : 1][PASS == 2 ? SK : 1];
 
     const int G = Hq / Hkv, np = NB * 32;
@@ -109,7 +111,6 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     const int rounds = PASS == 1 || few ? 1 : (NT + NWV - 1) / NWV;
     const int ts = few ? w % NT : w;                                 // task slot inside a round
     const int slot = few ? w / NT : 0;
-    const int w_last_slot = (NWV - 1) / NT;                          // the last wave's, if it has a task
 
     // where this lane's NLD 16-byte pieces of a stage come from: row inside the stage and chunk under the row swizzle
     const char* Ku = reinterpret_cast<const char*>(K + b * ks0 + (g / kv_div) * ks1);   // kv_div > 1: every query head is its own unit
@@ -300,10 +301,8 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             }
         };
         if (kHeldBias) load_bias();
-        // PASS 2: the scores of a stage's keys.  Every wave waits for them at the next barrier.  Where the last waves have no tile they make them
-        // meanwhile, stage by stage; else these add up the tasks' sums only, and what makes scores of them is left for kSumStages stages
-        // at a time, to all waves.
-        const bool idle = few && (w_last_slot >= KBS || NWV > NT * KS);
+        // PASS 2: the scores of a stage's keys, which every wave waits for at the next barrier: made by the last waves, or (BY_STAGE false) these add up
+        // the tasks' sums only, and what makes scores of them is left for kSumStages stages at a time, to all waves.
         // The tasks' column sums, in task order.
         auto key_sum = [&](int s, int t) {
             const float* col = &colbuf[s & 1][0][t];
@@ -369,7 +368,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             __syncthreads();
             if (s + kStageBufs - 1 < S) issue_stage(s + kStageBufs - 1);
             if (PASS == 2 && s > 0) {
-                if (idle || s % kSumStages == 0) write_scores(idle ? s - 1 : s - kSumStages, s);
+                if (BY_STAGE || s % kSumStages == 0) write_scores(BY_STAGE ? s - 1 : s - kSumStages, s);
                 else sum_stage(s - 1);
             }
             const int buf = s & 1;                                   // column-sum buffer of the stage
@@ -445,7 +444,7 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
         }
         if (PASS == 2) {
             __syncthreads();                                         // the last stage's column sums are in LDS
-            write_scores(idle ? S - 1 : (S - 1) / kSumStages * kSumStages, S);
+            write_scores(BY_STAGE ? S - 1 : (S - 1) / kSumStages * kSumStages, S);
         }
 
         if (PASS == 1) {
@@ -537,16 +536,25 @@ static RowStatsPlan row_stats_plan(int NT, int units, int nblk, int row_bytes, i
     return best;
 }
 
-template <typename T, int D, int PASS, int NWV>
+template <typename T, int D, int PASS, int NWV, bool BY_STAGE = true>
 static int reserve_lds() {
     static std::atomic<bool> done{false};                            // raising the dynamic-LDS cap is idempotent
     if (!done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&score_kernel<T, D, PASS, NWV>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&score_kernel<T, D, PASS, NWV, BY_STAGE>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, kStageBufs * ScoreCfg<T, D, NWV>::STG) != hipSuccess)
             return set_error(ZIPVL_EHIP, "score: cannot reserve LDS for the key stages");
         done = true;
     }
     return ZIPVL_OK;
+}
+
+// Whether 8 waves make the scores of a chunk of `bpc` key blocks stage by stage (16 always do): where waves without a tile are there for it, and where the
+// chunk has two stages at most.  us, eight stages at a time -> stage by stage: 28 heads on 4, n = 18432 32.4 -> 31.7,
+// 32 on 2, d = 64, n = 1000, m = 128 29.8 -> 29.0; 8 waves, d = 64, 4 x 32 heads, n = 577 (2 stages) 14.5 -> 14.2; past the line 4 x 32 heads, n = 4096,
+// m = 128 (16 stages) 62.4 -> 63.8, 32, d = 64, n = 8192 (4) 3 % slower.
+static bool scores_by_stage(int NT, int key_blocks, int bpc) {
+    const int last_slot = 7 / NT;                                    // of the last wave, if it has a task
+    return (NT < 8 && (last_slot >= key_blocks || 8 > NT * (8 / NT))) || bpc <= 2 * key_blocks;
 }
 
 // NW2: waves per workgroup of pass 2 (pass 1: 8)
@@ -560,27 +568,33 @@ static int launch_score_w(const void* Q, const void* K, const zipvl_dims& d, con
     constexpr size_t lds1 = (size_t)kStageBufs * ScoreCfg<T, D, 8>::STG, lds2 = (size_t)kStageBufs * ScoreCfg<T, D, NW2>::STG;
     int rc = reserve_lds<T, D, 1, 8>();
     if (rc) return rc;
-    rc = reserve_lds<T, D, 2, NW2>();
-    if (rc) return rc;
     const int nblk1 = (n_eff + 31) / 32;
     const RowStatsPlan plan = row_stats_plan(NT, units, nblk1, D * (int)sizeof(T), NW2, Elem<T>::kBytes == 4);
     const int groups = plan.groups, tpg = (NT + groups - 1) / groups, bpc1 = plan.bpc, nsplit = (nblk1 + bpc1 - 1) / bpc1;
     const int nblk2 = (d.n + 31) / 32, bpc2 = blocks_per_chunk(nblk2, units, resident_slots(NW2)), chunks2 = (nblk2 + bpc2 - 1) / bpc2;
     {
         KernelTimer tm(ZIPVL_K_SCORE_ROWSTATS, st);
-        hipLaunchKernelGGL((score_kernel<T, D, 1, 8>), dim3(nsplit, units, groups), dim3(512), lds1, st,
+        hipLaunchKernelGGL((score_kernel<T, D, 1, 8, true>), dim3(nsplit, units, groups), dim3(512), lds1, st,
             (const T*)Q, (const T*)K, d.q_strides[0], d.q_strides[1], d.q_strides[2],
             d.k_strides[0], d.k_strides[1], d.k_strides[2], pl, m, NB, d.n, n_eff, c, partial, nsplit, bpc1, tpg,
             (float*)nullptr, (float*)nullptr, d.Hq, d.Hkv, kv_div);
     }
     rc = check_launch("score_rowstats");
     if (rc) return rc;
-    KernelTimer tm(ZIPVL_K_SCORE_COLSUM, st);
-    hipLaunchKernelGGL((score_kernel<T, D, 2, NW2>), dim3(chunks2, units), dim3(64 * NW2), lds2, st,
-        (const T*)Q, (const T*)K, d.q_strides[0], d.q_strides[1], d.q_strides[2],
-        d.k_strides[0], d.k_strides[1], d.k_strides[2], pl, m, NB, d.n, n_eff, c, partial, nsplit, bpc2, NT,
-        mass, rank, d.Hq, d.Hkv, kv_div);
-    return check_launch("score_colsum");
+    auto pass2 = [&](auto by_stage) -> int {
+        constexpr bool kByStage = decltype(by_stage)::value;
+        rc = reserve_lds<T, D, 2, NW2, kByStage>();
+        if (rc) return rc;
+        KernelTimer tm(ZIPVL_K_SCORE_COLSUM, st);
+        hipLaunchKernelGGL((score_kernel<T, D, 2, NW2, kByStage>), dim3(chunks2, units), dim3(64 * NW2), lds2, st,
+            (const T*)Q, (const T*)K, d.q_strides[0], d.q_strides[1], d.q_strides[2],
+            d.k_strides[0], d.k_strides[1], d.k_strides[2], pl, m, NB, d.n, n_eff, c, partial, nsplit, bpc2, NT,
+            mass, rank, d.Hq, d.Hkv, kv_div);
+        return check_launch("score_colsum");
+    };
+    if constexpr (NW2 == 8)
+        if (!scores_by_stage(NT, ScoreCfg<T, D, NW2>::KBS, bpc2)) return pass2(std::false_type{});
+    return pass2(std::true_type{});
 }
 
 template <typename T, int D>

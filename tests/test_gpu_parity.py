@@ -335,6 +335,26 @@ def test_scores_of_wide_groups(dtype, d, G, Hkv, n, m):
     assert_scores_close(host64(rank), ro, dtype, "rank")
 
 
+# chunks of 2, 3, 8, 9 and more stages with 8 waves (scores stage by stage up to 2, eight stages at a time from 3 on), rounds of 16 waves
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,n,m", [("bf16", 64, 32, 32, 4096, 64), ("bf16", 64, 32, 32, 4097, 64), ("bf16", 64, 128, 128, 4096, 64), ("bf16", 64, 128, 128, 4200, 64),
+                                                ("bf16", 128, 32, 32, 2048, 128), ("bf16", 128, 32, 32, 2049, 128), ("bf16", 64, 128, 128, 8300, 128), ("f32", 64, 128, 128, 2100, 96),
+                                                ("bf16", 64, 36, 4, 3000, 64), ("bf16", 128, 36, 4, 3000, 64)])
+def test_scores_of_chunks_of_few_and_many_stages(dtype, d, Hq, Hkv, n, m):
+    """The last 32 and random probe rows against the oracle, in the first, a middle and the last KV head."""
+    say(f"score {dtype} d={d} Hq={Hq} Hkv={Hkv} n={n} m={m}")
+    G, gen = Hq // Hkv, torch.Generator(device=DEV)
+    gen.manual_seed(78)
+    Q, K = (torch.randn((1, h, n, d), generator=gen, device=DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32) for h in (Hq, Hkv))
+    r = np.random.Generator(np.random.PCG64(79))
+    pos = sorted([int(x) for x in r.choice(n - 32, m - 32, replace=False)] + list(range(n - 32, n)))
+    mass, rank = z.zipvl_score(Q, K, pos, d ** -0.5)
+    torch.cuda.synchronize()
+    for g in (0, Hkv // 2, Hkv - 1):
+        mo, ro = oz.token_scores(host64(Q[0, g * G : g * G + G]), host64(K[0, g : g + 1]), np.array(pos), d ** -0.5)
+        assert_scores_close(host64(mass[g : g + 1]), mo, dtype, "mass")
+        assert_scores_close(host64(rank[g : g + 1]), ro, dtype, "rank")
+
+
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,n", [("bf16", 128, 4, 4, 1500), ("bf16", 64, 28, 4, 700), ("f32", 64, 4, 2, 333), ("f32", 128, 20, 2, 200)])
 def test_scores_of_rows_whose_sums_do_not_fit_one_number(dtype, d, Hq, Hkv, n):
     """Sums of exp2 beyond 2^100 and below 2^-100, in some chunks, rows and heads and not in others, and a row that is not a number.
