@@ -355,6 +355,26 @@ def test_scores_of_chunks_of_few_and_many_stages(dtype, d, Hq, Hkv, n, m):
         assert_scores_close(host64(rank[g : g + 1]), ro, dtype, "rank")
 
 
+# bytes from a row of Q to the next, rows: 16 MiB and more (addresses of 64 bits), below with rows from 2 GiB on (offsets of 32 bits without a sign), below and 4 GiB in all
+@pytest.mark.parametrize("row_bytes,n", [((16 << 20) + 256, 70), (15 << 20, 200), (15 << 20, 290)])
+@pytest.mark.parametrize("dtype,d,Hq,Hkv", [("bf16", 128, 4, 2), ("bf16", 128, 10, 1), ("f32", 128, 3, 3), ("f32", 128, 10, 1), ("f32", 64, 4, 4), ("bf16", 64, 2, 2)])
+def test_scores_of_queries_in_rows_far_apart(dtype, d, Hq, Hkv, row_bytes, n):
+    """Probe rows of a Q whose rows lie up to 4 GiB and further from its first one: bit for bit the scores of the contiguous Q."""
+    say(f"score {dtype} d={d} Hq={Hq} Hkv={Hkv} n={n} rows {row_bytes} bytes apart")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(83)
+    Q, K = (torch.randn((1, h, n, d), generator=gen, device=DEV).to(torch.bfloat16 if dtype == "bf16" else torch.float32) for h in (Hq, Hkv))
+    stride = row_bytes // Q.element_size()
+    far = torch.empty((n * stride,), dtype=Q.dtype, device=DEV).as_strided((1, Hq, n, d), (0, d, stride, 1))
+    far.copy_(Q)
+    r = np.random.Generator(np.random.PCG64(84))
+    pos = sorted([0, n - 1] + [int(x) for x in r.choice(np.arange(1, n - 1), 57, replace=False)])
+    near = z.zipvl_score(Q, K, pos, d ** -0.5)
+    got = z.zipvl_score(far, K, pos, d ** -0.5)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(near, got)) and bool((got[0] > 0).all())
+
+
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,n", [("bf16", 128, 4, 4, 1500), ("bf16", 64, 28, 4, 700), ("f32", 64, 4, 2, 333), ("f32", 128, 20, 2, 200)])
 def test_scores_of_rows_whose_sums_do_not_fit_one_number(dtype, d, Hq, Hkv, n):
     """Sums of exp2 beyond 2^100 and below 2^-100, in some chunks, rows and heads and not in others, and a row that is not a number.
@@ -2039,10 +2059,21 @@ def test_decode_of_head_groups_at_tile_edges(dtype, d, G):
 
 # ------------------------------------------------------------------ calls without ctypes
 def test_calls_of_the_extension_module_are_the_general_ones(monkeypatch):
-    """Every call that _pycall takes, then the same call the general way: the same bits.  Calls that it leaves to the general way, and
+    """_pycall takes each of the calls; then the same call the general way: the same bits.  Calls that it leaves to the general way, and
     calls that the library refuses: the same errors."""
     say("extension module against ctypes")
     from paper_2410_08584_amd import binding
+    binding.load_library()
+    module, answers = binding._native, []
+
+    class Recorder:
+        def __getattr__(self, name):
+            def call(*args):
+                answers.append((name, getattr(module, name)(*args)))
+                return answers[-1][1]
+            return call
+
+    monkeypatch.setattr(binding, "_native", Recorder())
     B, Hq, Hkv, n, d = 2, 4, 2, 500, 64
     w = make_custom(B, Hq, Hkv, n, d, "bf16", seed=81, m=64)
     Q, K, V = (dev(x, "bf16") for x in (w.Q, w.K, w.V))
@@ -2094,7 +2125,14 @@ def test_calls_of_the_extension_module_are_the_general_ones(monkeypatch):
             out.append((type(e.value), str(e.value)))
         return out
 
-    direct, refused = calls(), refusals()
+    direct = calls()
+    assert sorted(answers) == [(name, 0) for name in ("compact_kv", "decode_attn_q", "decode_step", "kv_append", "score", "select", "sparse_prefill")]
+    answers.clear()
+    refused = refusals()
+    # the library's own refusals; None: dtype, strides or shape that the general way handles
+    taken = [("score", True)] * 3 + [("score", False)] * 3 + [("select", True), ("sparse_prefill", True), ("compact_kv", True), ("kv_append", True),
+                                                                ("decode_step", True), ("decode_step", False)]
+    assert [(name, rc is not None) for name, rc in answers] == taken and all(rc is None or rc < 0 for _, rc in answers)
     took = []
 
     class General:
