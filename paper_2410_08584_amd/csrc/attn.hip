@@ -46,7 +46,7 @@ namespace zipvl {
 
 constexpr int kBN = 64;      // keys per tile
 // Launch shape: 4 waves x 32 queries, or (launch_prefill_t) 2 x 32 queries x 2 key blocks.  Measured alternatives: 8 waves per
-// workgroup (half the L2 -> LDS traffic per query) is 3 % slower; 64 queries per wave (QB = 2, half the LDS operand reads per
+// workgroup (half the L2 -> LDS traffic per query) is 3 % slower; 64 queries per wave (half the LDS operand reads per
 // MFMA) does not fit the register file with the S^T double buffer and spills.
 constexpr int kFillSpan = 512;       // positions per workgroup that clears dropped output rows
 // Every workgroup reads all kept counts of a call (64 a load) unless they are more than kScanSets; a call of up to kScanBlocks
@@ -87,14 +87,13 @@ struct SplitCfg {
     static constexpr int CH = D / 16, ODB = D / 32;
 };
 
-// NW = waves per workgroup, QB = 32-query blocks per wave: a workgroup covers 32 QB NW kept queries, its
-// K / V^T tiles are fetched from L2 once per that many queries, and every LDS operand fragment a wave
-// reads feeds QB matrix instructions.
+// NW = waves per workgroup, of 32 queries each: a workgroup covers 32 NW kept queries, its K / V^T tiles are
+// fetched from L2 once per that many queries.
 // KS = 2: two waves share 32 queries and take one 32-key block of every tile each (their sums meet at the end).
-template <typename T, int D, int NW = 4, int QB = 1, int KS = 1>
+template <typename T, int D, int NW = 4, int KS = 1>
 struct AttnCfg {
     static constexpr int E = Elem<T>::kBytes;
-    static constexpr int BM = 32 * QB * NW / KS;             // queries per workgroup
+    static constexpr int BM = 32 * NW / KS;                  // queries per workgroup
     static constexpr int NBK = 2 / KS;                       // 32-key blocks of a tile per wave
     static constexpr int NT = 64 * NW;                       // threads per workgroup
     static constexpr int CH = D / Elem<T>::kPerChunk;       // Q/K fragments per row per lane
@@ -106,9 +105,8 @@ struct AttnCfg {
     static constexpr int TILE_BYTES = kBN * D * E;           // one K tile = one V tile
     static constexpr int NLD = TILE_BYTES / 1024 / NW;       // 1-KiB direct-to-LDS loads per wave per tile
     static constexpr int LDS_BYTES = E == 4 ? SplitCfg<D, KS>::LDS_BYTES : 4 * TILE_BYTES + 256 * NW;     // two K and two V buffers, positions of a wave's queries
-    // QB = 1: two waves per SIMD (<= 256 registers, accumulators stay in VGPRs), three for fp32 at d = 64 in workgroups of four;
-    // otherwise one wave per SIMD with the whole 512-entry register file
-    static constexpr int MIN_WGS = QB == 1 ? E == 4 ? (D == 64 && NW == 4 ? 3 : 2) : 8 / NW : 1;
+    // two waves per SIMD (<= 256 registers, accumulators stay in VGPRs), three for fp32 at d = 64 in workgroups of four
+    static constexpr int MIN_WGS = E == 4 ? (D == 64 && NW == 4 ? 3 : 2) : 8 / NW;
 };
 
 // ------------------------------------------------------------------ pack
@@ -214,33 +212,29 @@ __device__ __forceinline__ void tile_to_lds(const char* gtile, unsigned lds_dst,
     }
 }
 
-// S^T = K Q^T for 32 keys (block blk of the 64-key tile in LDS buffer kb) and the wave's QB query blocks:
-// acc[qb][blk][r] = key 32*blk + acc_row(r, h), this lane's query of block qb.  A K fragment is read once for all QB.
-template <typename T, int D, int NW, int QB, int KS>
+// S^T = K Q^T for 32 keys (block blk of the 64-key tile in LDS buffer kb) and the wave's queries:
+// acc[blk][r] = key 32*blk + acc_row(r, h), this lane's query.
+template <typename T, int D, int NW, int KS>
 __device__ __forceinline__ void qk_block(const char* kb, int blk, int i, int h, int sw,
-                                         const uintx4 (&qf)[QB][AttnCfg<T, D, NW, QB, KS>::CH], floatx16 (&acc)[QB][AttnCfg<T, D, NW, QB, KS>::NBK]) {
-    using C = AttnCfg<T, D, NW, QB, KS>;
-    floatx16 a[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) a[qb] = floatx16{0};
+                                         const uintx4 (&qf)[AttnCfg<T, D, NW, KS>::CH], floatx16 (&acc)[AttnCfg<T, D, NW, KS>::NBK]) {
+    using C = AttnCfg<T, D, NW, KS>;
+    floatx16 a = {0};
 #pragma unroll
     for (int cc = 0; cc < C::CH; ++cc) {
         const uintx4 kf = *reinterpret_cast<const uintx4*>(kb + (blk * 32 + i) * C::KRB + swz_chunk(2 * cc + h, sw));
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) a[qb] = mma_frag<T>(kf, qf[qb][cc], a[qb]);
+        a = mma_frag<T>(kf, qf[cc], a);
     }
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) acc[qb][blk] = a[qb];
+    acc[blk] = a;
 }
 
-// O^T += V^T P^T for the 32 keys of half HALF: p[qb][HALF] holds the probabilities of S^T block HALF of query block qb.
-template <typename T, int D, int NW, int QB, int KS> struct PV;
+// O^T += V^T P^T for the 32 keys of half HALF: p[HALF] holds the probabilities of S^T block HALF.
+template <typename T, int D, int NW, int KS> struct PV;
 
-template <int D, int NW, int QB, int KS> struct PV<__bf16, D, NW, QB, KS> {
-    using C = AttnCfg<__bf16, D, NW, QB, KS>;
-    // p[qb][blk][s2]: the probabilities of S^T block blk as P^T operand fragments.  Contraction slot t of
+template <int D, int NW, int KS> struct PV<__bf16, D, NW, KS> {
+    using C = AttnCfg<__bf16, D, NW, KS>;
+    // p[blk][s2]: the probabilities of S^T block blk as P^T operand fragments.  Contraction slot t of
     // this lane <-> key 16*s2 + 8*(t/4) + 4*h + t%4 of the block = accumulator register 8*s2 + t.
-    using Probs = uintx4[QB][C::NBK][2];
+    using Probs = uintx4[C::NBK][2];
     // The matching V^T operand (lane = channel 32 db + lane % 32, slots = those 8 keys) comes from the
     // row-major V tile through ds_read_b64_tr_b16: in every group of 16 lanes, lane 4e + q supplies the
     // address of 4 consecutive channels of key e, and lane l receives channel l of keys 0..3.  Two reads
@@ -255,7 +249,7 @@ template <int D, int NW, int QB, int KS> struct PV<__bf16, D, NW, QB, KS> {
     }
     template <int HALF>
     __device__ static __forceinline__ void run(const char* vb, const int (&lane_off)[C::ODB], const Probs& p,
-                                               floatx16 (&o)[QB][C::ODB]) {
+                                               floatx16 (&o)[C::ODB]) {
         typedef short shortx4 __attribute__((ext_vector_type(4)));
         using lds_ptr = __attribute__((address_space(3))) shortx4*;
 #pragma unroll
@@ -266,8 +260,7 @@ template <int D, int NW, int QB, int KS> struct PV<__bf16, D, NW, QB, KS> {
                 const uintx2 lo = __builtin_bit_cast(uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)a0));
                 const uintx2 hi = __builtin_bit_cast(uintx2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(a0 + 8 * C::VRB)));
                 const uintx4 vf = {lo[0], lo[1], hi[0], hi[1]};
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb) o[qb][db] = mma_frag<__bf16>(vf, p[qb][HALF][s2], o[qb][db]);
+                o[db] = mma_frag<__bf16>(vf, p[HALF][s2], o[db]);
             }
         }
     }
@@ -295,21 +288,21 @@ template <> __device__ __forceinline__ void store_out4<__bf16>(__bf16* dst, floa
 }
 
 // The kept queries i0 ... i0 + BM - 1 of one head by one workgroup.  Q: rows of the head; Kp, Vp: rows of its unit; O: of the head.
-template <typename T, int D, int NW, int QB, int KS>
+template <typename T, int D, int NW, int KS>
 __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t qs2, const T* __restrict__ Kp, const T* __restrict__ Vp,
                                               const int32_t* __restrict__ tidx, T* __restrict__ O, int i0, int kk, int npad, float c,
                                               int out_compact, int k_in_place, int v_in_place)
 {
-    using C = AttnCfg<T, D, NW, QB, KS>;
-    constexpr int kBM = C::BM, kRW = 32 * QB;                // queries per workgroup, queries per wave
+    using C = AttnCfg<T, D, NW, KS>;
+    constexpr int kBM = C::BM, kRW = 32;                     // queries per workgroup, queries per wave
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int tid = threadIdx.x;
     if constexpr (KS == 1) asm volatile("" : "+v"(tid));     // nothing of a lane is kept from one tile of queries for the next
     const int w = tid >> 6, lane = tid & 63, i = lane & 31, h = lane >> 5;
     // KS = 2: wave w has the queries of wave qw and key block kw of every tile
     const int qw = KS == 1 ? w : w % (NW / KS), kw = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(w / (NW / KS));
-    floatx16 o[QB][C::ODB];
-    float m_run[QB], l_run[QB];
+    floatx16 o[C::ODB];
+    float m_run, l_run;
 
     const int ntiles = (min(i0 + kBM, kk) + kBN - 1) / kBN;
     const int wave_first_row = i0 + kRW * qw, wave_last_row = wave_first_row + kRW - 1;
@@ -331,7 +324,7 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     lds_fill_offsets<C::KRB, NW, C::NLD>(w, lane, koff);
     lds_fill_offsets<C::VRB, NW, C::NLD, true>(w, lane, voff);
     int vlane[C::ODB];
-    PV<T, D, NW, QB, KS>::lane_offsets(lane, vlane);
+    PV<T, D, NW, KS>::lane_offsets(lane, vlane);
 
     const unsigned klds = lds_address(Kb0) + w * 1024, vlds = lds_address(Vb0) + w * 1024;
     auto load_k = [&](int t, int buf) {
@@ -345,7 +338,6 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     // took the address unit 64 clocks a load).  The rows lie where V tiles go from the first step on, in the swizzle of K rows.  A workgroup of
     // 17 steps had its rows 3.2 us after it asked for tiles, 3.0 so; with the rows of the output (below), calls with their sets and caches,
     // us: 4 x 32 heads, a third kept, n = 4000 120 -> 115, 32, n = 2933 39.7 -> 38.6, 28 on 4, n = 18432, 39 % 358 -> 353, d = 64, 3 x 40, n = 8000, a fifth 109.5 -> 107.
-    static_assert(QB == 1, "32 queries a wave");
     constexpr int kRowLanes = C::KRB / 16, kRowsAtOnce = 64 / kRowLanes, kQueryLoads = 32 / kRowsAtOnce;
     char* const held = smem + 4 * C::TILE_BYTES + w * 256;
     char* const rows_lds = Vb0 + w * 32 * C::KRB;
@@ -367,11 +359,11 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         load_kib_to_lds_at(reinterpret_cast<const char*>(Q + (int64_t)pos * qs2) + swz_chunk(lane % kRowLanes, k_row_swizzle<C::KRB>(r)),
                            lds_address(rows_lds) + q * 1024);
     }
-    int qrow[QB] = {first + i};                              // kept-token coordinate of this lane's query
-    uintx4 qf[QB][C::CH];
+    const int qrow = first + i;                              // kept-token coordinate of this lane's query
+    uintx4 qf[C::CH];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int cc = 0; cc < C::CH; ++cc) qf[0][cc] = *reinterpret_cast<const uintx4*>(rows_lds + i * C::KRB + swz_chunk(2 * cc + h, sw));
+    for (int cc = 0; cc < C::CH; ++cc) qf[cc] = *reinterpret_cast<const uintx4*>(rows_lds + i * C::KRB + swz_chunk(2 * cc + h, sw));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     // One pass over the key tiles.  SAFE = false: the exponent offset stays 0 (softmax is shift invariant, and
     // floating point keeps its relative precision at any magnitude), so there is no running maximum, no
@@ -379,14 +371,11 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     // fp32 range, which is checked afterwards.  SAFE = true: the offset follows the running maximum.
     auto pass = [&](auto safe_tag) {
     constexpr bool SAFE = decltype(safe_tag)::value;
-    using Probs = typename PV<T, D, NW, QB, KS>::Probs;
+    using Probs = typename PV<T, D, NW, KS>::Probs;
+    m_run = -INFINITY;
+    l_run = 0.f;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        m_run[qb] = -INFINITY;
-        l_run[qb] = 0.f;
-#pragma unroll
-        for (int db = 0; db < C::ODB; ++db) o[qb][db] = floatx16{0};
-    }
+    for (int db = 0; db < C::ODB; ++db) o[db] = floatx16{0};
     // Software pipeline over key tiles, three stages deep.  Step t runs, on the matrix cores, P.V of tile
     // t-1 (first half) and the S^T product of tile t+1 (second half), and on the vector ALU the
     // exponentials of tile t: the three work on different tiles, so nothing inside a step waits for
@@ -398,10 +387,10 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     load_v(0, 0);
-    floatx16 sa[QB][C::NBK], sb[QB][C::NBK];
+    floatx16 sa[C::NBK], sb[C::NBK];
     Probs pa, pb;
-    qk_block<T, D, NW, QB, KS>(Kb0 + kw * 32 * C::KRB, 0, i, h, sw, qf, sa);       // tile 0 is visible to every row
-    if constexpr (KS == 1) qk_block<T, D, NW, QB, KS>(Kb0, 1, i, h, sw, qf, sa);
+    qk_block<T, D, NW, KS>(Kb0 + kw * 32 * C::KRB, 0, i, h, sw, qf, sa);       // tile 0 is visible to every row
+    if constexpr (KS == 1) qk_block<T, D, NW, KS>(Kb0, 1, i, h, sw, qf, sa);
     __syncthreads();                                         // step 0 overwrites K tile 0
 
     // wait until at most `pending` of this wave's tile requests (NLD loads each) are outstanding, and for its LDS reads
@@ -409,15 +398,15 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         if (pending >= 2) __builtin_amdgcn_s_waitcnt(0x0070 | ((2 * C::NLD) & 15) | (((2 * C::NLD) >> 4) << 14));
         else __builtin_amdgcn_s_waitcnt(0x0070);
     };
-    // bf16, one query block per wave: the two halves of a steady-state step with the instruction order written
+    // The two halves of a steady-state step with the instruction order written
     // out.  Every matrix instruction is followed by its share of the half's vector work (16 pieces: two
     // products, two exponentials, a pack and a row-sum update per pair of keys) and preceded by the LDS reads
     // of the operand kSchedAhead matrix instructions ahead; nothing moves across the fences between them.
     // HALF 0: P.V of the previous tile (src = its V tile), exponentials of key block 0, requests for a K tile.
     // HALF 1: S^T of the next tile (src = its K tile), exponentials of key block 1, requests for a V tile.
-    static_assert(Elem<T>::kBytes == 2 && QB == 1, "the order below is for one query block of bf16");
-    auto steady_half = [&](auto half_tag, const char* src, floatx16 (&sc)[QB][C::NBK], floatx16 (&sn)[QB][C::NBK], Probs& pp, Probs& pc,
-                           float (&sum)[QB], const char* gt, unsigned lt) {
+    static_assert(Elem<T>::kBytes == 2, "the order below is for bf16");
+    auto steady_half = [&](auto half_tag, const char* src, floatx16 (&sc)[C::NBK], floatx16 (&sn)[C::NBK], Probs& pp, Probs& pc,
+                           float& sum, const char* gt, unsigned lt) {
         constexpr int HALF = decltype(half_tag)::value;
         constexpr int NM = (HALF == 0 ? 4 * C::ODB : 2 * C::CH) / KS;  // matrix instructions of the half
         constexpr int PPM = 16 / KS / NM;                           // vector pieces per matrix instruction
@@ -441,8 +430,8 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         auto piece = [&](int q) {                                   // q = 0..15 (KS = 2: 0..7 and 8..15): half a pair of keys
             const int r = 2 * (q >> 1);
             if ((q & 1) == 0) {
-                pe[r] = sc[0][BLK][r] * c;
-                pe[r + 1] = sc[0][BLK][r + 1] * c;
+                pe[r] = sc[BLK][r] * c;
+                pe[r + 1] = sc[BLK][r + 1] * c;
                 pe[r] = fast_exp2(pe[r]);
             } else {
                 pe[r + 1] = fast_exp2(pe[r + 1]);
@@ -455,8 +444,8 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
                         pe[r + 1] = __uint_as_float(pin);
                     }
                 const uint32_t pk = pack_bf16x2(pe[r], pe[r + 1]);
-                pc[0][BLK][r >> 3][(r & 7) >> 1] = pk;
-                sum[0] = add_bf16x2(pk, sum[0]);
+                pc[BLK][r >> 3][(r & 7) >> 1] = pk;
+                sum = add_bf16x2(pk, sum);
             }
         };
 #pragma unroll
@@ -466,17 +455,17 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
             if (j + kSchedAhead < NM) read(j + kSchedAhead);
             if constexpr (HALF == 0) {
                 const int hf = j / (2 * C::ODB), s2 = (j / C::ODB) & 1, db = j % C::ODB;
-                o[0][db] = mma_frag<__bf16>(frag[j], pp[0][hf][s2], o[0][db]);
+                o[db] = mma_frag<__bf16>(frag[j], pp[hf][s2], o[db]);
             } else {
                 const int blk = KS == 1 ? j & 1 : 0, cc = KS == 1 ? j >> 1 : j;
-                sn[0][blk] = mma_frag<__bf16>(frag[j], qf[0][cc], cc == 0 ? floatx16{0} : sn[0][blk]);
+                sn[blk] = mma_frag<__bf16>(frag[j], qf[cc], cc == 0 ? floatx16{0} : sn[blk]);
             }
 #pragma unroll
             for (int q = 0; q < PPM; ++q) piece((KS == 2 ? 8 * HALF : 0) + j * PPM + q);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto step = [&](int t, floatx16 (&sc)[QB][C::NBK], floatx16 (&sn)[QB][C::NBK], Probs& pp, Probs& pc) {
+    auto step = [&](int t, floatx16 (&sc)[C::NBK], floatx16 (&sn)[C::NBK], Probs& pp, Probs& pc) {
         // requests of this step: K tile t+2 into the buffer tile t has left (first half), V tile t+1 into the
         // one tile t-1 leaves at the middle barrier (second half).  In the steady state they are issued one
         // at a time, each tied to one exponential (a burst of them stalls every wave of the workgroup at the
@@ -488,31 +477,25 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         const bool has_pv = t >= 1 && t - 1 < my_tiles, has_s = t < my_tiles, has_next = t + 1 < my_tiles;
         const char* kb = Kb0 + ((t + 1) & 1) * C::TILE_BYTES + kw * 32 * C::KRB;
         const char* vb = Vb0 + ((t + 1) & 1) * C::TILE_BYTES + kw * 32 * C::VRB;      // V tile t-1
-        float mc[QB], sum[QB];
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) { mc[qb] = 0.f; sum[qb] = 0.f; }
+        float mc = 0.f, sum = 0.f;
         if (has_s && t * kBN + (KS == 1 ? kBN : 32 * kw + 32) - 1 > wave_first_row) {       // tile touches the diagonal (wave-uniform)
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
+            for (int blk = 0; blk < C::NBK; ++blk)
 #pragma unroll
-                for (int blk = 0; blk < C::NBK; ++blk)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        if (t * kBN + 32 * (KS == 1 ? blk : kw) + acc_row(r, h) > qrow[qb]) sc[qb][blk][r] = -INFINITY;
+                for (int r = 0; r < 16; ++r)
+                    if (t * kBN + 32 * (KS == 1 ? blk : kw) + acc_row(r, h) > qrow) sc[blk][r] = -INFINITY;
         }
         // Probabilities of this tile, packed once into P^T operand fragments; the row sums are taken over the values as rounded
         // to bf16, so that numerator and denominator of the output use the same weights.
         auto exps = [&](int blk) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    const float p0 = fast_exp2(SAFE ? fmaf(sc[qb][blk][r], c, -mc[qb]) : sc[qb][blk][r] * c);
-                    const float p1 = fast_exp2(SAFE ? fmaf(sc[qb][blk][r + 1], c, -mc[qb]) : sc[qb][blk][r + 1] * c);
-                    const uint32_t pk = pack_bf16x2(p0, p1);
-                    pc[qb][blk][r >> 3][(r & 7) >> 1] = pk;
-                    sum[qb] = add_bf16x2(pk, sum[qb]);
-                }
+            for (int r = 0; r < 16; r += 2) {
+                const float p0 = fast_exp2(SAFE ? fmaf(sc[blk][r], c, -mc) : sc[blk][r] * c);
+                const float p1 = fast_exp2(SAFE ? fmaf(sc[blk][r + 1], c, -mc) : sc[blk][r + 1] * c);
+                const uint32_t pk = pack_bf16x2(p0, p1);
+                pc[blk][r >> 3][(r & 7) >> 1] = pk;
+                sum = add_bf16x2(pk, sum);
+            }
         };
         const bool steady = has_pv && has_next && t < steady_end && !SAFE;
         // ---- first half: P.V of tile t-1 | exponentials of key block 0 of tile t | requests for K tile t+2
@@ -521,8 +504,8 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         } else {
             load_k(kt, t & 1);
             if (has_pv) {
-                PV<T, D, NW, QB, KS>::template run<0>(vb, vlane, pp, o);
-                if constexpr (KS == 1) PV<T, D, NW, QB, KS>::template run<1>(vb, vlane, pp, o);
+                PV<T, D, NW, KS>::template run<0>(vb, vlane, pp, o);
+                if constexpr (KS == 1) PV<T, D, NW, KS>::template run<1>(vb, vlane, pp, o);
             }
             if (has_s) {
                 if constexpr (SAFE) {
@@ -532,32 +515,23 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
                     // (which hold every tile up to t-1 by now) are rescaled rarely.  The first tile always moves
                     // it (offset -inf; key 0 is visible to every row, so the maximum is finite).
                     const float lazy = kLazyLog2 / c;
-                    float m_new[QB];
-                    bool moved = false;
+                    float mx = -INFINITY;
 #pragma unroll
-                    for (int qb = 0; qb < QB; ++qb) {
-                        float mx = -INFINITY;
+                    for (int blk = 0; blk < C::NBK; ++blk)
 #pragma unroll
-                        for (int blk = 0; blk < C::NBK; ++blk)
+                        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[blk][r]);
+                    mx = xhalf_max(mx);
+                    const bool grow = mx > m_run + lazy;
+                    const float m_new = grow ? mx : m_run;
+                    mc = KS == 1 || m_new > -INFINITY ? m_new * c : 0.f;          // KS = 2: a wave's keys may all lie in a row's future
+                    if (__any(grow)) {
+                        const float alpha = KS == 1 || m_run > -INFINITY ? fast_exp2(m_run * c - mc) : 0.f;       // 1 where the maximum stayed
+                        l_run *= alpha;
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sc[qb][blk][r]);
-                        mx = xhalf_max(mx);
-                        const bool grow = mx > m_run[qb] + lazy;
-                        m_new[qb] = grow ? mx : m_run[qb];
-                        mc[qb] = KS == 1 || m_new[qb] > -INFINITY ? m_new[qb] * c : 0.f;      // KS = 2: a wave's keys may all lie in a row's future
-                        moved |= grow;
-                    }
-                    if (__any(moved)) {
+                        for (int db = 0; db < C::ODB; ++db)
 #pragma unroll
-                        for (int qb = 0; qb < QB; ++qb) {
-                            const float alpha = KS == 1 || m_run[qb] > -INFINITY ? fast_exp2(m_run[qb] * c - mc[qb]) : 0.f;   // 1 where the maximum stayed
-                            l_run[qb] *= alpha;
-#pragma unroll
-                            for (int db = 0; db < C::ODB; ++db)
-#pragma unroll
-                                for (int r = 0; r < 16; ++r) o[qb][db][r] *= alpha;
-                            m_run[qb] = m_new[qb];
-                        }
+                            for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+                        m_run = m_new;
                     }
                 }
                 exps(0);
@@ -571,16 +545,13 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         } else {
             load_v(vt, (t + 1) & 1);
             if (has_next) {
-                qk_block<T, D, NW, QB, KS>(kb, 0, i, h, sw, qf, sn);
-                if constexpr (KS == 1) qk_block<T, D, NW, QB, KS>(kb, 1, i, h, sw, qf, sn);
+                qk_block<T, D, NW, KS>(kb, 0, i, h, sw, qf, sn);
+                if constexpr (KS == 1) qk_block<T, D, NW, KS>(kb, 1, i, h, sw, qf, sn);
             }
             if constexpr (KS == 1)
                 if (has_s) exps(1);
         }
-        if (has_s) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) l_run[qb] += sum[qb];
-        }
+        if (has_s) l_run += sum;
         wait_tiles(2);                                        // V tile t has landed (this wave's part)
         __syncthreads();
     };
@@ -608,65 +579,50 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         __syncthreads();
         return meet[((w_all + NW / KS) % NW) * 64 + lane_out];
     };
-    if constexpr (KS == 2)
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) l_run[qb] += partner(l_run[qb]);
+    if constexpr (KS == 2) l_run += partner(l_run);
     {
         // the offset-free pass stands if every row sum of the workgroup is finite and far from both ends of the
         // fp32 range (no exponential overflowed, the dominant terms did not underflow); otherwise the whole
         // workgroup repeats its tiles with running maxima
-        bool bad = false;
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const float l_tot = xhalf_sum(l_run[qb]);
-            bad |= qrow[qb] < kk && !(l_tot >= kSumLow && l_tot <= kSumHigh);   // rows past k are never stored
-        }
-        if (__syncthreads_or(bad)) {
+        const float l_tot = xhalf_sum(l_run);
+        if (__syncthreads_or(qrow < kk && !(l_tot >= kSumLow && l_tot <= kSumHigh))) {      // rows past k are never stored
             pass(std::true_type{});
             if constexpr (KS == 1) __syncthreads();              // the last requests of all waves have landed
-            if constexpr (KS == 2)
+            if constexpr (KS == 2) {                             // to the larger of the two offsets (key 0 is visible to every row: finite)
+                const float m_all = fmaxf(m_run, partner(m_run));
+                const float a = m_run > -INFINITY ? fast_exp2((m_run - m_all) * c) : 0.f;
+                l_run *= a;
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {            // to the larger of the two offsets (key 0 is visible to every row: finite)
-                    const float m_all = fmaxf(m_run[qb], partner(m_run[qb]));
-                    const float a = m_run[qb] > -INFINITY ? fast_exp2((m_run[qb] - m_all) * c) : 0.f;
-                    l_run[qb] *= a;
+                for (int db = 0; db < C::ODB; ++db)
 #pragma unroll
-                    for (int db = 0; db < C::ODB; ++db)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) o[qb][db][r] *= a;
-                    l_run[qb] += partner(l_run[qb]);
-                }
+                    for (int r = 0; r < 16; ++r) o[db][r] *= a;
+                l_run += partner(l_run);
+            }
         }
     }
-    // KS = 2: either wave keeps half of the channel blocks, o[.][0 .. ODB / 2), and hands over the others
+    // KS = 2: either wave keeps half of the channel blocks, o[0 .. ODB / 2), and hands over the others
     constexpr int kOut = C::ODB / KS;
     if constexpr (KS == 2) {
         const int w_all = tid_out >> 6, lane_out = tid_out & 63;
         if (kw) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                for (int db = 0; db < kOut; ++db) {
-                    const floatx16 x = o[qb][db];
-                    o[qb][db] = o[qb][db + kOut];
-                    o[qb][db + kOut] = x;
-                }
+            for (int db = 0; db < kOut; ++db) {
+                const floatx16 x = o[db];
+                o[db] = o[db + kOut];
+                o[db + kOut] = x;
+            }
         }
         __syncthreads();
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
+        for (int db = 0; db < kOut; ++db)
 #pragma unroll
-            for (int db = 0; db < kOut; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) meet[(((w_all * QB + qb) * kOut + db) * 16 + r) * 64 + lane_out] = o[qb][db + kOut][r];
+            for (int r = 0; r < 16; ++r) meet[((w_all * kOut + db) * 16 + r) * 64 + lane_out] = o[db + kOut][r];
         __syncthreads();
         const int w2 = (w_all + NW / KS) % NW;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
+        for (int db = 0; db < kOut; ++db)
 #pragma unroll
-            for (int db = 0; db < kOut; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o[qb][db][r] += meet[(((w2 * QB + qb) * kOut + db) * 16 + r) * 64 + lane_out];
+            for (int r = 0; r < 16; ++r) o[db][r] += meet[((w2 * kOut + db) * 16 + r) * 64 + lane_out];
     }
 
     // Rows leave through LDS (a wave's own part of the V buffers), 16 bytes a lane and whole rows a store: from the accumulators a lane has 8 bytes of
@@ -676,13 +632,13 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     constexpr int kOutBytes = D * Elem<T>::kBytes / KS, kOutLanes = kOutBytes / 16, kOutRows = 64 / kOutLanes;
     char* const mine = Vb0 + (tid_out >> 6) * 32 * kOutBytes;
     auto out_chunk = [](int row, int c) { return row * kOutBytes + ((c ^ (row / (256 / kOutBytes) & (kOutLanes - 1))) << 4); };
-    const float inv = 1.f / xhalf_sum(l_run[0]);
+    const float inv = 1.f / xhalf_sum(l_run);
 #pragma unroll
     for (int db = 0; db < kOut; ++db)
 #pragma unroll
         for (int a = 0; a < 4; ++a)
-            store_out4<T>(reinterpret_cast<T*>(mine + out_chunk(i_out, 4 * db + a) + 8 * h_out), o[0][db][4 * a] * inv, o[0][db][4 * a + 1] * inv,
-                          o[0][db][4 * a + 2] * inv, o[0][db][4 * a + 3] * inv);
+            store_out4<T>(reinterpret_cast<T*>(mine + out_chunk(i_out, 4 * db + a) + 8 * h_out), o[db][4 * a] * inv, o[db][4 * a + 1] * inv,
+                          o[db][4 * a + 2] * inv, o[db][4 * a + 3] * inv);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the rows below are other lanes' stores
     const int w_out = KS == 1 ? tid_out >> 6 : (tid_out >> 6) % (NW / KS), lane_row = (tid_out & 63) / kOutLanes, c_out = tid_out % kOutLanes;
     const char* const held_out = smem + 4 * C::TILE_BYTES + (tid_out >> 6) * 256;
@@ -1114,10 +1070,10 @@ template <typename T> struct FlashArgs {
     uint32_t inv_larger, inv_smaller, inv_g, inv_hkv;        // of (ug + 1) G, ug G, G, Hkv
 };
 
-template <typename T, int D, int NW, int QB, int KS>
-__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::MIN_WGS)) void flash_kept_kernel(FlashArgs<T> args)
+template <typename T, int D, int NW, int KS>
+__global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, KS == 0 ? 2 : KS>::MIN_WGS)) void flash_kept_kernel(FlashArgs<T> args)
 {
-    using C = AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>;
+    using C = AttnCfg<T, D, NW, KS == 0 ? 2 : KS>;
     constexpr int kBM = C::BM;                               // queries per tile
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int block = blockIdx.x;
@@ -1180,7 +1136,7 @@ __global__ __launch_bounds__(64 * NW, (AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>::
         auto queries = [&](auto ks) {
             constexpr int S = decltype(ks)::value;
             if constexpr (Elem<T>::kBytes == 4) flash_queries_f32<D, S>(q, a.qs2, kp, vp, tidx, Oh, i0, kk, a.c, a.out_compact);
-            else flash_queries<T, D, NW, QB, S>(q, a.qs2, kp, vp, tidx, Oh, i0, kk, a.npad, a.c, a.out_compact, a.k_in_place, a.v_in_place);
+            else flash_queries<T, D, NW, S>(q, a.qs2, kp, vp, tidx, Oh, i0, kk, a.npad, a.c, a.out_compact, a.k_in_place, a.v_in_place);
         };
         if constexpr (KS != 0) queries(std::integral_constant<int, KS>{});
         else if (wide) queries(std::integral_constant<int, 1>{});
@@ -1263,14 +1219,14 @@ static int scheduling_groups(int units, int G, int tiles, bool set) {
     return off(equal) <= 1.4143 ? equal : any;
 }
 
-template <typename T, int D, int NW, int QB, int KS>
+template <typename T, int D, int NW, int KS>
 static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const int32_t* idx, const int32_t* k,
                         float scale, int out_compact, int t_per_batch, int skip_k, int skip_v, const void* V, const T* Kp, const T* Vp, int npad, void* O, hipStream_t st)
 {
-    using C = AttnCfg<T, D, NW, QB, KS == 0 ? 2 : KS>;
+    using C = AttnCfg<T, D, NW, KS == 0 ? 2 : KS>;
     static std::atomic<bool> attr_done{false};       // raising the dynamic-LDS cap is idempotent
     if (!attr_done) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kept_kernel<T, D, NW, QB, KS>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kept_kernel<T, D, NW, KS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES) != hipSuccess)
             return set_error(ZIPVL_EHIP, "sparse_prefill: cannot reserve %d bytes of LDS", C::LDS_BYTES);
         attr_done = true;
@@ -1286,7 +1242,7 @@ static int launch_flash(const void* Q, const void* K, const zipvl_dims& d, const
         const int units = d.B * d.Hkv, groups = scheduling_groups<T>(units, G, (d.n + 127) / 128, idx != nullptr);
         const int scan = k && blocks > kScanBlocks && (t_per_batch ? d.B : d.B * d.Hkv) <= kScanSets;
         if (blocks + fill > 0x7fffffffLL) return set_error(ZIPVL_ESHAPE, "sparse_prefill: %lld workgroups exceed the grid limit", (long long)(blocks + fill));
-        hipLaunchKernelGGL((flash_kept_kernel<T, D, NW, QB, KS>), dim3((unsigned)(blocks + fill)), dim3(C::NT),
+        hipLaunchKernelGGL((flash_kept_kernel<T, D, NW, KS>), dim3((unsigned)(blocks + fill)), dim3(C::NT),
             C::LDS_BYTES, st, FlashArgs<T>{(const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
                 skip_k ? (const T*)K : Kp, skip_k ? d.k_strides[0] : (int64_t)d.Hkv * npad * D, skip_k ? d.k_strides[1] : (int64_t)npad * D,
                 skip_v ? (const T*)V : Vp, skip_v ? d.v_strides[0] : (int64_t)d.Hkv * npad * D, skip_v ? d.v_strides[1] : (int64_t)npad * D,
@@ -1336,7 +1292,7 @@ static int launch_prefill_t(const void* Q, const void* K, const void* V, const z
     // faster or equal (2 x 32 heads, n = 960, 512 tiles 12.5 -> 11.4), with all of a set kept up to 17 % slower.
     const int64_t tiles = (int64_t)((d.n + 127) / 128) * d.B * d.Hq, line = d.n >= 1000 ? 384 : 256;
     auto launch = [&](auto waves, auto ks) {
-        return launch_flash<T, D, decltype(waves)::value, 1, decltype(ks)::value>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
+        return launch_flash<T, D, decltype(waves)::value, decltype(ks)::value>(Q, K, d, idx, k, scale, out_compact, t_per_batch, skip_k, skip_v, V, Kp, Vp, npad, O, st);
     };
     constexpr std::integral_constant<int, 0> chosen{};
     constexpr std::integral_constant<int, 1> whole{};
