@@ -335,33 +335,41 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     };
     // Positions, then the first key tiles, then query rows, all straight into LDS: the rows wait for the positions only (a load into
     // registers would wait for the tiles too), and a load asks for whole rows (fragment by fragment, 16 bytes of a row a lane, a wave's
-    // took the address unit 64 clocks a load).  The rows lie where V tiles go from the first step on, in the swizzle of K rows.  A workgroup of
+    // took the address unit 64 clocks a load).  Without a set the rows are asked for first, and taken while the tiles are on their way.  The rows lie where
+    // V tiles go from the first step on, in the swizzle of K rows; KS = 2 leaves room there for the first V tile, asked for as early.  A workgroup of
     // 17 steps had its rows 3.2 us after it asked for tiles, 3.0 so; with the rows of the output (below), calls with their sets and caches,
     // us: 4 x 32 heads, a third kept, n = 4000 120 -> 115, 32, n = 2933 39.7 -> 38.6, 28 on 4, n = 18432, 39 % 358 -> 353, d = 64, 3 x 40, n = 8000, a fifth 109.5 -> 107.
+    // Where the longest tile has few queries there is little to gather, and it ends the call: every token kept, us, fragment by fragment, behind all tiles and before the first
+    // V tile, now: 4 heads, n = 583 12.8, 13.2, 12.9; 8, n = 1300 19.8, 20.1, 19.8; n = 900 16.0, 16.5, 16.2; full ones 4 x 4, n = 300 10.9, 10.6, 10.3, 28 on 4, n = 583 14.8, 14.3, 14.2.
     constexpr int kRowLanes = C::KRB / 16, kRowsAtOnce = 64 / kRowLanes, kQueryLoads = 32 / kRowsAtOnce;
     char* const held = smem + 4 * C::TILE_BYTES + w * 256;
-    char* const rows_lds = Vb0 + w * 32 * C::KRB;
+    char* const rows_lds = KS == 1 ? Vb0 + w * 32 * C::KRB : Vb0 + C::TILE_BYTES + qw * 32 * C::KRB;     // KS = 2: two waves load the same bytes to the same place
     auto request_first_tiles = [&]() {
         load_k(0, 0);
         if (ntiles > 1) load_k(1, 1);
     };
     const int first = i0 + kRW * qw;
+    auto request_rows = [&](auto position) {
+#pragma unroll
+        for (int q = 0; q < kQueryLoads; ++q) {
+            const int r = q * kRowsAtOnce + lane / kRowLanes;
+            load_kib_to_lds_at(reinterpret_cast<const char*>(Q + (int64_t)position(r) * qs2) + swz_chunk(lane % kRowLanes, k_row_swizzle<C::KRB>(r)),
+                               lds_address(rows_lds) + q * 1024);
+        }
+    };
     if (tidx) load_dwords_to_lds(reinterpret_cast<const char*>(tidx), min(first + i, kk - 1) * 4, lds_address(held));
+    else request_rows([&](int r) { return min(first + r, kk - 1); });
     request_first_tiles();
     if (tidx) {
         if (ntiles > 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::NLD) : "memory");
         else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(C::NLD) : "memory");
-    }
-#pragma unroll
-    for (int q = 0; q < kQueryLoads; ++q) {
-        const int r = q * kRowsAtOnce + lane / kRowLanes;
-        const int pos = tidx ? *reinterpret_cast<const int*>(held + 4 * r) : min(first + r, kk - 1);
-        load_kib_to_lds_at(reinterpret_cast<const char*>(Q + (int64_t)pos * qs2) + swz_chunk(lane % kRowLanes, k_row_swizzle<C::KRB>(r)),
-                           lds_address(rows_lds) + q * 1024);
+        request_rows([&](int r) { return *reinterpret_cast<const int*>(held + 4 * r); });
     }
     const int qrow = first + i;                              // kept-token coordinate of this lane's query
     uintx4 qf[C::CH];
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (KS == 2) load_v(0, 0);
+    if (tidx || ntiles == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(KS == 2 ? C::NLD : 0) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(KS == 2 ? 3 * C::NLD : 2 * C::NLD) : "memory");
 #pragma unroll
     for (int cc = 0; cc < C::CH; ++cc) qf[cc] = *reinterpret_cast<const uintx4*>(rows_lds + i * C::KRB + swz_chunk(2 * cc + h, sw));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -384,9 +392,11 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     // start of step t+2: every tile has a whole step to arrive.  Two barriers per step (middle and end),
     // each preceded by a wait that leaves this wave's two most recent tile requests outstanding.
     if constexpr (SAFE) request_first_tiles();                  // the first pass requested them before the query rows
-    __builtin_amdgcn_s_waitcnt(0);
+    if constexpr (SAFE && KS == 2) load_v(0, 0);
+    if constexpr (KS == 2) __builtin_amdgcn_s_waitcnt(0x0070 | C::NLD);
+    else __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    load_v(0, 0);
+    if constexpr (KS == 1) load_v(0, 0);
     floatx16 sa[C::NBK], sb[C::NBK];
     Probs pa, pb;
     qk_block<T, D, NW, KS>(Kb0 + kw * 32 * C::KRB, 0, i, h, sw, qf, sa);       // tile 0 is visible to every row

@@ -683,7 +683,7 @@ def test_attention_schedule(copies, Hq, Hkv, n, d, dtype, shared):
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("copies,n,ks", [(1, 1, (1, 1)), (1, 33, (32, 33)), (1, 300, (31, 130)), (1, 300, (0, 300)), (24, 1090, (65, 1089)), (24, 1090, (1, 700))])
+@pytest.mark.parametrize("copies,n,ks", [(1, 1, (1, 1)), (1, 33, (32, 33)), (1, 65, (64, 65)), (1, 130, (66, 128)), (1, 300, (31, 130)), (1, 300, (0, 300)), (24, 1090, (65, 1089)), (24, 1090, (1, 700))])
 @pytest.mark.parametrize("gain", [1.0, 60.0])
 def test_attention_of_queries_in_any_rows(copies, n, ks, d, gain):
     """Query rows at any distance from each other ([B, n, Hq, 2 d] and half of it), in tiles of 64 and of 128 queries with 1 to 128 of them, kept and all;
