@@ -49,12 +49,16 @@ struct ArCfg {
 // Which (head, block of register-side rows) a workgroup takes.  Workgroups go round-robin over the 8 XCDs; every XCD
 // gets whole heads (or 1 / split of the blocks of one, where the heads do not divide by 8) so that the rows it streams
 // stay in its own L2, the blocks with the most visible pairs of all its parts first: part after part, the heaviest block of the last one, a
-// sixth of the launch, began when the others were done (28 heads on 4, n = 18432 18 % of the CU time idle, now 7).  Where an XCD has so few workgroups that
-// all start at once, every second one of its 32 CUs' rounds is turned, so that a CU gets heavy and light ones (us, fp32, 8 heads,
-// n = 6000 987 -> 800, 2 x 32 on 8, n = 2000, d = 64 328 -> 288; bf16, 4 heads, n = 33000, d = 64 839 -> 775; more workgroups or short chains lose
-// 1 to 3 %: 28 on 4, n = 12000 1034 -> 1043, 4 x 32 on 8, n = 1000 56.6 -> 58.5).  Grid: x = (block of the part, XCD), y = part of the
-// XCD; neither dimension reaches the launch limits (2^32 threads, 65535) for any dims that are accepted.
-constexpr int kArTurned = 160, kArTurnedBlocks = 16;      // workgroups of an XCD (of 32 rows a wave) up to which, blocks of a head from which
+// sixth of the launch, began when the others were done (28 heads on 4, n = 18432 18 % of the CU time idle, now 7).  Where an XCD has few workgroups, 32 rows
+// a wave, every second 32 of them (it has 32 CUs) are turned, so that a CU gets heavy and light ones.  It is meant for those that start together, 96
+// of an XCD in bf16 and 64 in fp32, and pays for half as many more, which follow where light ones end; the lines are measured.  us, in order -> so, by workgroups of an XCD: bf16, d = 128,
+// 40 heads, n = 2500 (100) 88.8 -> 84.0, 32, n = 3500 (112) 123.9 -> 121.4, 32 on 8, n = 3800 (120) 144.8 -> 144.9, past it 32, n = 4096 (128) 158.9 -> 161.4,
+// 40, n = 4090 (160) 188 -> 197; d = 64, 32 on 8, n = 4096 (128) 115 -> 108, 40, n = 4090 (160) 132 -> 128, 36 on 4, n = 4480 (158) as before; fp32, d = 64, 4 heads,
+// n = 33 000 (129) 5140 -> 4282, 40, n = 4090 746 -> 730, d = 128, 8, n = 6000 (47) 992 -> 803, 40, n = 4090 1373 -> 1354.  Short chains lose (4 x 32 on 8, n = 1000 56.6 ->
+// 58.5).  Grid: x = (block of the part, XCD), y = part of the XCD; neither dimension reaches the launch limits (2^32 threads,
+// 65535) for any dims that are accepted.
+template <typename T, int D> constexpr int kArTurned = Elem<T>::kBytes == 2 && D == 128 ? 120 : 160;      // workgroups of an XCD up to which
+constexpr int kArTurnedBlocks = 16;                                                                       // blocks of a head from which
 // Blocks of 128 rows of all heads, and rows of a head, from which a wave takes 64 rows (us, 32 rows -> 64): 8 on 2, n = 33000 (2064 blocks) 2225 -> 2084, 32 on 8,
 // n = 8192 (2048) 563 -> 535, 4 x 40, n = 2800 (3520) 367 -> 361; past the lines 4 x 40, n = 2000 (2560) 204 -> 208, 4 heads, n = 33000,
 // d = 64 (1032) 839 -> 962, 32, n = 2933 (736) 95 -> 112.
@@ -76,7 +80,7 @@ __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 && RG == 1 ? 3 
     // the parts of an XCD take turns, block by block
     const int xcd_blocks = gridDim.x >> 3, total = xcd_blocks * gridDim.y;
     int turn = __builtin_amdgcn_readfirstlane(blockIdx.y * xcd_blocks + (blockIdx.x >> 3));
-    if (RG == 1 && (turn & 32) && total <= kArTurned && nblk >= kArTurnedBlocks) turn = (turn & ~31) + min(total - 1, turn | 31) - turn;
+    if (RG == 1 && (turn & 32) && total <= kArTurned<T, D> && nblk >= kArTurnedBlocks) turn = (turn & ~31) + min(total - 1, turn | 31) - turn;
     const int rank = __builtin_amdgcn_readfirstlane(turn / (int)gridDim.y);                                       // scalar from here on
     const int part = __builtin_amdgcn_readfirstlane((blockIdx.x & 7) * gridDim.y + turn - rank * gridDim.y);      // split parts per head
     const int order = rank * split + part % split;
