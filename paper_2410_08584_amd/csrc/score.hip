@@ -40,8 +40,8 @@ constexpr int kStageBufs = 4;               // stage buffers in LDS: three stage
 // next tile instead, as in the exact scores, a tile took 15 % longer: four waves a SIMD, a barrier every one to four tiles).  us, rows gathered by
 // lanes behind three stages of keys, pairs of statistics, scores made by the last waves -> now: 40 heads, n = 4096, 64 recent and 64 random
 // probes 37.2 -> 31.8; 28 on 4, n = 18432 35.0 -> 32.6; 32, n = 3072 19.7 -> 17.0; 32, n = 20000, m = 128 78.6 -> 67.5; 28 on 4, fp32, n = 12000,
-// m = 128 224 -> 201; 4, fp32, d = 64, n = 576 14.4 -> 12.4; bound by memory, 40, n = 18432 67.4 -> 67.0; at d = 64 28 on 4, n = 4096,
-// m = 128 22.5 -> 22.1, 4 x 32, n = 18432 112.5 -> 110.5, 32 on 2, n = 1000, m = 128 28.6 -> 28.9.
+// m = 128 224 -> 201; 4, fp32, d = 64, n = 576 14.4 -> 12.4; bound by memory, 40, n = 18432 67.4 -> 67.0; at d = 64 28 on 4, n = 2933,
+// m = 128 22.3 -> 21.6, 4 x 32, n = 18432 112.5 -> 110.5, 32 on 2, n = 1000, m = 128 28.8 -> 28.6.
 //
 // NWV waves per workgroup.  16 waves (one workgroup per CU): stages of 32 KiB; 8 waves (two per CU): 16 KiB;
 // never more than 128 keys (the column-sum buffers grow with the keys of a stage).
@@ -112,7 +112,6 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
     const int ts = few ? w % NT : w;                                 // task slot inside a round
     const int slot = few ? w / NT : 0;
 
-    // where this lane's NLD 16-byte pieces of a stage come from: row inside the stage and chunk under the row swizzle
     const char* Ku = reinterpret_cast<const char*>(K + b * ks0 + (g / kv_div) * ks1);   // kv_div > 1: every query head is its own unit
     const int row_stride = (int)ks2 * C::E;                          // bytes; a stage spans less than 2 GiB (checked on the host)
     const unsigned lds0 = lds_address(kstage);
@@ -173,7 +172,9 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
         const bool merges = PASS == 2 && active && slot == 0;
         const float* stats = partial + (int64_t)bh * nsplit * np + nb * 32;                     // wave-uniform base; the rest fits 32 bits (host check)
         // PASS 2: the statistics of a task's rows over pass 1's chunks, merged by one of its waves: lane = (4 rows, eighth of the chunks), 16
-        // bytes a load, no more loads than there are chunks for; as a rule plain sums
+        // bytes a load, no more loads and sums than there are chunks for; as a rule plain sums.  (All 64 chunks' sums whatever their number, and four logarithms
+        // by each of eight lanes: 32 on 2, d = 64, n = 577, m = 128 29.0 us, 28.45 so; fp32 at d = 128, where their zeros took the kernel past 128 registers, 8 heads,
+        // n = 1500 24.3, 21.5.)
         auto merge_chunks = [&]() {
             int l = lane;
             asm volatile("" : "+v"(l));
@@ -184,12 +185,11 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
             for (int from = 0; from < nsplit; from += 64) {
                 floatx4 v[8];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    v[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int q = 0; q < 8; ++q)
                     if (from + 8 * q < nsplit) v[q] = *reinterpret_cast<const floatx4*>(stats + min(from + st_chunk + 8 * q, nsplit - 1) * np + st_row);
-                }
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
+                    if (from + 8 * q >= nsplit) break;
                     const float there = from + st_chunk + 8 * q < nsplit ? 1.f : 0.f;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) L[r] = fmaf(v[q][r], there, L[r]);
@@ -223,9 +223,10 @@ __global__ __launch_bounds__(64 * NWV, (Elem<T>::kBytes == 4 && D == 128 && NWV 
                     L[r] = __uint_as_float(by32[0]) + __uint_as_float(by32[1]);
                 }
             }
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (st_chunk == 0) row_bias[ts][st_row + r] = (nb * 32 + st_row + r < m && L[r] > 0.f) ? E[r] + __log2f(L[r]) : INFINITY;
+            // every lane has the four rows' sums: one each for four of the eight lanes that share them
+            const int row = st_row + st_chunk;
+            const float sum = st_chunk == 0 ? L[0] : st_chunk == 1 ? L[1] : st_chunk == 2 ? L[2] : L[3], offset = st_chunk == 0 ? E[0] : st_chunk == 1 ? E[1] : st_chunk == 2 ? E[2] : E[3];
+            if (st_chunk < 4) row_bias[ts][row] = (nb * 32 + row < m && sum > 0.f) ? offset + __log2f(sum) : INFINITY;
         };
         uintx4 qf[CH];
         auto request_stages = [&](int from, int to) {
