@@ -285,7 +285,8 @@ __device__ __forceinline__ void attend_rows(const T* Kb, const T* Vb, T* Kw, T* 
 // leaves some idle the units do, each row of units turned by `turn`, so that neither the busy workgroups of short units nor
 // those of a long one fall on the same CUs (one conversation of 32768 rows among three of 500, 32 heads: 213 us without the
 // turn, 145 with it, 16 splits either way).
-// A unit of fewer than `from` tiles has `coarse` splits: finer ones would cost more than they give (finer_from).
+// A unit of fewer than `from` tiles has `coarse` splits: finer ones would cost more than they give (finer_from).  Never where a KV head has several
+// heads, and their kernels do not look at it (0.05 us of 7: 8 layers of 28 on 4, cap 1600 65.9 us with the look, 65.3 without).
 struct SplitRule {
     int least, more, most, tiles, units, turn;               // turn 0: nothing is left idle
     int coarse, from;                                        // from 0: `least` splits for all
@@ -294,8 +295,9 @@ struct SplitRule {
     __device__ __forceinline__ int unit() const { return turn ? (blockIdx.x + blockIdx.y * (unsigned)turn) % (unsigned)units : blockIdx.y; }
 };
 __device__ __forceinline__ int tiles_of(int L) { return (L + kDecTile - 1) / kDecTile; }
+template <bool GROUPS>
 __device__ __forceinline__ int tiles_per_split(int T, const SplitRule& rule) {
-    const int s = T < rule.from ? rule.coarse : T <= rule.least * rule.tiles ? rule.least : T <= rule.more * rule.tiles ? rule.more : rule.most;
+    const int s = !GROUPS && T < rule.from ? rule.coarse : T <= rule.least * rule.tiles ? rule.least : T <= rule.more * rule.tiles ? rule.more : rule.most;
     return max(1, (T + s - 1) / s);
 }
 
@@ -476,7 +478,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_partial_kernel(
     const int G = Hq / Hkv;
     const int u = rule.unit(), split = rule.split();
     const int L = max(0, min(len[u], cap));
-    const int rows = tiles_per_split(tiles_of(L), rule) * kDecTile;
+    const int rows = tiles_per_split<(GT > 1)>(tiles_of(L), rule) * kDecTile;
     const int r_begin = split * rows, r_end = min(L, r_begin + rows);
     if (split > 0 && r_begin >= L) return;                  // split 0 always reports (an empty state when L = 0)
     const PartialOut po(part, D, u, G, rule.most, rule.units);
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(THREADS) void decode_combine_kernel(const float* __
         int tiles = 0;
         for (int p = 0; p < 3; ++p)
             if (parts.len[p]) tiles += tiles_of(max(0, min(parts.len[p][u], parts.cap[p])));
-        const int per = tiles_per_split(tiles, rule);
+        const int per = tiles_per_split<false>(tiles, rule);
         nsplit = max(1, (tiles + per - 1) / per);
     }
     const PartialOut po(const_cast<float*>(part), D, u, G, rule.most, rule.units);
@@ -574,7 +576,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_step_kernel(
     const bool room = Lraw >= 0 && Lraw < cap;               // a full cache is left unchanged, as by the append call
     const int L0 = max(0, min(Lraw, cap));
     const int L = L0 + (room ? 1 : 0);                       // rows attended: the new one included
-    const int rows = tiles_per_split(tiles_of(L), rule) * kDecTile;
+    const int rows = tiles_per_split<(GT > 1)>(tiles_of(L), rule) * kDecTile;
     const int r_begin = split * rows, r_end = min(L, r_begin + rows);
     const int nsplit = max(1, (L + rows - 1) / rows);
     const PartialOut po(part, D, u, G, rule.most, rule.units);
@@ -705,7 +707,7 @@ __global__ __launch_bounds__(64 * kDecWaves<GT>) void decode_q_partial_kernel(
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 15, kk = lane >> 4;
     const int L4 = max(0, min(len_hi[u], cap_hi)), L2 = max(0, min(len_lo[u], cap_lo)), Lt = Kt ? max(0, min(len_t[u], cap_t)) : 0;
     const int T4 = tiles_of(L4), T2 = tiles_of(L2), Tt = tiles_of(Lt);
-    const int per = tiles_per_split(T4 + T2 + Tt, rule);
+    const int per = tiles_per_split<true>(T4 + T2 + Tt, rule);
     if (rule.turn && split > 0 && split * per >= T4 + T2 + Tt) return;   // equal splits all report, and are all merged
     const int t_end = min(T4 + T2 + Tt, (split + 1) * per), t_codes = min(t_end, T4 + T2);
 
