@@ -1176,42 +1176,45 @@ static int least_splits(const zipvl_dims& d, int cap) {
 
 // Finer splits, of 128 rows (fp32 of few heads 64), where splits of 256 leave the chip idle.
 //
-// One head: a tile less in a split saves 0.37 us, a workgroup more in the launch costs some 10 ns, idle ones too: all of them arrive at counters that
-// lie in one or two lines.  So a launch has at most kMostMore more, a unit takes the finer splits from the tiles on where that pays
+// One head: a tile less in a split saves 0.37 us, a workgroup more costs some 10 ns, idle ones too, for those whose units share a line of
+// arrival counters, kLineUnits of them.  So a line has at most kMostMore more, a unit takes the finer splits from the tiles on where that pays
 // (finer_from), and they are launched at all where caches from seven tenths of the capacity on take them; up to kFewMore more cost nothing
 // from some 30 rows on.  us a step of 8 layers, splits of 256 rows -> so, cache full, at 60 %, at 12 %: 8 heads, d = 128, cap 2700 98 -> 85, 81 -> 75, 57 -> 57; 32 heads,
 // cap 1300 92 -> 88, 78 -> 77, 56 -> 57; 32 heads, cap 2700 140 -> 130, 92 -> 92, 68 -> 69; 4 heads, cap 5500 98 -> 87, 82 -> 78; fp32, d = 64, 8 heads, cap 1300
 // 85 -> 71, 67 -> 60.  Finer splits at every length, without the line, and the idle workgroups dispatched before busy ones: 8 heads, cap 5500, full, 25 %, 12 %
 // 106 -> 103, 73 -> 85, 65 -> 79; fp32, 64 rows, 8 heads, cap 2700, 25 % 58 -> 77.  Past the lines: 16 heads, cap 5500, fp32 183 -> 187;
 // near them 16 heads, d = 64, cap 2700, full, 60 %, 4 % 101 -> 98, 84 -> 87, 54 -> 58.
+// Limits of a launch whatever its units, of a line, finer at every length, us: 4 x 40 heads, cap 482, 32 % full 75.5, 68.3, 68.3; 4 layers of 4 x 14, fp32, cap 1015, 53 % 51.2, 46.5, 45.5;
+// 4 x 32, fp32, d = 64, cap 561, 38 % 73.6, 68.3, 68.1; 4 x 8, cap 1562, 59 % 84.8, 85.6, 80.7.  Twice kMostMore makes steps 5 to 8 % slower a quarter full (8 heads, cap 5500 64.6 -> 69.2).
 //
 // Groups: bf16 at d = 128 above kFineGroups splits, where all forms of the step merge them in a launch of their own, up to a workgroup a CU.  us, 16 layers,
 // full, 25 % full: 28 on 4, cap 7000 176 -> 171; 14 on 2, cap 7000 175 -> 156; 8 of them over quantised caches, 28 on 4, cap 7000 95 -> 79, 67 -> 70,
 // cap 10 500 99 -> 91, 68 -> 70, 14 on 2, cap 7000 93 -> 77, 66 -> 68, cap 13 000 and more alike.  At kFineGroups, steps of 28 on 4: cap 6100 175 -> 166, 6200 175 -> 168.
 // It is not the line where the gain ends (8 on 2, cap 700 139 -> 117; 28 on 4, cap 4110 176 -> 155; fp32, cap 2300 240 -> 173, but 32 on 8, cap 6200
 // 306 -> 311; d = 64, 32 on 8, cap 2300 138 -> 140): below it the tests of the merge count the states that a step leaves by splits of 256 rows.
-constexpr int kFewMore = 32, kMostMore = 96;                 // workgroups of a launch
+constexpr int kFewMore = 32, kMostMore = 96;                 // workgroups of kLineUnits units
+constexpr int kLineUnits = 32;
 constexpr int kFineGroups = 24;                              // splits of 256 rows
 
 // Tiles of a unit from which it has `fine` splits and not `coarse` ones.
 static int finer_from(const zipvl_dims& d, int coarse, int fine) {
-    const int units = d.B * d.Hkv;
-    return d.Hq > d.Hkv || units * (fine - coarse) <= kFewMore ? 0 : ((units + 4) * coarse * fine + 47) / 48;
+    const int line = std::min(d.B * d.Hkv, kLineUnits);
+    return d.Hq > d.Hkv || line * (fine - coarse) <= kFewMore ? 0 : ((line + 4) * coarse * fine + 47) / 48;
 }
 
 // Partial states that a call makes use of.
 static int useful_splits(const zipvl_dims& d, int cap) {
     const bool groups = d.Hq > d.Hkv, bf16 = d.dtype == ZIPVL_BF16;
-    const int units = d.B * d.Hkv, coarse = least_splits(d, cap);
+    const int units = d.B * d.Hkv, line = std::min(units, kLineUnits), coarse = least_splits(d, cap);
     if (groups) {
         if (!bf16 || d.d == 64 || decode_splits(d, cap) <= kFineGroups) return coarse;
         return std::max(coarse, std::min(decode_splits(d, cap, 128), 256 / units));
     }
     if (!bf16) {
         const int fine = std::min(decode_splits(d, cap, 64), 512 / units);
-        if (units * (fine - coarse) <= kFewMore) return std::max(coarse, fine);
+        if (line * (fine - coarse) <= kFewMore) return std::max(coarse, fine);
     }
-    const int fine = std::min({decode_splits(d, cap, 128), 512 / units, coarse + kMostMore / units});
+    const int fine = std::min({decode_splits(d, cap, 128), 512 / units, coarse + kMostMore / line});
     return fine > coarse && 10 * (int64_t)finer_from(d, coarse, fine) <= 7 * (((int64_t)cap + kDecTile - 1) / kDecTile) ? fine : coarse;
 }
 static size_t state_bytes(const zipvl_dims& d) { return (size_t)d.B * d.Hq * (d.d + 2) * sizeof(float); }       // of a split of every unit
