@@ -68,12 +68,12 @@ template <typename T, int D, int PASS, int RG>
 __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 && RG == 1 ? 3 : 2) void allrows_pass_kernel(
     const T* __restrict__ R, int64_t rs0, int64_t rs1, int64_t rs2,     // register side: Q (pass 1) / K (pass 2)
     const T* __restrict__ S, int64_t ss0, int64_t ss1, int64_t ss2,     // streamed side: K (pass 1) / Q (pass 2)
-    int n, float c, float* __restrict__ lse, float* __restrict__ colsum_out, int Hq, int Hkv, int split)
+    int n, float c, float* __restrict__ lse, float* __restrict__ colsum_out, int Hq, int G, int split,
+    uint32_t inv_parts, uint32_t inv_split, uint32_t inv_hq, uint32_t inv_g)     // of the grid's y, split, Hq, G: places without divisions
 {
     using C = ArCfg<T, D, RG>;
     constexpr int CH = C::CH, RB = C::RB, NLD = C::NLD, STG = C::STG;
     extern __shared__ __attribute__((aligned(16))) char smem[];          // two chunks, then (pass 2) 2 x kArWaves x kArChunk lse values
-    const int G = Hq / Hkv;
     const int tid = threadIdx.x, lane = tid & 63, i = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nblk = (n + C::ROWS - 1) / C::ROWS;
@@ -81,12 +81,12 @@ __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 && RG == 1 ? 3 
     const int xcd_blocks = gridDim.x >> 3, total = xcd_blocks * gridDim.y;
     int turn = __builtin_amdgcn_readfirstlane(blockIdx.y * xcd_blocks + (blockIdx.x >> 3));
     if (RG == 1 && (turn & 32) && total <= kArTurned<T, D> && nblk >= kArTurnedBlocks) turn = (turn & ~31) + min(total - 1, turn | 31) - turn;
-    const int rank = __builtin_amdgcn_readfirstlane(turn / (int)gridDim.y);                                       // scalar from here on
+    const int rank = __builtin_amdgcn_readfirstlane(divided(turn, gridDim.y, inv_parts));                                       // scalar from here on
     const int part = __builtin_amdgcn_readfirstlane((blockIdx.x & 7) * gridDim.y + turn - rank * gridDim.y);      // split parts per head
-    const int order = rank * split + part % split;
+    const int bh = __builtin_amdgcn_readfirstlane(divided(part, split, inv_split)), order = rank * split + part - bh * split;
     if (order >= nblk) return;
-    const int bh = __builtin_amdgcn_readfirstlane(part / split), b = __builtin_amdgcn_readfirstlane(bh / Hq), head = bh - b * Hq;
-    const int g = __builtin_amdgcn_readfirstlane(head / G);
+    const int b = __builtin_amdgcn_readfirstlane(divided(bh, Hq, inv_hq)), head = bh - b * Hq;
+    const int g = __builtin_amdgcn_readfirstlane(divided(head, G, inv_g));
     // heavy blocks first: late queries in pass 1, early keys in pass 2
     const int row0 = (PASS == 1 ? nblk - 1 - order : order) * C::ROWS, wrow0 = row0 + 32 * RG * w;
 
@@ -113,7 +113,8 @@ __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 && RG == 1 ? 3 
         ld_off[q] = (narrow ? (unsigned)(r * row_bytes) : 0u) + ((p ^ k_row_swizzle<RB>(q * kLoadRows + r)) << 4);
     }
     // Every wave issues the same number of loads for every chunk; rows past the end re-read the chunk's first one.  That form, and
-    // the one for wide rows, derive what they need from the thread index.
+    // the one for wide rows, derive what they need from the thread index (one load after the other, and with divisions for the workgroup's place: 8 heads on 2,
+    // n = 300 19.1 us, 18.8 so, n = 130 16.0, 15.7; 15.0 when a call had no order written out and a third of the code).
     auto issue = [&](int t) {
         const int c0 = chunk_row(t), buf = (t & 1);
         const char* base = scalar_ptr(Sb + c0 * row_bytes);
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(64 * kArWaves, Elem<T>::kBytes == 2 && RG == 1 ? 3 
         } else {
             int l = lane;
             asm volatile("" : "+v"(l));
-#pragma unroll 1
+#pragma unroll
             for (int q = 0; q < NLD; ++q) {
                 const int r = (q * kArWaves + w) * kRowsPerLoad + l * 16 / RB, p = (l * 16 % RB) >> 4;
                 load_kib_to_lds_at(base + (c0 + r < n ? r * row_bytes + ((p ^ k_row_swizzle<RB>(r)) << 4) : 0), dst + q * kArWaves * 1024);
@@ -390,6 +391,7 @@ static int launch_allrows_t(const void* Q, const void* K, const zipvl_dims& d, f
     const int nblk = (d.n + C::ROWS - 1) / C::ROWS, heads = d.B * d.Hq;
     const int split = 8 / std::gcd(heads, 8);
     const dim3 grid(8 * ((nblk + split - 1) / split), heads * split / 8);
+    const int G = d.Hq / d.Hkv;
     float* lse = (float*)ws;
     float* colsum = lse + (size_t)heads * d.n;
     {
@@ -397,7 +399,7 @@ static int launch_allrows_t(const void* Q, const void* K, const zipvl_dims& d, f
         hipLaunchKernelGGL((allrows_pass_kernel<T, D, 1, RG>), grid, dim3(64 * kArWaves), C::LDS, st,
             (const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
             (const T*)K, d.k_strides[0], d.k_strides[1], d.k_strides[2],
-            d.n, c, lse, (float*)nullptr, d.Hq, d.Hkv, split);
+            d.n, c, lse, (float*)nullptr, d.Hq, G, split, inverse(grid.y), inverse(split), inverse(d.Hq), inverse(G));
     }
     int rc = check_launch("allrows_lse");
     if (rc) return rc;
@@ -405,7 +407,7 @@ static int launch_allrows_t(const void* Q, const void* K, const zipvl_dims& d, f
     hipLaunchKernelGGL((allrows_pass_kernel<T, D, 2, RG>), grid, dim3(64 * kArWaves), C::LDS, st,
         (const T*)K, d.k_strides[0], d.k_strides[1], d.k_strides[2],
         (const T*)Q, d.q_strides[0], d.q_strides[1], d.q_strides[2],
-        d.n, c, lse, colsum, d.Hq, d.Hkv, split);
+        d.n, c, lse, colsum, d.Hq, G, split, inverse(grid.y), inverse(split), inverse(d.Hq), inverse(G));
     rc = check_launch("allrows_colsum");
     if (rc) return rc;
     hipLaunchKernelGGL(allrows_finish_kernel, dim3((d.n + 255) / 256, d.B * d.Hkv), dim3(256), 0, st,

@@ -1057,15 +1057,6 @@ __device__ __forceinline__ void clear_dropped(T* __restrict__ O, const int32_t* 
         if (!kept[q / CPR]) __builtin_nontemporal_store(z, reinterpret_cast<uintx4*>(base + (int64_t)q * 16));
 }
 
-// n / d of whole numbers below 2^31, inv = inverse(d) from the host: the high half of the product is the quotient or one less.  The compiler's own division by
-// a number it does not know is some 20 dependent vector instructions, and a workgroup needs five of them to know its place: 0.8 us, 0.3 so.  Attention with
-// its set and cache, us: d = 64, 3 x 40 heads, n = 8000, a fifth kept 107.0 -> 104.1, 4 x 32, n = 4000, a third 115.2 -> 113.5, long tiles as before.
-static uint32_t inverse(int d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)d); }
-__device__ __forceinline__ int divided(int n, int d, uint32_t inv) {
-    const uint32_t q = (uint32_t)((uint64_t)(uint32_t)n * inv >> 32);
-    return (int)(q + ((uint32_t)n - q * d >= (uint32_t)d));
-}
-
 // kp, vp: of batch element, KV head.  slots: rows of attention workgroups in the grid, BH each; fill: workgroups after them that clear
 // rows; scan: whether the kept counts are read for the longest head; ug: KV heads of a scheduling group, one more in the first `extra` ones.
 template <typename T> struct FlashArgs {
