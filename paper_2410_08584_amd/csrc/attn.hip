@@ -335,7 +335,8 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     };
     // Positions, then the first key tiles, then query rows, all straight into LDS: the rows wait for the positions only (a load into
     // registers would wait for the tiles too), and a load asks for whole rows (fragment by fragment, 16 bytes of a row a lane, a wave's
-    // took the address unit 64 clocks a load).  Without a set the rows are asked for first, and taken while the tiles are on their way.  The rows lie where
+    // took the address unit 64 clocks a load).  KS = 2 without a set asks for the rows first, and takes them while the tiles are on their way
+    // (KS = 1 so: 3 x 40 heads, n = 390 16.6 -> 17.3).  The rows lie where
     // V tiles go from the first step on, in the swizzle of K rows; KS = 2 leaves room there for the first V tile, asked for as early.  A workgroup of
     // 17 steps had its rows 3.2 us after it asked for tiles, 3.0 so; with the rows of the output (below), calls with their sets and caches,
     // us: 4 x 32 heads, a third kept, n = 4000 120 -> 115, 32, n = 2933 39.7 -> 38.6, 28 on 4, n = 18432, 39 % 358 -> 353, d = 64, 3 x 40, n = 8000, a fifth 109.5 -> 107.
@@ -358,8 +359,9 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
         }
     };
     if (tidx) load_dwords_to_lds(reinterpret_cast<const char*>(tidx), min(first + i, kk - 1) * 4, lds_address(held));
-    else request_rows([&](int r) { return min(first + r, kk - 1); });
+    else if (KS == 2) request_rows([&](int r) { return min(first + r, kk - 1); });
     request_first_tiles();
+    if (!tidx && KS == 1) request_rows([&](int r) { return min(first + r, kk - 1); });
     if (tidx) {
         if (ntiles > 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::NLD) : "memory");
         else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(C::NLD) : "memory");
@@ -368,8 +370,8 @@ __device__ __forceinline__ void flash_queries(const T* __restrict__ Q, int64_t q
     const int qrow = first + i;                              // kept-token coordinate of this lane's query
     uintx4 qf[C::CH];
     if constexpr (KS == 2) load_v(0, 0);
-    if (tidx || ntiles == 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(KS == 2 ? C::NLD : 0) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(KS == 2 ? 3 * C::NLD : 2 * C::NLD) : "memory");
+    if (KS == 2 && !tidx && ntiles > 1) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * C::NLD) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" :: "n"(KS == 2 ? C::NLD : 0) : "memory");
 #pragma unroll
     for (int cc = 0; cc < C::CH; ++cc) qf[cc] = *reinterpret_cast<const uintx4*>(rows_lds + i * C::KRB + swz_chunk(2 * cc + h, sw));
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
