@@ -1178,7 +1178,8 @@ static int least_splits(const zipvl_dims& d, int cap) {
 //
 // One head: a tile less in a split saves 0.37 us, a workgroup more costs some 10 ns, idle ones too, for those whose units share a line of
 // arrival counters, kLineUnits of them.  So a line has at most kMostMore more, a unit takes the finer splits from the tiles on where that pays
-// (finer_from), and they are launched at all where caches from seven tenths of the capacity on take them; up to kFewMore more cost nothing
+// (finer_from), and they are launched at all where caches from seven tenths of the capacity on take them (from 85 % where they put two workgroups on
+// every CU: full caches, seven tenths -> so, 32 heads, cap 3461 137.8 -> 132.1, 2 x 32, cap 1700 134.3 -> 127.2, and as before at 25 and 60 %); up to kFewMore more cost nothing
 // from some 30 rows on.  us a step of 8 layers, splits of 256 rows -> so, cache full, at 60 %, at 12 %: 8 heads, d = 128, cap 2700 98 -> 85, 81 -> 75, 57 -> 57; 32 heads,
 // cap 1300 92 -> 88, 78 -> 77, 56 -> 57; 32 heads, cap 2700 140 -> 130, 92 -> 92, 68 -> 69; 4 heads, cap 5500 98 -> 87, 82 -> 78; fp32, d = 64, 8 heads, cap 1300
 // 85 -> 71, 67 -> 60.  Finer splits at every length, without the line, and the idle workgroups dispatched before busy ones: 8 heads, cap 5500, full, 25 %, 12 %
@@ -1215,7 +1216,8 @@ static int useful_splits(const zipvl_dims& d, int cap) {
         if (line * (fine - coarse) <= kFewMore) return std::max(coarse, fine);
     }
     const int fine = std::min({decode_splits(d, cap, 128), 512 / units, coarse + kMostMore / line});
-    return fine > coarse && 10 * (int64_t)finer_from(d, coarse, fine) <= 7 * (((int64_t)cap + kDecTile - 1) / kDecTile) ? fine : coarse;
+    const bool even = fine == 512 / units && units * fine > 480;                // two workgroups on every CU
+    return fine > coarse && 20 * (int64_t)finer_from(d, coarse, fine) <= (even ? 17 : 14) * (((int64_t)cap + kDecTile - 1) / kDecTile) ? fine : coarse;
 }
 static size_t state_bytes(const zipvl_dims& d) { return (size_t)d.B * d.Hq * (d.d + 2) * sizeof(float); }       // of a split of every unit
 
